@@ -12,7 +12,8 @@ Three kinds, all through the public entry points:
 
 ``listed()`` gives fixed cases, ``draw(rng)`` more of the same ranges, ``prepare(case, seed)`` what a
 program has in hand before the call, ``run(state)`` one pass, ``work(case)`` the bytes and operations the
-pass cannot do without and ``tolerance(case)`` how far another correct implementation may be off.
+pass cannot do without, ``tolerance(case)`` how far another correct implementation may be off and
+``exact(case, seed)`` the result in 64 bits.
 
 Channel counts after pruning belong to the case (``keep_seed``); the values of weights, batch-norm
 vectors and inputs, and with them which filters survive, come from the seed.
@@ -236,3 +237,85 @@ def tolerance(case):
     if case["kind"] == "conv":
         return {"rel": CONV_REL[case["dtype"]]}
     return {"rel": (MOBILE_REL if case["net"] in ("mobilenetv2", "mnasnet") else NET_REL)[case["dtype"]]}
+
+
+# ---- the same in 64 bits --------------------------------------------------------------------------
+
+def _act64(y, act):
+    return y if act == 0 else y.clamp(min=0) if act == 1 else y.clamp(0, 6)
+
+
+def _conv64(x, w, bias, stride, pad, groups):
+    """Cross-correlation in double; a depthwise layer as the sum of its shifted taps."""
+    if groups == 1:
+        return torch.nn.functional.conv2d(x, w, bias, stride, pad)
+    k, h, wd = w.shape[2], x.shape[2], x.shape[3]
+    ho, wo = (h + 2 * pad - k) // stride + 1, (wd + 2 * pad - k) // stride + 1
+    xp = torch.nn.functional.pad(x, (pad, pad, pad, pad))
+    y = bias.view(1, -1, 1, 1).expand(x.shape[0], -1, ho, wo).clone()
+    for u in range(k):
+        for v in range(k):
+            y += w[:, 0, u, v].view(1, -1, 1, 1) * xp[:, :, u:u + stride * (ho - 1) + 1:stride,
+                                                      v:v + stride * (wo - 1) + 1:stride]
+    return y
+
+
+def _prune64(net, params):
+    """Kept lists, and every layer's gathered and folded weights and bias, in double."""
+    kept = {}
+    for i, L in enumerate(net.layers):
+        if L.prune_out == "own":
+            score = sum(params[j]["w"].abs().flatten(1).sum(1) for j in [i] + list(L.score_with or []))
+            first = torch.sort(score, descending=True, stable=True).indices[:params[i]["keep"]]
+            kept[i] = first.sort().values
+    layers = []
+    for i, (L, p) in enumerate(zip(net.layers, params)):
+        if L.kind not in ("conv", "fc"):
+            layers.append(None)
+            continue
+        w = p["w"] if L.kind == "conv" else p["w"][:, :, None, None]
+        rows = i if L.prune_out == "own" else L.prune_out if isinstance(L.prune_out, int) else None
+        if L.prune_in is not None and L.groups == 1:
+            w = w[:, kept[L.prune_in]]
+        take = kept[rows] if rows is not None else torch.arange(w.shape[0])
+        w, b = w[take], p.get("b")
+        if L.kind == "conv" and L.bn:
+            s = (p["gamma"] / torch.sqrt(p["var"] + pipeline.BN_EPS))[take]
+            w, b = w * s.view(-1, 1, 1, 1), p["beta"][take] - p["mean"][take] * s
+        layers.append((w, b))
+    return kept, layers
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, in double precision on the CPU, from the same inputs as prepare()."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    tdt = B.TORCH_DTYPE[DTYPES[case["dtype"]]]
+    F = torch.nn.functional
+    if case["kind"] == "conv":
+        state = prepare(dict(case, tuned=False), seed)
+        x, w, b, res = (None if state[t] is None else state[t].double().cpu() for t in ("x", "w", "bias", "res"))
+        y = _conv64(x, w, b, case["stride"], case["k"] // 2, 1)
+        return _act64(y if res is None else y + res, case["act"])
+    net = _spec(case)
+    dev = _device_params(net, _kept_counts(net, case["keep_seed"]), gen)
+    params = [{k: v.double().cpu() if torch.is_tensor(v) else v for k, v in p.items()} for p in dev]
+    kept, layers = _prune64(net, params)
+    if case["kind"] == "prune":
+        return [{i: k.to(torch.int32) for i, k in kept.items()},
+                {i: q[0] for i, q in enumerate(layers) if q},
+                {i: q[1] for i, q in enumerate(layers) if q and net.layers[i].kind == "conv"}]
+    x = torch.randn((case["batch"], net.in_c, net.in_h, net.in_w), device="cuda", generator=gen).to(tdt)
+    acts = []
+    for L, q in zip(net.layers, layers):
+        src = x.double().cpu() if L.input < 0 else acts[L.input]
+        if L.kind == "conv":
+            y = _conv64(src, q[0], q[1], L.stride, L.pad, 1 if L.groups == 1 else src.shape[1])
+            y = _act64(y if L.residual is None else y + acts[L.residual], L.act)
+        elif L.kind == "maxpool":
+            y = F.max_pool2d(src, L.k, L.stride, L.pad)
+        elif L.kind == "gavgpool":
+            y = src.mean((2, 3), keepdim=True)
+        else:
+            y = _act64(F.linear(src.flatten(1), q[0].flatten(1), q[1]), L.act)
+        acts.append(y)
+    return acts[-1]
