@@ -82,17 +82,17 @@ int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay) {
   return best_v;
 }
 
+// The variant timed for exactly this shape and layout, or -1.
+static int timed_variant(const cprune_conv_desc& d, const ConvLayout& lay) {
+  std::lock_guard<std::mutex> lock(g_cache_mutex);
+  auto it = g_cache.find(key_of(d, lay));
+  return it != g_cache.end() ? it->second : -1;
+}
+
 int cached_or_heuristic_variant(const cprune_conv_desc& d, bool* timed, const ConvLayout& lay) {
-  {
-    std::lock_guard<std::mutex> lock(g_cache_mutex);
-    auto it = g_cache.find(key_of(d, lay));
-    if (it != g_cache.end()) {
-      if (timed) *timed = true;
-      return it->second;
-    }
-  }
-  if (timed) *timed = false;
-  return heuristic_variant(d, lay);
+  const int v = timed_variant(d, lay);
+  if (timed) *timed = v >= 0;
+  return v >= 0 ? v : heuristic_variant(d, lay);
 }
 
 static int conv_dispatch(const cprune_conv_desc& d, const void* x, const void* w, const float* bias,
@@ -602,6 +602,20 @@ static int net_run_mbconv(cprune_net* net, int i, int n, void* dst, hipStream_t 
   return CPRUNE_OK;
 }
 
+// The variant a layer runs at a batch of n: the one timed for that very shape if there is one, else the one chosen for
+// the handle's full batch wherever it runs the smaller shape too (with fewer images a layer keeps its reduction and
+// its filters, which the choice depends on most), and the untimed estimate only where it does not.  VGG-16 in fp16,
+// 37 images through a handle for 64: 222 us with the estimate, 99 us with the full batch's variants.
+static int layer_variant_at(const cprune_net* net, const NetLayer& L, const cprune_conv_desc& d, const ConvLayout& lay,
+                            int n) {
+  if (n == net->max_batch) return L.variant;
+  const int timed = timed_variant(d, lay);
+  if (timed >= 0) return timed;
+  if (L.variant >= 0 && variant_supports(d, L.variant, lay) && conv_ws_bytes(d, L.variant, lay) <= net->ws_bytes)
+    return L.variant;
+  return heuristic_variant(d, lay);
+}
+
 static int net_run_layer(cprune_net* net, int i, int n, const void* x, void* out_override, hipStream_t s) {
   NetLayer& L = net->layers[i];
   const void* src = L.d.input < 0 ? (L.nchw_in ? x : net->x_cl) : net->layers[L.d.input].act;
@@ -619,7 +633,7 @@ static int net_run_layer(cprune_net* net, int i, int n, const void* x, void* out
       const ConvLayout lay = layer_layout(L);
       const void* res = L.d.residual >= 0 ? net->layers[L.d.residual].act : nullptr;
       int v = -1;
-      if (d.groups == 1) v = (n == net->max_batch) ? L.variant : cached_or_heuristic_variant(d, nullptr, lay);
+      if (d.groups == 1) v = layer_variant_at(net, L, d, lay, n);
       return conv_dispatch(d, src, L.w, L.b, res, dst, v, net->ws, net->ws_bytes, s, lay);
     }
     case CPRUNE_LAYER_MAXPOOL:
