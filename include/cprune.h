@@ -190,6 +190,9 @@ typedef struct {
  * caller's scratch and are summed in run order (deterministic).  sched -1: kernels that
  * exist only for the channels-last layout inside a network handle (3x3 stride-1 layers,
  * one tile_p-pixel spatial block per work-group); unsupported through this NCHW call.
+ * (also sched -1: the split kernel, any window at stride 1 or 2, fp32 data as three 16-bit parts on the 16-bit
+ * matrix cores at no larger an error.  Inside a handle its weights are packed at creation; through
+ * cprune_conv2d_bn_relu each call packs them into the caller's scratch.)
  * sched -2: likewise channels-last only, for layers whose reduction is one contiguous run
  * per pixel (1x1 stride 1, fully connected): 16 filters x tile_p pixels per work-group, the
  * wavefronts of the group splitting the reduction; chosen when pixels are few.

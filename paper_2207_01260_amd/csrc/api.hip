@@ -55,13 +55,26 @@ void remember_variant(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
   g_cache[key_of(d, lay)] = v;
 }
 
+// Whether the split kernel is worth considering: inside a handle always; in the boundary's layout from 0.6 GFLOP up,
+// because there the weights are packed on every call, by a launch of its own (4-8 us: 128 -> 83 filters at 56x56,
+// batch 8, 74 -> 44 us in fp32 and 38 -> 22 us in bf16; 64 -> 45 at 32x32, batch 1, 10.5 -> 11.8 us).
+static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay) {
+  const long ho = conv_out_dim(d.h, d.kh, d.stride, d.pad), wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
+  return lay.nhwc || 2.0 * (double)d.n * ho * wo * d.c_out * d.c_in * d.kh * d.kw >= 6e8;
+}
+
 // Untimed fallback: the tile whose wavefronts reuse their LDS operands most (blocks
 // per operand fetched), discounted by the pixel columns a ragged last tile wastes;
 // work cut into equal runs for 512 resident work-groups, which needs no knowledge
 // of how the tile count divides the chip.  Used only for shapes never timed.
-int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay) {
+// Windows of more than one tap go to the split kernel where it pays; its own estimate says which variant.
+int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay, bool split) {
   const long ho = conv_out_dim(d.h, d.kh, d.stride, d.pad), wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
   const long P = (long)d.n * ho * wo, O = d.c_out;
+  if (split && d.groups == 1 && d.kh * d.kw > 1 && split_pays(d, lay)) {
+    const int v = best_split_variant(d, lay);
+    if (v >= 0) return v;
+  }
   double best = -1.0;
   int best_v = 0;
   for (int v = 0; v < num_variants(); ++v) {
@@ -101,7 +114,11 @@ static int conv_dispatch(const cprune_conv_desc& d, const void* x, const void* w
   if (d.groups != 1)
     return lay.nhwc ? launch_depthwise_nhwc(d, lay.cp_in, x, w, bias, residual, y, s)
                     : launch_conv_depthwise(d, x, w, bias, residual, y, s);
-  if (v < 0) v = cached_or_heuristic_variant(d, nullptr, lay);
+  if (v < 0) {
+    v = cached_or_heuristic_variant(d, nullptr, lay);
+    // the split kernel packs its weights into the caller's scratch: a caller without room gets a kernel that packs none
+    if (variant(v).split && conv_ws_bytes(d, v, lay) > (ws ? ws_bytes : 0)) v = heuristic_variant(d, lay, false);
+  }
   if (!variant_supports(d, v, lay)) return CPRUNE_ERR_UNSUPPORTED;
   const size_t need = conv_ws_bytes(d, v, lay);
   if (need > 0 && (!ws || ws_bytes < need)) return CPRUNE_ERR_WORKSPACE;
@@ -147,6 +164,7 @@ static int select_tile_impl(const cprune_conv_desc& d, const void* x, const void
     if (d.groups == 1) {
       if (!variant_supports(d, v, lay)) continue;
       ++supported;
+      if (variant(v).split && !split_pays(d, lay)) continue;
       if (conv_ws_bytes(d, v, lay) > ws_bytes) continue;  // not timed: the caller's scratch cannot run it
     }
     for (int i = 0; i < warmup && rc == CPRUNE_OK; ++i) rc = conv_dispatch(d, x, w, bias, residual, y, v, ws, ws_bytes, s, lay);
@@ -217,6 +235,9 @@ extern "C" int cprune_tile_variant_name(int v, int channels_last, cprune_dtype d
   if (tv.sched >= 0)
     n = snprintf(buf, buf_bytes, "%s<%s, %d, %d, %d, %d, %d>", channels_last ? "conv_nhwc_kernel" : "conv_igemm_kernel", t,
                  tv.wm, tv.wn, tv.mb, tv.nb, tv.kq);
+  else if (tv.split)
+    n = snprintf(buf, buf_bytes, "conv_split_kernel<%s, %s, %d, %d, %d, %d, %d, %d>", t, channels_last ? "false" : "true", tv.wm,
+                 tv.wn, tv.ks, tv.mb, tv.nb, tv.nib);
   else if (tv.sched == -4)
     n = snprintf(buf, buf_bytes, "conv_wave_kernel<%s, %d, %d, %d>", t, tv.wn, tv.nb, tv.ks);
   else if (tv.sched == -3)
@@ -361,6 +382,7 @@ struct NetLayer {
   void* w_rows = nullptr;     // layer the reduction-split kernel can run: weights once more, in its operand order
   void* w_wave = nullptr;     // 3x3 / stride 1 / pad 1 layer on a small map: weights once more, packed for the
                               // independent-wavefront kernel
+  void* w_split = nullptr;    // fp32 dense layer: weights once more, cut and packed for the split kernel
   bool stem = false;          // nchw_in layer that runs the first-layer kernel (whole reduction in LDS)
   void* w_stem7 = nullptr;    // 16-bit 7x7 / stride 2 / pad 3 first layer: weights packed for the kernel made for it
   int stem7 = 0;              // 1: that kernel runs the layer; 2: and the 3x3 / stride 2 max-pool pool3 with it
@@ -420,6 +442,7 @@ static ConvLayout layer_layout(const NetLayer& L) {
   lay.nhwc = 1; lay.cp_in = L.cp_in; lay.cp_out = L.cp_out; lay.pool = L.fused_pool ? 1 : 0;
   lay.w_wave = L.w_wave;
   lay.w_rows = L.w_rows;
+  lay.w_split = L.w_split;
   if (L.nchw_in) { lay.nhwc = 0; lay.nhwc_out = 1; lay.cp_in = 0; return lay; }
   if (L.map2x2) {
     lay.cp_in = 4 * L.cp_in;
@@ -896,6 +919,19 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     if (rows_packed_bytes(cd.c_out, k, dtype) >= ((size_t)1 << 31)) continue;   // the kernel then reads the row layout
     rc = dev_alloc(rows_packed_bytes(cd.c_out, k, dtype), &L.w_rows);
     if (rc == CPRUNE_OK) rc = launch_repack_rows(L.w, cd.c_out, k, dtype, L.w_rows, s);
+  }
+  // fp32 layers: a copy cut into 16-bit parts for the split kernel, where one of its variants can run the layer
+  for (int i = 0; i < n_layers && rc == CPRUNE_OK && dtype == CPRUNE_F32; ++i) {
+    NetLayer& L = net->layers[i];
+    if (!(L.d.kind == CPRUNE_LAYER_FC || (L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1)) || L.nchw_in) continue;
+    const cprune_conv_desc cd = layer_conv_desc(*net, L, max_batch);
+    ConvLayout lay = layer_layout(L);
+    lay.w_split = L.w;     // (only whether it is set matters here)
+    bool any = false;
+    for (int v = 0; v < num_variants() && !any; ++v) any = variant(v).split && variant_supports(cd, v, lay);
+    if (!any) continue;
+    rc = dev_alloc(split_packed_bytes(cd.c_out, lay.cp_in, cd.kh * cd.kw, dtype), &L.w_split);
+    if (rc == CPRUNE_OK) rc = launch_pack_split(L.w, cd.c_out, lay.cp_in, cd.kh * cd.kw, 1, dtype, L.w_split, s);
   }
   // variant per dense layer
   for (int i = 0; i < n_layers && rc == CPRUNE_OK; ++i) {

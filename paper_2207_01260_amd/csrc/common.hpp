@@ -43,8 +43,10 @@ struct TileVariant {
                 //      the reduction per work-group; wn * ks wavefronts of nb blocks each)
   int th = 0, tw = 0, ni = 1, patch_id = -1;
   int blk32 = 0;  // patch kernels: 1 = 32x32 MFMA blocks (patch_id then indexes that kernel's list)
-  int ks = 1;     // patch kernels on 16x16 blocks: wave groups per tile
+  int ks = 1;     // patch kernels on 16x16 blocks: wave groups per tile; split kernel: wavefronts that share a block
   int kwaves = 0; // reduction-split kernel: wavefronts that share one tile's reduction (patch_id indexes its list)
+  int split = 0;  // 1 (with sched = -1): split kernel, any window and stride, fp32 as three bf16 parts
+  int nib = 0;    // split kernel: staging items per thread (patch_id indexes its list)
   int nr = 0;     // short-reduction 1x1 kernel: 64-byte rounds of the reduction its filter tile holds
   int stride = 1; // spatial-patch kernel on 16x16 blocks: the window stride it is built for (patch_id then indexes the
                   // stride-2 list)
@@ -68,6 +70,9 @@ struct ConvLayout {
                                  // kernel (launch_repack_wave); that kernel runs only where this is set
   const void* w_rows = nullptr;  // the weights once more as [16-row tile][64-byte round of the reduction][lane][16
                                  // bytes] (launch_repack_rows): the reduction-split kernel reads these when set
+  const void* w_split = nullptr; // channels-last fp32: the weights cut and packed for the split kernel
+                                 // (launch_pack_split), which runs only where this is set; a call in the boundary's
+                                 // layout packs its weights into the caller's scratch
   int pool = 0;  // 1: channels-last 3x3 layer with a 2x2/2 max-pool fused behind the activation (patch kernels);
                  // 2: rows are (channel, position of a 2x2 map) and each group of four rows is reduced to its
                  //    maximum behind the activation; cp_out is the stride of the pooled output
@@ -77,7 +82,9 @@ inline int round_up_vec(int c, int dt) { const int v = dt == CPRUNE_F32 ? 4 : 8;
 int validate_conv_desc(const cprune_conv_desc* d);
 bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay = ConvLayout());
 size_t conv_ws_bytes(const cprune_conv_desc& d, int v, const ConvLayout& lay = ConvLayout());
-int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay = ConvLayout());
+// split: whether a variant that needs packed weights in scratch may be chosen
+int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay = ConvLayout(), bool split = true);
+int best_split_variant(const cprune_conv_desc& d, const ConvLayout& lay);   // by estimate; -1 if none runs the layer
 int cached_or_heuristic_variant(const cprune_conv_desc& d, bool* timed, const ConvLayout& lay = ConvLayout());
 void remember_variant(const cprune_conv_desc& d, int v, const ConvLayout& lay = ConvLayout());
 
@@ -111,6 +118,13 @@ int launch_repack_wave(const void* w_khwc, int o, int cp, int dt, void* y, hipSt
 // w [rows][k], k contiguous -> the operand order of the reduction-split kernel, zero padded; rows_packed_bytes: size
 size_t rows_packed_bytes(int rows, int k, int dt);
 int launch_repack_rows(const void* w, int rows, int k, int dt, void* y, hipStream_t s);
+// weights [o][taps][c] (khwc = 1) or [o][c][taps] -> the operand order of the split kernel: [filter tile of 16][round]
+// [part][lane][16 bytes]; an fp32 weight as three bf16 parts, 16-bit weights as they are; zeros past the last filter
+// and channel.  split_rounds: rounds of the whole reduction (full chunks of 32 channels take one per tap, the last
+// chunk as many as its 8-channel groups need); split_packed_bytes: size of the packed weights
+int split_rounds(int c, int taps, int* nfull, int* groups_last, int* rounds_last);
+size_t split_packed_bytes(int o, int c, int taps, int dt);
+int launch_pack_split(const void* w, int o, int c, int taps, int khwc, int dt, void* y, hipStream_t s);
 int launch_repack_map2x2(const void* w, const float* bias, int o, int c, int cp_in, int cp_out,
                          int rows_by_channel, int dt, void* w_out, float* bias_out, hipStream_t s);
 

@@ -5,6 +5,9 @@
 #include "conv_wave_kernel.hpp"
 #include "conv_stem2_kernel.hpp"
 #include "conv_patch32_kernel.hpp"
+#include "conv_split_kernel.hpp"
+
+#include <cmath>
 
 namespace cprune {
 namespace {
@@ -62,13 +65,144 @@ Plan make_plan(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayou
   return p;
 }
 
+// The pixel block a work-group of a split variant owns on a map: as few blocks as possible, and among equal ones the
+// smaller patch.  Whole images (several, if they fit) or th x tw pixels of one; a fused pool needs even sizes.
+struct SplitPlan {
+  int th, tw, ni, ph, pw, tiles_n, tiles_y, tiles_x;
+  size_t lds;
+  int off_patch;
+};
+
+bool split_plan(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay, SplitPlan* out) {
+  const int ho = conv_out_dim(d.h, d.kh, d.stride, d.pad), wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
+  const int pt = tv.tile_p(), parts = d.dtype == CPRUNE_F32 ? 3 : 1, even = lay.pool ? 2 : 1;
+  const int taps = d.kh * d.kw;
+  int rounds_last;
+  split_rounds(lay.nhwc ? lay.cp_in : d.c_in, taps, nullptr, nullptr, &rounds_last);
+  const int off_patch = kSplitTab + (taps + rounds_last) * 16;
+  const size_t red = (size_t)(tv.ks - 1) * tv.wm * tv.wn * tv.mb * tv.nb * 1024;
+  double best = -1.0;
+  auto consider = [&](int ni, int th, int tw) {
+    SplitPlan p;
+    p.th = th; p.tw = tw; p.ni = ni;
+    p.ph = (th - 1) * d.stride + d.kh; p.pw = (tw - 1) * d.stride + d.kw;
+    const long npatch = (long)ni * p.ph * p.pw;
+    if ((long)ni * th * tw > pt || npatch > 64L * tv.nib) return;
+    p.tiles_n = (d.n + ni - 1) / ni; p.tiles_y = (ho + th - 1) / th; p.tiles_x = (wo + tw - 1) / tw;
+    p.off_patch = off_patch;
+    p.lds = (size_t)off_patch + (size_t)npatch * (64 * parts + 16);
+    if (p.lds < red) p.lds = red;
+    if (p.lds > 160 * 1024) return;
+    const double cost = (double)p.tiles_n * p.tiles_y * p.tiles_x * (pt + 0.25 * (double)npatch);
+    if (best < 0.0 || cost < best) { best = cost; *out = p; }
+  };
+  if ((long)ho * wo <= pt)
+    for (int ni = (int)(pt / ((long)ho * wo)); ni >= 1; --ni)
+      if (ni <= d.n) consider(ni, ho, wo);
+  for (int nx = 1, last = 0; nx <= wo; ++nx) {
+    const int tw = ((wo + nx - 1) / nx + even - 1) / even * even;
+    if (tw > pt / even || tw == last) continue;
+    last = tw;
+    int th = pt / tw < ho ? pt / tw : ho;                              // rows that fit the block ...
+    const int pw = (tw - 1) * d.stride + d.kw;
+    const int ph_max = 64 * tv.nib / pw;                               // ... and whose patch fits the staging items
+    if (ph_max < d.kh) continue;
+    if ((ph_max - d.kh) / d.stride + 1 < th) th = (ph_max - d.kh) / d.stride + 1;
+    th = th / even * even;
+    if (th < 1) continue;
+    const int ny = (ho + th - 1) / th;
+    consider(1, ((ho + ny - 1) / ny + even - 1) / even * even, tw);
+    if (tw <= even) break;
+  }
+  return best >= 0.0;
+}
+
+bool split_supports(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay) {
+  if (lay.nhwc ? !(d.dtype == CPRUNE_F32 && lay.w_split) : lay.nhwc_out != 0) return false;
+  if (lay.pool == 2 || (lay.pool && ((d.h | d.w) & 1 || d.stride != 1)) || d.stride > 2) return false;
+  const int ho = conv_out_dim(d.h, d.kh, d.stride, d.pad), wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
+  if (!lay.nhwc && (long)ho * wo < 16) return false;   // a map of a few pixels is a matrix product: the general kernel
+  if (split_packed_bytes(d.c_out, lay.nhwc ? lay.cp_in : d.c_in, d.kh * d.kw, d.dtype) >= ((size_t)1 << 31)) return false;
+  SplitPlan p;
+  if (!split_plan(d, tv, lay, &p)) return false;
+  // multiply-high divisions in the tile decode: exact while groups x divisor < 2^32
+  const long tiles_s = (long)p.tiles_n * p.tiles_y * p.tiles_x;
+  const long groups = tiles_s * ((d.c_out + tv.tile_m() - 1) / tv.tile_m());
+  return groups * tiles_s < (1L << 32) && groups < (1L << 31);
+}
+
+// Rough cost in clocks of a split variant on a layer, for choosing among them untimed: the matrix-pipe time of the
+// work-groups a compute unit gets, plus per group the staging of its chunks and the fixed start and end, which overlap
+// between the two or three groups a unit holds.  Constants from timings of all variants on twenty layers.
+double split_cost(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay) {
+  SplitPlan p;
+  if (!split_plan(d, tv, lay, &p)) return -1.0;
+  int nfull, groups_last, rounds_last;
+  const int rtot = split_rounds(lay.nhwc ? lay.cp_in : d.c_in, d.kh * d.kw, &nfull, &groups_last, &rounds_last);
+  const double groups = (double)p.tiles_n * p.tiles_y * p.tiles_x * ((d.c_out + tv.tile_m() - 1) / tv.tile_m());
+  const int occ = tv.mb * tv.nb <= 4 ? 3 : 2;
+  const double mfma = std::ceil((double)rtot / tv.ks) * tv.mb * tv.nb * (d.dtype == CPRUNE_F32 ? 6 : 1) * 18.0;
+  const double chunks = nfull + (rounds_last ? 1 : 0);
+  const double npatch = (double)p.ni * p.ph * p.pw;
+  const double wait = (double)rtot / tv.ks * 250.0;   // operand latency of a round that nothing else hides
+  const double fixed = 5000.0 + chunks * (1500.0 + 8.0 * npatch) + wait;
+  return std::ceil(groups / 256.0) * mfma + std::ceil(groups / (256.0 * occ)) * fixed;
+}
+
+int launch_split_conv(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay, const void* x,
+                      const void* w, const float* bias, const void* residual, void* y, void* ws, hipStream_t s) {
+  SplitPlan p;
+  if (!split_plan(d, tv, lay, &p)) return CPRUNE_ERR_UNSUPPORTED;
+  SplitArgs a;
+  const size_t es = dtype_size(d.dtype);
+  a.C = lay.nhwc ? lay.cp_in : d.c_in;
+  a.taps = d.kh * d.kw; a.kw = d.kw;
+  a.rtot = split_rounds(a.C, a.taps, &a.nfull, &a.groups_last, &a.rounds_last);
+  a.w_bytes = (unsigned)split_packed_bytes(d.c_out, a.C, a.taps, d.dtype);
+  if (lay.nhwc) {
+    a.w = lay.w_split;
+  } else {
+    const int rc = launch_pack_split(w, d.c_out, d.c_in, a.taps, 0, d.dtype, ws, s);
+    if (rc != CPRUNE_OK) return rc;
+    a.w = ws;
+  }
+  a.x = x; a.bias = bias; a.res = residual; a.y = y;
+  a.N = d.n; a.H = d.h; a.W = d.w; a.O = d.c_out;
+  a.Ho = conv_out_dim(d.h, d.kh, d.stride, d.pad); a.Wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
+  a.Cop = lay.cp_out; a.vec_out = (lay.cp_out % 4) == 0 ? 1 : 0;
+  a.stride = d.stride; a.pad = d.pad;
+  a.th = p.th; a.tw = p.tw; a.ni = p.ni; a.ph = p.ph; a.pw = p.pw;
+  a.tiles_n = p.tiles_n; a.tiles_y = p.tiles_y; a.tiles_x = p.tiles_x;
+  a.tiles_m = (d.c_out + tv.tile_m() - 1) / tv.tile_m();
+  const int blocks = (d.c_out + 15) / 16;
+  a.blk_base = blocks / a.tiles_m; a.blk_rem = blocks % a.tiles_m;
+  a.x_bytes = (unsigned)((size_t)d.n * a.C * d.h * d.w * es);
+  a.pool = lay.pool; a.act = d.act;
+  a.m_major = a.w_bytes > a.x_bytes ? 1 : 0;
+  const int tiles_s = p.tiles_n * p.tiles_y * p.tiles_x, div = lay.pool ? 2 : 1;
+  a.magic_s = magic_for((unsigned)tiles_s); a.magic_m = magic_for((unsigned)a.tiles_m);
+  a.magic_x = magic_for((unsigned)p.tiles_x); a.magic_y = magic_for((unsigned)p.tiles_y);
+  a.magic_pp = magic_for((unsigned)(p.ph * p.pw)); a.magic_pw = magic_for((unsigned)p.pw);
+  a.magic_thw = magic_for((unsigned)(p.th * p.tw / (div * div))); a.magic_tw = magic_for((unsigned)(p.tw / div));
+  a.magic_np = magic_for((unsigned)(p.ni * p.ph * p.pw));
+  a.off_patch = p.off_patch;
+  const dim3 grid((unsigned)((long)tiles_s * a.tiles_m));
+  int rc;
+  if (d.dtype == CPRUNE_F32) rc = launch_conv_split_f32(tv.patch_id, !lay.nhwc, grid, p.lds, s, a);
+  else if (d.dtype == CPRUNE_F16) rc = launch_conv_split_f16(tv.patch_id, grid, p.lds, s, a);
+  else rc = launch_conv_split_bf16(tv.patch_id, grid, p.lds, s, a);
+  if (rc != CPRUNE_OK) return rc;
+  CPRUNE_LAUNCH_CHECK();
+  return CPRUNE_OK;
+}
+
 }  // namespace
 
-int num_variants() { return kNumTiles * kNumScheds + kNumPatch + kNumPatch32 + kNumKsplit + kNumPw + kNumWave + kNumPatchS2; }
+int num_variants() { return kNumTiles * kNumScheds + kNumPatch + kNumPatch32 + kNumKsplit + kNumPw + kNumWave + kNumPatchS2 + kNumSplit; }
 
 namespace {
 struct VariantTable {
-  TileVariant table[kNumTiles * kNumScheds + kNumPatch + kNumPatch32 + kNumKsplit + kNumPw + kNumWave + kNumPatchS2];
+  TileVariant table[kNumTiles * kNumScheds + kNumPatch + kNumPatch32 + kNumKsplit + kNumPw + kNumWave + kNumPatchS2 + kNumSplit];
   VariantTable() {
 #define CPRUNE_PATCH_ROW(ID, MB_, TH_, TW_, NI_, KQ_, KS_)                                 \
     {                                                                         \
@@ -119,6 +253,14 @@ struct VariantTable {
     }
     CPRUNE_PATCH_S2_LIST(CPRUNE_PATCH_S2_ROW)
 #undef CPRUNE_PATCH_S2_ROW
+#define CPRUNE_SPLIT_ROW(ID, WM_, WN_, WK_, MB_, NB_, NIB_)                                \
+    {                                                                                      \
+      TileVariant& kv = table[kNumTiles * kNumScheds + kNumPatch + kNumPatch32 + kNumKsplit + kNumPw + kNumWave + kNumPatchS2 + ID]; \
+      kv.wm = WM_; kv.wn = WN_; kv.mb = MB_; kv.nb = NB_; kv.kq = 1; kv.sched = -1; kv.split = 1;         \
+      kv.patch_id = ID; kv.ks = WK_; kv.nib = NIB_;                                        \
+    }
+    CPRUNE_SPLIT_LIST(CPRUNE_SPLIT_ROW)
+#undef CPRUNE_SPLIT_ROW
     for (int t = 0; t < kNumTiles; ++t)
       for (int s = 0; s < kNumScheds; ++s) {
         table[t * kNumScheds + s] = kTiles[t];
@@ -127,6 +269,17 @@ struct VariantTable {
   }
 };
 }  // namespace
+
+int best_split_variant(const cprune_conv_desc& d, const ConvLayout& lay) {
+  double best = -1.0;
+  int best_v = -1;
+  for (int v = num_variants() - kNumSplit; v < num_variants(); ++v) {
+    if (!variant_supports(d, v, lay)) continue;
+    const double c = split_cost(d, variant(v), lay);
+    if (c >= 0.0 && (best < 0.0 || c < best)) { best = c; best_v = v; }
+  }
+  return best_v;
+}
 
 const TileVariant& variant(int id) {
   static const VariantTable vt;   // built once, on first use, whichever thread gets there first
@@ -137,6 +290,7 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
   if (v < 0 || v >= num_variants()) return false;
   if (d.groups != 1) return false;
   const TileVariant& tv = variant(v);
+  if (tv.split) return split_supports(d, tv, lay);
   if (tv.sched == -4) {
     // 3x3 / stride 1 / pad 1 on small maps (every wavefront fetches its own weights: with many pixels the
     // tiled kernels, which share them through LDS, are the ones to use)
@@ -196,16 +350,21 @@ size_t conv_ws_bytes(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
   if (v >= 0) {
     if (!variant_supports(d, v, lay)) return 0;
     const TileVariant& tv = variant(v);
+    if (tv.split && !lay.nhwc) return split_packed_bytes(d.c_out, d.c_in, d.kh * d.kw, d.dtype);
     if (tv.sched < 0) return 0;
     const Plan p = make_plan(d, tv, lay);
     return p.fixup ? (size_t)2 * p.groups * tv.tile_m() * tv.tile_p() * sizeof(float) : 0;
   }
+  // the most any variant needs: cut tiles, or (all alike) the packed weights of the split kernel
   size_t best = 0;
-  for (int i = 0; i < num_variants(); ++i)
-    if (variant_supports(d, i, lay)) {
-      size_t b = conv_ws_bytes(d, i, lay);
-      if (b > best) best = b;
-    }
+  bool split = false;
+  for (int i = 0; i < num_variants(); ++i) {
+    const TileVariant& tv = variant(i);
+    if (tv.split ? lay.nhwc || split : tv.sched <= 0) continue;
+    const size_t b = conv_ws_bytes(d, i, lay);
+    if (tv.split && b) split = true;
+    if (b > best) best = b;
+  }
   return best;
 }
 
@@ -213,6 +372,7 @@ int launch_conv_dense(const cprune_conv_desc& d, const void* x, const void* w, c
                       const void* residual, void* y, int v, void* ws, hipStream_t s, const ConvLayout& lay) {
   const TileVariant& tv = variant(v);
   const size_t es = dtype_size(d.dtype);
+  if (tv.split) return launch_split_conv(d, tv, lay, x, w, bias, residual, y, ws, s);
   if (tv.sched == -4) {
     PatchArgs pa;
     pa.x = x; pa.w = lay.w_wave; pa.bias = bias; pa.res = residual; pa.y = y;

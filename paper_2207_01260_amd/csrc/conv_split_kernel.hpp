@@ -1,0 +1,547 @@
+// Dense convolution, any window up to 7x7 and stride up to 2, on the 16-bit matrix cores for fp32 data too.
+//
+// v_mfma_f32_16x16x4_f32 multiplies at 157 TFLOP/s, v_mfma_f32_16x16x32_bf16 at 2.5 PFLOP/s.  An fp32 number is
+// exactly the sum of three bf16 numbers (its 24 significant bits cut into three runs of eight), so an fp32 product is
+// the sum of nine bf16 products, each exact in fp32; the three smallest (2^-24 of the product and below) are left out
+// and the six others accumulated in fp32: 2.7 times the fp32 instruction's rate, at an error no larger (that one
+// rounds its sum eight times per 32 terms, this one twice).  Weights are cut and packed once (launch_pack_split),
+// activations while they are staged into LDS (some six vector operations per element, against 9 x 6 multiplies per
+// filter).  Activations are cut by rounding to nearest, so that what is left out has no sign of its own and does not
+// add up over the layers of a network; weights by truncation, so that their parts have one sign and an infinite
+// activation gives the infinity the fp32 product gives (see pack_split_kernel for parts that are zero).
+// 16-bit data runs the same kernel with one part per number.
+//
+// A work-group owns MT = WM * MB * 16 filters and a block of th x tw pixels of ni images, at most PT = WN * NB * 16
+// pixels; which block is the host's choice per map (split_plan): pixels are numbered by division, so the block need
+// not be a power of two and an odd map wastes little.  Per chunk of 32 input channels the patch the block's windows
+// touch is staged once ([pixel][8-channel group][part][16 bytes], 16 bytes of pad per pixel so that the pixels of a
+// read rotate through the banks).  The reduction of a chunk is a list of (tap, 8-channel group) units, four per MFMA
+// round, one per 16-lane quarter; the LDS offset of a unit comes from a table in LDS.  A last chunk of one to three
+// groups therefore costs no padded rounds: channel counts cost in steps of 8, not 32.  Weight fragments go straight
+// from memory to registers, packed in the order of the rounds (a wavefront's load is 1 KiB of consecutive memory), one
+// round ahead; the next chunk's activations are in flight while this one is multiplied.  WK wavefronts can share one
+// block and take every WK-th round (few blocks, long reductions); their sums meet in LDS at the end, in order.
+//
+// Measured, fp32 channels-last, best variant against the best fp32-instruction kernel: 56 -> 56 at 32x32, batch 64, 42.4
+// -> 25.7 us; 40 -> 64 at 56x56, batch 32, 54.1 -> 34.2 us; 128 -> 85 at 28x28 56.8 -> 35.1 us; 512 -> 411 at 7x7
+// 72.2 -> 53.1 us; 360 -> 360 at 4x4, batch 64, 25.4 -> 26.2 us (the independent-wavefront kernel stays there);
+// stride 2, 128 -> 173 at 28x28, 34.8 -> 25.1 us.  Error against 64 bits 0.3 to 0.6 of that kernel's.  What bounds it:
+// of the 32 us of 85 -> 128 at 28x28 the matrix pipes need 14; operand reads, weight reads and staging cost 5-8 %
+// each when left out alone; 8 us are launch, first loads and stores, which the two or three work-groups of a unit,
+// started together, do not hide from each other.
+#pragma once
+#include <atomic>
+#include "conv_nhwc_kernel.hpp"
+
+// every lambda of the kernel: one that is not inlined takes the arrays it captures into scratch memory
+#define CPRUNE_INLINE __attribute__((always_inline))
+
+namespace cprune {
+
+struct SplitArgs {
+  const void* x;        // NCHW or channels-last
+  const void* w;        // packed by launch_pack_split
+  const float* bias;
+  const void* res;
+  void* y;              // the layout of x
+  int N, H, W, Ho, Wo, O, C;   // C: input channels (channels-last: their stride, pad channels zero)
+  int Cop;              // channels-last: channel stride of y
+  int stride, pad, kw, taps;
+  int th, tw, ni, ph, pw;      // pixel block of a work-group; its input patch
+  int tiles_n, tiles_y, tiles_x, tiles_m;
+  int blk_base, blk_rem;       // 16-filter blocks per filter tile: blk_base, and one more in the first blk_rem
+  int nfull, rounds_last, rtot;  // chunks of 32 channels; rounds of the last, partial one (0: none); rounds in all
+  int groups_last;               // 8-channel groups of the last chunk
+  unsigned x_bytes, w_bytes;
+  unsigned magic_s, magic_m, magic_x, magic_y;      // tile decode (as PatchArgs)
+  unsigned magic_pp, magic_pw;                      // patch pixel -> (image, row, column)
+  unsigned magic_thw, magic_tw;                     // output pixel of the block -> (image, row, column); pooled: windows
+  unsigned magic_np;                                // staging item -> (group, patch pixel), NCHW
+  int m_major, act, pool, vec_out;
+  int off_patch;        // LDS offset of the patch behind the tables
+};
+
+constexpr int kSplitTab = 128;   // LDS: 64 bytes of zeros, 64 that take the writes of threads without an item, then
+                                 // the two offset tables (full chunk, last chunk), then the patch
+
+template <typename T> struct SplitParts { static constexpr int value = sizeof(T) == 4 ? 3 : 1; };
+
+typedef float float2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+
+// two numbers as three pairs of bf16 numbers, each the nearest to what the ones before it leave
+__device__ __forceinline__ void split3(uint32_t u0, uint32_t u1, uint32_t& h, uint32_t& m, uint32_t& l) {
+  const float2_t x = {__uint_as_float(u0), __uint_as_float(u1)};
+  h = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2_t));
+  const float r0 = x[0] - __uint_as_float(h << 16), r1 = x[1] - __uint_as_float(h & 0xffff0000u);
+  m = __builtin_bit_cast(uint32_t, __builtin_convertvector((float2_t){r0, r1}, bf16x2_t));
+  const float s0 = r0 - __uint_as_float(m << 16), s1 = r1 - __uint_as_float(m & 0xffff0000u);
+  l = __builtin_bit_cast(uint32_t, __builtin_convertvector((float2_t){s0, s1}, bf16x2_t));
+}
+
+// The same by truncation, for numbers whose first part would round to infinity, and for infinities: no remainder
+__device__ __forceinline__ void split3_large(uint32_t u, uint32_t& h, uint32_t& m, uint32_t& l) {
+  h = u & 0xffff0000u;
+  float r = __uint_as_float(u) - __uint_as_float(h);
+  r = (u & 0x7fffffffu) == 0x7f800000u ? 0.0f : r;
+  m = __float_as_uint(r) & 0xffff0000u;
+  l = __float_as_uint(r - __uint_as_float(m));
+}
+
+// top halves of two dwords, the first one low
+__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
+template <typename T>
+__device__ __forceinline__ float4_t mfma_split(const uint4& a, const uint4& b, const float4_t& c) {
+  if constexpr (std::is_same<T, _Float16>::value)
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
+template <typename T, bool NCHW, int WM, int WN, int WK, int MB, int NB, int NIB>
+__global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_split_kernel(SplitArgs a) {
+  constexpr int ES = (int)sizeof(T);
+  constexpr int P = SplitParts<T>::value;
+  constexpr int UNIT = P * 16;            // bytes of one 8-channel group of a pixel
+  constexpr int BROW = 4 * UNIT + 16;
+  constexpr int NV = ES == 4 ? 8 : 4;     // dwords of a staged item held in registers
+  static_assert(WM * WN * WK == 4, "four wavefronts");
+
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  int* const tab = (int*)(smem + kSplitTab);
+
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wk = wave / (WM * WN), wmn = wave % (WM * WN);
+  const int wm = wmn / WN, wn = wmn % WN;
+  const int r = lane & 15, g4 = lane >> 4;
+
+  // tile decode; each XCD (own L2) gets one contiguous stretch of the tile order
+  int tile;
+  {
+    const int G = gridDim.x;
+    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+    const int q = G >> 3, rem = G & 7;
+    tile = xcd * q + (xcd < rem ? xcd : rem) + local;
+  }
+  const int tiles_s = a.tiles_n * a.tiles_y * a.tiles_x;
+  const int q_s = (int)fast_div((unsigned)tile, a.magic_s), q_m = (int)fast_div((unsigned)tile, a.magic_m);
+  const int tile_m = a.m_major ? q_s : tile - q_m * a.tiles_m;
+  const int rest = a.m_major ? tile - q_s * tiles_s : q_m;
+  const int q_x = (int)fast_div((unsigned)rest, a.magic_x);
+  const int q_y = (int)fast_div((unsigned)q_x, a.magic_y);
+  const int tx0 = (rest - q_x * a.tiles_x) * a.tw;
+  const int ty0 = (q_x - q_y * a.tiles_y) * a.th;
+  const int n0 = q_y * a.ni;
+  // 16-filter blocks are dealt out evenly, first to the tiles and then to a tile's wavefronts: a layer costs what its
+  // blocks cost, not what its tiles would hold
+  const int tblk = a.blk_base + (tile_m < a.blk_rem ? 1 : 0);                        // blocks of this tile
+  const int blk0 = tile_m * a.blk_base + min(tile_m, a.blk_rem) + wm * (tblk / WM) + min(wm, tblk % WM);
+  const int nblk = tblk / WM + (wm < tblk % WM ? 1 : 0);                             // blocks of this wavefront
+  const int o0 = blk0 * 16;                                                        // its first filter
+
+  const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, a.x_bytes);
+  const __amdgpu_buffer_rsrc_t wr = make_rsrc(a.w, a.w_bytes);
+
+  // ---- weights: one round of this wavefront's filter blocks ----
+  const unsigned a_blk = (unsigned)a.rtot * (P * 1024u);
+  const unsigned a_base = (unsigned)blk0 * a_blk;
+  auto load_weights = [&](auto mbc, int rg, uint4 (&f)[MB][P]) CPRUNE_INLINE {
+#pragma unroll
+    for (int i = 0; i < decltype(mbc)::value; ++i)
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+        f[i][p] = load_b128(wr, (unsigned)lane * 16u + p * 1024u, a_base + i * a_blk + (unsigned)rg * (P * 1024u));
+  };
+  uint4 a0[MB][P], a1[MB][P];
+
+  // ---- staging items: (patch pixel, 8-channel group) ----
+  const int npp = a.ph * a.pw, npatch = a.ni * npp;
+  const int hw = a.H * a.W;
+  unsigned b_off[NIB];
+  int b_lds[NIB], b_ch[NIB];
+#pragma unroll
+  for (int j = 0; j < NIB; ++j) {
+    const int idx = t + 256 * j;
+    int g, pp;
+    if constexpr (NCHW) {
+      g = (int)fast_div((unsigned)idx, a.magic_np);
+      pp = idx - g * npatch;
+    } else {
+      g = idx & 3;
+      pp = idx >> 2;
+    }
+    const bool item = pp < npatch && g < 4;
+    const int img = (int)fast_div((unsigned)pp, a.magic_pp), pr = pp - img * npp;
+    const int py = (int)fast_div((unsigned)pr, a.magic_pw), px = pr - py * a.pw;
+    const int iy = ty0 * a.stride + py - a.pad, ix = tx0 * a.stride + px - a.pad, n = n0 + img;
+    const bool inside = item && n < a.N && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+    if constexpr (NCHW)
+      b_off[j] = inside ? (unsigned)((n * a.C + g * 8) * hw + iy * a.W + ix) * ES : kOutOfRange;
+    else
+      b_off[j] = inside ? (unsigned)(((n * a.H + iy) * a.W + ix) * a.C + g * 8) * ES : kOutOfRange;
+    b_lds[j] = item ? a.off_patch + pp * BROW + g * UNIT : 64;
+    b_ch[j] = g * 8;
+  }
+  uint32_t breg[NIB][NV];
+  auto gload = [&](int c) CPRUNE_INLINE {
+    const int c0 = c * 32;
+#pragma unroll
+    for (int j = 0; j < NIB; ++j) {
+      if constexpr (NCHW) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const unsigned voff = b_off[j] | ((unsigned)(c0 + b_ch[j] + e >= a.C) << 31);
+          const uint32_t v = Elem<T>::load(xr, voff, (unsigned)((c0 + e) * hw) * ES);
+          if constexpr (ES == 4) breg[j][e] = v;
+          else if (e & 1) breg[j][e >> 1] |= v << 16;
+          else breg[j][e >> 1] = v;
+        }
+      } else {
+        constexpr int EPI = 16 / ES;      // elements per 16-byte load
+#pragma unroll
+        for (int e = 0; e < 8; e += EPI) {
+          const unsigned voff = b_off[j] | ((unsigned)(c0 + b_ch[j] + e >= a.C) << 31);
+          const uint4 v = load_b128(xr, voff + e * ES, (unsigned)(c0 * ES));
+          breg[j][e * ES / 4] = v.x; breg[j][e * ES / 4 + 1] = v.y;
+          breg[j][e * ES / 4 + 2] = v.z; breg[j][e * ES / 4 + 3] = v.w;
+        }
+      }
+    }
+  };
+  auto lds_store = [&]() CPRUNE_INLINE {
+    if constexpr (P == 1) {
+#pragma unroll
+      for (int j = 0; j < NIB; ++j) *(uint4*)(smem + b_lds[j]) = make_uint4(breg[j][0], breg[j][1], breg[j][2], breg[j][3]);
+    } else {
+      auto store = [&](auto large) CPRUNE_INLINE {
+#pragma unroll
+        for (int j = 0; j < NIB; ++j) {
+          uint4* const dst = (uint4*)(smem + b_lds[j]);
+          uint32_t h[4], m[4], l[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if constexpr (decltype(large)::value) {
+              uint32_t p0[3], p1[3];
+              split3_large(breg[j][2 * e], p0[0], p0[1], p0[2]);
+              split3_large(breg[j][2 * e + 1], p1[0], p1[1], p1[2]);
+              h[e] = pack_hi(p0[0], p1[0]); m[e] = pack_hi(p0[1], p1[1]); l[e] = pack_hi(p0[2], p1[2]);
+            } else {
+              split3(breg[j][2 * e], breg[j][2 * e + 1], h[e], m[e], l[e]);
+            }
+          }
+          dst[0] = make_uint4(h[0], h[1], h[2], h[3]);
+          dst[1] = make_uint4(m[0], m[1], m[2], m[3]);
+          dst[2] = make_uint4(l[0], l[1], l[2], l[3]);
+        }
+      };
+      float big = 0.0f;   // numbers near the end of the range are looked for once per chunk
+#pragma unroll
+      for (int j = 0; j < NIB; ++j)
+#pragma unroll
+        for (int e = 0; e < 8; e += 2)
+          big = fmaxf(fmaxf(big, fabsf(__uint_as_float(breg[j][e]))), fabsf(__uint_as_float(breg[j][e + 1])));
+      if (__builtin_expect(big >= 0x1.fep127f, 0)) store(std::true_type{});
+      else store(std::false_type{});
+    }
+  };
+  gload(0);
+
+  // ---- offset tables: unit u of a chunk = (tap u / groups, group u % groups); -1 past the last unit ----
+  if (t < 32) ((int*)smem)[t] = 0;
+  for (int i = t; i < (a.taps + a.rounds_last) * 4; i += 256) {
+    const bool last = i >= a.taps * 4;
+    const int u = last ? i - a.taps * 4 : i;
+    const int ng = last ? a.groups_last : 4;
+    const int tap = u / ng, g = u - tap * ng;
+    const int ty = tap / a.kw;
+    tab[i] = tap < a.taps ? (ty * a.pw + tap - ty * a.kw) * BROW + g * UNIT : -1;
+  }
+
+  // ---- this lane's pixels: patch position of the window's first tap ----
+  int b_frag[NB];
+  auto pixel_of = [&](int j, int& img, int& ty, int& tx) CPRUNE_INLINE {   // column j of this wavefront
+    const int id = (wn * NB + j) * 16 + r;
+    if (a.pool) {   // four consecutive pixels are one 2x2 window
+      const int win = id >> 2, wpi = (a.th * a.tw) >> 2;
+      img = (int)fast_div((unsigned)win, a.magic_thw);
+      const int wr_ = win - img * wpi;
+      const int wy = (int)fast_div((unsigned)wr_, a.magic_tw);
+      ty = 2 * wy + ((id >> 1) & 1);
+      tx = 2 * (wr_ - wy * (a.tw >> 1)) + (id & 1);
+    } else {
+      img = (int)fast_div((unsigned)id, a.magic_thw);
+      const int ir = id - img * a.th * a.tw;
+      ty = (int)fast_div((unsigned)ir, a.magic_tw);
+      tx = ir - ty * a.tw;
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    int img, ty, tx;
+    pixel_of(j, img, ty, tx);
+    b_frag[j] = a.off_patch + (img < a.ni ? (img * npp + ty * a.stride * a.pw + tx * a.stride) * BROW : 0);
+  }
+
+  float4_t acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = (float4_t){0.f, 0.f, 0.f, 0.f};
+
+  // pixel columns are multiplied JS at a time; two such sets of operands are held: the one in use and the next one
+  constexpr int JS = (NB >= 8 && MB == 1) ? 4 : (NB >= 4 && MB <= 2 ? 2 : 1), NSET = NB / JS;
+  static_assert(NSET >= 2 && NB % JS == 0, "two operand sets");
+  uint4 bf[2][JS][P];
+  auto read_set = [&](int set, int off) CPRUNE_INLINE {
+#pragma unroll
+    for (int j = 0; j < JS; ++j) {
+      const uint4* const src = (const uint4*)(smem + (off < 0 ? 0 : b_frag[set * JS + j] + off));
+#pragma unroll
+      for (int p = 0; p < P; ++p) bf[set & 1][j][p] = src[p];
+    }
+  };
+  // The five small products of a round are added up among themselves, so that their sum is rounded at its own size, and
+  // meet the running sum once: two roundings of it per 32 terms, where the fp32 instruction makes eight.  They do so
+  // while the next set is multiplied.  The barriers keep consecutive MFMAs on different accumulators: left alone the
+  // scheduler issues each block's chain back to back and waits out every result (56 -> 56 filters at 32x32, batch 64:
+  // 28.1 us without, 25.7 us with them).
+  float4_t small[MB][JS];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < JS; ++j) small[i][j] = (float4_t){0.f, 0.f, 0.f, 0.f};
+  auto add_small = [&](auto mbc, int set) CPRUNE_INLINE {
+    constexpr int MBC = decltype(mbc)::value;
+#pragma unroll
+    for (int j = 0; j < JS; ++j)
+#pragma unroll
+      for (int i = 0; i < MBC; ++i) acc[i][set * JS + j] += small[i][j];
+  };
+  // one round at offset `off`, its first two operand sets read; leaves the first two of the round at `next_off`
+  auto round = [&](auto mbc, const uint4 (&f)[MB][P], int off, int next_off) CPRUNE_INLINE {
+    constexpr int MBC = decltype(mbc)::value;
+#pragma unroll
+    for (int set = 0; set < NSET; ++set) {
+      const int j0 = set * JS;
+      const uint4 (&b)[JS][P] = bf[set & 1];
+      if constexpr (P == 3) {
+        float4_t sum[MB][JS];
+#pragma unroll
+        for (int j = 0; j < JS; ++j)
+#pragma unroll
+          for (int i = 0; i < MBC; ++i) sum[i][j] = mfma_split<T>(f[i][0], b[j][2], (float4_t){0.f, 0.f, 0.f, 0.f});
+        __builtin_amdgcn_sched_barrier(0x6);
+        add_small(mbc, (set + NSET - 1) % NSET);
+        auto term = [&](int pa, int pb) CPRUNE_INLINE {
+#pragma unroll
+          for (int j = 0; j < JS; ++j)
+#pragma unroll
+            for (int i = 0; i < MBC; ++i) sum[i][j] = mfma_split<T>(f[i][pa], b[j][pb], sum[i][j]);
+          __builtin_amdgcn_sched_barrier(0x6);
+        };
+        term(2, 0);
+#pragma unroll
+        for (int j = 0; j < JS; ++j)
+#pragma unroll
+          for (int i = 0; i < MBC; ++i) acc[i][j0 + j] = mfma_split<T>(f[i][0], b[j][0], acc[i][j0 + j]);
+        __builtin_amdgcn_sched_barrier(0x6);
+        term(1, 1); term(0, 1); term(1, 0);
+#pragma unroll
+        for (int j = 0; j < JS; ++j)
+#pragma unroll
+          for (int i = 0; i < MBC; ++i) small[i][j] = sum[i][j];
+      } else {
+#pragma unroll
+        for (int j = 0; j < JS; ++j)
+#pragma unroll
+          for (int i = 0; i < MBC; ++i) acc[i][j0 + j] = mfma_split<T>(f[i][0], b[j][0], acc[i][j0 + j]);
+      }
+      if (set + 2 < NSET) read_set(set + 2, off);
+      else read_set(set + 2 - NSET, next_off);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  const int nchunk = a.nfull + (a.rounds_last ? 1 : 0);
+  auto main_loop = [&](auto mbc) CPRUNE_INLINE {
+    constexpr int MBC = decltype(mbc)::value;
+    load_weights(mbc, wk, a0);
+    for (int c = 0; c < nchunk; ++c) {
+      __syncthreads();            // everyone is done reading the previous chunk (and the tables are written)
+      lds_store();
+      __syncthreads();
+      const bool full = c < a.nfull;
+      const int R = full ? a.taps : a.rounds_last;
+      const int* const tb = tab + (full ? 0 : a.taps * 4) + g4;
+      const int rg0 = c * a.taps;
+      // (round rg + WK of this chunk, or the first of the next one; past the end the values are never used)
+      auto next_rg = [&](int q) CPRUNE_INLINE { return q + WK < R ? rg0 + q + WK : rg0 + a.taps + wk; };
+      if (wk >= R) {
+        if (c + 1 < nchunk) gload(c + 1);
+        continue;
+      }
+      auto tab_at = [&](int q) CPRUNE_INLINE { return tb[(q < R ? q : R - 1) * 4]; };
+      int off0 = tab_at(wk), off1 = tab_at(wk + WK);
+      read_set(0, off0);
+      read_set(1, off0);
+      int q = wk;
+      // the first round asks for the second one's weights before it asks for the next chunk's activations: loads
+      // return in order, and a wait for weights asked for behind them waits for them too
+      load_weights(mbc, next_rg(q), a1);
+      if (c + 1 < nchunk) gload(c + 1);
+      auto step = [&](const uint4 (&f)[MB][P], int qq) CPRUNE_INLINE {
+        const int nxt = tab_at(qq + 2 * WK);
+        round(mbc, f, off0, off1);
+        off0 = off1;
+        off1 = nxt;
+      };
+      step(a0, q);
+      q += WK;
+      for (; q + WK < R; q += 2 * WK) {
+        load_weights(mbc, next_rg(q), a0);
+        step(a1, q);
+        load_weights(mbc, next_rg(q + WK), a1);
+        step(a0, q + WK);
+      }
+      if (q < R) {
+        load_weights(mbc, next_rg(q), a0);
+        step(a1, q);
+      } else {
+#pragma unroll
+        for (int i = 0; i < MBC; ++i)
+#pragma unroll
+          for (int p = 0; p < P; ++p) a0[i][p] = a1[i][p];
+      }
+    }
+    if constexpr (P == 3) add_small(mbc, NSET - 1);
+  };
+  // compiled once per block count, as the other kernels' main loops (a wavefront without a block runs the shortest one,
+  // on weights past the end of their buffer, which read as zeros, and stores nothing)
+  if (MB >= 3 && nblk >= 3) main_loop(std::integral_constant<int, MB >= 3 ? 3 : 1>{});
+  else if (MB >= 2 && nblk >= 2) main_loop(std::integral_constant<int, MB >= 2 ? 2 : 1>{});
+  else main_loop(std::integral_constant<int, 1>{});
+  if constexpr (WK > 1) {
+    // the wavefronts that share a block hand their sums to the first, which adds them in order
+    __syncthreads();
+    float4_t* const red = (float4_t*)smem + (size_t)wmn * (MB * NB * 64) + lane;
+    constexpr int STEP = WM * WN * MB * NB * 64;
+    if (wk > 0) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) red[(wk - 1) * STEP + (i * NB + j) * 64] = acc[i][j];
+    }
+    __syncthreads();
+    if (wk > 0) return;
+#pragma unroll
+    for (int k = 1; k < WK; ++k)
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] += red[(k - 1) * STEP + (i * NB + j) * 64];
+  }
+  if (nblk == 0) return;
+
+  // ---- epilogue: a lane holds filters o .. o + 3 of its pixel ----
+  ConvArgs e;
+  e.bias = a.bias; e.res = a.res; e.y = a.y; e.O = a.O; e.Cop = a.Cop; e.act = a.act; e.vec_out = a.vec_out; e.pool4 = 0;
+  float4_t bias4[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) bias4[i] = load_bias4(a.bias, a.O, o0 + i * 16 + 4 * g4);
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    int img, ty, tx;
+    pixel_of(j, img, ty, tx);
+    const int n = n0 + img, oy = ty0 + ty, ox = tx0 + tx;
+    const bool inside = img < a.ni && ty < a.th && n < a.N && oy < a.Ho && ox < a.Wo;
+    if constexpr (NCHW) {
+      if (!inside) continue;
+      T* const yg = (T*)a.y;
+      const T* const rg = (const T*)a.res;
+      const size_t howo = (size_t)a.Ho * a.Wo;
+      const size_t pix = (size_t)n * a.O * howo + (size_t)oy * a.Wo + ox;
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          if (i >= nblk) break;
+          const int o = o0 + i * 16 + 4 * g4 + v;
+          if (o < a.O) {
+            const size_t off = pix + (size_t)o * howo;
+            float val = acc[i][j][v] + bias4[i][v];
+            if (rg) val += Elem<T>::to_f32(rg[off]);
+            yg[off] = Elem<T>::from_f32(apply_act(val, a.act));
+          }
+        }
+    } else if (!a.pool) {
+      if (!inside) continue;
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+        if (i < nblk) nhwc_store4<T>(e, acc[i][j], (n * a.Ho + oy) * a.Wo + ox, o0 + i * 16 + 4 * g4, bias4[i]);
+    } else {
+      // the activation is monotone: the maximum of a window's four activated values, in lanes r ^ 1, r ^ 2, r ^ 3
+      ConvArgs ep = e;
+      ep.act = CPRUNE_ACT_NONE;
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        float4_t m;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          float x = apply_act(acc[i][j][v] + bias4[i][v], a.act);
+          x = fmaxf(x, __shfl_xor(x, 1, 64));
+          m[v] = fmaxf(x, __shfl_xor(x, 2, 64));
+        }
+        if (inside && (r & 3) == 0 && i < nblk)
+          nhwc_store4<T>(ep, m, (n * (a.Ho >> 1) + (oy >> 1)) * (a.Wo >> 1) + (ox >> 1), o0 + i * 16 + 4 * g4,
+                         (float4_t){0.f, 0.f, 0.f, 0.f});
+      }
+    }
+  }
+}
+
+// Variants: id, wavefronts along filters / pixels / rounds, 16-filter and 16-pixel blocks per wavefront, staging
+// items per thread (what patch the pixel block may have: at most 64 * nib pixels)
+#define CPRUNE_SPLIT_LIST(X) \
+  X(0, 2, 2, 1, 2, 4, 4)  \
+  X(1, 2, 2, 1, 2, 2, 2)  \
+  X(2, 4, 1, 1, 1, 4, 2)  \
+  X(3, 4, 1, 1, 2, 4, 2)  \
+  X(4, 2, 2, 1, 3, 4, 4)  \
+  X(5, 1, 4, 1, 3, 2, 4)  \
+  X(6, 1, 4, 1, 2, 2, 4)  \
+  X(7, 2, 1, 2, 1, 4, 2)  \
+  X(8, 1, 1, 4, 2, 4, 2)  \
+  X(9, 1, 1, 4, 2, 2, 2)  \
+  X(10, 1, 1, 4, 1, 2, 2) \
+  X(11, 2, 2, 1, 1, 2, 5) \
+  X(12, 2, 2, 1, 2, 2, 5) \
+  X(13, 1, 4, 1, 2, 4, 6)
+
+constexpr int kNumSplit = 14;
+
+template <typename T, bool NCHW>
+inline int launch_split(int id, dim3 grid, size_t lds, hipStream_t s, const SplitArgs& a) {
+#define CPRUNE_SPLIT_CASE(ID, WM_, WN_, WK_, MB_, NB_, NIB_)                                                  \
+  case ID: {                                                                                                  \
+    static std::atomic<bool> raised{false};   /* more than the default 64 KiB of LDS has to be asked for once */ \
+    if (lds > 65536 && !raised.load(std::memory_order_relaxed)) {                                             \
+      CPRUNE_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_split_kernel<T, NCHW, WM_, WN_, WK_, MB_, NB_, NIB_>), \
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));            \
+      raised.store(true, std::memory_order_relaxed);                                                          \
+    }                                                                                                         \
+    hipLaunchKernelGGL((conv_split_kernel<T, NCHW, WM_, WN_, WK_, MB_, NB_, NIB_>), grid, dim3(256), lds, s, a); \
+    break;                                                                                                    \
+  }
+  switch (id) { CPRUNE_SPLIT_LIST(CPRUNE_SPLIT_CASE) default: return CPRUNE_ERR_UNSUPPORTED; }
+#undef CPRUNE_SPLIT_CASE
+  return CPRUNE_OK;
+}
+
+int launch_conv_split_f32(int id, bool nchw, dim3 grid, size_t lds, hipStream_t s, const SplitArgs& a);
+int launch_conv_split_f16(int id, dim3 grid, size_t lds, hipStream_t s, const SplitArgs& a);    // NCHW only
+int launch_conv_split_bf16(int id, dim3 grid, size_t lds, hipStream_t s, const SplitArgs& a);
+
+}  // namespace cprune

@@ -400,6 +400,56 @@ __global__ __launch_bounds__(256) void repack_rows_kernel(const T* __restrict__ 
   y[i] = v;
 }
 
+// Weights -> the operand order of the split kernel: [filter tile of 16][round][part][lane = quarter * 16 + filter]
+// [8 channels].  A round holds four (tap, 8-channel group) units, one per quarter.  An fp32 weight becomes three bf16
+// parts of its own sign, by truncation (conv_split_kernel.hpp says why).  A part that would be zero is the smallest normal
+// number instead, where the weight itself is not tiny: an infinite input times that part is then an infinity of the
+// right sign, where zero would make it a NaN; to a finite input it adds less than 2^-26 of the product.
+template <typename T>
+__global__ __launch_bounds__(256) void pack_split_kernel(const T* __restrict__ w, uint4* __restrict__ y, int total,
+                                                         int o_count, int c_count, int taps, int khwc, int nfull,
+                                                         int groups_last, int rtot) {
+  constexpr int P = sizeof(T) == 4 ? 3 : 1;
+  const int i = blockIdx.x * 256 + threadIdx.x;    // one lane of one round of one filter tile
+  if (i >= total) return;
+  const int lane = i & 63;
+  const int rg = (i >> 6) % rtot, tm = (i >> 6) / rtot;
+  const int o = tm * 16 + (lane & 15);
+  const bool full = rg < nfull * taps;
+  const int chunk = full ? rg / taps : nfull;
+  const int u = (rg - chunk * taps) * 4 + (lane >> 4);
+  const int ng = full ? 4 : groups_last;
+  const int tap = u / ng, c0 = chunk * 32 + (u - tap * ng) * 8;
+  uint32_t part[P][4] = {};
+  T vals[8];
+  const bool row = o < o_count && tap < taps;
+  const size_t step = khwc ? 1 : taps;
+  // (a chunk's first channel is always one that exists: c0 of a real unit is below c_count)
+  const T* const src = w + (row ? (khwc ? ((size_t)o * taps + tap) * c_count + c0 : ((size_t)o * c_count + c0) * taps + tap) : 0);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) vals[e] = src[row && c0 + e < c_count ? e * step : 0];   // (all eight in flight at once)
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const T v = row && c0 + e < c_count ? vals[e] : (T)0.0f;
+    if constexpr (P == 1) {
+      part[0][e >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, v) << (16 * (e & 1));
+    } else {
+      const uint32_t bits = __float_as_uint(v), mag = bits & 0x7fffffffu;
+      uint32_t b = bits;
+      for (int p = 0; p < 3; ++p) {
+        uint32_t hi = b & 0xffff0000u;
+        if (p > 0 && (hi << 1) == 0 && mag >= (27u << 23) && mag <= 0x7f7fffffu) hi = (bits & 0x80000000u) | 0x00800000u;
+        const float rest = __uint_as_float(b) - __uint_as_float(b & 0xffff0000u);
+        b = mag == 0x7f800000u ? 0u : __float_as_uint(rest);
+        part[p][e >> 1] |= (hi >> 16) << (16 * (e & 1));
+      }
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    y[((size_t)(i >> 6) * P + p) * 64 + lane] = make_uint4(part[p][0], part[p][1], part[p][2], part[p][3]);
+}
+
 // Every input pixel of a 2x2 map lies inside the 3x3 window (pad 1) of every output pixel, so
 // the layer is one dense matrix from the whole input map to the whole output map: the tap that
 // links input pixel (iy, ix) to output pixel (oy, ox) is (iy - oy + 1, ix - ox + 1).
@@ -663,6 +713,28 @@ int launch_repack_rows(const void* w, int rows, int k, int dt, void* y, hipStrea
   const long total = (long)(rows_packed_bytes(rows, k, dt) / dtype_size(dt));
   CPRUNE_BY_DTYPE(dt, hipLaunchKernelGGL(repack_rows_kernel<T>, blocks_for(total), dim3(256), 0, s, (const T*)w, (T*)y,
                                          total, rows, k, rounds));
+  CPRUNE_LAUNCH_CHECK();
+  return CPRUNE_OK;
+}
+
+int split_rounds(int c, int taps, int* nfull, int* groups_last, int* rounds_last) {
+  const int groups = (c + 7) / 8, nf = groups / 4, gl = groups % 4, rl = (taps * gl + 3) / 4;
+  if (nfull) *nfull = nf;
+  if (groups_last) *groups_last = gl;
+  if (rounds_last) *rounds_last = rl;
+  return nf * taps + rl;
+}
+
+size_t split_packed_bytes(int o, int c, int taps, int dt) {
+  return (size_t)((o + 15) / 16) * split_rounds(c, taps, nullptr, nullptr, nullptr) * (dt == CPRUNE_F32 ? 3072 : 1024);
+}
+
+int launch_pack_split(const void* w, int o, int c, int taps, int khwc, int dt, void* y, hipStream_t s) {
+  int nfull, groups_last, rounds_last;
+  const int rtot = split_rounds(c, taps, &nfull, &groups_last, &rounds_last);
+  const long total = (long)((o + 15) / 16) * rtot * 64;
+  CPRUNE_BY_DTYPE(dt, hipLaunchKernelGGL(pack_split_kernel<T>, blocks_for(total), dim3(256), 0, s, (const T*)w, (uint4*)y,
+                                         (int)total, o, c, taps, khwc, nfull, groups_last, rtot));
   CPRUNE_LAUNCH_CHECK();
   return CPRUNE_OK;
 }
