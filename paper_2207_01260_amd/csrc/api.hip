@@ -63,31 +63,45 @@ static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay) {
   return lay.nhwc || 2.0 * (double)d.n * ho * wo * d.c_out * d.c_in * d.kh * d.kw >= 6e8;
 }
 
-// Untimed fallback: the tile whose wavefronts reuse their LDS operands most (blocks
-// per operand fetched), discounted by the pixel columns a ragged last tile wastes;
-// work cut into equal runs for 512 resident work-groups, which needs no knowledge
-// of how the tile count divides the chip.  Used only for shapes never timed.
 // Windows of more than one tap go to the split kernel where it pays; its own estimate says which variant.
-int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay, bool split) {
+int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay, size_t ws_limit) {
   const long ho = conv_out_dim(d.h, d.kh, d.stride, d.pad), wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
   const long P = (long)d.n * ho * wo, O = d.c_out;
-  if (split && d.groups == 1 && d.kh * d.kw > 1 && split_pays(d, lay)) {
+  if (d.groups == 1 && d.kh * d.kw > 1 && split_pays(d, lay)) {
     const int v = best_split_variant(d, lay);
-    if (v >= 0) return v;
+    if (v >= 0 && conv_ws_bytes(d, v, lay) <= ws_limit) return v;
   }
+  // Everything else: the general kernel's tiles, whole or cut into equal runs, by estimated clocks.  A unit holds `occ`
+  // work-groups (local memory); a slab costs a group its matrix instructions times the groups it shares them with, and
+  // no less than the round trip of its operands; groups come in rounds; cut tiles pay a second launch and their pieces.
+  // (Cutting always, with the largest reuse per operand, gave a layer with a short reduction a dozen groups in all:
+  // 13 -> 36 filters, 1x1 at 49x49, batch 4, bf16 57 us, now 16 us; timed choice 15.7.)
+  const long K = (long)(lay.nhwc ? lay.cp_in : d.c_in) * d.kh * d.kw;
+  const bool f32 = d.dtype == CPRUNE_F32;
   double best = -1.0;
   int best_v = 0;
   for (int v = 0; v < num_variants(); ++v) {
     const TileVariant& tv = variant(v);
-    if (tv.sched != 2 || !variant_supports(d, v, lay)) continue;
-    const long mt = tv.tile_m(), pt = tv.tile_p();
-    const long tm = (O + mt - 1) / mt, tp = (P + pt - 1) / pt;
-    double rows16 = std::ceil((double)O / tm / 16.0 / tv.wm);
-    if (rows16 > tv.mb) rows16 = tv.mb;
-    const double reuse = rows16 * tv.nb / (rows16 + tv.nb);
-    const double fill = (double)P / (double)(tp * pt);
-    const double score = reuse * fill;
-    if (score > best) { best = score; best_v = v; }
+    if (!(tv.sched == 0 || tv.sched == 2 || tv.sched == 4) || !variant_supports(d, v, lay)) continue;
+    const long mt = tv.tile_m(), pt = tv.tile_p(), tiles = ((O + mt - 1) / mt) * ((P + pt - 1) / pt);
+    const double slabs = std::ceil((double)K / ((f32 ? 16 : 32) * tv.kq));
+    double groups = (double)tiles, run = slabs;
+    if (tv.sched > 0) {
+      groups = std::min(256.0 * tv.sched, std::ceil(tiles * slabs / 4.0));
+      run = std::ceil(tiles * slabs / groups);
+      groups = std::ceil(tiles * slabs / run);
+    }
+    const bool cut = std::fmod(run, slabs) != 0.0;
+    const double rows = std::min((double)tv.mb, std::ceil((double)O / 16.0 / tv.wm));   // filter blocks that exist
+    const double mfma = rows * tv.nb * tv.kq * (f32 ? 128.0 : 16.0);
+    const double bytes = (double)(mt + pt) * 64 * tv.kq;
+    const double occ = std::max(1.0, std::min(4.0, std::floor(160.0 * 1024 / (2.0 * (mt + pt) * (64 * tv.kq + 16)))));
+    const double held = std::min(occ, std::ceil(groups / 256.0));
+    const double slab = std::max(900.0 + bytes / 16.0, held * std::max(mfma, bytes / 16.0));
+    const double store = 2000.0 + (double)(mt * pt) / 8.0;
+    const double cost = std::ceil(groups / (256.0 * occ)) * (run * slab + std::ceil(run / slabs) * store) +
+                        (cut ? 9000.0 + 120.0 * slabs / run : 0.0);
+    if ((best < 0.0 || cost < best) && (!cut || conv_ws_bytes(d, v, lay) <= ws_limit)) { best = cost; best_v = v; }
   }
   if (best < 0.0)  // nothing among the cut-run variants (a fused pool needs a patch kernel): first that runs
     for (int v = 0; v < num_variants(); ++v)
@@ -115,9 +129,11 @@ static int conv_dispatch(const cprune_conv_desc& d, const void* x, const void* w
     return lay.nhwc ? launch_depthwise_nhwc(d, lay.cp_in, x, w, bias, residual, y, s)
                     : launch_conv_depthwise(d, x, w, bias, residual, y, s);
   if (v < 0) {
-    v = cached_or_heuristic_variant(d, nullptr, lay);
-    // the split kernel packs its weights into the caller's scratch: a caller without room gets a kernel that packs none
-    if (variant(v).split && conv_ws_bytes(d, v, lay) > (ws ? ws_bytes : 0)) v = heuristic_variant(d, lay, false);
+    // a timed choice needs the scratch it was timed with, except that a caller without room for packed weights gets a
+    // kernel that packs none; an untimed choice takes what scratch there is
+    const size_t have = ws ? ws_bytes : 0;
+    v = timed_variant(d, lay);
+    if (v < 0 || (variant(v).split && conv_ws_bytes(d, v, lay) > have)) v = heuristic_variant(d, lay, have);
   }
   if (!variant_supports(d, v, lay)) return CPRUNE_ERR_UNSUPPORTED;
   const size_t need = conv_ws_bytes(d, v, lay);

@@ -82,8 +82,8 @@ inline int round_up_vec(int c, int dt) { const int v = dt == CPRUNE_F32 ? 4 : 8;
 int validate_conv_desc(const cprune_conv_desc* d);
 bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay = ConvLayout());
 size_t conv_ws_bytes(const cprune_conv_desc& d, int v, const ConvLayout& lay = ConvLayout());
-// split: whether a variant that needs packed weights in scratch may be chosen
-int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay = ConvLayout(), bool split = true);
+// ws_limit: scratch bytes the chosen variant may need
+int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay = ConvLayout(), size_t ws_limit = SIZE_MAX);
 int best_split_variant(const cprune_conv_desc& d, const ConvLayout& lay);   // by estimate; -1 if none runs the layer
 int cached_or_heuristic_variant(const cprune_conv_desc& d, bool* timed, const ConvLayout& lay = ConvLayout());
 void remember_variant(const cprune_conv_desc& d, int v, const ConvLayout& lay = ConvLayout());

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wk = wave / (WM * WN), wmn = wave % (WM * WN);
-  const int wm = wmn / WN, wn = wmn % WN;
+  const int wn = wmn % WN;
   const int r = lane & 15, g4 = lane >> 4;
 
   // tile decode; each XCD (own L2) gets one contiguous stretch of the tile order
@@ -126,6 +126,9 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
     const int q = G >> 3, rem = G & 7;
     tile = xcd * q + (xcd < rem ? xcd : rem) + local;
   }
+  // (which wavefronts get a tile's first blocks rotates from work-group to work-group, so that where the blocks do not
+  // divide evenly the longer and the shorter shares meet on every SIMD of a unit)
+  const int wm = (wmn / WN + (tile >> 1)) % WM;
   const int tiles_s = a.tiles_n * a.tiles_y * a.tiles_x;
   const int q_s = (int)fast_div((unsigned)tile, a.magic_s), q_m = (int)fast_div((unsigned)tile, a.magic_m);
   const int tile_m = a.m_major ? q_s : tile - q_m * a.tiles_m;
@@ -508,19 +511,18 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
   X(0, 2, 2, 1, 2, 4, 4)  \
   X(1, 2, 2, 1, 2, 2, 2)  \
   X(2, 4, 1, 1, 1, 4, 2)  \
-  X(3, 4, 1, 1, 2, 4, 2)  \
-  X(4, 2, 2, 1, 3, 4, 4)  \
-  X(5, 1, 4, 1, 3, 2, 4)  \
-  X(6, 1, 4, 1, 2, 2, 4)  \
-  X(7, 2, 1, 2, 1, 4, 2)  \
-  X(8, 1, 1, 4, 2, 4, 2)  \
-  X(9, 1, 1, 4, 2, 2, 2)  \
-  X(10, 1, 1, 4, 1, 2, 2) \
-  X(11, 2, 2, 1, 1, 2, 5) \
-  X(12, 2, 2, 1, 2, 2, 5) \
-  X(13, 1, 4, 1, 2, 4, 6)
+  X(3, 2, 2, 1, 3, 4, 4)  \
+  X(4, 1, 4, 1, 3, 2, 4)  \
+  X(5, 1, 4, 1, 2, 2, 4)  \
+  X(6, 2, 1, 2, 1, 4, 2)  \
+  X(7, 1, 1, 4, 2, 4, 2)  \
+  X(8, 1, 1, 4, 2, 2, 2)  \
+  X(9, 1, 1, 4, 1, 2, 2) \
+  X(10, 2, 2, 1, 1, 2, 5) \
+  X(11, 2, 2, 1, 2, 2, 5) \
+  X(12, 1, 4, 1, 2, 4, 6)
 
-constexpr int kNumSplit = 14;
+constexpr int kNumSplit = 13;
 
 template <typename T, bool NCHW>
 inline int launch_split(int id, dim3 grid, size_t lds, hipStream_t s, const SplitArgs& a) {
