@@ -7,6 +7,7 @@
 #include <stddef.h>
 
 #include "cprune.h"
+#include "split_index.hpp"
 
 namespace cprune {
 
@@ -120,9 +121,7 @@ size_t rows_packed_bytes(int rows, int k, int dt);
 int launch_repack_rows(const void* w, int rows, int k, int dt, void* y, hipStream_t s);
 // weights [o][taps][c] (khwc = 1) or [o][c][taps] -> the operand order of the split kernel: [filter tile of 16][round]
 // [part][lane][16 bytes]; an fp32 weight as three bf16 parts, 16-bit weights as they are; zeros past the last filter
-// and channel.  split_rounds: rounds of the whole reduction (full chunks of 32 channels take one per tap, the last
-// chunk as many as its 8-channel groups need); split_packed_bytes: size of the packed weights
-int split_rounds(int c, int taps, int* nfull, int* groups_last, int* rounds_last);
+// and channel.  split_packed_bytes: size of the packed weights
 size_t split_packed_bytes(int o, int c, int taps, int dt);
 int launch_pack_split(const void* w, int o, int c, int taps, int khwc, int dt, void* y, hipStream_t s);
 int launch_repack_map2x2(const void* w, const float* bias, int o, int c, int cp_in, int cp_out,

@@ -32,6 +32,7 @@
 #pragma once
 #include <atomic>
 #include "conv_nhwc_kernel.hpp"
+#include "split_index.hpp"
 
 // every lambda of the kernel: one that is not inlined takes the arrays it captures into scratch memory
 #define CPRUNE_INLINE __attribute__((always_inline))
@@ -138,20 +139,18 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
   const int tx0 = (rest - q_x * a.tiles_x) * a.tw;
   const int ty0 = (q_x - q_y * a.tiles_y) * a.th;
   const int n0 = q_y * a.ni;
-  // 16-filter blocks are dealt out evenly, first to the tiles and then to a tile's wavefronts: a layer costs what its
-  // blocks cost, not what its tiles would hold
-  const int tblk = a.blk_base + (tile_m < a.blk_rem ? 1 : 0);                        // blocks of this tile
-  const int blk0 = tile_m * a.blk_base + min(tile_m, a.blk_rem) + wm * (tblk / WM) + min(wm, tblk % WM);
-  const int nblk = tblk / WM + (wm < tblk % WM ? 1 : 0);                             // blocks of this wavefront
-  const int o0 = blk0 * 16;                                                        // its first filter
+  const SplitShare share = split_share(tile_m, wm, WM, a.blk_base, a.blk_rem);
+  const int nblk = share.count;           // 16-filter blocks of this wavefront
+  const int o0 = share.first * 16;        // its first filter
 
   const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, a.x_bytes);
   const __amdgpu_buffer_rsrc_t wr = make_rsrc(a.w, a.w_bytes);
 
   // ---- weights: one round of this wavefront's filter blocks ----
   const unsigned a_blk = (unsigned)a.rtot * (P * 1024u);
-  const unsigned a_base = (unsigned)blk0 * a_blk;
-  auto load_weights = [&](auto mbc, int rg, uint4 (&f)[MB][P]) CPRUNE_INLINE {
+  const unsigned a_base = (unsigned)split_weight_block(share.first, a.blk_base * a.tiles_m + a.blk_rem) * a_blk;
+  auto load_weights = [&](auto mbc, int round, uint4 (&f)[MB][P]) CPRUNE_INLINE {
+    const int rg = split_weight_round(round, a.rtot);
 #pragma unroll
     for (int i = 0; i < decltype(mbc)::value; ++i)
 #pragma unroll
@@ -197,7 +196,7 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const unsigned voff = b_off[j] | ((unsigned)(c0 + b_ch[j] + e >= a.C) << 31);
-          const uint32_t v = Elem<T>::load(xr, voff, (unsigned)((c0 + e) * hw) * ES);
+          const uint32_t v = Elem<T>::load(xr, voff, (unsigned)(min(c0 + e, a.C - 1) * hw) * ES);
           if constexpr (ES == 4) breg[j][e] = v;
           else if (e & 1) breg[j][e >> 1] |= v << 16;
           else breg[j][e >> 1] = v;
@@ -380,8 +379,7 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
       const int R = full ? a.taps : a.rounds_last;
       const int* const tb = tab + (full ? 0 : a.taps * 4) + g4;
       const int rg0 = c * a.taps;
-      // (round rg + WK of this chunk, or the first of the next one; past the end the values are never used)
-      auto next_rg = [&](int q) CPRUNE_INLINE { return q + WK < R ? rg0 + q + WK : rg0 + a.taps + wk; };
+      auto next_rg = [&](int q) CPRUNE_INLINE { return split_next_round(q, wk, WK, R, rg0, a.taps); };
       if (wk >= R) {
         if (c + 1 < nchunk) gload(c + 1);
         continue;
@@ -421,8 +419,8 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
     }
     if constexpr (P == 3) add_small(mbc, NSET - 1);
   };
-  // compiled once per block count, as the other kernels' main loops (a wavefront without a block runs the shortest one,
-  // on weights past the end of their buffer, which read as zeros, and stores nothing)
+  // compiled once per block count, as the other kernels' main loops (a wavefront without a block runs the shortest one
+  // and stores nothing)
   if (MB >= 3 && nblk >= 3) main_loop(std::integral_constant<int, MB >= 3 ? 3 : 1>{});
   else if (MB >= 2 && nblk >= 2) main_loop(std::integral_constant<int, MB >= 2 ? 2 : 1>{});
   else main_loop(std::integral_constant<int, 1>{});
@@ -504,25 +502,6 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
     }
   }
 }
-
-// Variants: id, wavefronts along filters / pixels / rounds, 16-filter and 16-pixel blocks per wavefront, staging
-// items per thread (what patch the pixel block may have: at most 64 * nib pixels)
-#define CPRUNE_SPLIT_LIST(X) \
-  X(0, 2, 2, 1, 2, 4, 4)  \
-  X(1, 2, 2, 1, 2, 2, 2)  \
-  X(2, 4, 1, 1, 1, 4, 2)  \
-  X(3, 2, 2, 1, 3, 4, 4)  \
-  X(4, 1, 4, 1, 3, 2, 4)  \
-  X(5, 1, 4, 1, 2, 2, 4)  \
-  X(6, 2, 1, 2, 1, 4, 2)  \
-  X(7, 1, 1, 4, 2, 4, 2)  \
-  X(8, 1, 1, 4, 2, 2, 2)  \
-  X(9, 1, 1, 4, 1, 2, 2) \
-  X(10, 2, 2, 1, 1, 2, 5) \
-  X(11, 2, 2, 1, 2, 2, 5) \
-  X(12, 1, 4, 1, 2, 4, 6)
-
-constexpr int kNumSplit = 13;
 
 template <typename T, bool NCHW>
 inline int launch_split(int id, dim3 grid, size_t lds, hipStream_t s, const SplitArgs& a) {

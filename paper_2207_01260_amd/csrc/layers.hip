@@ -773,14 +773,6 @@ int launch_repack_rows(const void* w, int rows, int k, int dt, void* y, hipStrea
   return CPRUNE_OK;
 }
 
-int split_rounds(int c, int taps, int* nfull, int* groups_last, int* rounds_last) {
-  const int groups = (c + 7) / 8, nf = groups / 4, gl = groups % 4, rl = (taps * gl + 3) / 4;
-  if (nfull) *nfull = nf;
-  if (groups_last) *groups_last = gl;
-  if (rounds_last) *rounds_last = rl;
-  return nf * taps + rl;
-}
-
 size_t split_packed_bytes(int o, int c, int taps, int dt) {
   return (size_t)((o + 15) / 16) * split_rounds(c, taps, nullptr, nullptr, nullptr) * (dt == CPRUNE_F32 ? 3072 : 1024);
 }
