@@ -166,6 +166,7 @@ int launch_split_conv(const cprune_conv_desc& d, const TileVariant& tv, const Co
     if (rc != CPRUNE_OK) return rc;
     a.w = ws;
   }
+  a.w_raw = w; a.w_raw_bytes = (unsigned)((size_t)d.c_out * a.C * a.taps * es);
   a.x = x; a.bias = bias; a.res = residual; a.y = y;
   a.N = d.n; a.H = d.h; a.W = d.w; a.O = d.c_out;
   a.Ho = conv_out_dim(d.h, d.kh, d.stride, d.pad); a.Wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);

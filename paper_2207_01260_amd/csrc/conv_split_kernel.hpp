@@ -1,14 +1,15 @@
 // Dense convolution, any window up to 7x7 and stride up to 2, on the 16-bit matrix cores for fp32 data too.
 //
-// v_mfma_f32_16x16x4_f32 multiplies at 157 TFLOP/s, v_mfma_f32_16x16x32_bf16 at 2.5 PFLOP/s.  An fp32 number is
-// exactly the sum of three bf16 numbers (its 24 significant bits cut into three runs of eight), so an fp32 product is
-// the sum of nine bf16 products, each exact in fp32; the three smallest (2^-24 of the product and below) are left out
-// and the six others accumulated in fp32: 2.7 times the fp32 instruction's rate, at an error no larger (that one
-// rounds its sum eight times per 32 terms, this one twice).  Weights are cut and packed once (launch_pack_split),
-// activations while they are staged into LDS (some six vector operations per element, against 9 x 6 multiplies per
-// filter).  Activations are cut by rounding to nearest, so that what is left out has no sign of its own and does not
-// add up over the layers of a network; weights by truncation, so that their parts have one sign and an infinite
-// activation gives the infinity the fp32 product gives (see pack_split_kernel for parts that are zero).
+// v_mfma_f32_16x16x4_f32 multiplies at 157 TFLOP/s, v_mfma_f32_16x16x32_bf16 at 2.5 PFLOP/s.  An fp32 number of ordinary
+// size is exactly the sum of three bf16 numbers (its 24 significant bits cut into three runs of eight), so an fp32 product
+// is the sum of nine bf16 products, each exact in fp32; the three smallest are left out and the six others accumulated in
+// fp32: 2.7 times the fp32 instruction's rate, at an error no larger (that one rounds its sum eight times per 32 terms,
+// this one twice).  Weights are cut and packed once (launch_pack_split), activations while they are staged into LDS
+// (some six vector operations per element, against 9 x 6 multiplies per filter).  Activations are cut by rounding to
+// nearest, so that what is left out has no sign of its own and does not add up over the layers of a network.
+// What three bf16 numbers cannot hold (infinities, numbers that round to one, numbers below 2^-110 whose last part falls
+// off the end of the range) shows in the sums: such a sum is not finite, or too small for what was lost to be below its own
+// last place.  A wavefront that finds one multiplies its block again with the fp32 instruction (`again` below).
 // 16-bit data runs the same kernel with one part per number.
 //
 // A work-group owns MT = WM * MB * 16 filters and a block of th x tw pixels of ni images, at most PT = WN * NB * 16
@@ -42,6 +43,7 @@ namespace cprune {
 struct SplitArgs {
   const void* x;        // NCHW or channels-last
   const void* w;        // packed by launch_pack_split
+  const void* w_raw;    // fp32: the weights as they are, [o][c][taps] or channels-last [o][taps][C]
   const float* bias;
   const void* res;
   void* y;              // the layout of x
@@ -53,7 +55,7 @@ struct SplitArgs {
   int blk_base, blk_rem;       // 16-filter blocks per filter tile: blk_base, and one more in the first blk_rem
   int nfull, rounds_last, rtot;  // chunks of 32 channels; rounds of the last, partial one (0: none); rounds in all
   int groups_last;               // 8-channel groups of the last chunk
-  unsigned x_bytes, w_bytes;
+  unsigned x_bytes, w_bytes, w_raw_bytes;
   unsigned magic_s, magic_m, magic_x, magic_y;      // tile decode (as PatchArgs)
   unsigned magic_pp, magic_pw;                      // patch pixel -> (image, row, column)
   unsigned magic_thw, magic_tw;                     // output pixel of the block -> (image, row, column); pooled: windows
@@ -79,18 +81,6 @@ __device__ __forceinline__ void split3(uint32_t u0, uint32_t u1, uint32_t& h, ui
   const float s0 = r0 - __uint_as_float(m << 16), s1 = r1 - __uint_as_float(m & 0xffff0000u);
   l = __builtin_bit_cast(uint32_t, __builtin_convertvector((float2_t){s0, s1}, bf16x2_t));
 }
-
-// The same by truncation, for numbers whose first part would round to infinity, and for infinities: no remainder
-__device__ __forceinline__ void split3_large(uint32_t u, uint32_t& h, uint32_t& m, uint32_t& l) {
-  h = u & 0xffff0000u;
-  float r = __uint_as_float(u) - __uint_as_float(h);
-  r = (u & 0x7fffffffu) == 0x7f800000u ? 0.0f : r;
-  m = __float_as_uint(r) & 0xffff0000u;
-  l = __float_as_uint(r - __uint_as_float(m));
-}
-
-// top halves of two dwords, the first one low
-__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
 template <typename T>
 __device__ __forceinline__ float4_t mfma_split(const uint4& a, const uint4& b, const float4_t& c) {
@@ -218,35 +208,16 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
 #pragma unroll
       for (int j = 0; j < NIB; ++j) *(uint4*)(smem + b_lds[j]) = make_uint4(breg[j][0], breg[j][1], breg[j][2], breg[j][3]);
     } else {
-      auto store = [&](auto large) CPRUNE_INLINE {
 #pragma unroll
-        for (int j = 0; j < NIB; ++j) {
-          uint4* const dst = (uint4*)(smem + b_lds[j]);
-          uint32_t h[4], m[4], l[4];
+      for (int j = 0; j < NIB; ++j) {
+        uint4* const dst = (uint4*)(smem + b_lds[j]);
+        uint32_t h[4], m[4], l[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if constexpr (decltype(large)::value) {
-              uint32_t p0[3], p1[3];
-              split3_large(breg[j][2 * e], p0[0], p0[1], p0[2]);
-              split3_large(breg[j][2 * e + 1], p1[0], p1[1], p1[2]);
-              h[e] = pack_hi(p0[0], p1[0]); m[e] = pack_hi(p0[1], p1[1]); l[e] = pack_hi(p0[2], p1[2]);
-            } else {
-              split3(breg[j][2 * e], breg[j][2 * e + 1], h[e], m[e], l[e]);
-            }
-          }
-          dst[0] = make_uint4(h[0], h[1], h[2], h[3]);
-          dst[1] = make_uint4(m[0], m[1], m[2], m[3]);
-          dst[2] = make_uint4(l[0], l[1], l[2], l[3]);
-        }
-      };
-      float big = 0.0f;   // numbers near the end of the range are looked for once per chunk
-#pragma unroll
-      for (int j = 0; j < NIB; ++j)
-#pragma unroll
-        for (int e = 0; e < 8; e += 2)
-          big = fmaxf(fmaxf(big, fabsf(__uint_as_float(breg[j][e]))), fabsf(__uint_as_float(breg[j][e + 1])));
-      if (__builtin_expect(big >= 0x1.fep127f, 0)) store(std::true_type{});
-      else store(std::false_type{});
+        for (int e = 0; e < 4; ++e) split3(breg[j][2 * e], breg[j][2 * e + 1], h[e], m[e], l[e]);
+        dst[0] = make_uint4(h[0], h[1], h[2], h[3]);
+        dst[1] = make_uint4(m[0], m[1], m[2], m[3]);
+        dst[2] = make_uint4(l[0], l[1], l[2], l[3]);
+      }
     }
   };
   gload(0);
@@ -419,6 +390,47 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
     }
     if constexpr (P == 3) add_small(mbc, NSET - 1);
   };
+  // The wavefront's whole reduction once more, four terms at a time on the fp32 instruction, operands straight from
+  // memory: slow (some ten times the main loop), and for data that three parts do not hold only.
+  auto again = [&]() CPRUNE_INLINE {
+    const __amdgpu_buffer_rsrc_t ww = make_rsrc(a.w_raw, a.w_raw_bytes);
+    const unsigned step = NCHW ? (unsigned)hw * 4u : 4u, row = (unsigned)(a.taps * a.C) * 4u;
+    const unsigned wtap = NCHW ? 4u : (unsigned)a.C * 4u, wchan = NCHW ? (unsigned)a.taps * 4u : 4u;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[i][j] = (float4_t){0.f, 0.f, 0.f, 0.f};
+    for (int tap = 0; tap < a.taps; ++tap) {
+      const int u = tap / a.kw;
+      unsigned px[NB];      // this lane's pixels under the tap, channel 0
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        int img, ty, tx;
+        pixel_of(j, img, ty, tx);
+        const int n = n0 + img, iy = (ty0 + ty) * a.stride - a.pad + u, ix = (tx0 + tx) * a.stride - a.pad + tap - u * a.kw;
+        const bool inside = img < a.ni && n < a.N && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+        const int pix = NCHW ? n * a.C * hw + iy * a.W + ix : ((n * a.H + iy) * a.W + ix) * a.C;
+        px[j] = inside ? (unsigned)pix * 4u : kOutOfRange;
+      }
+      for (int c0 = 0; c0 < a.C; c0 += 4) {
+        const int c = c0 + g4;
+        const bool real = c < a.C;
+        float wv[MB], xv[NB];
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+          const int o = o0 + i * 16 + r;
+          const bool have = real && i < nblk && o < a.O;
+          wv[i] = __uint_as_float(Elem<float>::load(ww, have ? o * row + tap * wtap + c * wchan : kOutOfRange, 0));
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j) xv[j] = __uint_as_float(Elem<float>::load(xr, real ? px[j] + c * step : kOutOfRange, 0));
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i], xv[j], acc[i][j], 0, 0, 0);
+      }
+    }
+  };
   // compiled once per block count, as the other kernels' main loops (a wavefront without a block runs the shortest one
   // and stores nothing)
   if (MB >= 3 && nblk >= 3) main_loop(std::integral_constant<int, MB >= 3 ? 3 : 1>{});
@@ -445,6 +457,27 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
         for (int j = 0; j < NB; ++j) acc[i][j] += red[(k - 1) * STEP + (i * NB + j) * 64];
   }
   if (nblk == 0) return;
+
+  if constexpr (P == 3) {
+    // Every infinity and every number that rounds to one makes a sum infinite or NaN (its first part is infinite, the
+    // second infinite of the other sign or NaN).  A number under 2^-110 loses at most 2^-134 (half of bf16's last bit; the
+    // instruction keeps denormal operands: 1e-36 keeps 14 bits), times the other operand in its product: below half the last place
+    // of sums from 2^-50 up while the terms of a sum times that operand stay under 2^59.  (Sums of ordinary numbers that
+    // come out smaller, but not zero, are one in 10^15.)
+    constexpr uint32_t kInf = 0x7f800000u, kSmall = (127u - 50u) << 23;
+    uint32_t top = 0, low = ~0u;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const uint32_t mag = __float_as_uint(acc[i][j][v]) & 0x7fffffffu;
+          top = max(top, mag);
+          low = min(low, mag - 1);      // (zero goes to the other end)
+        }
+    if (__any(top >= kInf || low < kSmall - 1)) again();
+  }
 
   // ---- epilogue: a lane holds filters o .. o + 3 of its pixel ----
   ConvArgs e;

@@ -448,9 +448,7 @@ __global__ __launch_bounds__(256) void repack_rows_kernel(const T* __restrict__ 
 
 // Weights -> the operand order of the split kernel: [filter tile of 16][round][part][lane = quarter * 16 + filter]
 // [8 channels].  A round holds four (tap, 8-channel group) units, one per quarter.  An fp32 weight becomes three bf16
-// parts of its own sign, by truncation (conv_split_kernel.hpp says why).  A part that would be zero is the smallest normal
-// number instead, where the weight itself is not tiny: an infinite input times that part is then an infinity of the
-// right sign, where zero would make it a NaN; to a finite input it adds less than 2^-26 of the product.
+// parts by truncation.
 template <typename T>
 __global__ __launch_bounds__(256) void pack_split_kernel(const T* __restrict__ w, uint4* __restrict__ y, int total,
                                                          int o_count, int c_count, int taps, int khwc, int nfull,
@@ -480,14 +478,10 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const T* __restrict__ w
     if constexpr (P == 1) {
       part[0][e >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, v) << (16 * (e & 1));
     } else {
-      const uint32_t bits = __float_as_uint(v), mag = bits & 0x7fffffffu;
-      uint32_t b = bits;
+      uint32_t b = __float_as_uint(v);
       for (int p = 0; p < 3; ++p) {
-        uint32_t hi = b & 0xffff0000u;
-        if (p > 0 && (hi << 1) == 0 && mag >= (27u << 23) && mag <= 0x7f7fffffu) hi = (bits & 0x80000000u) | 0x00800000u;
-        const float rest = __uint_as_float(b) - __uint_as_float(b & 0xffff0000u);
-        b = mag == 0x7f800000u ? 0u : __float_as_uint(rest);
-        part[p][e >> 1] |= (hi >> 16) << (16 * (e & 1));
+        part[p][e >> 1] |= (b >> 16) << (16 * (e & 1));
+        b = __float_as_uint(__uint_as_float(b) - __uint_as_float(b & 0xffff0000u));
       }
     }
   }
