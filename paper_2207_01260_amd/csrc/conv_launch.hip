@@ -25,6 +25,7 @@ constexpr int kNumScheds = sizeof(kScheds) / sizeof(kScheds[0]);
 constexpr int kMinUnitsPerGroup = 4;
 constexpr long kMaxKsplitGroups = 8192;
 constexpr int kMaxWaveMap = 32;
+constexpr long kSplitMinTerms = 16;
 
 unsigned magic_for(unsigned d) {
   if (d <= 1) return 0;
@@ -120,6 +121,8 @@ bool split_plan(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayo
 bool split_supports(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay) {
   if (lay.nhwc ? !(d.dtype == CPRUNE_F32 && lay.w_split) : lay.nhwc_out != 0) return false;
   if (lay.pool == 2 || (lay.pool && ((d.h | d.w) & 1 || d.stride != 1)) || d.stride > 2) return false;
+  // fp32 sums of a few terms are less exact in parts than on the fp32 instruction (conv_split_kernel.hpp)
+  if (d.dtype == CPRUNE_F32 && (long)d.c_in * d.kh * d.kw < kSplitMinTerms) return false;
   const int ho = conv_out_dim(d.h, d.kh, d.stride, d.pad), wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
   if (!lay.nhwc && (long)ho * wo < 16) return false;   // a map of a few pixels is a matrix product: the general kernel
   if (split_packed_bytes(d.c_out, lay.nhwc ? lay.cp_in : d.c_in, d.kh * d.kw, d.dtype) >= ((size_t)1 << 31)) return false;

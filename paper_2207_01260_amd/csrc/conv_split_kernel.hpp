@@ -3,10 +3,13 @@
 // v_mfma_f32_16x16x4_f32 multiplies at 157 TFLOP/s, v_mfma_f32_16x16x32_bf16 at 2.5 PFLOP/s.  An fp32 number of ordinary
 // size is exactly the sum of three bf16 numbers (its 24 significant bits cut into three runs of eight), so an fp32 product
 // is the sum of nine bf16 products, each exact in fp32; the three smallest are left out and the six others accumulated in
-// fp32: 2.7 times the fp32 instruction's rate, at an error no larger (that one rounds its sum eight times per 32 terms,
-// this one twice).  Weights are cut and packed once (launch_pack_split), activations while they are staged into LDS
-// (some six vector operations per element, against 9 x 6 multiplies per filter).  Activations are cut by rounding to
-// nearest, so that what is left out has no sign of its own and does not add up over the layers of a network.
+// fp32, at 2.7 times the fp32 instruction's rate.  Weights are cut and packed once (launch_pack_split), activations while
+// they are staged into LDS (some six vector operations per element, against 9 x 6 multiplies per filter).  Both are cut
+// by rounding to nearest: a second part is then at most 2^-8 of the number and a third 2^-16, what is left out at most 2^-23
+// of a product (5.7e-9 in the 2-norm; by truncation 1.8e-8), and it has no sign of its own, so it does not add up over
+// the layers of a network.  A sum is rounded twice per 32 terms, by the fp32 instruction at every term: at 16 terms the
+// error is 3.3e-8 against 7.5e-8, at 24 3.7e-8 against 9.0e-8, at 2304 0.2 to 0.4 of it; a single product is 2.6e-8 off where
+// one rounding is 2.5e-8, so sums of fewer than 16 terms stay on the fp32 instruction (split_supports).
 // What three bf16 numbers cannot hold (infinities, numbers that round to one, numbers below 2^-110 whose last part falls
 // off the end of the range) shows in the sums: such a sum is not finite, or too small for what was lost to be below its own
 // last place.  A wavefront that finds one multiplies its block again with the fp32 instruction (`again` below).
@@ -26,7 +29,7 @@
 // Measured, fp32 channels-last, best variant against the best fp32-instruction kernel: 56 -> 56 at 32x32, batch 64, 42.4
 // -> 25.7 us; 40 -> 64 at 56x56, batch 32, 54.1 -> 34.2 us; 128 -> 85 at 28x28 56.8 -> 35.1 us; 512 -> 411 at 7x7
 // 72.2 -> 53.1 us; 360 -> 360 at 4x4, batch 64, 25.4 -> 26.2 us (the independent-wavefront kernel stays there);
-// stride 2, 128 -> 173 at 28x28, 34.8 -> 25.1 us.  Error against 64 bits 0.3 to 0.6 of that kernel's.  What bounds it:
+// stride 2, 128 -> 173 at 28x28, 34.8 -> 25.1 us.  What bounds it:
 // of the 32 us of 85 -> 128 at 28x28 the matrix pipes need 14; operand reads, weight reads and staging cost 5-8 %
 // each when left out alone; 8 us are launch, first loads and stores, which the two or three work-groups of a unit,
 // started together, do not hide from each other.
@@ -277,7 +280,7 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
     }
   };
   // The five small products of a round are added up among themselves, so that their sum is rounded at its own size, and
-  // meet the running sum once: two roundings of it per 32 terms, where the fp32 instruction makes eight.  They do so
+  // meet the running sum once: two roundings of it per 32 terms, where the fp32 instruction makes 32.  They do so
   // while the next set is multiplied.  The barriers keep consecutive MFMAs on different accumulators: left alone the
   // scheduler issues each block's chain back to back and waits out every result (56 -> 56 filters at 32x32, batch 64:
   // 28.1 us without, 25.7 us with them).
@@ -391,7 +394,8 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
     if constexpr (P == 3) add_small(mbc, NSET - 1);
   };
   // The wavefront's whole reduction once more, four terms at a time on the fp32 instruction, operands straight from
-  // memory: slow (some ten times the main loop), and for data that three parts do not hold only.
+  // memory: for data that three parts do not hold only, because it is slow (every wavefront of 128 -> 83 filters at 56x56, batch
+  // 8: 44 -> 200 us, of 512 -> 411 at 7x7, batch 32: 71 -> 550-630 us).
   auto again = [&]() CPRUNE_INLINE {
     const __amdgpu_buffer_rsrc_t ww = make_rsrc(a.w_raw, a.w_raw_bytes);
     const unsigned step = NCHW ? (unsigned)hw * 4u : 4u, row = (unsigned)(a.taps * a.C) * 4u;

@@ -3,7 +3,7 @@
 // max pooling and global average pooling.  No contraction across channels, so
 // these are plain coalesced kernels: consecutive lanes take consecutive output
 // columns of one (image, channel) plane.
-#include "conv_nhwc_kernel.hpp"
+#include "conv_split_kernel.hpp"
 
 namespace cprune {
 namespace {
@@ -447,8 +447,7 @@ __global__ __launch_bounds__(256) void repack_rows_kernel(const T* __restrict__ 
 }
 
 // Weights -> the operand order of the split kernel: [filter tile of 16][round][part][lane = quarter * 16 + filter]
-// [8 channels].  A round holds four (tap, 8-channel group) units, one per quarter.  An fp32 weight becomes three bf16
-// parts by truncation.
+// [8 channels].  A round holds four (tap, 8-channel group) units, one per quarter.
 template <typename T>
 __global__ __launch_bounds__(256) void pack_split_kernel(const T* __restrict__ w, uint4* __restrict__ y, int total,
                                                          int o_count, int c_count, int taps, int khwc, int nfull,
@@ -464,7 +463,7 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const T* __restrict__ w
   const int u = (rg - chunk * taps) * 4 + (lane >> 4);
   const int ng = full ? 4 : groups_last;
   const int tap = u / ng, c0 = chunk * 32 + (u - tap * ng) * 8;
-  uint32_t part[P][4] = {};
+  uint32_t part[P][4];
   T vals[8];
   const bool row = o < o_count && tap < taps;
   const size_t step = khwc ? 1 : taps;
@@ -473,17 +472,13 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const T* __restrict__ w
 #pragma unroll
   for (int e = 0; e < 8; ++e) vals[e] = src[row && c0 + e < c_count ? e * step : 0];   // (all eight in flight at once)
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const T v = row && c0 + e < c_count ? vals[e] : (T)0.0f;
-    if constexpr (P == 1) {
-      part[0][e >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, v) << (16 * (e & 1));
-    } else {
-      uint32_t b = __float_as_uint(v);
-      for (int p = 0; p < 3; ++p) {
-        part[p][e >> 1] |= (b >> 16) << (16 * (e & 1));
-        b = __float_as_uint(__uint_as_float(b) - __uint_as_float(b & 0xffff0000u));
-      }
-    }
+  for (int e = 0; e < 8; ++e) vals[e] = row && c0 + e < c_count ? vals[e] : (T)0.0f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (P == 1)
+      part[0][e] = (uint32_t)__builtin_bit_cast(uint16_t, vals[2 * e]) | (uint32_t)__builtin_bit_cast(uint16_t, vals[2 * e + 1]) << 16;
+    else
+      split3(__float_as_uint(vals[2 * e]), __float_as_uint(vals[2 * e + 1]), part[0][e], part[1][e], part[2][e]);
   }
 #pragma unroll
   for (int p = 0; p < P; ++p)

@@ -108,3 +108,43 @@ def test_small_numbers_beside_ordinary_ones(layout):
     for v, y in ys.items():
         e = float((y.double()[..., :5, :5] - ref).norm() / ref.norm())
         assert e <= max(1.1 * base, 2.0 ** -24), (v, e, base)
+
+
+@pytest.mark.parametrize("layout", ["boundary", "handle"])
+def test_what_is_left_out_of_a_product(layout):
+    """One term per sum: the rounding of the result (2.53e-8 in the 2-norm over random numbers) and the parts left out (5.7e-9
+    with both operands cut by rounding, 1.8e-8 with one cut by truncation) make 2.6e-8, by truncation 3.1e-8."""
+    cfg = (4, 32, 32, 32, 64, 1, 1)
+    x, w = _data(cfg)
+    x *= torch.nn.functional.one_hot(torch.arange(4 * 32 * 32) % 32, 32).reshape(4, 32, 32, 32).permute(0, 3, 1, 2)
+    ref = torch.nn.functional.conv2d(x.double(), w.double())
+    for v, y in _outputs(cfg, x, w, layout).items():
+        assert float((y.double() - ref).norm() / ref.norm()) < 2.75e-8, v
+
+
+@pytest.mark.parametrize("layout", ["boundary", "handle"])
+@pytest.mark.parametrize("c_in,k", [(2, 3), (16, 1), (17, 1), (24, 1), (3, 3), (4, 3), (32, 1), (1, 5), (40, 1)])
+def test_short_sums(c_in, k, layout):
+    """Sums of 16 to 40 terms: no less exact than on the fp32 instruction."""
+    if layout == "handle" and c_in <= 4:
+        pytest.skip("a handle reads at most four input channels in the caller's layout")
+    cfg = (4, c_in, 28, 28, 64, k, 1)
+    x, w = _data(cfg)
+    ref = torch.nn.functional.conv2d(x.double(), w.double(), None, 1, k // 2)
+    ys = _outputs(cfg, x, w, layout)
+    base = float((ys.pop(None).double() - ref).norm() / ref.norm())
+    for v, y in ys.items():
+        e = float((y.double() - ref).norm() / ref.norm())
+        print(cfg, layout, v, f"{e:.3e} against {base:.3e}", flush=True)
+        assert e <= base, (v, e, base)
+
+
+@pytest.mark.parametrize("c_in,k", [(1, 1), (2, 1), (3, 1), (5, 1), (8, 1), (15, 1), (1, 3)])
+def test_shorter_sums_stay_on_the_fp32_instruction(c_in, k):
+    x, w = _data((1, c_in, 16, 16, 32, k, 1))
+    d = B.conv_desc(x.shape, w.shape, 1, k // 2, 1, B.F32, B.ACT_NONE, False)
+    for v in range(B.cprune_num_tile_variants()):
+        if "conv_split" in B.cprune_tile_variant_name(v, False, B.F32):
+            with pytest.raises(B.CPruneError) as e:
+                B.cprune_conv2d_bn_relu(d, x.cuda(), w.cuda(), None, None, v)
+            assert e.value.status == B.ERR_UNSUPPORTED
