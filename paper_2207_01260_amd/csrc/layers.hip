@@ -270,8 +270,9 @@ __global__ __launch_bounds__(256) void maxpool_nhwc_vec_kernel(const T* __restri
 }
 
 // One 16-byte channel vector x TX neighbouring outputs per thread.  Every load is unconditional (outside the image it is
-// out of the buffer's range and reads as zero): behind branches each would be waited for before the next is issued,
-// and on small maps that chain is the kernel's whole time.  Batch 16, bf16: 5x5 on 374 channels at 14x14 11.5 -> 8.3 us,
+// out of the buffer's range and reads as zero, and so do the weights of a window row outside: a row that is not there
+// adds nothing, whatever its weights): behind branches each would be waited for before the next is issued, and on small
+// maps that chain is the kernel's whole time.  Batch 16, bf16: 5x5 on 374 channels at 14x14 11.5 -> 8.3 us,
 // 3x3 on 854 channels at 7x7 5.6 -> 3.5 us.
 template <typename T, int K, int S, int TX>
 __global__ __launch_bounds__(256) void depthwise_nhwc_vec_kernel(const T* __restrict__ x, unsigned x_bytes, const T* __restrict__ w,
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(256) void depthwise_nhwc_vec_kernel(const T* __rest
   const int n = (int)(r / (unsigned)ho);
   const int c0 = (int)cv * V;
 
-  const __amdgpu_buffer_rsrc_t xr = make_rsrc(x, x_bytes);
+  const __amdgpu_buffer_rsrc_t xr = make_rsrc(x, x_bytes), wr = make_rsrc(w, (unsigned)(K * K * cp) * ES);
   float4_t bv[V / 4];   // requested first: at the end they would be waited for in full
 #pragma unroll
   for (int i = 0; i < V / 4; ++i) bv[i] = load_bias4(bias, c_real, c0 + 4 * i);
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(256) void depthwise_nhwc_vec_kernel(const T* __rest
 #pragma unroll
     for (int j = 0; j < NIN; ++j) raw[j] = load_b128(xr, (col[j] | out) + row, 0);
 #pragma unroll
-    for (int v = 0; v < K; ++v) wraw[v] = *reinterpret_cast<const uint4*>(w + (size_t)(u * K + v) * cp + c0);
+    for (int v = 0; v < K; ++v) wraw[v] = load_b128(wr, (unsigned)((u * K + v) * cp + c0) * ES | out, 0);
     float wk[K][V];
 #pragma unroll
     for (int v = 0; v < K; ++v) unpack16<T, V>(wraw[v], wk[v]);

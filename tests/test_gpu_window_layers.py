@@ -39,3 +39,32 @@ def test_depthwise_and_pools(orc, cfg):
         check(np.asarray(got.float().cpu()), acts[i], dtype, f"{cfg} {name}")
     check(out.float().cpu().numpy(), acts[-1], dtype, f"{cfg} fc")
     handle.close()
+
+
+@pytest.mark.parametrize("cfg", [
+    # channels, map height, width, window, batch, dtype: one, two and four outputs per thread
+    (20, 9, 8, 3, 2, B.F32), (400, 29, 31, 3, 8, B.F32), (96, 90, 90, 3, 12, B.F16), (24, 12, 12, 5, 1, B.BF16),
+    (520, 28, 28, 5, 8, B.BF16), (160, 64, 64, 5, 12, B.F16),
+])
+def test_infinite_weight_of_a_row_outside(cfg):
+    """A window row outside the image adds nothing to a depthwise sum, even if its weight is infinite."""
+    c, h, w, k, batch, dtype = cfg
+    td = B.TORCH_DTYPE[dtype]
+    gen = torch.Generator().manual_seed(c)
+    net = synth.NetSpec("rows", 8, h, w)
+    a = net.add(synth.Layer("conv", -1, 8, c, k=1, stride=1, pad=0, act=synth.ACT_NONE, name="a"))
+    net.add(synth.Layer("conv", a, c, c, k=k, stride=1, pad=k // 2, groups=c, act=synth.ACT_NONE, name="dw"))
+    wa, wd = torch.randn(c, 8, 1, 1, generator=gen).to(td), torch.randn(c, 1, k, k, generator=gen).to(td)
+    wd[1, 0, 0, k // 2], wd[c - 1, 0, k - 1, k // 2] = float("inf"), -float("inf")
+    zero = torch.zeros(c, device="cuda")
+    handle = pipeline.build_net(net, [{"w": wa.cuda(), "b": zero}, {"w": wd.cuda(), "b": zero}], batch, dtype, tune=False)
+    y = handle.forward(torch.randn(batch, 8, h, w, generator=gen).to(td).cuda()).double().cpu()
+    x = handle.activation(0, batch, (c, h, w)).double().cpu()
+    handle.close()
+    p = k // 2
+    finite = torch.isfinite(y)
+    assert finite[:, 1, :p].all() and not finite[:, 1, p:].any()          # the first window row is outside
+    assert finite[:, c - 1, h - p:].all() and not finite[:, c - 1, :h - p].any()
+    wd[1, 0, 0, p], wd[c - 1, 0, k - 1, p] = 0.0, 0.0
+    ref = torch.nn.functional.conv2d(x, wd.double(), None, 1, p, groups=c)
+    check(y[finite].numpy(), ref[finite].numpy(), dtype, f"{cfg}")
