@@ -381,9 +381,10 @@ int cprune_lcm_step(const int64_t* l1, int n1, const int64_t* l2, int n2, int64_
 int cprune_prune_count(int c_out, int64_t step, int* count_out);
 /* The structure of tile variant `variant` on a layer of c_out filters, as that rule needs it:
  * both filter iterators walk (output tile, MFMA row block of the tile), so
- * main_loop[2] = epilogue[2] = {tiles, blocks per tile} and *unit_out = the filters per block
+ * main_loop[2] = epilogue[2] = {tiles, blocks a tile holds} and *unit_out = the filters per block
  * (16, or 32 for the variants built on 32x32 blocks; the rows inside a block are fixed by the
- * instruction and cannot shrink).  Host outs. */
+ * instruction and cannot shrink).  The split kernel deals a layer's blocks evenly to its tiles, so that a
+ * tile may run fewer than it holds; the step below is the same for either box.  Host outs. */
 int cprune_variant_filter_splits(int variant, int c_out, int64_t* main_loop, int64_t* epilogue,
                                  int* unit_out);
 /* cprune_lcm_step of those splits, in filters (times the unit). */

@@ -54,6 +54,8 @@ extern "C" int cprune_variant_filter_splits(int v, int c_out, int64_t* main_loop
   const int unit = tv.blk32 ? 32 : 16;   // rows of the MFMA block the variant is built on
   const int64_t tiles = (c_out + tile_m - 1) / tile_m;
   const int64_t blocks = std::min<int64_t>(tile_m / unit, (c_out + unit - 1) / unit);
+  // (what a tile holds: the split kernel deals a layer's blocks evenly to its tiles, 112 filters on a tile of 96 as 4 + 3
+  // blocks and not 6 + 1; the smallest slice of the box, min(tiles, blocks), is the same for both)
   // the reduction loop walks (tile, MFMA row block of the tile); the store loop walks the same
   // blocks (inside a block the rows are the MFMA result layout, not a loop)
   main_loop[0] = tiles; main_loop[1] = blocks;

@@ -2,6 +2,8 @@
 import os
 import subprocess
 
+from paper_2207_01260_amd import binding as B
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 # every tile, wavefront and chunk of every variant on layers at the edges of the 16-filter block, the 8-channel group and
@@ -60,3 +62,20 @@ def test_weight_loads_stay_inside(tmp_path):
                            "-o", str(exe)])
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
+
+
+def test_prune_step_of_evenly_dealt_blocks():
+    """The split kernel deals its 16-filter blocks evenly to its tiles, 112 filters on a tile of 96 as 4 + 3 blocks; the
+    splits the library reports are what a tile holds.  The pruning step is the same from either box."""
+    seen = 0
+    for v in range(B.cprune_num_tile_variants()):
+        if "conv_split" not in B.cprune_tile_variant_name(v, True, B.F32):
+            continue
+        tile = B.cprune_tile_variant_info(v)[0] // 16
+        for c_out in list(range(1, 1200, 7)) + [16, 48, 64, 96, 97, 112, 128, 512]:
+            blocks = -(-c_out // 16)
+            tiles = -(-blocks // tile)
+            dealt = [tiles, -(-blocks // tiles)]
+            assert B.cprune_variant_prune_step(v, c_out) == 16 * B.cprune_lcm_step(dealt, dealt), (v, c_out)
+        seen += 1
+    assert seen
