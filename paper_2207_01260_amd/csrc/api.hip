@@ -63,47 +63,19 @@ static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay) {
   return lay.nhwc || 2.0 * (double)d.n * ho * wo * d.c_out * d.c_in * d.kh * d.kw >= 6e8;
 }
 
-// Windows of more than one tap go to the split kernel where it pays; its own estimate says which variant.
+// Untimed choice: the cheapest by variant_cost among the general kernel's tiles, whole or cut into equal runs, and, for
+// windows of more than one tap, the split kernel's variants where it pays.
 int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay, size_t ws_limit) {
-  const long ho = conv_out_dim(d.h, d.kh, d.stride, d.pad), wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
-  const long P = (long)d.n * ho * wo, O = d.c_out;
-  if (d.groups == 1 && d.kh * d.kw > 1 && split_pays(d, lay)) {
-    const int v = best_split_variant(d, lay);
-    if (v >= 0 && conv_ws_bytes(d, v, lay) <= ws_limit) return v;
-  }
-  // Everything else: the general kernel's tiles, whole or cut into equal runs, by estimated clocks.  A unit holds `occ`
-  // work-groups (local memory); a slab costs a group its matrix instructions times the groups it shares them with, and
-  // no less than the round trip of its operands; groups come in rounds; cut tiles pay a second launch and their pieces.
-  // (Cutting always, with the largest reuse per operand, gave a layer with a short reduction a dozen groups in all:
-  // 13 -> 36 filters, 1x1 at 49x49, batch 4, bf16 57 us, now 16 us; timed choice 15.7.)
-  const long K = (long)(lay.nhwc ? lay.cp_in : d.c_in) * d.kh * d.kw;
-  const bool f32 = d.dtype == CPRUNE_F32;
+  const bool split = d.kh * d.kw > 1 && split_pays(d, lay);
   double best = -1.0;
   int best_v = 0;
   for (int v = 0; v < num_variants(); ++v) {
     const TileVariant& tv = variant(v);
-    if (!(tv.sched == 0 || tv.sched == 2 || tv.sched == 4) || !variant_supports(d, v, lay)) continue;
-    const long mt = tv.tile_m(), pt = tv.tile_p(), tiles = ((O + mt - 1) / mt) * ((P + pt - 1) / pt);
-    const double slabs = std::ceil((double)K / ((f32 ? 16 : 32) * tv.kq));
-    double groups = (double)tiles, run = slabs;
-    if (tv.sched > 0) {
-      groups = std::min(256.0 * tv.sched, std::ceil(tiles * slabs / 4.0));
-      run = std::ceil(tiles * slabs / groups);
-      groups = std::ceil(tiles * slabs / run);
-    }
-    const bool cut = std::fmod(run, slabs) != 0.0;
-    const double rows = std::min((double)tv.mb, std::ceil((double)O / 16.0 / tv.wm));   // filter blocks that exist
-    const double mfma = rows * tv.nb * tv.kq * (f32 ? 128.0 : 16.0);
-    const double bytes = (double)(mt + pt) * 64 * tv.kq;
-    const double occ = std::max(1.0, std::min(4.0, std::floor(160.0 * 1024 / (2.0 * (mt + pt) * (64 * tv.kq + 16)))));
-    const double held = std::min(occ, std::ceil(groups / 256.0));
-    const double slab = std::max(900.0 + bytes / 16.0, held * std::max(mfma, bytes / 16.0));
-    const double store = 2000.0 + (double)(mt * pt) / 8.0;
-    const double cost = std::ceil(groups / (256.0 * occ)) * (run * slab + std::ceil(run / slabs) * store) +
-                        (cut ? 9000.0 + 120.0 * slabs / run : 0.0);
-    if ((best < 0.0 || cost < best) && (!cut || conv_ws_bytes(d, v, lay) <= ws_limit)) { best = cost; best_v = v; }
+    if (!(tv.sched == 0 || tv.sched == 2 || tv.sched == 4 || (split && tv.split)) || !variant_supports(d, v, lay)) continue;
+    const double cost = variant_cost(d, v, lay);
+    if (cost >= 0.0 && (best < 0.0 || cost < best) && conv_ws_bytes(d, v, lay) <= ws_limit) { best = cost; best_v = v; }
   }
-  if (best < 0.0)  // nothing among the cut-run variants (a fused pool needs a patch kernel): first that runs
+  if (best < 0.0)  // none of those (a fused pool needs a patch kernel): first that runs
     for (int v = 0; v < num_variants(); ++v)
       if (variant_supports(d, v, lay)) return v;
   return best_v;

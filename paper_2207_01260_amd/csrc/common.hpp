@@ -85,7 +85,8 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay = 
 size_t conv_ws_bytes(const cprune_conv_desc& d, int v, const ConvLayout& lay = ConvLayout());
 // ws_limit: scratch bytes the chosen variant may need
 int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay = ConvLayout(), size_t ws_limit = SIZE_MAX);
-int best_split_variant(const cprune_conv_desc& d, const ConvLayout& lay);   // by estimate; -1 if none runs the layer
+// Estimated clocks of a variant that runs the layer, of the general kernel or the split kernel; -1 for the others.
+double variant_cost(const cprune_conv_desc& d, int v, const ConvLayout& lay);
 int cached_or_heuristic_variant(const cprune_conv_desc& d, bool* timed, const ConvLayout& lay = ConvLayout());
 void remember_variant(const cprune_conv_desc& d, int v, const ConvLayout& lay = ConvLayout());
 

@@ -7,6 +7,7 @@
 #include "conv_patch32_kernel.hpp"
 #include "conv_split_kernel.hpp"
 
+#include <algorithm>
 #include <cmath>
 
 namespace cprune {
@@ -64,6 +65,30 @@ Plan make_plan(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayou
     p.fixup = (p.units_per_wg % p.slabs) != 0;
   }
   return p;
+}
+
+// Rough cost in clocks of the general kernel's tiles, whole or cut into equal runs.  A unit holds `occ` work-groups (local
+// memory); a slab costs a group its matrix instructions times the groups it shares them with, and no less than the round
+// trip of its operands; groups come in rounds; cut tiles pay a second launch and their pieces.  (Cutting always, with the
+// largest reuse per operand, gave a layer with a short reduction a dozen groups in all: 13 -> 36 filters, 1x1 at 49x49,
+// batch 4, bf16 57 us, now 16 us; timed choice 15.7.)  Scaled to the clocks of split_cost, which it is compared with: over
+// 209 layers with windows of 3 to 7 that the scale was not taken from, the cheaper estimate loses 1.0 % (fp32 channels-last),
+// 0.9 % (fp32 in the boundary's layout) and 3.0 % (bf16 there) to the better of the two on average, always the split kernel 2.6,
+// 4.6 and 3.1 % and up to two times (a fully connected layer on a 7x7 map, 256 -> 1000, batch 32, 65.8 us; the general kernel 33.5).
+double tile_cost(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay) {
+  const Plan p = make_plan(d, tv, lay);
+  const bool f32 = d.dtype == CPRUNE_F32;
+  const long mt = tv.tile_m(), pt = tv.tile_p();
+  const double run = p.units_per_wg, slabs = p.slabs, groups = p.groups;
+  const double rows = std::min((double)tv.mb, std::ceil((double)d.c_out / 16.0 / tv.wm));   // filter blocks that exist
+  const double mfma = rows * tv.nb * tv.kq * (f32 ? 128.0 : 16.0);
+  const double bytes = (double)(mt + pt) * 64 * tv.kq;
+  const double occ = std::max(1.0, std::min(4.0, std::floor(160.0 * 1024 / (2.0 * (mt + pt) * (64 * tv.kq + 16)))));
+  const double held = std::min(occ, std::ceil(groups / 256.0));
+  const double slab = std::max(900.0 + bytes / 16.0, held * std::max(mfma, bytes / 16.0));
+  const double store = 2000.0 + (double)(mt * pt) / 8.0;
+  return (f32 ? 1.7 : 2.0) * (std::ceil(groups / (256.0 * occ)) * (run * slab + std::ceil(run / slabs) * store) +
+                              (p.fixup ? 9000.0 + 120.0 * slabs / run : 0.0));
 }
 
 // The pixel block a work-group of a split variant owns on a map: as few blocks as possible, and among equal ones the
@@ -274,20 +299,14 @@ struct VariantTable {
 };
 }  // namespace
 
-int best_split_variant(const cprune_conv_desc& d, const ConvLayout& lay) {
-  double best = -1.0;
-  int best_v = -1;
-  for (int v = num_variants() - kNumSplit; v < num_variants(); ++v) {
-    if (!variant_supports(d, v, lay)) continue;
-    const double c = split_cost(d, variant(v), lay);
-    if (c >= 0.0 && (best < 0.0 || c < best)) { best = c; best_v = v; }
-  }
-  return best_v;
-}
-
 const TileVariant& variant(int id) {
   static const VariantTable vt;   // built once, on first use, whichever thread gets there first
   return vt.table[id];
+}
+
+double variant_cost(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
+  const TileVariant& tv = variant(v);
+  return tv.split ? split_cost(d, tv, lay) : tv.sched >= 0 ? tile_cost(d, tv, lay) : -1.0;
 }
 
 bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
