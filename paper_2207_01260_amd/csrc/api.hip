@@ -354,6 +354,8 @@ struct NetLayer {
   void* act = nullptr;        // [max_batch][h_out][w_out][cp_out]
   size_t per_image = 0;       // elements per image of the output buffer
   int variant = -1;           // dense conv / fc: variant for max_batch
+  bool timed = false;         // ... chosen by timing or pinned, not estimated
+  std::vector<int> at_batch;  // dense conv / fc: variant chosen for a smaller batch, by batch (-1: not yet)
   bool fused_pool = false;    // conv: the 2x2 max-pool that follows runs in its epilogue; act is the pooled map
   bool alias = false;         // max-pool folded into its producer: no kernel, act is the producer's buffer
   bool map2x2 = false;        // 3x3 / stride 1 / pad 1 conv on a 2x2 map, run as one matrix over the whole map
@@ -613,18 +615,37 @@ static int net_run_mbconv(cprune_net* net, int i, int n, void* dst, hipStream_t 
   return CPRUNE_OK;
 }
 
-// The variant a layer runs at a batch of n: the one timed for that very shape if there is one, else the one chosen for
-// the handle's full batch wherever it runs the smaller shape too (with fewer images a layer keeps its reduction and
-// its filters, which the choice depends on most), and the untimed estimate only where it does not.  VGG-16 in fp16,
-// 37 images through a handle for 64: 222 us with the estimate, 99 us with the full batch's variants.
-static int layer_variant_at(const cprune_net* net, const NetLayer& L, const cprune_conv_desc& d, const ConvLayout& lay,
-                            int n) {
+// The variant a layer of a handle for larger batches runs at n images, where none was timed for that shape.  Without a timed
+// (or pinned) choice for the full batch: the estimate for n.  Otherwise the full batch's choice, which the timing of all
+// kernels stands behind, unless n is at most 7/8 of the full batch, the choice has an estimate and another tile of the same
+// kernel costs a tenth less by it: tiles chosen for many images leave most units idle at a few.  Graph replays in us, keeping
+// the choice always / by this rule: ResNet-18 fp32, 2 of 32 images 368 / 224, 24 of 32 609 / 566, bf16 2 of 32 199 / 200; VGG-16 fp32, 1 of 64
+// 157 / 136, 40 of 64 182 / 182, fp16 37 of 64 97 / 98; MobileNetV2 fp32, 4 of 64 444 / 401.  Estimating always, which knows two of
+// the kernels only, gave 222 us for VGG-16 fp16, 37 of 64.
+static int choose_at_batch(const cprune_net* net, const NetLayer& L, const cprune_conv_desc& d, const ConvLayout& lay) {
+  if (!(L.timed && L.variant >= 0 && variant_supports(d, L.variant, lay) && conv_ws_bytes(d, L.variant, lay) <= net->ws_bytes))
+    return heuristic_variant(d, lay, net->ws_bytes);
+  int best_v = L.variant;
+  double best = 0.9 * variant_cost(d, L.variant, lay);
+  if (best < 0.0 || 8 * d.n > 7 * net->max_batch) return best_v;
+  const bool split = variant(L.variant).split;
+  for (int v = 0; v < num_variants(); ++v) {
+    const TileVariant& tv = variant(v);
+    if (split ? !tv.split : !(tv.sched == 0 || tv.sched == 2 || tv.sched == 4)) continue;
+    if (!variant_supports(d, v, lay) || conv_ws_bytes(d, v, lay) > net->ws_bytes) continue;
+    const double cost = variant_cost(d, v, lay);
+    if (cost >= 0.0 && cost < best) { best = cost; best_v = v; }
+  }
+  return best_v;
+}
+
+static int layer_variant_at(const cprune_net* net, NetLayer& L, const cprune_conv_desc& d, const ConvLayout& lay, int n) {
   if (n == net->max_batch) return L.variant;
   const int timed = timed_variant(d, lay);
-  if (timed >= 0) return timed;
-  if (L.variant >= 0 && variant_supports(d, L.variant, lay) && conv_ws_bytes(d, L.variant, lay) <= net->ws_bytes)
-    return L.variant;
-  return heuristic_variant(d, lay);
+  if (timed >= 0 && variant_supports(d, timed, lay) && conv_ws_bytes(d, timed, lay) <= net->ws_bytes) return timed;
+  if (L.at_batch.empty()) L.at_batch.assign(net->max_batch, -1);
+  if (L.at_batch[n] < 0) L.at_batch[n] = choose_at_batch(net, L, d, lay);
+  return L.at_batch[n];
 }
 
 static int net_run_layer(cprune_net* net, int i, int n, const void* x, void* out_override, hipStream_t s) {
@@ -935,6 +956,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
       rc = select_tile_impl(cd, src, L.w, L.b, res, L.act, net->ws, net->ws_bytes, 2, 6, &v, nullptr, nullptr, s, lay);
     }
     L.variant = v;
+    L.timed = timed || tune;
   }
   // A first layer with an image-like input (<= 3 channels; 3x3 or 7x7 window) has a kernel of its
   // own that keeps the whole reduction in LDS; with tune != 0 it is timed against the chosen variant
@@ -1262,8 +1284,10 @@ extern "C" int cprune_net_task_key(const cprune_net* net, int layer, int32_t* ke
 }
 
 static void restore_variant(cprune_net* net, NetLayer& L) {
-  if (L.variant < 0 && !L.stem && !L.stem7)
-    L.variant = cached_or_heuristic_variant(layer_conv_desc(*net, L, net->max_batch), nullptr, layer_layout(L));
+  if (L.variant < 0 && !L.stem && !L.stem7) {
+    L.variant = cached_or_heuristic_variant(layer_conv_desc(*net, L, net->max_batch), &L.timed, layer_layout(L));
+    L.at_batch.clear();
+  }
 }
 
 extern "C" int cprune_net_fuse_first_layers(cprune_net* net, int enable) {
@@ -1363,6 +1387,8 @@ extern "C" int cprune_net_set_layer_variant(cprune_net* net, int layer, int vari
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
   drop_graphs(net);
   L.variant = variant;
+  L.timed = true;
+  L.at_batch.clear();
   return CPRUNE_OK;
 }
 

@@ -26,3 +26,53 @@ def test_every_smaller_batch(orc, dtype):
             torch.cuda.synchronize()
             check(out.float().cpu().numpy(), ref[:n], dtype, f"batch {n} of 9, graph {graph}")
     handle.close()
+
+
+@pytest.mark.parametrize("tune", [True, False])
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+def test_smaller_batches_choose_their_own_tiles(orc, dtype, tune):
+    """ResNet-18 on 32x32 images, built for 24: whatever a smaller batch runs, and in whatever order batches come, its logits
+    are the full batch's."""
+    net = synth.resnet18(10, 32, cifar_stem=True)
+    params = synth.layer_params(net, 72)
+    x = synth.net_input(net, 72, 24)
+    ref_layers, _ = orc.prune_net(net, params)
+    ref = orc.forward(net, ref_layers, x)
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(params), dtype)
+    B.cprune_clear_tile_cache()
+    handle = pipeline.build_net(net, layers, 24, dtype, tune=tune)
+    xd = torch.from_numpy(x).cuda().to(B.TORCH_DTYPE[dtype])
+    for n in (1, 24, 3, 11, 21, 1, 23, 24):
+        out = handle.forward(xd[:n].contiguous(), use_graph=n == 3)
+        torch.cuda.synchronize()
+        check(out.float().cpu().numpy(), ref[:n], dtype, f"batch {n} of 24, tune {tune}")
+    handle.close()
+
+
+def test_one_image_does_not_run_the_tiles_of_many():
+    """One 224x224 image through a timed handle for 32 (365 us on the full batch's tiles, 212 on its own) against an untimed
+    handle for one (198 us)."""
+    net = synth.resnet18(1000, 224)
+    params = pipeline.upload_params(synth.layer_params(net, 73))
+    layers, _ = pipeline.prune_net(net, params, B.F32)
+    x = torch.randn(1, 3, 224, 224, device="cuda")
+
+    def replay_us(max_batch, tune):
+        B.cprune_clear_tile_cache()
+        handle = pipeline.build_net(net, layers, max_batch, B.F32, tune=tune)
+        best = float("inf")
+        for _ in range(4):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            handle.forward(x, use_graph=True)
+            start.record()
+            for _ in range(10):
+                handle.forward(x, use_graph=True)
+            end.record()
+            end.synchronize()
+            best = min(best, start.elapsed_time(end) * 100.0)
+        handle.close()
+        return best
+
+    small = replay_us(1, False)
+    large = replay_us(32, True)
+    assert large < 1.4 * small, (large, small)
