@@ -55,9 +55,11 @@ void remember_variant(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
   g_cache[key_of(d, lay)] = v;
 }
 
-// Whether the split kernel is worth considering: inside a handle always; in the boundary's layout from 0.6 GFLOP up,
+// Whether an untimed choice considers the split kernel: inside a handle always; in the boundary's layout from 0.6 GFLOP up,
 // because there the weights are packed on every call, by a launch of its own (4-8 us: 128 -> 83 filters at 56x56,
-// batch 8, 74 -> 44 us in fp32 and 38 -> 22 us in bf16; 64 -> 45 at 32x32, batch 1, 10.5 -> 11.8 us).
+// batch 8, 74 -> 44 us in fp32 and 38 -> 22 us in bf16; 64 -> 45 at 32x32, batch 1, 10.5 -> 11.8 us).  On 232 layers under
+// 0.8 GFLOP a line at 0.6 loses 5.5 % of the device time to the better kernel on average, one at 0.2 4.3 %, always the general
+// kernel 7.1 %, always this one 14 %; the second launch also costs the caller's thread.
 static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay) {
   const long ho = conv_out_dim(d.h, d.kh, d.stride, d.pad), wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
   return lay.nhwc || 2.0 * (double)d.n * ho * wo * d.c_out * d.c_in * d.kh * d.kw >= 6e8;
@@ -152,7 +154,6 @@ static int select_tile_impl(const cprune_conv_desc& d, const void* x, const void
     if (d.groups == 1) {
       if (!variant_supports(d, v, lay)) continue;
       ++supported;
-      if (variant(v).split && !split_pays(d, lay)) continue;
       if (conv_ws_bytes(d, v, lay) > ws_bytes) continue;  // not timed: the caller's scratch cannot run it
     }
     for (int i = 0; i < warmup && rc == CPRUNE_OK; ++i) rc = conv_dispatch(d, x, w, bias, residual, y, v, ws, ws_bytes, s, lay);

@@ -1,4 +1,4 @@
-"""What a handle built without timing runs."""
+"""What a choice of variants looks at, timed and untimed."""
 import pytest
 import torch
 
@@ -35,3 +35,25 @@ def test_fully_connected_layer_on_a_map(c, hw, o, batch, split):
     handle.close()
     assert ("conv_split" in name) == split, name
     assert float((y - ref).norm() / ref.norm()) < 2e-6      # 12544 terms in fp32
+
+
+@pytest.mark.parametrize("shape", [(1, 16, 8, 24, 3, 1), (2, 64, 14, 45, 3, 2), (1, 256, 14, 300, 3, 1)])   # n, c_in, hw, c_out, k, stride
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+def test_timing_tries_every_variant_that_runs(shape, dtype):
+    """However small the layer, cprune_select_tile times each variant that runs it and fits the scratch."""
+    n, c, hw, o, k, stride = shape
+    td = B.TORCH_DTYPE[dtype]
+    x, w = torch.randn(n, c, hw, hw, device="cuda").to(td), torch.randn(o, c, k, k, device="cuda").to(td)
+    d = B.conv_desc(x.shape, w.shape, stride, k // 2, 1, dtype)
+    B.cprune_clear_tile_cache()
+    best, _, ms = B.cprune_select_tile(d, x, w, iters=2)
+    assert ms[best] > 0
+    for v in range(B.cprune_num_tile_variants()):
+        try:
+            B.cprune_conv2d_bn_relu(d, x, w, None, None, v)
+            runs = True
+        except B.CPruneError as e:
+            assert e.status == B.ERR_UNSUPPORTED
+            runs = False
+        assert (ms[v] > 0) == runs, (v, B.cprune_tile_variant_name(v, False, dtype))
+    B.cprune_clear_tile_cache()
