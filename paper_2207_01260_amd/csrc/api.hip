@@ -83,11 +83,16 @@ int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay, size_t w
   return best_v;
 }
 
-// The variant timed for exactly this shape and layout, or -1.
+// The variant timed for exactly this shape and layout, or -1; also -1 where it does not run here: the key does not say
+// which packed copies of its weights a handle's layer has.
 static int timed_variant(const cprune_conv_desc& d, const ConvLayout& lay) {
-  std::lock_guard<std::mutex> lock(g_cache_mutex);
-  auto it = g_cache.find(key_of(d, lay));
-  return it != g_cache.end() ? it->second : -1;
+  int v = -1;
+  {
+    std::lock_guard<std::mutex> lock(g_cache_mutex);
+    auto it = g_cache.find(key_of(d, lay));
+    if (it != g_cache.end()) v = it->second;
+  }
+  return v >= 0 && variant_supports(d, v, lay) ? v : -1;
 }
 
 int cached_or_heuristic_variant(const cprune_conv_desc& d, bool* timed, const ConvLayout& lay) {
@@ -443,6 +448,30 @@ static ConvLayout layer_layout(const NetLayer& L) {
   return lay;
 }
 
+// fp32 dense layers can have a copy of their weights cut and packed for the split kernel; it is 1.5 times the weights and made
+// only for a layer that runs that kernel (while variants are timed, for every layer that could).
+static ConvLayout layout_if_split(const cprune_net& net, const NetLayer& L) {
+  ConvLayout lay = layer_layout(L);
+  if (net.dtype == CPRUNE_F32 && !L.nchw_in) lay.w_split = L.w;     // (only whether it is set matters to a choice)
+  return lay;
+}
+
+static int pack_split(cprune_net* net, NetLayer& L, hipStream_t s) {
+  if (L.w_split) return CPRUNE_OK;
+  const cprune_conv_desc d = layer_conv_desc(*net, L, net->max_batch);
+  const int cp = layer_layout(L).cp_in, taps = d.kh * d.kw;
+  CPRUNE_HIP_TRY(hipMalloc(&L.w_split, split_packed_bytes(d.c_out, cp, taps, net->dtype)));
+  net->allocs.push_back(L.w_split);
+  return launch_pack_split(L.w, d.c_out, cp, taps, 1, net->dtype, L.w_split, s);
+}
+
+static void drop_split(cprune_net* net, NetLayer& L) {      // (nothing that reads it is in flight)
+  if (!L.w_split) return;
+  net->allocs.erase(std::find(net->allocs.begin(), net->allocs.end(), L.w_split));
+  hipFree(L.w_split);
+  L.w_split = nullptr;
+}
+
 constexpr size_t kMaxGraphs = 8;
 
 static void drop_graphs(cprune_net* net) {
@@ -643,7 +672,7 @@ static int choose_at_batch(const cprune_net* net, const NetLayer& L, const cprun
 static int layer_variant_at(const cprune_net* net, NetLayer& L, const cprune_conv_desc& d, const ConvLayout& lay, int n) {
   if (n == net->max_batch) return L.variant;
   const int timed = timed_variant(d, lay);
-  if (timed >= 0 && variant_supports(d, timed, lay) && conv_ws_bytes(d, timed, lay) <= net->ws_bytes) return timed;
+  if (timed >= 0 && conv_ws_bytes(d, timed, lay) <= net->ws_bytes) return timed;
   if (L.at_batch.empty()) L.at_batch.assign(net->max_batch, -1);
   if (L.at_batch[n] < 0) L.at_batch[n] = choose_at_batch(net, L, d, lay);
   return L.at_batch[n];
@@ -930,27 +959,19 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     rc = dev_alloc(rows_packed_bytes(cd.c_out, k, dtype), &L.w_rows);
     if (rc == CPRUNE_OK) rc = launch_repack_rows(L.w, cd.c_out, k, dtype, L.w_rows, s);
   }
-  // fp32 layers: a copy cut into 16-bit parts for the split kernel, where one of its variants can run the layer
-  for (int i = 0; i < n_layers && rc == CPRUNE_OK && dtype == CPRUNE_F32; ++i) {
-    NetLayer& L = net->layers[i];
-    if (!(L.d.kind == CPRUNE_LAYER_FC || (L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1)) || L.nchw_in) continue;
-    const cprune_conv_desc cd = layer_conv_desc(*net, L, max_batch);
-    ConvLayout lay = layer_layout(L);
-    lay.w_split = L.w;     // (only whether it is set matters here)
-    bool any = false;
-    for (int v = 0; v < num_variants() && !any; ++v) any = variant(v).split && variant_supports(cd, v, lay);
-    if (!any) continue;
-    rc = dev_alloc(split_packed_bytes(cd.c_out, lay.cp_in, cd.kh * cd.kw, dtype), &L.w_split);
-    if (rc == CPRUNE_OK) rc = launch_pack_split(L.w, cd.c_out, lay.cp_in, cd.kh * cd.kw, 1, dtype, L.w_split, s);
-  }
   // variant per dense layer
   for (int i = 0; i < n_layers && rc == CPRUNE_OK; ++i) {
     NetLayer& L = net->layers[i];
     if (!(L.d.kind == CPRUNE_LAYER_FC || (L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1))) continue;
     cprune_conv_desc cd = layer_conv_desc(*net, L, max_batch);
-    const ConvLayout lay = layer_layout(L);
-    bool timed = false;
+    ConvLayout lay = layout_if_split(*net, L);
+    bool timed = false, any_split = false;
     int v = cached_or_heuristic_variant(cd, &timed, lay);
+    for (int k = 0; k < num_variants() && !any_split; ++k)
+      any_split = variant(k).split && (tune && !timed ? variant_supports(cd, k, lay) : k == v);
+    if (any_split && dtype == CPRUNE_F32) rc = pack_split(net, L, s);
+    if (rc != CPRUNE_OK) break;
+    lay = layer_layout(L);
     if (tune && !timed) {
       const void* src = L.d.input < 0 ? net->x_cl : net->layers[L.d.input].act;
       const void* res = L.d.residual >= 0 ? net->layers[L.d.residual].act : nullptr;
@@ -958,6 +979,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     }
     L.variant = v;
     L.timed = timed || tune;
+    if (rc == CPRUNE_OK && !variant(v).split) drop_split(net, L);
   }
   // A first layer with an image-like input (<= 3 channels; 3x3 or 7x7 window) has a kernel of its
   // own that keeps the whole reduction in LDS; with tune != 0 it is timed against the chosen variant
@@ -1158,6 +1180,8 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     if (e != hipSuccess) { set_last_hip_error(e); rc = CPRUNE_ERR_DEVICE; }
   }
   if (rc != CPRUNE_OK) { net_free(net); return rc; }
+  for (NetLayer& L : net->layers)
+    if (L.variant < 0) drop_split(net, L);      // runs inside another kernel
   *out = net;
   return CPRUNE_OK;
 }
@@ -1284,11 +1308,17 @@ extern "C" int cprune_net_task_key(const cprune_net* net, int layer, int32_t* ke
   return CPRUNE_OK;
 }
 
-static void restore_variant(cprune_net* net, NetLayer& L) {
-  if (L.variant < 0 && !L.stem && !L.stem7) {
-    L.variant = cached_or_heuristic_variant(layer_conv_desc(*net, L, net->max_batch), &L.timed, layer_layout(L));
-    L.at_batch.clear();
+static int restore_variant(cprune_net* net, NetLayer& L) {
+  if (L.variant >= 0 || L.stem || L.stem7) return CPRUNE_OK;
+  const int v = cached_or_heuristic_variant(layer_conv_desc(*net, L, net->max_batch), &L.timed, layout_if_split(*net, L));
+  if (variant(v).split) {
+    const int rc = pack_split(net, L, nullptr);
+    if (rc != CPRUNE_OK) return rc;
+    CPRUNE_HIP_TRY(hipDeviceSynchronize());
   }
+  L.variant = v;
+  L.at_batch.clear();
+  return CPRUNE_OK;
 }
 
 extern "C" int cprune_net_fuse_first_layers(cprune_net* net, int enable) {
@@ -1304,7 +1334,7 @@ extern "C" int cprune_net_fuse_first_layers(cprune_net* net, int enable) {
   F.fused_away = enable != 0;
   L.fuse_stem = enable ? first : -1;
   if (enable) L.variant = -1;
-  else restore_variant(net, L);
+  else return restore_variant(net, L);
   return CPRUNE_OK;
 }
 
@@ -1321,7 +1351,7 @@ extern "C" int cprune_net_first_layer_form(cprune_net* net, int form) {
   L.stem7 = form;
   if (L.pool3 >= 0) net->layers[L.pool3].in_producer = form == 2;
   if (form) L.variant = -1;
-  else restore_variant(net, L);
+  else return restore_variant(net, L);
   return CPRUNE_OK;
 }
 
@@ -1335,13 +1365,14 @@ extern "C" int cprune_net_fuse_depthwise(cprune_net* net, int layer, int enable)
   if (P.fuse_block >= 0) {             // leaves the one-kernel block form either way
     NetLayer& E = net->layers[P.fuse_block];
     E.fused_away = false;
-    restore_variant(net, E);
     P.fuse_block = -1;
+    const int rc = restore_variant(net, E);
+    if (rc != CPRUNE_OK) return rc;
   }
   D.fused_away = enable != 0;
   P.fuse_dw = enable ? layer : -1;
   if (enable) P.variant = -1;
-  else restore_variant(net, P);
+  else return restore_variant(net, P);
   return CPRUNE_OK;
 }
 
@@ -1359,8 +1390,9 @@ extern "C" int cprune_net_fuse_block(cprune_net* net, int layer, int enable) {
     P.variant = -1; E.variant = -1;
   } else if (P.fuse_block >= 0) {      // back to the depthwise + projection pair in one kernel, expansion on its own
     E.fused_away = false;
-    restore_variant(net, E);
     P.fuse_block = -1;
+    const int rc = restore_variant(net, E);
+    if (rc != CPRUNE_OK) return rc;
   }
   return CPRUNE_OK;
 }
@@ -1382,11 +1414,18 @@ extern "C" int cprune_net_set_layer_variant(cprune_net* net, int layer, int vari
     L.stem7 = 0;
   }
   const cprune_conv_desc cd = layer_conv_desc(*net, L, net->max_batch);
-  const ConvLayout lay = layer_layout(L);
+  const ConvLayout lay = layout_if_split(*net, L);
   if (!variant_supports(cd, variant, lay)) return CPRUNE_ERR_UNSUPPORTED;
   if (conv_ws_bytes(cd, variant, lay) > net->ws_bytes) return CPRUNE_ERR_WORKSPACE;
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
   drop_graphs(net);
+  if (cprune::variant(variant).split) {
+    const int rc = pack_split(net, L, nullptr);
+    if (rc != CPRUNE_OK) return rc;
+    CPRUNE_HIP_TRY(hipDeviceSynchronize());
+  } else {
+    drop_split(net, L);
+  }
   L.variant = variant;
   L.timed = true;
   L.at_batch.clear();
