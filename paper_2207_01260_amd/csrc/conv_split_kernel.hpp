@@ -469,18 +469,28 @@ __global__ __launch_bounds__(256, MB * NB <= 4 && NIB <= 4 ? 3 : 2) void conv_sp
     // of sums from 2^-50 up while the terms of a sum times that operand stay under 2^59.  (Sums of ordinary numbers that
     // come out smaller, but not zero, are one in 10^15.)
     constexpr uint32_t kInf = 0x7f800000u, kSmall = (127u - 50u) << 23;
-    uint32_t top = 0, low = ~0u;
+    // (first a look that takes one and a half operations per sum and cannot tell zeros from small numbers)
+    uint32_t odd = 0;
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const uint32_t mag = __float_as_uint(acc[i][j][v]) & 0x7fffffffu;
-          top = max(top, mag);
-          low = min(low, mag - 1);      // (zero goes to the other end)
-        }
-    if (__any(top >= kInf || low < kSmall - 1)) again();
+        for (int v = 0; v < 4; ++v) odd = max(odd, (__float_as_uint(acc[i][j][v]) << 1) - (kSmall << 1));
+    if (__any(odd >= (kInf - kSmall) << 1)) {
+      uint32_t top = 0, low = ~0u;
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const uint32_t mag = __float_as_uint(acc[i][j][v]) & 0x7fffffffu;
+            top = max(top, mag);
+            low = min(low, mag - 1);      // (zero goes to the other end)
+          }
+      if (__any(top >= kInf || low < kSmall - 1)) again();
+    }
   }
 
   // ---- epilogue: a lane holds filters o .. o + 3 of its pixel ----
