@@ -68,14 +68,14 @@ static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay) {
 // Untimed choice: the cheapest by variant_cost among the general kernel's tiles, whole or cut into equal runs, and, for
 // windows of more than one tap, the split kernel's variants where it pays.
 int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay, size_t ws_limit) {
-  const bool split = d.kh * d.kw > 1 && split_pays(d, lay);
   double best = -1.0;
-  int best_v = 0;
+  int best_v = d.kh * d.kw > 1 && split_pays(d, lay) ? best_split_variant(d, lay, &best) : -1;
+  if (best_v < 0 || variant_ws_bytes(d, best_v, lay) > ws_limit) { best = -1.0; best_v = 0; }
   for (int v = 0; v < num_variants(); ++v) {
     const TileVariant& tv = variant(v);
-    if (!(tv.sched == 0 || tv.sched == 2 || tv.sched == 4 || (split && tv.split)) || !variant_supports(d, v, lay)) continue;
+    if (!(tv.sched == 0 || tv.sched == 2 || tv.sched == 4) || !variant_supports(d, v, lay)) continue;
     const double cost = variant_cost(d, v, lay);
-    if (cost >= 0.0 && (best < 0.0 || cost < best) && conv_ws_bytes(d, v, lay) <= ws_limit) { best = cost; best_v = v; }
+    if (cost >= 0.0 && (best < 0.0 || cost < best) && variant_ws_bytes(d, v, lay) <= ws_limit) { best = cost; best_v = v; }
   }
   if (best < 0.0)  // none of those (a fused pool needs a patch kernel): first that runs
     for (int v = 0; v < num_variants(); ++v)
@@ -112,11 +112,13 @@ static int conv_dispatch(const cprune_conv_desc& d, const void* x, const void* w
     // kernel that packs none; an untimed choice takes what scratch there is
     const size_t have = ws ? ws_bytes : 0;
     v = timed_variant(d, lay);
-    if (v < 0 || (variant(v).split && conv_ws_bytes(d, v, lay) > have)) v = heuristic_variant(d, lay, have);
+    if (v < 0 || (variant(v).split && variant_ws_bytes(d, v, lay) > have)) v = heuristic_variant(d, lay, have);
   }
-  if (!variant_supports(d, v, lay)) return CPRUNE_ERR_UNSUPPORTED;
-  const size_t need = conv_ws_bytes(d, v, lay);
-  if (need > 0 && (!ws || ws_bytes < need)) return CPRUNE_ERR_WORKSPACE;
+  const bool split = variant(v).split;      // (its launch finds out by itself whether it runs the layer)
+  if (!split && !variant_supports(d, v, lay)) return CPRUNE_ERR_UNSUPPORTED;
+  const size_t need = variant_ws_bytes(d, v, lay);
+  if (need > 0 && (!ws || ws_bytes < need))
+    return split && !variant_supports(d, v, lay) ? CPRUNE_ERR_UNSUPPORTED : CPRUNE_ERR_WORKSPACE;
   return launch_conv_dense(d, x, w, bias, residual, y, v, ws, s, lay);
 }
 
@@ -655,24 +657,27 @@ static int net_run_mbconv(cprune_net* net, int i, int n, void* dst, hipStream_t 
 static int choose_at_batch(const cprune_net* net, const NetLayer& L, const cprune_conv_desc& d, const ConvLayout& lay) {
   if (!(L.timed && L.variant >= 0 && variant_supports(d, L.variant, lay) && conv_ws_bytes(d, L.variant, lay) <= net->ws_bytes))
     return heuristic_variant(d, lay, net->ws_bytes);
-  int best_v = L.variant;
-  double best = 0.9 * variant_cost(d, L.variant, lay);
-  if (best < 0.0 || 8 * d.n > 7 * net->max_batch) return best_v;
-  const bool split = variant(L.variant).split;
-  for (int v = 0; v < num_variants(); ++v) {
-    const TileVariant& tv = variant(v);
-    if (split ? !tv.split : !(tv.sched == 0 || tv.sched == 2 || tv.sched == 4)) continue;
-    if (!variant_supports(d, v, lay) || conv_ws_bytes(d, v, lay) > net->ws_bytes) continue;
-    const double cost = variant_cost(d, v, lay);
-    if (cost >= 0.0 && cost < best) { best = cost; best_v = v; }
+  const double kept = variant_cost(d, L.variant, lay);
+  if (kept < 0.0 || 8 * d.n > 7 * net->max_batch) return L.variant;
+  int best_v = -1;
+  double best = 0.0;
+  if (variant(L.variant).split) {
+    best_v = best_split_variant(d, lay, &best);
+  } else {
+    for (int v = 0; v < num_variants(); ++v) {
+      const TileVariant& tv = variant(v);
+      if (!(tv.sched == 0 || tv.sched == 2 || tv.sched == 4) || !variant_supports(d, v, lay)) continue;
+      const double cost = variant_cost(d, v, lay);
+      if ((best_v < 0 || cost < best) && variant_ws_bytes(d, v, lay) <= net->ws_bytes) { best = cost; best_v = v; }
+    }
   }
-  return best_v;
+  return best_v >= 0 && best < 0.9 * kept ? best_v : L.variant;
 }
 
 static int layer_variant_at(const cprune_net* net, NetLayer& L, const cprune_conv_desc& d, const ConvLayout& lay, int n) {
   if (n == net->max_batch) return L.variant;
   const int timed = timed_variant(d, lay);
-  if (timed >= 0 && conv_ws_bytes(d, timed, lay) <= net->ws_bytes) return timed;
+  if (timed >= 0 && variant_ws_bytes(d, timed, lay) <= net->ws_bytes) return timed;
   if (L.at_batch.empty()) L.at_batch.assign(net->max_batch, -1);
   if (L.at_batch[n] < 0) L.at_batch[n] = choose_at_batch(net, L, d, lay);
   return L.at_batch[n];

@@ -85,7 +85,10 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay = 
 size_t conv_ws_bytes(const cprune_conv_desc& d, int v, const ConvLayout& lay = ConvLayout());
 // ws_limit: scratch bytes the chosen variant may need
 int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay = ConvLayout(), size_t ws_limit = SIZE_MAX);
-// Estimated clocks of a variant that runs the layer, of the general kernel or the split kernel; -1 for the others.
+size_t variant_ws_bytes(const cprune_conv_desc& d, int v, const ConvLayout& lay);   // of a variant that runs the layer
+// Estimated clocks of a variant: of the general kernel on a layer it runs, of the split kernel (-1 where it does not run
+// the layer); -1 for the others.
+int best_split_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost);   // the cheapest; -1: none runs it
 double variant_cost(const cprune_conv_desc& d, int v, const ConvLayout& lay);
 int cached_or_heuristic_variant(const cprune_conv_desc& d, bool* timed, const ConvLayout& lay = ConvLayout());
 void remember_variant(const cprune_conv_desc& d, int v, const ConvLayout& lay = ConvLayout());

@@ -125,10 +125,10 @@ bool split_plan(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayo
   if ((long)ho * wo <= pt)
     for (int ni = (int)(pt / ((long)ho * wo)); ni >= 1; --ni)
       if (ni <= d.n) consider(ni, ho, wo);
-  for (int nx = 1, last = 0; nx <= wo; ++nx) {
-    const int tw = ((wo + nx - 1) / nx + even - 1) / even * even;
-    if (tw > pt / even || tw == last) continue;
-    last = tw;
+  // every width that some number of blocks per row gives, the widest first
+  for (int tw = (wo + even - 1) / even * even, nx; tw > 0; nx = tw > even ? (wo + tw - even - 1) / (tw - even) : 0,
+           tw = nx ? ((wo + nx - 1) / nx + even - 1) / even * even : 0) {
+    if (tw > pt / even) continue;
     int th = pt / tw < ho ? pt / tw : ho;                              // rows that fit the block ...
     const int pw = (tw - 1) * d.stride + d.kw;
     const int ph_max = 64 * tv.nib / pw;                               // ... and whose patch fits the staging items
@@ -138,33 +138,37 @@ bool split_plan(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayo
     if (th < 1) continue;
     const int ny = (ho + th - 1) / th;
     consider(1, ((ho + ny - 1) / ny + even - 1) / even * even, tw);
-    if (tw <= even) break;
   }
   return best >= 0.0;
 }
 
-bool split_supports(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay) {
+// Whether the split kernel runs a layer, as far as that does not depend on the variant.
+bool split_layer(const cprune_conv_desc& d, const ConvLayout& lay) {
   if (lay.nhwc ? !(d.dtype == CPRUNE_F32 && lay.w_split) : lay.nhwc_out != 0) return false;
   if (lay.pool == 2 || (lay.pool && ((d.h | d.w) & 1 || d.stride != 1)) || d.stride > 2) return false;
   // fp32 sums of a few terms are less exact in parts than on the fp32 instruction (conv_split_kernel.hpp)
   if (d.dtype == CPRUNE_F32 && (long)d.c_in * d.kh * d.kw < kSplitMinTerms) return false;
   const int ho = conv_out_dim(d.h, d.kh, d.stride, d.pad), wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
   if (!lay.nhwc && (long)ho * wo < 16) return false;   // a map of a few pixels is a matrix product: the general kernel
-  if (split_packed_bytes(d.c_out, lay.nhwc ? lay.cp_in : d.c_in, d.kh * d.kw, d.dtype) >= ((size_t)1 << 31)) return false;
-  SplitPlan p;
-  if (!split_plan(d, tv, lay, &p)) return false;
-  // multiply-high divisions in the tile decode: exact while groups x divisor < 2^32
+  return split_packed_bytes(d.c_out, lay.nhwc ? lay.cp_in : d.c_in, d.kh * d.kw, d.dtype) < ((size_t)1 << 31);
+}
+
+// multiply-high divisions in the tile decode: exact while groups x divisor < 2^32
+bool split_groups_fit(const cprune_conv_desc& d, const TileVariant& tv, const SplitPlan& p) {
   const long tiles_s = (long)p.tiles_n * p.tiles_y * p.tiles_x;
   const long groups = tiles_s * ((d.c_out + tv.tile_m() - 1) / tv.tile_m());
   return groups * tiles_s < (1L << 32) && groups < (1L << 31);
 }
 
+// Whether a split variant runs a layer, and the plan it runs by.
+bool split_supports(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay, SplitPlan* plan) {
+  return split_layer(d, lay) && split_plan(d, tv, lay, plan) && split_groups_fit(d, tv, *plan);
+}
+
 // Rough cost in clocks of a split variant on a layer, for choosing among them untimed: the matrix-pipe time of the
 // work-groups a compute unit gets, plus per group the staging of its chunks and the fixed start and end, which overlap
 // between the two or three groups a unit holds.  Constants from timings of all variants on twenty layers.
-double split_cost(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay) {
-  SplitPlan p;
-  if (!split_plan(d, tv, lay, &p)) return -1.0;
+double split_cost(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay, const SplitPlan& p) {
   int nfull, groups_last, rounds_last;
   const int rtot = split_rounds(lay.nhwc ? lay.cp_in : d.c_in, d.kh * d.kw, &nfull, &groups_last, &rounds_last);
   const double groups = (double)p.tiles_n * p.tiles_y * p.tiles_x * ((d.c_out + tv.tile_m() - 1) / tv.tile_m());
@@ -180,7 +184,7 @@ double split_cost(const cprune_conv_desc& d, const TileVariant& tv, const ConvLa
 int launch_split_conv(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay, const void* x,
                       const void* w, const float* bias, const void* residual, void* y, void* ws, hipStream_t s) {
   SplitPlan p;
-  if (!split_plan(d, tv, lay, &p)) return CPRUNE_ERR_UNSUPPORTED;
+  if (!split_supports(d, tv, lay, &p)) return CPRUNE_ERR_UNSUPPORTED;
   SplitArgs a;
   const size_t es = dtype_size(d.dtype);
   a.C = lay.nhwc ? lay.cp_in : d.c_in;
@@ -304,16 +308,41 @@ const TileVariant& variant(int id) {
   return vt.table[id];
 }
 
+// (the plan is a search over block shapes, the same for variants with equal pixel blocks and staging items: five for 13 variants)
+int best_split_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost) {
+  if (!split_layer(d, lay)) return -1;
+  SplitPlan plan[kNumSplit];
+  bool have[kNumSplit];
+  int best_v = -1;
+  for (int id = 0; id < kNumSplit; ++id) {
+    const int v = num_variants() - kNumSplit + id;
+    const TileVariant& tv = variant(v);
+    int same = 0;
+    while (same < id && !(variant(v - id + same).tile_p() == tv.tile_p() && variant(v - id + same).nib == tv.nib)) ++same;
+    if (same < id) { plan[id] = plan[same]; have[id] = have[same]; }
+    else have[id] = split_plan(d, tv, lay, &plan[id]);
+    if (!have[id] || !split_groups_fit(d, tv, plan[id])) continue;
+    const double c = split_cost(d, tv, lay, plan[id]);
+    if (best_v < 0 || c < *cost) { *cost = c; best_v = v; }
+  }
+  return best_v;
+}
+
 double variant_cost(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
   const TileVariant& tv = variant(v);
-  return tv.split ? split_cost(d, tv, lay) : tv.sched >= 0 ? tile_cost(d, tv, lay) : -1.0;
+  SplitPlan p;
+  if (tv.split) return split_supports(d, tv, lay, &p) ? split_cost(d, tv, lay, p) : -1.0;
+  return tv.sched >= 0 ? tile_cost(d, tv, lay) : -1.0;
 }
 
 bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
   if (v < 0 || v >= num_variants()) return false;
   if (d.groups != 1) return false;
   const TileVariant& tv = variant(v);
-  if (tv.split) return split_supports(d, tv, lay);
+  if (tv.split) {
+    SplitPlan p;
+    return split_supports(d, tv, lay, &p);
+  }
   if (tv.sched == -4) {
     // 3x3 / stride 1 / pad 1 on small maps (every wavefront fetches its own weights: with many pixels the
     // tiled kernels, which share them through LDS, are the ones to use)
@@ -368,15 +397,18 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
   return units < (1L << 30);
 }
 
+size_t variant_ws_bytes(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
+  const TileVariant& tv = variant(v);
+  if (tv.split && !lay.nhwc) return split_packed_bytes(d.c_out, d.c_in, d.kh * d.kw, d.dtype);
+  if (tv.sched < 0) return 0;
+  const Plan p = make_plan(d, tv, lay);
+  return p.fixup ? (size_t)2 * p.groups * tv.tile_m() * tv.tile_p() * sizeof(float) : 0;
+}
+
 size_t conv_ws_bytes(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
   if (d.groups != 1) return 0;
   if (v >= 0) {
-    if (!variant_supports(d, v, lay)) return 0;
-    const TileVariant& tv = variant(v);
-    if (tv.split && !lay.nhwc) return split_packed_bytes(d.c_out, d.c_in, d.kh * d.kw, d.dtype);
-    if (tv.sched < 0) return 0;
-    const Plan p = make_plan(d, tv, lay);
-    return p.fixup ? (size_t)2 * p.groups * tv.tile_m() * tv.tile_p() * sizeof(float) : 0;
+    return variant_supports(d, v, lay) ? variant_ws_bytes(d, v, lay) : 0;
   }
   // the most any variant needs: cut tiles, or (all alike) the packed weights of the split kernel
   size_t best = 0;
