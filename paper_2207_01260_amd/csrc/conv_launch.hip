@@ -167,12 +167,13 @@ bool split_supports(const cprune_conv_desc& d, const TileVariant& tv, const Conv
 
 // Rough cost in clocks of a split variant on a layer, for choosing among them untimed: the matrix-pipe time of the
 // work-groups a compute unit gets, plus per group the staging of its chunks and the fixed start and end, which overlap
-// between the two or three groups a unit holds.  Constants from timings of all variants on twenty layers.
+// between the two or three groups a unit holds (the kernel's launch bound).  Constants from timings of all variants on twenty
+// layers.
 double split_cost(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay, const SplitPlan& p) {
   int nfull, groups_last, rounds_last;
   const int rtot = split_rounds(lay.nhwc ? lay.cp_in : d.c_in, d.kh * d.kw, &nfull, &groups_last, &rounds_last);
   const double groups = (double)p.tiles_n * p.tiles_y * p.tiles_x * ((d.c_out + tv.tile_m() - 1) / tv.tile_m());
-  const int occ = tv.mb * tv.nb <= 4 ? 3 : 2;
+  const int occ = tv.mb * tv.nb <= 4 && tv.nib <= 4 ? 3 : 2;
   const double mfma = std::ceil((double)rtot / tv.ks) * tv.mb * tv.nb * (d.dtype == CPRUNE_F32 ? 6 : 1) * 18.0;
   const double chunks = nfull + (rounds_last ? 1 : 0);
   const double npatch = (double)p.ni * p.ph * p.pw;

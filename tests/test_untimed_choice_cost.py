@@ -25,3 +25,14 @@ def test_windows_cost_little_more_than_one_tap(n, c_in, hw, c_out, k):
     window = _choice_us(B.conv_desc(shape, (c_out, c_in, k, k), 1, k // 2, 1, B.F32))
     one_tap = _choice_us(B.conv_desc(shape, (c_out, c_in, 1, 1), 1, 0, 1, B.F32))
     assert window < 3.0 * one_tap, (window, one_tap)
+
+
+@pytest.mark.parametrize("n,c_in,hw,c_out,k,stride,old", [(5, 491, 80, 151, 3, 2, "1, 2, 5"),
+                                                          (44, 128, 24, 202, 3, 2, "2, 2, 5")])
+def test_estimate_knows_how_many_groups_a_unit_holds(n, c_in, hw, c_out, k, stride, old):
+    """Variants that stage five items per thread hold two work-groups per unit, not three: the estimate that counted three
+    took them on layers others run faster (491 -> 151 at 80x80, stride 2, batch 5, 123 us; now 98)."""
+    B.cprune_clear_tile_cache()
+    v, timed = B.cprune_cached_tile(B.conv_desc((n, c_in, hw, hw), (c_out, c_in, k, k), stride, k // 2, 1, B.F32))
+    assert not timed
+    assert not B.cprune_tile_variant_name(v, False, B.F32).endswith(old + ">"), B.cprune_tile_variant_name(v, False, B.F32)
