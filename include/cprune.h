@@ -187,12 +187,16 @@ typedef struct {
  * output pixels) and a scheduling mode.  sched 0: one output tile per work-group.
  * sched n > 0: the (tile, reduction slab) work is laid out in one line and cut
  * into equal runs for n * 256 work-groups; tiles cut between runs go through the
- * caller's scratch and are summed in run order (deterministic).  sched -1: kernels that
- * exist only for the channels-last layout inside a network handle (3x3 stride-1 layers,
- * one tile_p-pixel spatial block per work-group); unsupported through this NCHW call.
- * (also sched -1: the split kernel, any window at stride 1 or 2, fp32 data as three 16-bit parts on the 16-bit
- * matrix cores at no larger an error.  Inside a handle its weights are packed at creation; through
- * cprune_conv2d_bn_relu each call packs them into the caller's scratch.)
+ * caller's scratch and are summed in run order (deterministic).  sched -1: one spatial block of at
+ * most tile_p pixels per work-group.  Two kinds, told apart by cprune_tile_variant_name: the patch
+ * kernels (conv_patch*: 3x3 layers, channels-last inside a network handle only, unsupported through
+ * the NCHW call) and the split kernel (conv_split_kernel: any window at stride 1 or 2).  The split
+ * kernel multiplies fp32 data as three 16-bit parts per number on the 16-bit matrix cores; it runs fp32
+ * layers of at least 16 terms per output, where its error is no larger than the fp32 instruction's, and
+ * redoes with that instruction what three parts do not hold (infinities, results below 2^-50; inputs or
+ * weights below 2^-133, all denormal, count as zero in larger sums).  It runs through
+ * cprune_conv2d_bn_relu, where each call packs the weights into the caller's scratch, in fp32 and 16-bit
+ * data, and in fp32 handles, which keep packed copies for the layers that run it.
  * sched -2: likewise channels-last only, for layers whose reduction is one contiguous run
  * per pixel (1x1 stride 1, fully connected): 16 filters x tile_p pixels per work-group, the
  * wavefronts of the group splitting the reduction; chosen when pixels are few.

@@ -27,8 +27,8 @@
 // block and take every WK-th round (few blocks, long reductions); their sums meet in LDS at the end, in order.
 //
 // Measured, fp32 channels-last, best variant against the best fp32-instruction kernel: 56 -> 56 at 32x32, batch 64, 42.4
-// -> 25.7 us; 40 -> 64 at 56x56, batch 32, 54.1 -> 34.2 us; 128 -> 85 at 28x28 56.8 -> 35.1 us; 512 -> 411 at 7x7
-// 72.2 -> 53.1 us; 360 -> 360 at 4x4, batch 64, 25.4 -> 26.2 us (the independent-wavefront kernel stays there);
+// -> 26.5 us; 40 -> 64 at 56x56, batch 32, 54.1 -> 35.0 us; 128 -> 85 at 28x28 56.8 -> 37.0 us; 512 -> 411 at 7x7
+// 72.2 -> 52.0 us; 360 -> 360 at 4x4, batch 64, 25.4 -> 26.2 us (the independent-wavefront kernel stays there);
 // stride 2, 128 -> 173 at 28x28, 34.8 -> 25.1 us.  What bounds it:
 // of the 32 us of 85 -> 128 at 28x28 the matrix pipes need 14; operand reads, weight reads and staging cost 5-8 %
 // each when left out alone; 8 us are launch, first loads and stores, which the two or three work-groups of a unit,

@@ -210,11 +210,6 @@ __global__ __launch_bounds__(256) void depthwise_nhwc_kernel(const T* __restrict
   st(y + i, act_f(acc, act));
 }
 
-// Channels-last depthwise, vectorised: a thread owns one 16-byte channel vector (4 floats /
-// 8 halves) of TX neighbouring output pixels of a row.  Consecutive lanes take consecutive
-// channel vectors, so every access is a coalesced 16-byte load or store; the K x K weights of
-// the vector sit in registers; each input column loaded serves every output of the run whose
-// window covers it ((TX - 1) * S + K loads per row for TX outputs instead of TX * K).
 // Channels-last max-pool on 16-byte channel vectors (one output pixel and vector per thread).  A window position outside
 // the image reads the nearest one inside, which is in the window too (pad < k): the K * K loads need no branches and are
 // in flight together (K = 0: any other window).  3x3 / stride 2 on 64 channels at 112x112, batch 32, fp32 28.4 -> 26.9 us.
@@ -269,7 +264,10 @@ __global__ __launch_bounds__(256) void maxpool_nhwc_vec_kernel(const T* __restri
   *reinterpret_cast<uint4*>(y + (size_t)idx * V) = q;
 }
 
-// One 16-byte channel vector x TX neighbouring outputs per thread.  Every load is unconditional (outside the image it is
+// Channels-last depthwise, vectorised: a thread owns one 16-byte channel vector (4 floats / 8 halves) of TX neighbouring
+// output pixels of a row.  Consecutive lanes take consecutive channel vectors, so every access is a coalesced 16-byte load
+// or store; each input column loaded serves every output of the run whose window covers it ((TX - 1) * S + K loads per
+// row for TX outputs instead of TX * K), each window row's weights are read with it.  Every load is unconditional (outside the image it is
 // out of the buffer's range and reads as zero, and so do the weights of a window row outside: a row that is not there
 // adds nothing, whatever its weights): behind branches each would be waited for before the next is issued, and on small
 // maps that chain is the kernel's whole time.  Batch 16, bf16: 5x5 on 374 channels at 14x14 11.5 -> 8.3 us,
