@@ -11,7 +11,8 @@ when timing starts.
 Prints ONE JSON line.  `value`: images/s over the timed steps.  `roofline`: the dominant
 kernel (the conv instantiation with the most device time per step): useful FLOP of the layers it
 runs over the sum of their device times (HIP events around back-to-back launches of each layer),
-against the dense fp32 / fp16 MFMA peak; `traffic`: its bytes between L2 and fabric per launch
+against the dense MFMA peak of the instructions it runs (fp32: 157.3 TFLOP/s, the split kernel, which
+makes six bf16 products of an fp32 one, 2500 / 6); `traffic`: its bytes between L2 and fabric per launch
 from hardware counters (fixed figures for the default workload).  `conv_layers`: the same ratio
 over all 13 conv layers.
 `cpu_baseline`: the CPU oracle's forward on a bounded sample of the same images.
@@ -26,53 +27,42 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK = {"f32": 157.3, "f16": 2500.0, "bf16": 2500.0}   # dense MFMA TFLOP/s, MI355X
 # Bytes between L2 and fabric per launch (FETCH_SIZE + WRITE_SIZE, each scaled by what the counter
 # reads for a copy kernel of known size), by (kernel instantiation, batch, layer), for the default
-# workload: from the rocprofv3 counter runs summarised in profiles/vgg16_b64_f32_hbm_traffic.md (five
+# workload: from the rocprofv3 counter runs summarised in profiles/vgg16_b64_f32_hbm_traffic.md (three
 # pinned selections, because the timed selection flips between near-equal variants).  The figures belong
 # to the kernel sources they were measured on: TRAFFIC_SOURCE_HASH is kernel_source_hash() of that tree,
 # and any change to a file under csrc/ since then reports null instead of a stale figure (as does a
 # selection that runs a kernel on a layer it was not profiled on).
-TRAFFIC_SOURCE_HASH = "44ade6751b488d6a"
+TRAFFIC_SOURCE_HASH = "742727968da6a9ad"
 TRAFFIC = {
-    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3350342,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 1, 1>", 64, "conv3"): 10522153,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 2, 1>", 64, "conv3"): 10552867,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 2, 2>", 64, "conv3"): 10528295,
-    ("conv_patch_kernel<float, 2, 8, 8, 1, 1, 1>", 64, "conv3"): 10578463,
-    ("conv_patch32_kernel<float, 1, 1, 4, 8, 16, 1, 1>", 64, "conv4"): 10128045,
-    ("conv_patch_kernel<float, 2, 8, 16, 1, 1, 1>", 64, "conv4"): 10117802,
-    ("conv_patch_kernel<float, 2, 8, 16, 1, 1, 2>", 64, "conv4"): 10109612,
-    ("conv_patch_kernel<float, 2, 8, 8, 1, 1, 1>", 64, "conv4"): 10100399,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 1, 1>", 64, "conv5"): 4493931,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 2, 1>", 64, "conv5"): 4524648,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 2, 2>", 64, "conv5"): 4500075,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 1, 1>", 64, "conv6"): 10399661,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 2, 1>", 64, "conv6"): 10430378,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 2, 2>", 64, "conv6"): 10405808,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 1, 1>", 64, "conv7"): 12095845,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 2, 1>", 64, "conv7"): 12126557,
-    ("conv_patch_kernel<float, 1, 8, 8, 1, 2, 2>", 64, "conv7"): 12104034,
-    ("conv_wave_kernel<float, 2, 2, 2>", 64, "conv7"): 13495440,
-    ("conv_wave_kernel<float, 2, 2, 2>", 64, "conv8"): 9394120,
-    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv8"): 9401286,
-    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv8"): 16851363,
-    ("conv_wave_kernel<float, 2, 2, 2>", 64, "conv9"): 15049581,
-    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv9"): 15056750,
-    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv9"): 20934069,
-    ("conv_wave_kernel<float, 2, 2, 2>", 64, "conv10"): 11484552,
-    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv10"): 11491715,
-    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv10"): 18686818,
-    ("conv_ksplit_kernel<float, 1, 16>", 64, "conv11"): 7694001,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7678645,
-    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv11"): 7689905,
-    ("conv_ksplit_kernel<float, 1, 16>", 64, "conv12"): 6407791,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392431,
-    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv12"): 6403696,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv13"): 7768205,
-    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537585,
-    ("conv_ksplit_kernel<float, 2, 8>", 64, "conv13"): 7537586,
+    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3350377,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 2, 2>", 64, "conv3"): 11261480,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 4, 4>", 64, "conv3"): 11438611,
+    ("conv_split_kernel<float, false, 4, 1, 1, 1, 4, 2>", 64, "conv3"): 11234859,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 2, 2>", 64, "conv4"): 11636471,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 4, 4>", 64, "conv4"): 11786981,
+    ("conv_split_kernel<float, false, 4, 1, 1, 1, 4, 2>", 64, "conv4"): 11645686,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv5"): 5613106,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv5"): 5709350,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv6"): 14330536,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv6"): 14403231,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv7"): 17857518,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv7"): 17947620,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv8"): 10622233,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv8"): 11436727,
+    ("conv_wave_kernel<float, 1, 2, 4>", 64, "conv9"): 15058162,
+    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv9"): 15057138,
+    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv9"): 20934546,
+    ("conv_wave_kernel<float, 1, 2, 4>", 64, "conv10"): 11493054,
+    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv10"): 11492030,
+    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv10"): 18687239,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7678851,
+    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv11"): 7690114,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392605,
+    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv12"): 6403868,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv13"): 7768422,
+    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537793,
 }
 
 
@@ -142,6 +132,7 @@ def main():
 
     from paper_2207_01260_amd import binding as B
     from paper_2207_01260_amd import pipeline, synth
+    from paper_2207_01260_amd.report import kernel_peak
 
     assert torch.cuda.is_available(), "bench.py needs the GPU"
     torch.cuda.set_device(0)
@@ -226,6 +217,7 @@ def main():
     by_kernel = {}        # kernel instantiation -> [launches, ms, flop]
     shp = synth.shapes(net, kept_counts)
     tname = {"f32": "float", "f16": "_Float16", "bf16": "__bf16"}[args.dtype]
+    s_at_peak = 0.0        # every conv layer's FLOP at the peak of the kernel that runs it
     carried = 0.0          # FLOP of a layer that runs inside its reader's kernel
     fused_first = False
     for i, (L, m) in enumerate(zip(net.layers, layer_ms)):
@@ -251,6 +243,7 @@ def main():
             tm, tp, sk = B.cprune_tile_variant_info(v)
             kern = B.cprune_tile_variant_name(v, channels_last=not first, dtype=dt)
         fl, carried = fl + carried, 0.0
+        s_at_peak += fl / (kernel_peak(kern, dt) * 1e12)
         note = (" + fix-up" if sk > 0 else "") + (" (2x2 map as one matrix)" if (ho == 2 and sk >= 0) else "")
         g = by_kernel.setdefault(kern, [0, 0.0, 0.0, []])
         g[0] += 1; g[1] += m; g[2] += fl; g[3].append(L.name)
@@ -261,6 +254,7 @@ def main():
     dom = max(by_kernel, key=lambda k: by_kernel[k][1])
     d_n, d_ms, d_fl, d_layers = by_kernel[dom]
     achieved = d_fl / (d_ms * 1e-3) / 1e12
+    d_peak = kernel_peak(dom, dt)
     agg = conv_flops / (conv_ms * 1e-3) / 1e12
 
     out = {
@@ -282,8 +276,8 @@ def main():
                   "note": "raw weights read by scoring and by the gather + folded weights written, per run"},
         "tune_s": round(tune_s, 2), "variants": variants,
         "roofline": {"bound": "mfma", "kernel": dom, "launches_per_step": d_n,
-                     "achieved": round(achieved, 2), "peak": PEAK[args.dtype], "unit": "TFLOP/s",
-                     "frac": round(achieved / PEAK[args.dtype], 4),
+                     "achieved": round(achieved, 2), "peak": round(d_peak, 1), "unit": "TFLOP/s",
+                     "frac": round(achieved / d_peak, 4),
                      "layers": d_layers,
                      "traffic": dominant_traffic(dom, args.batch, d_layers),
                      "traffic_unit": "bytes per launch between L2 and fabric (FETCH_SIZE + WRITE_SIZE, scaled); null when "
@@ -293,7 +287,7 @@ def main():
                      "useful_gflop_per_launch": round(d_fl / d_n / 1e9, 3),
                      "share_of_step": round(d_ms / ms, 3)},
         "conv_layers": {"layers": n_conv, "launches_per_step": n_conv - (1 if fused_first else 0), "tflops": round(agg, 2),
-                        "frac_of_peak": round(agg / PEAK[args.dtype], 4),
+                        "frac_of_peak": round(s_at_peak / (conv_ms * 1e-3), 4),
                         "avg_layer_us": round(conv_ms / n_conv * 1e3, 2),
                         "useful_gflop_per_layer_avg": round(conv_flops / n_conv / 1e9, 3)},
         "layers": per_layer,
@@ -397,7 +391,7 @@ def main():
             us = [rows[c]["us"] for c in counts]
             cfg["conv3x3_56x56_cin128_b8_f32_sweep"] = {
                 "us_by_c_out": {str(c): rows[c]["us"] for c in counts},
-                "tflops_at_128": rows[128]["tflops"], "frac_at_128": round(rows[128]["tflops"] / 157.3, 4),
+                "tflops_at_128": rows[128]["tflops"], "frac_at_128": round(rows[128]["tflops"] / kernel_peak(rows[128]["kernel"], B.F32), 4),
                 "bound": "mfma", "inversions_over_3pct": sum(1 for a, b in zip(us, us[1:]) if b < 0.97 * a)}
             extras["configs"] = cfg
 

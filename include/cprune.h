@@ -323,7 +323,7 @@ int cprune_net_copy_activation(cprune_net* net, int layer, int n, void* dst, siz
                                void* stream);
 /* Shape of one image's output (the last layer's c_out, h_out, w_out); host outs. */
 int cprune_net_output_shape(const cprune_net* net, int* c_out, int* h_out, int* w_out);
-/* The tile variant in use for layer `layer` (-1 for layers without one); host out. */
+/* The tile variant layer `layer` runs at the full batch (-1 for layers without one); host out. */
 int cprune_net_layer_variant(const cprune_net* net, int layer, int* variant_out);
 /* The first two layers in one kernel, where the network opens with two 3x3 / stride 1 / pad 1 convolutions,
  * the first on the image (at most 3 channels) with at most 32 filters and read by the second only (the
@@ -365,7 +365,8 @@ int cprune_net_layer_fused(const cprune_net* net, int layer, int* fused_out);
  * depthwise layer of a block that runs as one kernel. */
 int cprune_net_fuse_block(cprune_net* net, int layer, int enable);
 /* Pins the tile variant of a dense conv / fully connected layer (what a stored tuning result
- * is applied with).  CPRUNE_ERR_INVALID_ARG for a layer without variants,
+ * is applied with) at the handle's full batch; a smaller batch may run another tile of the same
+ * kernel.  A split variant's packed weights are made here.  CPRUNE_ERR_INVALID_ARG for a layer without variants,
  * CPRUNE_ERR_UNSUPPORTED when the variant cannot run that layer's shape.  Recorded graphs
  * are dropped (they hold the old choice).  Not to be called while a forward is in flight. */
 int cprune_net_set_layer_variant(cprune_net* net, int layer, int variant);

@@ -462,8 +462,10 @@ static int pack_split(cprune_net* net, NetLayer& L, hipStream_t s) {
   if (L.w_split) return CPRUNE_OK;
   const cprune_conv_desc d = layer_conv_desc(*net, L, net->max_batch);
   const int cp = layer_layout(L).cp_in, taps = d.kh * d.kw;
-  CPRUNE_HIP_TRY(hipMalloc(&L.w_split, split_packed_bytes(d.c_out, cp, taps, net->dtype)));
-  net->allocs.push_back(L.w_split);
+  void* copy = nullptr;
+  CPRUNE_HIP_TRY(hipMalloc(&copy, split_packed_bytes(d.c_out, cp, taps, net->dtype)));
+  net->allocs.push_back(copy);
+  L.w_split = copy;
   return launch_pack_split(L.w, d.c_out, cp, taps, 1, net->dtype, L.w_split, s);
 }
 

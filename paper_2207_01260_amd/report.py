@@ -31,6 +31,12 @@ from . import pipeline, synth
 
 PEAK_TFLOPS = {B.F32: 157.3, B.F16: 2500.0, B.BF16: 2500.0}
 PEAK_GBS = 8000.0
+
+
+def kernel_peak(kernel: str, dtype: int) -> float:
+    """Dense MFMA TFLOP/s a kernel (cprune_tile_variant_name) can reach: the split kernel runs an fp32 product as six bf16
+    ones."""
+    return PEAK_TFLOPS[B.BF16] / 6 if dtype == B.F32 and kernel.startswith("conv_split_kernel") else PEAK_TFLOPS[dtype]
 DT_NAME = {B.F32: "f32", B.F16: "f16", B.BF16: "bf16"}
 
 
@@ -101,14 +107,17 @@ def net_report(name, net, cid, batch, dtype, steps, ceilings=None, variants=None
             kind, fl, by = "fc", 2.0 * batch * cin * hin * win * cout, 0.0
         else:
             kind, fl, by = "pool", 0.0, (moved if t > 0 else 0.0)
-        g = groups.setdefault(kind, {"ms": 0.0, "flop": 0.0, "bytes": 0.0, "launches": 0})
+        v = handle.layer_variant(i)
+        peak = kernel_peak(B.cprune_tile_variant_name(v, True, dtype) if v >= 0 else "", dtype)
+        g = groups.setdefault(kind, {"ms": 0.0, "flop": 0.0, "bytes": 0.0, "launches": 0, "s_at_peak": 0.0})
+        g["s_at_peak"] += fl / (peak * 1e12)      # every layer against the peak of the kernel that runs it
         g["ms"] += t; g["flop"] += fl; g["bytes"] += by; g["launches"] += 1 if t > 0 else 0
     by_kind = {}
     for kind, g in groups.items():
         row = {"ms": round(g["ms"], 4), "layers": g["launches"]}
         if g["flop"] and kind in ("dense_conv", "fc") and g["ms"] > 0:
             tf = g["flop"] / (g["ms"] * 1e-3) / 1e12
-            row.update(tflops=round(tf, 2), frac_mfma_peak=round(tf / PEAK_TFLOPS[dtype], 4))
+            row.update(tflops=round(tf, 2), frac_mfma_peak=round(g["s_at_peak"] / (g["ms"] * 1e-3), 4))
         if g["bytes"] and g["ms"] > 0:
             gbs = g["bytes"] / (g["ms"] * 1e-3) / 1e9
             row.update(gbs=round(gbs, 1), frac_hbm_peak=round(gbs / PEAK_GBS, 4))

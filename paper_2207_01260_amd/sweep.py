@@ -41,7 +41,7 @@ def run(c_in=128, c_full=128, hw=56, batch=8, dtype=B.F32, step=1, iters=20, dir
         tm, tp, sched = B.cprune_tile_variant_info(v)
         flops = 2.0 * batch * hw * hw * c_out * c_in * 9
         rows.append({"c_out": c_out, "us": round(ms * 1e3, 2), "tflops": round(flops / ms / 1e9, 2),
-                     "tile_m": tm, "tile_p": tp, "sched": sched})
+                     "tile_m": tm, "tile_p": tp, "sched": sched, "kernel": B.cprune_tile_variant_name(v, not direct_api, dtype)})
     return rows
 
 
