@@ -57,3 +57,22 @@ def test_timing_tries_every_variant_that_runs(shape, dtype):
             runs = False
         assert (ms[v] > 0) == runs, (v, B.cprune_tile_variant_name(v, False, dtype))
     B.cprune_clear_tile_cache()
+
+
+@pytest.mark.parametrize("timed", [False, True])
+def test_a_call_takes_the_scratch_of_the_variant_it_runs(timed, monkeypatch):
+    """cprune_conv2d_bn_relu without scratch of the caller's: what the chosen variant needs, not what the most demanding would."""
+    x, w = torch.randn(8, 128, 56, 56, device="cuda"), torch.randn(83, 128, 3, 3, device="cuda") * 0.03
+    d = B.conv_desc(x.shape, w.shape, 1, 1, 1, B.F32, B.ACT_NONE)
+    B.cprune_clear_tile_cache()
+    if timed:
+        B.cprune_select_tile(d, x, w, iters=2)
+    v, was_timed = B.cprune_cached_tile(d)
+    assert was_timed == timed
+    need, asked = B.cprune_conv_workspace_bytes(d, v), []
+    make = B._ws
+    monkeypatch.setattr(B, "_ws", lambda nbytes, device: asked.append(nbytes) or make(nbytes, device))
+    y = B.cprune_conv2d_bn_relu(d, x, w)
+    assert asked == [need] and need < B.cprune_conv_workspace_bytes(d, -1) // 10
+    assert torch.equal(y, B.cprune_conv2d_bn_relu(d, x, w, None, None, v))
+    B.cprune_clear_tile_cache()
