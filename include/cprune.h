@@ -231,11 +231,12 @@ int cprune_conv2d_bn_relu(const cprune_conv_desc* desc, const void* x, const voi
  * Variant selection by timing on the device (paper Section 3.1, Fig. 3: for each
  * task the compiler generates candidate programs and keeps the one that runs
  * fastest on the target; layers of equal shape share a task).  Times every
- * variant that supports desc with `warmup` untimed and `iters` timed launches on
+ * variant that supports desc (split variants, which pack the weights on every call, from 0.2
+ * GFLOP up) with `warmup` untimed and `iters` timed launches on
  * the caller's buffers (y and ws are overwritten), remembers the fastest for
  * this shape (process-wide, keyed by every field of desc) and returns it.
  * all_ms_out: host [cprune_num_tile_variants()] per-launch ms, < 0 where
- * unsupported; may be NULL.  variant_out / best_ms_out: host.  Synchronises.
+ * not timed; may be NULL.  variant_out / best_ms_out: host.  Synchronises.
  */
 int cprune_select_tile(const cprune_conv_desc* desc, const void* x, const void* w_folded,
                        const float* bias, const void* residual, void* y, void* ws,

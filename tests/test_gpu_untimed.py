@@ -37,11 +37,13 @@ def test_fully_connected_layer_on_a_map(c, hw, o, batch, split):
     assert float((y - ref).norm() / ref.norm()) < 2e-6      # 12544 terms in fp32
 
 
-@pytest.mark.parametrize("shape", [(1, 16, 8, 24, 3, 1), (2, 64, 14, 45, 3, 2), (1, 256, 14, 300, 3, 1)])   # n, c_in, hw, c_out, k, stride
+@pytest.mark.parametrize("shape", [(1, 16, 8, 24, 3, 1), (2, 64, 14, 45, 3, 2), (1, 256, 14, 300, 3, 1), (10, 54, 54, 5, 5, 1)])
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
 def test_timing_tries_every_variant_that_runs(shape, dtype):
-    """However small the layer, cprune_select_tile times each variant that runs it and fits the scratch."""
+    """cprune_select_tile times each variant that runs the layer and fits the scratch; the split kernel, which costs a launch
+    more per call, from 0.2 GFLOP up."""
     n, c, hw, o, k, stride = shape
+    large = 2 * n * o * c * k * k * (-(-hw // stride)) ** 2 >= 2e8
     td = B.TORCH_DTYPE[dtype]
     x, w = torch.randn(n, c, hw, hw, device="cuda").to(td), torch.randn(o, c, k, k, device="cuda").to(td)
     d = B.conv_desc(x.shape, w.shape, stride, k // 2, 1, dtype)
@@ -55,6 +57,8 @@ def test_timing_tries_every_variant_that_runs(shape, dtype):
         except B.CPruneError as e:
             assert e.status == B.ERR_UNSUPPORTED
             runs = False
+        if "conv_split" in B.cprune_tile_variant_name(v, False, dtype):
+            runs = runs and large
         assert (ms[v] > 0) == runs, (v, B.cprune_tile_variant_name(v, False, dtype))
     B.cprune_clear_tile_cache()
 
