@@ -34,35 +34,35 @@ if ROOT not in sys.path:
 # to the kernel sources they were measured on: TRAFFIC_SOURCE_HASH is kernel_source_hash() of that tree,
 # and any change to a file under csrc/ since then reports null instead of a stale figure (as does a
 # selection that runs a kernel on a layer it was not profiled on).
-TRAFFIC_SOURCE_HASH = "742727968da6a9ad"
+TRAFFIC_SOURCE_HASH = "6ea4384bb925dc03"
 TRAFFIC = {
-    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3350377,
-    ("conv_split_kernel<float, false, 2, 2, 1, 2, 2, 2>", 64, "conv3"): 11261480,
-    ("conv_split_kernel<float, false, 2, 2, 1, 2, 4, 4>", 64, "conv3"): 11438611,
-    ("conv_split_kernel<float, false, 4, 1, 1, 1, 4, 2>", 64, "conv3"): 11234859,
-    ("conv_split_kernel<float, false, 2, 2, 1, 2, 2, 2>", 64, "conv4"): 11636471,
-    ("conv_split_kernel<float, false, 2, 2, 1, 2, 4, 4>", 64, "conv4"): 11786981,
-    ("conv_split_kernel<float, false, 4, 1, 1, 1, 4, 2>", 64, "conv4"): 11645686,
-    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv5"): 5613106,
-    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv5"): 5709350,
-    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv6"): 14330536,
-    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv6"): 14403231,
-    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv7"): 17857518,
-    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv7"): 17947620,
-    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv8"): 10622233,
-    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv8"): 11436727,
-    ("conv_wave_kernel<float, 1, 2, 4>", 64, "conv9"): 15058162,
-    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv9"): 15057138,
-    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv9"): 20934546,
-    ("conv_wave_kernel<float, 1, 2, 4>", 64, "conv10"): 11493054,
-    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv10"): 11492030,
-    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv10"): 18687239,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7678851,
-    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv11"): 7690114,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392605,
-    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv12"): 6403868,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv13"): 7768422,
-    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537793,
+    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3350372,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 2, 2>", 64, "conv3"): 11261465,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 4, 4>", 64, "conv3"): 11438595,
+    ("conv_split_kernel<float, false, 4, 1, 1, 1, 4, 2>", 64, "conv3"): 11234845,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 2, 2>", 64, "conv4"): 11636431,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 4, 4>", 64, "conv4"): 11786940,
+    ("conv_split_kernel<float, false, 4, 1, 1, 1, 4, 2>", 64, "conv4"): 11645645,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv5"): 5613091,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv5"): 5709335,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv6"): 14330492,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv6"): 14403187,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv7"): 17857453,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv7"): 17947554,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv8"): 10622197,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv8"): 11436688,
+    ("conv_wave_kernel<float, 1, 2, 4>", 64, "conv9"): 15058109,
+    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv9"): 15057085,
+    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv9"): 20934482,
+    ("conv_wave_kernel<float, 1, 2, 4>", 64, "conv10"): 11493011,
+    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv10"): 11491987,
+    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv10"): 18687182,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7678823,
+    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv11"): 7690086,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392581,
+    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv12"): 6403844,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv13"): 7768392,
+    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537765,
 }
 
 
