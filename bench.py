@@ -34,35 +34,35 @@ if ROOT not in sys.path:
 # to the kernel sources they were measured on: TRAFFIC_SOURCE_HASH is kernel_source_hash() of that tree,
 # and any change to a file under csrc/ since then reports null instead of a stale figure (as does a
 # selection that runs a kernel on a layer it was not profiled on).
-TRAFFIC_SOURCE_HASH = "6ea4384bb925dc03"
+TRAFFIC_SOURCE_HASH = "cacd099d71854360"
 TRAFFIC = {
-    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3350372,
-    ("conv_split_kernel<float, false, 2, 2, 1, 2, 2, 2>", 64, "conv3"): 11261465,
-    ("conv_split_kernel<float, false, 2, 2, 1, 2, 4, 4>", 64, "conv3"): 11438595,
-    ("conv_split_kernel<float, false, 4, 1, 1, 1, 4, 2>", 64, "conv3"): 11234845,
-    ("conv_split_kernel<float, false, 2, 2, 1, 2, 2, 2>", 64, "conv4"): 11636431,
-    ("conv_split_kernel<float, false, 2, 2, 1, 2, 4, 4>", 64, "conv4"): 11786940,
-    ("conv_split_kernel<float, false, 4, 1, 1, 1, 4, 2>", 64, "conv4"): 11645645,
-    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv5"): 5613091,
-    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv5"): 5709335,
-    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv6"): 14330492,
-    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv6"): 14403187,
-    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv7"): 17857453,
-    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv7"): 17947554,
-    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv8"): 10622197,
-    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv8"): 11436688,
-    ("conv_wave_kernel<float, 1, 2, 4>", 64, "conv9"): 15058109,
-    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv9"): 15057085,
-    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv9"): 20934482,
-    ("conv_wave_kernel<float, 1, 2, 4>", 64, "conv10"): 11493011,
-    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv10"): 11491987,
-    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv10"): 18687182,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7678823,
-    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv11"): 7690086,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392581,
-    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv12"): 6403844,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv13"): 7768392,
-    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537765,
+    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3350370,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 2, 2>", 64, "conv3"): 11261458,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 4, 4>", 64, "conv3"): 11438588,
+    ("conv_split_kernel<float, false, 4, 1, 1, 1, 4, 2>", 64, "conv3"): 11234837,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 2, 2>", 64, "conv4"): 11636410,
+    ("conv_split_kernel<float, false, 2, 2, 1, 2, 4, 4>", 64, "conv4"): 11786919,
+    ("conv_split_kernel<float, false, 4, 1, 1, 1, 4, 2>", 64, "conv4"): 11645625,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv5"): 5613084,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv5"): 5709328,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv6"): 14330471,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv6"): 14403166,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv7"): 17858092,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv7"): 17947521,
+    ("conv_split_kernel<float, false, 1, 1, 4, 1, 2, 2>", 64, "conv8"): 10622179,
+    ("conv_split_kernel<float, false, 1, 1, 4, 2, 2, 2>", 64, "conv8"): 11436669,
+    ("conv_wave_kernel<float, 1, 2, 4>", 64, "conv9"): 15058082,
+    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv9"): 15057058,
+    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv9"): 20934450,
+    ("conv_wave_kernel<float, 1, 2, 4>", 64, "conv10"): 11492990,
+    ("conv_wave_kernel<float, 2, 2, 4>", 64, "conv10"): 11491966,
+    ("conv_wave_kernel<float, 5, 1, 3>", 64, "conv10"): 18687154,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7678809,
+    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv11"): 7690071,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392570,
+    ("conv_ksplit_kernel<float, 1, 8>", 64, "conv12"): 6403832,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv13"): 7768378,
+    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537751,
 }
 
 

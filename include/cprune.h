@@ -231,7 +231,7 @@ int cprune_conv2d_bn_relu(const cprune_conv_desc* desc, const void* x, const voi
  * Variant selection by timing on the device (paper Section 3.1, Fig. 3: for each
  * task the compiler generates candidate programs and keeps the one that runs
  * fastest on the target; layers of equal shape share a task).  Times every
- * variant that supports desc (split variants, which pack the weights on every call, from 0.2
+ * variant that supports desc (split variants, which pack the weights on every call, from 0.3
  * GFLOP up) with `warmup` untimed and `iters` timed launches on
  * the caller's buffers (y and ws are overwritten), remembers the fastest for
  * this shape (process-wide, keyed by every field of desc) and returns it.

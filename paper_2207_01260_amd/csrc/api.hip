@@ -55,13 +55,14 @@ void remember_variant(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
   g_cache[key_of(d, lay)] = v;
 }
 
-// Whether a choice considers the split kernel: inside a handle always; in the boundary's layout from 0.2 GFLOP up where
+// Whether a choice considers the split kernel: inside a handle always; in the boundary's layout from 0.3 GFLOP up where
 // variants are timed and from 0.6 untimed, because there the weights are packed on every call, by a launch of its own (4-8 us of
 // the device, 3 us of the caller's thread, which bounds calls of under 20 us).  Timed, device time of this kernel / the best
 // other, whole call: nine layers of 0.002-0.06 GFLOP 7.5-10.9 / 7.8-12.1 us, 17-19 / 14-17; 0.22 (89 -> 21 at 33x33 b6 bf16)
-// 11.0 / 13.4, 17.8 / 15; 0.27 14.9 / 16.8, 16.9 / 17; 0.3-0.4 13.0-16.5 / 17.7-34, 17-18 / 18-34.  Untimed, 128 -> 83 filters at
-// 56x56, batch 8, 74 -> 44 us in fp32 and 38 -> 22 us in bf16; on 232 layers under 0.8 GFLOP a line at 0.6 loses 5.5 % of the device
-// time to the better kernel on average, one at 0.2 4.3 %, always the general kernel 7.1 %, always this one 14 %.
+// 11.0 / 13.4, 17.8 / 15; 0.24 (28 -> 11 at 58x58 b13 fp32), whole call 16.2 / 14.4; 0.27 14.9 / 16.8, 16.9 / 17; three of 0.30-0.39
+// 13.0-16.5 / 17.7-34, 17-18 / 18-34.  Untimed, 128 -> 83 filters at 56x56, batch 8, 74 -> 44 us in fp32 and 38 -> 22 us in bf16;
+// on 232 layers under 0.8 GFLOP a line at 0.6 loses 5.5 % of the device time to the better kernel on average, one at 0.2 4.3 %,
+// always the general kernel 7.1 %, always this one 14 %.
 static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay, double line) {
   const long ho = conv_out_dim(d.h, d.kh, d.stride, d.pad), wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
   return lay.nhwc || 2.0 * (double)d.n * ho * wo * d.c_out * d.c_in * d.kh * d.kw >= line;
@@ -163,7 +164,7 @@ static int select_tile_impl(const cprune_conv_desc& d, const void* x, const void
     if (d.groups == 1) {
       if (!variant_supports(d, v, lay)) continue;
       ++supported;
-      if (variant(v).split && !split_pays(d, lay, 2e8)) continue;
+      if (variant(v).split && !split_pays(d, lay, 3e8)) continue;
       if (conv_ws_bytes(d, v, lay) > ws_bytes) continue;  // not timed: the caller's scratch cannot run it
     }
     for (int i = 0; i < warmup && rc == CPRUNE_OK; ++i) rc = conv_dispatch(d, x, w, bias, residual, y, v, ws, ws_bytes, s, lay);
