@@ -360,8 +360,9 @@ int cprune_net_layer_fused(const cprune_net* net, int layer, int* fused_out);
  * block whose depthwise layer is `layer`: enable != 0 runs the block as one kernel, 0 leaves
  * the expansion on its own (the depthwise layer stays inside its reader's kernel).
  * cprune_net_fuse_depthwise on the same layer also leaves the one-kernel form.
- * CPRUNE_ERR_UNSUPPORTED when the layer heads no such block or the block's input patch does not
- * fit the local memory of a compute unit.  Recorded graphs are dropped.  Not to be called while
+ * CPRUNE_ERR_UNSUPPORTED when the layer heads no such block or the block's weights and input patch do not
+ * fit the local memory of a compute unit (such a block runs as one kernel only where cprune_net_create timed it as
+ * the fastest form; enable = 0 is accepted there).  Recorded graphs are dropped.  Not to be called while
  * a forward is in flight.  cprune_net_layer_fused reports 1 for the expansion and the
  * depthwise layer of a block that runs as one kernel. */
 int cprune_net_fuse_block(cprune_net* net, int layer, int enable);

@@ -372,12 +372,17 @@ struct NetLayer {
   bool alias = false;         // max-pool folded into its producer: no kernel, act is the producer's buffer
   bool map2x2 = false;        // 3x3 / stride 1 / pad 1 conv on a 2x2 map, run as one matrix over the whole map
   int fuse_dw = -1;           // 1x1 conv: index of the depthwise layer computed inside its kernel, or -1
-  int dw_ks = 1;              // ... and how many groups of four wavefronts share one pixel block there
+  int dw_ks = 0;              // ... and how many wavefronts share a strip there (1, 2, 4, 8; 0: not timed)
+  int dw_low = 1;             // ... and whether its strips are the low ones
   bool fused_away = false;    // depthwise conv that runs inside its consumer's kernel (no launch, no activation)
   int dw_reader = -1;         // depthwise conv that may run inside the 1x1 conv dw_reader's kernel
   int fuse_block = -1;        // 1x1 conv with fuse_dw set: index of the 1x1 expansion in front of that depthwise
                               // layer when the whole block (expansion, depthwise, this projection) is one kernel
+  int block_ks = 0;           // ... and how many wavefronts share a strip there
+  int block_low = 1;          // ... and whether its strips are the low ones
   int block_expand = -1;      // depthwise conv: the expansion layer that may join it and dw_reader in one kernel
+  void* w_expand = nullptr;   // expansion of such a block: weights once more, in that kernel's operand order
+  void* w_proj = nullptr;     // 1x1 conv that may run behind a depthwise layer in one kernel: weights in its operand order
   int fuse_stem = -1;         // 3x3 conv: index of the first layer (on the image) computed inside its kernel, or -1
   int stem_reader = -1;       // first layer that may run inside the 3x3 conv stem_reader's kernel
   void* w_stem = nullptr;     // weights packed for the first-layer kernel
@@ -570,87 +575,80 @@ static int net_run_stem2(cprune_net* net, int i, int n, const void* x, void* dst
   return launch_conv_stem2(d2, layer_layout(L), x, F.d.c_in, F.w_stem, F.b, F.d.c_out, F.d.act, L.w, L.b, dst, s);
 }
 
-// Depthwise layer P.fuse_dw and the 1x1 layer i in one kernel: reads the depthwise layer's input.
-static int net_run_dwproj(cprune_net* net, int i, int n, void* dst, hipStream_t s) {
+// Strips of a map in the inverted-residual kernel.
+static void mbrow_tiles(const NetLayer& D, int mb, int low, MbArgs* a) {
+  const int hl = mbrow_halo_left(D.d.k, D.d.stride), hr = mbrow_halo_right(D.d.k, D.d.stride), step = 16 - hl - hr;
+  // two images side by side where an image with the columns its windows reach past the right edge fits eight lanes
+  const int last = D.d.stride == 1 ? D.w_in + hr : D.w_out + 1;
+  a->ipt = last <= 8 ? 2 : 1;
+  a->tiles_x = a->ipt == 2 || D.w_out <= 16 ? 1 : (D.w_out - hl - hr + step - 1) / step;
+  const int r = mbrow_rows(D.d.k, D.d.stride, mb, low);
+  a->tiles_y = (D.h_out + r - 1) / r;
+}
+
+// Wavefronts that share a strip at n images, where none were timed: doubled from `ks` while the strips leave most of the chip idle
+// (1024 SIMDs) and every wavefront still has a chunk.  Timed with 1 / 2 / 4 / 8: MobileNetV2 at batch 64, 32 -> 92 -> 32 at 28x28, 896
+// strips 18.8 / 17.6 / 21.0 / 35.3 us; 64 -> 330 -> 64 at 14x14, 256 strips 43 / 43 / 26.8 / 26.2.
+static int mbrow_auto_ks(const MbArgs& a, int n, int tiles_m, int ks) {
+  const long strips = (long)((n + a.ipt - 1) / a.ipt) * a.tiles_y * a.tiles_x * tiles_m;
+  while (ks < 8 && strips * ks < 1024 && 2 * ks <= a.nchunk) ks *= 2;
+  return ks;
+}
+
+// Depthwise layer P.fuse_dw and the 1x1 layer i in one kernel, reading the depthwise layer's input; with the expansion
+// P.fuse_block in it as well, reading the expansion's input.
+static int net_run_mbrow(cprune_net* net, int i, int n, void* dst, hipStream_t s) {
   const NetLayer& P = net->layers[i];
   const NetLayer& D = net->layers[P.fuse_dw];
+  const NetLayer* E = P.fuse_block >= 0 ? &net->layers[P.fuse_block] : nullptr;
   const size_t es = dtype_size(net->dtype);
-  DwProjArgs a;
-  a.x = net->layers[D.d.input].act;
-  a.wdw = D.w; a.bdw = D.b; a.wp = P.w; a.bp = P.b;
+  int mb = 0, xh = 0;
+  if (!mbrow_form(net->dtype, P.d.c_out, E ? E->cp_in : 0, &mb, &xh)) return CPRUNE_ERR_UNSUPPORTED;
+  MbArgs a;
+  a.x = net->layers[E ? E->d.input : D.d.input].act;
+  a.we = E ? E->w_expand : nullptr; a.be = E ? E->b : nullptr;
+  a.wdw = D.w; a.bdw = D.b; a.wp = P.w_proj; a.bp = P.b;
   a.res = P.d.residual >= 0 ? net->layers[P.d.residual].act : nullptr;
   a.y = dst;
   a.N = n; a.H = D.h_in; a.W = D.w_in; a.Ho = D.h_out; a.Wo = D.w_out;
-  a.Ce = D.d.c_out; a.Cpe = D.cp_in; a.O = P.d.c_out; a.Cop = P.cp_out;
-  a.pad = D.d.pad; a.act_dw = D.d.act; a.act_out = P.d.act;
-  const int mb = P.d.c_out <= 32 ? 2 : (P.d.c_out <= 64 ? 4 : 8);
-  a.tiles_y = (a.Ho + 7) / 8; a.tiles_x = (a.Wo + 7) / 8; a.tiles_m = (a.O + mb * 16 - 1) / (mb * 16);
-  a.x_bytes = (unsigned)((size_t)n * a.H * a.W * a.Cpe * es);
-  a.wp_bytes = (unsigned)((size_t)a.O * a.Cpe * es);
+  a.Cpi = E ? E->cp_in : 0; a.Ce = D.d.c_out; a.Cpe = D.cp_in; a.O = P.d.c_out; a.Cop = P.cp_out;
+  a.act_e = E ? E->d.act : CPRUNE_ACT_NONE; a.act_dw = D.d.act; a.act_out = P.d.act;
+  const int low = E ? P.block_low : P.dw_low;
+  mbrow_tiles(D, mb, low, &a);
+  a.magic_x = a.tiles_x > 1 ? (unsigned)((0x100000000ull + a.tiles_x - 1) / a.tiles_x) : 0u;
+  a.magic_y = a.tiles_y > 1 ? (unsigned)((0x100000000ull + a.tiles_y - 1) / a.tiles_y) : 0u;
+  a.x_bytes = (unsigned)((size_t)n * a.H * a.W * (E ? a.Cpi : a.Cpe) * es);
+  a.we_bytes = E ? (unsigned)expand_packed_bytes(a.Ce, xh, net->dtype) : 0u;
+  a.wp_bytes = (unsigned)rows_packed_bytes(a.O, a.Cpe, net->dtype);
   a.wdw_bytes = (unsigned)((size_t)D.d.k * D.d.k * a.Cpe * es);
-  a.vec_out = (a.Cop % 4) == 0 ? 1 : 0;
-  dim3 grid((unsigned)(n * a.tiles_y * a.tiles_x * a.tiles_m));
+  a.y_bytes = (unsigned)((size_t)n * a.Ho * a.Wo * a.Cop * es);
+  a.nchunk = (int)((a.Cpe * es + 63) / 64);
+  a.slots = 0;
+  const int tiles_m = (a.O + mb * 16 - 1) / (mb * 16);
+  const dim3 grid((unsigned)((n + a.ipt - 1) / a.ipt * a.tiles_y * a.tiles_x), (unsigned)tiles_m);
+  int ks = E ? P.block_ks : P.dw_ks;                        // the timed choice holds at the full batch
+  if (!ks || n < net->max_batch) ks = mbrow_auto_ks(a, n, tiles_m, ks ? ks : 1);
   int rc;
-  if (net->dtype == CPRUNE_F32) rc = launch_dwproj_f32(D.d.k, D.d.stride, mb, P.dw_ks, grid, s, a);
-  else if (net->dtype == CPRUNE_F16) rc = launch_dwproj_f16(D.d.k, D.d.stride, mb, P.dw_ks, grid, s, a);
-  else rc = launch_dwproj_bf16(D.d.k, D.d.stride, mb, P.dw_ks, grid, s, a);
+  if (net->dtype == CPRUNE_F32) rc = launch_mbrow_f32(D.d.k, D.d.stride, mb, xh, low, grid, ks, s, a);
+  else if (net->dtype == CPRUNE_F16) rc = launch_mbrow_f16(D.d.k, D.d.stride, mb, xh, low, grid, ks, s, a);
+  else rc = launch_mbrow_bf16(D.d.k, D.d.stride, mb, xh, low, grid, ks, s, a);
   if (rc != CPRUNE_OK) return rc;
   CPRUNE_LAUNCH_CHECK();
   return CPRUNE_OK;
 }
 
-// Expansion P.fuse_block, depthwise P.fuse_dw and projection i in one kernel: reads the expansion's input.
-static bool mbconv_fits(const cprune_net& net, const NetLayer& E, const NetLayer& D, const NetLayer& P, int* mb_out,
-                        size_t* lds_out) {
-  const int es = (int)dtype_size(net.dtype);
+// Which blocks cprune_net_fuse_block may turn into one kernel at the caller's wish: up to 128 projection filters and layers
+// whose weights, input patch (8 x 8 outputs with the halo) and chunk tiles stay within the 160 KiB of a compute unit.
+// Blocks beyond that are one kernel only where cprune_net_create timed them so.
+static bool block_on_request(const cprune_net& net, const NetLayer& E, const NetLayer& D, const NetLayer& P) {
+  const size_t es = dtype_size(net.dtype);
   if (P.d.c_out > 128) return false;
-  const int mb = P.d.c_out <= 32 ? 2 : (P.d.c_out <= 64 ? 4 : 8);
-  MbConvArgs lay;
-  const size_t lds = mbconv_lds_layout(D.d.k, D.d.stride, mb, E.cp_in, D.cp_in, es, &lay);
-  if (lds > 160 * 1024) return false;      // the block's weights do not fit beside its tiles
-  const int ph = 7 * D.d.stride + D.d.k, npatchp = (ph * ph + 31) / 32 * 32;
-  if ((long)npatchp * lay.xq > 256L * 10) return false;   // the next patch travels in ten registers per thread
-  if (mb_out) *mb_out = mb;
-  if (lds_out) *lds_out = lds;
-  return true;
-}
-
-static int net_run_mbconv(cprune_net* net, int i, int n, void* dst, hipStream_t s) {
-  const NetLayer& P = net->layers[i];
-  const NetLayer& D = net->layers[P.fuse_dw];
-  const NetLayer& E = net->layers[P.fuse_block];
-  const size_t es = dtype_size(net->dtype);
-  int mb = 0;
-  size_t lds = 0;
-  if (!mbconv_fits(*net, E, D, P, &mb, &lds)) return CPRUNE_ERR_UNSUPPORTED;
-  MbConvArgs a;
-  mbconv_lds_layout(D.d.k, D.d.stride, mb, E.cp_in, D.cp_in, (int)es, &a);
-  a.x = net->layers[E.d.input].act;
-  a.we = E.w; a.be = E.b; a.wdw = D.w; a.bdw = D.b; a.wp = P.w; a.bp = P.b;
-  a.res = P.d.residual >= 0 ? net->layers[P.d.residual].act : nullptr;
-  a.y = dst;
-  a.N = n; a.H = D.h_in; a.W = D.w_in; a.Ho = D.h_out; a.Wo = D.w_out;
-  a.Cpi = E.cp_in; a.Ce = D.d.c_out; a.Cpe = D.cp_in; a.O = P.d.c_out; a.Cop = P.cp_out;
-  a.pad = D.d.pad; a.act_e = E.d.act; a.act_dw = D.d.act; a.act_out = P.d.act;
-  a.tiles_y = (a.Ho + 7) / 8; a.tiles_x = (a.Wo + 7) / 8;
-  a.x_bytes = (unsigned)((size_t)n * a.H * a.W * a.Cpi * es);
-  a.we_bytes = (unsigned)((size_t)a.Ce * a.Cpi * es);
-  a.wp_bytes = (unsigned)((size_t)a.O * a.Cpe * es);
-  a.wdw_bytes = (unsigned)((size_t)D.d.k * D.d.k * a.Cpe * es);
-  a.vec_out = (a.Cop % 4) == 0 ? 1 : 0;
-  // as many work-groups as stay resident (LDS decides), each walking over its share of the pixel blocks
-  const long ntiles = (long)n * a.tiles_y * a.tiles_x;
-  long per_cu = (long)(160 * 1024 / lds);
-  per_cu = per_cu > 4 ? 4 : (per_cu < 1 ? 1 : per_cu);
-  const long workers = ntiles < 256 * per_cu ? ntiles : 256 * per_cu;
-  dim3 grid((unsigned)workers);
-  int rc;
-  if (net->dtype == CPRUNE_F32) rc = launch_mbconv_f32(D.d.k, D.d.stride, mb, grid, lds, s, a);
-  else if (net->dtype == CPRUNE_F16) rc = launch_mbconv_f16(D.d.k, D.d.stride, mb, grid, lds, s, a);
-  else rc = launch_mbconv_bf16(D.d.k, D.d.stride, mb, grid, lds, s, a);
-  if (rc != CPRUNE_OK) return rc;
-  CPRUNE_LAUNCH_CHECK();
-  return CPRUNE_OK;
+  const size_t filters = P.d.c_out <= 32 ? 32 : P.d.c_out <= 64 ? 64 : 128;
+  const size_t ph = 7 * D.d.stride + D.d.k, patch = (ph * ph + 31) / 32 * 32, kk = (size_t)D.d.k * D.d.k;
+  const size_t in = (E.cp_in * es + 63) / 64 * 64, chunks = (D.cp_in * es + 63) / 64, cc = 64 / es;
+  if (patch * in / 16 > 2560) return false;
+  const size_t lds = patch * (in + 16) + 2 * (patch + 64) * 80 + chunks * (cc * (in + 16) + filters * 80 + kk * 64 + 2 * cc * 4);
+  return lds <= 160 * 1024;
 }
 
 // The variant a layer of a handle for larger batches runs at n images, where none was timed for that shape.  Without a timed
@@ -694,8 +692,7 @@ static int net_run_layer(cprune_net* net, int i, int n, const void* x, void* out
   const void* src = L.d.input < 0 ? (L.nchw_in ? x : net->x_cl) : net->layers[L.d.input].act;
   void* dst = out_override ? out_override : L.act;
   if (L.fused_away) return CPRUNE_OK;
-  if (L.fuse_block >= 0) return net_run_mbconv(net, i, n, dst, s);
-  if (L.fuse_dw >= 0) return net_run_dwproj(net, i, n, dst, s);
+  if (L.fuse_dw >= 0) return net_run_mbrow(net, i, n, dst, s);
   if (L.fuse_stem >= 0) return net_run_stem2(net, i, n, x, dst, s);
   if (L.stem7) return net_run_stem7(net, i, n, src, dst, s);
   if (L.stem) return net_run_stem(net, i, n, src, dst, s);
@@ -744,6 +741,31 @@ static int time_layers(cprune_net* net, const int* layers, int n_layers, int bat
   if (rc != CPRUNE_OK) return rc;
   if (e != hipSuccess) { set_last_hip_error(e); return CPRUNE_ERR_DEVICE; }
   *ms_out = best;
+  return CPRUNE_OK;
+}
+
+// Times the given layers, the last of which runs as one kernel with those before it, with tall and low strips and with the
+// wavefronts per strip that the rule for untimed layers names, or twice as many; leaves the fastest in *low and *ks.
+static int time_mbrow(cprune_net* net, const int* layers, int n_layers, int* low, int* ks, float* best, hipStream_t s) {
+  const NetLayer& P = net->layers[layers[n_layers - 1]];
+  const NetLayer& D = net->layers[P.fuse_dw];
+  int mb = 0, xh = 0, best_low = 0, best_ks = 0;
+  mbrow_form(net->dtype, P.d.c_out, P.fuse_block >= 0 ? net->layers[P.fuse_block].cp_in : 0, &mb, &xh);
+  for (int l = 0; l < 2; ++l) {
+    if (l && mbrow_rows(D.d.k, D.d.stride, mb, 0) == mbrow_rows(D.d.k, D.d.stride, mb, 1)) break;
+    MbArgs a;
+    mbrow_tiles(D, mb, l, &a);
+    a.nchunk = (int)((D.cp_in * dtype_size(net->dtype) + 63) / 64);
+    const int k0 = mbrow_auto_ks(a, net->max_batch, (P.d.c_out + mb * 16 - 1) / (mb * 16), 1);
+    for (int k = k0; k <= 8 && k <= 2 * k0; k *= 2) {
+      float ms = 0.f;
+      *low = l; *ks = k;
+      const int rc = time_layers(net, layers, n_layers, net->max_batch, nullptr, s, &ms);
+      if (rc != CPRUNE_OK) return rc;
+      if (!best_ks || ms < *best) { *best = ms; best_ks = k; best_low = l; }
+    }
+  }
+  *low = best_low; *ks = best_ks;
   return CPRUNE_OK;
 }
 
@@ -1100,91 +1122,83 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
   }
 
   // A depthwise conv whose only reader is a 1x1 conv can run inside that conv's kernel: the
-  // expanded activations are then read once and never written.  It pays on large maps (enough
-  // 8x8 pixel blocks to fill the chip); with tune != 0 both forms are timed and the faster kept.
+  // expanded activations are then read once and never written.  When its input is a 1x1 expansion that nobody
+  // else reads, the whole inverted-residual block can be one kernel, and they never reach memory at all.  With
+  // tune != 0 the forms are timed and the fastest kept; otherwise a pair is fused on large maps (enough
+  // 8x8 pixel blocks to fill the chip) and only cprune_net_fuse_block turns a whole block into one kernel.
   for (int i = 0; i < n_layers && rc == CPRUNE_OK; ++i) {
     NetLayer& D = net->layers[i];
     const cprune_layer_desc& dd = D.d;
     if (!(dd.kind == CPRUNE_LAYER_CONV && dd.groups != 1 && dd.input >= 0 && dd.residual < 0)) continue;
     if (!((dd.k == 3 || dd.k == 5) && (dd.stride == 1 || dd.stride == 2) && dd.pad == dd.k / 2)) continue;
-    int reader = -1, readers = 0;
-    for (int j = 0; j < n_layers; ++j) {
-      if (net->layers[j].d.input == i) { reader = j; ++readers; }
-      if (net->layers[j].d.residual == i) readers += 2;
-    }
-    if (readers != 1 || i == n_layers - 1) continue;
+    auto only_reader = [&](int layer) -> int {      // the one layer that reads it, as its input; -1: none or several
+      int reader = -1, readers = 0;
+      for (int j = 0; j < n_layers; ++j) {
+        if (net->layers[j].d.input == layer) { reader = j; ++readers; }
+        if (net->layers[j].d.residual == layer) readers += 2;
+      }
+      return readers == 1 ? reader : -1;
+    };
+    const int reader = only_reader(i);
+    if (reader < 0 || i == n_layers - 1) continue;
     NetLayer& P = net->layers[reader];
     const cprune_layer_desc& pd = P.d;
     if (!(pd.kind == CPRUNE_LAYER_CONV && pd.groups == 1 && pd.k == 1 && pd.stride == 1 && pd.pad == 0)) continue;
     if (P.cp_out != round_up_vec(pd.c_out, dtype) || P.nchw_in || P.map2x2 || P.fused_pool) continue;
     D.dw_reader = reader;
-    const int mt = pd.c_out <= 32 ? 32 : (pd.c_out <= 64 ? 64 : 128);
-    const long groups = (long)max_batch * ((D.h_out + 7) / 8) * ((D.w_out + 7) / 8) * ((pd.c_out + mt - 1) / mt);
-    // Few pixel blocks (small maps) leave one group of four wavefronts per compute unit, whose channel
-    // loop is a chain of waits: then 2 or 4 groups share a block and split the channel chunks.
-    const int ks_max = (dd.k == 3 && dd.stride == 1) ? 4 : 2;
-    P.dw_ks = groups <= 320 ? ks_max : (groups <= 640 ? 2 : 1);
-    bool fuse = groups >= 512;
-    if (tune) {
-      const int pair[2] = {i, reader};
-      float apart = 0.f, best = 0.f;
-      D.fused_away = false; P.fuse_dw = -1;
-      rc = time_layers(net, pair, 2, max_batch, nullptr, s, &apart);
-      D.fused_away = true; P.fuse_dw = i;
-      int best_ks = 1;
-      for (int ks = 1; ks <= ks_max && rc == CPRUNE_OK; ks *= 2) {
-        float ms = 0.f;
-        P.dw_ks = ks;
-        rc = time_layers(net, pair, 2, max_batch, nullptr, s, &ms);
-        if (ks == 1 || ms < best) { best = ms; best_ks = ks; }
-      }
-      P.dw_ks = best_ks;
-      fuse = best < apart;
+    P.w_proj = P.w_rows;
+    if (!P.w_proj) {
+      rc = dev_alloc(rows_packed_bytes(pd.c_out, P.cp_in, dtype), &P.w_proj);
+      if (rc == CPRUNE_OK) rc = launch_repack_rows(P.w, pd.c_out, P.cp_in, dtype, P.w_proj, s);
+      if (rc != CPRUNE_OK) break;
     }
-    D.fused_away = fuse;
-    P.fuse_dw = fuse ? i : -1;
-    if (fuse) P.variant = -1;
-  }
-  // When the depthwise layer's input is a 1x1 expansion that nobody else reads, the whole
-  // inverted-residual block can be one kernel, and the expanded activations never reach memory.
-  // It needs the projection's filters in one tile (at most 128) and all weights of the three layers
-  // in LDS beside the tiles; with tune != 0 it is timed against the layers as decided so far and
-  // taken when faster, otherwise only cprune_net_fuse_block turns it on.
-  for (int i = 0; i < n_layers && rc == CPRUNE_OK; ++i) {
-    NetLayer& D = net->layers[i];
-    if (D.dw_reader < 0 || D.d.input < 0) continue;
-    NetLayer& E = net->layers[D.d.input];
-    NetLayer& P = net->layers[D.dw_reader];
+
+    NetLayer& E = net->layers[dd.input];
     const cprune_layer_desc& ed = E.d;
-    if (!(ed.kind == CPRUNE_LAYER_CONV && ed.groups == 1 && ed.k == 1 && ed.stride == 1 && ed.pad == 0)) continue;
-    if (ed.input < 0 || ed.residual >= 0 || E.nchw_in || E.map2x2 || E.fused_pool || E.fuse_dw >= 0) continue;
-    if (E.cp_out != round_up_vec(ed.c_out, dtype) || E.cp_out != D.cp_in) continue;
-    int readers = 0;
-    for (int j = 0; j < n_layers; ++j) {
-      if (net->layers[j].d.input == D.d.input) ++readers;
-      if (net->layers[j].d.residual == D.d.input) readers += 2;
+    int mb = 0, xh = 0;
+    bool block = ed.kind == CPRUNE_LAYER_CONV && ed.groups == 1 && ed.k == 1 && ed.stride == 1 && ed.pad == 0 && ed.input >= 0 &&
+                 ed.residual < 0 && !E.nchw_in && !E.map2x2 && !E.fused_pool && E.fuse_dw < 0 &&
+                 E.cp_out == round_up_vec(ed.c_out, dtype) && E.cp_out == D.cp_in && only_reader(dd.input) == i &&
+                 mbrow_form(dtype, pd.c_out, E.cp_in, &mb, &xh);
+    const bool on_request = block && block_on_request(*net, E, D, P);
+    block = block && (on_request || tune);
+    if (block) {
+      rc = dev_alloc(expand_packed_bytes(ed.c_out, xh, dtype), &E.w_expand);
+      if (rc == CPRUNE_OK) rc = launch_pack_expand(E.w, ed.c_out, E.cp_in, xh, dtype, E.w_expand, s);
+      if (rc != CPRUNE_OK) break;
+      if (on_request) D.block_expand = dd.input;
     }
-    if (readers != 1 || !mbconv_fits(*net, E, D, P, nullptr, nullptr)) continue;
-    D.block_expand = D.d.input;
-    bool fuse = false;   // untimed, the layers stay apart: so far the one-kernel form has not been the faster one
-    const bool dw_fused = D.fused_away;
+
+    auto set_form = [&](int form) {      // 0: three layers, 1: the depthwise layer inside the projection, 2: one kernel
+      D.fused_away = form > 0;
+      P.fuse_dw = form > 0 ? i : -1;
+      if (block) E.fused_away = form == 2;
+      P.fuse_block = form == 2 ? dd.input : -1;
+    };
+    const long groups = (long)max_batch * ((D.h_out + 7) / 8) * ((D.w_out + 7) / 8) * ((pd.c_out + 127) / 128);
+    int form = groups >= 512 ? 1 : 0;
     if (tune) {
-      float ms[2] = {0.f, 0.f};
-      const int block[3] = {D.d.input, i, D.dw_reader};
-      for (int form = 0; form < 2 && rc == CPRUNE_OK; ++form) {   // 0: as decided so far, 1: one kernel
-        E.fused_away = form == 1;
-        D.fused_away = form == 1 || dw_fused;
-        P.fuse_dw = D.fused_away ? i : -1;
-        P.fuse_block = form == 1 ? D.d.input : -1;
-        rc = time_layers(net, block, 3, max_batch, nullptr, s, &ms[form]);
+      const int layers_of[3] = {dd.input, i, reader};
+      const int* timed = block ? layers_of : layers_of + 1;
+      const int n_timed = block ? 3 : 2;
+      float best = 0.f, ms = 0.f;
+      set_form(0);
+      rc = time_layers(net, timed, n_timed, max_batch, nullptr, s, &best);
+      form = 0;
+      if (rc == CPRUNE_OK && block) {
+        set_form(2);
+        rc = time_mbrow(net, timed, n_timed, &P.block_low, &P.block_ks, &ms, s);
+        if (ms < best) { form = 2; best = ms < 0.8f * best ? 0.f : ms; }     // (far ahead: the third form is not timed)
       }
-      fuse = ms[1] < ms[0];
+      if (rc == CPRUNE_OK && best > 0.f) {
+        set_form(1);
+        rc = time_mbrow(net, timed, n_timed, &P.dw_low, &P.dw_ks, &ms, s);
+        if (ms < best) form = 1;
+      }
     }
-    E.fused_away = fuse;
-    D.fused_away = fuse || dw_fused;
-    P.fuse_dw = D.fused_away ? i : -1;
-    P.fuse_block = fuse ? D.d.input : -1;
-    if (fuse) { P.variant = -1; E.variant = -1; }
+    set_form(form);
+    if (form) P.variant = -1;
+    if (form == 2) E.variant = -1;
   }
   if (rc == CPRUNE_OK) {
     hipError_t e = hipStreamSynchronize(s);
@@ -1390,14 +1404,15 @@ extern "C" int cprune_net_fuse_depthwise(cprune_net* net, int layer, int enable)
 extern "C" int cprune_net_fuse_block(cprune_net* net, int layer, int enable) {
   if (!net || layer < 0 || layer >= (int)net->layers.size()) return CPRUNE_ERR_INVALID_ARG;
   NetLayer& D = net->layers[layer];
-  if (D.dw_reader < 0 || D.block_expand < 0) return CPRUNE_ERR_UNSUPPORTED;
+  if (D.dw_reader < 0) return CPRUNE_ERR_UNSUPPORTED;
+  NetLayer& P = net->layers[D.dw_reader];
+  if (D.block_expand < 0 && (enable || P.fuse_block < 0)) return CPRUNE_ERR_UNSUPPORTED;
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
   drop_graphs(net);
-  NetLayer& P = net->layers[D.dw_reader];
-  NetLayer& E = net->layers[D.block_expand];
+  NetLayer& E = net->layers[D.d.input];
   if (enable) {
     E.fused_away = true; D.fused_away = true;
-    P.fuse_dw = layer; P.fuse_block = D.block_expand;
+    P.fuse_dw = layer; P.fuse_block = D.d.input;
     P.variant = -1; E.variant = -1;
   } else if (P.fuse_block >= 0) {      // back to the depthwise + projection pair in one kernel, expansion on its own
     E.fused_away = false;

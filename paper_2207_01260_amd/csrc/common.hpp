@@ -131,80 +131,51 @@ int launch_pack_split(const void* w, int o, int c, int taps, int khwc, int dt, v
 int launch_repack_map2x2(const void* w, const float* bias, int o, int c, int cp_in, int cp_out,
                          int rows_by_channel, int dt, void* w_out, float* bias_out, hipStream_t s);
 
-// Fused depthwise k x k (+ bias + activation) and the 1x1 convolution behind it, channels-last.
-struct DwProjArgs {
-  const void* x;        // [n][h][w][cpe], expanded activations
-  const void* wdw;      // [k][k][cpe] depthwise weights (folded)
-  const float* bdw;     // [ce] depthwise bias or null
-  const void* wp;       // [o][cpe] projection weights (folded)
-  const float* bp;      // [o] projection bias or null
-  const void* res;      // [n][ho][wo][cop] or null
-  void* y;              // [n][ho][wo][cop]
-  int N, H, W, Ho, Wo, Ce, Cpe, O, Cop;
-  int pad, act_dw, act_out;
-  int tiles_y, tiles_x, tiles_m;
-  unsigned x_bytes, wp_bytes, wdw_bytes;
-  int vec_out;
-};
-
-// k in {3, 5}, stride in {1, 2}, mb in {2, 4, 8} (16-filter blocks per tile), ks in {1, 2, 4} (groups of four
-// wavefronts per work-group that split the channel chunks; 4 only with k = 3 at stride 1); grid = one work-group per
-// (image, 8x8 output block, filter tile).  CPRUNE_ERR_UNSUPPORTED for other combinations.
-int launch_dwproj_f32(int k, int stride, int mb, int ks, dim3 grid, hipStream_t s, const DwProjArgs& a);
-int launch_dwproj_f16(int k, int stride, int mb, int ks, dim3 grid, hipStream_t s, const DwProjArgs& a);
-int launch_dwproj_bf16(int k, int stride, int mb, int ks, dim3 grid, hipStream_t s, const DwProjArgs& a);
-
-// A whole inverted-residual block in one kernel: 1x1 expansion, depthwise k x k, 1x1 projection, channels-last.
-struct MbConvArgs {
-  const void* x;        // [n][h][w][cpi] block input
-  const void* we;       // [ce][cpi] expansion weights (folded)
+// Inverted-residual blocks, channels-last: depthwise k x k (+ bias + activation) and the 1x1 convolution behind it in one
+// kernel, with (xh > 0) or without the 1x1 expansion in front of them.
+struct MbArgs {
+  const void* x;        // xh > 0: [n][h][w][cpi] block input; xh = 0: [n][h][w][cpe] expanded activations
+  const void* we;       // expansion weights from launch_pack_expand, or null
   const float* be;      // [ce] or null
   const void* wdw;      // [k][k][cpe] depthwise weights (folded)
   const float* bdw;     // [ce] or null
-  const void* wp;       // [o][cpe] projection weights (folded)
+  const void* wp;       // [o][cpe] projection weights from launch_repack_rows
   const float* bp;      // [o] or null
   const void* res;      // [n][ho][wo][cop] shortcut or null
   void* y;              // [n][ho][wo][cop]
   int N, H, W, Ho, Wo, Cpi, Ce, Cpe, O, Cop;
-  int pad, act_e, act_dw, act_out;
-  int tiles_y, tiles_x;
-  unsigned x_bytes, we_bytes, wp_bytes, wdw_bytes;
-  int vec_out;
-  int xq;               // 16-byte quads per staged input row: cpi * sizeof(T) rounded up to 64 bytes, / 16
-  unsigned magic_xq;    // division by xq
+  int act_e, act_dw, act_out;
+  int tiles_y, tiles_x; // strips of a map
+  int ipt;              // images side by side in the 16 columns of a strip: 1 or 2
+  unsigned magic_x, magic_y;   // ceil(2^32 / tiles_x), ceil(2^32 / tiles_y), 0 for a divisor of 1
+  unsigned x_bytes, we_bytes, wp_bytes, wdw_bytes, y_bytes;
   int nchunk;           // 64-byte chunks of expanded channels
-  int off_e, off_b, off_we, off_a, off_w, off_bias;   // byte offsets of the LDS regions behind the input patch
+  int slots;            // wavefronts whose sums fit the exchange area (set by the launcher)
 };
 
-// LDS bytes the kernel needs (and the offsets of its regions, xq, nchunk) for a window, stride, filter
-// tile (mb 16-filter blocks), input channel stride cpi, expanded channel stride cpe and element size
-inline size_t mbconv_lds_layout(int k, int s, int mb, int cpi, int cpe, int es, MbConvArgs* a) {
-  const int ph = 7 * s + k, npatch = ph * ph, npatchp = (npatch + 31) / 32 * 32;
-  const int xrow = (cpi * es + 63) / 64 * 64 + 16, row = 64 + 16;
-  const int cc = 64 / es, nchunk = (cpe + cc - 1) / cc;
-  size_t off = (size_t)npatchp * xrow;
-  const int off_e = (int)off; off += (size_t)2 * npatchp * row;   // double buffers of the two chunk tiles
-  const int off_b = (int)off; off += (size_t)2 * 64 * row;
-  const int off_we = (int)off; off += (size_t)nchunk * cc * xrow;
-  const int off_a = (int)off; off += (size_t)nchunk * mb * 16 * row;
-  const int off_w = (int)off; off += (size_t)nchunk * k * k * 64;
-  const int off_bias = (int)off; off += (size_t)2 * nchunk * cc * sizeof(float);
-  if (a) {
-    a->xq = (xrow - 16) / 16;
-    a->magic_xq = (unsigned)((0x100000000ull + a->xq - 1) / a->xq);
-    a->nchunk = nchunk;
-    a->off_e = off_e; a->off_b = off_b; a->off_we = off_we; a->off_a = off_a; a->off_w = off_w; a->off_bias = off_bias;
-  }
-  return off;
+// Output rows a wavefront owns (k in {3, 5}, stride in {1, 2}, mb filter blocks): as many as its registers hold beside the
+// window's weights, multiples or halves of 7 where possible (the maps of the evaluated networks are 7 x 2^n); low = 1: about
+// half as many, for maps whose tall strips leave units idle.
+constexpr int mbrow_rows(int k, int s, int mb, int low) {
+  if (s == 1 && k == 3) return mb <= 4 ? (low ? 4 : 7) : mb == 6 ? (low ? 3 : 5) : (low ? 2 : 3);
+  if (s == 1) return mb <= 2 ? (low ? 2 : 4) : 2;
+  if (k == 3) return mb <= 4 ? (low ? 2 : 4) : 2;
+  return mb <= 4 ? 2 : 1;
 }
-
-// k in {3, 5}, stride in {1, 2}, mb in {2, 4, 8} (the projection has at most 16 * mb filters); grid = persistent
-// work-groups that share the (image, 8x8 output block) list round-robin; lds_bytes from mbconv_lds_layout
-// (at most 160 KiB).
+// columns at the left / right end of a strip whose window reaches into the neighbouring strip
+constexpr int mbrow_halo_left(int k, int s) { return s == 1 ? k / 2 : 1; }
+constexpr int mbrow_halo_right(int k, int s) { return s == 1 ? k / 2 : k == 5 ? 1 : 0; }
+// The smallest built form for c_out filters and an input of cp_in channels (0: no expansion): mb 16-filter blocks and xh
+// 32-byte units of a pixel's input.  false: none (c_out above 128 with an expansion, or too many input channels).
+bool mbrow_form(int dt, int c_out, int cp_in, int* mb, int* xh);
+// grid = (strips, filter tiles), ks in {1, 2, 4, 8} wavefronts that share a strip.
 // CPRUNE_ERR_UNSUPPORTED for other combinations.
-int launch_mbconv_f32(int k, int stride, int mb, dim3 grid, size_t lds_bytes, hipStream_t s, const MbConvArgs& a);
-int launch_mbconv_f16(int k, int stride, int mb, dim3 grid, size_t lds_bytes, hipStream_t s, const MbConvArgs& a);
-int launch_mbconv_bf16(int k, int stride, int mb, dim3 grid, size_t lds_bytes, hipStream_t s, const MbConvArgs& a);
+int launch_mbrow_f32(int k, int stride, int mb, int xh, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a);
+int launch_mbrow_f16(int k, int stride, int mb, int xh, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a);
+int launch_mbrow_bf16(int k, int stride, int mb, int xh, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a);
+// expansion weights [ce][cp] -> the operand order of that kernel, [block of 16 channels][xh 32-byte units], zero padded
+size_t expand_packed_bytes(int ce, int xh, int dt);
+int launch_pack_expand(const void* w, int ce, int cp, int xh, int dt, void* y, hipStream_t s);
 
 // The first two layers of a network in one kernel: both 3x3 / stride 1 / pad 1, the first on the NCHW image
 // (at most 3 channels) with c1 <= 32 filters, the second dense and channels-last.  d2 / lay2 describe the second

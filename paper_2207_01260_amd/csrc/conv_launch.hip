@@ -637,4 +637,21 @@ int launch_conv_stem2(const cprune_conv_desc& d2, const ConvLayout& lay2, const 
   return CPRUNE_OK;
 }
 
+bool mbrow_form(int dt, int c_out, int cp_in, int* mb, int* xh) {
+  static const int f32[][2] = {{2, 2}, {2, 3}, {2, 4}, {4, 4}, {4, 8}, {6, 8}, {6, 12}, {8, 12}};
+  static const int half[][2] = {{2, 2}, {2, 4}, {4, 2}, {4, 4}, {6, 4}, {6, 6}, {8, 10}};
+  *xh = 0;
+  if (cp_in == 0) {
+    *mb = c_out <= 16 ? 1 : c_out <= 32 ? 2 : c_out <= 64 ? 4 : c_out <= 96 ? 6 : 8;
+    return true;
+  }
+  const int need = (cp_in * (int)dtype_size(dt) + 31) / 32;
+  const int count = dt == CPRUNE_F32 ? 8 : 7;
+  for (int i = 0; i < count; ++i) {
+    const int* f = dt == CPRUNE_F32 ? f32[i] : half[i];
+    if (f[0] * 16 >= c_out && f[1] >= need) { *mb = f[0]; *xh = f[1]; return true; }
+  }
+  return false;
+}
+
 }  // namespace cprune

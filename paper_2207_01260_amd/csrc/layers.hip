@@ -445,6 +445,34 @@ __global__ __launch_bounds__(256) void repack_rows_kernel(const T* __restrict__ 
   y[i] = v;
 }
 
+// Expansion weights [ce][cp] -> the order in which the inverted-residual kernel's lanes fetch them, [block of 16 channels][xh
+// 32-byte units of the reduction]: whole 64-byte rounds as [lane = quad * 16 + row][16 bytes], an odd last unit (fp32) as
+// [lane][8 bytes].  In 16-bit data two blocks share 32 channels, four at a time, so that a lane's results of both are
+// eight consecutive channels.  Zero past the last channel.
+template <typename T>
+__global__ __launch_bounds__(256) void pack_expand_kernel(const T* __restrict__ w, T* __restrict__ y, long total, int ce, int cp,
+                                                          int xh) {
+  constexpr int ES = (int)sizeof(T), EPI = 16 / ES;
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;   // one element of the output
+  if (i >= total) return;
+  const int per = xh * (512 / ES);
+  const int blk = (int)(i / per), off = (int)(i % per);
+  const int whole = (xh / 2) * (1024 / ES);
+  int lane, k;
+  if (off < whole) {
+    const int rnd = off / (1024 / ES), q = off % (1024 / ES);
+    lane = q / EPI;
+    k = rnd * 4 * EPI + (lane >> 4) * EPI + q % EPI;
+  } else {
+    const int q = off - whole;
+    lane = q / (EPI / 2);
+    k = (xh / 2) * 4 * EPI + (lane >> 4) * (EPI / 2) + q % (EPI / 2);
+  }
+  const int row = lane & 15;
+  const int ch = ES == 4 ? blk * 16 + row : (blk >> 1) * 32 + (row >> 2) * 8 + (blk & 1) * 4 + (row & 3);
+  y[i] = (ch < ce && k < cp) ? w[(long)ch * cp + k] : (T)0.0f;
+}
+
 // Weights -> the operand order of the split kernel: [filter tile of 16][round][part][lane = quarter * 16 + filter]
 // [8 channels].  A round holds four (tap, 8-channel group) units, one per quarter.
 template <typename T>
@@ -757,6 +785,19 @@ int launch_repack_rows(const void* w, int rows, int k, int dt, void* y, hipStrea
   const long total = (long)(rows_packed_bytes(rows, k, dt) / dtype_size(dt));
   CPRUNE_BY_DTYPE(dt, hipLaunchKernelGGL(repack_rows_kernel<T>, blocks_for(total), dim3(256), 0, s, (const T*)w, (T*)y,
                                          total, rows, k, rounds));
+  CPRUNE_LAUNCH_CHECK();
+  return CPRUNE_OK;
+}
+
+size_t expand_packed_bytes(int ce, int xh, int dt) {
+  const int cc = (int)(64 / dtype_size(dt));   // channels per chunk
+  return (size_t)((ce + cc - 1) / cc) * (cc / 16) * xh * 512;
+}
+
+int launch_pack_expand(const void* w, int ce, int cp, int xh, int dt, void* y, hipStream_t s) {
+  const long total = (long)(expand_packed_bytes(ce, xh, dt) / dtype_size(dt));
+  CPRUNE_BY_DTYPE(dt, hipLaunchKernelGGL(pack_expand_kernel<T>, blocks_for(total), dim3(256), 0, s, (const T*)w, (T*)y,
+                                         total, ce, cp, xh));
   CPRUNE_LAUNCH_CHECK();
   return CPRUNE_OK;
 }

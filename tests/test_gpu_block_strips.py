@@ -1,0 +1,100 @@
+"""Inverted-residual blocks as one kernel, and their depthwise + 1x1 half alone, at the sizes where strips of 16 columns x a few
+rows can go wrong: maps of one strip, one column more, odd rows at the bottom, eight lanes per row (two images side by side,
+the second one missing), fewer chunks of channels than wavefronts, several filter tiles.  Against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2207_01260_amd import binding as B
+from paper_2207_01260_amd import pipeline, synth
+from parity import nmax
+
+pytestmark = pytest.mark.gpu
+
+TOL = {B.F32: 1e-4, B.F16: 2e-2, B.BF16: 2e-2}
+
+
+def _block(c_in, c_exp, c_out, hw, k, stride, shortcut):
+    net = synth.NetSpec(f"strip_{c_in}_{c_exp}_{c_out}_{hw}_{k}_{stride}", 3, hw, hw)
+    a = net.add(synth.Layer("conv", -1, 3, c_in, k=1, act=synth.ACT_RELU, bn=True, name="a"))
+    e = net.add(synth.Layer("conv", a, c_in, c_exp, k=1, act=synth.ACT_RELU, bn=True, name="e"))
+    d = net.add(synth.Layer("conv", e, c_exp, c_exp, k=k, stride=stride, pad=k // 2, groups=c_exp, act=synth.ACT_RELU6,
+                            bn=True, name="d"))
+    net.add(synth.Layer("conv", d, c_exp, c_out, k=1, act=synth.ACT_NONE, bn=True, residual=a if shortcut else None, name="p"))
+    return net, e, d
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("cfg", [
+    # c_in, c_exp, c_out, hw, k, stride, shortcut, batch
+    (16, 16, 16, 16, 3, 1, True, 1),       # one strip wide, a single chunk
+    (16, 36, 24, 17, 3, 1, False, 3),      # one column into the second strip
+    (24, 50, 24, 31, 3, 1, True, 2),       # three strips, ragged rows
+    (24, 40, 32, 33, 3, 2, False, 2),      # stride 2: 17 output columns
+    (32, 33, 33, 7, 3, 1, False, 3),       # two images per strip, the last one alone
+    (32, 90, 64, 14, 3, 2, False, 5),      # stride 2 onto 7 columns: two images per strip
+    (32, 44, 32, 8, 3, 1, True, 2),        # eight columns: too wide to share
+    (16, 40, 40, 6, 5, 1, False, 3),       # 5x5 window, two images per strip
+    (40, 70, 40, 29, 5, 1, True, 1),       # 5x5, three strips
+    (16, 48, 40, 27, 5, 2, False, 2),      # 5x5, stride 2, odd map
+    (8, 20, 100, 9, 3, 1, False, 2),       # widest built filter tile
+    (8, 260, 24, 5, 3, 1, False, 1),       # many chunks, one small strip: eight wavefronts share it
+    (8, 24, 20, 2, 3, 1, False, 2),        # a 2x2 map: most neighbours are padding
+])
+def test_block_strips(orc, cfg, dtype):
+    c_in, c_exp, c_out, hw, k, stride, shortcut, batch = cfg
+    print(cfg, dtype, flush=True)
+    net, e, d = _block(c_in, c_exp, c_out, hw, k, stride, shortcut)
+    params = synth.layer_params(net, 70)
+    x = synth.net_input(net, 70, batch)
+    ref_layers, _ = orc.prune_net(net, params)
+    ref = orc.forward(net, ref_layers, x)
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(params), dtype)
+    handle = pipeline.build_net(net, layers, batch, dtype, tune=False)
+    xd = torch.from_numpy(x).cuda().to(B.TORCH_DTYPE[dtype])
+    for form in ("block", "depthwise", "apart"):
+        if form == "block":
+            handle.fuse_block(d, True)
+        else:
+            handle.fuse_depthwise(d, form == "depthwise")
+        assert handle.layer_fused(e) == (form == "block") and handle.layer_fused(d) == (form != "apart")
+        out = handle.forward(xd)
+        torch.cuda.synchronize()
+        err = nmax(out.float().cpu().numpy(), ref)
+        assert err < TOL[dtype], (form, err)
+    handle.close()
+
+
+def test_depthwise_half_with_several_filter_tiles(orc):
+    """300 projection filters: three filter tiles, each with the depthwise half of its own."""
+    net, e, d = _block(16, 60, 300, 15, 3, 1, False)
+    params = synth.layer_params(net, 71)
+    x = synth.net_input(net, 71, 2)
+    ref_layers, _ = orc.prune_net(net, params)
+    ref = orc.forward(net, ref_layers, x)
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(params), B.F32)
+    handle = pipeline.build_net(net, layers, 2, B.F32, tune=False)
+    handle.fuse_depthwise(d, True)
+    out = handle.forward(torch.from_numpy(x).cuda())
+    torch.cuda.synchronize()
+    assert nmax(out.cpu().numpy(), ref) < 1e-4
+    handle.close()
+
+
+@pytest.mark.parametrize("form", ["block", "depthwise"])
+@pytest.mark.parametrize("hw,k,stride", [(7, 3, 1), (14, 3, 2), (6, 5, 1)])
+def test_images_of_one_strip_do_not_meet(hw, k, stride, form):
+    """Two images share a strip's 16 columns: infinities in one leave the other's result as it was, bit for bit."""
+    net, e, d = _block(16, 40, 24, hw, k, stride, False)
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(synth.layer_params(net, 72)), B.F32)
+    handle = pipeline.build_net(net, layers, 2, B.F32, tune=False)
+    (handle.fuse_block if form == "block" else handle.fuse_depthwise)(d, True)
+    x = torch.from_numpy(synth.net_input(net, 72, 2)).cuda()
+    want = handle.forward(x).clone()
+    for bad in (0, 1):
+        xb = x.clone()
+        xb[bad] = float("inf")
+        got = handle.forward(xb).clone()
+        torch.cuda.synchronize()
+        assert torch.equal(got[1 - bad], want[1 - bad]), bad
+    handle.close()
