@@ -188,9 +188,10 @@ typedef struct {
  * sched n > 0: the (tile, reduction slab) work is laid out in one line and cut
  * into equal runs for n * 256 work-groups; tiles cut between runs go through the
  * caller's scratch and are summed in run order (deterministic).  sched -1: one spatial block of at
- * most tile_p pixels per work-group.  Two kinds, told apart by cprune_tile_variant_name: the patch
+ * most tile_p pixels per work-group.  Three kinds, told apart by cprune_tile_variant_name: the patch
  * kernels (conv_patch*: 3x3 layers, channels-last inside a network handle only, unsupported through
- * the NCHW call) and the split kernel (conv_split_kernel: any window at stride 1 or 2).  The split
+ * the NCHW call), the row-strip kernel (conv_rows_kernel: 3x3 / stride 1 / pad 1 layers of 16-bit
+ * handles) and the split kernel (conv_split_kernel: any window at stride 1 or 2).  The split
  * kernel multiplies fp32 data as three 16-bit parts per number on the 16-bit matrix cores; it runs fp32
  * layers of at least 16 terms per output, where its error is no larger than the fp32 instruction's, and
  * redoes with that instruction what three parts do not hold (infinities, results below 2^-50; inputs or

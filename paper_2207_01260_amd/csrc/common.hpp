@@ -47,6 +47,8 @@ struct TileVariant {
   int ks = 1;     // patch kernels on 16x16 blocks: wave groups per tile; split kernel: wavefronts that share a block
   int kwaves = 0; // reduction-split kernel: wavefronts that share one tile's reduction (patch_id indexes its list)
   int split = 0;  // 1 (with sched = -1): split kernel, any window and stride, fp32 as three bf16 parts
+  int rows = 0;   // 1 (with sched = -1): row-strip kernel, 16-bit 3x3 layers; th = rows of a strip, ks = wavefronts that
+                  // share one (patch_id indexes its list)
   int nib = 0;    // split kernel: staging items per thread (patch_id indexes its list)
   int nr = 0;     // short-reduction 1x1 kernel: 64-byte rounds of the reduction its filter tile holds
   int stride = 1; // spatial-patch kernel on 16x16 blocks: the window stride it is built for (patch_id then indexes the
@@ -86,9 +88,10 @@ size_t conv_ws_bytes(const cprune_conv_desc& d, int v, const ConvLayout& lay = C
 // ws_limit: scratch bytes the chosen variant may need
 int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay = ConvLayout(), size_t ws_limit = SIZE_MAX);
 size_t variant_ws_bytes(const cprune_conv_desc& d, int v, const ConvLayout& lay);   // of a variant that runs the layer
-// Estimated clocks of a variant: of the general kernel on a layer it runs, of the split kernel (-1 where it does not run
-// the layer); -1 for the others.
+// Estimated clocks of a variant: of the general kernel on a layer it runs, of the split and the row-strip kernel (-1 where
+// they do not run the layer); -1 for the others.
 int best_split_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost);   // the cheapest; -1: none runs it
+int best_rows_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost);    // likewise of the row-strip kernel
 double variant_cost(const cprune_conv_desc& d, int v, const ConvLayout& lay);
 int cached_or_heuristic_variant(const cprune_conv_desc& d, bool* timed, const ConvLayout& lay = ConvLayout());
 void remember_variant(const cprune_conv_desc& d, int v, const ConvLayout& lay = ConvLayout());

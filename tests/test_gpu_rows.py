@@ -1,0 +1,94 @@
+"""The row-strip kernel (3x3 / stride 1 / pad 1, 16-bit data, inside a handle) at the sizes where its strips can go wrong: one
+strip of 16 columns, one column more, ragged rows, two and four images side by side with the last one missing, one chunk of
+channels and fewer chunks than wavefronts, filter tiles of one to four blocks with a partial last block; with and without a
+fused 2x2 max-pool and a shortcut.  Every variant that accepts the layer, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2207_01260_amd import binding as B
+from paper_2207_01260_amd import pipeline, synth
+from parity import nmax
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows_variants(dtype):
+    return [v for v in range(B.cprune_num_tile_variants()) if "conv_rows" in B.cprune_tile_variant_name(v, True, dtype)]
+
+
+@pytest.mark.parametrize("dtype", [B.F16, B.BF16])
+@pytest.mark.parametrize("cfg", [
+    # c_in, c_out, hw, batch, pool, shortcut
+    (32, 16, 16, 1, False, False),     # one strip, one chunk, one block
+    (33, 17, 17, 2, False, True),      # one column into the second strip, a channel into the second chunk
+    (40, 50, 31, 1, False, False),     # edge columns on both sides, ragged rows
+    (72, 33, 33, 2, False, True),      # three strips
+    (130, 48, 7, 3, False, True),      # two images per strip, one missing; five chunks
+    (260, 70, 8, 5, False, False),     # eight columns: the images of a strip touch
+    (70, 65, 4, 6, False, True),       # four images per strip, two missing
+    (300, 20, 3, 3, False, False),     # three columns of four lanes
+    (48, 40, 32, 2, True, False),      # pool, two strips
+    (64, 30, 18, 1, True, False),      # pool, ragged strip
+    (96, 36, 8, 3, True, False),       # pool, two images
+    (160, 24, 4, 5, True, False),      # pool, four images
+    (20, 24, 6, 3, True, False),
+])
+def test_rows_variants(orc, cfg, dtype):
+    c_in, c_out, hw, batch, pool, shortcut = cfg
+    print(cfg, dtype, flush=True)
+    net = synth.NetSpec(f"rows_{c_in}_{c_out}_{hw}_{pool}", 3, hw, hw)
+    a = net.add(synth.Layer("conv", -1, 3, c_in, k=1, act=synth.ACT_RELU, bn=True, name="a"))
+    r = net.add(synth.Layer("conv", -1, 3, c_out, k=1, act=synth.ACT_NONE, bn=True, name="r")) if shortcut else None
+    b = net.add(synth.Layer("conv", a, c_in, c_out, k=3, stride=1, pad=1, act=synth.ACT_RELU, bn=True, residual=r, name="b"))
+    if pool:
+        p = net.add(synth.Layer("maxpool", b, c_out, c_out, k=2, stride=2, name="p"))
+        net.add(synth.Layer("conv", p, c_out, 8, k=1, act=synth.ACT_NONE, bn=True, name="c"))
+    params = synth.layer_params(net, 80)
+    x = synth.net_input(net, 80, batch)
+    ref_layers, _ = orc.prune_net(net, params)
+    ref = orc.forward(net, ref_layers, x)
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(params), dtype)
+    handle = pipeline.build_net(net, layers, batch, dtype, tune=False)
+    xd = torch.from_numpy(x).cuda().to(B.TORCH_DTYPE[dtype])
+    ran = 0
+    assert handle.layer_variant(b) in _rows_variants(dtype)          # the untimed choice
+    for v in _rows_variants(dtype):
+        try:
+            handle.set_layer_variant(b, v)
+        except B.CPruneError as e:
+            assert e.status == B.ERR_UNSUPPORTED
+            continue
+        out = handle.forward(xd)
+        torch.cuda.synchronize()
+        err = nmax(out.float().cpu().numpy(), ref)
+        assert err < 2e-2, (B.cprune_tile_variant_name(v, True, dtype), err)
+        ran += 1
+    assert ran >= 5
+    handle.close()
+
+
+@pytest.mark.parametrize("hw,batch", [(8, 2), (4, 4), (17, 1)])
+def test_rows_neighbours_do_not_leak(hw, batch):
+    """An infinity in one image of a strip leaves the others bit for bit, and one pixel reaches its 3x3 neighbours only."""
+    net = synth.NetSpec(f"rowsleak_{hw}", 16, hw, hw)
+    a = net.add(synth.Layer("conv", -1, 16, 40, k=1, act=synth.ACT_NONE, bn=True, name="a"))
+    net.add(synth.Layer("conv", a, 40, 24, k=3, stride=1, pad=1, act=synth.ACT_NONE, bn=True, name="b"))
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(synth.layer_params(net, 81)), B.BF16)
+    handle = pipeline.build_net(net, layers, batch, B.BF16, tune=False)
+    x = torch.from_numpy(synth.net_input(net, 81, batch)).cuda().to(torch.bfloat16)
+    for v in _rows_variants(B.BF16):
+        try:
+            handle.set_layer_variant(1, v)
+        except B.CPruneError:
+            continue
+        want = handle.forward(x).clone()
+        for px in ((0, 0), (hw - 1, hw - 1), (hw // 2, min(15, hw - 1))):
+            xb = x.clone()
+            xb[batch - 1, :, px[0], px[1]] = float("inf")
+            got = handle.forward(xb)
+            torch.cuda.synchronize()
+            near = torch.zeros(got.shape, dtype=torch.bool, device="cuda")
+            near[batch - 1, :, max(0, px[0] - 1):px[0] + 2, max(0, px[1] - 1):px[1] + 2] = True
+            assert torch.equal(got[~near], want[~near]), (v, px)
+    handle.close()
