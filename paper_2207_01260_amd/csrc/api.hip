@@ -68,13 +68,24 @@ static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay, double 
   return lay.nhwc || 2.0 * (double)d.n * ho * wo * d.c_out * d.c_in * d.kh * d.kw >= line;
 }
 
-// Untimed choice: the row-strip kernel where it runs (16-bit 3x3 layers of a handle: on 72 random layers 2.35 times as fast as the
-// general kernel, at least 1.15 times); otherwise the cheapest by variant_cost among the general kernel's tiles, whole or cut into
-// equal runs, and, for windows of more than one tap, the split kernel's variants where it pays.
+// Whether an untimed layer takes the row-strip kernel where it runs (3x3 layers of a handle).  16-bit data: always (on 72 random
+// layers 2.35 times as fast as the general kernel, at least 1.15 times).  fp32, against the split kernel: from 0.2 GFLOP up on maps one
+// strip wide and 0.3 on wider ones whose strips are well filled (56 of 4 x 16 columns, not 32 of 3 x 16); there 1.3 times as
+// fast on average, 0.94 times at worst, and below those lines 0.7-1.2 times.
+static bool rows_pay(const cprune_conv_desc& d) {
+  if (d.dtype != CPRUNE_F32) return true;
+  const double flops = 18.0 * d.n * d.h * d.w * (double)d.c_out * d.c_in;
+  if (d.w <= 16) return flops >= 2e8;
+  return flops >= 3e8 && d.w >= 0.85 * 16 * ((d.w - 16 + 13) / 14 + 1);
+}
+
+// Untimed choice: the row-strip kernel where it pays; otherwise the cheapest by variant_cost among the general kernel's tiles,
+// whole or cut into equal runs, and, for windows of more than one tap, the split kernel's variants where it pays.
 int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay, size_t ws_limit) {
   double best = -1.0;
-  const int rows = best_rows_variant(d, lay, &best);
+  const int rows = rows_pay(d) ? best_rows_variant(d, lay, &best) : -1;
   if (rows >= 0) return rows;
+  best = -1.0;
   int best_v = d.kh * d.kw > 1 && split_pays(d, lay, 6e8) ? best_split_variant(d, lay, &best) : -1;
   if (best_v < 0 || variant_ws_bytes(d, best_v, lay) > ws_limit) { best = -1.0; best_v = 0; }
   for (int v = 0; v < num_variants(); ++v) {
@@ -241,6 +252,8 @@ extern "C" int cprune_tile_variant_name(int v, int channels_last, cprune_dtype d
   else if (tv.split)
     n = snprintf(buf, buf_bytes, "conv_split_kernel<%s, %s, %d, %d, %d, %d, %d, %d>", t, channels_last ? "false" : "true", tv.wm,
                  tv.wn, tv.ks, tv.mb, tv.nb, tv.nib);
+  else if (tv.rows && channels_last && dtype == CPRUNE_F32)
+    n = snprintf(buf, buf_bytes, "conv_split_rows_kernel<%d, %d>", tv.th, tv.ks);
   else if (tv.rows)
     n = snprintf(buf, buf_bytes, "conv_rows_kernel<%s, %d, %d, %d>", t, tv.mb, tv.th, tv.ks);
   else if (tv.sched == -4)
@@ -395,6 +408,7 @@ struct NetLayer {
   void* w_wave = nullptr;     // 3x3 / stride 1 / pad 1 layer on a small map: weights once more, packed for the
                               // independent-wavefront kernel
   void* w_split = nullptr;    // fp32 dense layer: weights once more, cut and packed for the split kernel
+  void* w_rows3 = nullptr;    // fp32 3x3 / stride 1 / pad 1 layer: likewise, for the row-strip kernel
   bool stem = false;          // nchw_in layer that runs the first-layer kernel (whole reduction in LDS)
   void* w_stem7 = nullptr;    // 16-bit 7x7 / stride 2 / pad 3 first layer: weights packed for the kernel made for it
   int stem7 = 0;              // 1: that kernel runs the layer; 2: and the 3x3 / stride 2 max-pool pool3 with it
@@ -455,6 +469,7 @@ static ConvLayout layer_layout(const NetLayer& L) {
   lay.w_wave = L.w_wave;
   lay.w_rows = L.w_rows;
   lay.w_split = L.w_split;
+  lay.w_rows3 = L.w_rows3;
   if (L.nchw_in) { lay.nhwc = 0; lay.nhwc_out = 1; lay.cp_in = 0; return lay; }
   if (L.map2x2) {
     lay.cp_in = 4 * L.cp_in;
@@ -464,30 +479,41 @@ static ConvLayout layer_layout(const NetLayer& L) {
   return lay;
 }
 
-// fp32 dense layers can have a copy of their weights cut and packed for the split kernel; it is 1.5 times the weights and made
-// only for a layer that runs that kernel (while variants are timed, for every layer that could).
+// fp32 dense layers can have copies of their weights cut and packed for the split and the row-strip kernel; each is 1.5 times the
+// weights or more and made only for a layer that runs that kernel (while variants are timed, for every layer that could).
 static ConvLayout layout_if_split(const cprune_net& net, const NetLayer& L) {
   ConvLayout lay = layer_layout(L);
-  if (net.dtype == CPRUNE_F32 && !L.nchw_in) lay.w_split = L.w;     // (only whether it is set matters to a choice)
+  if (net.dtype == CPRUNE_F32 && !L.nchw_in) lay.w_split = lay.w_rows3 = L.w;     // (only whether they are set matters to a choice)
   return lay;
 }
 
-static int pack_split(cprune_net* net, NetLayer& L, hipStream_t s) {
-  if (L.w_split) return CPRUNE_OK;
+static int packed_copy(cprune_net* net, NetLayer& L, bool rows, hipStream_t s) {
+  void*& slot = rows ? L.w_rows3 : L.w_split;
+  if (slot || net->dtype != CPRUNE_F32) return CPRUNE_OK;
   const cprune_conv_desc d = layer_conv_desc(*net, L, net->max_batch);
   const int cp = layer_layout(L).cp_in, taps = d.kh * d.kw;
   void* copy = nullptr;
-  CPRUNE_HIP_TRY(hipMalloc(&copy, split_packed_bytes(d.c_out, cp, taps, net->dtype)));
+  CPRUNE_HIP_TRY(hipMalloc(&copy, split_packed_bytes(d.c_out, cp, taps, net->dtype, rows)));
   net->allocs.push_back(copy);
-  L.w_split = copy;
-  return launch_pack_split(L.w, d.c_out, cp, taps, 1, net->dtype, L.w_split, s);
+  slot = copy;
+  return launch_pack_split(L.w, d.c_out, cp, taps, 1, net->dtype, copy, s, rows);
 }
 
-static void drop_split(cprune_net* net, NetLayer& L) {      // (nothing that reads it is in flight)
-  if (!L.w_split) return;
-  net->allocs.erase(std::find(net->allocs.begin(), net->allocs.end(), L.w_split));
-  hipFree(L.w_split);
-  L.w_split = nullptr;
+// the copy variant v reads, if it reads one
+static int pack_for(cprune_net* net, NetLayer& L, int v, hipStream_t s) {
+  if (variant(v).split) return packed_copy(net, L, false, s);
+  if (variant(v).rows) return packed_copy(net, L, true, s);
+  return CPRUNE_OK;
+}
+
+// gives back what variant v (-1: none) does not read (nothing that reads it is in flight)
+static void drop_copies(cprune_net* net, NetLayer& L, int v) {
+  for (void** slot : {&L.w_split, &L.w_rows3}) {
+    if (!*slot || (v >= 0 && (slot == &L.w_split ? variant(v).split : variant(v).rows))) continue;
+    net->allocs.erase(std::find(net->allocs.begin(), net->allocs.end(), *slot));
+    hipFree(*slot);
+    *slot = nullptr;
+  }
 }
 
 constexpr size_t kMaxGraphs = 8;
@@ -1006,11 +1032,10 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     if (!(L.d.kind == CPRUNE_LAYER_FC || (L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1))) continue;
     cprune_conv_desc cd = layer_conv_desc(*net, L, max_batch);
     ConvLayout lay = layout_if_split(*net, L);
-    bool timed = false, any_split = false;
+    bool timed = false;
     int v = cached_or_heuristic_variant(cd, &timed, lay);
-    for (int k = 0; k < num_variants() && !any_split; ++k)
-      any_split = variant(k).split && (tune && !timed ? variant_supports(cd, k, lay) : k == v);
-    if (any_split && dtype == CPRUNE_F32) rc = pack_split(net, L, s);
+    for (int k = 0; k < num_variants() && rc == CPRUNE_OK; ++k)
+      if (tune && !timed ? variant_supports(cd, k, lay) : k == v) rc = pack_for(net, L, k, s);
     if (rc != CPRUNE_OK) break;
     lay = layer_layout(L);
     if (tune && !timed) {
@@ -1020,7 +1045,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     }
     L.variant = v;
     L.timed = timed || tune;
-    if (rc == CPRUNE_OK && !variant(v).split) drop_split(net, L);
+    if (rc == CPRUNE_OK) drop_copies(net, L, v);
   }
   // A first layer with an image-like input (<= 3 channels; 3x3 or 7x7 window) has a kernel of its
   // own that keeps the whole reduction in LDS; with tune != 0 it is timed against the chosen variant
@@ -1214,7 +1239,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
   }
   if (rc != CPRUNE_OK) { net_free(net); return rc; }
   for (NetLayer& L : net->layers)
-    if (L.variant < 0) drop_split(net, L);      // runs inside another kernel
+    if (L.variant < 0) drop_copies(net, L, -1);      // runs inside another kernel
   *out = net;
   return CPRUNE_OK;
 }
@@ -1344,11 +1369,9 @@ extern "C" int cprune_net_task_key(const cprune_net* net, int layer, int32_t* ke
 static int restore_variant(cprune_net* net, NetLayer& L) {
   if (L.variant >= 0 || L.stem || L.stem7) return CPRUNE_OK;
   const int v = cached_or_heuristic_variant(layer_conv_desc(*net, L, net->max_batch), &L.timed, layout_if_split(*net, L));
-  if (variant(v).split) {
-    const int rc = pack_split(net, L, nullptr);
-    if (rc != CPRUNE_OK) return rc;
-    CPRUNE_HIP_TRY(hipDeviceSynchronize());
-  }
+  const int rc = pack_for(net, L, v, nullptr);
+  if (rc != CPRUNE_OK) return rc;
+  CPRUNE_HIP_TRY(hipDeviceSynchronize());
   L.variant = v;
   L.at_batch.clear();
   return CPRUNE_OK;
@@ -1453,13 +1476,10 @@ extern "C" int cprune_net_set_layer_variant(cprune_net* net, int layer, int vari
   if (conv_ws_bytes(cd, variant, lay) > net->ws_bytes) return CPRUNE_ERR_WORKSPACE;
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
   drop_graphs(net);
-  if (cprune::variant(variant).split) {
-    const int rc = pack_split(net, L, nullptr);
-    if (rc != CPRUNE_OK) return rc;
-    CPRUNE_HIP_TRY(hipDeviceSynchronize());
-  } else {
-    drop_split(net, L);
-  }
+  const int rc = pack_for(net, L, variant, nullptr);
+  if (rc != CPRUNE_OK) return rc;
+  CPRUNE_HIP_TRY(hipDeviceSynchronize());
+  drop_copies(net, L, variant);
   L.variant = variant;
   L.timed = true;
   L.at_batch.clear();

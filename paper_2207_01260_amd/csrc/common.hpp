@@ -47,7 +47,7 @@ struct TileVariant {
   int ks = 1;     // patch kernels on 16x16 blocks: wave groups per tile; split kernel: wavefronts that share a block
   int kwaves = 0; // reduction-split kernel: wavefronts that share one tile's reduction (patch_id indexes its list)
   int split = 0;  // 1 (with sched = -1): split kernel, any window and stride, fp32 as three bf16 parts
-  int rows = 0;   // 1 (with sched = -1): row-strip kernel, 16-bit 3x3 layers; th = rows of a strip, ks = wavefronts that
+  int rows = 0;   // 1 (with sched = -1): row-strip kernel, 3x3 layers of a handle; th = rows of a strip, ks = wavefronts that
                   // share one (patch_id indexes its list)
   int nib = 0;    // split kernel: staging items per thread (patch_id indexes its list)
   int nr = 0;     // short-reduction 1x1 kernel: 64-byte rounds of the reduction its filter tile holds
@@ -76,6 +76,8 @@ struct ConvLayout {
   const void* w_split = nullptr; // channels-last fp32: the weights cut and packed for the split kernel
                                  // (launch_pack_split), which runs only where this is set; a call in the boundary's
                                  // layout packs its weights into the caller's scratch
+  const void* w_rows3 = nullptr; // channels-last fp32 3x3 / stride 1 / pad 1: cut and packed in whole chunks of 32 channels for the
+                                 // row-strip kernel, which runs fp32 data only where this is set
   int pool = 0;  // 1: channels-last 3x3 layer with a 2x2/2 max-pool fused behind the activation (patch kernels);
                  // 2: rows are (channel, position of a 2x2 map) and each group of four rows is reduced to its
                  //    maximum behind the activation; cp_out is the stride of the pooled output
@@ -129,8 +131,9 @@ int launch_repack_rows(const void* w, int rows, int k, int dt, void* y, hipStrea
 // weights [o][taps][c] (khwc = 1) or [o][c][taps] -> the operand order of the split kernel: [filter tile of 16][round]
 // [part][lane][16 bytes]; an fp32 weight as three bf16 parts, 16-bit weights as they are; zeros past the last filter
 // and channel.  split_packed_bytes: size of the packed weights
-size_t split_packed_bytes(int o, int c, int taps, int dt);
-int launch_pack_split(const void* w, int o, int c, int taps, int khwc, int dt, void* y, hipStream_t s);
+// (whole: the last chunk of 32 channels packed like the others, zero padded; otherwise its groups only)
+size_t split_packed_bytes(int o, int c, int taps, int dt, bool whole = false);
+int launch_pack_split(const void* w, int o, int c, int taps, int khwc, int dt, void* y, hipStream_t s, bool whole = false);
 int launch_repack_map2x2(const void* w, const float* bias, int o, int c, int cp_in, int cp_out,
                          int rows_by_channel, int dt, void* w_out, float* bias_out, hipStream_t s);
 

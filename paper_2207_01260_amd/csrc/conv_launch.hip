@@ -341,27 +341,34 @@ int best_split_variant(const cprune_conv_desc& d, const ConvLayout& lay, double*
 }
 
 // Strips of the row-strip kernel on a layer: 16 columns x th rows of one image, or of two (four) images of at most 8 (4) columns.
-static RowsArgs rows_tiles(const cprune_conv_desc& d, const TileVariant& tv) {
+static RowsArgs rows_tiles(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay) {
   RowsArgs a;
   a.lane_shift = d.w <= 4 ? 2 : d.w <= 8 ? 3 : 4;
   const int ipt = 16 >> a.lane_shift;
   a.tiles_x = (d.w + 15) / 16;
+  a.step = 16;
+  if (d.dtype == CPRUNE_F32 && a.tiles_x > 1) {
+    a.step = lay.pool ? 12 : 14;
+    a.tiles_x = (d.w - 16 + a.step - 1) / a.step + 1;
+  }
   a.tiles_y = (d.h + tv.th - 1) / tv.th;
   a.tiles_m = (d.c_out + tv.tile_m() - 1) / tv.tile_m();
   a.strips = (d.n + ipt - 1) / ipt * a.tiles_y * a.tiles_x;
   return a;
 }
 
-// Clocks of a row-strip variant, to choose among them untimed: a wavefront's chunks, 16 clocks per MFMA and the wait for the
-// weights of the next chunk, or the whole layer's on 1024 SIMDs where that is longer; the meeting of the sums.  On 72 random bf16
-// layers (maps 4 to 56, batch 1-64) its choice takes 3 % longer than the best of the variants on average, 17 % at most.
+// Clocks of a row-strip variant, to choose among them untimed: a wavefront's chunks, 16 clocks per MFMA (six for one in fp32) and
+// what a wavefront alone on its SIMD waits per chunk, or the whole layer's on 1024 SIMDs where that is longer; the meeting of the
+// sums.  On 72 random layers (maps 4 to 56, batch 1-64) its choice takes 3 % longer than the best of the variants on average, 17 % at
+// most, in bf16, 0.4 % on average in fp32.
 static double rows_cost(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay) {
-  const RowsArgs p = rows_tiles(d, tv);
+  const RowsArgs p = rows_tiles(d, tv, lay);
+  const bool f32 = d.dtype == CPRUNE_F32;
   const double waves = (double)p.strips * p.tiles_m * tv.ks;
   const double chunks = ((lay.cp_in + 31) / 32 + tv.ks - 1) / tv.ks;
-  const double mma = 144.0 * tv.mb * std::min(tv.th, d.h);
-  return std::max(chunks * (mma + 500.0), waves / 1024.0 * chunks * (mma + 300.0)) + (tv.ks > 1 ? 160.0 * tv.mb * tv.th : 0.0) +
-         500.0 * std::ceil(waves / 1024.0);
+  const double mma = (f32 ? 864.0 : 144.0) * tv.mb * std::min(tv.th, d.h);
+  return std::max(chunks * (mma + (f32 ? 4000.0 : 500.0)), waves / 1024.0 * chunks * (mma + 300.0)) +
+         (tv.ks > 1 && !f32 ? 160.0 * tv.mb * tv.th : 0.0) + 500.0 * std::ceil(waves / 1024.0);
 }
 
 int best_rows_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost) {
@@ -391,12 +398,13 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
     return split_supports(d, tv, lay, &p);
   }
   if (tv.rows) {
-    // 16-bit 3x3 / stride 1 / pad 1; wavefronts share a strip only while there is a chunk for each, and not where strips
+    // 3x3 / stride 1 / pad 1 in a handle; wavefronts share a strip only while there is a chunk for each, and not where strips
     // alone fill the chip several times
-    if (!(lay.nhwc && lay.w_wave && d.dtype != CPRUNE_F32 && d.kh == 3 && d.kw == 3 && d.stride == 1 && d.pad == 1)) return false;
+    if (!(lay.nhwc && (d.dtype == CPRUNE_F32 ? lay.w_rows3 && tv.mb == 1 : lay.w_wave != nullptr) && d.kh == 3 && d.kw == 3 && d.stride == 1 && d.pad == 1)) return false;
     if (lay.pool == 2 || (lay.pool && ((d.h | d.w) & 1))) return false;
-    const RowsArgs p = rows_tiles(d, tv);
+    const RowsArgs p = rows_tiles(d, tv, lay);
     const long waves = (long)p.strips * p.tiles_m;
+    if (d.dtype == CPRUNE_F32 && split_packed_bytes(d.c_out, lay.cp_in, 9, d.dtype, true) >= ((size_t)1 << 31)) return false;
     if (tv.ks > 1 && (tv.ks > (lay.cp_in + 31) / 32 || waves * tv.ks > 8192)) return false;
     // multiply-high divisions of the tile decode: exact while groups x divisor < 2^32
     const long groups = (long)((p.strips + tv.wn - 1) / tv.wn) * p.tiles_m;
@@ -489,17 +497,24 @@ int launch_conv_dense(const cprune_conv_desc& d, const void* x, const void* w, c
   const size_t es = dtype_size(d.dtype);
   if (tv.split) return launch_split_conv(d, tv, lay, x, w, bias, residual, y, ws, s);
   if (tv.rows) {
-    RowsArgs a = rows_tiles(d, tv);
+    RowsArgs a = rows_tiles(d, tv, lay);
     a.x = x; a.w = lay.w_wave; a.bias = bias; a.res = residual; a.y = y;
     a.N = d.n; a.H = d.h; a.W = d.w; a.O = d.c_out; a.Cp = lay.cp_in; a.Cop = lay.cp_out;
     a.magic_m = magic_for((unsigned)a.tiles_m); a.magic_x = magic_for((unsigned)a.tiles_x); a.magic_y = magic_for((unsigned)a.tiles_y);
     a.x_bytes = (unsigned)((size_t)d.n * lay.cp_in * d.h * d.w * es);
     a.w_bytes = (unsigned)wave_packed_bytes(d.c_out, lay.cp_in, d.dtype);
+    if (d.dtype == CPRUNE_F32) {
+      a.w = lay.w_rows3;
+      a.w_bytes = (unsigned)split_packed_bytes(d.c_out, lay.cp_in, 9, d.dtype, true);
+    }
+    a.w_raw = w;
+    a.w_raw_bytes = (unsigned)((size_t)d.c_out * 9 * lay.cp_in * es);
     a.y_bytes = (unsigned)((size_t)d.n * lay.cp_out * d.h * d.w * es);
     a.nchunk = (lay.cp_in + 31) / 32;
     a.act = d.act; a.pool = lay.pool;
     const dim3 grid((unsigned)((a.strips + tv.wn - 1) / tv.wn * a.tiles_m));
-    const int rc = d.dtype == CPRUNE_F16 ? launch_conv_rows_f16(tv.patch_id, grid, s, a) : launch_conv_rows_bf16(tv.patch_id, grid, s, a);
+    const int rc = d.dtype == CPRUNE_F32 ? launch_conv_rows_f32(tv.patch_id, grid, s, a) :
+                   d.dtype == CPRUNE_F16 ? launch_conv_rows_f16(tv.patch_id, grid, s, a) : launch_conv_rows_bf16(tv.patch_id, grid, s, a);
     if (rc != CPRUNE_OK) return rc;
     CPRUNE_LAUNCH_CHECK();
     return CPRUNE_OK;

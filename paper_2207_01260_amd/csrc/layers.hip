@@ -492,9 +492,8 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const T* __restrict__ w
   const int tap = u / ng, c0 = chunk * 32 + (u - tap * ng) * 8;
   uint32_t part[P][4];
   T vals[8];
-  const bool row = o < o_count && tap < taps;
+  const bool row = o < o_count && tap < taps && c0 < c_count;
   const size_t step = khwc ? 1 : taps;
-  // (a chunk's first channel is always one that exists: c0 of a real unit is below c_count)
   const T* const src = w + (row ? (khwc ? ((size_t)o * taps + tap) * c_count + c0 : ((size_t)o * c_count + c0) * taps + tap) : 0);
 #pragma unroll
   for (int e = 0; e < 8; ++e) vals[e] = src[row && c0 + e < c_count ? e * step : 0];   // (all eight in flight at once)
@@ -802,13 +801,13 @@ int launch_pack_expand(const void* w, int ce, int cp, int xh, int dt, void* y, h
   return CPRUNE_OK;
 }
 
-size_t split_packed_bytes(int o, int c, int taps, int dt) {
-  return (size_t)((o + 15) / 16) * split_rounds(c, taps, nullptr, nullptr, nullptr) * (dt == CPRUNE_F32 ? 3072 : 1024);
+size_t split_packed_bytes(int o, int c, int taps, int dt, bool whole) {
+  return (size_t)((o + 15) / 16) * split_rounds(whole ? (c + 31) / 32 * 32 : c, taps, nullptr, nullptr, nullptr) * (dt == CPRUNE_F32 ? 3072 : 1024);
 }
 
-int launch_pack_split(const void* w, int o, int c, int taps, int khwc, int dt, void* y, hipStream_t s) {
+int launch_pack_split(const void* w, int o, int c, int taps, int khwc, int dt, void* y, hipStream_t s, bool whole) {
   int nfull, groups_last, rounds_last;
-  const int rtot = split_rounds(c, taps, &nfull, &groups_last, &rounds_last);
+  const int rtot = split_rounds(whole ? (c + 31) / 32 * 32 : c, taps, &nfull, &groups_last, &rounds_last);
   const long total = (long)((o + 15) / 16) * rtot * 64;
   CPRUNE_BY_DTYPE(dt, hipLaunchKernelGGL(pack_split_kernel<T>, blocks_for(total), dim3(256), 0, s, (const T*)w, (uint4*)y,
                                          (int)total, o, c, taps, khwc, nfull, groups_last, rtot));
