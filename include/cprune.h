@@ -321,8 +321,10 @@ int cprune_net_layer_times(cprune_net* net, const void* x, int n, int iters, flo
  * NCHW [n][c_out][h_out][w_out].  For the last layer of a net whose output map is 1x1 the
  * values are those of the last cprune_net_layer_times pass (forward writes that layer
  * straight into `logits`).  A conv layer whose following 2x2 max-pool was fused into its
- * epilogue has no activation of its own: CPRUNE_ERR_UNSUPPORTED (ask for the pool layer); so
- * has a depthwise layer that runs inside the kernel of the 1x1 conv that reads it. */
+ * epilogue has no activation of its own: CPRUNE_ERR_UNSUPPORTED (ask for the pool layer); neither
+ * has a layer that runs inside the kernel of a later one (cprune_net_layer_fused): a depthwise layer inside the 1x1
+ * conv that reads it, the expansion in front of it, and, in handles created with tune != 0, a 3x3 / stride 2 first layer
+ * in front of it. */
 int cprune_net_copy_activation(cprune_net* net, int layer, int n, void* dst, size_t dst_bytes,
                                void* stream);
 /* Shape of one image's output (the last layer's c_out, h_out, w_out); host outs. */

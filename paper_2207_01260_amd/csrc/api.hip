@@ -628,27 +628,34 @@ static int mbrow_auto_ks(const MbArgs& a, int n, int tiles_m, int ks) {
 
 // Depthwise layer P.fuse_dw and the 1x1 layer i in one kernel, reading the depthwise layer's input; with the expansion
 // P.fuse_block in it as well, reading the expansion's input.
-static int net_run_mbrow(cprune_net* net, int i, int n, void* dst, hipStream_t s) {
+static bool mbrow_form_of(const cprune_net& net, const NetLayer& P, const NetLayer* E, int* mb, int* xh) {
+  if (E && E->nchw_in) return mbrow_image_form(net.dtype, P.d.c_out, mb, xh);
+  return mbrow_form(net.dtype, P.d.c_out, E ? E->cp_in : 0, mb, xh);
+}
+
+static int net_run_mbrow(cprune_net* net, int i, int n, const void* x, void* dst, hipStream_t s) {
   const NetLayer& P = net->layers[i];
   const NetLayer& D = net->layers[P.fuse_dw];
   const NetLayer* E = P.fuse_block >= 0 ? &net->layers[P.fuse_block] : nullptr;
   const size_t es = dtype_size(net->dtype);
   int mb = 0, xh = 0;
-  if (!mbrow_form(net->dtype, P.d.c_out, E ? E->cp_in : 0, &mb, &xh)) return CPRUNE_ERR_UNSUPPORTED;
+  if (!mbrow_form_of(*net, P, E, &mb, &xh)) return CPRUNE_ERR_UNSUPPORTED;
+  const bool image = E && E->nchw_in;
   MbArgs a;
-  a.x = net->layers[E ? E->d.input : D.d.input].act;
+  a.x = image ? x : net->layers[E ? E->d.input : D.d.input].act;
+  a.Hi = image ? E->h_in : 0; a.Wi = image ? E->w_in : 0;
   a.we = E ? E->w_expand : nullptr; a.be = E ? E->b : nullptr;
   a.wdw = D.w; a.bdw = D.b; a.wp = P.w_proj; a.bp = P.b;
   a.res = P.d.residual >= 0 ? net->layers[P.d.residual].act : nullptr;
   a.y = dst;
   a.N = n; a.H = D.h_in; a.W = D.w_in; a.Ho = D.h_out; a.Wo = D.w_out;
-  a.Cpi = E ? E->cp_in : 0; a.Ce = D.d.c_out; a.Cpe = D.cp_in; a.O = P.d.c_out; a.Cop = P.cp_out;
+  a.Cpi = image ? E->d.c_in : E ? E->cp_in : 0; a.Ce = D.d.c_out; a.Cpe = D.cp_in; a.O = P.d.c_out; a.Cop = P.cp_out;
   a.act_e = E ? E->d.act : CPRUNE_ACT_NONE; a.act_dw = D.d.act; a.act_out = P.d.act;
   const int low = E ? P.block_low : P.dw_low;
   mbrow_tiles(D, mb, low, &a);
   a.magic_x = a.tiles_x > 1 ? (unsigned)((0x100000000ull + a.tiles_x - 1) / a.tiles_x) : 0u;
   a.magic_y = a.tiles_y > 1 ? (unsigned)((0x100000000ull + a.tiles_y - 1) / a.tiles_y) : 0u;
-  a.x_bytes = (unsigned)((size_t)n * a.H * a.W * (E ? a.Cpi : a.Cpe) * es);
+  a.x_bytes = (unsigned)((size_t)n * (image ? (size_t)a.Hi * a.Wi : (size_t)a.H * a.W) * (E ? a.Cpi : a.Cpe) * es);
   a.we_bytes = E ? (unsigned)expand_packed_bytes(a.Ce, xh, net->dtype) : 0u;
   a.wp_bytes = (unsigned)rows_packed_bytes(a.O, a.Cpe, net->dtype);
   a.wdw_bytes = (unsigned)((size_t)D.d.k * D.d.k * a.Cpe * es);
@@ -725,7 +732,7 @@ static int net_run_layer(cprune_net* net, int i, int n, const void* x, void* out
   const void* src = L.d.input < 0 ? (L.nchw_in ? x : net->x_cl) : net->layers[L.d.input].act;
   void* dst = out_override ? out_override : L.act;
   if (L.fused_away) return CPRUNE_OK;
-  if (L.fuse_dw >= 0) return net_run_mbrow(net, i, n, dst, s);
+  if (L.fuse_dw >= 0) return net_run_mbrow(net, i, n, x, dst, s);
   if (L.fuse_stem >= 0) return net_run_stem2(net, i, n, x, dst, s);
   if (L.stem7) return net_run_stem7(net, i, n, src, dst, s);
   if (L.stem) return net_run_stem(net, i, n, src, dst, s);
@@ -783,7 +790,7 @@ static int time_mbrow(cprune_net* net, const int* layers, int n_layers, int* low
   const NetLayer& P = net->layers[layers[n_layers - 1]];
   const NetLayer& D = net->layers[P.fuse_dw];
   int mb = 0, xh = 0, best_low = 0, best_ks = 0;
-  mbrow_form(net->dtype, P.d.c_out, P.fuse_block >= 0 ? net->layers[P.fuse_block].cp_in : 0, &mb, &xh);
+  mbrow_form_of(*net, P, P.fuse_block >= 0 ? &net->layers[P.fuse_block] : nullptr, &mb, &xh);
   for (int l = 0; l < 2; ++l) {
     if (l && mbrow_rows(D.d.k, D.d.stride, mb, 0) == mbrow_rows(D.d.k, D.d.stride, mb, 1)) break;
     MbArgs a;
@@ -793,7 +800,7 @@ static int time_mbrow(cprune_net* net, const int* layers, int n_layers, int* low
     for (int k = k0; k <= 8 && k <= 2 * k0; k *= 2) {
       float ms = 0.f;
       *low = l; *ks = k;
-      const int rc = time_layers(net, layers, n_layers, net->max_batch, nullptr, s, &ms);
+      const int rc = time_layers(net, layers, n_layers, net->max_batch, net->x_cl, s, &ms);
       if (rc != CPRUNE_OK) return rc;
       if (!best_ks || ms < *best) { *best = ms; best_ks = k; best_low = l; }
     }
@@ -1194,10 +1201,15 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
                  E.cp_out == round_up_vec(ed.c_out, dtype) && E.cp_out == D.cp_in && only_reader(dd.input) == i &&
                  mbrow_form(dtype, pd.c_out, E.cp_in, &mb, &xh);
     const bool on_request = block && block_on_request(*net, E, D, P);
+    // the network's first layer in the place of the expansion (3x3 / stride 2 on the image): only where timed as faster
+    if (!block && tune && E.nchw_in && ed.c_in <= 3 && ed.k == 3 && ed.stride == 2 && ed.pad == 1 && ed.groups == 1 && ed.residual < 0 &&
+        !E.fused_pool && !E.fused_away && E.stem_reader < 0 && E.cp_out == D.cp_in && dd.k == 3 && dd.stride == 1 &&
+        only_reader(dd.input) == i && D.w_in > 8)
+      block = mbrow_image_form(dtype, pd.c_out, &mb, &xh);
     block = block && (on_request || tune);
     if (block) {
       rc = dev_alloc(expand_packed_bytes(ed.c_out, xh, dtype), &E.w_expand);
-      if (rc == CPRUNE_OK) rc = launch_pack_expand(E.w, ed.c_out, E.cp_in, xh, dtype, E.w_expand, s);
+      if (rc == CPRUNE_OK) rc = launch_pack_expand(E.w, ed.c_out, E.nchw_in ? ed.c_in * 9 : E.cp_in, xh, dtype, E.w_expand, s);
       if (rc != CPRUNE_OK) break;
       if (on_request) D.block_expand = dd.input;
     }
@@ -1216,7 +1228,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
       const int n_timed = block ? 3 : 2;
       float best = 0.f, ms = 0.f;
       set_form(0);
-      rc = time_layers(net, timed, n_timed, max_batch, nullptr, s, &best);
+      rc = time_layers(net, timed, n_timed, max_batch, net->x_cl, s, &best);
       form = 0;
       if (rc == CPRUNE_OK && block) {
         set_form(2);

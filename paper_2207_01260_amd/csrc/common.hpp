@@ -150,6 +150,7 @@ struct MbArgs {
   const void* res;      // [n][ho][wo][cop] shortcut or null
   void* y;              // [n][ho][wo][cop]
   int N, H, W, Ho, Wo, Cpi, Ce, Cpe, O, Cop;
+  int Hi, Wi;           // image form (x is the NCHW image of cpi channels, H x W the first layer's map): its size, otherwise 0
   int act_e, act_dw, act_out;
   int tiles_y, tiles_x; // strips of a map
   int ipt;              // images side by side in the 16 columns of a strip: 1 or 2
@@ -168,12 +169,17 @@ constexpr int mbrow_rows(int k, int s, int mb, int low) {
   if (k == 3) return mb <= 4 ? (low ? 2 : 4) : 2;
   return mb <= 4 ? 2 : 1;
 }
+// elements from row to row of the staged image: 33 columns and what turns the rows' banks
+constexpr int mbrow_image_pitch(int es) { return es == 4 ? 35 : 38; }
 // columns at the left / right end of a strip whose window reaches into the neighbouring strip
 constexpr int mbrow_halo_left(int k, int s) { return s == 1 ? k / 2 : 1; }
 constexpr int mbrow_halo_right(int k, int s) { return s == 1 ? k / 2 : k == 5 ? 1 : 0; }
 // The smallest built form for c_out filters and an input of cp_in channels (0: no expansion): mb 16-filter blocks and xh
 // 32-byte units of a pixel's input.  false: none (c_out above 128 with an expansion, or too many input channels).
 bool mbrow_form(int dt, int c_out, int cp_in, int* mb, int* xh);
+// The image form: a 3x3 / stride 2 / pad 1 first layer on at most 3 channels, a 3x3 / stride 1 depthwise layer on a map
+// wider than 8, up to 32 filters.
+bool mbrow_image_form(int dt, int c_out, int* mb, int* xh);
 // grid = (strips, filter tiles), ks in {1, 2, 4, 8} wavefronts that share a strip.
 // CPRUNE_ERR_UNSUPPORTED for other combinations.
 int launch_mbrow_f32(int k, int stride, int mb, int xh, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a);

@@ -744,4 +744,10 @@ bool mbrow_form(int dt, int c_out, int cp_in, int* mb, int* xh) {
   return false;
 }
 
+bool mbrow_image_form(int dt, int c_out, int* mb, int* xh) {
+  *mb = c_out <= 16 ? 1 : 2;
+  *xh = dt == CPRUNE_F32 ? 4 : 2;
+  return c_out <= 32;
+}
+
 }  // namespace cprune

@@ -16,6 +16,8 @@
 // No LDS access, no barrier and no conversion lies between the steps.  LDS holds the block input of the strip (read as
 // the expansion's B operand once per chunk); KS wavefronts of a work-group share a strip and split its chunks, their sums
 // meet in LDS at the end, in order.  Weights come from L2 in operand order, once per chunk and wavefront.
+// IMG: the layer in front of the depthwise one is the network's first, a 3x3 / stride 2 layer on an NCHW image of at most 3
+// channels; the image is staged, and a lane gathers its terms of a window from there.
 // Neighbouring strips overlap by the window's halo: 14 of 16 columns (k = 3) and R of R + k - 1 rows are new.
 //
 // Values handed from step to step are rounded to the activation type, as the separate layers store them.
@@ -24,7 +26,7 @@
 // faster of both / this kernel.  MobileNetV2 fp32 at batch 64: 16 -> 50 -> 24, 112x112 stride 2: 110 / 42; 24 -> 65 -> 24 at 56x56:
 // 70 / 33; 24 -> 86 -> 32, 56x56 stride 2: 56 / 24; 32 -> 92 -> 32 at 28x28: 30 / 18; 64 -> 330 -> 64 at 14x14: 38 / 26.  MnasNet bf16 at
 // batch 16: 16 -> 38 -> 24, 112x112: 20 / 11; 24 -> 58 -> 24 at 56x56: 15 / 9.  Without an expansion: 32 -> 16 at 112x112, fp32 b64
-// 52 / 42.  In fp32 the matrix cores bound it: inside the chunk loop they are busy 60 % of the time (24 -> 65 -> 24: 4.9 us per chunk
+// 52 / 42; with the first layer in front of it (image 3 -> 32 -> 16) 88 / 62, bf16 b16 20.3 / 16.6 (the windows' gather from LDS).  In fp32 the matrix cores bound it: inside the chunk loop they are busy 60 % of the time (24 -> 65 -> 24: 4.9 us per chunk
 // for 2048 strips, 3.0 us of it MFMA issue), launch, staging and stores are 9 of the 33 us.
 #pragma once
 #include <atomic>
@@ -62,7 +64,7 @@ __device__ __forceinline__ uint2 load_b64(__amdgpu_buffer_rsrc_t r, unsigned vof
   return make_uint2(v.x, v.y);
 }
 
-template <typename T, int K, int S, int MB, int XH, int R>
+template <typename T, int K, int S, int MB, int XH, int R, bool IMG>
 __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   constexpr int ES = (int)sizeof(T);
   constexpr int EPI = 16 / ES;
@@ -75,6 +77,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   constexpr int XP = XH * 32 + 16;             // bytes per staged pixel
   constexpr int XR = XH / 2;                   // whole 64-byte rounds of the expansion's reduction
   constexpr bool EXP = XH > 0;
+  constexpr int IROWS = 2 * ROWS + 1, IPITCH = mbrow_image_pitch(ES);   // IMG: rows and row pitch of the staged image
   constexpr bool AHEAD = !(EXP && K == 5 && ES == 2);   // window weights asked for one block ahead (there they do not fit)
 
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -112,8 +115,28 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
 
   if constexpr (EXP) {
     // the strip's block input: zeros outside the image and past the last channel
-    constexpr int ITEMS = ROWS * CW * XQ;
     const int nthr = ks * 64;
+    if constexpr (IMG) {
+      // the image under the strip's windows, [channel][row][column], zeros outside; all loads of a batch in flight together
+      constexpr int ITEMS = 3 * IROWS * 33, U = 16;
+      for (int b0 = t; b0 < ITEMS; b0 += nthr * U) {
+        typename Elem<T>::raw_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int idx = b0 + u * nthr;
+          const int row = idx / 33, ix = 2 * j0 - 1 + idx - row * 33;
+          const int c = row / IROWS, iy = 2 * iy0 - 1 + row - c * IROWS;
+          const bool in = (idx < ITEMS) & (c < a.Cpi) & ((unsigned)iy < (unsigned)a.Hi) & ((unsigned)ix < (unsigned)a.Wi);
+          v[u] = Elem<T>::load(xr, in ? (unsigned)(((n0 * a.Cpi + c) * a.Hi + iy) * a.Wi + ix) * ES : kOutOfRange, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int idx = b0 + u * nthr;
+          if (idx < ITEMS) ((typename Elem<T>::raw_t*)lds)[(idx / 33) * IPITCH + idx % 33] = v[u];
+        }
+      }
+    } else {
+    constexpr int ITEMS = ROWS * CW * XQ;
     auto stage = [&](auto u_tag) {
       constexpr int U = decltype(u_tag)::value;       // loads in flight per thread
       for (int b0 = t; b0 < ITEMS; b0 += nthr * U) {
@@ -139,6 +162,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
     constexpr int ONE = (ITEMS + 63) / 64;
     if (ks == 1) stage(std::integral_constant<int, (ONE > 20 ? 20 : ONE)>{});
     else stage(std::integral_constant<int, 10>{});
+    }
   }
 
   // depthwise weights: byte offset of the lane's channels, out of range for taps outside the image
@@ -185,6 +209,26 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
     for (int i = 0; i < ROWS; ++i) load_row(wave, i);
   }
   const unsigned char* xl = lds + S * r * XP + g4 * 16;
+  // IMG: where the lane's terms of a window lie in the staged image, k = (channel, row, column); terms past the last are zero
+  int i_off[IMG ? XR * EPI : 1];
+  bool i_ok[IMG ? XR * EPI : 1];
+  if constexpr (IMG) {
+#pragma unroll
+    for (int q = 0; q < XR * EPI; ++q) {
+      const int k = (q / EPI) * 4 * EPI + g4 * EPI + q % EPI, c = k / 9, u = (k - c * 9) / 3;
+      i_ok[q] = k < a.Cpi * 9;
+      i_off[q] = i_ok[q] ? (c * IROWS + u) * IPITCH + k - c * 9 - u * 3 + 2 * r : 0;
+    }
+  }
+  auto window = [&](int i, int j) -> uint4 {
+    T v[EPI];
+#pragma unroll
+    for (int e = 0; e < EPI; ++e) {
+      const T w = ((const T*)lds)[2 * i * IPITCH + i_off[IMG ? j * EPI + e : 0]];
+      v[e] = i_ok[IMG ? j * EPI + e : 0] ? w : (T)0.0f;
+    }
+    return *(const uint4*)v;
+  };
   // Weights of one block of 16 channels (chunk c, block h), carried in registers: those of the next block are asked for as
   // soon as the last row has used the present ones.
   typedef typename std::conditional<ES == 4, uint4, uint2>::type Quad;     // four channels
@@ -263,7 +307,9 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
             float4_t ev = be;
 #pragma unroll
             for (int j = 0; j < XR; ++j) {
-              const uint4 b = *(const uint4*)&xl[(i * CW + s) * XP + j * 64];
+              uint4 b;
+              if constexpr (IMG) b = window(i, j);
+              else b = *(const uint4*)&xl[(i * CW + s) * XP + j * 64];
               float4_t d[1][1] = {{ev}};
               const uint4 aa[1] = {ae[j]}, bb[1] = {b};
               mma_slab<T, 1, 1, 1>(aa, bb, d);
@@ -460,9 +506,10 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
 }
 
 // LDS of a work-group: the strip's input, later the sums of `slots` wavefronts
-template <typename T, int K, int S, int MB, int XH, int R>
+template <typename T, int K, int S, int MB, int XH, int R, bool IMG>
 inline int launch_mbrow_rows(dim3 grid, int ks, hipStream_t s, MbArgs a) {
-  constexpr int strip = ((R - 1) * S + K) * 16 * S * (XH ? XH * 32 + 16 : 0);
+  constexpr int strip = IMG ? 3 * (2 * (R + 2) + 1) * mbrow_image_pitch((int)sizeof(T)) * (int)sizeof(T)
+                            : ((R - 1) * S + K) * 16 * S * (XH ? XH * 32 + 16 : 0);
   constexpr int slot = R * MB * 1024;
   static_assert(strip <= 160 * 1024 && 4 * slot <= 160 * 1024, "LDS budget");
   a.slots = ks > 4 ? 4 : ks;
@@ -471,20 +518,20 @@ inline int launch_mbrow_rows(dim3 grid, int ks, hipStream_t s, MbArgs a) {
   if (bytes > 65536) {   // more than the default 64 KiB has to be asked for once
     static std::atomic<bool> raised{false};
     if (!raised.load(std::memory_order_relaxed)) {
-      CPRUNE_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&mbrow_kernel<T, K, S, MB, XH, R>),
+      CPRUNE_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&mbrow_kernel<T, K, S, MB, XH, R, IMG>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
       raised.store(true, std::memory_order_relaxed);
     }
   }
-  hipLaunchKernelGGL((mbrow_kernel<T, K, S, MB, XH, R>), grid, dim3(64 * ks), bytes, s, a);
+  hipLaunchKernelGGL((mbrow_kernel<T, K, S, MB, XH, R, IMG>), grid, dim3(64 * ks), bytes, s, a);
   return CPRUNE_OK;
 }
 
-template <typename T, int K, int S, int MB, int XH>
+template <typename T, int K, int S, int MB, int XH, bool IMG = false>
 inline int launch_mbrow_one(int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a) {
   constexpr int R0 = mbrow_rows(K, S, MB, 0), R1 = mbrow_rows(K, S, MB, 1);
-  if (R0 == R1 || !low) return launch_mbrow_rows<T, K, S, MB, XH, R0>(grid, ks, s, a);
-  return launch_mbrow_rows<T, K, S, MB, XH, R1>(grid, ks, s, a);
+  if (R0 == R1 || !low) return launch_mbrow_rows<T, K, S, MB, XH, R0, IMG>(grid, ks, s, a);
+  return launch_mbrow_rows<T, K, S, MB, XH, R1, IMG>(grid, ks, s, a);
 }
 
 // (MB, XH) pairs that are built; XH = 0: depthwise + projection only.  mbrow_form picks one of them.
@@ -504,8 +551,18 @@ inline int launch_mbrow_ks(int mb, int xh, int low, dim3 grid, int ks, hipStream
   return CPRUNE_ERR_UNSUPPORTED;
 }
 
+// The image form: 27 terms in one 32-byte unit per 8 (16) numbers.
+template <typename T>
+inline int launch_mbrow_image(int mb, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a) {
+  constexpr int XH = sizeof(T) == 4 ? 4 : 2;
+  if (mb == 1) return launch_mbrow_one<T, 3, 1, 1, XH, true>(low, grid, ks, s, a);
+  if (mb == 2) return launch_mbrow_one<T, 3, 1, 2, XH, true>(low, grid, ks, s, a);
+  return CPRUNE_ERR_UNSUPPORTED;
+}
+
 template <typename T>
 inline int launch_mbrow(int k, int stride, int mb, int xh, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a) {
+  if (a.Hi > 0) return k == 3 && stride == 1 ? launch_mbrow_image<T>(mb, low, grid, ks, s, a) : CPRUNE_ERR_UNSUPPORTED;
   if (k == 3 && stride == 1) return launch_mbrow_ks<T, 3, 1>(mb, xh, low, grid, ks, s, a);
   if (k == 3 && stride == 2) return launch_mbrow_ks<T, 3, 2>(mb, xh, low, grid, ks, s, a);
   if (k == 5 && stride == 1) return launch_mbrow_ks<T, 5, 1>(mb, xh, low, grid, ks, s, a);

@@ -98,3 +98,37 @@ def test_images_of_one_strip_do_not_meet(hw, k, stride, form):
         torch.cuda.synchronize()
         assert torch.equal(got[1 - bad], want[1 - bad]), bad
     handle.close()
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.F16, B.BF16])
+@pytest.mark.parametrize("cfg", [(3, 32, 16, 224, 4), (3, 27, 24, 150, 3), (1, 40, 32, 131, 2)])
+def test_first_layer_in_the_block(orc, cfg, dtype):
+    """A 3x3 / stride 2 first layer, the depthwise layer and the projection behind it, as a tuned handle runs them (one kernel
+    where it times faster: there is no call that forces it): even and odd images, one channel, ragged filter counts."""
+    c, c_exp, c_out, hw, batch = cfg
+    net = synth.NetSpec(f"first_{c}_{c_exp}_{c_out}_{hw}", c, hw, hw)
+    e = net.add(synth.Layer("conv", -1, c, c_exp, k=3, stride=2, pad=1, act=synth.ACT_RELU6, bn=True, name="e"))
+    d = net.add(synth.Layer("conv", e, c_exp, c_exp, k=3, stride=1, pad=1, groups=c_exp, act=synth.ACT_RELU6, bn=True, name="d"))
+    net.add(synth.Layer("conv", d, c_exp, c_out, k=1, act=synth.ACT_NONE, bn=True, name="p"))
+    params = synth.layer_params(net, 73)
+    x = synth.net_input(net, 73, batch)
+    ref_layers, _ = orc.prune_net(net, params)
+    ref = orc.forward(net, ref_layers, x)
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(params), dtype)
+    handle = pipeline.build_net(net, layers, batch, dtype, tune=True)
+    xd = torch.from_numpy(x).cuda().to(B.TORCH_DTYPE[dtype])
+    print(cfg, dtype, "one kernel:", handle.layer_fused(e), flush=True)
+    for n in (batch, 1):
+        for graph in (False, True):
+            out = handle.forward(xd[:n].contiguous(), use_graph=graph)
+            torch.cuda.synchronize()
+            assert nmax(out.float().cpu().numpy(), ref[:n]) < TOL[dtype]
+    if handle.layer_fused(e):
+        handle.fuse_block(d, False)                 # the first layer on its own again
+        assert not handle.layer_fused(e) and handle.layer_fused(d)
+        with pytest.raises(B.CPruneError):
+            handle.fuse_block(d, True)
+        out = handle.forward(xd)
+        torch.cuda.synchronize()
+        assert nmax(out.float().cpu().numpy(), ref) < TOL[dtype]
+    handle.close()
