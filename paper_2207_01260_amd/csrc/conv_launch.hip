@@ -402,6 +402,7 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
     // alone fill the chip several times
     if (!(lay.nhwc && (d.dtype == CPRUNE_F32 ? lay.w_rows3 && tv.mb == 1 : lay.w_wave != nullptr) && d.kh == 3 && d.kw == 3 && d.stride == 1 && d.pad == 1)) return false;
     if (lay.pool == 2 || (lay.pool && ((d.h | d.w) & 1))) return false;
+    if (lay.cp_out & 3) return false;      // four filters per store: not a dense map of logits
     const RowsArgs p = rows_tiles(d, tv, lay);
     const long waves = (long)p.strips * p.tiles_m;
     if (d.dtype == CPRUNE_F32 && split_packed_bytes(d.c_out, lay.cp_in, 9, d.dtype, true) >= ((size_t)1 << 31)) return false;

@@ -92,3 +92,96 @@ def test_rows_neighbours_do_not_leak(hw, batch):
             near[batch - 1, :, max(0, px[0] - 1):px[0] + 2, max(0, px[1] - 1):px[1] + 2] = True
             assert torch.equal(got[~near], want[~near]), (v, px)
     handle.close()
+
+
+@pytest.mark.parametrize("cfg", [
+    # c_in, c_out, hw, batch, pool, shortcut
+    (32, 16, 16, 1, False, False),     # one strip, one chunk, one block
+    (33, 17, 17, 2, False, True),      # one column into the second strip, a channel into the second chunk
+    (40, 50, 30, 1, False, False),     # strips of 14 new columns: two exactly
+    (24, 20, 31, 2, False, True),      # and one column more, ragged rows
+    (130, 48, 7, 3, False, True),      # two images per strip, one missing; five chunks
+    (260, 70, 8, 5, False, False),     # eight columns: the images of a strip touch
+    (70, 65, 4, 6, False, True),       # four images per strip, two missing
+    (300, 20, 3, 3, False, False),     # three columns of four lanes, eight wavefronts share a strip
+    (48, 40, 28, 2, True, False),      # pool: strips of 12 new columns, two exactly
+    (64, 30, 30, 1, True, False),      # pool, two columns more
+    (40, 24, 18, 2, True, False),      # pool, ragged strip
+    (96, 36, 8, 3, True, False),       # pool, two images
+    (160, 24, 4, 5, True, False),      # pool, four images
+    (20, 24, 6, 3, True, False),       # pool, six of eight lanes
+])
+def test_split_rows_variants(orc, cfg):
+    """The fp32 kernel, whose strips overlap where a map is wider than 16.  Its sums of at most 2700 terms are off by less than 1e-6
+    of their largest; 1e-5 leaves room for the layers around it."""
+    c_in, c_out, hw, batch, pool, shortcut = cfg
+    print(cfg, flush=True)
+    net = synth.NetSpec(f"rows3_{c_in}_{c_out}_{hw}_{pool}", 3, hw, hw)
+    a = net.add(synth.Layer("conv", -1, 3, c_in, k=1, act=synth.ACT_RELU, bn=True, name="a"))
+    r = net.add(synth.Layer("conv", -1, 3, c_out, k=1, act=synth.ACT_NONE, bn=True, name="r")) if shortcut else None
+    b = net.add(synth.Layer("conv", a, c_in, c_out, k=3, stride=1, pad=1, act=synth.ACT_RELU, bn=True, residual=r, name="b"))
+    if pool:
+        p = net.add(synth.Layer("maxpool", b, c_out, c_out, k=2, stride=2, name="p"))
+        net.add(synth.Layer("conv", p, c_out, 8, k=1, act=synth.ACT_NONE, bn=True, name="c"))
+    params = synth.layer_params(net, 82)
+    x = synth.net_input(net, 82, batch)
+    ref_layers, _ = orc.prune_net(net, params)
+    ref = orc.forward(net, ref_layers, x)
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(params))
+    handle = pipeline.build_net(net, layers, batch, tune=False)
+    xd = torch.from_numpy(x).cuda()
+    ran = []
+    for v in range(B.cprune_num_tile_variants()):
+        if "conv_split_rows" not in B.cprune_tile_variant_name(v, True, B.F32):
+            continue
+        try:
+            handle.set_layer_variant(b, v)
+        except B.CPruneError as e:
+            assert e.status == B.ERR_UNSUPPORTED
+            continue
+        out = handle.forward(xd)
+        torch.cuda.synchronize()
+        err = nmax(out.cpu().numpy(), ref)
+        assert err < 1e-5, (B.cprune_tile_variant_name(v, True, B.F32), err)
+        ran.append(v)
+    assert len(ran) >= 2, ran        # tall and low strips, more with wavefronts that share a strip
+    handle.close()
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.F16, B.BF16])
+@pytest.mark.parametrize("c_out", [45, 46, 48])
+def test_a_dense_map_of_logits_is_written_filter_by_filter(orc, c_out, dtype):
+    """A network that ends in a 3x3 layer on a 1x1 map has its logits written without padding: a kernel that stores four filters at
+    a time takes it only where a multiple of four filters is left.  Nothing behind the logits is touched."""
+    batch = 5
+    net = synth.NetSpec(f"rows_logits_{c_out}", 3, 1, 1)
+    a = net.add(synth.Layer("conv", -1, 3, 24, k=1, act=synth.ACT_RELU, bn=True, name="a"))
+    b = net.add(synth.Layer("conv", a, 24, c_out, k=3, stride=1, pad=1, act=synth.ACT_NONE, bn=True, name="b"))
+    params = synth.layer_params(net, 83)
+    x = synth.net_input(net, 83, batch)
+    ref_layers, _ = orc.prune_net(net, params)
+    ref = orc.forward(net, ref_layers, x)
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(params), dtype)
+    handle = pipeline.build_net(net, layers, batch, dtype, tune=False)
+    xd = torch.from_numpy(x).cuda().to(B.TORCH_DTYPE[dtype])
+    taken = []
+    for v in [-1] + list(range(B.cprune_num_tile_variants())):
+        if v >= 0:
+            if "_rows_kernel" not in B.cprune_tile_variant_name(v, True, dtype):
+                continue
+            try:
+                handle.set_layer_variant(b, v)
+            except B.CPruneError as e:
+                assert e.status == B.ERR_UNSUPPORTED
+                continue
+            taken.append(v)
+            if c_out % 4:
+                continue                 # (must not be reached; not run)
+        out = torch.full((batch * c_out + 64,), 7.0, dtype=B.TORCH_DTYPE[dtype], device="cuda")
+        handle.forward(xd, logits=out)
+        torch.cuda.synchronize()
+        got = out.float().cpu().numpy()
+        assert (got[batch * c_out:] == 7.0).all(), v
+        assert nmax(got[:batch * c_out].reshape(ref.shape), ref) < (1e-5 if dtype == B.F32 else 2e-2), v
+    assert bool(taken) == (c_out % 4 == 0), taken
+    handle.close()
