@@ -653,8 +653,7 @@ static int net_run_mbrow(cprune_net* net, int i, int n, const void* x, void* dst
   a.act_e = E ? E->d.act : CPRUNE_ACT_NONE; a.act_dw = D.d.act; a.act_out = P.d.act;
   const int low = E ? P.block_low : P.dw_low;
   mbrow_tiles(D, mb, low, &a);
-  a.magic_x = a.tiles_x > 1 ? (unsigned)((0x100000000ull + a.tiles_x - 1) / a.tiles_x) : 0u;
-  a.magic_y = a.tiles_y > 1 ? (unsigned)((0x100000000ull + a.tiles_y - 1) / a.tiles_y) : 0u;
+  a.magic_x = strip_magic(a.tiles_x); a.magic_y = strip_magic(a.tiles_y);
   a.x_bytes = (unsigned)((size_t)n * (image ? (size_t)a.Hi * a.Wi : (size_t)a.H * a.W) * (E ? a.Cpi : a.Cpe) * es);
   a.we_bytes = E ? (unsigned)expand_packed_bytes(a.Ce, xh, net->dtype) : 0u;
   a.wp_bytes = (unsigned)rows_packed_bytes(a.O, a.Cpe, net->dtype);

@@ -8,6 +8,7 @@
 
 #include "cprune.h"
 #include "split_index.hpp"
+#include "strip_index.hpp"
 
 namespace cprune {
 
@@ -154,7 +155,7 @@ struct MbArgs {
   int act_e, act_dw, act_out;
   int tiles_y, tiles_x; // strips of a map
   int ipt;              // images side by side in the 16 columns of a strip: 1 or 2
-  unsigned magic_x, magic_y;   // ceil(2^32 / tiles_x), ceil(2^32 / tiles_y), 0 for a divisor of 1
+  unsigned magic_x, magic_y;   // strip_magic of tiles_x and tiles_y
   unsigned x_bytes, we_bytes, wp_bytes, wdw_bytes, y_bytes;
   int nchunk;           // 64-byte chunks of expanded channels
   int slots;            // wavefronts whose sums fit the exchange area (set by the launcher)

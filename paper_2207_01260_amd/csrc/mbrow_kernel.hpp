@@ -95,10 +95,8 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
     tile = xcd * q + (xcd < rem ? xcd : rem) + local;
   }
   const int o0 = blockIdx.y * (MB * 16);
-  const int rest = (int)fast_div((unsigned)tile, a.magic_x);
-  const int tx = tile - rest * a.tiles_x;
-  const int grp = (int)fast_div((unsigned)rest, a.magic_y);
-  const int ty = rest - grp * a.tiles_y;
+  const StripAt strip = strip_at(tile, a.tiles_x, a.tiles_y, a.magic_x, a.magic_y);
+  const int tx = strip.tx, ty = strip.ty, grp = strip.group;
   const bool two = a.ipt == 2;
   const int n0 = two ? 2 * grp : grp;
   const int j0 = tx * (16 - HL - HR);
