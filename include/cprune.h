@@ -136,7 +136,9 @@ int cprune_gather_pruned_weights(const float* w, int c_out, int c_in, int kh, in
  *   bias_out     device fp32 [rows kept]; may be NULL when there is neither BN nor conv_bias
  *   kept_out     device int32 [keep], ascending; required for ranked layers
  * The plan owns a few KB of device memory (its tables and the scores); inputs and outputs
- * stay the caller's and must outlive it.  create and destroy synchronise; run only enqueues. */
+ * stay the caller's and must outlive it.  create and destroy synchronise; run only enqueues.
+ * Runs of one plan share its memory and its outputs: runs that overlap (two streams) give the right result only on
+ * unchanged weights; where the weights change between them, order them (one stream, or an event). */
 typedef struct {
   const float* w;
   int32_t c_out, c_in, kh, kw;

@@ -324,7 +324,7 @@ __global__ __launch_bounds__(256) void plan_score_kernel(const RankJob* __restri
 // filters in front of it, so no filter waits for another and a layer is as many work-groups as it has 64 filters; each of
 // the 16 wavefronts counts a sixteenth of the scores, which are the same for all lanes (scalar loads, no LDS).  Scores are
 // sums of absolute values: as integers their bits order the same way.  The places behind a group's scores hold zeros, which
-// rank in front of nothing.  Nothing is handed between work-groups, so runs of a plan may overlap.
+// rank in front of nothing.  Nothing is handed between work-groups, so runs of a plan on the same weights may overlap.
 // Against one work-group per layer that sorts: 13 layers of VGG-16 9.9 -> 4.2 us.
 __global__ __launch_bounds__(1024) void plan_rank_kernel(const RankJob* __restrict__ jobs, int n_jobs,
                                                          const unsigned long long* __restrict__ scores,
@@ -379,7 +379,9 @@ __device__ __forceinline__ int kept_before(unsigned long long mask) {
 }
 
 // The kept lists come from the ranking's bits: every wavefront finds its row's filter by itself, and the work-group
-// spreads the kept channels into LDS while the source row travels there.
+// spreads the kept channels into LDS while the source row travels there.  A layer's bits count its survivors unless runs overlap
+// while the weights change (work-groups of one layer then rank different scores); whatever they count, every index stays
+// inside the source, the kept list and LDS.
 template <typename T>
 __global__ __launch_bounds__(256) void plan_gather_kernel(const GatherJob* __restrict__ jobs, int n_jobs, int list_at) {
   extern __shared__ __align__(16) float row[];
@@ -400,11 +402,12 @@ __global__ __launch_bounds__(256) void plan_gather_kernel(const GatherJob* __res
   int o = i;
   if (g.mask_out) {                      // the filter whose bit is the (i + 1)th set one
     const int first = kept_before(out);
-    const int m = __builtin_ctzll(__ballot(first <= i && i < first + __popcll(out)));
+    const unsigned long long at = __ballot(first <= i && i < first + __popcll(out));
+    const int m = at ? __builtin_ctzll(at) : 0;
     const unsigned long long word = __shfl(out, m, 64);
     const int rank = i - __shfl(first, m, 64);
-    const bool here = (word >> lane & 1ull) && __popcll(word & ((1ull << lane) - 1ull)) == rank;
-    o = m * 64 + __builtin_ctzll(__ballot(here));
+    const unsigned long long here = __ballot((word >> lane & 1ull) && __popcll(word & ((1ull << lane) - 1ull)) == rank);
+    o = here ? m * 64 + __builtin_ctzll(here) : g.c_out - 1;
     if (g.kept && slice == 0 && threadIdx.x == 0) g.kept[i] = o;
   }
   o = __builtin_amdgcn_readfirstlane(o);
@@ -413,10 +416,10 @@ __global__ __launch_bounds__(256) void plan_gather_kernel(const GatherJob* __res
     for (int f = threadIdx.x; f < (g.c_in + 63 & ~63); f += 256) {     // a wavefront's 64 channels are one word
       const unsigned long long word = __shfl(in, f >> 6, 64);
       const int at = __shfl(first, f >> 6, 64) + __popcll(word & ((1ull << lane) - 1ull));
-      if (word >> lane & 1ull) list[at] = (uint16_t)f;
+      if ((word >> lane & 1ull) && at < g.n_in) list[at] = (uint16_t)f;
     }
   }
-  gather_row<T>(g, i, o, slice, !g.mask_in, [&](unsigned c) { return (int)list[c]; }, row, terms);
+  gather_row<T>(g, i, o, slice, !g.mask_in, [&](unsigned c) { return min((int)list[c], g.c_in - 1); }, row, terms);
 }
 
 template <typename T>

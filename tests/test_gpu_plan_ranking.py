@@ -34,3 +34,43 @@ def test_plan_ranking_and_gather_at_word_edges(c):
             assert np.array_equal(plan.w_out[0].cpu().numpy(), w[kept]), (c, keep, rep)
             assert np.array_equal(plan.w_out[1].cpu().numpy(), v[second][:, kept]), (c, keep, rep)
         plan.close()
+
+
+def test_runs_that_overlap_while_weights_change_stay_in_bounds():
+    """Two streams run one plan while a third swaps its weights: results of those runs are not defined, but every kept index is a
+    filter and every gathered value one of the sources' (all powers of two here), and a run by itself afterwards is right."""
+    c, keep = 1024, 500
+    rng = np.random.default_rng(7)
+    sources = [2.0 ** rng.integers(-8, 9, (c, 9, 1, 1)).astype(np.float32) for _ in range(2)]
+    v = 2.0 ** rng.integers(-8, 9, (70, c, 1, 2)).astype(np.float32)
+    dev = [torch.from_numpy(q).cuda() for q in sources]
+    w = dev[0].clone()
+    plan = B.PrunePlan([{"w": w, "keep": keep, "rows_from": 0, "cols_from": -1},
+                        {"w": torch.from_numpy(v).cuda(), "keep": 66, "rows_from": 1, "cols_from": 0}], 1e-5)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    for rep in range(50):
+        for k, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                if k == 2:
+                    w.copy_(dev[rep & 1])
+                else:
+                    plan.run()
+        if rep % 10 == 9:
+            torch.cuda.synchronize()
+            print("overlapping plan runs", rep, flush=True)
+            kept = plan.kept[0].cpu().numpy()
+            assert kept.min() >= 0 and kept.max() < c
+            for got in (plan.w_out[0], plan.w_out[1]):
+                assert np.isin(got.cpu().numpy(), 2.0 ** np.arange(-8, 9)).all()
+    w.copy_(dev[1])
+    torch.cuda.synchronize()
+    plan.run()
+    torch.cuda.synchronize()
+    order = np.lexsort((np.arange(c), -sources[1].astype(np.float64).sum((1, 2, 3))))
+    kept = np.sort(order[:keep])
+    second = np.sort(np.lexsort((np.arange(70), -v.astype(np.float64).sum((1, 2, 3))))[:66])
+    assert np.array_equal(plan.kept[0].cpu().numpy(), kept)
+    assert np.array_equal(plan.w_out[0].cpu().numpy(), sources[1][kept])
+    assert np.array_equal(plan.w_out[1].cpu().numpy(), v[second][:, kept])
+    plan.close()
