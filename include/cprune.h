@@ -194,7 +194,7 @@ typedef struct {
  * kernels (conv_patch*: 3x3 layers, channels-last inside a network handle only, unsupported through
  * the NCHW call), the row-strip kernel (conv_rows_kernel in 16-bit, conv_split_rows_kernel in fp32 data:
  * 3x3 / stride 1 / pad 1 layers of a handle; its last template argument, which depends on the map, is not
- * part of the name here) and the split kernel (conv_split_kernel: any window at stride 1 or 2).  The split
+ * part of the name here; tile_m is at least the 32 filters that the two wavefronts of a SIMD hold) and the split kernel (conv_split_kernel: any window at stride 1 or 2).  The split
  * kernel multiplies fp32 data as three 16-bit parts per number on the 16-bit matrix cores; it runs fp32
  * layers of at least 16 terms per output, where its error is no larger than the fp32 instruction's, and
  * redoes with that instruction what three parts do not hold (infinities, results below 2^-50; inputs or
@@ -398,7 +398,8 @@ int cprune_prune_count(int c_out, int64_t step, int* count_out);
  * main_loop[2] = epilogue[2] = {tiles, blocks a tile holds} and *unit_out = the filters per block
  * (16, or 32 for the variants built on 32x32 blocks; the rows inside a block are fixed by the
  * instruction and cannot shrink).  The split kernel deals a layer's blocks evenly to its tiles, so that a
- * tile may run fewer than it holds; the step below is the same for either box.  Host outs. */
+ * tile may run fewer than it holds; the step below is the same for either box.  A tile of the row-strip kernel
+ * holds at least two blocks here, one for each of the two wavefronts that a SIMD runs side by side.  Host outs. */
 int cprune_variant_filter_splits(int variant, int c_out, int64_t* main_loop, int64_t* epilogue,
                                  int* unit_out);
 /* cprune_lcm_step of those splits, in filters (times the unit). */

@@ -235,7 +235,7 @@ extern "C" int cprune_num_tile_variants(void) { return num_variants(); }
 extern "C" int cprune_tile_variant_info(int v, int* tile_m, int* tile_p, int* sched) {
   if (v < 0 || v >= num_variants()) return CPRUNE_ERR_INVALID_ARG;
   const TileVariant& tv = variant(v);
-  if (tile_m) *tile_m = tv.tile_m();
+  if (tile_m) *tile_m = tv.step_m();
   if (tile_p) *tile_p = tv.tile_p();
   if (sched) *sched = tv.sched;
   return CPRUNE_OK;

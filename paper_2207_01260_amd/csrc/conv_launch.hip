@@ -406,13 +406,6 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
     const RowsArgs p = rows_tiles(d, tv, lay);
     const long waves = (long)p.strips * p.tiles_m;
     if (d.dtype == CPRUNE_F32 && split_packed_bytes(d.c_out, lay.cp_in, 9, d.dtype, true) >= ((size_t)1 << 31)) return false;
-    // fp32 on wide maps: where strips of 8 rows are 1.5 to 2 wavefronts per SIMD the layer takes the time of two, and 16 filters fewer
-    // change it by as little as 3 %, less than the step of 16 filters that these variants are pruned by is meant to show.  The
-    // split kernel steps by a tenth there (128 filters on 128 channels at 56x56, batch 8: 46 us, 112: 44, 96: 37; this kernel 39, 37-38, 37).
-    if (d.dtype == CPRUNE_F32 && d.w > 16) {
-      const long tall = (long)d.n * p.tiles_x * ((d.h + 7) / 8) * p.tiles_m;
-      if (tall > 1536 && tall < 2048) return false;
-    }
     if (tv.ks > 1 && (tv.ks > (lay.cp_in + 31) / 32 || waves * tv.ks > 8192)) return false;
     // multiply-high divisions of the tile decode: exact while groups x divisor < 2^32
     const long groups = (long)((p.strips + tv.wn - 1) / tv.wn) * p.tiles_m;

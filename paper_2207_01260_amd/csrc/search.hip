@@ -50,7 +50,7 @@ extern "C" int cprune_variant_filter_splits(int v, int c_out, int64_t* main_loop
                                             int* unit_out) {
   if (v < 0 || v >= num_variants() || c_out < 1 || !main_loop || !epilogue || !unit_out) return CPRUNE_ERR_INVALID_ARG;
   const TileVariant& tv = variant(v);
-  const int tile_m = tv.tile_m();
+  const int tile_m = tv.step_m();
   const int unit = tv.blk32 ? 32 : 16;   // rows of the MFMA block the variant is built on
   const int64_t tiles = (c_out + tile_m - 1) / tile_m;
   const int64_t blocks = std::min<int64_t>(tile_m / unit, (c_out + unit - 1) / unit);

@@ -49,6 +49,52 @@ def test_smaller_batches_choose_their_own_tiles(orc, dtype, tune):
     handle.close()
 
 
+def _rows_layer(full):
+    """One 3x3 layer of 32 channels (a single chunk of the row-strip kernel, whose variants then all add in one order) on 56x56."""
+    gen = torch.Generator().manual_seed(5)
+    net = synth.NetSpec("rows_at_batch", 32, 56, 56)
+    net.add(synth.Layer("conv", -1, 32, 128, k=3, stride=1, pad=1, act=synth.ACT_RELU, name="c"))
+    layers = [{"w": (torch.randn(128, 32, 3, 3, generator=gen) / 12.0).cuda(), "b": torch.zeros(128, device="cuda")}]
+    return net, layers, torch.randn(full, 32, 56, 56, generator=gen).cuda()
+
+
+def test_row_strips_at_every_smaller_batch():
+    """A handle whose layer runs the fp32 row-strip kernel at its full batch has no other packed copy: every smaller batch runs
+    that kernel too, which shows in the bits (the general kernel's fp32 instruction gives others)."""
+    net, layers, x = _rows_layer(12)
+    B.cprune_clear_tile_cache()
+    handle = pipeline.build_net(net, layers, 12, B.F32, tune=False)
+    rows = [v for v in range(B.cprune_num_tile_variants()) if B.cprune_tile_variant_name(v, True, B.F32) == "conv_split_rows_kernel<8, 1>"]
+    handle.set_layer_variant(0, 0)
+    general = handle.forward(x).clone()
+    done = 0
+    for v in rows:
+        try:
+            handle.set_layer_variant(0, v)
+        except B.CPruneError as e:
+            assert e.status == B.ERR_UNSUPPORTED
+            continue
+        want = handle.forward(x).clone()
+        assert not torch.equal(want, general)
+        for n in range(1, 13):
+            assert torch.equal(handle.forward(x[:n].contiguous()), want[:n]), n
+        done += 1
+    assert done == 1
+    handle.close()
+    # at any batch as the full one
+    for full in (7, 8, 9):
+        handle = pipeline.build_net(net, layers, full, B.F32, tune=False)
+        ok = 0
+        for v in rows:
+            try:
+                handle.set_layer_variant(0, v)
+                ok += 1
+            except B.CPruneError as e:
+                assert e.status == B.ERR_UNSUPPORTED
+        handle.close()
+        assert ok == 1, full
+
+
 def test_one_image_does_not_run_the_tiles_of_many():
     """One 224x224 image through a timed handle for 32 (365 us on the full batch's tiles, 212 on its own) against an untimed
     handle for one (198 us)."""
