@@ -71,9 +71,11 @@ static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay, double 
 // Whether an untimed layer takes the row-strip kernel where it runs (3x3 layers of a handle).  16-bit data: always (on 72 random
 // layers 2.35 times as fast as the general kernel, at least 1.15 times).  fp32, against the split kernel: from 0.2 GFLOP up on maps one
 // strip wide and 0.3 on wider ones whose strips are well filled (56 of 4 x 16 columns, not 32 of 3 x 16); there 1.3 times as
-// fast on average, 0.94 times at worst, and below those lines 0.7-1.2 times.
-static bool rows_pay(const cprune_conv_desc& d) {
-  if (d.dtype != CPRUNE_F32) return true;
+// fast on average, 0.94 times at worst, and below those lines 0.7-1.2 times.  A layer without the split kernel's copy (a smaller batch in a
+// handle whose full batch runs row strips) has the general kernel's fp32 instruction in its place, and always takes them:
+// ResNet-18 built for 32, 2 and 1 images 213 -> 198 and 269 -> 190 us, VGG-16 built for 64, 8 images 173 -> 141.
+static bool rows_pay(const cprune_conv_desc& d, const ConvLayout& lay) {
+  if (d.dtype != CPRUNE_F32 || !lay.w_split) return true;
   const double flops = 18.0 * d.n * d.h * d.w * (double)d.c_out * d.c_in;
   if (d.w <= 16) return flops >= 2e8;
   return flops >= 3e8 && d.w >= 0.85 * 16 * ((d.w - 16 + 13) / 14 + 1);
@@ -83,7 +85,7 @@ static bool rows_pay(const cprune_conv_desc& d) {
 // whole or cut into equal runs, and, for windows of more than one tap, the split kernel's variants where it pays.
 int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay, size_t ws_limit) {
   double best = -1.0;
-  const int rows = rows_pay(d) ? best_rows_variant(d, lay, &best) : -1;
+  const int rows = rows_pay(d, lay) ? best_rows_variant(d, lay, &best) : -1;
   if (rows >= 0) return rows;
   best = -1.0;
   int best_v = d.kh * d.kw > 1 && split_pays(d, lay, 6e8) ? best_split_variant(d, lay, &best) : -1;

@@ -81,6 +81,12 @@ def test_row_strips_at_every_smaller_batch():
         done += 1
     assert done == 1
     handle.close()
+    # likewise where the full batch's choice was not timed, down to sizes where the split kernel would be the choice if it were there
+    handle = pipeline.build_net(net, layers, 12, B.F32, tune=False)
+    assert "conv_split_rows" in B.cprune_tile_variant_name(handle.layer_variant(0), True, B.F32)
+    for n in range(1, 13):
+        assert torch.equal(handle.forward(x[:n].contiguous()), want[:n]), n
+    handle.close()
     # at any batch as the full one
     for full in (7, 8, 9):
         handle = pipeline.build_net(net, layers, full, B.F32, tune=False)
