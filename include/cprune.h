@@ -201,7 +201,7 @@ typedef struct {
  * weights below 2^-133, all denormal, count as zero in larger sums).  It runs through
  * cprune_conv2d_bn_relu, where each call packs the weights into the caller's scratch, in fp32 and 16-bit
  * data, and in fp32 handles, which keep packed copies for the layers that run it.  The fp32 row-strip
- * kernel multiplies in the same way, with a packed copy of its own.
+ * kernel multiplies in the same way, within the same limits, with a packed copy of its own.
  * sched -2: likewise channels-last only, for layers whose reduction is one contiguous run
  * per pixel (1x1 stride 1, fully connected): 16 filters x tile_p pixels per work-group, the
  * wavefronts of the group splitting the reduction; chosen when pixels are few.

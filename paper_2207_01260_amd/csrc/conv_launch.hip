@@ -405,7 +405,10 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
     if (lay.cp_out & 3) return false;      // four filters per store: not a dense map of logits
     const RowsArgs p = rows_tiles(d, tv, lay);
     const long waves = (long)p.strips * p.tiles_m;
-    if (d.dtype == CPRUNE_F32 && split_packed_bytes(d.c_out, lay.cp_in, 9, d.dtype, true) >= ((size_t)1 << 31)) return false;
+    if (d.dtype == CPRUNE_F32) {
+      if ((long)d.c_in * 9 < kSplitMinTerms) return false;      // as the split kernel
+      if (split_packed_bytes(d.c_out, lay.cp_in, 9, d.dtype, true) >= ((size_t)1 << 31)) return false;
+    }
     if (tv.ks > 1 && (tv.ks > (lay.cp_in + 31) / 32 || waves * tv.ks > 8192)) return false;
     // multiply-high divisions of the tile decode: exact while groups x divisor < 2^32
     const long groups = (long)((p.strips + tv.wn - 1) / tv.wn) * p.tiles_m;

@@ -185,3 +185,41 @@ def test_a_dense_map_of_logits_is_written_filter_by_filter(orc, c_out, dtype):
         assert nmax(got[:batch * c_out].reshape(ref.shape), ref) < (1e-5 if dtype == B.F32 else 2e-2), v
     assert bool(taken) == (c_out % 4 == 0), taken
     handle.close()
+
+
+@pytest.mark.parametrize("c_in,runs", [(1, False), (2, True)])
+def test_split_rows_need_as_many_terms_as_the_split_kernel(c_in, runs):
+    """Three parts are for fp32 sums of at least 16 terms: nine (one channel that is left) stay with the fp32 instruction, timed or
+    not, and sums of 18 are as exact in parts (2-norm error against 64 bits at most 1.1 times the instruction's, or half a unit)."""
+    gen = torch.Generator().manual_seed(c_in)
+    net = synth.NetSpec(f"rows_terms_{c_in}", 16, 56, 56)
+    a = net.add(synth.Layer("conv", -1, 16, c_in, k=1, act=synth.ACT_NONE, name="a"))
+    b = net.add(synth.Layer("conv", a, c_in, 128, k=3, stride=1, pad=1, act=synth.ACT_NONE, name="b"))
+    wa, wb = torch.randn(c_in, 16, 1, 1, generator=gen), torch.randn(128, c_in, 3, 3, generator=gen)
+    layers = [{"w": wa.cuda(), "b": torch.zeros(c_in).cuda()}, {"w": wb.cuda(), "b": torch.zeros(128).cuda()}]
+    x = torch.randn(48, 16, 56, 56, generator=gen).cuda()
+    B.cprune_clear_tile_cache()
+    for tune in (False, True):
+        handle = pipeline.build_net(net, layers, 48, B.F32, tune=tune)
+        if not runs:
+            assert "rows_kernel" not in B.cprune_tile_variant_name(handle.layer_variant(b), True, B.F32)
+        if not tune:
+            handle.set_layer_variant(b, 0)
+            base = handle.forward(x).double().cpu()
+            mid = handle.activation(a, 48, (c_in, 56, 56))
+            ref = torch.nn.functional.conv2d(mid.double().cpu(), wb.double(), None, 1, 1)
+            e_base = float((base - ref).norm() / ref.norm())
+            took = 0
+            for v in range(B.cprune_num_tile_variants()):
+                if "conv_split_rows" not in B.cprune_tile_variant_name(v, True, B.F32):
+                    continue
+                try:
+                    handle.set_layer_variant(b, v)
+                except B.CPruneError as e:
+                    assert e.status == B.ERR_UNSUPPORTED
+                    continue
+                e = float((handle.forward(x).double().cpu() - ref).norm() / ref.norm())
+                assert e <= max(1.1 * e_base, 2.0 ** -24), (v, e, e_base)
+                took += 1
+            assert bool(took) == runs
+        handle.close()
