@@ -407,8 +407,8 @@ struct NetLayer {
   int stem_reader = -1;       // first layer that may run inside the 3x3 conv stem_reader's kernel
   void* w_stem = nullptr;     // weights packed for the first-layer kernel
   void* w_rows = nullptr;     // layer the reduction-split kernel can run: weights once more, in its operand order
-  void* w_wave = nullptr;     // 3x3 / stride 1 / pad 1 layer on a small map: weights once more, packed for the
-                              // independent-wavefront kernel
+  void* w_wave = nullptr;     // 3x3 / stride 1 / pad 1 layer: weights once more, packed for the independent-wavefront kernel
+                              // (small maps) and, in 16-bit data, the row-strip kernel
   void* w_split = nullptr;    // fp32 dense layer: weights once more, cut and packed for the split kernel
   void* w_rows3 = nullptr;    // fp32 3x3 / stride 1 / pad 1 layer: likewise, for the row-strip kernel
   bool stem = false;          // nchw_in layer that runs the first-layer kernel (whole reduction in LDS)
@@ -481,37 +481,47 @@ static ConvLayout layer_layout(const NetLayer& L) {
   return lay;
 }
 
-// fp32 dense layers can have copies of their weights cut and packed for the split and the row-strip kernel; each is 1.5 times the
-// weights or more and made only for a layer that runs that kernel (while variants are timed, for every layer that could).
-static ConvLayout layout_if_split(const cprune_net& net, const NetLayer& L) {
-  ConvLayout lay = layer_layout(L);
-  if (net.dtype == CPRUNE_F32 && !L.nchw_in) lay.w_split = lay.w_rows3 = L.w;     // (only whether they are set matters to a choice)
-  return lay;
+// 3x3 / stride 1 / pad 1 on a map of its own: what the independent-wavefront and the row-strip kernels run.
+static bool strips_layer(const cprune_net& net, const NetLayer& L) {
+  return L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1 && L.d.k == 3 && L.d.stride == 1 && L.d.pad == 1 && !L.map2x2 && !L.nchw_in &&
+         wave_packed_bytes(L.d.c_out, L.cp_in, net.dtype) < ((size_t)1 << 31);      // 31-bit offsets in the kernels
 }
 
-static int packed_copy(cprune_net* net, NetLayer& L, bool rows, hipStream_t s) {
-  void*& slot = rows ? L.w_rows3 : L.w_split;
-  if (slot || net->dtype != CPRUNE_F32) return CPRUNE_OK;
-  const cprune_conv_desc d = layer_conv_desc(*net, L, net->max_batch);
-  const int cp = layer_layout(L).cp_in, taps = d.kh * d.kw;
-  void* copy = nullptr;
-  CPRUNE_HIP_TRY(hipMalloc(&copy, split_packed_bytes(d.c_out, cp, taps, net->dtype, rows)));
-  net->allocs.push_back(copy);
-  slot = copy;
-  return launch_pack_split(L.w, d.c_out, cp, taps, 1, net->dtype, copy, s, rows);
+// ... on a map that the independent-wavefront kernel takes: it keeps the copy that kernel reads
+static bool wave_layer(const cprune_net& net, const NetLayer& L) {
+  return strips_layer(net, L) && L.h_in >= 3 && L.w_in >= 3 && L.h_in <= 32 && L.w_in <= 32;
+}
+
+// The other copies of a dense layer's weights are made only for a layer that runs the kernel that reads them (while variants are
+// timed, for every layer that could): fp32, cut and packed for the split and the row-strip kernel, each 1.5 times the weights or
+// more; 16-bit data, the row-strip kernel's copy on maps that are not the independent-wavefront kernel's, as large as the weights.
+static ConvLayout layout_if_packed(const cprune_net& net, const NetLayer& L) {
+  ConvLayout lay = layer_layout(L);      // (only whether the copies are set matters to a choice)
+  if (net.dtype == CPRUNE_F32 && !L.nchw_in) lay.w_split = lay.w_rows3 = L.w;
+  if (net.dtype != CPRUNE_F32 && !lay.w_wave && strips_layer(net, L)) lay.w_wave = L.w;
+  return lay;
 }
 
 // the copy variant v reads, if it reads one
 static int pack_for(cprune_net* net, NetLayer& L, int v, hipStream_t s) {
-  if (variant(v).split) return packed_copy(net, L, false, s);
-  if (variant(v).rows) return packed_copy(net, L, true, s);
-  return CPRUNE_OK;
+  const bool f32 = net->dtype == CPRUNE_F32, rows = variant(v).rows;
+  if (!rows && !(f32 && variant(v).split)) return CPRUNE_OK;
+  void*& slot = !rows ? L.w_split : f32 ? L.w_rows3 : L.w_wave;
+  if (slot) return CPRUNE_OK;
+  const cprune_conv_desc d = layer_conv_desc(*net, L, net->max_batch);
+  const int cp = layer_layout(L).cp_in, taps = d.kh * d.kw;
+  void* copy = nullptr;
+  CPRUNE_HIP_TRY(hipMalloc(&copy, f32 ? split_packed_bytes(d.c_out, cp, taps, net->dtype, rows) : wave_packed_bytes(d.c_out, cp, net->dtype)));
+  net->allocs.push_back(copy);
+  slot = copy;
+  return f32 ? launch_pack_split(L.w, d.c_out, cp, taps, 1, net->dtype, copy, s, rows) : launch_repack_wave(L.w, d.c_out, cp, net->dtype, copy, s);
 }
 
 // gives back what variant v (-1: none) does not read (nothing that reads it is in flight)
 static void drop_copies(cprune_net* net, NetLayer& L, int v) {
-  for (void** slot : {&L.w_split, &L.w_rows3}) {
+  for (void** slot : {&L.w_split, &L.w_rows3, &L.w_wave}) {
     if (!*slot || (v >= 0 && (slot == &L.w_split ? variant(v).split : variant(v).rows))) continue;
+    if (slot == &L.w_wave && wave_layer(*net, L)) continue;
     net->allocs.erase(std::find(net->allocs.begin(), net->allocs.end(), *slot));
     hipFree(*slot);
     *slot = nullptr;
@@ -1008,16 +1018,12 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
       if (e != hipSuccess) { set_last_hip_error(e); rc = CPRUNE_ERR_DEVICE; }
     }
   }
-  // 3x3 layers (fp32: on small maps): a second copy of the weights in the operand order of the kernels made for them
+  // 3x3 layers on small maps: a second copy of the weights in the operand order of the kernels made for them
   for (int i = 0; i < n_layers && rc == CPRUNE_OK; ++i) {
     NetLayer& L = net->layers[i];
-    const cprune_layer_desc& d = L.d;
-    if (!(d.kind == CPRUNE_LAYER_CONV && d.groups == 1 && d.k == 3 && d.stride == 1 && d.pad == 1)) continue;
-    if (L.map2x2 || L.nchw_in) continue;
-    if (dtype == CPRUNE_F32 && (L.h_in < 3 || L.w_in < 3 || L.h_in > 32 || L.w_in > 32)) continue;
-    if (wave_packed_bytes(d.c_out, L.cp_in, dtype) >= ((size_t)1 << 31)) continue;   // 31-bit offsets in the kernel
-    rc = dev_alloc(wave_packed_bytes(d.c_out, L.cp_in, dtype), &L.w_wave);
-    if (rc == CPRUNE_OK) rc = launch_repack_wave(L.w, d.c_out, L.cp_in, dtype, L.w_wave, s);
+    if (!wave_layer(*net, L)) continue;
+    rc = dev_alloc(wave_packed_bytes(L.d.c_out, L.cp_in, dtype), &L.w_wave);
+    if (rc == CPRUNE_OK) rc = launch_repack_wave(L.w, L.d.c_out, L.cp_in, dtype, L.w_wave, s);
   }
   // layers the reduction-split kernel can run (1x1 / stride 1, fully connected, 2x2 maps as one matrix; few
   // pixels): likewise a copy in its operand order
@@ -1039,7 +1045,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     NetLayer& L = net->layers[i];
     if (!(L.d.kind == CPRUNE_LAYER_FC || (L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1))) continue;
     cprune_conv_desc cd = layer_conv_desc(*net, L, max_batch);
-    ConvLayout lay = layout_if_split(*net, L);
+    ConvLayout lay = layout_if_packed(*net, L);
     bool timed = false;
     int v = cached_or_heuristic_variant(cd, &timed, lay);
     for (int k = 0; k < num_variants() && rc == CPRUNE_OK; ++k)
@@ -1381,7 +1387,7 @@ extern "C" int cprune_net_task_key(const cprune_net* net, int layer, int32_t* ke
 
 static int restore_variant(cprune_net* net, NetLayer& L) {
   if (L.variant >= 0 || L.stem || L.stem7) return CPRUNE_OK;
-  const int v = cached_or_heuristic_variant(layer_conv_desc(*net, L, net->max_batch), &L.timed, layout_if_split(*net, L));
+  const int v = cached_or_heuristic_variant(layer_conv_desc(*net, L, net->max_batch), &L.timed, layout_if_packed(*net, L));
   const int rc = pack_for(net, L, v, nullptr);
   if (rc != CPRUNE_OK) return rc;
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
@@ -1484,7 +1490,7 @@ extern "C" int cprune_net_set_layer_variant(cprune_net* net, int layer, int vari
     L.stem7 = 0;
   }
   const cprune_conv_desc cd = layer_conv_desc(*net, L, net->max_batch);
-  const ConvLayout lay = layout_if_split(*net, L);
+  const ConvLayout lay = layout_if_packed(*net, L);
   if (!variant_supports(cd, variant, lay)) return CPRUNE_ERR_UNSUPPORTED;
   if (conv_ws_bytes(cd, variant, lay) > net->ws_bytes) return CPRUNE_ERR_WORKSPACE;
   CPRUNE_HIP_TRY(hipDeviceSynchronize());

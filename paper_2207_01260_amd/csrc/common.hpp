@@ -76,7 +76,8 @@ struct ConvLayout {
   int nhwc_out = 0;  // with nhwc = 0: NCHW input and OIHW weights (the boundary's layout) but a channels-last
                      // output of channel stride cp_out: the first layer of a network handle
   const void* w_wave = nullptr;  // the weights once more, in the order of the independent-wavefront 3x3
-                                 // kernel (launch_repack_wave); that kernel runs only where this is set
+                                 // kernel (launch_repack_wave); that kernel, and the row-strip kernel in 16-bit
+                                 // data, run only where this is set
   const void* w_rows = nullptr;  // the weights once more as [16-row tile][64-byte round of the reduction][lane][16
                                  // bytes] (launch_repack_rows): the reduction-split kernel reads these when set
   const void* w_split = nullptr; // channels-last fp32: the weights cut and packed for the split kernel

@@ -101,3 +101,33 @@ def test_leaving_a_fused_form_brings_the_copy_back():
     assert torch.equal(apart, again)
     assert float((fused - apart).norm() / apart.norm()) < 1e-5
     handle.close()
+
+
+def test_a_16_bit_layer_gives_the_row_strips_copy_back():
+    """On maps over 32 the row-strip kernel's copy is made for the layers that run it: pinned to another variant they give it back,
+    pinned to that kernel again they answer as before."""
+    c, n_layers = 1536, 3
+    net, layers = _net(c, 34, n_layers, k=3)
+    for q in layers:
+        q["w"] = q["w"].to(torch.bfloat16)
+    x = torch.randn(1, c, 34, 34).cuda().to(torch.bfloat16)
+    B.cprune_clear_tile_cache()
+    handle = pipeline.build_net(net, layers, 1, B.BF16, tune=False)
+    rows = handle.layer_variant(0)
+    assert "conv_rows" in B.cprune_tile_variant_name(rows, True, B.BF16)
+    want = handle.forward(x).clone()
+    torch.cuda.synchronize()
+    with_copies = torch.cuda.mem_get_info()[0]
+    for i in range(n_layers):
+        handle.set_layer_variant(i, 0)
+    general = handle.forward(x).clone()
+    torch.cuda.synchronize()
+    weights = c * c * 9 * 2
+    assert torch.cuda.mem_get_info()[0] - with_copies > 0.9 * n_layers * weights
+    for i in range(n_layers):
+        handle.set_layer_variant(i, rows)
+    again = handle.forward(x)
+    torch.cuda.synchronize()
+    assert torch.equal(again, want)
+    assert float((general.float() - want.float()).norm() / want.float().norm()) < 2e-2
+    handle.close()
