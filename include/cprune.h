@@ -326,7 +326,7 @@ int cprune_net_layer_times(cprune_net* net, const void* x, int n, int iters, flo
  * epilogue has no activation of its own: CPRUNE_ERR_UNSUPPORTED (ask for the pool layer); neither
  * has a layer that runs inside the kernel of a later one (cprune_net_layer_fused): a depthwise layer inside the 1x1
  * conv that reads it, the expansion in front of it, and, in handles created with tune != 0, a 3x3 / stride 2 first layer
- * in front of it. */
+ * in front of it (cprune_net_block_form with form 1 or 0 brings its activation back). */
 int cprune_net_copy_activation(cprune_net* net, int layer, int n, void* dst, size_t dst_bytes,
                                void* stream);
 /* Shape of one image's output (the last layer's c_out, h_out, w_out); host outs. */
@@ -369,10 +369,20 @@ int cprune_net_layer_fused(const cprune_net* net, int layer, int* fused_out);
  * cprune_net_fuse_depthwise on the same layer also leaves the one-kernel form.
  * CPRUNE_ERR_UNSUPPORTED when the layer heads no such block or the block's weights and input patch do not
  * fit the local memory of a compute unit (such a block runs as one kernel only where cprune_net_create timed it as
- * the fastest form; enable = 0 is accepted there).  Recorded graphs are dropped.  Not to be called while
+ * the fastest form or cprune_net_block_form asked for it; enable = 0 is accepted there).  Recorded graphs are dropped.  Not to be called while
  * a forward is in flight.  cprune_net_layer_fused reports 1 for the expansion and the
  * depthwise layer of a block that runs as one kernel. */
 int cprune_net_fuse_block(cprune_net* net, int layer, int enable);
+/* The same decision in full, as cprune_net_create(tune = 1) takes it by timing, for the block whose depthwise layer is
+ * `layer` (what a stored tuning result is applied with).  form 0: the layers apart; 1: the depthwise layer
+ * inside its reader's kernel; 2: the whole block as one kernel, where the layer in front is a 1x1 expansion that nobody
+ * else reads or, with a 3x3 / stride 1 depthwise layer on a map wider than 8 and at most 32 filters behind it, the
+ * network's first layer (3x3 / stride 2 / pad 1 on an image of at most 3 channels).  low 0 / 1: strips as tall as the
+ * kernel has them, or about half as tall; wavefronts 1, 2, 4 or 8: how many share a strip at the full batch (smaller
+ * batches double it while units idle).  Both are ignored for form 0.  CPRUNE_ERR_INVALID_ARG for other values;
+ * CPRUNE_ERR_UNSUPPORTED when the layer heads no such block, the kernel is not built for its widths, or a layer of it runs
+ * inside another block's kernel.  Recorded graphs are dropped.  Not to be called while a forward is in flight. */
+int cprune_net_block_form(cprune_net* net, int layer, int form, int low, int wavefronts);
 /* Pins the tile variant of a dense conv / fully connected layer (what a stored tuning result
  * is applied with) at the handle's full batch; a smaller batch may run another tile of the same
  * kernel.  A split variant's packed weights are made here.  CPRUNE_ERR_INVALID_ARG for a layer without variants,

@@ -60,6 +60,7 @@ EXPORTS = [
     "cprune_net_create", "cprune_net_forward", "cprune_net_layer_times",
     "cprune_net_copy_activation", "cprune_net_output_shape", "cprune_net_layer_variant",
     "cprune_net_set_layer_variant", "cprune_net_fuse_depthwise", "cprune_net_fuse_block",
+    "cprune_net_block_form",
     "cprune_net_fuse_first_layers", "cprune_net_first_layer_form", "cprune_net_layer_fused",
     "cprune_net_destroy",
     "cprune_probe_scratch_bytes", "cprune_probe_mfma", "cprune_probe_copy", "cprune_probe_read",
@@ -645,6 +646,12 @@ class Net:
     def fuse_block(self, layer: int, enable: bool):
         _check(lib().cprune_net_fuse_block(self._h, C.c_int(layer), C.c_int(1 if enable else 0)),
                "cprune_net_fuse_block")
+
+    def block_form(self, layer: int, form: int, low: int = 1, wavefronts: int = 1):
+        """How the block of depthwise layer `layer` runs: 0 apart, 1 with its 1x1 reader, 2 with the layer in front as well; tall
+        (0) or low (1) strips, 1 / 2 / 4 / 8 wavefronts each."""
+        _check(lib().cprune_net_block_form(self._h, C.c_int(layer), C.c_int(form), C.c_int(low), C.c_int(wavefronts)),
+               "cprune_net_block_form")
 
     def first_layer_form(self, form: int):
         """How a 16-bit 7x7 / stride 2 first layer runs: 0 general kernels, 1 its own kernel, 2 with the max-pool."""

@@ -700,6 +700,42 @@ static bool block_on_request(const cprune_net& net, const NetLayer& E, const Net
   return lds <= 160 * 1024;
 }
 
+// The one layer that reads `layer`, as its input; -1: none or several.
+static int only_reader(const cprune_net& net, int layer) {
+  int reader = -1, readers = 0;
+  for (int j = 0; j < (int)net.layers.size(); ++j) {
+    if (net.layers[j].d.input == layer) { reader = j; ++readers; }
+    if (net.layers[j].d.residual == layer) readers += 2;
+  }
+  return readers == 1 ? reader : -1;
+}
+
+// Whether the layer that depthwise layer i reads can join it and its 1x1 reader in one kernel: a 1x1 expansion, or the network's
+// first layer (3x3 / stride 2 on the image), that nobody else reads; and the kernel's form for it.
+static bool block_joins(const cprune_net& net, int i, int* mb, int* xh) {
+  const NetLayer& D = net.layers[i];
+  const NetLayer& E = net.layers[D.d.input];
+  const NetLayer& P = net.layers[D.dw_reader];
+  const cprune_layer_desc& ed = E.d;
+  if (ed.kind != CPRUNE_LAYER_CONV || ed.groups != 1 || ed.residual >= 0 || E.fused_pool || E.cp_out != D.cp_in ||
+      only_reader(net, D.d.input) != i)
+    return false;
+  if (E.nchw_in)
+    return ed.c_in <= 3 && ed.k == 3 && ed.stride == 2 && ed.pad == 1 && !E.fused_away && E.stem_reader < 0 && D.d.k == 3 &&
+           D.d.stride == 1 && D.w_in > 8 && mbrow_image_form(net.dtype, P.d.c_out, mb, xh);
+  return ed.k == 1 && ed.stride == 1 && ed.pad == 0 && ed.input >= 0 && !E.map2x2 && E.fuse_dw < 0 &&
+         E.cp_out == round_up_vec(ed.c_out, net.dtype) && mbrow_form(net.dtype, P.d.c_out, E.cp_in, mb, xh);
+}
+
+static int pack_expansion(cprune_net* net, NetLayer& E, int xh, hipStream_t s) {
+  if (E.w_expand) return CPRUNE_OK;
+  void* copy = nullptr;
+  CPRUNE_HIP_TRY(hipMalloc(&copy, expand_packed_bytes(E.d.c_out, xh, net->dtype)));
+  net->allocs.push_back(copy);
+  E.w_expand = copy;
+  return launch_pack_expand(E.w, E.d.c_out, E.nchw_in ? E.d.c_in * 9 : E.cp_in, xh, net->dtype, copy, s);
+}
+
 // The variant a layer of a handle for larger batches runs at n images, where none was timed for that shape.  Without a timed
 // (or pinned) choice for the full batch: the estimate for n.  Otherwise the full batch's choice, which the timing of all
 // kernels stands behind, unless n is at most 7/8 of the full batch, the choice has an estimate and another tile of the same
@@ -1178,15 +1214,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     const cprune_layer_desc& dd = D.d;
     if (!(dd.kind == CPRUNE_LAYER_CONV && dd.groups != 1 && dd.input >= 0 && dd.residual < 0)) continue;
     if (!((dd.k == 3 || dd.k == 5) && (dd.stride == 1 || dd.stride == 2) && dd.pad == dd.k / 2)) continue;
-    auto only_reader = [&](int layer) -> int {      // the one layer that reads it, as its input; -1: none or several
-      int reader = -1, readers = 0;
-      for (int j = 0; j < n_layers; ++j) {
-        if (net->layers[j].d.input == layer) { reader = j; ++readers; }
-        if (net->layers[j].d.residual == layer) readers += 2;
-      }
-      return readers == 1 ? reader : -1;
-    };
-    const int reader = only_reader(i);
+    const int reader = only_reader(*net, i);
     if (reader < 0 || i == n_layers - 1) continue;
     NetLayer& P = net->layers[reader];
     const cprune_layer_desc& pd = P.d;
@@ -1201,22 +1229,12 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     }
 
     NetLayer& E = net->layers[dd.input];
-    const cprune_layer_desc& ed = E.d;
     int mb = 0, xh = 0;
-    bool block = ed.kind == CPRUNE_LAYER_CONV && ed.groups == 1 && ed.k == 1 && ed.stride == 1 && ed.pad == 0 && ed.input >= 0 &&
-                 ed.residual < 0 && !E.nchw_in && !E.map2x2 && !E.fused_pool && E.fuse_dw < 0 &&
-                 E.cp_out == round_up_vec(ed.c_out, dtype) && E.cp_out == D.cp_in && only_reader(dd.input) == i &&
-                 mbrow_form(dtype, pd.c_out, E.cp_in, &mb, &xh);
-    const bool on_request = block && block_on_request(*net, E, D, P);
-    // the network's first layer in the place of the expansion (3x3 / stride 2 on the image): only where timed as faster
-    if (!block && tune && E.nchw_in && ed.c_in <= 3 && ed.k == 3 && ed.stride == 2 && ed.pad == 1 && ed.groups == 1 && ed.residual < 0 &&
-        !E.fused_pool && !E.fused_away && E.stem_reader < 0 && E.cp_out == D.cp_in && dd.k == 3 && dd.stride == 1 &&
-        only_reader(dd.input) == i && D.w_in > 8)
-      block = mbrow_image_form(dtype, pd.c_out, &mb, &xh);
-    block = block && (on_request || tune);
+    bool block = block_joins(*net, i, &mb, &xh);
+    const bool on_request = block && !E.nchw_in && block_on_request(*net, E, D, P);
+    block = block && (on_request || tune);       // (the first layer in the expansion's place: only where timed as faster)
     if (block) {
-      rc = dev_alloc(expand_packed_bytes(ed.c_out, xh, dtype), &E.w_expand);
-      if (rc == CPRUNE_OK) rc = launch_pack_expand(E.w, ed.c_out, E.nchw_in ? ed.c_in * 9 : E.cp_in, xh, dtype, E.w_expand, s);
+      rc = pack_expansion(net, E, xh, s);
       if (rc != CPRUNE_OK) break;
       if (on_request) D.block_expand = dd.input;
     }
@@ -1470,6 +1488,40 @@ extern "C" int cprune_net_fuse_block(cprune_net* net, int layer, int enable) {
     const int rc = restore_variant(net, E);
     if (rc != CPRUNE_OK) return rc;
   }
+  return CPRUNE_OK;
+}
+
+extern "C" int cprune_net_block_form(cprune_net* net, int layer, int form, int low, int wavefronts) {
+  if (!net || layer < 0 || layer >= (int)net->layers.size() || form < 0 || form > 2 || low < 0 || low > 1) return CPRUNE_ERR_INVALID_ARG;
+  if (wavefronts != 1 && wavefronts != 2 && wavefronts != 4 && wavefronts != 8) return CPRUNE_ERR_INVALID_ARG;
+  NetLayer& D = net->layers[layer];
+  if (D.dw_reader < 0) return CPRUNE_ERR_UNSUPPORTED;
+  NetLayer& P = net->layers[D.dw_reader];
+  NetLayer& E = net->layers[D.d.input];
+  int mb = 0, xh = 0;
+  if (P.fused_away) return CPRUNE_ERR_UNSUPPORTED;      // itself inside a later block's kernel
+  const bool joined = P.fuse_block >= 0;
+  if (form == 2 && !joined && !block_joins(*net, layer, &mb, &xh)) return CPRUNE_ERR_UNSUPPORTED;
+  CPRUNE_HIP_TRY(hipDeviceSynchronize());
+  drop_graphs(net);
+  if (form == 2 && !joined) {
+    const int rc = pack_expansion(net, E, xh, nullptr);
+    if (rc != CPRUNE_OK) return rc;
+    CPRUNE_HIP_TRY(hipDeviceSynchronize());
+  }
+  D.fused_away = form > 0;
+  P.fuse_dw = form > 0 ? layer : -1;
+  P.fuse_block = form == 2 ? D.d.input : -1;
+  if (form == 1) { P.dw_low = low; P.dw_ks = wavefronts; }
+  if (form == 2) { P.block_low = low; P.block_ks = wavefronts; }
+  if (form == 2 || joined) E.fused_away = form == 2;
+  if (form == 2) E.variant = -1;
+  else if (joined) {
+    const int rc = restore_variant(net, E);
+    if (rc != CPRUNE_OK) return rc;
+  }
+  if (form) P.variant = -1;
+  else return restore_variant(net, P);
   return CPRUNE_OK;
 }
 

@@ -161,5 +161,6 @@ def test_pool_fc_net_reject_bad_args():
     assert L.cprune_net_first_layer_form(None, C.c_int(1)) == B.ERR_INVALID_ARG
     assert L.cprune_net_fuse_depthwise(None, C.c_int(0), C.c_int(1)) == B.ERR_INVALID_ARG
     assert L.cprune_net_fuse_block(None, C.c_int(0), C.c_int(1)) == B.ERR_INVALID_ARG
+    assert L.cprune_net_block_form(None, C.c_int(0), C.c_int(2), C.c_int(1), C.c_int(1)) == B.ERR_INVALID_ARG
     dims = (C.c_int * 3)()
     assert L.cprune_net_output_shape(None, dims, dims, dims) == B.ERR_INVALID_ARG

@@ -104,7 +104,7 @@ def test_images_of_one_strip_do_not_meet(hw, k, stride, form):
 @pytest.mark.parametrize("cfg", [(3, 32, 16, 224, 4), (3, 27, 24, 150, 3), (1, 40, 32, 131, 2)])
 def test_first_layer_in_the_block(orc, cfg, dtype):
     """A 3x3 / stride 2 first layer, the depthwise layer and the projection behind it, as a tuned handle runs them (one kernel
-    where it times faster: there is no call that forces it): even and odd images, one channel, ragged filter counts."""
+    where it times faster; forced in test_pinned_image_form): even and odd images, one channel, ragged filter counts."""
     c, c_exp, c_out, hw, batch = cfg
     net = synth.NetSpec(f"first_{c}_{c_exp}_{c_out}_{hw}", c, hw, hw)
     e = net.add(synth.Layer("conv", -1, c, c_exp, k=3, stride=2, pad=1, act=synth.ACT_RELU6, bn=True, name="e"))
@@ -131,4 +131,134 @@ def test_first_layer_in_the_block(orc, cfg, dtype):
         out = handle.forward(xd)
         torch.cuda.synchronize()
         assert nmax(out.float().cpu().numpy(), ref) < TOL[dtype]
+    handle.close()
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.F16, B.BF16])
+@pytest.mark.parametrize("cfg", [
+    # c_in, c_exp, c_out, hw, k, stride, shortcut, batch: every height of strips (7 and 4 rows, 5 and 3, 3 and 2; stride 2: 4 and 2;
+    # 5x5: 4 and 2), maps a row more or less than whole strips, fewer chunks than wavefronts
+    (24, 50, 24, 15, 3, 1, True, 2),
+    (16, 70, 60, 28, 3, 1, False, 1),
+    (90, 70, 90, 16, 3, 1, True, 1),
+    (40, 140, 100, 7, 3, 1, False, 3),
+    (24, 40, 32, 33, 3, 2, False, 2),
+    (32, 90, 64, 14, 3, 2, False, 5),
+    (40, 60, 90, 18, 3, 2, False, 1),
+    (16, 40, 30, 9, 5, 1, False, 3),
+    (40, 70, 40, 29, 5, 1, True, 1),
+    (16, 48, 40, 27, 5, 2, False, 2),
+    (40, 70, 120, 13, 5, 2, False, 1),
+])
+def test_pinned_block_forms(orc, cfg, dtype):
+    """Tall and low strips with 1, 2, 4 and 8 wavefronts each, the whole block and its depthwise half, against the oracle.  The
+    forms round alike from step to step and differ in the order of the projection's sums only."""
+    c_in, c_exp, c_out, hw, k, stride, shortcut, batch = cfg
+    net, e, d = _block(c_in, c_exp, c_out, hw, k, stride, shortcut)
+    params = synth.layer_params(net, 74)
+    x = synth.net_input(net, 74, batch)
+    ref_layers, _ = orc.prune_net(net, params)
+    ref = orc.forward(net, ref_layers, x)
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(params), dtype)
+    handle = pipeline.build_net(net, layers, batch, dtype, tune=False)
+    xd = torch.from_numpy(x).cuda().to(B.TORCH_DTYPE[dtype])
+    for form in (2, 1):
+        for low in (0, 1):
+            for ks in (1, 2, 4, 8):
+                print(cfg, dtype, form, low, ks, flush=True)
+                handle.block_form(d, form, low, ks)
+                assert handle.layer_fused(e) == (form == 2) and handle.layer_fused(d)
+                out = handle.forward(xd)
+                torch.cuda.synchronize()
+                err = nmax(out.float().cpu().numpy(), ref)
+                assert err < TOL[dtype], (form, low, ks, err)
+    handle.block_form(d, 0)
+    assert not handle.layer_fused(e) and not handle.layer_fused(d)
+    out = handle.forward(xd)
+    torch.cuda.synchronize()
+    assert nmax(out.float().cpu().numpy(), ref) < TOL[dtype]
+    handle.close()
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.F16, B.BF16])
+@pytest.mark.parametrize("cfg", [
+    # channels, first layer, projection, image, batch: even and odd images, one and two channels, maps of one strip, one column more
+    # and a row more or less than whole strips, one and two filter blocks
+    (3, 32, 16, 224, 2), (3, 27, 24, 61, 3), (1, 40, 32, 33, 2), (2, 20, 9, 31, 1), (3, 70, 17, 19, 5), (3, 5, 32, 57, 1),
+])
+def test_pinned_image_form(orc, cfg, dtype):
+    """The network's first layer inside the first block's kernel, on request: tall and low strips, every number of wavefronts, a
+    smaller batch, a replayed graph, and back to the first layer on its own, whose activation can be read again."""
+    c, c_exp, c_out, hw, batch = cfg
+    net = synth.NetSpec(f"image_{c}_{c_exp}_{c_out}_{hw}", c, hw, hw)
+    e = net.add(synth.Layer("conv", -1, c, c_exp, k=3, stride=2, pad=1, act=synth.ACT_RELU6, bn=True, name="e"))
+    d = net.add(synth.Layer("conv", e, c_exp, c_exp, k=3, stride=1, pad=1, groups=c_exp, act=synth.ACT_RELU6, bn=True, name="d"))
+    net.add(synth.Layer("conv", d, c_exp, c_out, k=1, act=synth.ACT_NONE, bn=True, name="p"))
+    params = synth.layer_params(net, 75)
+    x = synth.net_input(net, 75, batch)
+    ref_layers, _ = orc.prune_net(net, params)
+    acts = orc.forward(net, ref_layers, x, return_all=True)
+    ref = acts[-1]
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(params), dtype)
+    handle = pipeline.build_net(net, layers, batch, dtype, tune=False)
+    xd = torch.from_numpy(x).cuda().to(B.TORCH_DTYPE[dtype])
+    for low in (0, 1):
+        for ks in (1, 2, 4, 8):
+            print(cfg, dtype, low, ks, flush=True)
+            handle.block_form(d, 2, low, ks)
+            assert handle.layer_fused(e) and handle.layer_fused(d)
+            for n in (batch, 1):
+                for graph in (False, True):
+                    out = handle.forward(xd[:n].contiguous(), use_graph=graph)
+                    torch.cuda.synchronize()
+                    assert nmax(out.float().cpu().numpy(), ref[:n]) < TOL[dtype], (low, ks, n, graph)
+    with pytest.raises(B.CPruneError):
+        handle.activation(e, batch, acts[e].shape[1:])
+    for form in (1, 0, 2, 0):
+        handle.block_form(d, form)
+        assert handle.layer_fused(e) == (form == 2) and handle.layer_fused(d) == (form > 0)
+        out = handle.forward(xd)
+        torch.cuda.synchronize()
+        assert nmax(out.float().cpu().numpy(), ref) < TOL[dtype]
+    assert nmax(handle.activation(e, batch, acts[e].shape[1:]).float().cpu().numpy(), acts[e]) < TOL[dtype]
+    handle.close()
+
+
+def test_block_form_refuses_what_it_cannot_run():
+    """A depthwise layer behind the image, a block wider than the kernel is built for, values out of range; and a layer that runs
+    inside another block's kernel."""
+    net = synth.NetSpec("forms", 8, 20, 20)
+    a = net.add(synth.Layer("conv", -1, 8, 16, k=1, act=synth.ACT_RELU, bn=True, name="a"))
+    d1 = net.add(synth.Layer("conv", a, 16, 16, k=3, stride=1, pad=1, groups=16, act=synth.ACT_RELU, bn=True, name="d1"))
+    b = net.add(synth.Layer("conv", d1, 16, 24, k=1, act=synth.ACT_RELU, bn=True, name="b"))
+    d2 = net.add(synth.Layer("conv", b, 24, 24, k=3, stride=1, pad=1, groups=24, act=synth.ACT_RELU, bn=True, name="d2"))
+    c = net.add(synth.Layer("conv", d2, 24, 100, k=1, act=synth.ACT_RELU, bn=True, name="c"))
+    d3 = net.add(synth.Layer("conv", c, 100, 100, k=3, stride=1, pad=1, groups=100, act=synth.ACT_RELU, bn=True, name="d3"))
+    net.add(synth.Layer("conv", d3, 100, 300, k=1, act=synth.ACT_NONE, bn=True, name="p"))
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(synth.layer_params(net, 76)), B.F32)
+    handle = pipeline.build_net(net, layers, 1, B.F32, tune=False)
+    x = torch.from_numpy(synth.net_input(net, 76, 1)).cuda()
+
+    def refused(status, *args):
+        with pytest.raises(B.CPruneError) as e:
+            handle.block_form(*args)
+        assert e.value.status == status, args
+
+    for layer in (d1, d2, d3):
+        handle.block_form(layer, 0)
+    want = handle.forward(x).clone()
+    for bad in ((d2, 3, 0, 1), (d2, -1, 0, 1), (d2, 2, 2, 1), (d2, 2, 0, 3), (d2, 2, 0, 16), (99, 1, 0, 1)):
+        refused(B.ERR_INVALID_ARG, *bad)
+    refused(B.ERR_UNSUPPORTED, a, 1, 1, 1)               # no depthwise layer
+    refused(B.ERR_UNSUPPORTED, d1, 2, 1, 1)              # reads a layer on the image
+    refused(B.ERR_UNSUPPORTED, d3, 2, 1, 1)              # 300 filters: the whole block is built for up to 128
+    handle.block_form(d1, 1)
+    refused(B.ERR_UNSUPPORTED, d2, 2, 1, 1)              # its expansion already runs the first depthwise layer
+    handle.block_form(d1, 0)
+    handle.block_form(d2, 2, 0, 2)
+    refused(B.ERR_UNSUPPORTED, d1, 1, 1, 1)              # and the other way round
+    handle.block_form(d3, 1, 0, 2)
+    got = handle.forward(x)
+    torch.cuda.synchronize()
+    assert float((got - want).norm() / want.norm()) < 1e-5
     handle.close()
