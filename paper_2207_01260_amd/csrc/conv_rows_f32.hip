@@ -3,6 +3,6 @@
 
 namespace cprune {
 
-int launch_conv_rows_f32(int id, dim3 grid, hipStream_t s, const RowsArgs& a) { return launch_rows3(id, grid, s, a); }
+int launch_conv_rows_f32(int id, dim3 grid, hipStream_t s, const RowsArgs& a) { return launch_rows3<float>(id, grid, s, a); }
 
 }  // namespace cprune

@@ -531,10 +531,12 @@ inline int launch_rows(int id, dim3 grid, hipStream_t s, const RowsArgs& a) {
   return CPRUNE_OK;
 }
 
+// (a template like the other: its kernels are compiled where it is called, not in every file that includes this one)
+template <typename T>
 inline int launch_rows3(int id, dim3 grid, hipStream_t s, const RowsArgs& a) {
 #define CPRUNE_ROWS_CASE(ID, MB_, R_, KS_)                                                                           \
   case ID:                                                                                                           \
-    if constexpr (MB_ == 1) {                                                                                        \
+    if constexpr (MB_ == 1 && std::is_same<T, float>::value) {                                                       \
       const dim3 block(KS_ == 8 ? 512 : 256);                                                                        \
       if (a.lane_shift < 4) hipLaunchKernelGGL((conv_split_rows_kernel<R_, KS_, true>), grid, block, 0, s, a);       \
       else hipLaunchKernelGGL((conv_split_rows_kernel<R_, KS_, false>), grid, block, 0, s, a);                       \
