@@ -223,3 +223,54 @@ def test_split_rows_need_as_many_terms_as_the_split_kernel(c_in, runs):
                 took += 1
             assert bool(took) == runs
         handle.close()
+
+
+@pytest.mark.parametrize("cfg", [
+    # batch, c_in, h, w, c_out: two images side by side, the last alone; four, two missing; three columns of four lanes; strips that
+    # overlap, ragged rows; one column into the second strip; several chunks for wavefronts that share a strip
+    (3, 20, 8, 8, 24), (6, 70, 4, 4, 40), (5, 130, 3, 3, 17), (1, 40, 31, 44, 20), (2, 33, 9, 17, 33), (2, 260, 7, 7, 48),
+])
+def test_split_rows_second_pass(cfg):
+    """What three parts do not hold is multiplied again on the fp32 instruction: numbers around 1e-30, as exact as that instruction
+    (its least exact variant and 10 %); one infinity, which reaches its 3x3 neighbours of the same image with the sign of the
+    weight and leaves everything else (of the same wavefront as well) as exact as before."""
+    n, c_in, h, w, c_out = cfg
+    gen = torch.Generator().manual_seed(c_in)
+    net = synth.NetSpec(f"second_{c_in}_{h}", c_in, h, w)
+    net.add(synth.Layer("conv", -1, c_in, c_out, k=3, stride=1, pad=1, act=synth.ACT_NONE, name="a"))
+    wt = torch.randn(c_out, c_in, 3, 3, generator=gen) / (4.5 * c_in) ** 0.5
+    x = torch.randn(n, c_in, h, w, generator=gen)
+    handle = pipeline.build_net(net, [{"w": wt.cuda(), "b": torch.zeros(c_out, device="cuda")}], n, B.F32, tune=False)
+    small = x * 1e-30
+    bad = []
+    for img, py, px in ((n - 1, 0, 0), (0, h - 1, w - 1), (n // 2, h // 2, min(w - 1, 15)), (0, 0, min(w - 1, 13))):
+        b = x.clone()
+        b[img, c_in // 2, py, px] = float("inf")
+        bad.append((b, torch.nn.functional.conv2d(b.double(), wt.double(), None, 1, 1)))
+    ref = torch.nn.functional.conv2d(small.double(), wt.double(), None, 1, 1)
+    errors, rows = {}, []
+    for v in range(B.cprune_num_tile_variants()):
+        name = B.cprune_tile_variant_name(v, True, B.F32)
+        if "conv_split" in name and "rows" not in name:
+            continue
+        try:
+            handle.set_layer_variant(0, v)
+        except B.CPruneError as e:
+            assert e.status == B.ERR_UNSUPPORTED
+            continue
+        print(cfg, name, flush=True)
+        y = handle.forward(small.cuda()).double().cpu()
+        errors[v] = float((y - ref).norm() / ref.norm())
+        if "rows" not in name:
+            continue
+        rows.append(v)
+        for b, want in bad:
+            got = handle.forward(b.cuda()).double().cpu()
+            inf = want.isinf()
+            assert not want.isnan().any() and torch.equal(got[inf], want[inf]), name
+            assert float((got[~inf] - want[~inf]).norm() / want[~inf].norm()) < 1e-6, name
+    base = max(e for v, e in errors.items() if v not in rows)
+    assert len(rows) >= 2
+    for v in rows:
+        assert errors[v] <= 1.1 * base, (v, errors[v], base)
+    handle.close()
