@@ -377,12 +377,13 @@ int cprune_net_fuse_block(cprune_net* net, int layer, int enable);
  * `layer` (what a stored tuning result is applied with).  form 0: the layers apart; 1: the depthwise layer
  * inside its reader's kernel; 2: the whole block as one kernel, where the layer in front is a 1x1 expansion that nobody
  * else reads or, with a 3x3 / stride 1 depthwise layer on a map wider than 8 and at most 32 filters behind it, the
- * network's first layer (3x3 / stride 2 / pad 1 on an image of at most 3 channels).  low 0 / 1: strips as tall as the
- * kernel has them, or about half as tall; wavefronts 1, 2, 4 or 8: how many share a strip at the full batch (smaller
- * batches double it while units idle).  Both are ignored for form 0.  CPRUNE_ERR_INVALID_ARG for other values;
- * CPRUNE_ERR_UNSUPPORTED when the layer heads no such block, the kernel is not built for its widths, or a layer of it runs
- * inside another block's kernel.  Recorded graphs are dropped.  Not to be called while a forward is in flight. */
-int cprune_net_block_form(cprune_net* net, int layer, int form, int low, int wavefronts);
+ * network's first layer (3x3 / stride 2 / pad 1 on an image of at most 3 channels).  tile 0 / 1: strips as tall as the
+ * kernel has them, or about half as tall; 2, for form 1 with a 5x5 window: blocks of 8 x 8 output pixels.  wavefronts 1, 2,
+ * 4 or 8 (4 or 8 with tile 2): how many share a strip or block at the full batch (smaller batches double a strip's while
+ * units idle).  Both are ignored for form 0.  CPRUNE_ERR_INVALID_ARG for other values;
+ * CPRUNE_ERR_UNSUPPORTED when the layer heads no such block, the kernel is not built for its widths, window or wavefronts,
+ * or a layer of it runs inside another block's kernel.  Recorded graphs are dropped.  Not to be called while a forward is in flight. */
+int cprune_net_block_form(cprune_net* net, int layer, int form, int tile, int wavefronts);
 /* Pins the tile variant of a dense conv / fully connected layer (what a stored tuning result
  * is applied with) at the handle's full batch; a smaller batch may run another tile of the same
  * kernel.  A split variant's packed weights are made here.  CPRUNE_ERR_INVALID_ARG for a layer without variants,

@@ -647,10 +647,10 @@ class Net:
         _check(lib().cprune_net_fuse_block(self._h, C.c_int(layer), C.c_int(1 if enable else 0)),
                "cprune_net_fuse_block")
 
-    def block_form(self, layer: int, form: int, low: int = 1, wavefronts: int = 1):
+    def block_form(self, layer: int, form: int, tile: int = 1, wavefronts: int = 1):
         """How the block of depthwise layer `layer` runs: 0 apart, 1 with its 1x1 reader, 2 with the layer in front as well; tall
-        (0) or low (1) strips, 1 / 2 / 4 / 8 wavefronts each."""
-        _check(lib().cprune_net_block_form(self._h, C.c_int(layer), C.c_int(form), C.c_int(low), C.c_int(wavefronts)),
+        (0) or low (1) strips, 1 / 2 / 4 / 8 wavefronts each, or 8 x 8 pixel blocks (2; form 1 with a 5x5 window, 4 / 8)."""
+        _check(lib().cprune_net_block_form(self._h, C.c_int(layer), C.c_int(form), C.c_int(tile), C.c_int(wavefronts)),
                "cprune_net_block_form")
 
     def first_layer_form(self, form: int):

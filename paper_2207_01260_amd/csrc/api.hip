@@ -377,6 +377,10 @@ extern "C" int cprune_fc(const void* x, const void* w, const float* bias, int n,
 // to one 16-byte vector (pad channels are zero and stay zero through every layer).  The
 // boundary stays NCHW: a dense first layer with few input channels reads the caller's tensor
 // as it is (any other reader gets a converted copy); activations are converted on the way out.
+// What a work-group of a depthwise layer inside its 1x1 reader's kernel owns: strips of a map (mbrow_kernel.hpp), or, 5x5 windows
+// only, 8 x 8 output pixels (dwproj_kernel.hpp).
+enum DwTile { kTallStrips = 0, kLowStrips = 1, kPixelBlocks = 2 };
+
 struct NetLayer {
   cprune_layer_desc d;
   int h_in, w_in, h_out, w_out;
@@ -392,8 +396,8 @@ struct NetLayer {
   bool alias = false;         // max-pool folded into its producer: no kernel, act is the producer's buffer
   bool map2x2 = false;        // 3x3 / stride 1 / pad 1 conv on a 2x2 map, run as one matrix over the whole map
   int fuse_dw = -1;           // 1x1 conv: index of the depthwise layer computed inside its kernel, or -1
-  int dw_ks = 0;              // ... and how many wavefronts share a strip there (1, 2, 4, 8; 0: not timed)
-  int dw_low = 1;             // ... and whether its strips are the low ones
+  int dw_ks = 0;              // ... and how many wavefronts share a strip there (1, 2, 4, 8; 0: not timed), or a pixel block (4, 8)
+  int dw_tile = kLowStrips;   // ... and what a work-group owns (DwTile)
   bool fused_away = false;    // depthwise conv that runs inside its consumer's kernel (no launch, no activation)
   int dw_reader = -1;         // depthwise conv that may run inside the 1x1 conv dw_reader's kernel
   int fuse_block = -1;        // 1x1 conv with fuse_dw set: index of the 1x1 expansion in front of that depthwise
@@ -663,7 +667,7 @@ static int net_run_mbrow(cprune_net* net, int i, int n, const void* x, void* dst
   a.N = n; a.H = D.h_in; a.W = D.w_in; a.Ho = D.h_out; a.Wo = D.w_out;
   a.Cpi = image ? E->d.c_in : E ? E->cp_in : 0; a.Ce = D.d.c_out; a.Cpe = D.cp_in; a.O = P.d.c_out; a.Cop = P.cp_out;
   a.act_e = E ? E->d.act : CPRUNE_ACT_NONE; a.act_dw = D.d.act; a.act_out = P.d.act;
-  const int low = E ? P.block_low : P.dw_low;
+  const int low = E ? P.block_low : P.dw_tile != kTallStrips;
   mbrow_tiles(D, mb, low, &a);
   a.magic_x = strip_magic(a.tiles_x); a.magic_y = strip_magic(a.tiles_y);
   a.x_bytes = (unsigned)((size_t)n * (image ? (size_t)a.Hi * a.Wi : (size_t)a.H * a.W) * (E ? a.Cpi : a.Cpe) * es);
@@ -675,12 +679,62 @@ static int net_run_mbrow(cprune_net* net, int i, int n, const void* x, void* dst
   a.slots = 0;
   const int tiles_m = (a.O + mb * 16 - 1) / (mb * 16);
   const dim3 grid((unsigned)((n + a.ipt - 1) / a.ipt * a.tiles_y * a.tiles_x), (unsigned)tiles_m);
-  int ks = E ? P.block_ks : P.dw_ks;                        // the timed choice holds at the full batch
+  int ks = E ? P.block_ks : P.dw_tile == kPixelBlocks ? 0 : P.dw_ks;     // the timed choice holds at the full batch
   if (!ks || n < net->max_batch) ks = mbrow_auto_ks(a, n, tiles_m, ks ? ks : 1);
   int rc;
   if (net->dtype == CPRUNE_F32) rc = launch_mbrow_f32(D.d.k, D.d.stride, mb, xh, low, grid, ks, s, a);
   else if (net->dtype == CPRUNE_F16) rc = launch_mbrow_f16(D.d.k, D.d.stride, mb, xh, low, grid, ks, s, a);
   else rc = launch_mbrow_bf16(D.d.k, D.d.stride, mb, xh, low, grid, ks, s, a);
+  if (rc != CPRUNE_OK) return rc;
+  CPRUNE_LAUNCH_CHECK();
+  return CPRUNE_OK;
+}
+
+// Likewise without an expansion and on pixel blocks.
+static DwProjArgs dwproj_tiles(const NetLayer& P, const NetLayer& D, int* mb) {
+  DwProjArgs a;
+  *mb = P.d.c_out <= 32 ? 2 : (P.d.c_out <= 64 ? 4 : 8);
+  a.tiles_y = (D.h_out + 7) / 8; a.tiles_x = (D.w_out + 7) / 8; a.tiles_m = (P.d.c_out + *mb * 16 - 1) / (*mb * 16);
+  return a;
+}
+
+static long dwproj_groups(const NetLayer& P, const NetLayer& D, int n) {
+  int mb = 0;
+  const DwProjArgs a = dwproj_tiles(P, D, &mb);
+  return (long)n * a.tiles_y * a.tiles_x * a.tiles_m;
+}
+
+// What an untimed 5x5 half runs on: pixel blocks in 16-bit data and at stride 2 (fp32: onto maps of at least 28 columns), from 512
+// work-groups up.  Time of pixel blocks / strips there: f16 0.53-0.82, bf16 0.46-0.93 from 1024 work-groups up, 0.7-1.05 from 512
+// (f16 28x28 1.2-1.3); fp32 at stride 2 0.62-1.02, onto smaller maps 1.1-1.4; fp32 at stride 1 0.8-1.5; below 512 work-groups 1.0-1.6.
+static int dw_tile_untimed(const NetLayer& P, const NetLayer& D, int max_batch, int dtype) {
+  const bool blocks = D.d.k == 5 && (dtype != CPRUNE_F32 || (D.d.stride == 2 && D.w_out >= 28)) && dwproj_groups(P, D, max_batch) >= 512;
+  return blocks ? kPixelBlocks : kLowStrips;
+}
+
+static int net_run_dwproj(cprune_net* net, int i, int n, void* dst, hipStream_t s) {
+  const NetLayer& P = net->layers[i];
+  const NetLayer& D = net->layers[P.fuse_dw];
+  const size_t es = dtype_size(net->dtype);
+  int mb = 0;
+  DwProjArgs a = dwproj_tiles(P, D, &mb);
+  a.x = net->layers[D.d.input].act;
+  a.wdw = D.w; a.bdw = D.b; a.wp = P.w; a.bp = P.b;
+  a.res = P.d.residual >= 0 ? net->layers[P.d.residual].act : nullptr;
+  a.y = dst;
+  a.N = n; a.H = D.h_in; a.W = D.w_in; a.Ho = D.h_out; a.Wo = D.w_out;
+  a.Ce = D.d.c_out; a.Cpe = D.cp_in; a.O = P.d.c_out; a.Cop = P.cp_out;
+  a.pad = D.d.pad; a.act_dw = D.d.act; a.act_out = P.d.act;
+  a.x_bytes = (unsigned)((size_t)n * a.H * a.W * a.Cpe * es);
+  a.wp_bytes = (unsigned)((size_t)a.O * a.Cpe * es);
+  a.wdw_bytes = (unsigned)((size_t)D.d.k * D.d.k * a.Cpe * es);
+  a.vec_out = (a.Cop % 4) == 0 ? 1 : 0;
+  const dim3 grid((unsigned)(n * a.tiles_y * a.tiles_x * a.tiles_m));
+  const int ks = P.dw_ks > 4 ? 2 : 1;
+  int rc;
+  if (net->dtype == CPRUNE_F32) rc = launch_dwproj_f32(D.d.k, D.d.stride, mb, ks, grid, s, a);
+  else if (net->dtype == CPRUNE_F16) rc = launch_dwproj_f16(D.d.k, D.d.stride, mb, ks, grid, s, a);
+  else rc = launch_dwproj_bf16(D.d.k, D.d.stride, mb, ks, grid, s, a);
   if (rc != CPRUNE_OK) return rc;
   CPRUNE_LAUNCH_CHECK();
   return CPRUNE_OK;
@@ -779,7 +833,12 @@ static int net_run_layer(cprune_net* net, int i, int n, const void* x, void* out
   const void* src = L.d.input < 0 ? (L.nchw_in ? x : net->x_cl) : net->layers[L.d.input].act;
   void* dst = out_override ? out_override : L.act;
   if (L.fused_away) return CPRUNE_OK;
-  if (L.fuse_dw >= 0) return net_run_mbrow(net, i, n, x, dst, s);
+  if (L.fuse_dw >= 0) {
+    // (a smaller batch of few pixel blocks runs on strips, which more wavefronts can share)
+    const bool blocks = L.fuse_block < 0 && L.dw_tile == kPixelBlocks &&
+                        (n == net->max_batch || dwproj_groups(L, net->layers[L.fuse_dw], n) >= 256);
+    return blocks ? net_run_dwproj(net, i, n, dst, s) : net_run_mbrow(net, i, n, x, dst, s);
+  }
   if (L.fuse_stem >= 0) return net_run_stem2(net, i, n, x, dst, s);
   if (L.stem7) return net_run_stem7(net, i, n, src, dst, s);
   if (L.stem) return net_run_stem(net, i, n, src, dst, s);
@@ -832,7 +891,8 @@ static int time_layers(cprune_net* net, const int* layers, int n_layers, int bat
 }
 
 // Times the given layers, the last of which runs as one kernel with those before it, with tall and low strips and with the
-// wavefronts per strip that the rule for untimed layers names, or twice as many; leaves the fastest in *low and *ks.
+// wavefronts per strip that the rule for untimed layers names, or twice as many (5x5 halves also on pixel blocks); leaves the fastest
+// in *low (DwTile) and *ks.
 static int time_mbrow(cprune_net* net, const int* layers, int n_layers, int* low, int* ks, float* best, hipStream_t s) {
   const NetLayer& P = net->layers[layers[n_layers - 1]];
   const NetLayer& D = net->layers[P.fuse_dw];
@@ -851,6 +911,14 @@ static int time_mbrow(cprune_net* net, const int* layers, int n_layers, int* low
       if (rc != CPRUNE_OK) return rc;
       if (!best_ks || ms < *best) { *best = ms; best_ks = k; best_low = l; }
     }
+  }
+  // without an expansion, a 5x5 window: on pixel blocks as well
+  for (int k = 4; k <= 8 && P.fuse_block < 0 && D.d.k == 5; k *= 2) {
+    float ms = 0.f;
+    *low = kPixelBlocks; *ks = k;
+    const int rc = time_layers(net, layers, n_layers, net->max_batch, net->x_cl, s, &ms);
+    if (rc != CPRUNE_OK) return rc;
+    if (ms < *best) { *best = ms; best_ks = k; best_low = kPixelBlocks; }
   }
   *low = best_low; *ks = best_ks;
   return CPRUNE_OK;
@@ -1221,6 +1289,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     if (!(pd.kind == CPRUNE_LAYER_CONV && pd.groups == 1 && pd.k == 1 && pd.stride == 1 && pd.pad == 0)) continue;
     if (P.cp_out != round_up_vec(pd.c_out, dtype) || P.nchw_in || P.map2x2 || P.fused_pool) continue;
     D.dw_reader = reader;
+    P.dw_tile = dw_tile_untimed(P, D, max_batch, dtype);
     P.w_proj = P.w_rows;
     if (!P.w_proj) {
       rc = dev_alloc(rows_packed_bytes(pd.c_out, P.cp_in, dtype), &P.w_proj);
@@ -1258,11 +1327,11 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
       if (rc == CPRUNE_OK && block) {
         set_form(2);
         rc = time_mbrow(net, timed, n_timed, &P.block_low, &P.block_ks, &ms, s);
-        if (ms < best) { form = 2; best = ms < 0.8f * best ? 0.f : ms; }     // (far ahead: the third form is not timed)
+        if (ms < best) { form = 2; best = dd.k == 3 && ms < 0.8f * best ? 0.f : ms; }     // (far ahead: the third form is not timed)
       }
       if (rc == CPRUNE_OK && best > 0.f) {
         set_form(1);
-        rc = time_mbrow(net, timed, n_timed, &P.dw_low, &P.dw_ks, &ms, s);
+        rc = time_mbrow(net, timed, n_timed, &P.dw_tile, &P.dw_ks, &ms, s);
         if (ms < best) form = 1;
       }
     }
@@ -1491,8 +1560,8 @@ extern "C" int cprune_net_fuse_block(cprune_net* net, int layer, int enable) {
   return CPRUNE_OK;
 }
 
-extern "C" int cprune_net_block_form(cprune_net* net, int layer, int form, int low, int wavefronts) {
-  if (!net || layer < 0 || layer >= (int)net->layers.size() || form < 0 || form > 2 || low < 0 || low > 1) return CPRUNE_ERR_INVALID_ARG;
+extern "C" int cprune_net_block_form(cprune_net* net, int layer, int form, int tile, int wavefronts) {
+  if (!net || layer < 0 || layer >= (int)net->layers.size() || form < 0 || form > 2 || tile < 0 || tile > 2) return CPRUNE_ERR_INVALID_ARG;
   if (wavefronts != 1 && wavefronts != 2 && wavefronts != 4 && wavefronts != 8) return CPRUNE_ERR_INVALID_ARG;
   NetLayer& D = net->layers[layer];
   if (D.dw_reader < 0) return CPRUNE_ERR_UNSUPPORTED;
@@ -1500,6 +1569,7 @@ extern "C" int cprune_net_block_form(cprune_net* net, int layer, int form, int l
   NetLayer& E = net->layers[D.d.input];
   int mb = 0, xh = 0;
   if (P.fused_away) return CPRUNE_ERR_UNSUPPORTED;      // itself inside a later block's kernel
+  if (form && tile == kPixelBlocks && (form != 1 || D.d.k != 5 || wavefronts < 4)) return CPRUNE_ERR_UNSUPPORTED;
   const bool joined = P.fuse_block >= 0;
   if (form == 2 && !joined && !block_joins(*net, layer, &mb, &xh)) return CPRUNE_ERR_UNSUPPORTED;
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
@@ -1512,8 +1582,8 @@ extern "C" int cprune_net_block_form(cprune_net* net, int layer, int form, int l
   D.fused_away = form > 0;
   P.fuse_dw = form > 0 ? layer : -1;
   P.fuse_block = form == 2 ? D.d.input : -1;
-  if (form == 1) { P.dw_low = low; P.dw_ks = wavefronts; }
-  if (form == 2) { P.block_low = low; P.block_ks = wavefronts; }
+  if (form == 1) { P.dw_tile = tile; P.dw_ks = wavefronts; }
+  if (form == 2) { P.block_low = tile; P.block_ks = wavefronts; }
   if (form == 2 || joined) E.fused_away = form == 2;
   if (form == 2) E.variant = -1;
   else if (joined) {

@@ -196,6 +196,28 @@ int launch_mbrow_bf16(int k, int stride, int mb, int xh, int low, dim3 grid, int
 size_t expand_packed_bytes(int ce, int xh, int dt);
 int launch_pack_expand(const void* w, int ce, int cp, int xh, int dt, void* y, hipStream_t s);
 
+// The depthwise 5x5 layer and the 1x1 convolution behind it through local memory, an 8 x 8 block of output pixels per work-group.
+struct DwProjArgs {
+  const void* x;        // [n][h][w][cpe], expanded activations
+  const void* wdw;      // [k][k][cpe] depthwise weights (folded)
+  const float* bdw;     // [ce] depthwise bias or null
+  const void* wp;       // [o][cpe] projection weights (folded)
+  const float* bp;      // [o] projection bias or null
+  const void* res;      // [n][ho][wo][cop] or null
+  void* y;              // [n][ho][wo][cop]
+  int N, H, W, Ho, Wo, Ce, Cpe, O, Cop;
+  int pad, act_dw, act_out;
+  int tiles_y, tiles_x, tiles_m;
+  unsigned x_bytes, wp_bytes, wdw_bytes;
+  int vec_out;
+};
+// k = 5, stride in {1, 2}, mb in {2, 4, 8} (16-filter blocks per tile), ks in {1, 2} (groups of four wavefronts per work-group
+// that split the channel chunks); grid = one work-group per (image, 8x8 output block, filter tile).
+// CPRUNE_ERR_UNSUPPORTED for other combinations.
+int launch_dwproj_f32(int k, int stride, int mb, int ks, dim3 grid, hipStream_t s, const DwProjArgs& a);
+int launch_dwproj_f16(int k, int stride, int mb, int ks, dim3 grid, hipStream_t s, const DwProjArgs& a);
+int launch_dwproj_bf16(int k, int stride, int mb, int ks, dim3 grid, hipStream_t s, const DwProjArgs& a);
+
 // The first two layers of a network in one kernel: both 3x3 / stride 1 / pad 1, the first on the NCHW image
 // (at most 3 channels) with c1 <= 32 filters, the second dense and channels-last.  d2 / lay2 describe the second
 // layer (c_in = c1, cp_in = its channel stride in w2 <= 32, pool = 0 / 1); w1_packed from launch_repack_stem

@@ -151,8 +151,8 @@ def test_first_layer_in_the_block(orc, cfg, dtype):
     (40, 70, 120, 13, 5, 2, False, 1),
 ])
 def test_pinned_block_forms(orc, cfg, dtype):
-    """Tall and low strips with 1, 2, 4 and 8 wavefronts each, the whole block and its depthwise half, against the oracle.  The
-    forms round alike from step to step and differ in the order of the projection's sums only."""
+    """Tall and low strips with 1, 2, 4 and 8 wavefronts each, the whole block and its depthwise half, 5x5 halves also on pixel blocks,
+    against the oracle, and a smaller batch.  The forms round alike from step to step and differ in the order of the projection's sums only."""
     c_in, c_exp, c_out, hw, k, stride, shortcut, batch = cfg
     net, e, d = _block(c_in, c_exp, c_out, hw, k, stride, shortcut)
     params = synth.layer_params(net, 74)
@@ -162,16 +162,16 @@ def test_pinned_block_forms(orc, cfg, dtype):
     layers, _ = pipeline.prune_net(net, pipeline.upload_params(params), dtype)
     handle = pipeline.build_net(net, layers, batch, dtype, tune=False)
     xd = torch.from_numpy(x).cuda().to(B.TORCH_DTYPE[dtype])
-    for form in (2, 1):
-        for low in (0, 1):
-            for ks in (1, 2, 4, 8):
-                print(cfg, dtype, form, low, ks, flush=True)
-                handle.block_form(d, form, low, ks)
-                assert handle.layer_fused(e) == (form == 2) and handle.layer_fused(d)
-                out = handle.forward(xd)
-                torch.cuda.synchronize()
-                err = nmax(out.float().cpu().numpy(), ref)
-                assert err < TOL[dtype], (form, low, ks, err)
+    pinned = [(form, tile, ks) for form in (2, 1) for tile in (0, 1) for ks in (1, 2, 4, 8)]
+    for form, tile, ks in pinned + ([(1, 2, 4), (1, 2, 8)] if k == 5 else []):
+        print(cfg, dtype, form, tile, ks, flush=True)
+        handle.block_form(d, form, tile, ks)
+        assert handle.layer_fused(e) == (form == 2) and handle.layer_fused(d)
+        for n in (batch, 1):
+            out = handle.forward(xd[:n].contiguous())
+            torch.cuda.synchronize()
+            err = nmax(out.float().cpu().numpy(), ref[:n])
+            assert err < TOL[dtype], (form, tile, ks, n, err)
     handle.block_form(d, 0)
     assert not handle.layer_fused(e) and not handle.layer_fused(d)
     out = handle.forward(xd)
@@ -247,9 +247,11 @@ def test_block_form_refuses_what_it_cannot_run():
     for layer in (d1, d2, d3):
         handle.block_form(layer, 0)
     want = handle.forward(x).clone()
-    for bad in ((d2, 3, 0, 1), (d2, -1, 0, 1), (d2, 2, 2, 1), (d2, 2, 0, 3), (d2, 2, 0, 16), (99, 1, 0, 1)):
+    for bad in ((d2, 3, 0, 1), (d2, -1, 0, 1), (d2, 2, 3, 1), (d2, 2, 0, 3), (d2, 2, 0, 16), (99, 1, 0, 1)):
         refused(B.ERR_INVALID_ARG, *bad)
     refused(B.ERR_UNSUPPORTED, a, 1, 1, 1)               # no depthwise layer
+    refused(B.ERR_UNSUPPORTED, d2, 1, 2, 4)              # pixel blocks are for 5x5 windows
+    refused(B.ERR_UNSUPPORTED, d2, 2, 2, 4)              # without an expansion
     refused(B.ERR_UNSUPPORTED, d1, 2, 1, 1)              # reads a layer on the image
     refused(B.ERR_UNSUPPORTED, d3, 2, 1, 1)              # 300 filters: the whole block is built for up to 128
     handle.block_form(d1, 1)
