@@ -70,15 +70,18 @@ static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay, double 
 
 // Whether an untimed layer takes the row-strip kernel where it runs (3x3 layers of a handle).  16-bit data: always (on 72 random
 // layers 2.35 times as fast as the general kernel, at least 1.15 times).  fp32, against the split kernel: from 0.2 GFLOP up on maps one
-// strip wide and 0.3 on wider ones whose strips are well filled (56 of 4 x 16 columns, not 32 of 3 x 16); there 1.3 times as
-// fast on average, 0.94 times at worst, and below those lines 0.7-1.2 times.  A layer without the split kernel's copy (a smaller batch in a
+// strip wide and 0.3 on wider ones whose strips are well filled (56 of 4 x 16 columns, not 32 of 3 x 16 or, with a pool, 56 of 5 x
+// 16) and whose chunks of 32 channels are not mostly padding as well; there 1.12 times as fast on average (63 random layers of 28 to 400 us),
+// 0.95 times at worst; the layers left out by the fill alone 0.9-1.07 times, and below the lines 0.7-1.2 times.  A layer without the split kernel's copy (a smaller batch in a
 // handle whose full batch runs row strips) has the general kernel's fp32 instruction in its place, and always takes them:
 // ResNet-18 built for 32, 2 and 1 images 213 -> 198 and 269 -> 190 us, VGG-16 built for 64, 8 images 173 -> 141.
 static bool rows_pay(const cprune_conv_desc& d, const ConvLayout& lay) {
   if (d.dtype != CPRUNE_F32 || !lay.w_split) return true;
   const double flops = 18.0 * d.n * d.h * d.w * (double)d.c_out * d.c_in;
   if (d.w <= 16) return flops >= 2e8;
-  return flops >= 3e8 && d.w >= 0.85 * 16 * ((d.w - 16 + 13) / 14 + 1);
+  const int step = lay.pool ? 12 : 14, strips = (d.w - 16 + step - 1) / step + 1;      // (as rows_tiles has them)
+  const double cols = d.w / (16.0 * strips), chans = lay.cp_in / (32.0 * ((lay.cp_in + 31) / 32));
+  return flops >= 3e8 && cols >= 0.85 && cols * chans >= 0.6;
 }
 
 // Untimed choice: the row-strip kernel where it pays; otherwise the cheapest by variant_cost among the general kernel's tiles,
