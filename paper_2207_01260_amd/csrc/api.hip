@@ -893,35 +893,37 @@ static int time_layers(cprune_net* net, const int* layers, int n_layers, int bat
   return CPRUNE_OK;
 }
 
-// Times the given layers, the last of which runs as one kernel with those before it, with tall and low strips and with the
-// wavefronts per strip that the rule for untimed layers names, or twice as many (5x5 halves also on pixel blocks); leaves the fastest
-// in *low (DwTile) and *ks.
-static int time_mbrow(cprune_net* net, const int* layers, int n_layers, int* low, int* ks, float* best, hipStream_t s) {
+// Times the given layers, the last of which runs as one kernel with those before it: with tall and low strips and with the
+// wavefronts per strip that the rule for untimed layers names, or twice as many (strips = false: not); 5x5 halves of 256 work-groups and more
+// on pixel blocks as well.  Leaves the fastest in *low (DwTile) and *ks, its time in *best (infinite, and both untouched: none timed).
+static int time_mbrow(cprune_net* net, const int* layers, int n_layers, bool strips, int* low, int* ks, float* best, hipStream_t s) {
   const NetLayer& P = net->layers[layers[n_layers - 1]];
   const NetLayer& D = net->layers[P.fuse_dw];
-  int mb = 0, xh = 0, best_low = 0, best_ks = 0;
+  int mb = 0, xh = 0, best_low = *low, best_ks = *ks;
+  *best = __builtin_inff();
+  auto take = [&](int tile, int k) -> int {
+    float ms = 0.f;
+    *low = tile; *ks = k;
+    const int rc = time_layers(net, layers, n_layers, net->max_batch, net->x_cl, s, &ms);
+    if (rc == CPRUNE_OK && ms < *best) { *best = ms; best_ks = k; best_low = tile; }
+    return rc;
+  };
   mbrow_form_of(*net, P, P.fuse_block >= 0 ? &net->layers[P.fuse_block] : nullptr, &mb, &xh);
-  for (int l = 0; l < 2; ++l) {
+  for (int l = 0; l < 2 && strips; ++l) {
     if (l && mbrow_rows(D.d.k, D.d.stride, mb, 0) == mbrow_rows(D.d.k, D.d.stride, mb, 1)) break;
     MbArgs a;
     mbrow_tiles(D, mb, l, &a);
     a.nchunk = (int)((D.cp_in * dtype_size(net->dtype) + 63) / 64);
     const int k0 = mbrow_auto_ks(a, net->max_batch, (P.d.c_out + mb * 16 - 1) / (mb * 16), 1);
     for (int k = k0; k <= 8 && k <= 2 * k0; k *= 2) {
-      float ms = 0.f;
-      *low = l; *ks = k;
-      const int rc = time_layers(net, layers, n_layers, net->max_batch, net->x_cl, s, &ms);
+      const int rc = take(l, k);
       if (rc != CPRUNE_OK) return rc;
-      if (!best_ks || ms < *best) { *best = ms; best_ks = k; best_low = l; }
     }
   }
-  // without an expansion, a 5x5 window: on pixel blocks as well
-  for (int k = 4; k <= 8 && P.fuse_block < 0 && D.d.k == 5; k *= 2) {
-    float ms = 0.f;
-    *low = kPixelBlocks; *ks = k;
-    const int rc = time_layers(net, layers, n_layers, net->max_batch, net->x_cl, s, &ms);
+  const long groups = dwproj_groups(P, D, net->max_batch);
+  if (P.fuse_block < 0 && D.d.k == 5 && groups >= 256) {
+    const int rc = take(kPixelBlocks, groups <= 320 ? 8 : 4);
     if (rc != CPRUNE_OK) return rc;
-    if (ms < *best) { *best = ms; best_ks = k; best_low = kPixelBlocks; }
   }
   *low = best_low; *ks = best_ks;
   return CPRUNE_OK;
@@ -1324,17 +1326,19 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
       const int* timed = block ? layers_of : layers_of + 1;
       const int n_timed = block ? 3 : 2;
       float best = 0.f, ms = 0.f;
+      bool ahead = false;
       set_form(0);
       rc = time_layers(net, timed, n_timed, max_batch, net->x_cl, s, &best);
       form = 0;
       if (rc == CPRUNE_OK && block) {
         set_form(2);
-        rc = time_mbrow(net, timed, n_timed, &P.block_low, &P.block_ks, &ms, s);
-        if (ms < best) { form = 2; best = dd.k == 3 && ms < 0.8f * best ? 0.f : ms; }     // (far ahead: the third form is not timed)
+        rc = time_mbrow(net, timed, n_timed, true, &P.block_low, &P.block_ks, &ms, s);
+        ahead = ms < 0.8f * best;      // (the depthwise half on strips is not timed then)
+        if (ms < best) { form = 2; best = ms; }
       }
-      if (rc == CPRUNE_OK && best > 0.f) {
+      if (rc == CPRUNE_OK) {
         set_form(1);
-        rc = time_mbrow(net, timed, n_timed, &P.dw_tile, &P.dw_ks, &ms, s);
+        rc = time_mbrow(net, timed, n_timed, !ahead, &P.dw_tile, &P.dw_ks, &ms, s);
         if (ms < best) form = 1;
       }
     }

@@ -167,9 +167,11 @@ struct MbArgs {
   int slots;            // wavefronts whose sums fit the exchange area (set by the launcher)
 };
 
-// Output rows a wavefront owns (k in {3, 5}, stride in {1, 2}, mb filter blocks): as many as its registers hold beside the
+// Output rows a wavefront owns (k in {3, 5}, stride in {1, 2}, mb filter blocks): about as many as its registers hold beside the
 // window's weights, multiples or halves of 7 where possible (the maps of the evaluated networks are 7 x 2^n); low = 1: about
-// half as many, for maps whose tall strips leave units idle.
+// half as many, for maps whose tall strips leave units idle.  Some forms hold more than fit and spill: 14 of the 82 fp32 forms, 21 of the
+// 75 bf16 and 8 of the 75 fp16 ones, by 1 to 94 registers, most where the window is 5x5 (its widened weights are 100
+// registers) or a tall strip has 48 filters and more.  Timing chooses among tall and low all the same.
 constexpr int mbrow_rows(int k, int s, int mb, int low) {
   if (s == 1 && k == 3) return mb <= 4 ? (low ? 4 : 7) : mb == 6 ? (low ? 3 : 5) : (low ? 2 : 3);
   if (s == 1) return mb <= 2 ? (low ? 2 : 4) : 2;

@@ -26,8 +26,11 @@
 // faster of both / this kernel.  MobileNetV2 fp32 at batch 64: 16 -> 50 -> 24, 112x112 stride 2: 110 / 42; 24 -> 65 -> 24 at 56x56:
 // 70 / 33; 24 -> 86 -> 32, 56x56 stride 2: 56 / 24; 32 -> 92 -> 32 at 28x28: 30 / 18; 64 -> 330 -> 64 at 14x14: 38 / 26.  MnasNet bf16 at
 // batch 16: 16 -> 38 -> 24, 112x112: 20 / 11; 24 -> 58 -> 24 at 56x56: 15 / 9.  Without an expansion: 32 -> 16 at 112x112, fp32 b64
-// 52 / 42; with the first layer in front of it (image 3 -> 32 -> 16) 88 / 62, bf16 b16 20.3 / 16.6 (the windows' gather from LDS).  In fp32 the matrix cores bound it: inside the chunk loop they are busy 60 % of the time (24 -> 65 -> 24: 4.9 us per chunk
-// for 2048 strips, 3.0 us of it MFMA issue), launch, staging and stores are 9 of the 33 us.
+// 52 / 42; with the first layer in front of it (image 3 -> 32 -> 16) 88 / 62, bf16 b16 20.3 / 16.6 (the windows' gather from LDS).  In fp32 the
+// matrix cores bound it most: over whole launches of MobileNetV2's blocks they are busy 29-58 % of the cycles in which their units have
+// work, the vector ALU 18-37 % (image form 37 and 60), and wavefronts wait to issue for 34-60 % of their cycles and for memory 15-39;
+// in the chunk loop 24 -> 65 -> 24 takes 4.9 us per chunk for 2048 strips, 3.0 us of it MFMA issue; launch, staging and stores are 9
+// of its 33 us.
 #pragma once
 #include <atomic>
 #include "conv_nhwc_kernel.hpp"
