@@ -314,8 +314,8 @@ int cprune_net_forward(cprune_net* net, const void* x, int n, void* logits, int 
                        void* stream);
 /* Per-layer device time: after one untimed pass that gives every layer its inputs, each
  * layer is launched `iters` times back to back between two events on `stream`; ms_out
- * (host, [n_layers]) gets the time per launch (0 for a pool folded into its producer and for a depthwise layer
- * that runs inside its reader's kernel).
+ * (host, [n_layers]) gets the time per launch (0 for a pool folded into its producer and for a layer that runs
+ * inside a later layer's kernel).
  * Synchronises. */
 int cprune_net_layer_times(cprune_net* net, const void* x, int n, int iters, float* ms_out,
                            void* stream);
