@@ -367,6 +367,8 @@ int cprune_net_layer_fused(const cprune_net* net, int layer, int* fused_out);
  * block whose depthwise layer is `layer`: enable != 0 runs the block as one kernel, 0 leaves
  * the expansion on its own (the depthwise layer stays inside its reader's kernel).
  * cprune_net_fuse_depthwise on the same layer also leaves the one-kernel form.
+ * A 1x1 conv between two depthwise layers is the reader of one and the expansion of the other: it leaves the kernel it is in
+ * when either call puts it into the other's.
  * CPRUNE_ERR_UNSUPPORTED when the layer heads no such block or the block's weights and input patch do not
  * fit the local memory of a compute unit (such a block runs as one kernel only where cprune_net_create timed it as
  * the fastest form or cprune_net_block_form asked for it; enable = 0 is accepted there).  Recorded graphs are dropped.  Not to be called while

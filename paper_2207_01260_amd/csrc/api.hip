@@ -1531,6 +1531,11 @@ extern "C" int cprune_net_fuse_depthwise(cprune_net* net, int layer, int enable)
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
   drop_graphs(net);
   NetLayer& P = net->layers[D.dw_reader];
+  if (enable && P.fused_away) {        // the reader is the expansion of a later block's kernel: out of there first
+    for (NetLayer& Q : net->layers)
+      if (Q.fuse_block == D.dw_reader) Q.fuse_block = -1;
+    P.fused_away = false;
+  }
   if (P.fuse_block >= 0) {             // leaves the one-kernel block form either way
     NetLayer& E = net->layers[P.fuse_block];
     E.fused_away = false;
@@ -1555,6 +1560,11 @@ extern "C" int cprune_net_fuse_block(cprune_net* net, int layer, int enable) {
   drop_graphs(net);
   NetLayer& E = net->layers[D.d.input];
   if (enable) {
+    if (E.fuse_dw >= 0) {              // the expansion runs an earlier depthwise layer inside its own kernel: apart first
+      if (E.fuse_block >= 0) return CPRUNE_ERR_UNSUPPORTED;
+      net->layers[E.fuse_dw].fused_away = false;
+      E.fuse_dw = -1;
+    }
     E.fused_away = true; D.fused_away = true;
     P.fuse_dw = layer; P.fuse_block = D.d.input;
     P.variant = -1; E.variant = -1;

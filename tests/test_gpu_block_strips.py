@@ -264,3 +264,32 @@ def test_block_form_refuses_what_it_cannot_run():
     torch.cuda.synchronize()
     assert float((got - want).norm() / want.norm()) < 1e-5
     handle.close()
+
+
+def test_a_1x1_layer_between_two_depthwise_layers():
+    """It is the projection of the first and the expansion of the second: whichever form is asked for last, no layer is left out."""
+    net = synth.NetSpec("between", 8, 20, 20)
+    a = net.add(synth.Layer("conv", -1, 8, 16, k=1, act=synth.ACT_RELU, bn=True, name="a"))
+    d1 = net.add(synth.Layer("conv", a, 16, 16, k=3, stride=1, pad=1, groups=16, act=synth.ACT_RELU, bn=True, name="d1"))
+    b = net.add(synth.Layer("conv", d1, 16, 24, k=1, act=synth.ACT_RELU, bn=True, name="b"))
+    d2 = net.add(synth.Layer("conv", b, 24, 24, k=3, stride=1, pad=1, groups=24, act=synth.ACT_RELU, bn=True, name="d2"))
+    net.add(synth.Layer("conv", d2, 24, 20, k=1, act=synth.ACT_NONE, bn=True, name="c"))
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(synth.layer_params(net, 77)), B.F32)
+    handle = pipeline.build_net(net, layers, 2, B.F32, tune=False)
+    x = torch.from_numpy(synth.net_input(net, 77, 2)).cuda()
+    want = handle.forward(x).clone()
+    for step, fused in ((lambda: handle.fuse_block(d2, True), (d1, 0, b, 1, d2, 1)),
+                        (lambda: handle.fuse_depthwise(d1, True), (d1, 1, b, 0, d2, 1)),
+                        (lambda: handle.fuse_block(d2, True), (d1, 0, b, 1, d2, 1)),
+                        (lambda: handle.fuse_depthwise(d1, False), (d1, 0, b, 1, d2, 1)),
+                        (lambda: handle.fuse_depthwise(d1, True), (d1, 1, b, 0, d2, 1)),
+                        (lambda: handle.fuse_block(d2, False), (d1, 1, b, 0, d2, 1)),
+                        (lambda: handle.fuse_depthwise(d2, False), (d1, 1, b, 0, d2, 0))):
+        step()
+        for i, on in zip(fused[::2], fused[1::2]):
+            assert handle.layer_fused(i) == bool(on), (fused, i)
+        handle.forward(torch.zeros_like(x))                 # (what an earlier form left in a buffer does not help)
+        got = handle.forward(x + 0)
+        torch.cuda.synchronize()
+        assert float((got - want).norm() / want.norm()) < 1e-5, fused
+    handle.close()
