@@ -34,22 +34,22 @@ if ROOT not in sys.path:
 # to the kernel sources they were measured on: TRAFFIC_SOURCE_HASH is kernel_source_hash() of that tree,
 # and any change to a file under csrc/ since then reports null instead of a stale figure (as does a
 # selection that runs a kernel on a layer it was not profiled on).
-TRAFFIC_SOURCE_HASH = "5b12e2caef974f5b"
+TRAFFIC_SOURCE_HASH = "9ad4917eb63fe9f8"
 TRAFFIC = {
-    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3351365,
-    ("conv_split_rows_kernel<4, 1>", 64, "conv3"): 11213258,
-    ("conv_split_rows_kernel<8, 1>", 64, "conv3"): 14311393,
-    ("conv_split_rows_kernel<8, 4>", 64, "conv4"): 19437790,
-    ("conv_split_rows_kernel<4, 2>", 64, "conv5"): 6012296,
-    ("conv_split_rows_kernel<4, 4>", 64, "conv6"): 15570302,
-    ("conv_split_rows_kernel<8, 4>", 64, "conv6"): 15678618,
-    ("conv_split_rows_kernel<4, 4>", 64, "conv7"): 18453163,
-    ("conv_split_rows_kernel<4, 2>", 64, "conv8"): 27363538,
-    ("conv_split_rows_kernel<4, 8>", 64, "conv9"): 35619804,
-    ("conv_split_rows_kernel<4, 4>", 64, "conv10"): 33343691,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7679407,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392429,
-    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537580,
+    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3351368,
+    ("conv_split_rows_kernel<4, 1>", 64, "conv3"): 11213257,
+    ("conv_split_rows_kernel<8, 1>", 64, "conv3"): 14311407,
+    ("conv_split_rows_kernel<8, 4>", 64, "conv4"): 19437732,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv5"): 6012307,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv6"): 15570208,
+    ("conv_split_rows_kernel<8, 4>", 64, "conv6"): 15678650,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv7"): 18452216,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv8"): 27363604,
+    ("conv_split_rows_kernel<4, 8>", 64, "conv9"): 35619892,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv10"): 33343775,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7679426,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392445,
+    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537599,
 }
 
 
