@@ -419,7 +419,7 @@ struct NetLayer {
   void* w_split = nullptr;    // fp32 dense layer: weights once more, cut and packed for the split kernel
   void* w_rows3 = nullptr;    // fp32 3x3 / stride 1 / pad 1 layer: likewise, for the row-strip kernel
   bool stem = false;          // nchw_in layer that runs the first-layer kernel (whole reduction in LDS)
-  void* w_stem7 = nullptr;    // 16-bit 7x7 / stride 2 / pad 3 first layer: weights packed for the kernel made for it
+  void* w_stem7 = nullptr;    // 7x7 / stride 2 / pad 3 first layer: weights packed for the kernel made for it
   int stem7 = 0;              // 1: that kernel runs the layer; 2: and the 3x3 / stride 2 max-pool pool3 with it
   int pool3 = -1;             // the max-pool that can run inside that kernel (the layer's only reader), or -1
   bool in_producer = false;   // max-pool computed inside its producer's kernel: no launch, its buffer is written there
@@ -535,6 +535,11 @@ static void drop_copies(cprune_net* net, NetLayer& L, int v) {
   }
 }
 
+// The opening of the ImageNet networks, which has kernels of its own.
+static bool stem7_layer(const NetLayer& L) {
+  return L.nchw_in && L.d.c_in <= 3 && L.d.k == 7 && L.d.stride == 2 && L.d.pad == 3 && L.d.residual < 0;
+}
+
 constexpr size_t kMaxGraphs = 8;
 
 static void drop_graphs(cprune_net* net) {
@@ -581,7 +586,35 @@ static int net_run_stem(cprune_net* net, int i, int n, const void* x, void* dst,
   return CPRUNE_OK;
 }
 
-// The 16-bit 7x7 / stride 2 first-layer kernel on the caller's NCHW input, with or without the max-pool behind it.
+// The fp32 7x7 / stride 2 first-layer kernel.  A work-group walks over a band of rows and repeats the row above it for the pool;
+// the bands are those for which the rounds of 1024 work-groups that fit the chip (four of two wavefronts per unit) take the fewest steps,
+// a work-group's start and its repeated row counted as one step and a fifth.  64 filters at 224x224 (us), as many bands as fit one
+// round / this rule: batch 32 60 / 60, 33 76 / 69; one image 9.0 / 8.6.
+static int net_run_stem7_f32(const NetLayer& L, bool pool, int n, StemArgs a, hipStream_t s) {
+  const int mb = a.O <= 32 ? 1 : 2;
+  a.tiles_m = (a.O + 32 * mb - 1) / (32 * mb);
+  a.tiles_x = pool ? (a.Wp + 6) / 7 : (a.Wo + 15) / 16;
+  const long strips = (long)n * a.tiles_x * a.tiles_m, steps = pool ? a.Hp : (a.Ho + 1) / 2;
+  double best = 0.0;
+  for (long bands = 1; bands <= steps; ++bands) {
+    const long band = (steps + bands - 1) / bands;
+    const double cost = ((strips * bands + 1023) / 1024) * (band + 1.2);
+    if (bands == 1 || cost < best) { best = cost; a.band = (int)band; }
+  }
+  a.tiles_y = (int)((steps + a.band - 1) / a.band);
+  a.magic_x = a.tiles_x > 1 ? (unsigned)((0x100000000ull + a.tiles_x - 1) / a.tiles_x) : 0u;
+  a.magic_y = a.tiles_y > 1 ? (unsigned)((0x100000000ull + a.tiles_y - 1) / a.tiles_y) : 0u;
+  a.w_raw = L.w;
+  a.x_bytes = (unsigned)((size_t)n * a.C * a.H * a.W * 4);
+  a.w_bytes = (unsigned)stem7_packed_bytes(a.O);
+  a.w_raw_bytes = (unsigned)((size_t)a.O * a.C * 49 * 4);
+  const int rc = launch_conv_stem7_f32(mb, pool ? 1 : 0, dim3((unsigned)((long)n * a.tiles_y * a.tiles_x), (unsigned)a.tiles_m), s, a);
+  if (rc != CPRUNE_OK) return rc;
+  CPRUNE_LAUNCH_CHECK();
+  return CPRUNE_OK;
+}
+
+// The 7x7 / stride 2 first-layer kernel on the caller's NCHW input, with or without the max-pool behind it.
 static int net_run_stem7(cprune_net* net, int i, int n, const void* x, void* dst, hipStream_t s) {
   const NetLayer& L = net->layers[i];
   const bool pool = L.stem7 == 2;
@@ -595,7 +628,9 @@ static int net_run_stem7(cprune_net* net, int i, int n, const void* x, void* dst
     const NetLayer& P = net->layers[L.pool3];
     a.y = P.act; a.Hp = P.h_out; a.Wp = P.w_out; a.Cop = P.cp_out;
     a.tiles_y = (a.Hp + 6) / 7; a.tiles_x = (a.Wp + 6) / 7;
+    if (net->dtype == CPRUNE_F32) return net_run_stem7_f32(L, true, n, a, s);
   } else {
+    if (net->dtype == CPRUNE_F32) return net_run_stem7_f32(L, false, n, a, s);
     a.tiles_y = (a.Ho + 15) / 16; a.tiles_x = (a.Wo + 15) / 16;
   }
   a.vec_out = (a.Cop % 4) == 0 ? 1 : 0;
@@ -1188,7 +1223,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
       if (rc != CPRUNE_OK) break;
     }
     bool use = true;
-    if (tune) {
+    if (tune && !(dtype == CPRUNE_F32 && stem7_layer(L))) {
       float ms[2] = {0.f, 0.f};
       for (int form = 0; form < 2 && rc == CPRUNE_OK; ++form) {   // 0: general kernel, 1: first-layer kernel
         L.stem = form == 1;
@@ -1200,15 +1235,22 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     if (use) L.variant = -1;
   }
 
-  // 16-bit data, 7x7 / stride 2 / pad 3 on the image (the first layer of the ImageNet networks): a kernel whose
+  // 7x7 / stride 2 / pad 3 on the image (the first layer of the ImageNet networks): a kernel whose
   // reduction order makes every MFMA operand one LDS read, and which can run the 3x3 / stride 2 / pad 1 max-pool
   // behind the layer as well when nobody else reads the conv map.  With tune != 0 the three forms (as decided so far;
-  // that kernel; that kernel with the pool) are timed and the fastest kept; otherwise the most fused one is taken.
+  // that kernel; that kernel with the pool) are timed and the fastest kept; otherwise the most fused one is taken.  In fp32 nothing
+  // is timed: the kernel is always the faster one (with the pool inside, the layers apart / this, us: 64 filters at 224x224, 1 image
+  // 13.1 / 9.0, 8 40.5 / 22.6, 32 120 / 60; 96 filters, 8 images 58 / 34; 64 at 16x16, 128 images 10.9 / 9.5; 8 at 64x64, 4 images
+  // 8.4 / 5.3; 16 at 224x224, 8 images 15.3 / 12.8); an untimed fp32 handle keeps the conv map.
   for (int i = 0; i < n_layers && rc == CPRUNE_OK; ++i) {
     NetLayer& L = net->layers[i];
     const cprune_layer_desc& d = L.d;
-    if (dtype == CPRUNE_F32 || !L.nchw_in || d.c_in > 3 || d.k != 7 || d.stride != 2 || d.pad != 3 || d.residual >= 0) continue;
-    {
+    if (!stem7_layer(L)) continue;
+    if (dtype == CPRUNE_F32) {
+      rc = dev_alloc(stem7_packed_bytes(d.c_out), &L.w_stem7);
+      if (rc == CPRUNE_OK) rc = launch_pack_stem7(L.w, d.c_out, d.c_in, L.w_stem7, s);
+      if (rc != CPRUNE_OK) break;
+    } else {
       const int mb = d.c_out <= 32 ? 2 : 4;
       const int rows = (d.c_out + mb * 16 - 1) / (mb * 16) * (mb * 16);
       rc = dev_alloc((size_t)rows * kStem7K * es, &L.w_stem7);
@@ -1229,8 +1271,8 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
       if (L.pool3 >= 0) net->layers[L.pool3].in_producer = form == 2;
     };
     const int n_forms = L.pool3 >= 0 ? 3 : 2;
-    int best = n_forms - 1;
-    if (tune) {
+    int best = dtype == CPRUNE_F32 && !tune ? 1 : n_forms - 1;
+    if (tune && dtype != CPRUNE_F32) {
       const int pair[2] = {i, L.pool3};
       float ms[3] = {0.f, 0.f, 0.f};
       for (int form = 0; form < n_forms && rc == CPRUNE_OK; ++form) {
@@ -1515,6 +1557,7 @@ extern "C" int cprune_net_first_layer_form(cprune_net* net, int form) {
   if (first < 0) return CPRUNE_ERR_UNSUPPORTED;
   NetLayer& L = net->layers[first];
   if (form == 2 && L.pool3 < 0) return CPRUNE_ERR_UNSUPPORTED;
+  if (net->dtype == CPRUNE_F32 && (form == 1 || L.pool3 < 0)) return CPRUNE_ERR_UNSUPPORTED;
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
   drop_graphs(net);
   L.stem7 = form;

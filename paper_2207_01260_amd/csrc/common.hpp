@@ -242,8 +242,11 @@ struct StemArgs {
   unsigned magic_x, magic_y;   // ceil(2^32 / tiles_x), ceil(2^32 / tiles_y), 0 for a divisor of 1 (exact while
                                // pixel blocks x divisor < 2^32: always, for tensors below 2^31 bytes)
   int vec_out;
-  int Hp = 0, Wp = 0;   // 7x7 / stride 2 kernel with the 3x3 / stride 2 / pad 1 max-pool inside: the pooled map; y is
-                        // then [n][hp][wp][cop] and tiles_y, tiles_x count 7 x 7 blocks of it
+  int Hp = 0, Wp = 0;   // 7x7 / stride 2 kernels with the 3x3 / stride 2 / pad 1 max-pool inside: the pooled map; y is
+                        // then [n][hp][wp][cop] and tiles_y, tiles_x count 7 x 7 blocks of it (fp32: bands of rows x 7 columns)
+  int band = 0;         // fp32 7x7 / stride 2 kernel: pairs of conv rows a work-group walks over
+  const void* w_raw = nullptr;          // ... the weights as they are, [o][c][7][7]
+  unsigned x_bytes = 0, w_bytes = 0, w_raw_bytes = 0;
 };
 // (k, stride) in {(3, 1), (3, 2), (7, 2)}, mb in {2, 4} (16-filter blocks per tile); grid.x = workers
 // that share the (image, 8x16 output block) list round-robin, grid.y = filter tiles.
@@ -261,5 +264,12 @@ constexpr int kStem7K = 224;
 int launch_repack_stem7(const void* w, int o, int c, int rows, int dt, void* y, hipStream_t s);
 int launch_conv_stem7_f16(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a);
 int launch_conv_stem7_bf16(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a);
+// The same layer in fp32 on three bf16 parts, reduction ordered (channel, window row, 8 columns: zero, then the window's), weights
+// [16-filter block][6 rounds][3 parts][lane][16 bytes] from launch_pack_stem7.  mb in {1, 2} blocks per wavefront, two wavefronts per
+// work-group; grid.x = (image, band of rows, strip), grid.y = tiles of 32 mb filters.
+constexpr int kStem7SplitRounds = 6;
+inline size_t stem7_packed_bytes(int o) { return (size_t)((o + 15) / 16) * kStem7SplitRounds * 3 * 1024; }
+int launch_pack_stem7(const void* w, int o, int c, void* y, hipStream_t s);
+int launch_conv_stem7_f32(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a);
 
 }  // namespace cprune
