@@ -50,6 +50,7 @@ struct TileVariant {
   int split = 0;  // 1 (with sched = -1): split kernel, any window and stride, fp32 as three bf16 parts
   int rows = 0;   // 1 (with sched = -1): row-strip kernel, 3x3 layers of a handle; th = rows of a strip, ks = wavefronts that
                   // share one (patch_id indexes its list)
+  int pw3 = 0;    // 1, 2 (deep) (with sched = -1): 1x1 kernel on three 16-bit parts, fp32 layers of a handle (patch_id indexes its list)
   int nib = 0;    // split kernel: staging items per thread (patch_id indexes its list)
   int nr = 0;     // short-reduction 1x1 kernel: 64-byte rounds of the reduction its filter tile holds
   int stride = 1; // spatial-patch kernel on 16x16 blocks: the window stride it is built for (patch_id then indexes the
@@ -83,8 +84,8 @@ struct ConvLayout {
   const void* w_split = nullptr; // channels-last fp32: the weights cut and packed for the split kernel
                                  // (launch_pack_split), which runs only where this is set; a call in the boundary's
                                  // layout packs its weights into the caller's scratch
-  const void* w_rows3 = nullptr; // channels-last fp32 3x3 / stride 1 / pad 1: cut and packed in whole chunks of 32 channels for the
-                                 // row-strip kernel, which runs fp32 data only where this is set
+  const void* w_rows3 = nullptr; // channels-last fp32 3x3 / stride 1 / pad 1, or 1x1: cut and packed in whole chunks of 32 channels for
+                                 // the row-strip kernel (the 1x1 kernel), which runs fp32 data only where this is set
   int pool = 0;  // 1: channels-last 3x3 layer with a 2x2/2 max-pool fused behind the activation (patch kernels);
                  // 2: rows are (channel, position of a 2x2 map) and each group of four rows is reduced to its
                  //    maximum behind the activation; cp_out is the stride of the pooled output
@@ -100,6 +101,7 @@ size_t variant_ws_bytes(const cprune_conv_desc& d, int v, const ConvLayout& lay)
 // Estimated clocks of a variant: of the general kernel on a layer it runs, of the split and the row-strip kernel (-1 where
 // they do not run the layer); -1 for the others.
 int best_split_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost);   // the cheapest; -1: none runs it
+int best_pw3_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost);     // and of the 1x1 kernel on three parts
 int best_rows_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost);    // likewise of the row-strip kernel
 double variant_cost(const cprune_conv_desc& d, int v, const ConvLayout& lay);
 int cached_or_heuristic_variant(const cprune_conv_desc& d, bool* timed, const ConvLayout& lay = ConvLayout());

@@ -7,6 +7,7 @@
 #include "conv_patch32_kernel.hpp"
 #include "conv_split_kernel.hpp"
 #include "conv_rows_kernel.hpp"
+#include "conv_pw3_kernel.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -235,11 +236,12 @@ int launch_split_conv(const cprune_conv_desc& d, const TileVariant& tv, const Co
 
 constexpr int kFirstSplit = kNumTiles * kNumScheds + kNumPatch + kNumPatch32 + kNumKsplit + kNumPw + kNumWave + kNumPatchS2;
 constexpr int kFirstRows = kFirstSplit + kNumSplit;
-int num_variants() { return kFirstRows + kNumRows; }
+constexpr int kFirstPw3 = kFirstRows + kNumRows;
+int num_variants() { return kFirstPw3 + kNumPw3; }
 
 namespace {
 struct VariantTable {
-  TileVariant table[kFirstRows + kNumRows];
+  TileVariant table[kFirstPw3 + kNumPw3];
   VariantTable() {
 #define CPRUNE_PATCH_ROW(ID, MB_, TH_, TW_, NI_, KQ_, KS_)                                 \
     {                                                                         \
@@ -306,6 +308,13 @@ struct VariantTable {
     }
     CPRUNE_ROWS_LIST(CPRUNE_ROWS_ROW)
 #undef CPRUNE_ROWS_ROW
+#define CPRUNE_PW3_ROW(ID, MB_, NB_, DEEP_)                                                \
+    {                                                                                      \
+      TileVariant& kv = table[kFirstPw3 + ID];                                             \
+      kv.wm = 4; kv.wn = 1; kv.mb = MB_; kv.nb = NB_; kv.kq = 2; kv.sched = -1; kv.pw3 = 1 + DEEP_; kv.patch_id = ID; \
+    }
+    CPRUNE_PW3_LIST(CPRUNE_PW3_ROW)
+#undef CPRUNE_PW3_ROW
     for (int t = 0; t < kNumTiles; ++t)
       for (int s = 0; s < kNumScheds; ++s) {
         table[t * kNumScheds + s] = kTiles[t];
@@ -381,8 +390,38 @@ int best_rows_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* 
   return best_v;
 }
 
+// Work-groups of the 1x1 kernel on three parts along pixels and filters.
+static long pw3_groups(const cprune_conv_desc& d, const TileVariant& tv, long* tiles_m) {
+  const long P = (long)d.n * conv_out_dim(d.h, 1, d.stride, 0) * conv_out_dim(d.w, 1, d.stride, 0);
+  *tiles_m = (d.c_out + tv.tile_m() - 1) / tv.tile_m();
+  return (P + tv.tile_p() - 1) / tv.tile_p() * *tiles_m;
+}
+
+// Clocks of one of its variants, to choose among them: as split_cost, constants from timings of all variants on 160 random layers.
+static double pw3_cost(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay) {
+  long tiles_m;
+  const double groups = (double)pw3_groups(d, tv, &tiles_m), rounds = (lay.cp_in + 31) / 32;
+  const double blocks = std::ceil((d.c_out + 15) / 16 / (double)tiles_m / 4.0);      // of a tile's longest share
+  const bool deep = tv.pw3 == 2;
+  const int occ = tv.nb > 2 ? (tv.mb == 1 ? 3 : 2) : tv.mb == 1 ? (deep ? 4 : 6) : deep ? 2 : 4;
+  const double held = std::max(1.0, std::min((double)occ, groups / 256.0));      // work-groups of a unit hide each other's waits
+  return std::ceil(groups / 256.0) * rounds * blocks * tv.nb * 108.0 +
+         std::ceil(groups / (256.0 * occ)) * ((deep ? 5500.0 : 5000.0) + rounds * (deep ? 650.0 : 850.0) / held);
+}
+
+int best_pw3_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost) {
+  int best_v = -1;
+  for (int v = kFirstPw3; v < kFirstPw3 + kNumPw3; ++v) {
+    if (!variant_supports(d, v, lay)) continue;
+    const double c = pw3_cost(d, variant(v), lay);
+    if (best_v < 0 || c < *cost) { *cost = c; best_v = v; }
+  }
+  return best_v;
+}
+
 double variant_cost(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
   const TileVariant& tv = variant(v);
+  if (tv.pw3) return variant_supports(d, v, lay) ? pw3_cost(d, tv, lay) : -1.0;
   SplitPlan p;
   if (tv.split) return split_supports(d, tv, lay, &p) ? split_cost(d, tv, lay, p) : -1.0;
   if (tv.rows) return variant_supports(d, v, lay) ? rows_cost(d, tv, lay) : -1.0;
@@ -414,6 +453,17 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
     const long groups = (long)((p.strips + tv.wn - 1) / tv.wn) * p.tiles_m;
     return groups * p.tiles_m < (1L << 32) && ((long)p.strips + 4) * p.tiles_x < (1L << 32) &&
            ((long)p.strips / p.tiles_x + 4) * p.tiles_y < (1L << 32);
+  }
+  if (tv.pw3) {
+    // 1x1 / stride 1 or 2 in an fp32 handle; sums of at least 16 terms, as the split kernel; four filters per store
+    if (!(lay.nhwc && d.dtype == CPRUNE_F32 && lay.w_rows3 && d.kh == 1 && d.kw == 1 && d.pad == 0 && d.stride <= 2)) return false;
+    if (lay.pool || (lay.cp_out & 3) || d.c_in < kSplitMinTerms) return false;
+    if (split_packed_bytes(d.c_out, lay.cp_in, 1, d.dtype, true) >= ((size_t)1 << 31)) return false;
+    // multiply-high divisions of the decode: exact while dividend x divisor < 2^32
+    long tiles_m;
+    const long groups = pw3_groups(d, tv, &tiles_m);
+    const long P = groups / tiles_m * tv.tile_p(), side = std::max(conv_out_dim(d.h, 1, d.stride, 0), conv_out_dim(d.w, 1, d.stride, 0));
+    return groups * tiles_m < (1L << 32) && P * side < (1L << 32);
   }
   if (tv.sched == -4) {
     // 3x3 / stride 1 / pad 1 on small maps (every wavefront fetches its own weights: with many pixels the
@@ -519,6 +569,27 @@ int launch_conv_dense(const cprune_conv_desc& d, const void* x, const void* w, c
     const dim3 grid((unsigned)((a.strips + tv.wn - 1) / tv.wn * a.tiles_m));
     const int rc = d.dtype == CPRUNE_F32 ? launch_conv_rows_f32(tv.patch_id, grid, s, a) :
                    d.dtype == CPRUNE_F16 ? launch_conv_rows_f16(tv.patch_id, grid, s, a) : launch_conv_rows_bf16(tv.patch_id, grid, s, a);
+    if (rc != CPRUNE_OK) return rc;
+    CPRUNE_LAUNCH_CHECK();
+    return CPRUNE_OK;
+  }
+  if (tv.pw3) {
+    Pw3Args a;
+    a.x = x; a.w = lay.w_rows3; a.w_raw = w; a.bias = bias; a.res = residual; a.y = y;
+    a.H = d.h; a.W = d.w; a.Ho = conv_out_dim(d.h, 1, d.stride, 0); a.Wo = conv_out_dim(d.w, 1, d.stride, 0);
+    a.P = d.n * a.Ho * a.Wo; a.O = d.c_out; a.Cp = lay.cp_in; a.Cop = lay.cp_out; a.stride = d.stride;
+    long tiles_m;
+    const long groups = pw3_groups(d, tv, &tiles_m);
+    const int blocks = (d.c_out + 15) / 16;
+    a.tiles_m = (int)tiles_m; a.blk_base = blocks / a.tiles_m; a.blk_rem = blocks % a.tiles_m;
+    a.rounds = (lay.cp_in + 31) / 32;
+    a.x_bytes = (unsigned)((size_t)d.n * lay.cp_in * d.h * d.w * 4);
+    a.w_bytes = (unsigned)split_packed_bytes(d.c_out, lay.cp_in, 1, d.dtype, true);
+    a.w_raw_bytes = (unsigned)((size_t)d.c_out * lay.cp_in * 4);
+    a.y_bytes = (unsigned)((size_t)a.P * lay.cp_out * 4);
+    a.magic_m = magic_for((unsigned)a.tiles_m); a.magic_wo = magic_for((unsigned)a.Wo); a.magic_ho = magic_for((unsigned)a.Ho);
+    a.act = d.act;
+    const int rc = launch_conv_pw3_f32(tv.patch_id, dim3((unsigned)groups), s, a);
     if (rc != CPRUNE_OK) return rc;
     CPRUNE_LAUNCH_CHECK();
     return CPRUNE_OK;
