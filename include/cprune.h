@@ -359,6 +359,11 @@ int cprune_net_first_layer_form(cprune_net* net, int form);
  * a forward is in flight.  cprune_net_layer_fused reports the current state (host out). */
 int cprune_net_fuse_depthwise(cprune_net* net, int layer, int enable);
 int cprune_net_layer_fused(const cprune_net* net, int layer, int* fused_out);
+/* (A 1x1 / stride 2 conv beside a 3x3 / stride 2 / pad 1 conv on the same input, as where a residual network halves its
+ * map, can run in that layer's launch: cprune_net_create decides, in a fp32 handle only by timing.  Both activations are
+ * stored as always; cprune_net_layer_fused reports 1 for the 1x1 conv and cprune_net_layer_variant -1, its time is
+ * part of the other layer's.  cprune_net_set_layer_variant on the 1x1 conv, or on the 3x3 conv with a variant of another
+ * kernel, gives each its own launch again.) */
 /* When the input of such a depthwise conv is a 1x1 / stride 1 conv that nobody else reads (the
  * expansion of an inverted-residual block of MobileNetV2 / MnasNet1.0, Sec. 4.1 and Table 1 of the
  * paper; its filters are the ones Sec. 3.5 prunes), and the 1x1

@@ -49,6 +49,8 @@ static DescKey key_of(const cprune_conv_desc& d, const ConvLayout& lay) {
 }
 static std::mutex g_cache_mutex;
 static std::map<DescKey, int> g_cache;
+// likewise the variant a pair of layers in one launch runs, or -1 where the layers apart were faster
+static std::map<std::array<int, 21>, int> g_pairs;
 
 void remember_variant(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
   std::lock_guard<std::mutex> lock(g_cache_mutex);
@@ -72,11 +74,17 @@ static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay, double 
 // layers 2.35 times as fast as the general kernel, at least 1.15 times).  fp32, against the split kernel: from 0.2 GFLOP up on maps one
 // strip wide and 0.3 on wider ones whose strips are well filled (56 of 4 x 16 columns, not 32 of 3 x 16 or, with a pool, 56 of 5 x
 // 16) and whose chunks of 32 channels are not mostly padding as well; there 1.12 times as fast on average (63 random layers of 28 to 400 us),
-// 0.95 times at worst; the layers left out by the fill alone 0.9-1.07 times, and below the lines 0.7-1.2 times.  A layer without the split kernel's copy (a smaller batch in a
+// 0.95 times at worst; the layers left out by the fill alone 0.9-1.07 times, and below the lines 0.7-1.2 times.  Stride 2 in fp32: from
+// four chunks of channels up, on maps of two strips at most, to 2 GFLOP (45 random layers: there 1.2 times as fast on average; with one to
+// three chunks 0.6-1.1 times: 18 -> 44 at 28x28, batch 2, 4.6 / 7.7 us); 16-bit data always (45 random layers: 1.99 times).  A layer without the split kernel's copy (a smaller batch in a
 // handle whose full batch runs row strips) has the general kernel's fp32 instruction in its place, and always takes them:
 // ResNet-18 built for 32, 2 and 1 images 213 -> 198 and 269 -> 190 us, VGG-16 built for 64, 8 images 173 -> 141.
 static bool rows_pay(const cprune_conv_desc& d, const ConvLayout& lay) {
   if (d.dtype != CPRUNE_F32 || !lay.w_split) return true;
+  if (d.stride == 2) {
+    const long ho = conv_out_dim(d.h, 3, 2, 1), wo = conv_out_dim(d.w, 3, 2, 1);
+    return lay.cp_in >= 112 && wo <= 32 && (lay.cp_in <= 384 || d.c_out > 16) && 18.0 * d.n * ho * wo * (double)d.c_out * d.c_in <= 2e9;
+  }
   const double flops = 18.0 * d.n * d.h * d.w * (double)d.c_out * d.c_in;
   if (d.w <= 16) return flops >= 2e8;
   const int step = lay.pool ? 12 : 14, strips = (d.w - 16 + step - 1) / step + 1;      // (as rows_tiles has them)
@@ -259,8 +267,10 @@ extern "C" int cprune_tile_variant_name(int v, int channels_last, cprune_dtype d
   else if (tv.split)
     n = snprintf(buf, buf_bytes, "conv_split_kernel<%s, %s, %d, %d, %d, %d, %d, %d>", t, channels_last ? "false" : "true", tv.wm,
                  tv.wn, tv.ks, tv.mb, tv.nb, tv.nib);
-  else if (tv.rows && channels_last && dtype == CPRUNE_F32)
+  else if (tv.rows && tv.stride == 1 && channels_last && dtype == CPRUNE_F32)
     n = snprintf(buf, buf_bytes, "conv_split_rows_kernel<%d, %d>", tv.th, tv.ks);
+  else if (tv.rows && tv.stride == 2)
+    n = snprintf(buf, buf_bytes, "conv_rows_s2_kernel<%s, %d, %d, %d>", t, tv.mb, tv.th, tv.ks);
   else if (tv.pw3)
     n = snprintf(buf, buf_bytes, "conv_pw3_kernel<%d, %d, %s>", tv.mb, tv.nb, tv.pw3 == 2 ? "true" : "false");
   else if (tv.rows)
@@ -314,6 +324,7 @@ extern "C" int cprune_select_tile(const cprune_conv_desc* desc, const void* x, c
 extern "C" void cprune_clear_tile_cache(void) {
   std::lock_guard<std::mutex> lock(g_cache_mutex);
   g_cache.clear();
+  g_pairs.clear();
 }
 
 extern "C" int cprune_cached_tile(const cprune_conv_desc* desc, int* variant_out, int* was_timed_out) {
@@ -414,6 +425,12 @@ struct NetLayer {
   int block_expand = -1;      // depthwise conv: the expansion layer that may join it and dw_reader in one kernel
   void* w_expand = nullptr;   // expansion of such a block: weights once more, in that kernel's operand order
   void* w_proj = nullptr;     // 1x1 conv that may run behind a depthwise layer in one kernel: weights in its operand order
+  int pair = -1;              // 3x3 / stride 2 conv: index of the 1x1 / stride 2 layer on the same input that runs in its launch, or -1
+  int pair_by = -1;           // that 1x1 layer: index of the 3x3 layer whose launch it runs in now, or -1
+  int pair_with = -1;         // 3x3 layer: the 1x1 layer that could run in its launch
+  int pair_variant = -1;      // ... variant of the pair at max_batch
+  std::vector<int> pair_at;   // ... and at a smaller batch (-1: not yet)
+  void* w_pair = nullptr;     // both: weights once more, as that kernel reads them
   int fuse_stem = -1;         // 3x3 conv: index of the first layer (on the image) computed inside its kernel, or -1
   int stem_reader = -1;       // first layer that may run inside the 3x3 conv stem_reader's kernel
   void* w_stem = nullptr;     // weights packed for the first-layer kernel
@@ -492,15 +509,15 @@ static ConvLayout layer_layout(const NetLayer& L) {
   return lay;
 }
 
-// 3x3 / stride 1 / pad 1 on a map of its own: what the independent-wavefront and the row-strip kernels run.
+// 3x3 / stride 1 or 2 / pad 1 on a map of its own: what the row-strip and, at stride 1, the independent-wavefront kernels run.
 static bool strips_layer(const cprune_net& net, const NetLayer& L) {
-  return L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1 && L.d.k == 3 && L.d.stride == 1 && L.d.pad == 1 && !L.map2x2 && !L.nchw_in &&
+  return L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1 && L.d.k == 3 && L.d.stride <= 2 && L.d.pad == 1 && !L.map2x2 && !L.nchw_in &&
          wave_packed_bytes(L.d.c_out, L.cp_in, net.dtype) < ((size_t)1 << 31);      // 31-bit offsets in the kernels
 }
 
 // ... on a map that the independent-wavefront kernel takes: it keeps the copy that kernel reads
 static bool wave_layer(const cprune_net& net, const NetLayer& L) {
-  return strips_layer(net, L) && L.h_in >= 3 && L.w_in >= 3 && L.h_in <= 32 && L.w_in <= 32;
+  return strips_layer(net, L) && L.d.stride == 1 && L.h_in >= 3 && L.w_in >= 3 && L.h_in <= 32 && L.w_in <= 32;
 }
 
 // The other copies of a dense layer's weights are made only for a layer that runs the kernel that reads them (while variants are
@@ -872,11 +889,43 @@ static int layer_variant_at(const cprune_net* net, NetLayer& L, const cprune_con
   return L.at_batch[n];
 }
 
+// The layout and the second layer of a pair (3x3 layer L and the 1x1 layer beside it).
+static ConvPair pair_of(const cprune_net* net, const NetLayer& L) {
+  const NetLayer& S = net->layers[L.pair_with];
+  return ConvPair{S.w_pair, S.w, S.b, S.act, S.d.c_out, S.cp_out, S.d.act};
+}
+
+static ConvLayout pair_layout(const NetLayer& L, const ConvPair* pair) {
+  ConvLayout lay = layer_layout(L);
+  lay.w_wave = lay.w_rows3 = L.w_pair;
+  lay.pair = pair;
+  return lay;
+}
+
+static int net_run_pair(cprune_net* net, NetLayer& L, int n, const void* src, hipStream_t s) {
+  const ConvPair pair = pair_of(net, L);
+  const ConvLayout lay = pair_layout(L, &pair);
+  const cprune_conv_desc d = layer_conv_desc(*net, L, n);
+  int v = L.pair_variant;
+  if (8 * n <= 7 * net->max_batch) {       // as choose_at_batch
+    if (L.pair_at.empty()) L.pair_at.assign(net->max_batch, -1);
+    if (L.pair_at[n] < 0) {
+      double cost = 0.0;
+      const int best = best_rows_variant(d, lay, &cost);
+      L.pair_at[n] = best >= 0 && cost < 0.9 * variant_cost(d, v, lay) ? best : v;
+    }
+    v = L.pair_at[n];
+  }
+  const void* res = L.d.residual >= 0 ? net->layers[L.d.residual].act : nullptr;
+  return launch_conv_dense(d, src, L.w, L.b, res, L.act, v, net->ws, s, lay);
+}
+
 static int net_run_layer(cprune_net* net, int i, int n, const void* x, void* out_override, hipStream_t s) {
   NetLayer& L = net->layers[i];
   const void* src = L.d.input < 0 ? (L.nchw_in ? x : net->x_cl) : net->layers[L.d.input].act;
   void* dst = out_override ? out_override : L.act;
-  if (L.fused_away) return CPRUNE_OK;
+  if (L.fused_away || L.pair_by >= 0) return CPRUNE_OK;
+  if (L.pair >= 0) return net_run_pair(net, L, n, src, s);
   if (L.fuse_dw >= 0) {
     // (a smaller batch of few pixel blocks runs on strips, which more wavefronts can share)
     const bool blocks = L.fuse_block < 0 && L.dw_tile == kPixelBlocks &&
@@ -967,6 +1016,100 @@ static int time_mbrow(cprune_net* net, const int* layers, int n_layers, bool str
     if (rc != CPRUNE_OK) return rc;
   }
   *low = best_low; *ks = best_ks;
+  return CPRUNE_OK;
+}
+
+static void set_pair(cprune_net* net, NetLayer& L, bool on) {
+  NetLayer& S = net->layers[L.pair_with];
+  L.pair = on ? L.pair_with : -1;
+  S.pair_by = on ? (int)(&L - net->layers.data()) : -1;
+}
+
+// Layer i, if it is the 3x3 / stride 2 / pad 1 layer that halves a residual network's map, takes the 1x1 / stride 2 layer on the same input
+// into its launch.
+static int make_pair(cprune_net* net, int i, bool tune, hipStream_t s) {
+  NetLayer& L = net->layers[i];
+  const int nl = (int)net->layers.size();
+  if (!(strips_layer(*net, L) && L.d.stride == 2 && L.d.input >= 0 && i != nl - 1 && L.cp_out == round_up_vec(L.d.c_out, net->dtype))) return CPRUNE_OK;
+  if (L.fused_away || L.fuse_dw >= 0 || L.fuse_stem >= 0) return CPRUNE_OK;
+  int with = -1;
+  for (int j = 0; j < nl - 1 && with < 0; ++j) {
+    const NetLayer& S = net->layers[j];
+    if (S.d.kind != CPRUNE_LAYER_CONV || S.d.groups != 1 || S.d.input != L.d.input || S.d.k != 1 || S.d.stride != 2 || S.d.pad != 0) continue;
+    if (S.d.residual >= 0 || S.fused_away || S.fuse_dw >= 0 || S.pair_by >= 0 || S.cp_out != round_up_vec(S.d.c_out, net->dtype)) continue;
+    if (S.h_out != L.h_out || S.w_out != L.w_out || (net->dtype == CPRUNE_F32 && S.d.c_in < 16)) continue;      // (as the other kernels on parts)
+    bool late = true;                                    // its readers come behind layer i, where it is computed
+    for (int k = 0; k <= i; ++k) late &= net->layers[k].d.input != j && net->layers[k].d.residual != j;
+    if (late) with = j;
+  }
+  if (with < 0) return CPRUNE_OK;
+  NetLayer& S = net->layers[with];
+  const bool f32 = net->dtype == CPRUNE_F32;
+  const size_t b1 = split_packed_bytes(S.d.c_out, S.cp_in, 1, net->dtype, true);
+  const size_t b3 = f32 ? split_packed_bytes(L.d.c_out, L.cp_in, 9, net->dtype, true) : wave_packed_bytes(L.d.c_out, L.cp_in, net->dtype);
+  if (b1 >= ((size_t)1 << 31) || b3 >= ((size_t)1 << 31)) return CPRUNE_OK;
+  L.pair_with = with;
+  const cprune_conv_desc d = layer_conv_desc(*net, L, net->max_batch);
+  std::array<int, 21> key;
+  {
+    const DescKey k = key_of(d, layer_layout(L));
+    std::copy(k.begin(), k.end(), key.begin());
+    key[18] = S.d.c_out; key[19] = S.d.act; key[20] = S.cp_out;
+  }
+  int known = -2;
+  if (tune) {
+    std::lock_guard<std::mutex> lock(g_cache_mutex);
+    auto it = g_pairs.find(key);
+    if (it != g_pairs.end()) known = it->second;
+  }
+  if (known == -1 || (!tune && !(L.variant >= 0 && variant(L.variant).rows))) return CPRUNE_OK;
+  CPRUNE_HIP_TRY(hipMalloc(&S.w_pair, b1));
+  net->allocs.push_back(S.w_pair);
+  CPRUNE_HIP_TRY(hipMalloc(&L.w_pair, b3));
+  net->allocs.push_back(L.w_pair);
+  int rc = launch_pack_split(S.w, S.d.c_out, S.cp_in, 1, 1, net->dtype, S.w_pair, s, true);
+  if (rc == CPRUNE_OK) rc = f32 ? launch_pack_split(L.w, L.d.c_out, L.cp_in, 9, 1, net->dtype, L.w_pair, s, true)
+                                : launch_repack_wave(L.w, L.d.c_out, L.cp_in, net->dtype, L.w_pair, s);
+  if (rc != CPRUNE_OK) return rc;
+  const ConvPair pair = pair_of(net, L);
+  const ConvLayout lay = pair_layout(L, &pair);
+  int best_v = known >= 0 ? known : -1;
+  if (known < 0 && !tune) {
+    double cost = 0.0;
+    best_v = best_rows_variant(d, lay, &cost);
+  } else if (known < 0) {
+    const int apart[2] = {with, i};
+    float best = 0.f;
+    rc = time_layers(net, apart, 2, net->max_batch, net->x_cl, s, &best);
+    std::vector<std::pair<float, int>> timed;
+    auto time_pair = [&](int v, float* ms) -> int {
+      L.pair_variant = v;
+      set_pair(net, L, true);
+      const int r = time_layers(net, &i, 1, net->max_batch, net->x_cl, s, ms);
+      set_pair(net, L, false);
+      return r;
+    };
+    for (int v = 0; v < num_variants() && rc == CPRUNE_OK; ++v) {
+      if (!(variant(v).rows && variant(v).stride == 2) || !variant_supports(d, v, lay)) continue;
+      timed.emplace_back(0.f, v);
+      rc = time_pair(v, &timed.back().first);
+    }
+    std::sort(timed.begin(), timed.end());
+    for (size_t k = 0; k < timed.size() && k < 3 && rc == CPRUNE_OK; ++k) {      // the fastest once more, and the layers apart between them
+      float ms = 0.f, two = 0.f;
+      rc = time_pair(timed[k].second, &ms);
+      timed[k].first = std::min(timed[k].first, ms);
+      if (rc == CPRUNE_OK) rc = time_layers(net, apart, 2, net->max_batch, net->x_cl, s, &two);
+      if (rc == CPRUNE_OK) best = std::min(best, two);
+    }
+    for (const auto& t : timed)
+      if (t.first < best) { best = t.first; best_v = t.second; }
+    if (rc != CPRUNE_OK) return rc;
+    std::lock_guard<std::mutex> lock(g_cache_mutex);
+    g_pairs[key] = best_v;
+  }
+  L.pair_variant = best_v;
+  if (best_v >= 0) set_pair(net, L, true);
   return CPRUNE_OK;
 }
 
@@ -1394,6 +1537,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     if (form) P.variant = -1;
     if (form == 2) E.variant = -1;
   }
+  for (int i = 0; i < n_layers && rc == CPRUNE_OK; ++i) rc = make_pair(net, i, tune != 0, s);
   if (rc == CPRUNE_OK) {
     hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) { set_last_hip_error(e); rc = CPRUNE_ERR_DEVICE; }
@@ -1462,7 +1606,8 @@ extern "C" int cprune_net_layer_times(cprune_net* net, const void* x, int n, int
   for (int i = 0; i < nl && rc == CPRUNE_OK; ++i) {
     ms_out[i] = 0.0f;
     rc = net_run_layer(net, i, n, x, nullptr, s);   // untimed first run
-    if (rc != CPRUNE_OK || net->layers[i].alias || net->layers[i].fused_away || net->layers[i].in_producer) continue;
+    if (rc != CPRUNE_OK || net->layers[i].alias || net->layers[i].fused_away || net->layers[i].in_producer ||
+        net->layers[i].pair_by >= 0) continue;
     hipError_t e = hipEventRecord(e0, s);
     for (int it = 0; it < iters && rc == CPRUNE_OK && e == hipSuccess; ++it) rc = net_run_layer(net, i, n, x, nullptr, s);
     if (e == hipSuccess) e = hipEventRecord(e1, s);
@@ -1498,7 +1643,8 @@ extern "C" int cprune_net_output_shape(const cprune_net* net, int* c_out, int* h
 
 extern "C" int cprune_net_layer_variant(const cprune_net* net, int layer, int* variant_out) {
   if (!net || !variant_out || layer < 0 || layer >= (int)net->layers.size()) return CPRUNE_ERR_INVALID_ARG;
-  *variant_out = net->layers[layer].variant;
+  const NetLayer& L = net->layers[layer];
+  *variant_out = L.pair_by >= 0 ? -1 : L.pair >= 0 ? L.pair_variant : L.variant;
   return CPRUNE_OK;
 }
 
@@ -1663,7 +1809,7 @@ extern "C" int cprune_net_block_form(cprune_net* net, int layer, int form, int t
 
 extern "C" int cprune_net_layer_fused(const cprune_net* net, int layer, int* fused_out) {
   if (!net || !fused_out || layer < 0 || layer >= (int)net->layers.size()) return CPRUNE_ERR_INVALID_ARG;
-  *fused_out = net->layers[layer].fused_away ? 1 : 0;
+  *fused_out = net->layers[layer].fused_away || net->layers[layer].pair_by >= 0 ? 1 : 0;
   return CPRUNE_OK;
 }
 
@@ -1672,6 +1818,18 @@ extern "C" int cprune_net_set_layer_variant(cprune_net* net, int layer, int vari
   NetLayer& L = net->layers[layer];
   if (!(L.d.kind == CPRUNE_LAYER_FC || (L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1))) return CPRUNE_ERR_INVALID_ARG;
   if (L.fuse_dw >= 0 || L.fuse_stem >= 0 || L.fused_away) return CPRUNE_ERR_INVALID_ARG;   // runs inside a fused kernel: no variants
+  if (L.pair >= 0) {
+    // a variant of the kernel that runs pairs keeps the pair; any other means a launch of its own
+    const ConvPair pair = pair_of(net, L);
+    if (variant >= 0 && variant < num_variants() && cprune::variant(variant).rows &&
+        variant_supports(layer_conv_desc(*net, L, net->max_batch), variant, pair_layout(L, &pair))) {
+      CPRUNE_HIP_TRY(hipDeviceSynchronize());
+      drop_graphs(net);
+      L.pair_variant = variant;
+      L.pair_at.clear();
+      return CPRUNE_OK;
+    }
+  }
   if (L.stem) L.stem = false;                          // a pinned variant means the general kernel
   if (L.stem7) {
     if (L.pool3 >= 0) net->layers[L.pool3].in_producer = false;
@@ -1686,6 +1844,8 @@ extern "C" int cprune_net_set_layer_variant(cprune_net* net, int layer, int vari
   const int rc = pack_for(net, L, variant, nullptr);
   if (rc != CPRUNE_OK) return rc;
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
+  if (L.pair >= 0) set_pair(net, L, false);
+  if (L.pair_by >= 0) set_pair(net, net->layers[L.pair_by], false);
   drop_copies(net, L, variant);
   L.variant = variant;
   L.timed = true;

@@ -70,6 +70,14 @@ const TileVariant& variant(int id);
 // boundary's layout).  nhwc = 1: channels-last inside a network handle, channel strides
 // cp_in / cp_out in elements (counts rounded up to one 16-byte vector, except a final
 // dense output), weights [c_out][kh][kw][cp_in].
+// A 1x1 / stride 2 layer that runs in the launch of a 3x3 / stride 2 / pad 1 layer on the same input (row-strip kernel at stride 2).
+struct ConvPair {
+  const void* w;        // launch_pack_split, whole chunks
+  const void* w_raw;    // [o][cp_in]
+  const float* bias;
+  void* y;
+  int c_out, cp_out, act;
+};
 struct ConvLayout {
   int nhwc = 0;
   int cp_in = 0;
@@ -86,6 +94,7 @@ struct ConvLayout {
                                  // layout packs its weights into the caller's scratch
   const void* w_rows3 = nullptr; // channels-last fp32 3x3 / stride 1 / pad 1, or 1x1: cut and packed in whole chunks of 32 channels for
                                  // the row-strip kernel (the 1x1 kernel), which runs fp32 data only where this is set
+  const ConvPair* pair = nullptr;
   int pool = 0;  // 1: channels-last 3x3 layer with a 2x2/2 max-pool fused behind the activation (patch kernels);
                  // 2: rows are (channel, position of a 2x2 map) and each group of four rows is reduced to its
                  //    maximum behind the activation; cp_out is the stride of the pooled output

@@ -8,6 +8,7 @@
 #include "conv_split_kernel.hpp"
 #include "conv_rows_kernel.hpp"
 #include "conv_pw3_kernel.hpp"
+#include "conv_rows_s2_kernel.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -237,11 +238,12 @@ int launch_split_conv(const cprune_conv_desc& d, const TileVariant& tv, const Co
 constexpr int kFirstSplit = kNumTiles * kNumScheds + kNumPatch + kNumPatch32 + kNumKsplit + kNumPw + kNumWave + kNumPatchS2;
 constexpr int kFirstRows = kFirstSplit + kNumSplit;
 constexpr int kFirstPw3 = kFirstRows + kNumRows;
-int num_variants() { return kFirstPw3 + kNumPw3; }
+constexpr int kFirstRowsS2 = kFirstPw3 + kNumPw3;
+int num_variants() { return kFirstRowsS2 + kNumRowsS2; }
 
 namespace {
 struct VariantTable {
-  TileVariant table[kFirstPw3 + kNumPw3];
+  TileVariant table[kFirstRowsS2 + kNumRowsS2];
   VariantTable() {
 #define CPRUNE_PATCH_ROW(ID, MB_, TH_, TW_, NI_, KQ_, KS_)                                 \
     {                                                                         \
@@ -315,6 +317,14 @@ struct VariantTable {
     }
     CPRUNE_PW3_LIST(CPRUNE_PW3_ROW)
 #undef CPRUNE_PW3_ROW
+#define CPRUNE_ROWS_S2_ROW(ID, MB_, R_, KS_)                                               \
+    {                                                                                      \
+      TileVariant& kv = table[kFirstRowsS2 + ID];                                          \
+      kv.wm = 1; kv.wn = KS_ >= 4 ? 1 : 4 / KS_; kv.mb = MB_; kv.nb = R_; kv.kq = 1; kv.sched = -1; kv.rows = 1; \
+      kv.th = R_; kv.tw = 16; kv.patch_id = ID; kv.ks = KS_; kv.stride = 2;                \
+    }
+    CPRUNE_ROWS_S2_LIST(CPRUNE_ROWS_S2_ROW)
+#undef CPRUNE_ROWS_S2_ROW
     for (int t = 0; t < kNumTiles; ++t)
       for (int s = 0; s < kNumScheds; ++s) {
         table[t * kNumScheds + s] = kTiles[t];
@@ -349,18 +359,20 @@ int best_split_variant(const cprune_conv_desc& d, const ConvLayout& lay, double*
   return best_v;
 }
 
-// Strips of the row-strip kernel on a layer: 16 columns x th rows of one image, or of two (four) images of at most 8 (4) columns.
+// Strips of the row-strip kernel on a layer: 16 columns x th rows of one image's output, or of two (four) images of at most 8 (4)
+// columns.
 static RowsArgs rows_tiles(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay) {
   RowsArgs a;
-  a.lane_shift = d.w <= 4 ? 2 : d.w <= 8 ? 3 : 4;
+  a.H = conv_out_dim(d.h, 3, tv.stride, 1); a.W = conv_out_dim(d.w, 3, tv.stride, 1);
+  a.lane_shift = a.W <= 4 ? 2 : a.W <= 8 ? 3 : 4;
   const int ipt = 16 >> a.lane_shift;
-  a.tiles_x = (d.w + 15) / 16;
+  a.tiles_x = (a.W + 15) / 16;
   a.step = 16;
-  if (d.dtype == CPRUNE_F32 && a.tiles_x > 1) {
-    a.step = lay.pool ? 12 : 14;
-    a.tiles_x = (d.w - 16 + a.step - 1) / a.step + 1;
+  if (a.tiles_x > 1 && (tv.stride == 2 || d.dtype == CPRUNE_F32)) {
+    a.step = tv.stride == 2 ? 15 : lay.pool ? 12 : 14;
+    a.tiles_x = (a.W - 16 + a.step - 1) / a.step + 1;
   }
-  a.tiles_y = (d.h + tv.th - 1) / tv.th;
+  a.tiles_y = (a.H + tv.th - 1) / tv.th;
   a.tiles_m = (d.c_out + tv.tile_m() - 1) / tv.tile_m();
   a.strips = (d.n + ipt - 1) / ipt * a.tiles_y * a.tiles_x;
   return a;
@@ -375,14 +387,22 @@ static double rows_cost(const cprune_conv_desc& d, const TileVariant& tv, const 
   const bool f32 = d.dtype == CPRUNE_F32;
   const double waves = (double)p.strips * p.tiles_m * tv.ks;
   const double chunks = ((lay.cp_in + 31) / 32 + tv.ks - 1) / tv.ks;
-  const double mma = (f32 ? 864.0 : 144.0) * tv.mb * std::min(tv.th, d.h);
+  const double mma = (f32 ? 864.0 : 144.0) * tv.mb * std::min(tv.th, p.H);
+  if (tv.stride == 2) {
+    // every row is two operands (fp32: of two loads, and cut), weights are shared by the work-group's strips; a kilobyte each from the
+    // vector cache, which four SIMDs share at 64 bytes a clock
+    const double rows = 2 * std::min(tv.th, p.H) + 1, parts = f32 ? 3.0 : 1.0;
+    const double load = (rows * (f32 ? 4.0 : 2.0) + 9.0 * parts * tv.mb / tv.wn) * 64.0, cut = f32 ? 352.0 * rows : 0.0;
+    return std::max(chunks * (mma + cut + (f32 ? 1500.0 : 500.0)), waves / 1024.0 * chunks * (std::max(mma, load) + 0.4 * cut + 300.0)) +
+           (tv.ks > 1 && !f32 ? 160.0 * tv.mb * tv.th : 0.0) + 500.0 * std::ceil(waves / 1024.0);
+  }
   return std::max(chunks * (mma + (f32 ? 4000.0 : 500.0)), waves / 1024.0 * chunks * (mma + 300.0)) +
          (tv.ks > 1 && !f32 ? 160.0 * tv.mb * tv.th : 0.0) + 500.0 * std::ceil(waves / 1024.0);
 }
 
 int best_rows_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost) {
   int best_v = -1;
-  for (int v = kFirstRows; v < kFirstRows + kNumRows; ++v) {
+  for (int v = d.stride == 1 ? kFirstRows : kFirstRowsS2; v < (d.stride == 1 ? kFirstRows + kNumRows : kFirstRowsS2 + kNumRowsS2); ++v) {
     if (!variant_supports(d, v, lay)) continue;
     const double c = rows_cost(d, variant(v), lay);
     if (best_v < 0 || c < *cost) { *cost = c; best_v = v; }
@@ -437,10 +457,11 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
     return split_supports(d, tv, lay, &p);
   }
   if (tv.rows) {
-    // 3x3 / stride 1 / pad 1 in a handle; wavefronts share a strip only while there is a chunk for each, and not where strips
+    // 3x3 / pad 1 at the variant's stride in a handle; wavefronts share a strip only while there is a chunk for each, and not where strips
     // alone fill the chip several times
-    if (!(lay.nhwc && (d.dtype == CPRUNE_F32 ? lay.w_rows3 && tv.mb == 1 : lay.w_wave != nullptr) && d.kh == 3 && d.kw == 3 && d.stride == 1 && d.pad == 1)) return false;
-    if (lay.pool == 2 || (lay.pool && ((d.h | d.w) & 1))) return false;
+    if (!(lay.nhwc && (d.dtype == CPRUNE_F32 ? lay.w_rows3 && tv.mb == 1 && (tv.stride == 1 || tv.th <= 4) : lay.w_wave != nullptr) && d.kh == 3 && d.kw == 3 &&
+          d.stride == tv.stride && d.pad == 1)) return false;
+    if (lay.pool == 2 || (lay.pool && (((d.h | d.w) & 1) || tv.stride != 1))) return false;
     if (lay.cp_out & 3) return false;      // four filters per store: not a dense map of logits
     const RowsArgs p = rows_tiles(d, tv, lay);
     const long waves = (long)p.strips * p.tiles_m;
@@ -450,8 +471,9 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
     }
     if (tv.ks > 1 && (tv.ks > (lay.cp_in + 31) / 32 || waves * tv.ks > 8192)) return false;
     // multiply-high divisions of the tile decode: exact while groups x divisor < 2^32
-    const long groups = (long)((p.strips + tv.wn - 1) / tv.wn) * p.tiles_m;
-    return groups * p.tiles_m < (1L << 32) && ((long)p.strips + 4) * p.tiles_x < (1L << 32) &&
+    const long tiles_m = p.tiles_m + (lay.pair ? (lay.pair->c_out + tv.tile_m() - 1) / tv.tile_m() : 0);
+    const long groups = (long)((p.strips + tv.wn - 1) / tv.wn) * tiles_m;
+    return groups * tiles_m < (1L << 32) && ((long)p.strips + 4) * p.tiles_x < (1L << 32) &&
            ((long)p.strips / p.tiles_x + 4) * p.tiles_y < (1L << 32);
   }
   if (tv.pw3) {
@@ -551,10 +573,11 @@ int launch_conv_dense(const cprune_conv_desc& d, const void* x, const void* w, c
   const size_t es = dtype_size(d.dtype);
   if (tv.split) return launch_split_conv(d, tv, lay, x, w, bias, residual, y, ws, s);
   if (tv.rows) {
-    RowsArgs a = rows_tiles(d, tv, lay);
+    RowsS2Args a;
+    (RowsArgs&)a = rows_tiles(d, tv, lay);
     a.x = x; a.w = lay.w_wave; a.bias = bias; a.res = residual; a.y = y;
-    a.N = d.n; a.H = d.h; a.W = d.w; a.O = d.c_out; a.Cp = lay.cp_in; a.Cop = lay.cp_out;
-    a.magic_m = magic_for((unsigned)a.tiles_m); a.magic_x = magic_for((unsigned)a.tiles_x); a.magic_y = magic_for((unsigned)a.tiles_y);
+    a.N = d.n; a.O = d.c_out; a.Cp = lay.cp_in; a.Cop = lay.cp_out;
+    a.Hi = d.h; a.Wi = d.w;
     a.x_bytes = (unsigned)((size_t)d.n * lay.cp_in * d.h * d.w * es);
     a.w_bytes = (unsigned)wave_packed_bytes(d.c_out, lay.cp_in, d.dtype);
     if (d.dtype == CPRUNE_F32) {
@@ -563,12 +586,27 @@ int launch_conv_dense(const cprune_conv_desc& d, const void* x, const void* w, c
     }
     a.w_raw = w;
     a.w_raw_bytes = (unsigned)((size_t)d.c_out * 9 * lay.cp_in * es);
-    a.y_bytes = (unsigned)((size_t)d.n * lay.cp_out * d.h * d.w * es);
+    a.y_bytes = (unsigned)((size_t)d.n * lay.cp_out * a.H * a.W * es);
     a.nchunk = (lay.cp_in + 31) / 32;
     a.act = d.act; a.pool = lay.pool;
+    a.tiles_m1 = a.tiles_m;
+    if (lay.pair) {
+      const ConvPair& q = *lay.pair;
+      a.tiles_m += (q.c_out + tv.tile_m() - 1) / tv.tile_m();
+      a.w2 = q.w; a.w2_raw = q.w_raw; a.bias2 = q.bias; a.y2 = q.y; a.O2 = q.c_out; a.Cop2 = q.cp_out; a.act2 = q.act;
+      a.w2_bytes = (unsigned)split_packed_bytes(q.c_out, lay.cp_in, 1, d.dtype, true);
+      a.w2_raw_bytes = (unsigned)((size_t)q.c_out * lay.cp_in * es);
+      a.y2_bytes = (unsigned)((size_t)d.n * q.cp_out * a.H * a.W * es);
+    }
+    a.magic_m = magic_for((unsigned)a.tiles_m); a.magic_x = magic_for((unsigned)a.tiles_x); a.magic_y = magic_for((unsigned)a.tiles_y);
     const dim3 grid((unsigned)((a.strips + tv.wn - 1) / tv.wn * a.tiles_m));
-    const int rc = d.dtype == CPRUNE_F32 ? launch_conv_rows_f32(tv.patch_id, grid, s, a) :
-                   d.dtype == CPRUNE_F16 ? launch_conv_rows_f16(tv.patch_id, grid, s, a) : launch_conv_rows_bf16(tv.patch_id, grid, s, a);
+    int rc;
+    if (tv.stride == 2)
+      rc = d.dtype == CPRUNE_F32 ? launch_conv_rows_s2_f32(tv.patch_id, grid, s, a) :
+           d.dtype == CPRUNE_F16 ? launch_conv_rows_s2_f16(tv.patch_id, grid, s, a) : launch_conv_rows_s2_bf16(tv.patch_id, grid, s, a);
+    else
+      rc = d.dtype == CPRUNE_F32 ? launch_conv_rows_f32(tv.patch_id, grid, s, a) :
+           d.dtype == CPRUNE_F16 ? launch_conv_rows_f16(tv.patch_id, grid, s, a) : launch_conv_rows_bf16(tv.patch_id, grid, s, a);
     if (rc != CPRUNE_OK) return rc;
     CPRUNE_LAUNCH_CHECK();
     return CPRUNE_OK;

@@ -33,11 +33,11 @@ struct RowsArgs {
   const float* bias;
   const void* res;
   void* y;              // [n][h][w][cop], pooled: [n][h / 2][w / 2][cop]
-  int N, H, W, O, Cp, Cop;
+  int N, H, W, O, Cp, Cop;         // H, W: the output map
   int tiles_y, tiles_x, tiles_m;   // strips of a map, filter tiles
   int strips;                      // of the whole batch
   int lane_shift;                  // lanes per image: 1 << lane_shift
-  int step;                        // columns from strip to strip: 16, or 14 (12 with a pool) where strips overlap (fp32)
+  int step;                        // columns from strip to strip: 16, or 14 (12 with a pool) where strips overlap (fp32), 15 at stride 2
   unsigned magic_m, magic_x, magic_y;
   unsigned x_bytes, w_bytes, y_bytes;
   int nchunk;                      // chunks of 32 channels
@@ -87,8 +87,9 @@ __device__ __forceinline__ RowsAt rows_at(const RowsArgs& a) {
   p.cx = p.tx * a.step + p.lr;
   p.live = strip < a.strips;
   p.col_ok = p.live & (p.img < a.N) & (p.cx < a.W);
-  const int margin = (16 - a.step) >> 1;       // columns whose neighbours, or pool windows, lie in the next strip
-  p.out_ok = p.col_ok & ((p.tx == 0) | (p.lr >= margin)) & ((p.tx == a.tiles_x - 1) | (p.lr < 16 - margin));
+  // columns whose neighbours, or pool windows, lie in the strip before and behind (at stride 2 only the one before is missed)
+  const int before = (17 - a.step) >> 1, behind = (16 - a.step) >> 1;
+  p.out_ok = p.col_ok & ((p.tx == 0) | (p.lr >= before)) & ((p.tx == a.tiles_x - 1) | (p.lr < 16 - behind));
   return p;
 }
 
