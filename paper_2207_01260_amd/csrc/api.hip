@@ -70,7 +70,7 @@ static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay, double 
   return lay.nhwc || 2.0 * (double)d.n * ho * wo * d.c_out * d.c_in * d.kh * d.kw >= line;
 }
 
-// Whether an untimed layer takes the row-strip kernel where it runs (3x3 layers of a handle).  16-bit data: always (on 72 random
+// Whether an untimed layer takes the row-strip kernel where it runs (3x3 layers).  In the boundary's layout: see there; in a handle, 16-bit data: always (on 72 random
 // layers 2.35 times as fast as the general kernel, at least 1.15 times).  fp32, against the split kernel: from 0.2 GFLOP up on maps one
 // strip wide and 0.3 on wider ones whose strips are well filled (56 of 4 x 16 columns, not 32 of 3 x 16 or, with a pool, 56 of 5 x
 // 16) and whose chunks of 32 channels are not mostly padding as well; there 1.12 times as fast on average (63 random layers of 28 to 400 us),
@@ -80,6 +80,14 @@ static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay, double 
 // handle whose full batch runs row strips) has the general kernel's fp32 instruction in its place, and always takes them:
 // ResNet-18 built for 32, 2 and 1 images 213 -> 198 and 269 -> 190 us, VGG-16 built for 64, 8 images 173 -> 141.
 static bool rows_pay(const cprune_conv_desc& d, const ConvLayout& lay) {
+  if (!lay.nhwc) {
+    // no more than 5.5 GFLOP (45 -> 364 at 42x42, batch 29, fp32 105 / 121 us; in 16-bit data 10 from 64 channels up: 105 -> 60 at 43x43, batch
+    // 30, bf16 26 / 20), few channels (fp32 4 -> 110 at 44x44, batch 5, 7.9 / 9.6), or, in fp32, a long chain of chunks under a small layer (247 ->
+    // 13 at 8x8, batch 29, 13.8 / 15.6).  130 random layers a type: the untimed choice is 1.06 times the time of the timed one on average.
+    const double flops = 18.0 * d.n * d.h * d.w * (double)d.c_out * d.c_in;
+    if (d.dtype != CPRUNE_F32) return d.c_in >= 4 && flops <= (d.c_in >= 64 ? 1e10 : 5.5e9);
+    return d.c_in >= 8 && flops <= 5.5e9 && ((d.c_in + 63) / 64 <= 3 || flops >= 4e8);
+  }
   if (d.dtype != CPRUNE_F32 || !lay.w_split) return true;
   if (d.stride == 2) {
     const long ho = conv_out_dim(d.h, 3, 2, 1), wo = conv_out_dim(d.w, 3, 2, 1);
@@ -267,8 +275,10 @@ extern "C" int cprune_tile_variant_name(int v, int channels_last, cprune_dtype d
   else if (tv.split)
     n = snprintf(buf, buf_bytes, "conv_split_kernel<%s, %s, %d, %d, %d, %d, %d, %d>", t, channels_last ? "false" : "true", tv.wm,
                  tv.wn, tv.ks, tv.mb, tv.nb, tv.nib);
-  else if (tv.rows && tv.stride == 1 && channels_last && dtype == CPRUNE_F32)
+  else if (tv.rows == 1 && tv.stride == 1 && channels_last && dtype == CPRUNE_F32)
     n = snprintf(buf, buf_bytes, "conv_split_rows_kernel<%d, %d>", tv.th, tv.ks);
+  else if (tv.rows == 2)
+    n = snprintf(buf, buf_bytes, "conv_rows_nchw_kernel<%s, %d, %d, %d>", t, tv.mb, tv.th, tv.ks);
   else if (tv.rows && tv.stride == 2)
     n = snprintf(buf, buf_bytes, "conv_rows_s2_kernel<%s, %d, %d, %d>", t, tv.mb, tv.th, tv.ks);
   else if (tv.pw3)

@@ -48,7 +48,7 @@ struct TileVariant {
   int ks = 1;     // patch kernels on 16x16 blocks: wave groups per tile; split kernel: wavefronts that share a block
   int kwaves = 0; // reduction-split kernel: wavefronts that share one tile's reduction (patch_id indexes its list)
   int split = 0;  // 1 (with sched = -1): split kernel, any window and stride, fp32 as three bf16 parts
-  int rows = 0;   // 1 (with sched = -1): row-strip kernel, 3x3 layers of a handle; th = rows of a strip, ks = wavefronts that
+  int rows = 0;   // 1 (with sched = -1): row-strip kernel, 3x3 layers of a handle (2: in the boundary's layout); th = rows of a strip, ks = wavefronts that
                   // share one (patch_id indexes its list)
   int pw3 = 0;    // 1, 2 (deep) (with sched = -1): 1x1 kernel on three 16-bit parts, fp32 layers of a handle (patch_id indexes its list)
   int nib = 0;    // split kernel: staging items per thread (patch_id indexes its list)

@@ -9,6 +9,7 @@
 #include "conv_rows_kernel.hpp"
 #include "conv_pw3_kernel.hpp"
 #include "conv_rows_s2_kernel.hpp"
+#include "conv_rows_nchw_kernel.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -239,11 +240,12 @@ constexpr int kFirstSplit = kNumTiles * kNumScheds + kNumPatch + kNumPatch32 + k
 constexpr int kFirstRows = kFirstSplit + kNumSplit;
 constexpr int kFirstPw3 = kFirstRows + kNumRows;
 constexpr int kFirstRowsS2 = kFirstPw3 + kNumPw3;
-int num_variants() { return kFirstRowsS2 + kNumRowsS2; }
+constexpr int kFirstRowsNchw = kFirstRowsS2 + kNumRowsS2;
+int num_variants() { return kFirstRowsNchw + kNumRowsNchw; }
 
 namespace {
 struct VariantTable {
-  TileVariant table[kFirstRowsS2 + kNumRowsS2];
+  TileVariant table[kFirstRowsNchw + kNumRowsNchw];
   VariantTable() {
 #define CPRUNE_PATCH_ROW(ID, MB_, TH_, TW_, NI_, KQ_, KS_)                                 \
     {                                                                         \
@@ -325,6 +327,14 @@ struct VariantTable {
     }
     CPRUNE_ROWS_S2_LIST(CPRUNE_ROWS_S2_ROW)
 #undef CPRUNE_ROWS_S2_ROW
+#define CPRUNE_ROWS_NCHW_ROW(ID, MB_, R_, KS_)                                             \
+    {                                                                                      \
+      TileVariant& kv = table[kFirstRowsNchw + ID];                                        \
+      kv.wm = 1; kv.wn = 4 / KS_; kv.mb = MB_; kv.nb = R_; kv.kq = 1; kv.sched = -1; kv.rows = 2; \
+      kv.th = R_; kv.tw = 16; kv.patch_id = ID; kv.ks = KS_;                               \
+    }
+    CPRUNE_ROWS_NCHW_LIST(CPRUNE_ROWS_NCHW_ROW)
+#undef CPRUNE_ROWS_NCHW_ROW
     for (int t = 0; t < kNumTiles; ++t)
       for (int s = 0; s < kNumScheds; ++s) {
         table[t * kNumScheds + s] = kTiles[t];
@@ -368,7 +378,7 @@ static RowsArgs rows_tiles(const cprune_conv_desc& d, const TileVariant& tv, con
   const int ipt = 16 >> a.lane_shift;
   a.tiles_x = (a.W + 15) / 16;
   a.step = 16;
-  if (a.tiles_x > 1 && (tv.stride == 2 || d.dtype == CPRUNE_F32)) {
+  if (a.tiles_x > 1 && (tv.stride == 2 || tv.rows == 2 || d.dtype == CPRUNE_F32)) {
     a.step = tv.stride == 2 ? 15 : lay.pool ? 12 : 14;
     a.tiles_x = (a.W - 16 + a.step - 1) / a.step + 1;
   }
@@ -385,6 +395,15 @@ static RowsArgs rows_tiles(const cprune_conv_desc& d, const TileVariant& tv, con
 static double rows_cost(const cprune_conv_desc& d, const TileVariant& tv, const ConvLayout& lay) {
   const RowsArgs p = rows_tiles(d, tv, lay);
   const bool f32 = d.dtype == CPRUNE_F32;
+  if (tv.rows == 2) {
+    // in the boundary's layout: a chunk of a wavefront alone on its SIMD, and of one among many (from timings of all variants on 60
+    // random layers a type)
+    const double chunks = (d.c_in + 31) / 32, turns = std::ceil(chunks / tv.ks), r = tv.th, mb = tv.mb;
+    const double alone = f32 ? 1800.0 * r + 2200.0 : r * (150.0 + 850.0 * mb) + 600.0;
+    const double busy = f32 ? 1250.0 * r + 3300.0 : (r * (850.0 * mb - 250.0) + 1250.0) * (tv.ks == 4 ? 1.5 : 1.0);
+    const double load = (double)p.strips * p.tiles_m * tv.ks / 1024.0;      // wavefronts of a SIMD
+    return std::max(turns * alone, (load < 4.0 ? std::ceil(load) : load + 0.5) * turns * busy) + (tv.ks > 1 ? 1200.0 : 0.0);
+  }
   const double waves = (double)p.strips * p.tiles_m * tv.ks;
   const double chunks = ((lay.cp_in + 31) / 32 + tv.ks - 1) / tv.ks;
   const double mma = (f32 ? 864.0 : 144.0) * tv.mb * std::min(tv.th, p.H);
@@ -402,7 +421,9 @@ static double rows_cost(const cprune_conv_desc& d, const TileVariant& tv, const 
 
 int best_rows_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost) {
   int best_v = -1;
-  for (int v = d.stride == 1 ? kFirstRows : kFirstRowsS2; v < (d.stride == 1 ? kFirstRows + kNumRows : kFirstRowsS2 + kNumRowsS2); ++v) {
+  const int first = !lay.nhwc ? kFirstRowsNchw : d.stride == 1 ? kFirstRows : kFirstRowsS2;
+  const int count = !lay.nhwc ? kNumRowsNchw : d.stride == 1 ? kNumRows : kNumRowsS2;
+  for (int v = first; v < first + count; ++v) {
     if (!variant_supports(d, v, lay)) continue;
     const double c = rows_cost(d, variant(v), lay);
     if (best_v < 0 || c < *cost) { *cost = c; best_v = v; }
@@ -457,8 +478,17 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
     return split_supports(d, tv, lay, &p);
   }
   if (tv.rows) {
-    // 3x3 / pad 1 at the variant's stride in a handle; wavefronts share a strip only while there is a chunk for each, and not where strips
+    // 3x3 / pad 1 at the variant's stride in a handle, or (rows = 2) at stride 1 in the boundary's layout; wavefronts share a strip only while there is a chunk for each, and not where strips
     // alone fill the chip several times
+    if (tv.rows == 2) {
+      if (lay.nhwc || lay.nhwc_out || lay.pool || !(d.kh == 3 && d.kw == 3 && d.stride == 1 && d.pad == 1)) return false;
+      const RowsArgs p = rows_tiles(d, tv, lay);
+      const long groups = (long)((p.strips + tv.wn - 1) / tv.wn) * p.tiles_m;
+      if (d.dtype == CPRUNE_F32 && ((long)d.c_in * 9 < kSplitMinTerms || tv.mb > 1 || tv.th > 6 || tv.ks > 2)) return false;
+      if (tv.ks > 1 && tv.ks > (d.c_in + 31) / 32) return false;
+      return groups * p.tiles_m < (1L << 32) && ((long)p.strips + 4) * p.tiles_x < (1L << 32) &&
+             ((long)p.strips / p.tiles_x + 4) * p.tiles_y < (1L << 32);
+    }
     if (!(lay.nhwc && (d.dtype == CPRUNE_F32 ? lay.w_rows3 && tv.mb == 1 && (tv.stride == 1 || tv.th <= 4) : lay.w_wave != nullptr) && d.kh == 3 && d.kw == 3 &&
           d.stride == tv.stride && d.pad == 1)) return false;
     if (lay.pool == 2 || (lay.pool && (((d.h | d.w) & 1) || tv.stride != 1))) return false;
@@ -575,6 +605,22 @@ int launch_conv_dense(const cprune_conv_desc& d, const void* x, const void* w, c
   if (tv.rows) {
     RowsS2Args a;
     (RowsArgs&)a = rows_tiles(d, tv, lay);
+    if (tv.rows == 2) {
+      a.x = x; a.w = w; a.bias = bias; a.res = residual; a.y = y;
+      a.N = d.n; a.O = d.c_out; a.Cp = d.c_in; a.Cop = d.c_out;
+      a.x_bytes = (unsigned)((size_t)d.n * d.c_in * d.h * d.w * es);
+      a.w_bytes = (unsigned)((size_t)d.c_out * d.c_in * 9 * es);
+      a.y_bytes = (unsigned)((size_t)d.n * d.c_out * d.h * d.w * es);
+      a.w_raw = nullptr; a.w_raw_bytes = 0;
+      a.nchunk = (d.c_in + 31) / 32; a.act = d.act; a.pool = 0;
+      a.magic_m = magic_for((unsigned)a.tiles_m); a.magic_x = magic_for((unsigned)a.tiles_x); a.magic_y = magic_for((unsigned)a.tiles_y);
+      const dim3 grid((unsigned)((a.strips + tv.wn - 1) / tv.wn * a.tiles_m));
+      const int rc = d.dtype == CPRUNE_F32 ? launch_conv_rows_nchw_f32(tv.patch_id, grid, s, a) :
+                     d.dtype == CPRUNE_F16 ? launch_conv_rows_nchw_f16(tv.patch_id, grid, s, a) : launch_conv_rows_nchw_bf16(tv.patch_id, grid, s, a);
+      if (rc != CPRUNE_OK) return rc;
+      CPRUNE_LAUNCH_CHECK();
+      return CPRUNE_OK;
+    }
     a.x = x; a.w = lay.w_wave; a.bias = bias; a.res = residual; a.y = y;
     a.N = d.n; a.O = d.c_out; a.Cp = lay.cp_in; a.Cop = lay.cp_out;
     a.Hi = d.h; a.Wi = d.w;

@@ -1,0 +1,10 @@
+// Instantiations of the row-strip kernel for tensors in the boundary's layout, __bf16 data.
+#include "conv_rows_nchw_kernel.hpp"
+
+namespace cprune {
+
+int launch_conv_rows_nchw_bf16(int id, dim3 grid, hipStream_t s, const RowsArgs& a) {
+  return launch_rows_nchw<__bf16>(id, grid, s, a);
+}
+
+}  // namespace cprune
