@@ -99,6 +99,8 @@ def lib():
                      "cprune_fc_workspace_bytes", "cprune_probe_scratch_bytes", "cprune_probe_l2_bytes"):
             getattr(L, name).restype = C.c_size_t
         L.cprune_clear_tile_cache.restype = None
+        # (the call that is made most often: with its types known, addresses are passed as plain integers)
+        L.cprune_conv2d_bn_relu.argtypes = [C.POINTER(ConvDesc)] + [C.c_void_p] * 5 + [C.c_int, C.c_void_p, C.c_size_t, C.c_void_p]
         _lib = L
     return _lib
 
@@ -115,13 +117,21 @@ def _ptr(t: Optional[torch.Tensor]):
     return C.c_void_p(t.data_ptr())
 
 
+def _addr(t: Optional[torch.Tensor]):
+    """_ptr for calls whose argument types are declared."""
+    if t is None:
+        return None
+    assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensors only"
+    return t.data_ptr()
+
+
 def _stream(stream=None):
     s = stream if stream is not None else torch.cuda.current_stream()
     return C.c_void_p(s.cuda_stream)
 
 
 def _ws(nbytes: int, device) -> Optional[torch.Tensor]:
-    return torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=device)
+    return torch.empty(max(int(nbytes), 16) if nbytes else 0, dtype=torch.uint8, device=device)
 
 
 # ---- ranking / gather ------------------------------------------------------
@@ -331,19 +341,21 @@ def cprune_conv_workspace_bytes(d: ConvDesc, variant: int = -1) -> int:
 def cprune_conv2d_bn_relu(d: ConvDesc, x, w, bias=None, residual=None, tile_variant: int = -1,
                           ws: Optional[torch.Tensor] = None, y: Optional[torch.Tensor] = None,
                           stream=None) -> torch.Tensor:
+    L = lib()
     if y is None:
-        y = torch.empty(out_shape(d), dtype=TORCH_DTYPE[d.dtype], device=x.device)
+        y = x.new_empty(out_shape(d), dtype=TORCH_DTYPE[d.dtype])
     if ws is None:
         # the scratch of the variant the call will run, not the most any variant could ask for (128 -> 83 at 56x56, batch 8:
-        # 0.7 MB and 264 MB, and looking through all variants is 4 us of the call)
+        # 0.7 MB and 264 MB, and looking through all variants is 4 us of the call); most variants need none
+        ref = C.byref(d)
         if tile_variant == -1 and d.groups == 1:
             v = C.c_int()
-            if lib().cprune_cached_tile(C.byref(d), C.byref(v), None) == OK:
+            if L.cprune_cached_tile(ref, C.byref(v), None) == OK:
                 tile_variant = v.value
-        ws = _ws(cprune_conv_workspace_bytes(d, tile_variant), x.device)
-    st = lib().cprune_conv2d_bn_relu(C.byref(d), _ptr(x), _ptr(w), _ptr(bias), _ptr(residual),
-                                     _ptr(y), C.c_int(tile_variant), _ptr(ws),
-                                     C.c_size_t(ws.numel()), _stream(stream))
+        ws = _ws(L.cprune_conv_workspace_bytes(ref, C.c_int(tile_variant)), x.device)
+    st = L.cprune_conv2d_bn_relu(d, _addr(x), _addr(w), _addr(bias), _addr(residual), _addr(y), tile_variant, _addr(ws),
+                                 ws.numel(),
+                                 (stream if stream is not None else torch.cuda.current_stream()).cuda_stream)
     _check(st, "cprune_conv2d_bn_relu")
     return y
 

@@ -49,6 +49,10 @@ static DescKey key_of(const cprune_conv_desc& d, const ConvLayout& lay) {
 }
 static std::mutex g_cache_mutex;
 static std::map<DescKey, int> g_cache;
+// Untimed choices of the boundary's layout, which every call of an untimed shape needs: the estimates take 4-6 us of the caller's
+// thread, a look here 0.2.  They depend on the shape alone; at most kMaxChoices are kept.
+static std::map<DescKey, int> g_choices;
+constexpr size_t kMaxChoices = 1024;
 // likewise the variant a pair of layers in one launch runs, or -1 where the layers apart were faster
 static std::map<std::array<int, 21>, int> g_pairs;
 
@@ -138,7 +142,19 @@ static int timed_variant(const cprune_conv_desc& d, const ConvLayout& lay) {
 int cached_or_heuristic_variant(const cprune_conv_desc& d, bool* timed, const ConvLayout& lay) {
   const int v = timed_variant(d, lay);
   if (timed) *timed = v >= 0;
-  return v >= 0 ? v : heuristic_variant(d, lay);
+  if (v >= 0) return v;
+  if (lay.nhwc || lay.nhwc_out) return heuristic_variant(d, lay);
+  const DescKey key = key_of(d, lay);
+  {
+    std::lock_guard<std::mutex> lock(g_cache_mutex);
+    auto it = g_choices.find(key);
+    if (it != g_choices.end()) return it->second;
+  }
+  const int choice = heuristic_variant(d, lay);
+  std::lock_guard<std::mutex> lock(g_cache_mutex);
+  if (g_choices.size() >= kMaxChoices) g_choices.clear();
+  g_choices[key] = choice;
+  return choice;
 }
 
 static int conv_dispatch(const cprune_conv_desc& d, const void* x, const void* w, const float* bias,
@@ -334,6 +350,7 @@ extern "C" int cprune_select_tile(const cprune_conv_desc* desc, const void* x, c
 extern "C" void cprune_clear_tile_cache(void) {
   std::lock_guard<std::mutex> lock(g_cache_mutex);
   g_cache.clear();
+  g_choices.clear();
   g_pairs.clear();
 }
 
