@@ -105,9 +105,9 @@ static bool rows_pay(const cprune_conv_desc& d, const ConvLayout& lay) {
 }
 
 // Untimed choice: the row-strip kernel where it pays; otherwise the cheapest by variant_cost among the general kernel's tiles,
-// whole or cut into equal runs, and, for windows of more than one tap, the split kernel's variants where it pays, for 1x1 layers of an
-// fp32 handle those of the 1x1 kernel on three parts (90 random layers: 1.50 times as fast as the general kernel's choice on average,
-// none slower; 1.16 times the time of the timed choice).
+// whole or cut into equal runs, and, for windows of more than one tap, the split kernel's variants where it pays, for 1x1 layers of a
+// handle those of the 1x1 kernel on the 16-bit matrix cores (90 random fp32 layers: 1.50 times as fast as the general kernel's choice on
+// average, none slower, 1.16 times the time of the timed choice; 80 in bf16: 1.44 and 1.12 times).
 int heuristic_variant(const cprune_conv_desc& d, const ConvLayout& lay, size_t ws_limit) {
   double best = -1.0;
   const int rows = rows_pay(d, lay) ? best_rows_variant(d, lay, &best) : -1;
@@ -298,7 +298,7 @@ extern "C" int cprune_tile_variant_name(int v, int channels_last, cprune_dtype d
   else if (tv.rows && tv.stride == 2)
     n = snprintf(buf, buf_bytes, "conv_rows_s2_kernel<%s, %d, %d, %d>", t, tv.mb, tv.th, tv.ks);
   else if (tv.pw3)
-    n = snprintf(buf, buf_bytes, "conv_pw3_kernel<%d, %d, %s>", tv.mb, tv.nb, tv.pw3 == 2 ? "true" : "false");
+    n = snprintf(buf, buf_bytes, "conv_pw3_kernel<%s, %d, %d, %s>", t, tv.mb, tv.nb, tv.pw3 == 2 ? "true" : "false");
   else if (tv.rows)
     n = snprintf(buf, buf_bytes, "conv_rows_kernel<%s, %d, %d, %d>", t, tv.mb, tv.th, tv.ks);
   else if (tv.sched == -4)
@@ -465,7 +465,7 @@ struct NetLayer {
   void* w_wave = nullptr;     // 3x3 / stride 1 / pad 1 layer: weights once more, packed for the independent-wavefront kernel
                               // (small maps) and, in 16-bit data, the row-strip kernel
   void* w_split = nullptr;    // fp32 dense layer: weights once more, cut and packed for the split kernel
-  void* w_rows3 = nullptr;    // fp32 3x3 / stride 1 / pad 1 (1x1) layer: likewise, for the row-strip (1x1) kernel
+  void* w_rows3 = nullptr;    // fp32 3x3 / pad 1 layer, or 1x1 layer of any type: likewise, for the row-strip (the 1x1) kernel
   bool stem = false;          // nchw_in layer that runs the first-layer kernel (whole reduction in LDS)
   void* w_stem7 = nullptr;    // 7x7 / stride 2 / pad 3 first layer: weights packed for the kernel made for it
   int stem7 = 0;              // 1: that kernel runs the layer; 2: and the 3x3 / stride 2 max-pool pool3 with it
@@ -548,28 +548,30 @@ static bool wave_layer(const cprune_net& net, const NetLayer& L) {
 }
 
 // The other copies of a dense layer's weights are made only for a layer that runs the kernel that reads them (while variants are
-// timed, for every layer that could): fp32, cut and packed for the split and the row-strip kernel, each 1.5 times the weights or
-// more; 16-bit data, the row-strip kernel's copy on maps that are not the independent-wavefront kernel's, as large as the weights.
+// timed, for every layer that could): fp32, cut and packed for the split, the row-strip and the 1x1 kernel, each 1.5 times the weights or
+// more; 16-bit data, the 1x1 kernel's, and the row-strip kernel's copy on maps that are not the independent-wavefront kernel's, as large as the weights.
 static ConvLayout layout_if_packed(const cprune_net& net, const NetLayer& L) {
   ConvLayout lay = layer_layout(L);      // (only whether the copies are set matters to a choice)
   if (net.dtype == CPRUNE_F32 && !L.nchw_in) lay.w_split = lay.w_rows3 = L.w;
+  if (L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1 && L.d.k == 1 && !L.nchw_in) lay.w_rows3 = L.w;
   if (net.dtype != CPRUNE_F32 && !lay.w_wave && strips_layer(net, L)) lay.w_wave = L.w;
   return lay;
 }
 
 // the copy variant v reads, if it reads one
 static int pack_for(cprune_net* net, NetLayer& L, int v, hipStream_t s) {
-  const bool f32 = net->dtype == CPRUNE_F32, rows = variant(v).rows || variant(v).pw3;
+  const bool f32 = net->dtype == CPRUNE_F32, pw = variant(v).pw3, rows = variant(v).rows || pw;
   if (!rows && !(f32 && variant(v).split)) return CPRUNE_OK;
-  void*& slot = !rows ? L.w_split : f32 ? L.w_rows3 : L.w_wave;
+  void*& slot = !rows ? L.w_split : f32 || pw ? L.w_rows3 : L.w_wave;
   if (slot) return CPRUNE_OK;
   const cprune_conv_desc d = layer_conv_desc(*net, L, net->max_batch);
   const int cp = layer_layout(L).cp_in, taps = d.kh * d.kw;
+  const bool split = f32 || pw;
   void* copy = nullptr;
-  CPRUNE_HIP_TRY(hipMalloc(&copy, f32 ? split_packed_bytes(d.c_out, cp, taps, net->dtype, rows) : wave_packed_bytes(d.c_out, cp, net->dtype)));
+  CPRUNE_HIP_TRY(hipMalloc(&copy, split ? split_packed_bytes(d.c_out, cp, taps, net->dtype, rows) : wave_packed_bytes(d.c_out, cp, net->dtype)));
   net->allocs.push_back(copy);
   slot = copy;
-  return f32 ? launch_pack_split(L.w, d.c_out, cp, taps, 1, net->dtype, copy, s, rows) : launch_repack_wave(L.w, d.c_out, cp, net->dtype, copy, s);
+  return split ? launch_pack_split(L.w, d.c_out, cp, taps, 1, net->dtype, copy, s, rows) : launch_repack_wave(L.w, d.c_out, cp, net->dtype, copy, s);
 }
 
 // gives back what variant v (-1: none) does not read (nothing that reads it is in flight)

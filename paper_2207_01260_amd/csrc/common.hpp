@@ -50,7 +50,7 @@ struct TileVariant {
   int split = 0;  // 1 (with sched = -1): split kernel, any window and stride, fp32 as three bf16 parts
   int rows = 0;   // 1 (with sched = -1): row-strip kernel, 3x3 layers of a handle (2: in the boundary's layout); th = rows of a strip, ks = wavefronts that
                   // share one (patch_id indexes its list)
-  int pw3 = 0;    // 1, 2 (deep) (with sched = -1): 1x1 kernel on three 16-bit parts, fp32 layers of a handle (patch_id indexes its list)
+  int pw3 = 0;    // 1, 2 (deep) (with sched = -1): 1x1 kernel on the 16-bit matrix cores, layers of a handle (patch_id indexes its list)
   int nib = 0;    // split kernel: staging items per thread (patch_id indexes its list)
   int nr = 0;     // short-reduction 1x1 kernel: 64-byte rounds of the reduction its filter tile holds
   int stride = 1; // spatial-patch kernel on 16x16 blocks: the window stride it is built for (patch_id then indexes the
@@ -92,8 +92,8 @@ struct ConvLayout {
   const void* w_split = nullptr; // channels-last fp32: the weights cut and packed for the split kernel
                                  // (launch_pack_split), which runs only where this is set; a call in the boundary's
                                  // layout packs its weights into the caller's scratch
-  const void* w_rows3 = nullptr; // channels-last fp32 3x3 / stride 1 / pad 1, or 1x1: cut and packed in whole chunks of 32 channels for
-                                 // the row-strip kernel (the 1x1 kernel), which runs fp32 data only where this is set
+  const void* w_rows3 = nullptr; // channels-last fp32 3x3 / pad 1, and 1x1 layers of any type: cut and packed in whole chunks of 32 channels
+                                 // for the row-strip kernel (the 1x1 kernel), which runs such a layer only where this is set
   const ConvPair* pair = nullptr;
   int pool = 0;  // 1: channels-last 3x3 layer with a 2x2/2 max-pool fused behind the activation (patch kernels);
                  // 2: rows are (channel, position of a 2x2 map) and each group of four rows is reduced to its

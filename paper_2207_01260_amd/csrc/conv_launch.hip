@@ -443,11 +443,11 @@ static double pw3_cost(const cprune_conv_desc& d, const TileVariant& tv, const C
   long tiles_m;
   const double groups = (double)pw3_groups(d, tv, &tiles_m), rounds = (lay.cp_in + 31) / 32;
   const double blocks = std::ceil((d.c_out + 15) / 16 / (double)tiles_m / 4.0);      // of a tile's longest share
-  const bool deep = tv.pw3 == 2;
-  const int occ = tv.nb > 2 ? (tv.mb == 1 ? 3 : 2) : tv.mb == 1 ? (deep ? 4 : 6) : deep ? 2 : 4;
+  const bool deep = tv.pw3 == 2, f32 = d.dtype == CPRUNE_F32;
+  const int occ = !f32 ? (tv.nb > 2 ? (tv.mb == 1 ? 4 : 3) : tv.mb == 1 ? 6 : 4) : tv.nb > 2 ? (tv.mb == 1 ? 3 : 2) : tv.mb == 1 ? (deep ? 4 : 6) : deep ? 2 : 4;
   const double held = std::max(1.0, std::min((double)occ, groups / 256.0));      // work-groups of a unit hide each other's waits
-  return std::ceil(groups / 256.0) * rounds * blocks * tv.nb * 108.0 +
-         std::ceil(groups / (256.0 * occ)) * ((deep ? 5500.0 : 5000.0) + rounds * (deep ? 650.0 : 850.0) / held);
+  return std::ceil(groups / 256.0) * rounds * blocks * tv.nb * (f32 ? 108.0 : 40.0) +
+         std::ceil(groups / (256.0 * occ)) * ((deep ? 5500.0 : 5000.0) + rounds * (!f32 ? 300.0 : deep ? 650.0 : 850.0) / held);
 }
 
 int best_pw3_variant(const cprune_conv_desc& d, const ConvLayout& lay, double* cost) {
@@ -507,9 +507,11 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
            ((long)p.strips / p.tiles_x + 4) * p.tiles_y < (1L << 32);
   }
   if (tv.pw3) {
-    // 1x1 / stride 1 or 2 in an fp32 handle; sums of at least 16 terms, as the split kernel; four filters per store
-    if (!(lay.nhwc && d.dtype == CPRUNE_F32 && lay.w_rows3 && d.kh == 1 && d.kw == 1 && d.pad == 0 && d.stride <= 2)) return false;
-    if (lay.pool || (lay.cp_out & 3) || d.c_in < kSplitMinTerms) return false;
+    // 1x1 / stride 1 or 2 in a handle; fp32 sums of at least 16 terms, as the split kernel; four filters per store
+    const bool f32 = d.dtype == CPRUNE_F32;
+    if (!(lay.nhwc && lay.w_rows3 && d.kh == 1 && d.kw == 1 && d.pad == 0 && d.stride <= 2)) return false;
+    if (lay.pool || (lay.cp_out & 3) || (f32 && d.c_in < kSplitMinTerms)) return false;
+    if (f32 ? tv.nb == 4 && tv.pw3 == 2 : tv.pw3 != 2) return false;      // (built: see CPRUNE_PW3_LIST)
     if (split_packed_bytes(d.c_out, lay.cp_in, 1, d.dtype, true) >= ((size_t)1 << 31)) return false;
     // multiply-high divisions of the decode: exact while dividend x divisor < 2^32
     long tiles_m;
@@ -667,13 +669,15 @@ int launch_conv_dense(const cprune_conv_desc& d, const void* x, const void* w, c
     const int blocks = (d.c_out + 15) / 16;
     a.tiles_m = (int)tiles_m; a.blk_base = blocks / a.tiles_m; a.blk_rem = blocks % a.tiles_m;
     a.rounds = (lay.cp_in + 31) / 32;
-    a.x_bytes = (unsigned)((size_t)d.n * lay.cp_in * d.h * d.w * 4);
+    a.x_bytes = (unsigned)((size_t)d.n * lay.cp_in * d.h * d.w * es);
     a.w_bytes = (unsigned)split_packed_bytes(d.c_out, lay.cp_in, 1, d.dtype, true);
-    a.w_raw_bytes = (unsigned)((size_t)d.c_out * lay.cp_in * 4);
-    a.y_bytes = (unsigned)((size_t)a.P * lay.cp_out * 4);
+    a.w_raw_bytes = (unsigned)((size_t)d.c_out * lay.cp_in * es);
+    a.y_bytes = (unsigned)((size_t)a.P * lay.cp_out * es);
     a.magic_m = magic_for((unsigned)a.tiles_m); a.magic_wo = magic_for((unsigned)a.Wo); a.magic_ho = magic_for((unsigned)a.Ho);
     a.act = d.act;
-    const int rc = launch_conv_pw3_f32(tv.patch_id, dim3((unsigned)groups), s, a);
+    const dim3 grid((unsigned)groups);
+    const int rc = d.dtype == CPRUNE_F32 ? launch_conv_pw3_f32(tv.patch_id, grid, s, a) :
+                   d.dtype == CPRUNE_F16 ? launch_conv_pw3_f16(tv.patch_id, grid, s, a) : launch_conv_pw3_bf16(tv.patch_id, grid, s, a);
     if (rc != CPRUNE_OK) return rc;
     CPRUNE_LAUNCH_CHECK();
     return CPRUNE_OK;

@@ -1,9 +1,9 @@
-// 1x1 convolution of fp32 data, channels-last, stride 1 or 2, on the 16-bit matrix cores: every number cut into three bf16
-// parts, six of the nine products multiplied (conv_split_kernel.hpp has the error and the range of that).
+// 1x1 convolution, channels-last, stride 1 or 2, on the 16-bit matrix cores: an fp32 number cut into three bf16 parts, six of the
+// nine products multiplied (conv_split_kernel.hpp has the error and the range of that), 16-bit data as it is.
 //
 // A matrix product of short reductions (three to thirty rounds of 32 channels) on few pixels: what the split kernel for any window
 // loses on it is two barriers, a table walk and a wait for the chunk per round.  Here a work-group of four wavefronts owns NB * 16 pixels
-// and up to 4 * MB 16-filter blocks, dealt evenly.  A chunk of two rounds is cut once, while it is stored to LDS ([round][part][pixel][64
+// and up to 4 * MB 16-filter blocks, dealt evenly.  A chunk of two rounds (16-bit data: four) is cut once, while it is stored to LDS ([round][part][pixel][64
 // bytes]: every store and operand read is 1 KiB of consecutive memory), and read by all four wavefronts; there are two buffers,
 // so one barrier per chunk, and the chunk behind them is on its way in registers.  Weights, packed in whole rounds
 // (launch_pack_split), go from memory to registers a round ahead.  DEEP: two chunks on their way and weights a chunk ahead, for long
@@ -13,10 +13,11 @@
 // Measured, the best other kernel / this one (us): 96 -> 385 at 14x14, batch 64, 19.7 / 12.1; 160 -> 829 at 7x7 16.0 / 9.5; 829 -> 320 at
 // 7x7 29 / 15, 320 -> 1280 31 / 18 (143 TFLOP/s); stride 2, batch 32: 64 -> 128 at 56x56 12.1 / 7.7, 256 -> 512 at 14x14 10.6 / 6.5; 90
 // random layers of 0.01-4 GFLOP, timed choice before / now 1.29 times on average, untimed 1.50.  Deep or not: 739 -> 58 at 28x28
-// stride 2, batch 30, 9.6 / 12.3; 29 -> 232 at 56x56, batch 28, 32.0 / 23.8.  What bounds it: launch, first loads and stores (some 4 us);
+// stride 2, batch 30, 9.6 / 12.3; 29 -> 232 at 56x56, batch 28, 32.0 / 23.8.  bf16, 80 random layers: timed choice 1.23 times as fast as before,
+// untimed 1.44 (865 -> 78 at 56x56 stride 2, batch 28, 12 us; 16 -> 292 at 56x56, batch 55, stays on the short-reduction kernel, 35.5 / 40.9).  What bounds it: launch, first loads and stores (some 4 us);
 // 96 -> 385 moves 24 MB, 5 us at the copy rate; 320 -> 1280 the matrix pipes (35 %) and the wait for weights.
 #pragma once
-#include "conv_split_kernel.hpp"
+#include "conv_rows_s2_kernel.hpp"
 
 namespace cprune {
 
@@ -36,18 +37,20 @@ struct Pw3Args {
   int act;
 };
 
-// Variants: id, 16-filter blocks per wavefront, 16-pixel blocks of a work-group, deep
+// Variants: id, 16-filter blocks per wavefront, 16-pixel blocks of a work-group, deep (16-bit data: always)
 #define CPRUNE_PW3_LIST(X) \
-  X(0, 1, 2, 0) X(1, 2, 2, 0) X(2, 1, 4, 0) X(3, 2, 4, 0) X(4, 1, 2, 1) X(5, 2, 2, 1)
+  X(0, 1, 2, 0) X(1, 2, 2, 0) X(2, 1, 4, 0) X(3, 2, 4, 0) X(4, 1, 2, 1) X(5, 2, 2, 1) \
+  X(6, 1, 4, 1) X(7, 2, 4, 1)
 
-constexpr int kNumPw3 = 6;
+constexpr int kNumPw3 = 8;      // (fp32: the first six)
 
-template <int MB, int NB, bool DEEP>
+template <typename T, int MB, int NB, bool DEEP>
 __global__ __launch_bounds__(256, 2) void conv_pw3_kernel(Pw3Args a) {
-  constexpr int RC = 2;                        // rounds of a chunk
+  constexpr int ES = (int)sizeof(T), P = SplitParts<T>::value, NQ = ES / 2;
+  constexpr int RC = P == 3 ? 2 : 4;           // rounds of a chunk
   constexpr int PT = NB * 16;
   constexpr int NI = PT * 4 * RC / 256;        // staging items (8 channels of a pixel) per thread
-  constexpr int PART = PT * 64, ROUND = 3 * PART, BUF = RC * ROUND;
+  constexpr int PART = PT * 64, ROUND = P * PART, BUF = RC * ROUND;
   static_assert(NI >= 1 && NI * 256 == PT * 4 * RC, "staging items");
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BUF];
 
@@ -75,7 +78,7 @@ __global__ __launch_bounds__(256, 2) void conv_pw3_kernel(Pw3Args a) {
       const int q = (int)fast_div((unsigned)p, a.magic_wo), n = (int)fast_div((unsigned)q, a.magic_ho);
       at = (n * a.H + (q - n * a.Ho) * a.stride) * a.W + (p - q * a.Wo) * a.stride;
     }
-    return p < a.P ? (unsigned)(at * a.Cp) * 4u : kOutOfRange;
+    return p < a.P ? (unsigned)(at * a.Cp) * ES : kOutOfRange;
   };
 
   // ---- staging ----
@@ -84,70 +87,74 @@ __global__ __launch_bounds__(256, 2) void conv_pw3_kernel(Pw3Args a) {
 #pragma unroll
   for (int j = 0; j < NI; ++j) {
     const int idx = t + 256 * j, g = idx & 3, px = (idx >> 2) % PT, rd = idx / (4 * PT);
-    x_off[j] = pixel(tile_p * PT + px) + (unsigned)(rd * 128 + g * 32);
+    x_off[j] = pixel(tile_p * PT + px) + (unsigned)(rd * 32 + g * 8) * ES;
     x_ch[j] = rd * 32 + g * 8;
     x_lds[j] = rd * ROUND + px * 64 + g * 16;
   }
-  auto gload = [&](int c, uint4 (&raw)[NI][2]) CPRUNE_INLINE {
+  auto gload = [&](int c, RawRow<T> (&raw)[NI]) CPRUNE_INLINE {
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll
-      for (int e = 0; e < 2; ++e)
-        raw[j][e] = load_b128(xr, c * (RC * 32) + x_ch[j] + e * 4 < a.Cp ? x_off[j] + (unsigned)(c * (RC * 128) + e * 16) : kOutOfRange, 0);
+      for (int e = 0; e < NQ; ++e)
+        raw[j].q[e] = load_b128(xr, c * (RC * 32) + x_ch[j] + e * (16 / ES) < a.Cp ? x_off[j] + (unsigned)(c * (RC * 32 * ES) + e * 16) : kOutOfRange, 0);
   };
-  auto lds_store = [&](int buf, const uint4 (&raw)[NI][2]) CPRUNE_INLINE {
+  auto lds_store = [&](int buf, const RawRow<T> (&raw)[NI]) CPRUNE_INLINE {
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
-      uint32_t h[4], m[4], l[4];
-      split3(raw[j][0].x, raw[j][0].y, h[0], m[0], l[0]); split3(raw[j][0].z, raw[j][0].w, h[1], m[1], l[1]);
-      split3(raw[j][1].x, raw[j][1].y, h[2], m[2], l[2]); split3(raw[j][1].z, raw[j][1].w, h[3], m[3], l[3]);
-      unsigned char* const d = smem + buf * BUF + x_lds[j];
-      *(uint4*)d = make_uint4(h[0], h[1], h[2], h[3]);
-      *(uint4*)(d + PART) = make_uint4(m[0], m[1], m[2], m[3]);
-      *(uint4*)(d + 2 * PART) = make_uint4(l[0], l[1], l[2], l[3]);
+      const Operand<T> v = to_operand(raw[j]);
+#pragma unroll
+      for (int p = 0; p < P; ++p) *(uint4*)(smem + buf * BUF + x_lds[j] + p * PART) = v.p[p];
     }
   };
 
-  const unsigned w_blk = (unsigned)a.rounds * 3072u;
+  const unsigned w_blk = (unsigned)a.rounds * (P * 1024u);
   const unsigned w_base = (unsigned)split_weight_block(share.first, a.blk_base * a.tiles_m + a.blk_rem) * w_blk;
-  auto load_weights = [&](auto mbc, int round, uint4 (&f)[MB][3]) CPRUNE_INLINE {
-    const unsigned at = w_base + (unsigned)split_weight_round(round, a.rounds) * 3072u;
+  auto load_weights = [&](auto mbc, int round, uint4 (&f)[MB][P]) CPRUNE_INLINE {
+    const unsigned at = w_base + (unsigned)split_weight_round(round, a.rounds) * (P * 1024u);
 #pragma unroll
     for (int i = 0; i < decltype(mbc)::value; ++i)
 #pragma unroll
-      for (int p = 0; p < 3; ++p) f[i][p] = load_b128(wr, (unsigned)lane * 16u + p * 1024u, at + i * w_blk);
+      for (int p = 0; p < P; ++p) f[i][p] = load_b128(wr, (unsigned)lane * 16u + p * 1024u, at + i * w_blk);
   };
 
-  float4_t big[MB][NB], small[MB][NB];
+  float4_t big[MB][NB], small[P == 3 ? MB : 1][NB];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) big[i][j] = small[i][j] = (float4_t){0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NB; ++j) big[i][j] = small[P == 3 ? i : 0][j] = (float4_t){0.f, 0.f, 0.f, 0.f};
   const unsigned char* const b_at = smem + r * 64 + g4 * 16;
   // consecutive MFMAs on different sums: the scheduler by itself issues each block's chain back to back
-  auto multiply = [&](auto mbc, const uint4 (&f)[MB][3], int off) CPRUNE_INLINE {
+  auto multiply = [&](auto mbc, const uint4 (&f)[MB][P], int off) CPRUNE_INLINE {
     constexpr int MBC = decltype(mbc)::value;
     constexpr int JS = 2;
 #pragma unroll
     for (int j0 = 0; j0 < NB; j0 += JS) {
-      uint4 b[JS][3];
+      uint4 b[JS][P];
 #pragma unroll
       for (int j = 0; j < JS; ++j)
 #pragma unroll
-        for (int p = 0; p < 3; ++p) b[j][p] = *(const uint4*)(b_at + off + p * PART + (j0 + j) * 1024);
-      auto term = [&](int pw, int px, float4_t (&d)[MB][NB]) CPRUNE_INLINE {
+        for (int p = 0; p < P; ++p) b[j][p] = *(const uint4*)(b_at + off + p * PART + (j0 + j) * 1024);
+      auto term = [&](int pw, int px) CPRUNE_INLINE {
 #pragma unroll
         for (int j = 0; j < JS; ++j)
 #pragma unroll
-          for (int i = 0; i < MBC; ++i) d[i][j0 + j] = mfma_split<float>(f[i][pw], b[j][px], d[i][j0 + j]);
+          for (int i = 0; i < MBC; ++i) {
+            float4_t& d = pw + px == 0 ? big[i][j0 + j] : small[P == 3 ? i : 0][j0 + j];
+            d = mfma_split<T>(f[i][pw], b[j][px], d);
+          }
       };
-      term(0, 2, small); term(0, 0, big); term(2, 0, small); term(1, 1, small); term(0, 1, small); term(1, 0, small);
+      if constexpr (P == 3) {
+        term(0, 2); term(0, 0); term(2, 0); term(1, 1); term(0, 1); term(1, 0);
+      } else {
+        term(0, 0);
+      }
     }
   };
 
   const int nchunk = (a.rounds + RC - 1) / RC;
   auto main_loop = [&](auto mbc) CPRUNE_INLINE {
-    uint4 w0[DEEP ? RC : 1][MB][3], w1[DEEP ? RC : 1][MB][3], raw0[NI][2], raw1[NI][2];
+    uint4 w0[DEEP ? RC : 1][MB][P], w1[DEEP ? RC : 1][MB][P];
+    RawRow<T> raw0[NI], raw1[NI];
     if constexpr (DEEP) {
       gload(0, raw1);
 #pragma unroll
@@ -157,12 +164,13 @@ __global__ __launch_bounds__(256, 2) void conv_pw3_kernel(Pw3Args a) {
       gload(2, raw1);
       __syncthreads();
       // chunk c, its weights at hand; the raw chunk c + 1 goes to LDS, its place to chunk c + 3
-      auto step = [&](int c, const uint4 (&w)[RC][MB][3], uint4 (&next)[RC][MB][3], uint4 (&raw)[NI][2]) CPRUNE_INLINE {
+      auto step = [&](int c, const uint4 (&w)[RC][MB][P], uint4 (&next)[RC][MB][P], RawRow<T> (&raw)[NI]) CPRUNE_INLINE {
         const int at = (c & 1) * BUF;
 #pragma unroll
         for (int q = 0; q < RC; ++q) load_weights(mbc, RC * c + RC + q, next[q]);
-        multiply(mbc, w[0], at);
-        if (RC * c + 1 < a.rounds) multiply(mbc, w[1], at + ROUND);
+#pragma unroll
+        for (int q = 0; q < RC; ++q)
+          if (q == 0 || RC * c + q < a.rounds) multiply(mbc, w[q], at + q * ROUND);
         if (c + 1 < nchunk) {
           lds_store((c + 1) & 1, raw);
           gload(c + 3, raw);
@@ -200,6 +208,7 @@ __global__ __launch_bounds__(256, 2) void conv_pw3_kernel(Pw3Args a) {
   float4_t bias[MB];
 #pragma unroll
   for (int i = 0; i < MB; ++i) bias[i] = load_bias4(a.bias, i < nblk ? a.O : 0, o0 + i * 16 + 4 * g4);
+  if constexpr (P == 3) {
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -252,6 +261,7 @@ __global__ __launch_bounds__(256, 2) void conv_pw3_kernel(Pw3Args a) {
       }
     }
   }
+  }
 
   // bias, shortcut (a block's loads before its stores), activation, four filters of a pixel per store
   const __amdgpu_buffer_rsrc_t rr = make_rsrc(a.res, a.res ? a.y_bytes : 0u);
@@ -263,11 +273,15 @@ __global__ __launch_bounds__(256, 2) void conv_pw3_kernel(Pw3Args a) {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       const int o = o0 + i * 16 + 4 * g4;
-      off[i] = (p < a.P) & (i < nblk) & (o < a.Cop) ? (unsigned)(p * a.Cop + o) * 4u : kOutOfRange;
+      off[i] = (p < a.P) & (i < nblk) & (o < a.Cop) ? (unsigned)(p * a.Cop + o) * ES : kOutOfRange;
       s[i] = big[i][j] + bias[i];
       if (a.res) {
-        const uint4 q = load_b128(rr, off[i], 0);
-        s[i] += __builtin_bit_cast(float4_t, q);
+        if constexpr (ES == 4) {
+          const uint4 q = load_b128(rr, off[i], 0);
+          s[i] += __builtin_bit_cast(float4_t, q);
+        } else {
+          s[i] += widen4<T>(load_b64(rr, off[i], 0));
+        }
       }
     }
 #pragma unroll
@@ -275,7 +289,8 @@ __global__ __launch_bounds__(256, 2) void conv_pw3_kernel(Pw3Args a) {
       if (off[i] == kOutOfRange) continue;
 #pragma unroll
       for (int q = 0; q < 4; ++q) s[i][q] = apply_act(s[i][q], a.act);
-      *(float4_t*)((char*)a.y + off[i]) = s[i];
+      if constexpr (ES == 4) *(float4_t*)((char*)a.y + off[i]) = s[i];
+      else *(uint2*)((char*)a.y + off[i]) = narrow4<T>(s[i]);
     }
   }
 }
@@ -283,12 +298,19 @@ __global__ __launch_bounds__(256, 2) void conv_pw3_kernel(Pw3Args a) {
 template <typename T>
 inline int launch_pw3(int id, dim3 grid, hipStream_t s, const Pw3Args& a) {
 #define CPRUNE_PW3_CASE(ID, MB_, NB_, DEEP_) \
-  case ID: hipLaunchKernelGGL((conv_pw3_kernel<MB_, NB_, DEEP_ != 0>), grid, dim3(256), 0, s, a); break;
-  switch (id) { CPRUNE_PW3_LIST(CPRUNE_PW3_CASE) default: return CPRUNE_ERR_UNSUPPORTED; }
+  case ID:                                                                                                                 \
+    if constexpr (sizeof(T) == 4 ? !(NB_ == 4 && DEEP_) : DEEP_ != 0) {                                                  \
+      hipLaunchKernelGGL((conv_pw3_kernel<T, MB_, NB_, DEEP_ != 0>), grid, dim3(256), 0, s, a);                          \
+      return CPRUNE_OK;                                                                                                    \
+    }                                                                                                                      \
+    break;
+  switch (id) { CPRUNE_PW3_LIST(CPRUNE_PW3_CASE) default: break; }
 #undef CPRUNE_PW3_CASE
-  return CPRUNE_OK;
+  return CPRUNE_ERR_UNSUPPORTED;
 }
 
 int launch_conv_pw3_f32(int id, dim3 grid, hipStream_t s, const Pw3Args& a);
+int launch_conv_pw3_f16(int id, dim3 grid, hipStream_t s, const Pw3Args& a);
+int launch_conv_pw3_bf16(int id, dim3 grid, hipStream_t s, const Pw3Args& a);
 
 }  // namespace cprune

@@ -47,26 +47,6 @@ __device__ __forceinline__ float row_shift(float v) {
   }
 }
 
-template <typename T>
-__device__ __forceinline__ float4_t widen4(uint2 q) {
-  const T* h = reinterpret_cast<const T*>(&q);
-  return (float4_t){Elem<T>::to_f32(h[0]), Elem<T>::to_f32(h[1]), Elem<T>::to_f32(h[2]), Elem<T>::to_f32(h[3])};
-}
-
-template <typename T>
-__device__ __forceinline__ uint2 narrow4(float4_t v) {
-  T h[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) h[i] = Elem<T>::from_f32(v[i]);
-  return *reinterpret_cast<const uint2*>(h);
-}
-
-__device__ __forceinline__ uint2 load_b64(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-  typedef unsigned int uint32x2_t __attribute__((ext_vector_type(2)));
-  const uint32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0);
-  return make_uint2(v.x, v.y);
-}
-
 template <typename T, int K, int S, int MB, int XH, int R, bool IMG>
 __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   constexpr int ES = (int)sizeof(T);
