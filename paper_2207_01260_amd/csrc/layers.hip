@@ -264,23 +264,42 @@ __global__ __launch_bounds__(256) void maxpool_nhwc_vec_kernel(const T* __restri
   *reinterpret_cast<uint4*>(y + (size_t)idx * V) = q;
 }
 
-// Channels-last depthwise, vectorised: a thread owns one 16-byte channel vector (4 floats / 8 halves) of TX neighbouring
-// output pixels of a row.  Consecutive lanes take consecutive channel vectors, so every access is a coalesced 16-byte load
+// Channels-last depthwise, vectorised: a thread owns one vector of V channels of TX neighbouring output pixels of a row.
+// Consecutive lanes take consecutive vectors, so every access is a coalesced 16-byte (5x5 on 16-bit data: 8-byte) load
 // or store; each input column loaded serves every output of the run whose window covers it ((TX - 1) * S + K loads per
 // row for TX outputs instead of TX * K), each window row's weights are read with it.  Every load is unconditional (outside the image it is
 // out of the buffer's range and reads as zero, and so do the weights of a window row outside: a row that is not there
 // adds nothing, whatever its weights): behind branches each would be waited for before the next is issued, and on small
-// maps that chain is the kernel's whole time.  Batch 16, bf16: 5x5 on 374 channels at 14x14 11.5 -> 8.3 us,
-// 3x3 on 854 channels at 7x7 5.6 -> 3.5 us.
+// maps that chain is the kernel's whole time.  Batch 16, bf16: 3x3 on 854 channels at 7x7 5.6 -> 3.5 us.
+// What bounds it on larger batches is the first-level cache: 3x3 with TX = 7 reads 4.3 vectors per output, with TX = 2
+// 10.5 (829 channels at 7x7, batch 64, fp32: 9.1 -> 6.3 us, 3.4 TB/s of input and output).  A 5x5 window unrolled whole
+// holds so many rows at once that one or two wavefronts fit a SIMD and runs of four spill; so its rows go round a loop
+// with the next row requested while this one is used, and 16-bit data takes four channels per thread instead of eight:
+// 900 channels at 7x7, batch 256: fp32 57 -> 30 us, bf16 47 -> 22 us; 374 at 14x14, batch 16, bf16: 7.8 -> 6.5 us.
+template <typename T, int K> struct DwVec { static constexpr int V = K == 5 ? 4 : VecOf<T>::V; };
+template <int BYTES> struct DwRaw { typedef uint4 type; };
+template <> struct DwRaw<8> { typedef uint2 type; };
+
+__device__ __forceinline__ void dw_load(__amdgpu_buffer_rsrc_t r, unsigned off, uint4& q) { q = load_b128(r, off, 0); }
+__device__ __forceinline__ void dw_load(__amdgpu_buffer_rsrc_t r, unsigned off, uint2& q) { q = load_b64(r, off, 0); }
+template <typename T, int V> __device__ __forceinline__ void dw_unpack(const uint4& q, float (&f)[V]) { unpack16<T, V>(q, f); }
+template <typename T, int V> __device__ __forceinline__ void dw_unpack(const uint2& q, float (&f)[V]) {
+  const T* h = reinterpret_cast<const T*>(&q);
+#pragma unroll
+  for (int e = 0; e < V; ++e) f[e] = (float)h[e];
+}
+
 template <typename T, int K, int S, int TX>
 __global__ __launch_bounds__(256) void depthwise_nhwc_vec_kernel(const T* __restrict__ x, unsigned x_bytes, const T* __restrict__ w,
                                                                  const float* __restrict__ bias,
                                                                  const T* __restrict__ res, T* __restrict__ y,
                                                                  unsigned total, int c_real, int cp, int h, int wd,
                                                                  int ho, int wo, int xblocks, int pad, int act) {
-  constexpr int V = VecOf<T>::V;
+  constexpr int V = DwVec<T, K>::V;
   constexpr int ES = (int)sizeof(T);
   constexpr int NIN = (TX - 1) * S + K;
+  constexpr int AHEAD = K == 5 ? 2 : 1;   // sets of row registers
+  typedef typename DwRaw<V * ES>::type raw_t;
   const unsigned idx = blockIdx.x * 256u + threadIdx.x;
   if (idx >= total) return;
   const unsigned nvec = (unsigned)cp / V;
@@ -307,24 +326,25 @@ __global__ __launch_bounds__(256) void depthwise_nhwc_vec_kernel(const T* __rest
 #pragma unroll
   for (int j = 0; j < NIN; ++j)
     col[j] = (unsigned)(ix_base + j) < (unsigned)wd ? (unsigned)((ix_base + j) * cp + c0) * ES : kOutOfRange;
-#pragma unroll
-  for (int u = 0; u < K; ++u) {
+  raw_t raw[AHEAD][NIN], wraw[AHEAD][K];
+  auto request = [&](int u, int b) {
     const int iy = oy * S - pad + u;
     const bool inside = (unsigned)iy < (unsigned)h;
     const unsigned row = inside ? (unsigned)((n * h + iy) * wd * cp) * ES : 0u;
     const unsigned out = inside ? 0u : kOutOfRange;
-    uint4 raw[NIN], wraw[K];
 #pragma unroll
-    for (int j = 0; j < NIN; ++j) raw[j] = load_b128(xr, (col[j] | out) + row, 0);
+    for (int j = 0; j < NIN; ++j) dw_load(xr, (col[j] | out) + row, raw[b][j]);
 #pragma unroll
-    for (int v = 0; v < K; ++v) wraw[v] = load_b128(wr, (unsigned)((u * K + v) * cp + c0) * ES | out, 0);
+    for (int v = 0; v < K; ++v) dw_load(wr, (unsigned)((u * K + v) * cp + c0) * ES | out, wraw[b][v]);
+  };
+  auto use = [&](int b) {
     float wk[K][V];
 #pragma unroll
-    for (int v = 0; v < K; ++v) unpack16<T, V>(wraw[v], wk[v]);
+    for (int v = 0; v < K; ++v) dw_unpack<T, V>(wraw[b][v], wk[v]);
 #pragma unroll
     for (int j = 0; j < NIN; ++j) {
       float in[V];
-      unpack16<T, V>(raw[j], in);
+      dw_unpack<T, V>(raw[b][j], in);
 #pragma unroll
       for (int t = 0; t < TX; ++t) {
         const int v = j - t * S;
@@ -334,6 +354,15 @@ __global__ __launch_bounds__(256) void depthwise_nhwc_vec_kernel(const T* __rest
         }
       }
     }
+  };
+  if constexpr (AHEAD == 1) {
+#pragma unroll
+    for (int u = 0; u < K; ++u) { request(u, 0); use(0); }
+  } else {
+    request(0, 0);
+#pragma unroll 1
+    for (int u = 0; u + 2 < K; u += 2) { request(u + 1, 1); use(0); request(u + 2, 0); use(1); }
+    use(0);
   }
 #pragma unroll
   for (int t = 0; t < TX; ++t) {
@@ -345,20 +374,20 @@ __global__ __launch_bounds__(256) void depthwise_nhwc_vec_kernel(const T* __rest
     for (int e = 0; e < V; ++e) o[e] = acc[t][e] + bv[e / 4][e % 4];
     if (res) {
       float rv[V];
-      unpack16<T, V>(*reinterpret_cast<const uint4*>(res + off), rv);
+      dw_unpack<T, V>(*reinterpret_cast<const raw_t*>(res + off), rv);
 #pragma unroll
       for (int e = 0; e < V; ++e) o[e] += rv[e];
     }
-    uint4 q;
-    if constexpr (V == 4) {
+    raw_t q;
+    if constexpr (ES == 4) {
       q.x = __float_as_uint(act_f(o[0], act)); q.y = __float_as_uint(act_f(o[1], act));
       q.z = __float_as_uint(act_f(o[2], act)); q.w = __float_as_uint(act_f(o[3], act));
     } else {
       T* hq = reinterpret_cast<T*>(&q);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) hq[e] = (T)act_f(o[e], act);
+      for (int e = 0; e < V; ++e) hq[e] = (T)act_f(o[e], act);
     }
-    *reinterpret_cast<uint4*>(y + off) = q;
+    *reinterpret_cast<raw_t*>(y + off) = q;
   }
 }
 
@@ -691,17 +720,38 @@ int launch_gavgpool_nhwc(const void* x, int n, int cp, int hw, int dt, void* y, 
   return CPRUNE_OK;
 }
 
+// Outputs per thread.  A long run loads less per output, a short one leaves more threads: with few vectors of output
+// (`vecs` = pixels times channel vectors) the kernel's time is one thread's, with many it is the loads'.  Sevens, made
+// for the widths 7, 14, 28 and 56, only where they leave little undone at the row's end
+// (400 at 15x15, bf16: 8.2 us in fours, 10.1 in sevens; 200 at 20x20: 8.1 and 7.5).  us for runs of 1 / 2 / 4 / 7, batch
+// 64 unless said:
+//   3x3, fp32:  829 at 7x7 (652k) 11.2 / 9.1 / 6.9 / 6.3; 374 at 14x14, batch 16 (301k) 5.1 / 4.4 / 4.3 / 4.1;
+//               829 at 7x7, batch 16 (163k) 3.9 / 3.5 / 3.3 / 3.9; 400 at 14x14, batch 4 (78k) 3.0 / 2.7 / 3.1 / 3.7
+//   3x3, bf16:  500 at 14x14 (803k) 10.8 / 11.1 / 9.7 / 7.9; 300 at 14x14 (477k) 7.5 / 6.7 / 7.2 / 7.0
+//   3x3 / stride 2, fp32: 500 to 7x7 (401k) 8.8 / 7.7 / 6.6 / 5.3; 400 to 8x8 (410k) 8.1 / 7.4 / 6.0 / 6.9;
+//               70 to 28x28, batch 16 (251k) 4.6 / 4.0 / 4.7 / 4.6
+//   5x5, fp32:  374 at 14x14, batch 16 (301k) 9.6 / 7.2 / 6.7 / 5.6; 829 at 7x7, batch 16 (163k) 6.4 / 5.3 / 4.4 / 5.3;
+//               400 at 14x14, batch 4 (78k) 4.8 / 3.7 / 4.2 / 5.1; 900 at 7x7, batch 4 (45k) 3.4 / 3.6 / 4.1 / 5.1
+//   5x5, bf16:  374 at 14x14, batch 16 (301k) 9.1 / 7.3 / 7.0 / 6.5; 900 at 7x7, batch 4 (45k) 3.4 / 4.1 / 5.1 / 6.3
+//   5x5 / stride 2, bf16: 300 to 11x11, batch 48 (441k) 12.3 / 9.8 / 7.9 / 10.4; 374 to 7x7, batch 16 (75k) 4.8 / 4.4 / 5.6 / 7.0
+static int depthwise_run(long vecs, int wo, int k, int stride, bool f32) {
+  const int by7 = (wo + 6) / 7 * 7, by4 = (wo + 3) / 4 * 4;
+  const bool sevens = stride == 1 ? by7 * 5 <= by4 * 6 : k == 3 && f32 && wo % 7 == 0;
+  const long full = k == 3 && !f32 && stride == 1 ? 512 : stride == 2 && k == 3 ? 256 : 128;   // thousands of vectors
+  if (sevens && vecs >= (stride == 2 ? 384L : full < 256 ? 256L : full) * 1024) return 7;
+  if (vecs >= full * 1024) return 4;
+  return vecs >= 64L * 1024 ? 2 : 1;
+}
+
 template <typename T>
 static int depthwise_nhwc_dispatch(const cprune_conv_desc& d, int cp, const void* x, const void* w,
                                    const float* bias, const void* res, void* y, hipStream_t s) {
   const int ho = conv_out_dim(d.h, d.kh, d.stride, d.pad), wo = conv_out_dim(d.w, d.kw, d.stride, d.pad);
   constexpr int V = VecOf<T>::V;
-  // vectorised kernel: 3x3 and 5x5 at stride 1 or 2, channel stride a whole number of vectors;
-  // four outputs per thread when that still leaves every compute unit several work-groups; two, with the smaller
-  // window, when it leaves one (377 channels at 14x14, batch 16, bf16: 4.2 us, with one 6.5; 5x5 on 374: 10.4 and 8.3)
+  // vectorised kernel: 3x3 and 5x5 at stride 1 or 2, channel stride a whole number of vectors
   if ((d.kh == 3 || d.kh == 5) && (d.stride == 1 || d.stride == 2) && cp % V == 0) {
-    const long per_row = (long)d.n * ho * (cp / V);
-    const int tx = per_row * ((wo + 3) / 4) >= 256L * 1024 ? 4 : (d.kh == 3 && per_row * ((wo + 1) / 2) >= 64L * 1024 ? 2 : 1);
+    const long per_row = (long)d.n * ho * (cp / (d.kh == 5 ? DwVec<T, 5>::V : V));
+    const int tx = depthwise_run(per_row * wo, wo, d.kh, d.stride, sizeof(T) == 4);
     const int xblocks = (wo + tx - 1) / tx;
     const long total = per_row * xblocks;
     const size_t xb = (size_t)d.n * d.h * d.w * cp * sizeof(T);
@@ -716,12 +766,17 @@ static int depthwise_nhwc_dispatch(const cprune_conv_desc& d, int cp, const void
         case 311: GOV(3, 1, 1); break;
         case 312: GOV(3, 1, 2); break;
         case 314: GOV(3, 1, 4); break;
+        case 317: GOV(3, 1, 7); break;
         case 321: GOV(3, 2, 1); break;
         case 322: GOV(3, 2, 2); break;
         case 324: GOV(3, 2, 4); break;
+        case 327: GOV(3, 2, 7); break;
         case 511: GOV(5, 1, 1); break;
+        case 512: GOV(5, 1, 2); break;
         case 514: GOV(5, 1, 4); break;
+        case 517: GOV(5, 1, 7); break;
         case 521: GOV(5, 2, 1); break;
+        case 522: GOV(5, 2, 2); break;
         case 524: GOV(5, 2, 4); break;
       }
 #undef GOV
