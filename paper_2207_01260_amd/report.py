@@ -34,9 +34,11 @@ PEAK_GBS = 8000.0
 
 
 def kernel_peak(kernel: str, dtype: int) -> float:
-    """Dense MFMA TFLOP/s a kernel (cprune_tile_variant_name) can reach: the split kernel runs an fp32 product as six bf16
-    ones."""
-    return PEAK_TFLOPS[B.BF16] / 6 if dtype == B.F32 and kernel.startswith("conv_split") else PEAK_TFLOPS[dtype]
+    """Dense MFMA TFLOP/s a kernel (cprune_tile_variant_name) can reach: the kernels on three bf16 parts run an fp32
+    product as six bf16 ones."""
+    parts = kernel.startswith(("conv_split", "conv_pw3", "conv_rows_s2", "conv_rows_nchw"))
+    return PEAK_TFLOPS[B.BF16] / 6 if dtype == B.F32 and parts else PEAK_TFLOPS[dtype]
+
 DT_NAME = {B.F32: "f32", B.F16: "f16", B.BF16: "bf16"}
 
 
