@@ -482,6 +482,8 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
     // alone fill the chip several times
     if (tv.rows == 2) {
       if (lay.nhwc || lay.nhwc_out || lay.pool || !(d.kh == 3 && d.kw == 3 && d.stride == 1 && d.pad == 1)) return false;
+      // the kernel addresses its output (and shortcut) with 31-bit byte offsets; a call bounds it in elements only
+      if ((size_t)d.n * d.c_out * d.h * d.w * dtype_size(d.dtype) >= ((size_t)1 << 31)) return false;
       const RowsArgs p = rows_tiles(d, tv, lay);
       const long groups = (long)((p.strips + tv.wn - 1) / tv.wn) * p.tiles_m;
       if (d.dtype == CPRUNE_F32 && ((long)d.c_in * 9 < kSplitMinTerms || tv.mb > 1 || tv.th > 6 || tv.ks > 2)) return false;
