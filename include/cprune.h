@@ -346,7 +346,9 @@ int cprune_net_fuse_first_layers(cprune_net* net, int enable);
  * behind the layer inside it (the conv map is then never stored: cprune_net_copy_activation of the conv
  * layer returns CPRUNE_ERR_UNSUPPORTED, the pool layer's activation is the pooled map as always; form 0 brings it back).
  * A 16-bit handle: cprune_net_create(tune = 1) times the forms and keeps the fastest, tune = 0 takes the highest available.
- * An fp32 handle: tune = 1 takes the highest available, tune = 0 the kernel without the pool, and keeps the conv map.
+ * An fp32 handle keeps the conv map until its caller asks for form 2: tune = 1 runs the kernel with the pool inside and stores the
+ * conv map besides, tune = 0 the kernel and the pool apart.  In it form 0 means the fp32 instruction, and forms 0 and 2 are for a layer
+ * with such a pool only; there is no form for the two starts (another handle, or for the layer alone cprune_net_set_layer_variant).
  * CPRUNE_ERR_UNSUPPORTED for networks that do not open that way, for form 1 in fp32 handles, and for form 2 (in fp32
  * also form 0) when the conv map has another reader or no such pool follows.  Synchronises; recorded graphs are dropped. */
 int cprune_net_first_layer_form(cprune_net* net, int form);

@@ -468,7 +468,8 @@ struct NetLayer {
   void* w_rows3 = nullptr;    // fp32 3x3 / pad 1 layer, or 1x1 layer of any type: likewise, for the row-strip (the 1x1) kernel
   bool stem = false;          // nchw_in layer that runs the first-layer kernel (whole reduction in LDS)
   void* w_stem7 = nullptr;    // 7x7 / stride 2 / pad 3 first layer: weights packed for the kernel made for it
-  int stem7 = 0;              // 1: that kernel runs the layer; 2: and the 3x3 / stride 2 max-pool pool3 with it
+  int stem7 = 0;              // 1: that kernel runs the layer; 2: and the 3x3 / stride 2 max-pool pool3 with it; 3 (fp32): the same,
+                              // and the conv map is stored too
   int pool3 = -1;             // the max-pool that can run inside that kernel (the layer's only reader), or -1
   bool in_producer = false;   // max-pool computed inside its producer's kernel: no launch, its buffer is written there
   int stem_ok = 0;            // that kernel exists for the layer's window and stride
@@ -640,7 +641,7 @@ static int net_run_stem(cprune_net* net, int i, int n, const void* x, void* dst,
 // the bands are those for which the rounds of 1024 work-groups that fit the chip (four of two wavefronts per unit) take the fewest steps,
 // a work-group's start and its repeated row counted as one step and a fifth.  64 filters at 224x224 (us), as many bands as fit one
 // round / this rule: batch 32 60 / 60, 33 76 / 69; one image 9.0 / 8.6.
-static int net_run_stem7_f32(const NetLayer& L, bool pool, int n, StemArgs a, hipStream_t s) {
+static int net_run_stem7_f32(const NetLayer& L, int pool, int n, StemArgs a, hipStream_t s) {
   const int mb = a.O <= 32 ? 1 : 2;
   a.tiles_m = (a.O + 32 * mb - 1) / (32 * mb);
   a.tiles_x = pool ? (a.Wp + 6) / 7 : (a.Wo + 15) / 16;
@@ -658,7 +659,7 @@ static int net_run_stem7_f32(const NetLayer& L, bool pool, int n, StemArgs a, hi
   a.x_bytes = (unsigned)((size_t)n * a.C * a.H * a.W * 4);
   a.w_bytes = (unsigned)stem7_packed_bytes(a.O);
   a.w_raw_bytes = (unsigned)((size_t)a.O * a.C * 49 * 4);
-  const int rc = launch_conv_stem7_f32(mb, pool ? 1 : 0, dim3((unsigned)((long)n * a.tiles_y * a.tiles_x), (unsigned)a.tiles_m), s, a);
+  const int rc = launch_conv_stem7_f32(mb, pool, dim3((unsigned)((long)n * a.tiles_y * a.tiles_x), (unsigned)a.tiles_m), s, a);
   if (rc != CPRUNE_OK) return rc;
   CPRUNE_LAUNCH_CHECK();
   return CPRUNE_OK;
@@ -667,7 +668,7 @@ static int net_run_stem7_f32(const NetLayer& L, bool pool, int n, StemArgs a, hi
 // The 7x7 / stride 2 first-layer kernel on the caller's NCHW input, with or without the max-pool behind it.
 static int net_run_stem7(cprune_net* net, int i, int n, const void* x, void* dst, hipStream_t s) {
   const NetLayer& L = net->layers[i];
-  const bool pool = L.stem7 == 2;
+  const bool pool = L.stem7 >= 2;
   StemArgs a;
   a.x = x; a.w = L.w_stem7; a.bias = L.b; a.y = dst;
   a.N = n; a.C = L.d.c_in; a.H = L.h_in; a.W = L.w_in; a.Ho = L.h_out; a.Wo = L.w_out;
@@ -678,9 +679,10 @@ static int net_run_stem7(cprune_net* net, int i, int n, const void* x, void* dst
     const NetLayer& P = net->layers[L.pool3];
     a.y = P.act; a.Hp = P.h_out; a.Wp = P.w_out; a.Cop = P.cp_out;
     a.tiles_y = (a.Hp + 6) / 7; a.tiles_x = (a.Wp + 6) / 7;
-    if (net->dtype == CPRUNE_F32) return net_run_stem7_f32(L, true, n, a, s);
+    if (L.stem7 == 3) a.y_map = dst;
+    if (net->dtype == CPRUNE_F32) return net_run_stem7_f32(L, L.stem7 - 1, n, a, s);
   } else {
-    if (net->dtype == CPRUNE_F32) return net_run_stem7_f32(L, false, n, a, s);
+    if (net->dtype == CPRUNE_F32) return net_run_stem7_f32(L, 0, n, a, s);
     a.tiles_y = (a.Ho + 15) / 16; a.tiles_x = (a.Wo + 15) / 16;
   }
   a.vec_out = (a.Cop % 4) == 0 ? 1 : 0;
@@ -1417,9 +1419,11 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
   // reduction order makes every MFMA operand one LDS read, and which can run the 3x3 / stride 2 / pad 1 max-pool
   // behind the layer as well when nobody else reads the conv map.  With tune != 0 the three forms (as decided so far;
   // that kernel; that kernel with the pool) are timed and the fastest kept; otherwise the most fused one is taken.  In fp32 nothing
-  // is timed: the kernel is always the faster one (with the pool inside, the layers apart / this, us: 64 filters at 224x224, 1 image
-  // 13.1 / 9.0, 8 40.5 / 22.6, 32 120 / 60; 96 filters, 8 images 58 / 34; 64 at 16x16, 128 images 10.9 / 9.5; 8 at 64x64, 4 images
-  // 8.4 / 5.3; 16 at 224x224, 8 images 15.3 / 12.8); an untimed fp32 handle keeps the conv map.
+  // is timed: a timed handle takes the kernel with the pool inside and the conv map stored as well, an untimed one the kernel alone; a
+  // caller that can do without the conv map asks for form 2.  With the general kernels' fp32 instruction / kernel and pool apart / one
+  // kernel and the conv map / one kernel (us): 64 filters at 224x224, 32 images 121 / 91 / 69 / 62, 1 15.6 / 9.5 / 9.5 / 8.6; 96, 8 images 56 /
+  // 44 / 36 / 32; 64 at 16x16, 128 images 14.7 / 9.5 / 9.4 / 8.9; 31 sizes in all: one kernel and the map at most the time of the fp32
+  // instruction (8.6 / 8.6 at worst) and of the two apart, except 10 filters at 29x96, 33 images 7.7 / 8.6, and 92 at 22x255, 9 images 11.3 / 14.2.
   for (int i = 0; i < n_layers && rc == CPRUNE_OK; ++i) {
     NetLayer& L = net->layers[i];
     const cprune_layer_desc& d = L.d;
@@ -1446,10 +1450,10 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     }
     auto set_form = [&](int form) {
       L.stem7 = form;
-      if (L.pool3 >= 0) net->layers[L.pool3].in_producer = form == 2;
+      if (L.pool3 >= 0) net->layers[L.pool3].in_producer = form >= 2;
     };
     const int n_forms = L.pool3 >= 0 ? 3 : 2;
-    int best = dtype == CPRUNE_F32 && !tune ? 1 : n_forms - 1;
+    int best = dtype != CPRUNE_F32 ? n_forms - 1 : tune && L.pool3 >= 0 ? 3 : 1;
     if (tune && dtype != CPRUNE_F32) {
       const int pair[2] = {i, L.pool3};
       float ms[3] = {0.f, 0.f, 0.f};

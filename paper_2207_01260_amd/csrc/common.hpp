@@ -255,6 +255,7 @@ struct StemArgs {
   int vec_out;
   int Hp = 0, Wp = 0;   // 7x7 / stride 2 kernels with the 3x3 / stride 2 / pad 1 max-pool inside: the pooled map; y is
                         // then [n][hp][wp][cop] and tiles_y, tiles_x count 7 x 7 blocks of it (fp32: bands of rows x 7 columns)
+  void* y_map = nullptr;   // fp32 7x7 / stride 2 kernel with the pool inside: the conv map as well (pool = 2)
   int band = 0;         // fp32 7x7 / stride 2 kernel: pairs of conv rows a work-group walks over
   const void* w_raw = nullptr;          // ... the weights as they are, [o][c][7][7]
   unsigned x_bytes = 0, w_bytes = 0, w_raw_bytes = 0;

@@ -14,18 +14,22 @@
 //             loaded a step ahead, cut and stored into ring rows that nobody reads meanwhile: one barrier a step.
 //   pool      a finished row is reduced over its neighbouring lanes (DPP) and over the step's two rows in registers; the
 //             odd row is carried to the next step.  Strips then advance by 14 columns (7 pooled ones), and a band of rows
-//             begins with the row above it.  The conv map, the largest tensor of such a network, is never written.
+//             begins with the row above it.  The conv map, the largest tensor of such a network, is written only where it is
+//             asked for (a timed handle keeps it readable), each of its pixels by the strip and the band that own it, and
+//             never read again.
 //
-// Measured, 64 filters at 224x224 (us), the first-layer kernel on the fp32 instruction and the pool behind it / this kernel with the
-// pool: batch 32 120 / 60, 8 40 / 23, 1 13.1 / 8.6.  The MFMAs of batch 32 take 27 us at full rate (147 of 192 terms and 14 of 16 columns
-// real); two wavefronts per SIMD hide the rest in part: 18 LDS reads of 16 bytes a row, cutting, the sums' look and the pool.  Error
-// against 64 bits 7.4e-8, on the fp32 instruction 2.1e-7.
+// Measured, 64 filters at 224x224 (us), the first-layer kernel on the fp32 instruction and the pool behind it / this kernel and the pool
+// behind it / with the pool and the conv map / with the pool alone: batch 32 120 / 91 / 69 / 60-65, 8 40 / 29 / 25 / 22.5, 1 15.6 / 9.5 / 9.5 /
+// 8.6.  The MFMAs of batch 32 take 27 us at full rate (147 of 192 terms and 14 of 16 columns real); two wavefronts per SIMD hide the rest in
+// part: 18 LDS reads of 16 bytes a row, cutting, the sums' look and the pool.  The conv map is 103 MB, 20 us at the copy rate (streaming
+// stores: the same time).  Error against 64 bits 7.4e-8, on the fp32 instruction 2.1e-7.
 #pragma once
 #include "conv_split_kernel.hpp"
 
 namespace cprune {
 
-template <int MB, bool POOL>
+// POOL 0: the layer alone; 1: with the pool; 2: with the pool, and the conv map written as well
+template <int MB, int POOL>
 __global__ __launch_bounds__(128, 2) void conv_stem7_split_kernel(StemArgs a) {
   constexpr int NT = 128, NR = kStem7SplitRounds;
   constexpr int PAIRS = 19;                     // column pairs a strip needs: 2 * 15 + 8 columns
@@ -203,11 +207,11 @@ __global__ __launch_bounds__(128, 2) void conv_stem7_split_kernel(StemArgs a) {
         v[i][q] = fmaxf(fmaxf(c0, next(std::integral_constant<int, 1>{})), next(std::integral_constant<int, 2>{}));
       }
   };
-  auto store = [&](int y, int x, int w, int h, bool lane_ok, const float4_t (&v)[MB]) CPRUNE_INLINE {
+  auto store = [&](void* map, int y, int x, int w, int h, bool lane_ok, const float4_t (&v)[MB]) CPRUNE_INLINE {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       const int o = o0 + i * 16 + 4 * g4;
-      if (lane_ok & (x < w) & (o < a.Cop)) *(float4_t*)((float*)a.y + ((size_t)(n * h + y) * w + x) * a.Cop + o) = v[i];
+      if (lane_ok & (x < w) & (o < a.Cop)) *(float4_t*)((float*)map + ((size_t)(n * h + y) * w + x) * a.Cop + o) = v[i];
     }
   };
 
@@ -232,7 +236,8 @@ __global__ __launch_bounds__(128, 2) void conv_stem7_split_kernel(StemArgs a) {
       if (cy < a.Ho && o0 < a.O) {
         float4_t s[MB];
         multiply(cy, s);
-        if constexpr (POOL) {
+        if constexpr (POOL == 2) store(a.y_map, cy, cx, a.Wo, a.Ho, (r > 0) & (r < 15), s);      // (14 columns are the strip's own)
+        if constexpr (POOL != 0) {
           across(s);
           if (z == 0) {
 #pragma unroll
@@ -245,15 +250,15 @@ __global__ __launch_bounds__(128, 2) void conv_stem7_split_kernel(StemArgs a) {
             for (int i = 0; i < MB; ++i)
 #pragma unroll
               for (int q = 0; q < 4; ++q) m[i][q] = fmaxf(carry[i][q], s[i][q]);
-            store(p, 7 * tx + (r >> 1), a.Wp, a.Hp, ((r & 1) == 0) & (r < 14), m);
+            store(a.y, p, 7 * tx + (r >> 1), a.Wp, a.Hp, ((r & 1) == 0) & (r < 14), m);
 #pragma unroll
             for (int i = 0; i < MB; ++i) carry[i] = s[i];
           }
         } else {
-          store(cy, cx, a.Wo, a.Ho, true, s);
+          store(a.y, cy, cx, a.Wo, a.Ho, true, s);
         }
       } else if (POOL && o0 < a.O) {
-        store(p, 7 * tx + (r >> 1), a.Wp, a.Hp, ((r & 1) == 0) & (r < 14), carry);
+        store(a.y, p, 7 * tx + (r >> 1), a.Wp, a.Hp, ((r & 1) == 0) & (r < 14), carry);
       }
     }
     if (more) {
@@ -267,11 +272,11 @@ __global__ __launch_bounds__(128, 2) void conv_stem7_split_kernel(StemArgs a) {
 template <typename T>
 inline int launch_stem7_split(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a) {
 #define CPRUNE_STEM7S(MB_, POOL_)                                                                       \
-  if (mb == MB_ && (pool != 0) == POOL_) {                                                              \
+  if (mb == MB_ && pool == POOL_) {                                                                     \
     hipLaunchKernelGGL((conv_stem7_split_kernel<MB_, POOL_>), grid, dim3(128), 0, s, a);                \
     return CPRUNE_OK;                                                                                   \
   }
-  CPRUNE_STEM7S(1, false) CPRUNE_STEM7S(1, true) CPRUNE_STEM7S(2, false) CPRUNE_STEM7S(2, true)
+  CPRUNE_STEM7S(1, 0) CPRUNE_STEM7S(1, 1) CPRUNE_STEM7S(1, 2) CPRUNE_STEM7S(2, 0) CPRUNE_STEM7S(2, 1) CPRUNE_STEM7S(2, 2)
 #undef CPRUNE_STEM7S
   return CPRUNE_ERR_UNSUPPORTED;
 }

@@ -54,6 +54,35 @@ def test_first_layer_on_three_parts(orc, cfg):
     handle.close()
 
 
+@pytest.mark.parametrize("cfg", [
+    # c_in, filters, height, width, batch, activation
+    (3, 64, 112, 112, 2, synth.ACT_RELU), (3, 20, 37, 35, 3, synth.ACT_RELU6), (1, 40, 30, 57, 3, synth.ACT_NONE),
+    (2, 100, 18, 22, 2, synth.ACT_RELU), (3, 33, 8, 113, 2, synth.ACT_NONE), (3, 9, 20, 20, 300, synth.ACT_RELU),
+    (3, 32, 7, 7, 1, synth.ACT_RELU),
+])
+def test_a_timed_handle_keeps_the_conv_map(orc, cfg):
+    """The pool runs inside the layer's kernel, and the layer's own map is there to be copied, at smaller batches and in graphs too."""
+    c_in, c1, h, w, batch, act = cfg
+    net = _net(c_in, c1, h, w, act)
+    params = synth.layer_params(net, 77)
+    x = synth.net_input(net, 78, batch)
+    ref_layers, _ = orc.prune_net(net, params)
+    acts = orc.forward(net, ref_layers, x, return_all=True)
+    layers, _ = pipeline.prune_net(net, pipeline.upload_params(params))
+    handle = pipeline.build_net(net, layers, batch, tune=True)
+    xd = torch.from_numpy(x).cuda()
+    for n, graph in ((batch, False), ((batch + 1) // 2, False), (batch, True), (batch, True)):
+        xn = xd[:n].contiguous()
+        out = handle.forward(xn, use_graph=graph)
+        for i in (0, 1):
+            got = handle.activation(i, n, acts[i].shape[1:]).cpu().numpy()
+            check(got, acts[i][:n], B.F32, f"{cfg} layer {i} n {n} graph {graph}")
+        check(out.cpu().numpy(), acts[2][:n], B.F32, f"{cfg} n {n} graph {graph}")
+    times = handle.layer_times(xd)
+    assert times[0] > 0 and times[1] == 0            # one launch
+    handle.close()
+
+
 def test_error_is_no_larger_than_on_the_fp32_instruction():
     net = _net(3, 64, 96, 96, synth.ACT_NONE)
     layers, _ = pipeline.prune_net(net, pipeline.upload_params(synth.layer_params(net, 73)))
