@@ -615,8 +615,7 @@ static int net_run_stem(cprune_net* net, int i, int n, const void* x, void* dst,
   const int mb = L.d.c_out <= 32 ? 2 : 4;
   a.tiles_y = (a.Ho + 7) / 8; a.tiles_x = (a.Wo + 15) / 16; a.tiles_m = (a.O + mb * 16 - 1) / (mb * 16);
   a.vec_out = (a.Cop % 4) == 0 ? 1 : 0;
-  a.magic_x = a.tiles_x > 1 ? (unsigned)((0x100000000ull + a.tiles_x - 1) / a.tiles_x) : 0u;
-  a.magic_y = a.tiles_y > 1 ? (unsigned)((0x100000000ull + a.tiles_y - 1) / a.tiles_y) : 0u;
+  a.magic_x = strip_magic(a.tiles_x); a.magic_y = strip_magic(a.tiles_y);
   const long ptiles = (long)n * a.tiles_y * a.tiles_x;
   // as many workers as stay resident: LDS per work-group = weight tile + patch + offset table
   const int es = (int)dtype_size(net->dtype), kp = stem_packed_k(L.d.k, net->dtype);
@@ -653,8 +652,7 @@ static int net_run_stem7_f32(const NetLayer& L, int pool, int n, StemArgs a, hip
     if (bands == 1 || cost < best) { best = cost; a.band = (int)band; }
   }
   a.tiles_y = (int)((steps + a.band - 1) / a.band);
-  a.magic_x = a.tiles_x > 1 ? (unsigned)((0x100000000ull + a.tiles_x - 1) / a.tiles_x) : 0u;
-  a.magic_y = a.tiles_y > 1 ? (unsigned)((0x100000000ull + a.tiles_y - 1) / a.tiles_y) : 0u;
+  a.magic_x = strip_magic(a.tiles_x); a.magic_y = strip_magic(a.tiles_y);
   a.w_raw = L.w;
   a.x_bytes = (unsigned)((size_t)n * a.C * a.H * a.W * 4);
   a.w_bytes = (unsigned)stem7_packed_bytes(a.O);
@@ -686,8 +684,7 @@ static int net_run_stem7(cprune_net* net, int i, int n, const void* x, void* dst
     a.tiles_y = (a.Ho + 15) / 16; a.tiles_x = (a.Wo + 15) / 16;
   }
   a.vec_out = (a.Cop % 4) == 0 ? 1 : 0;
-  a.magic_x = a.tiles_x > 1 ? (unsigned)((0x100000000ull + a.tiles_x - 1) / a.tiles_x) : 0u;
-  a.magic_y = a.tiles_y > 1 ? (unsigned)((0x100000000ull + a.tiles_y - 1) / a.tiles_y) : 0u;
+  a.magic_x = strip_magic(a.tiles_x); a.magic_y = strip_magic(a.tiles_y);
   const long ptiles = (long)n * a.tiles_y * a.tiles_x;
   // as many workers as stay resident: weight tile + patch (+ the conv block the pool reads)
   const long lds = (long)mb * 16 * (kStem7K * 2 + 16) + 37L * 320 + (pool ? 256L * (mb * 32 + 16) : 16L);

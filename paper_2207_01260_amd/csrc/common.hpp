@@ -250,8 +250,7 @@ struct StemArgs {
   int N, C, H, W, Ho, Wo, O, Cop;
   int pad, act;
   int tiles_y, tiles_x, tiles_m;
-  unsigned magic_x, magic_y;   // ceil(2^32 / tiles_x), ceil(2^32 / tiles_y), 0 for a divisor of 1 (exact while
-                               // pixel blocks x divisor < 2^32: always, for tensors below 2^31 bytes)
+  unsigned magic_x, magic_y;   // strip_magic of tiles_x, tiles_y
   int vec_out;
   int Hp = 0, Wp = 0;   // 7x7 / stride 2 kernels with the 3x3 / stride 2 / pad 1 max-pool inside: the pooled map; y is
                         // then [n][hp][wp][cop] and tiles_y, tiles_x count 7 x 7 blocks of it (fp32: bands of rows x 7 columns)

@@ -21,6 +21,7 @@
 // never reaches memory, and the pool's launch goes away.
 #pragma once
 #include "conv_patch_kernel.hpp"
+#include "strip_index.hpp"
 
 namespace cprune {
 
@@ -80,11 +81,10 @@ __global__ __launch_bounds__(256) void conv_stem7_kernel(StemArgs a) {
 
   // block -> (image, conv origin of the 16 x 16 block)
   auto origin = [&](int tile, int& n, int& cy0, int& cx0) {
-    const int rest = (int)fast_div((unsigned)tile, a.magic_x);
-    n = (int)fast_div((unsigned)rest, a.magic_y);
-    const int tx = tile - rest * a.tiles_x, ty = rest - n * a.tiles_y;
-    cy0 = POOL ? 14 * ty - 1 : 16 * ty;
-    cx0 = POOL ? 14 * tx - 1 : 16 * tx;
+    const StripAt at = strip_at(tile, a.tiles_x, a.tiles_y, a.magic_x, a.magic_y);
+    n = at.group;
+    cy0 = POOL ? 14 * at.ty - 1 : 16 * at.ty;
+    cx0 = POOL ? 14 * at.tx - 1 : 16 * at.tx;
   };
 
   // the patch of the next block travels to registers while this one is multiplied: per thread NL pairs of

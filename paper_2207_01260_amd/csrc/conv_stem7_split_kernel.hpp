@@ -25,6 +25,7 @@
 // stores: the same time).  Error against 64 bits 7.4e-8, on the fp32 instruction 2.1e-7.
 #pragma once
 #include "conv_split_kernel.hpp"
+#include "strip_index.hpp"
 
 namespace cprune {
 
@@ -50,9 +51,8 @@ __global__ __launch_bounds__(128, 2) void conv_stem7_split_kernel(StemArgs a) {
     const int q = G >> 3, rem = G & 7;
     tile = xcd * q + (xcd < rem ? xcd : rem) + local;
   }
-  const int q_x = (int)fast_div((unsigned)tile, a.magic_x);
-  const int n = (int)fast_div((unsigned)q_x, a.magic_y);
-  const int tx = tile - q_x * a.tiles_x, ty = q_x - n * a.tiles_y;
+  const StripAt strip = strip_at(tile, a.tiles_x, a.tiles_y, a.magic_x, a.magic_y);
+  const int n = strip.group, tx = strip.tx, ty = strip.ty;
   const int o0 = ((int)blockIdx.y * 2 + wave) * (MB * 16);
   const int p_end = POOL ? a.Hp : (a.Ho + 1) >> 1;            // steps of the whole map
   const int p0 = ty * a.band, p1 = min(p0 + a.band, p_end);

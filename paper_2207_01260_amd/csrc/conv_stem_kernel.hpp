@@ -16,6 +16,7 @@
 // 16-byte quad of a 64-byte round for both operands.
 #pragma once
 #include "conv_nhwc_kernel.hpp"
+#include "strip_index.hpp"
 
 namespace cprune {
 
@@ -90,10 +91,8 @@ __global__ __launch_bounds__(256) void conv_stem_kernel(StemArgs a) {
   T pre[NL];
   const int plimit = a.C * PH * PWP;
   auto load_patch = [&](int tile) {
-    const int rest = (int)fast_div((unsigned)tile, a.magic_x);   // multiply-high: no scalar division chains
-    const int n = (int)fast_div((unsigned)rest, a.magic_y);
-    const int tx0 = (tile - rest * a.tiles_x) * TW;
-    const int ty0 = (rest - n * a.tiles_y) * TH;
+    const StripAt at = strip_at(tile, a.tiles_x, a.tiles_y, a.magic_x, a.magic_y);   // multiply-high: no scalar division chains
+    const int n = at.group, tx0 = at.tx * TW, ty0 = at.ty * TH;
     const int iy0 = ty0 * S - a.pad, ix0 = tx0 * S - a.pad;
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
@@ -112,10 +111,8 @@ __global__ __launch_bounds__(256) void conv_stem_kernel(StemArgs a) {
   const int ptiles = a.N * a.tiles_y * a.tiles_x;
   if (worker < ptiles) load_patch(worker);
   for (int tile = worker; tile < ptiles; tile += gridDim.x) {
-    const int rest = (int)fast_div((unsigned)tile, a.magic_x);   // multiply-high: no scalar division chains
-    const int n = (int)fast_div((unsigned)rest, a.magic_y);
-    const int tx0 = (tile - rest * a.tiles_x) * TW;
-    const int ty0 = (rest - n * a.tiles_y) * TH;
+    const StripAt at = strip_at(tile, a.tiles_x, a.tiles_y, a.magic_x, a.magic_y);   // multiply-high: no scalar division chains
+    const int n = at.group, tx0 = at.tx * TW, ty0 = at.ty * TH;
 
     __syncthreads();          // the previous block's reads of the patch are done
 #pragma unroll

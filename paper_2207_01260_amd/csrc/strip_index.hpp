@@ -1,5 +1,5 @@
-// The integer rules of the inverted-residual kernel's strips.  Plain C++, shared by the kernel, the host that launches it, and a
-// host program that walks every strip of a map.
+// The integer rules of the inverted-residual kernel's strips and of the first-layer kernels' pixel blocks.  Plain C++, shared by the
+// kernels, the host that launches them, and a host program that walks every strip of a map.
 #pragma once
 #include "split_index.hpp"
 

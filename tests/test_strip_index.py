@@ -36,3 +36,25 @@ def test_every_strip_decodes_to_its_own_place(tmp_path):
                            "-o", str(exe)])
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
+
+
+# The largest maps of the first-layer kernels (32-bit tensors below 2^31 bytes): blocks across, down, images.  One row of 2.7e8 and
+# 1.3e8 pixels in pooled strips of 14 and blocks of 16, rows of 6272 pixels over 85598 images, 2047 x 65536 in blocks of 8 x 16, 290 x 1.8 million in bands.
+FIRST_LAYER = "{{9586980, 1, 1}, {8388607, 1, 1}, {224, 1, 85598}, {4096, 256, 1}, {65536, 10, 1}, {1171, 4096, 1}}"
+
+
+def test_blocks_of_the_largest_first_layers(tmp_path):
+    """A multiply-high without a correction puts some of these blocks behind the last image; all first-layer kernels decode by the rule
+    that is walked here."""
+    for across in (9586980, 8388607):
+        assert (across - 1) * -(-2 ** 32 // across) >> 32 == 1
+    csrc = os.path.join(ROOT, "paper_2207_01260_amd", "csrc")
+    for kernel in ("conv_stem_kernel.hpp", "conv_stem7_kernel.hpp", "conv_stem7_split_kernel.hpp"):
+        text = open(os.path.join(csrc, kernel)).read()
+        assert "strip_at(" in text and "fast_div" not in text, kernel
+    head, tail = WALK.split("const int maps[][3] = ")
+    src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
+    src.write_text(head + "const int maps[][3] = " + FIRST_LAYER + tail[tail.index(";"):])
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-I", csrc, str(src), "-o", str(exe)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
