@@ -362,7 +362,7 @@ int cprune_net_first_layer_form(cprune_net* net, int form);
 int cprune_net_fuse_depthwise(cprune_net* net, int layer, int enable);
 int cprune_net_layer_fused(const cprune_net* net, int layer, int* fused_out);
 /* (A 1x1 / stride 2 conv beside a 3x3 / stride 2 / pad 1 conv on the same input, as where a residual network halves its
- * map, can run in that layer's launch: cprune_net_create decides, in a fp32 handle only by timing.  Both activations are
+ * map, can run in that layer's launch: cprune_net_create decides, tune = 1 by timing, tune = 0 by size (small layers).  Both activations are
  * stored as always; cprune_net_layer_fused reports 1 for the 1x1 conv and cprune_net_layer_variant -1, its time is
  * part of the other layer's.  cprune_net_set_layer_variant on the 1x1 conv, or on the 3x3 conv with a variant of another
  * kernel, gives each its own launch again.) */

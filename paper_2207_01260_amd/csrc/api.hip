@@ -1053,6 +1053,16 @@ static void set_pair(cprune_net* net, NetLayer& L, bool on) {
   S.pair_by = on ? (int)(&L - net->layers.data()) : -1;
 }
 
+// Whether an untimed pair (3x3 layer d, 1x1 layer S) runs in one launch: up to 0.3 GFLOP in fp32, 0.6 in 16-bit data.  250 random pairs a
+// type, the layers apart / in one launch, untimed choices both: below the line 1.43 times the time on average (0.91 at worst), 16-bit
+// 1.50 (0.88); above it 0.92 (0.41: 256 -> 56 and 440 at 40x40, batch 6, 22.5 / 51 us), 16-bit 0.92 (0.49): there the 1x1 kernel by
+// itself has the better tiles.  Which variant runs is the 3x3 layer's estimate; with the 1x1 layer's tiles counted in it the choice was no
+// better (1.01 times the time of the best variant both ways, 16-bit 1.06 and 1.06-1.08).
+static bool pair_pays(const cprune_conv_desc& d, const NetLayer& S) {
+  const long ho = conv_out_dim(d.h, 3, 2, 1), wo = conv_out_dim(d.w, 3, 2, 1);
+  return 2.0 * d.n * ho * wo * d.c_in * (9.0 * d.c_out + S.d.c_out) <= (d.dtype == CPRUNE_F32 ? 3e8 : 6e8);
+}
+
 // Layer i, if it is the 3x3 / stride 2 / pad 1 layer that halves a residual network's map, takes the 1x1 / stride 2 layer on the same input
 // into its launch.
 static int make_pair(cprune_net* net, int i, bool tune, hipStream_t s) {
@@ -1090,7 +1100,8 @@ static int make_pair(cprune_net* net, int i, bool tune, hipStream_t s) {
     auto it = g_pairs.find(key);
     if (it != g_pairs.end()) known = it->second;
   }
-  if (known == -1 || (!tune && !(L.variant >= 0 && variant(L.variant).rows))) return CPRUNE_OK;
+  if (known == -1 || (!tune && !pair_pays(d, S))) return CPRUNE_OK;
+  if (!tune && !(L.variant >= 0 && variant(L.variant).rows)) return CPRUNE_OK;
   CPRUNE_HIP_TRY(hipMalloc(&S.w_pair, b1));
   net->allocs.push_back(S.w_pair);
   CPRUNE_HIP_TRY(hipMalloc(&L.w_pair, b3));

@@ -104,6 +104,25 @@ def test_every_variant(cfg, dtype):
 
 
 @pytest.mark.parametrize("dtype", sorted(DT))
+def test_untimed_pairs_are_small_layers(dtype):
+    """One launch up to 0.3 GFLOP in fp32 and 0.6 in 16-bit data, two above: the same activations."""
+    c, o, o1, h = 160, 40, 64, 28                     # 26.6 MFLOP an image
+    dt = DT[dtype]
+    conv = torch.nn.functional.conv2d
+    for batch, small in ((4, True), (11 if dtype == "f32" else 22, True), (12 if dtype == "f32" else 23, False), (32, False)):
+        x, w3, w1, b3, b1 = _data(c, o, o1, h, h, batch, dt, 5)
+        net, q = _net(c, o, o1, h, h)
+        handle = _build(net, c, o, w3, w1, b3, b1, batch, dt, o1)
+        assert bool(handle.layer_fused(q - 1)) == small and (handle.layer_variant(q - 1) == -1) == small, batch
+        handle.forward(x.cuda())
+        ref3 = conv(x.double(), w3.double(), b3.double(), 2, 1).clamp(min=0)
+        ref1 = conv(x.double(), w1.double(), b1.double(), 2, 0).clamp(0, 6)
+        assert _rel(handle.activation(q, batch, ref3.shape[1:]), ref3) < REL[dtype]
+        assert _rel(handle.activation(q - 1, batch, ref1.shape[1:]), ref1) < REL[dtype]
+        handle.close()
+
+
+@pytest.mark.parametrize("dtype", sorted(DT))
 def test_a_timed_handle(dtype):
     """Layers apart or in one launch, whichever was the faster, and a smaller batch: the same activations."""
     c, o, o1, h, w, batch = 64, 70, 128, 28, 28, 16
