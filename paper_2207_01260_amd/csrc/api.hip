@@ -457,7 +457,6 @@ struct NetLayer {
   int pair_with = -1;         // 3x3 layer: the 1x1 layer that could run in its launch
   int pair_variant = -1;      // ... variant of the pair at max_batch
   std::vector<int> pair_at;   // ... and at a smaller batch (-1: not yet)
-  void* w_pair = nullptr;     // both: weights once more, as that kernel reads them
   int fuse_stem = -1;         // 3x3 conv: index of the first layer (on the image) computed inside its kernel, or -1
   int stem_reader = -1;       // first layer that may run inside the 3x3 conv stem_reader's kernel
   void* w_stem = nullptr;     // weights packed for the first-layer kernel
@@ -920,12 +919,11 @@ static int layer_variant_at(const cprune_net* net, NetLayer& L, const cprune_con
 // The layout and the second layer of a pair (3x3 layer L and the 1x1 layer beside it).
 static ConvPair pair_of(const cprune_net* net, const NetLayer& L) {
   const NetLayer& S = net->layers[L.pair_with];
-  return ConvPair{S.w_pair, S.w, S.b, S.act, S.d.c_out, S.cp_out, S.d.act};
+  return ConvPair{S.w_rows3, S.w, S.b, S.act, S.d.c_out, S.cp_out, S.d.act};
 }
 
 static ConvLayout pair_layout(const NetLayer& L, const ConvPair* pair) {
   ConvLayout lay = layer_layout(L);
-  lay.w_wave = lay.w_rows3 = L.w_pair;
   lay.pair = pair;
   return lay;
 }
@@ -1102,13 +1100,12 @@ static int make_pair(cprune_net* net, int i, bool tune, hipStream_t s) {
   }
   if (known == -1 || (!tune && !pair_pays(d, S))) return CPRUNE_OK;
   if (!tune && !(L.variant >= 0 && variant(L.variant).rows)) return CPRUNE_OK;
-  CPRUNE_HIP_TRY(hipMalloc(&S.w_pair, b1));
-  net->allocs.push_back(S.w_pair);
-  CPRUNE_HIP_TRY(hipMalloc(&L.w_pair, b3));
-  net->allocs.push_back(L.w_pair);
-  int rc = launch_pack_split(S.w, S.d.c_out, S.cp_in, 1, 1, net->dtype, S.w_pair, s, true);
-  if (rc == CPRUNE_OK) rc = f32 ? launch_pack_split(L.w, L.d.c_out, L.cp_in, 9, 1, net->dtype, L.w_pair, s, true)
-                                : launch_repack_wave(L.w, L.d.c_out, L.cp_in, net->dtype, L.w_pair, s);
+  // the copies it reads are those of the row-strip and the 1x1 kernel
+  int v3 = 0, v1 = 0;
+  while (!(variant(v3).rows == 1 && variant(v3).stride == 2)) ++v3;
+  while (!variant(v1).pw3) ++v1;
+  int rc = pack_for(net, L, v3, s);
+  if (rc == CPRUNE_OK) rc = pack_for(net, S, v1, s);
   if (rc != CPRUNE_OK) return rc;
   const ConvPair pair = pair_of(net, L);
   const ConvLayout lay = pair_layout(L, &pair);
@@ -1149,6 +1146,8 @@ static int make_pair(cprune_net* net, int i, bool tune, hipStream_t s) {
   }
   L.pair_variant = best_v;
   if (best_v >= 0) set_pair(net, L, true);
+  drop_copies(net, L, best_v >= 0 ? best_v : L.variant);
+  drop_copies(net, S, best_v >= 0 ? v1 : S.variant);
   return CPRUNE_OK;
 }
 
@@ -1882,11 +1881,16 @@ extern "C" int cprune_net_set_layer_variant(cprune_net* net, int layer, int vari
   if (conv_ws_bytes(cd, variant, lay) > net->ws_bytes) return CPRUNE_ERR_WORKSPACE;
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
   drop_graphs(net);
-  const int rc = pack_for(net, L, variant, nullptr);
+  // (the other layer of a pair that ends here runs its own variant, whose copy the pair may not have read)
+  NetLayer* const other = L.pair >= 0 ? &net->layers[L.pair] : L.pair_by >= 0 ? &net->layers[L.pair_by] : nullptr;
+  int rc = pack_for(net, L, variant, nullptr);
+  if (rc == CPRUNE_OK && other) rc = pack_for(net, *other, other->variant, nullptr);
   if (rc != CPRUNE_OK) return rc;
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
-  if (L.pair >= 0) set_pair(net, L, false);
-  if (L.pair_by >= 0) set_pair(net, net->layers[L.pair_by], false);
+  if (other) {
+    set_pair(net, L.pair >= 0 ? L : *other, false);
+    drop_copies(net, *other, other->variant);
+  }
   drop_copies(net, L, variant);
   L.variant = variant;
   L.timed = true;

@@ -177,3 +177,65 @@ def test_numbers_three_parts_do_not_hold():
             # 630 terms in fp32, in other orders
             assert float((got[n][ok] - want[n][ok]).norm() / want[n][ok].norm()) < 2e-6, (v, n)
     handle.close()
+
+
+def _in_use():
+    torch.cuda.synchronize()
+    free, total = torch.cuda.mem_get_info()
+    return total - free
+
+
+def test_copies_of_a_pair_that_loses_are_given_back():
+    """fp32, 32 images, layers that run faster apart: a handle that found so by timing holds no more than one that remembers it (packed
+    for the pair the two layers' weights are 15.7 MB)."""
+    c, o, o1, h, batch = 512, 512, 512, 28, 32
+    gen = torch.Generator().manual_seed(4)
+    layers = [{"w": torch.eye(c).view(c, c, 1, 1).cuda(), "b": torch.zeros(c, device="cuda")},
+              {"w": torch.randn(o1, c, 1, 1, generator=gen).cuda(), "b": torch.zeros(o1, device="cuda")},
+              {"w": torch.randn(o, c, 3, 3, generator=gen).cuda(), "b": torch.zeros(o, device="cuda")},
+              {"w": torch.randn(8, o, 1, 1, generator=gen).cuda(), "b": torch.zeros(8, device="cuda")}]
+    net, _ = _net(c, o, o1, h, h)
+    pipeline.build_net(net, layers, batch, B.F32, tune=True).close()      # (what the first handle of a process leaves behind)
+    used = []
+    for remembered in (False, True):
+        if not remembered:
+            B.cprune_clear_tile_cache()
+        before = _in_use()
+        handle = pipeline.build_net(net, layers, batch, B.F32, tune=True)
+        used.append(_in_use() - before)
+        handle.close()
+    B.cprune_clear_tile_cache()
+    assert used[0] - used[1] < 8 << 20, used
+
+
+@pytest.mark.parametrize("dtype", sorted(DT))
+@pytest.mark.parametrize("tune", [False, True])
+def test_layers_of_a_pair_that_ends(dtype, tune):
+    """Either layer pinned to a kernel of its own: the other runs the variant it has, from its own copy of the weights."""
+    c, o, o1, h, batch = 130, 20, 70, 16, 2
+    dt = DT[dtype]
+    x, w3, w1, b3, b1 = _data(c, o, o1, h, h, batch, dt, 6)
+    conv = torch.nn.functional.conv2d
+    ref3 = conv(x.double(), w3.double(), b3.double(), 2, 1).clamp(min=0)
+    ref1 = conv(x.double(), w1.double(), b1.double(), 2, 0).clamp(0, 6)
+    net, q = _net(c, o, o1, h, h)
+    td = B.TORCH_DTYPE[dt]
+    layers = [{"w": torch.eye(c, device="cuda").view(c, c, 1, 1).to(td), "b": torch.zeros(c, device="cuda")},
+              {"w": w1.cuda(), "b": b1.cuda()}, {"w": w3.cuda(), "b": b3.cuda()},
+              {"w": torch.ones(8, o, 1, 1, device="cuda").to(td), "b": torch.zeros(8, device="cuda")}]
+    for pinned in (q, q - 1):
+        B.cprune_clear_tile_cache()
+        handle = pipeline.build_net(net, layers, batch, dt, tune=tune)
+        assert tune or handle.layer_fused(q - 1)
+        for graph in (False, True):
+            handle.forward(x.cuda(), use_graph=graph)
+            if not graph:
+                handle.set_layer_variant(pinned, 0)
+                assert not handle.layer_fused(q - 1) and handle.layer_variant(pinned) == 0
+                assert handle.layer_variant(2 * q - 1 - pinned) >= 0
+        for n in (batch, 1):
+            handle.forward(x[:n].cuda())
+            assert _rel(handle.activation(q, n, ref3.shape[1:]), ref3[:n]) < REL[dtype]
+            assert _rel(handle.activation(q - 1, n, ref1.shape[1:]), ref1[:n]) < REL[dtype]
+        handle.close()
+    B.cprune_clear_tile_cache()
