@@ -1865,8 +1865,10 @@ extern "C" int cprune_net_set_layer_variant(cprune_net* net, int layer, int vari
         variant_supports(layer_conv_desc(*net, L, net->max_batch), variant, pair_layout(L, &pair))) {
       CPRUNE_HIP_TRY(hipDeviceSynchronize());
       drop_graphs(net);
-      L.pair_variant = variant;
+      L.pair_variant = L.variant = variant;      // (for this layer alone too, when the pair ends: the same copy)
       L.pair_at.clear();
+      L.timed = true;
+      L.at_batch.clear();
       return CPRUNE_OK;
     }
   }

@@ -239,3 +239,28 @@ def test_layers_of_a_pair_that_ends(dtype, tune):
             assert _rel(handle.activation(q - 1, n, ref1.shape[1:]), ref1[:n]) < REL[dtype]
         handle.close()
     B.cprune_clear_tile_cache()
+
+
+@pytest.mark.parametrize("dtype", sorted(DT))
+def test_a_pinned_variant_outlives_the_pair(dtype):
+    c, o, o1, h, batch = 130, 20, 70, 16, 2
+    dt = DT[dtype]
+    x, w3, w1, b3, b1 = _data(c, o, o1, h, h, batch, dt, 7)
+    ref3 = torch.nn.functional.conv2d(x.double(), w3.double(), b3.double(), 2, 1).clamp(min=0)
+    net, q = _net(c, o, o1, h, h)
+    pinned = 0
+    for v in _variants(dt):
+        handle = _build(net, c, o, w3, w1, b3, b1, batch, dt, o1)
+        assert handle.layer_fused(q - 1)
+        try:
+            handle.set_layer_variant(q, v)
+        except B.CPruneError as e:
+            assert e.status == B.ERR_UNSUPPORTED
+        else:
+            pinned += 1
+            handle.set_layer_variant(q - 1, 0)
+            assert handle.layer_variant(q) == v and handle.layer_variant(q - 1) == 0
+            handle.forward(x.cuda())
+            assert _rel(handle.activation(q, batch, ref3.shape[1:]), ref3) < REL[dtype]
+        handle.close()
+    assert pinned >= 2
