@@ -73,6 +73,34 @@ def run_search(model, a_goal: float, alpha: float, beta: float, tune: Callable, 
 
 # ---- the pieces, on the device ------------------------------------------------------
 
+def paired_layers(net: synth.NetSpec, fused: List[bool], variants: List[int], s2_variants) -> Dict[int, int]:
+    """1x1 / stride 2 layers that run in the launch of the 3x3 / stride 2 layer on the same input (they report no time and no
+    variant of their own) -> that layer.  `fused`, `variants`: what the handle reports per layer; `s2_variants`: the variants
+    that such a launch can run."""
+    out = {}
+    for i, L in enumerate(net.layers):
+        if not (L.kind == "conv" and L.groups == 1 and L.k == 1 and L.stride == 2 and fused[i]):
+            continue
+        for j, M in enumerate(net.layers):
+            if (M.kind == "conv" and M.groups == 1 and M.k == 3 and M.stride == 2 and M.input == L.input
+                    and variants[j] in s2_variants and j not in out.values()):
+                out[i] = j
+                break
+    return out
+
+
+def shared_times(net: synth.NetSpec, times: List[float], pairs: Dict[int, int], shp) -> List[float]:
+    """Layer times with that of a launch of two layers shared between them by their multiply-adds: it is reported whole for
+    the 3x3 layer, and a layer that seems to take no time is one that no search would prune."""
+    out = list(times)
+    for i, j in pairs.items():
+        macs = [shp[q][1] * net.layers[q].k ** 2 for q in (i, j)]      # the same input channels and output map
+        out[i] = times[j] * macs[0] / sum(macs)
+        out[j] = times[j] * macs[1] / sum(macs)
+    return out
+
+
+
 class DeviceSearch:
     """tune / prune / measure for a seeded synthetic network on the GPU.  A model is the dict
     {prunable layer index: filters kept}; every other quantity is derived from it by the
@@ -99,8 +127,14 @@ class DeviceSearch:
         layers, _ = pipeline.prune_net(self.net, self.dparams, self.dtype, keep_override=model)
         handle = pipeline.build_net(self.net, layers, self.batch, self.dtype, tune=True)
         task_of, n_tasks = handle.task_table()
-        lt = handle.layer_times(self.x, iters=10)
         shp = synth.shapes(self.net, model)
+        n = len(self.net.layers)
+        variants = [handle.layer_variant(i) for i in range(n)]
+        s2 = {v for v in set(variants) if v >= 0 and "conv_rows_s2" in B.cprune_tile_variant_name(v, True, self.dtype)}
+        pairs = paired_layers(self.net, [handle.layer_fused(i) for i in range(n)], variants, s2)
+        lt = shared_times(self.net, handle.layer_times(self.x, iters=10), pairs, shp)
+        for i, j in pairs.items():
+            variants[i] = variants[j]      # both are tiles of one program
         members: List[List[int]] = [[] for _ in range(n_tasks)]
         for i, t in enumerate(task_of):
             if t >= 0:
@@ -122,7 +156,7 @@ class DeviceSearch:
         ms = (time.perf_counter() - t0) / self.steps * 1e3
         table = {}
         for t, m in enumerate(members):
-            v = handle.layer_variant(m[0])
+            v = variants[m[0]]
             # kernels without tile variants (first layer, fused depthwise + 1x1) work on 16-filter blocks
             step = B.cprune_variant_prune_step(v, shp[m[0]][1]) if v >= 0 else 16
             table[keys[t]] = (m, {"variant": v, "c_out": shp[m[0]][1], "time_ms": times[t], "impact": impact[t],
