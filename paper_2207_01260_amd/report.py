@@ -9,7 +9,7 @@ the device.  One JSON object per line.
 --only keeps the networks whose name contains NAME (and, with --batch / --dtype, that one run) and
 skips the device ceilings and the single layer: the form a profiler run of one workload uses.  Every line
 carries the tile variant each layer ran (`variants`, -1 for layers without one); --variants pins them (and skips
-the timed selection, which a profiler's per-launch overhead would distort), --first-layer-form pins how a 16-bit
+the timed selection, which a profiler's per-launch overhead would distort), --first-layer-form pins how a
 7x7 first layer runs, so that a profiled run executes the kernels an undisturbed run chose.
 
 For each network and batch: images/s and ms per forward (at batch 1 also with the caches scrubbed
@@ -28,6 +28,7 @@ import torch
 
 from . import binding as B
 from . import pipeline, synth
+from .search import paired_layers
 
 PEAK_TFLOPS = {B.F32: 157.3, B.F16: 2500.0, B.BF16: 2500.0}
 PEAK_GBS = 8000.0
@@ -36,8 +37,26 @@ PEAK_GBS = 8000.0
 def kernel_peak(kernel: str, dtype: int) -> float:
     """Dense MFMA TFLOP/s a kernel (cprune_tile_variant_name) can reach: the kernels on three bf16 parts run an fp32
     product as six bf16 ones."""
-    parts = kernel.startswith(("conv_split", "conv_pw3", "conv_rows_s2", "conv_rows_nchw"))
+    parts = kernel.startswith(("conv_split", "conv_pw3", "conv_rows_s2", "conv_rows_nchw", "conv_stem7_split"))
     return PEAK_TFLOPS[B.BF16] / 6 if dtype == B.F32 and parts else PEAK_TFLOPS[dtype]
+
+
+def layer_kernels(net, handle, dtype, first_layer_form=None):
+    """The kernel every layer of a handle runs in, as far as its peak depends on it: the variant's; for a 1x1 layer in a 3x3
+    layer's launch that layer's; for a 7x7 / stride 2 first layer of a fp32 handle the one made for it.  "" for other layers
+    without a variant of their own (on the fp32 instruction in fp32)."""
+    n = len(net.layers)
+    variants = [handle.layer_variant(i) for i in range(n)]
+    names = [B.cprune_tile_variant_name(v, True, dtype) if v >= 0 else "" for v in variants]
+    s2 = {v for v, name in zip(variants, names) if name.startswith("conv_rows_s2")}
+    for i, j in paired_layers(net, [handle.layer_fused(i) for i in range(n)], variants, s2).items():
+        names[i] = names[j]
+    for i, L in enumerate(net.layers):
+        if (dtype == B.F32 and first_layer_form != 0 and variants[i] < 0 and L.kind == "conv" and L.groups == 1 and L.input < 0
+                and L.c_in <= 3 and (L.k, L.stride, L.pad) == (7, 2, 3) and L.residual is None):
+            names[i] = "conv_stem7_split_kernel"
+    return names
+
 
 DT_NAME = {B.F32: "f32", B.F16: "f16", B.BF16: "bf16"}
 
@@ -93,6 +112,7 @@ def net_report(name, net, cid, batch, dtype, steps, ceilings=None, variants=None
     ms_cold = time_forward_cold(handle, x, min(steps, 20)) if batch == 1 else None
     lt = handle.layer_times(x, iters=10)
     shp = synth.shapes(net, kept_counts)
+    kernels = layer_kernels(net, handle, dtype, first_layer_form)
     es = 4 if dtype == B.F32 else 2
     groups = {}
     for i, (L, t) in enumerate(zip(net.layers, lt)):
@@ -109,8 +129,7 @@ def net_report(name, net, cid, batch, dtype, steps, ceilings=None, variants=None
             kind, fl, by = "fc", 2.0 * batch * cin * hin * win * cout, 0.0
         else:
             kind, fl, by = "pool", 0.0, (moved if t > 0 else 0.0)
-        v = handle.layer_variant(i)
-        peak = kernel_peak(B.cprune_tile_variant_name(v, True, dtype) if v >= 0 else "", dtype)
+        peak = kernel_peak(kernels[i], dtype)
         g = groups.setdefault(kind, {"ms": 0.0, "flop": 0.0, "bytes": 0.0, "launches": 0, "s_at_peak": 0.0})
         g["s_at_peak"] += fl / (peak * 1e12)      # every layer against the peak of the kernel that runs it
         g["ms"] += t; g["flop"] += fl; g["bytes"] += by; g["launches"] += 1 if t > 0 else 0
@@ -167,7 +186,7 @@ def main():
     ap.add_argument("--variants", default="", help="with --only, --batch and --dtype: pin these tile variants (one per layer, "
                                                    "-1 = leave) instead of selecting by timing")
     ap.add_argument("--first-layer-form", type=int, default=None, choices=[0, 1, 2],
-                    help="with --variants: how a 16-bit 7x7 / stride 2 first layer runs (see cprune_net_first_layer_form)")
+                    help="with --variants: how a 7x7 / stride 2 first layer runs (see cprune_net_first_layer_form)")
     args = ap.parse_args()
     steps = 20 if args.quick else 100
     props = torch.cuda.get_device_properties(0)
