@@ -4,7 +4,7 @@
 namespace cprune {
 
 int launch_conv_stem7_f32(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a) {
-  return launch_stem7_split<float>(mb, pool, grid, s, a);
+  return launch_stem7_split(mb, pool, grid, s, a);
 }
 
 }  // namespace cprune

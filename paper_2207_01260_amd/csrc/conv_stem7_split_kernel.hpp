@@ -269,7 +269,6 @@ __global__ __launch_bounds__(128, 2) void conv_stem7_split_kernel(StemArgs a) {
   }
 }
 
-template <typename T>
 inline int launch_stem7_split(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a) {
 #define CPRUNE_STEM7S(MB_, POOL_)                                                                       \
   if (mb == MB_ && pool == POOL_) {                                                                     \

@@ -770,7 +770,7 @@ static int depthwise_nhwc_dispatch(const cprune_conv_desc& d, int cp, const void
         case 321: GOV(3, 2, 1); break;
         case 322: GOV(3, 2, 2); break;
         case 324: GOV(3, 2, 4); break;
-        case 327: GOV(3, 2, 7); break;
+        case 327: if constexpr (sizeof(T) == 4) { GOV(3, 2, 7); } break;      // (16-bit data: 290-940 bytes of scratch a lane)
         case 511: GOV(5, 1, 1); break;
         case 512: GOV(5, 1, 2); break;
         case 514: GOV(5, 1, 4); break;
