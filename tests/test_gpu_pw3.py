@@ -89,11 +89,14 @@ def test_numbers_three_parts_do_not_hold():
     handle.set_layer_variant(0, 0)               # the fp32 instruction
     want = handle.forward(x.cuda()).double().cpu()
     assert not want[0].isfinite().all() and want[1:].isfinite().all()
+    ran = 0
     for v in _variants():
         try:
             handle.set_layer_variant(0, v)
-        except B.CPruneError:                    # built for 16-bit data only
+        except B.CPruneError as e:               # built for 16-bit data only
+            assert e.status == B.ERR_UNSUPPORTED
             continue
+        ran += 1
         got = handle.forward(x.cuda()).double().cpu()
         assert torch.equal(got.isfinite(), want.isfinite()), v
         for n in range(3):
@@ -104,4 +107,5 @@ def test_numbers_three_parts_do_not_hold():
                 assert not got[n, 7].any() and not tiny.any()
                 continue
             assert float((got[n, 7][ok[7]] - tiny).norm() / tiny.norm()) < 2e-6, (v, n)
+    assert ran == 6
     handle.close()

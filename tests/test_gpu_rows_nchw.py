@@ -17,6 +17,13 @@ def _variants(dtype):
     return [v for v in range(B.cprune_num_tile_variants()) if "conv_rows_nchw" in B.cprune_tile_variant_name(v, False, dtype)]
 
 
+def _runs(v, dtype, c):
+    """Whether a variant runs a layer of c channels: a chunk of 32 for each wavefront that shares a strip, and in fp32 one filter block,
+    at most six rows and two wavefronts."""
+    blocks, rows, waves = (int(q) for q in B.cprune_tile_variant_name(v, False, dtype).rstrip(">").split(", ")[1:])
+    return (waves == 1 or waves <= (c + 31) // 32) and (dtype != B.F32 or (blocks == 1 and rows <= 6 and waves <= 2))
+
+
 @pytest.mark.parametrize("dtype", sorted(DT))
 @pytest.mark.parametrize("cfg", [
     # images, c_in, filters, height, width, shortcut, activation
@@ -45,8 +52,9 @@ def test_every_variant(cfg, dtype):
             try:
                 y = B.cprune_conv2d_bn_relu(d, xd, wd, bd, rd, v)
             except B.CPruneError as e:
-                assert e.status == B.ERR_UNSUPPORTED
+                assert e.status == B.ERR_UNSUPPORTED and not _runs(v, dt, c), v
                 continue
+            assert _runs(v, dt, c), v
             err = float((y.double().cpu() - ref).norm() / ref.norm())
             assert err < REL[dtype], (B.cprune_tile_variant_name(v, False, dt), shift, err)
 
@@ -83,13 +91,17 @@ def test_numbers_three_parts_do_not_hold():
     d = B.conv_desc(x.shape, wt.shape, 1, 1, 1, B.F32, B.ACT_NONE)
     want = B.cprune_conv2d_bn_relu(d, x.cuda(), wt, tile_variant=0).double().cpu()      # the fp32 instruction
     assert not want[0].isfinite().all() and want[1:].isfinite().all()
+    ran = 0
     for v in _variants(B.F32):
         try:
             got = B.cprune_conv2d_bn_relu(d, x.cuda(), wt, tile_variant=v).double().cpu()
-        except B.CPruneError:
+        except B.CPruneError as e:
+            assert e.status == B.ERR_UNSUPPORTED and not _runs(v, B.F32, c), v
             continue
+        ran += 1
         assert torch.equal(got.isfinite(), want.isfinite()), v
         for n in range(3):
             ok = want[n].isfinite()
             # 630 terms in fp32, in other orders
             assert float((got[n][ok] - want[n][ok]).norm() / want[n][ok].norm()) < 2e-6, (v, n)
+    assert ran == 5                                  # one block; 2 and 4 rows alone or shared by two, 6 rows

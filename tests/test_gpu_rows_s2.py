@@ -165,17 +165,21 @@ def test_numbers_three_parts_do_not_hold():
     handle.set_layer_variant(0, 0)                   # the fp32 instruction
     want = handle.forward(x.cuda()).double().cpu()
     assert not want[0].isfinite().all() and want[1:].isfinite().all()
+    ran = 0
     for v in _variants(B.F32):
         try:
             handle.set_layer_variant(0, v)
-        except B.CPruneError:
+        except B.CPruneError as e:
+            assert e.status == B.ERR_UNSUPPORTED
             continue
+        ran += 1
         got = handle.forward(x.cuda()).double().cpu()
         assert torch.equal(got.isfinite(), want.isfinite()), v
         for n in range(3):
             ok = want[n].isfinite()
             # 630 terms in fp32, in other orders
             assert float((got[n][ok] - want[n][ok]).norm() / want[n][ok].norm()) < 2e-6, (v, n)
+    assert ran == 3                                  # one block, three chunks: 4 rows alone or shared by two, 2 shared by two
     handle.close()
 
 
