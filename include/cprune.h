@@ -365,7 +365,9 @@ int cprune_net_layer_fused(const cprune_net* net, int layer, int* fused_out);
  * map, can run in that layer's launch: cprune_net_create decides, tune = 1 by timing, tune = 0 by size (small layers).  Both activations are
  * stored as always; cprune_net_layer_fused reports 1 for the 1x1 conv and cprune_net_layer_variant -1, its time is
  * part of the other layer's.  cprune_net_set_layer_variant on the 1x1 conv, or on the 3x3 conv with a variant of another
- * kernel, gives each its own launch again.) */
+ * kernel, gives each its own launch again.  In a handle created with tune = 0, a variant of the pair's kernel set on the 3x3 conv
+ * makes the pair, unless one was set on the 1x1 conv before: the variants that a timed handle reports, -1 left out, run the same
+ * kernels in another handle.) */
 /* When the input of such a depthwise conv is a 1x1 / stride 1 conv that nobody else reads (the
  * expansion of an inverted-residual block of MobileNetV2 / MnasNet1.0, Sec. 4.1 and Table 1 of the
  * paper; its filters are the ones Sec. 3.5 prunes), and the 1x1

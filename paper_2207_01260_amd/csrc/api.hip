@@ -456,6 +456,7 @@ struct NetLayer {
   int pair_by = -1;           // that 1x1 layer: index of the 3x3 layer whose launch it runs in now, or -1
   int pair_with = -1;         // 3x3 layer: the 1x1 layer that could run in its launch
   int pair_variant = -1;      // ... variant of the pair at max_batch
+  bool pinned = false;        // the caller has named the variant
   std::vector<int> pair_at;   // ... and at a smaller batch (-1: not yet)
   int fuse_stem = -1;         // 3x3 conv: index of the first layer (on the image) computed inside its kernel, or -1
   int stem_reader = -1;       // first layer that may run inside the 3x3 conv stem_reader's kernel
@@ -490,6 +491,7 @@ struct cprune_net {
   int in_c, in_h, in_w, in_cp, max_batch, dtype;
   std::vector<void*> allocs;
   void* x_cl = nullptr;       // the network input, channels-last
+  bool tuned = false;         // forms and variants were timed at creation
   bool convert_input = true;  // false when every reader of the input takes the caller's NCHW tensor itself
   void* ws = nullptr;
   size_t ws_bytes = 0;
@@ -1051,6 +1053,18 @@ static void set_pair(cprune_net* net, NetLayer& L, bool on) {
   S.pair_by = on ? (int)(&L - net->layers.data()) : -1;
 }
 
+// The copies a pair reads are those of the row-strip and of the 1x1 kernel.
+static int any_pw3() {
+  int v = 0;
+  while (!variant(v).pw3) ++v;
+  return v;
+}
+
+static int pack_pair(cprune_net* net, NetLayer& L, int rows_variant, hipStream_t s) {
+  const int rc = pack_for(net, L, rows_variant, s);
+  return rc != CPRUNE_OK ? rc : pack_for(net, net->layers[L.pair_with], any_pw3(), s);
+}
+
 // Whether an untimed pair (3x3 layer d, 1x1 layer S) runs in one launch: up to 0.3 GFLOP in fp32, 0.6 in 16-bit data.  250 random pairs a
 // type, the layers apart / in one launch, untimed choices both: below the line 1.43 times the time on average (0.91 at worst), 16-bit
 // 1.50 (0.88); above it 0.92 (0.41: 256 -> 56 and 440 at 40x40, batch 6, 22.5 / 51 us), 16-bit 0.92 (0.49): there the 1x1 kernel by
@@ -1100,12 +1114,9 @@ static int make_pair(cprune_net* net, int i, bool tune, hipStream_t s) {
   }
   if (known == -1 || (!tune && !pair_pays(d, S))) return CPRUNE_OK;
   if (!tune && !(L.variant >= 0 && variant(L.variant).rows)) return CPRUNE_OK;
-  // the copies it reads are those of the row-strip and the 1x1 kernel
-  int v3 = 0, v1 = 0;
+  int v3 = 0;
   while (!(variant(v3).rows == 1 && variant(v3).stride == 2)) ++v3;
-  while (!variant(v1).pw3) ++v1;
-  int rc = pack_for(net, L, v3, s);
-  if (rc == CPRUNE_OK) rc = pack_for(net, S, v1, s);
+  int rc = pack_pair(net, L, v3, s);
   if (rc != CPRUNE_OK) return rc;
   const ConvPair pair = pair_of(net, L);
   const ConvLayout lay = pair_layout(L, &pair);
@@ -1147,7 +1158,7 @@ static int make_pair(cprune_net* net, int i, bool tune, hipStream_t s) {
   L.pair_variant = best_v;
   if (best_v >= 0) set_pair(net, L, true);
   drop_copies(net, L, best_v >= 0 ? best_v : L.variant);
-  drop_copies(net, S, best_v >= 0 ? v1 : S.variant);
+  drop_copies(net, S, best_v >= 0 ? any_pw3() : S.variant);
   return CPRUNE_OK;
 }
 
@@ -1176,7 +1187,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
   if (!dtype_ok(dtype)) return CPRUNE_ERR_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
   cprune_net* net = new cprune_net();
-  net->in_c = in_c; net->in_h = in_h; net->in_w = in_w; net->max_batch = max_batch; net->dtype = dtype;
+  net->in_c = in_c; net->in_h = in_h; net->in_w = in_w; net->max_batch = max_batch; net->dtype = dtype; net->tuned = tune != 0;
   net->in_cp = round_up_vec(in_c, dtype);
   net->layers.resize(n_layers);
   const size_t es = dtype_size(dtype);
@@ -1858,13 +1869,22 @@ extern "C" int cprune_net_set_layer_variant(cprune_net* net, int layer, int vari
   NetLayer& L = net->layers[layer];
   if (!(L.d.kind == CPRUNE_LAYER_FC || (L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1))) return CPRUNE_ERR_INVALID_ARG;
   if (L.fuse_dw >= 0 || L.fuse_stem >= 0 || L.fused_away) return CPRUNE_ERR_INVALID_ARG;   // runs inside a fused kernel: no variants
-  if (L.pair >= 0) {
-    // a variant of the kernel that runs pairs keeps the pair; any other means a launch of its own
+  if (L.pair >= 0 || (L.pair_with >= 0 && !net->tuned && !net->layers[L.pair_with].pinned)) {
+    // a variant of the kernel that runs pairs keeps the pair; any other means a launch of its own.  In an untimed handle it also makes
+    // the pair, unless the 1x1 layer has been given a variant of its own: how the choices of a timed handle are applied to another
+    NetLayer& S = net->layers[L.pair_with];
     const ConvPair pair = pair_of(net, L);
+    ConvLayout lay = pair_layout(L, &pair);
+    lay.w_wave = lay.w_rows3 = L.w;                    // (only whether they are set matters here)
     if (variant >= 0 && variant < num_variants() && cprune::variant(variant).rows &&
-        variant_supports(layer_conv_desc(*net, L, net->max_batch), variant, pair_layout(L, &pair))) {
+        variant_supports(layer_conv_desc(*net, L, net->max_batch), variant, lay)) {
+      const int rc = pack_pair(net, L, variant, nullptr);
+      if (rc != CPRUNE_OK) return rc;
       CPRUNE_HIP_TRY(hipDeviceSynchronize());
       drop_graphs(net);
+      set_pair(net, L, true);
+      drop_copies(net, L, variant);
+      drop_copies(net, S, any_pw3());
       L.pair_variant = L.variant = variant;      // (for this layer alone too, when the pair ends: the same copy)
       L.pair_at.clear();
       L.timed = true;
@@ -1895,6 +1915,7 @@ extern "C" int cprune_net_set_layer_variant(cprune_net* net, int layer, int vari
   }
   drop_copies(net, L, variant);
   L.variant = variant;
+  L.pinned = true;
   L.timed = true;
   L.at_batch.clear();
   return CPRUNE_OK;

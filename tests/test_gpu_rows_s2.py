@@ -268,3 +268,48 @@ def test_a_pinned_variant_outlives_the_pair(dtype):
             assert _rel(handle.activation(q, batch, ref3.shape[1:]), ref3) < REL[dtype]
         handle.close()
     assert pinned >= 2
+
+
+@pytest.mark.parametrize("dtype", sorted(DT))
+@pytest.mark.parametrize("batch", [2, 32])
+def test_choices_of_a_timed_handle_applied_to_another(dtype, batch):
+    """Both forms of a layer pair too large to be paired untimed, and of a small one: the variants a handle reports, set on an untimed one."""
+    c, o, o1, h = 160, 72, 64, 28
+    dt = DT[dtype]
+    x, w3, w1, b3, b1 = _data(c, o, o1, h, h, batch, dt, 8)
+    conv = torch.nn.functional.conv2d
+    ref3 = conv(x.double(), w3.double(), b3.double(), 2, 1).clamp(min=0)
+    ref1 = conv(x.double(), w1.double(), b1.double(), 2, 0).clamp(0, 6)
+    net, q = _net(c, o, o1, h, h)
+    strips = next(v for v in _variants(dt) if _name(v, dt).endswith(" 1, 4, 1>"))
+    pw = next(v for v in range(B.cprune_num_tile_variants()) if "conv_pw3" in _name(v, dt) and _name(v, dt).endswith("1, 2, true>"))
+    for choices, fused in (([-1, strips], True), ([pw, strips], False), ([pw, 0], False)):
+        handle = _build(net, c, o, w3, w1, b3, b1, batch, dt, o1)
+        for layer, v in zip((q - 1, q), choices):
+            if v >= 0:
+                handle.set_layer_variant(layer, v)
+        assert handle.layer_fused(q - 1) == fused
+        assert [handle.layer_variant(q - 1), handle.layer_variant(q)] == choices
+        for graph in (False, True):
+            handle.forward(x.cuda(), use_graph=graph)
+            assert _rel(handle.activation(q, batch, ref3.shape[1:]), ref3) < REL[dtype]
+            assert _rel(handle.activation(q - 1, batch, ref1.shape[1:]), ref1) < REL[dtype]
+        handle.close()
+    # a timed handle's own, whatever they are
+    td = B.TORCH_DTYPE[dt]
+    layers = [{"w": torch.eye(c, device="cuda").view(c, c, 1, 1).to(td), "b": torch.zeros(c, device="cuda")},
+              {"w": w1.cuda(), "b": b1.cuda()}, {"w": w3.cuda(), "b": b3.cuda()},
+              {"w": torch.ones(8, o, 1, 1, device="cuda").to(td), "b": torch.zeros(8, device="cuda")}]
+    B.cprune_clear_tile_cache()
+    timed = pipeline.build_net(net, layers, batch, dt, tune=True)
+    want = [(timed.layer_variant(i), timed.layer_fused(i)) for i in range(4)]
+    outputs = []
+    for handle in (timed, _build(net, c, o, w3, w1, b3, b1, batch, dt, o1)):
+        for i, (v, _) in enumerate(want):
+            if v >= 0 and handle is not timed:
+                handle.set_layer_variant(i, v)
+        assert [(handle.layer_variant(i), handle.layer_fused(i)) for i in range(4)] == want
+        handle.forward(x.cuda())
+        outputs.append([handle.activation(i, batch, ref.shape[1:]).clone() for i, ref in ((q, ref3), (q - 1, ref1))])
+        handle.close()
+    assert all(torch.equal(a, b) for a, b in zip(*outputs))
