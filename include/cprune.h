@@ -190,18 +190,22 @@ typedef struct {
  * sched n > 0: the (tile, reduction slab) work is laid out in one line and cut
  * into equal runs for n * 256 work-groups; tiles cut between runs go through the
  * caller's scratch and are summed in run order (deterministic).  sched -1: one spatial block of at
- * most tile_p pixels per work-group.  Three kinds, told apart by cprune_tile_variant_name: the patch
+ * most tile_p pixels per work-group.  Four kinds, told apart by cprune_tile_variant_name: the patch
  * kernels (conv_patch*: 3x3 layers, channels-last inside a network handle only, unsupported through
- * the NCHW call), the row-strip kernel (conv_rows_kernel in 16-bit, conv_split_rows_kernel in fp32 data:
- * 3x3 / stride 1 / pad 1 layers of a handle; its last template argument, which depends on the map, is not
- * part of the name here; tile_m is at least the 32 filters that the two wavefronts of a SIMD hold) and the split kernel (conv_split_kernel: any window at stride 1 or 2).  The split
+ * the NCHW call), the row-strip kernels (conv_rows_kernel in 16-bit, conv_split_rows_kernel in fp32 data:
+ * 3x3 / stride 1 / pad 1 layers of a handle; their last template argument, which depends on the map, is not
+ * part of the name here; conv_rows_s2_kernel: likewise at stride 2; conv_rows_nchw_kernel: 3x3 / stride 1 / pad 1 through
+ * cprune_conv2d_bn_relu, outputs below 2 GiB, no scratch; tile_m is at least the 32 filters that the two wavefronts of a SIMD hold),
+ * the 1x1 kernel (conv_pw3_kernel: 1x1 layers of a handle at stride 1 or 2) and the split kernel (conv_split_kernel: any window at stride 1 or 2).  The split
  * kernel multiplies fp32 data as three 16-bit parts per number on the 16-bit matrix cores; it runs fp32
  * layers of at least 16 terms per output, where its error is no larger than the fp32 instruction's, and
- * redoes with that instruction what three parts do not hold (infinities, results below 2^-50; inputs or
- * weights below 2^-133, all denormal, count as zero in larger sums).  It runs through
+ * redoes with that instruction what three parts do not hold (infinities, results below 2^-50 but not zero; inputs or
+ * weights below 2^-133, all denormal, count as zero in larger sums).  Numbers below 2^-110 lose their last bits where the
+ * other factor is 2^59 or more, and a sum that comes out as zero is not redone.  It runs through
  * cprune_conv2d_bn_relu, where each call packs the weights into the caller's scratch, in fp32 and 16-bit
  * data, and in fp32 handles, which keep packed copies for the layers that run it.  The fp32 row-strip
- * kernel multiplies in the same way, within the same limits, with a packed copy of its own.
+ * kernels, the 1x1 kernel and the kernel of a 7x7 / stride 2 first layer (cprune_net_first_layer_form) multiply fp32 data in the
+ * same way, within the same limits, in a handle from packed copies of their own.
  * sched -2: likewise channels-last only, for layers whose reduction is one contiguous run
  * per pixel (1x1 stride 1, fully connected): 16 filters x tile_p pixels per work-group, the
  * wavefronts of the group splitting the reduction; chosen when pixels are few.

@@ -49,8 +49,9 @@ static DescKey key_of(const cprune_conv_desc& d, const ConvLayout& lay) {
 }
 static std::mutex g_cache_mutex;
 static std::map<DescKey, int> g_cache;
-// Untimed choices of the boundary's layout, which every call of an untimed shape needs: the estimates take 4-6 us of the caller's
-// thread, a look here 0.2.  They depend on the shape alone; at most kMaxChoices are kept.
+// Untimed choices of the boundary's layout, as cprune_cached_tile gives them (the Python entry asks it before each call, to size the
+// scratch): the estimates take 4-6 us of the caller's thread, a look here 0.2.  They depend on the shape alone; at most kMaxChoices are
+// kept.  A call with variant -1 chooses among what its scratch allows, and makes the estimates itself.
 static std::map<DescKey, int> g_choices;
 constexpr size_t kMaxChoices = 1024;
 // likewise the variant a pair of layers in one launch runs, or -1 where the layers apart were faster

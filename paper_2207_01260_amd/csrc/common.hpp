@@ -59,7 +59,8 @@ struct TileVariant {
   // Filters of the box the variant is pruned by.  A wavefront of the row-strip kernel holds one to four 16-filter blocks and a SIMD
   // two wavefronts; a block less in one of two leaves the layer the time of the other, so one block is never a step: 3x3 on 128
   // channels at 56x56, batch 8, fp32, 128 / 112 / 96 filters on 8 rows 39.4 / 37.7 / 36.6 us, 8 rows shared by two 41.5 / 40.7 / 31.5, 4 rows
-  // 43.9 / 42.7 / 33.7; bf16 on 4 rows 21.5 / 21.1 / 16.9.
+  // 43.9 / 42.7 / 33.7; bf16 on 4 rows 21.5 / 21.1 / 16.9.  At stride 2 fp32, batch 32, 4 rows, 128 / 112 / 96 / 80 / 64 filters 80 / 76 / 58 / 59 / 40,
+  // batch 8, 2 rows shared by two 28.1 / 27.6 / 21.9 / 21.6 / 15.5; in the boundary's layout, batch 8, 4 rows 56 / 50 / 40 / 40 / 28.
   int step_m() const { return rows && mb == 1 ? 32 : tile_m(); }
   int tile_p() const { return wn * nb * 16; }
 };

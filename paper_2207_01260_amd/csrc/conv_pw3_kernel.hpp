@@ -15,7 +15,8 @@
 // random layers of 0.01-4 GFLOP, timed choice before / now 1.29 times on average, untimed 1.50.  Deep or not: 739 -> 58 at 28x28
 // stride 2, batch 30, 9.6 / 12.3; 29 -> 232 at 56x56, batch 28, 32.0 / 23.8.  bf16, 80 random layers: timed choice 1.23 times as fast as before,
 // untimed 1.44 (865 -> 78 at 56x56 stride 2, batch 28, 12 us; 16 -> 292 at 56x56, batch 55, stays on the short-reduction kernel, 35.5 / 40.9).  What bounds it: launch, first loads and stores (some 4 us);
-// 96 -> 385 moves 24 MB, 5 us at the copy rate; 320 -> 1280 the matrix pipes (35 %) and the wait for weights.
+// 96 -> 385 moves 24 MB, 5 us at the copy rate.  Counters, fp32: matrix pipes busy 16-26 %, 320 -> 1280 44, wavefronts waiting for memory or the
+// barrier 37-60 % of their cycles; bf16 5 and 59.
 #pragma once
 #include "conv_rows_s2_kernel.hpp"
 

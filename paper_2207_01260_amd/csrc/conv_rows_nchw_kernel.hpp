@@ -11,7 +11,8 @@
 // Measured, the best other kernel (the split kernel with its packing launch, or the general one) / this one (us): fp32 128 -> 83 at 56x56,
 // batch 8, 44 / 35.5 (135 TFLOP/s); 64 -> 45 at 32x32, one image, 10.4 / 6.6; 205 -> 13 at 110x110, batch 9, 68 / 46; bf16 128 -> 83 24 / 17.3;
 // 64 -> 45 10.6 / 4.9; 322 -> 167 at 44x44, one image, 26 / 16.  What bounds it: one image, launch and a chain of loads, LDS, MFMAs and stores;
-// large layers in fp32 the matrix pipes (33 %) and cutting, in 16-bit data the eight loads of a number per row and chunk.  16-bit weights
+// large layers in fp32 cutting and the matrix pipes (128 -> 83: a third of the rate of six bf16 products; counters: vector ALU busy 59 %, matrix
+// pipes 51, waiting 19), in 16-bit data the eight loads of a number per row and chunk (vector ALU 40 %, matrix pipes 16, waiting 35).  16-bit weights
 // of an odd channel count come as whole dwords shifted into place: a load per number (eighteen a thread) made 495 -> 276 at 41x41 48 us, now 28.
 #pragma once
 #include "conv_rows_s2_kernel.hpp"

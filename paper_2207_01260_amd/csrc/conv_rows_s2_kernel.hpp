@@ -11,9 +11,9 @@
 // Measured, bf16 (us), the best other kernel / this one: batch 32, 64 -> 67 at 56x56 12.4 / 12.2, 256 -> 158 at 14x14 10.1 / 7.5; one image,
 // 128 -> 173 at 28x28 5.2 / 3.9, 256 -> 158 7.6 / 4.3; with the 1x1 layer beside it (two launches / one): batch 32, 64 -> 67 and 128 at 56x56
 // 20.0 / 15.8, 128 -> 173 and 256 17.7 / 15.0, 256 -> 158 and 512 16.5 / 12.6; one image 8.0 / 4.0, 9.6 / 5.3, 12.5 / 4.4; 45 random layers, timed
-// choice 1.33 times as fast as before, fp32 1.13.  What bounds it: the vector cache: 2 R + 1 rows of two operands and nine taps a chunk, a
-// kilobyte each, for 9 R MFMAs per filter block, which is why two and three blocks per wavefront win at batch 32; in fp32 cutting four
-// operands per output row.  Four blocks (a wavefront per SIMD) were never the fastest.
+// choice 1.33 times as fast as before, fp32 1.13.  What bounds it: loads: 2 R + 1 rows of two operands and nine taps a chunk, a
+// kilobyte each from the vector cache, for 9 R MFMAs per filter block, which is why two and three blocks per wavefront win at batch 32 (counters there,
+// bf16: wavefronts waiting for memory 46-51 % of their cycles, matrix pipes busy 13-15 %); in fp32 also cutting, four operands per output row.  Four blocks (a wavefront per SIMD) were never the fastest.
 #pragma once
 #include "conv_rows_kernel.hpp"
 
