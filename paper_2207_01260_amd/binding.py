@@ -666,7 +666,8 @@ class Net:
                "cprune_net_block_form")
 
     def first_layer_form(self, form: int):
-        """How a 16-bit 7x7 / stride 2 first layer runs: 0 general kernels, 1 its own kernel, 2 with the max-pool."""
+        """How a 7x7 / stride 2 first layer runs: 0 general kernels, 1 its own kernel (16-bit handles), 2 with the max-pool inside
+        and no conv map stored."""
         _check(lib().cprune_net_first_layer_form(self._h, C.c_int(form)), "cprune_net_first_layer_form")
 
     def fuse_first_layers(self, enable: bool):

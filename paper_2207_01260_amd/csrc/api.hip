@@ -1158,6 +1158,7 @@ static int make_pair(cprune_net* net, int i, bool tune, hipStream_t s) {
   }
   L.pair_variant = best_v;
   if (best_v >= 0) set_pair(net, L, true);
+  CPRUNE_HIP_TRY(hipStreamSynchronize(s));      // (copies may still be on their way)
   drop_copies(net, L, best_v >= 0 ? best_v : L.variant);
   drop_copies(net, S, best_v >= 0 ? any_pw3() : S.variant);
   return CPRUNE_OK;
@@ -1442,7 +1443,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
   // caller that can do without the conv map asks for form 2.  With the general kernels' fp32 instruction / kernel and pool apart / one
   // kernel and the conv map / one kernel (us): 64 filters at 224x224, 32 images 121 / 91 / 69 / 62, 1 15.6 / 9.5 / 9.5 / 8.6; 96, 8 images 56 /
   // 44 / 36 / 32; 64 at 16x16, 128 images 14.7 / 9.5 / 9.4 / 8.9; 31 sizes in all: one kernel and the map at most the time of the fp32
-  // instruction (8.6 / 8.6 at worst) and of the two apart, except 10 filters at 29x96, 33 images 7.7 / 8.6, and 92 at 22x255, 9 images 11.3 / 14.2.
+  // instruction (8.6 / 8.6 at worst) and, to 0.4 us, of the two apart, except 10 filters at 29x96, 33 images 7.7 / 8.6, and 92 at 22x255, 9 images 11.3 / 14.2.
   for (int i = 0; i < n_layers && rc == CPRUNE_OK; ++i) {
     NetLayer& L = net->layers[i];
     const cprune_layer_desc& d = L.d;
