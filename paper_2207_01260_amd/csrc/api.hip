@@ -1871,7 +1871,7 @@ extern "C" int cprune_net_set_layer_variant(cprune_net* net, int layer, int vari
   NetLayer& L = net->layers[layer];
   if (!(L.d.kind == CPRUNE_LAYER_FC || (L.d.kind == CPRUNE_LAYER_CONV && L.d.groups == 1))) return CPRUNE_ERR_INVALID_ARG;
   if (L.fuse_dw >= 0 || L.fuse_stem >= 0 || L.fused_away) return CPRUNE_ERR_INVALID_ARG;   // runs inside a fused kernel: no variants
-  if (L.pair >= 0 || (L.pair_with >= 0 && !net->tuned && !net->layers[L.pair_with].pinned)) {
+  if (L.pair >= 0 || (L.pair_with >= 0 && !net->tuned && !net->layers[L.pair_with].pinned && net->layers[L.pair_with].pair_by < 0)) {
     // a variant of the kernel that runs pairs keeps the pair; any other means a launch of its own.  In an untimed handle it also makes
     // the pair, unless the 1x1 layer has been given a variant of its own: how the choices of a timed handle are applied to another
     NetLayer& S = net->layers[L.pair_with];

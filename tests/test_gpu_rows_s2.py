@@ -313,3 +313,37 @@ def test_choices_of_a_timed_handle_applied_to_another(dtype, batch):
         outputs.append([handle.activation(i, batch, ref.shape[1:]).clone() for i, ref in ((q, ref3), (q - 1, ref1))])
         handle.close()
     assert all(torch.equal(a, b) for a, b in zip(*outputs))
+
+
+@pytest.mark.parametrize("dtype", sorted(DT))
+def test_one_1x1_layer_between_two(dtype):
+    """Two 3x3 layers on the input of one 1x1 layer: it runs in one launch at most, whichever 3x3 layer is given a variant of that kernel."""
+    c, o, o1, h, batch = 130, 20, 70, 16, 2
+    dt = DT[dtype]
+    x, w3, w1, b3, b1 = _data(c, o, o1, h, h, batch, dt, 9)
+    conv = torch.nn.functional.conv2d
+    ref3 = conv(x.double(), w3.double(), b3.double(), 2, 1).clamp(min=0)
+    ref1 = conv(x.double(), w1.double(), b1.double(), 2, 0).clamp(0, 6)
+    net = synth.NetSpec("s2two", c, h, h)
+    a = net.add(synth.Layer("conv", -1, c, c, k=1, stride=1, pad=0, act=synth.ACT_NONE, name="a"))
+    p = net.add(synth.Layer("conv", a, c, o1, k=1, stride=2, pad=0, act=synth.ACT_RELU6, name="p"))
+    qs = [net.add(synth.Layer("conv", a, c, o, k=3, stride=2, pad=1, act=synth.ACT_RELU, name=f"q{i}")) for i in range(2)]
+    net.add(synth.Layer("conv", qs[1], o, 8, k=1, stride=1, pad=0, act=synth.ACT_NONE, name="z"))
+    td = B.TORCH_DTYPE[dt]
+    three = {"w": w3.cuda(), "b": b3.cuda()}
+    layers = [{"w": torch.eye(c, device="cuda").view(c, c, 1, 1).to(td), "b": torch.zeros(c, device="cuda")}, {"w": w1.cuda(), "b": b1.cuda()},
+              three, three, {"w": torch.ones(8, o, 1, 1, device="cuda").to(td), "b": torch.zeros(8, device="cuda")}]
+    B.cprune_clear_tile_cache()
+    handle = pipeline.build_net(net, layers, batch, dt, tune=False)
+    strips = next(v for v in _variants(dt) if _name(v, dt).endswith(" 1, 4, 1>"))
+    for order in (qs, qs[::-1], [p]):
+        for layer in order:
+            handle.set_layer_variant(layer, strips if layer != p else 0)
+        handle.forward(x.cuda())
+        assert _rel(handle.activation(p, batch, ref1.shape[1:]), ref1) < REL[dtype]
+        for q in qs:
+            assert handle.layer_variant(q) == strips
+            assert _rel(handle.activation(q, batch, ref3.shape[1:]), ref3) < REL[dtype]
+        times = handle.layer_times(x.cuda())
+        assert all(times[q] > 0 for q in qs) and bool(handle.layer_fused(p)) == (order != [p]) == (times[p] == 0)
+    handle.close()
