@@ -723,7 +723,11 @@ int launch_gavgpool_nhwc(const void* x, int n, int cp, int hw, int dt, void* y, 
 // Outputs per thread.  A long run loads less per output, a short one leaves more threads: with few vectors of output
 // (`vecs` = pixels times channel vectors) the kernel's time is one thread's, with many it is the loads'.  Sevens, made
 // for the widths 7, 14, 28 and 56, only where they leave little undone at the row's end
-// (400 at 15x15, bf16: 8.2 us in fours, 10.1 in sevens; 200 at 20x20: 8.1 and 7.5).  us for runs of 1 / 2 / 4 / 7, batch
+// (400 at 15x15, bf16: 8.2 us in fours, 10.1 in sevens; 200 at 20x20: 8.1 and 7.5), and not on input rows over 40 KB, where window rows
+// lie too many threads apart (584 at 28x28, batch 33, fp32, 64 KB, fours / sevens 29 / 36; 5x5 on 598 at 56x56, batch 3, 19 / 25; 5x5 on
+// 16-bit data has no such case: 310 at 112x112, batch 4, 69 KB, 33 / 31).  At stride 2 fours from where they are
+// well over a work-group a unit (110 at 64x64, batch 10, fp32, 280k vectors, 1.1 groups, twos / fours 5.2 / 6.8).  800 random layers a
+// type, window and stride: 1.00-1.02 times the best run's time on average.  us for runs of 1 / 2 / 4 / 7, batch
 // 64 unless said:
 //   3x3, fp32:  829 at 7x7 (652k) 11.2 / 9.1 / 6.9 / 6.3; 374 at 14x14, batch 16 (301k) 5.1 / 4.4 / 4.3 / 4.1;
 //               829 at 7x7, batch 16 (163k) 3.9 / 3.5 / 3.3 / 3.9; 400 at 14x14, batch 4 (78k) 3.0 / 2.7 / 3.1 / 3.7
@@ -734,11 +738,12 @@ int launch_gavgpool_nhwc(const void* x, int n, int cp, int hw, int dt, void* y, 
 //               400 at 14x14, batch 4 (78k) 4.8 / 3.7 / 4.2 / 5.1; 900 at 7x7, batch 4 (45k) 3.4 / 3.6 / 4.1 / 5.1
 //   5x5, bf16:  374 at 14x14, batch 16 (301k) 9.1 / 7.3 / 7.0 / 6.5; 900 at 7x7, batch 4 (45k) 3.4 / 4.1 / 5.1 / 6.3
 //   5x5 / stride 2, bf16: 300 to 11x11, batch 48 (441k) 12.3 / 9.8 / 7.9 / 10.4; 374 to 7x7, batch 16 (75k) 4.8 / 4.4 / 5.6 / 7.0
-static int depthwise_run(long vecs, int wo, int k, int stride, bool f32) {
+static int depthwise_run(long vecs, int wo, int k, int stride, bool f32, size_t row_bytes) {
   const int by7 = (wo + 6) / 7 * 7, by4 = (wo + 3) / 4 * 4;
-  const bool sevens = stride == 1 ? by7 * 5 <= by4 * 6 : k == 3 && f32 && wo % 7 == 0;
-  const long full = k == 3 && !f32 && stride == 1 ? 512 : stride == 2 && k == 3 ? 256 : 128;   // thousands of vectors
-  if (sevens && vecs >= (stride == 2 ? 384L : full < 256 ? 256L : full) * 1024) return 7;
+  bool sevens = stride == 1 ? by7 * 5 <= by4 * 6 : k == 3 && f32 && wo % 7 == 0;
+  if (row_bytes > 40 * 1024 && (f32 || k == 3)) sevens = false;
+  const long full = k == 3 && (stride == 2 || !f32) ? 384 : 128;   // thousands of vectors
+  if (sevens && vecs >= (k == 3 && stride == 1 && !f32 ? 512L : 256L) * 1024) return 7;
   if (vecs >= full * 1024) return 4;
   return vecs >= 64L * 1024 ? 2 : 1;
 }
@@ -751,7 +756,7 @@ static int depthwise_nhwc_dispatch(const cprune_conv_desc& d, int cp, const void
   // vectorised kernel: 3x3 and 5x5 at stride 1 or 2, channel stride a whole number of vectors
   if ((d.kh == 3 || d.kh == 5) && (d.stride == 1 || d.stride == 2) && cp % V == 0) {
     const long per_row = (long)d.n * ho * (cp / (d.kh == 5 ? DwVec<T, 5>::V : V));
-    const int tx = depthwise_run(per_row * wo, wo, d.kh, d.stride, sizeof(T) == 4);
+    const int tx = depthwise_run(per_row * wo, wo, d.kh, d.stride, sizeof(T) == 4, (size_t)d.w * cp * sizeof(T));
     const int xblocks = (wo + tx - 1) / tx;
     const long total = per_row * xblocks;
     const size_t xb = (size_t)d.n * d.h * d.w * cp * sizeof(T);
