@@ -88,10 +88,15 @@ static bool rows_pay(const cprune_conv_desc& d, const ConvLayout& lay) {
   if (!lay.nhwc) {
     // no more than 5.5 GFLOP (45 -> 364 at 42x42, batch 29, fp32 105 / 121 us; in 16-bit data 10 from 64 channels up: 105 -> 60 at 43x43, batch
     // 30, bf16 26 / 20), few channels (fp32 4 -> 110 at 44x44, batch 5, 7.9 / 9.6), or, in fp32, a long chain of chunks under a small layer (247 ->
-    // 13 at 8x8, batch 29, 13.8 / 15.6).  130 random layers a type: the untimed choice is 1.06 times the time of the timed one on average.
+    // 13 at 8x8, batch 29, 13.8 / 15.6; 141 -> 13 at 12x12, one image, 10.3 / 12.2).  Over 1 GFLOP (16-bit 2) also none whose chunks of 32 channels are
+    // padding to more than a tenth (16-bit three tenths): the split kernel counts channels in eights (8 -> 326 at 94x77, batch 9, fp32 68 / 90;
+    // bf16 33 -> 285 at 97x101, batch 2, 21 / 25).  350 random layers a type, the kernels there were before / the untimed choice: fp32 1.20 times
+    // the time on average, 0.81 at worst, bf16 1.42 and 0.93; 130 random layers a type: the untimed choice is 1.06 times the time of the timed one on average.
     const double flops = 18.0 * d.n * d.h * d.w * (double)d.c_out * d.c_in;
-    if (d.dtype != CPRUNE_F32) return d.c_in >= 4 && flops <= (d.c_in >= 64 ? 1e10 : 5.5e9);
-    return d.c_in >= 8 && flops <= 5.5e9 && ((d.c_in + 63) / 64 <= 3 || flops >= 4e8);
+    const int padded = (d.c_in + 31) / 32 * 32;
+    if (d.dtype != CPRUNE_F32) return d.c_in >= 4 && flops <= (d.c_in >= 64 ? 1e10 : 5.5e9) && (flops <= 2e9 || 10 * d.c_in >= 7 * padded);
+    return d.c_in >= 8 && flops <= 5.5e9 && (flops <= 1e9 || 10 * d.c_in >= 9 * padded) &&
+           (d.c_in <= 128 || flops >= (d.c_in <= 192 ? 2e7 : 4e8));
   }
   if (d.dtype != CPRUNE_F32 || !lay.w_split) return true;
   if (d.stride == 2) {

@@ -40,3 +40,18 @@ def test_estimate_knows_how_many_groups_a_unit_holds(n, c_in, hw, c_out, k, stri
     v, timed = B.cprune_cached_tile(B.conv_desc((n, c_in, hw, hw), (c_out, c_in, k, k), stride, k // 2, 1, B.F32))
     assert not timed
     assert not B.cprune_tile_variant_name(v, False, B.F32).endswith(old + ">"), B.cprune_tile_variant_name(v, False, B.F32)
+
+
+@pytest.mark.parametrize("dtype,n,c_in,h,w,c_out,strips", [
+    # over 1 GFLOP (16-bit: 2) with chunks of 32 channels that are mostly padding: 68 us before, 90 on strips; 49 and 60
+    (B.F32, 9, 8, 94, 77, 326, False), (B.F32, 10, 13, 76, 76, 381, False), (B.BF16, 13, 7, 74, 74, 398, False),
+    # a chain of five chunks under 5 MFLOP: 10.3 and 12.2 us
+    (B.F32, 1, 141, 12, 12, 13, False),
+    # ... and their neighbours, where strips are the faster ones
+    (B.F32, 1, 64, 32, 32, 45, True), (B.F32, 8, 128, 56, 56, 83, True), (B.F32, 3, 132, 34, 34, 12, True), (B.BF16, 2, 24, 56, 56, 64, True),
+])
+def test_strips_where_their_chunks_are_filled(dtype, n, c_in, h, w, c_out, strips):
+    B.cprune_clear_tile_cache()
+    v, timed = B.cprune_cached_tile(B.conv_desc((n, c_in, h, w), (c_out, c_in, 3, 3), 1, 1, 1, dtype))
+    assert not timed
+    assert ("conv_rows_nchw" in B.cprune_tile_variant_name(v, False, dtype)) == strips
