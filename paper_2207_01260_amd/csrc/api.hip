@@ -80,8 +80,10 @@ static bool split_pays(const cprune_conv_desc& d, const ConvLayout& lay, double 
 // strip wide and 0.3 on wider ones whose strips are well filled (56 of 4 x 16 columns, not 32 of 3 x 16 or, with a pool, 56 of 5 x
 // 16) and whose chunks of 32 channels are not mostly padding as well; there 1.12 times as fast on average (63 random layers of 28 to 400 us),
 // 0.95 times at worst; the layers left out by the fill alone 0.9-1.07 times, and below the lines 0.7-1.2 times.  Stride 2 in fp32: from
-// four chunks of channels up, on maps of two strips at most, to 2 GFLOP (45 random layers: there 1.2 times as fast on average; with one to
-// three chunks 0.6-1.1 times: 18 -> 44 at 28x28, batch 2, 4.6 / 7.7 us); 16-bit data always (45 random layers: 1.99 times).  A layer without the split kernel's copy (a smaller batch in a
+// four chunks of channels up, on maps of two strips at most, to 1 GFLOP, and long chains from 0.2 (200 random layers, before / now: 73 met
+// the line of 2 GFLOP and any chain, 1.12 times as fast on average, 17 of them slower: 181 -> 265 at 20x20, batch 14, 16.8 / 24.1, 683 -> 94 at
+// 14x14, one image, 14.1 / 17.2; now 55, 1.20 times, 0.81 at worst); with one to
+// three chunks 0.6-1.1 times: 18 -> 44 at 28x28, batch 2, 4.6 / 7.7 us; 16-bit data always (200 random layers: 1.74 times, 0.80 at worst).  A layer without the split kernel's copy (a smaller batch in a
 // handle whose full batch runs row strips) has the general kernel's fp32 instruction in its place, and always takes them:
 // ResNet-18 built for 32, 2 and 1 images 213 -> 198 and 269 -> 190 us, VGG-16 built for 64, 8 images 173 -> 141.
 static bool rows_pay(const cprune_conv_desc& d, const ConvLayout& lay) {
@@ -101,7 +103,8 @@ static bool rows_pay(const cprune_conv_desc& d, const ConvLayout& lay) {
   if (d.dtype != CPRUNE_F32 || !lay.w_split) return true;
   if (d.stride == 2) {
     const long ho = conv_out_dim(d.h, 3, 2, 1), wo = conv_out_dim(d.w, 3, 2, 1);
-    return lay.cp_in >= 112 && wo <= 32 && (lay.cp_in <= 384 || d.c_out > 16) && 18.0 * d.n * ho * wo * (double)d.c_out * d.c_in <= 2e9;
+    const double flops = 18.0 * d.n * ho * wo * (double)d.c_out * d.c_in;
+    return lay.cp_in >= 112 && wo <= 32 && (lay.cp_in <= 384 || flops >= 2e8) && flops <= 1e9;
   }
   const double flops = 18.0 * d.n * d.h * d.w * (double)d.c_out * d.c_in;
   if (d.w <= 16) return flops >= 2e8;
