@@ -34,7 +34,7 @@ if ROOT not in sys.path:
 # to the kernel sources they were measured on: TRAFFIC_SOURCE_HASH is kernel_source_hash() of that tree,
 # and any change to a file under csrc/ since then reports null instead of a stale figure (as does a
 # selection that runs a kernel on a layer it was not profiled on).
-TRAFFIC_SOURCE_HASH = "2c93b72c1eb0aba1"
+TRAFFIC_SOURCE_HASH = "a51cab823751d270"
 TRAFFIC = {
     ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3351368,
     ("conv_split_rows_kernel<4, 1>", 64, "conv3"): 11213257,
