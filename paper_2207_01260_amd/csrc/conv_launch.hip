@@ -388,6 +388,15 @@ static RowsArgs rows_tiles(const cprune_conv_desc& d, const TileVariant& tv, con
   return a;
 }
 
+// Whether the work-groups of a layer in a handle run filter tile by filter tile.  Each XCD owns a contiguous stretch of them; the other
+// way round (strips slowest) all eight read all weights, which, cut in parts, are the larger operand of the small maps.  Below 3 MB an
+// XCD's L2 holds them with its pixels and the order does not matter (fp32, 209 -> 197 at 8x8, 2.2 MB: 20.4 us either way) or costs 1-2 %
+// (bf16 284 -> 360 at 4x4, 1.8 MB); above: fp32 411 -> 512 at 7x7 b32 37.4 -> 32.7 us, 512 -> 411 38.0 -> 34.4, 360 -> 360 at 4x4 b64 19.9 ->
+// 17.4, 284 -> 360 17.3 -> 15.3; bf16 512 -> 411 10.75 -> 10.45.  Not with the 1x1 layer's (shorter) work-groups behind: they would all be one XCD's.
+static bool rows_m_major(const RowsArgs& a, long groups_s, bool pair) {
+  return !pair && a.w_bytes > (3u << 20) && a.w_bytes > a.x_bytes && groups_s * a.tiles_m * groups_s < (1L << 32);
+}
+
 // Clocks of a row-strip variant, to choose among them untimed: a wavefront's chunks, 16 clocks per MFMA (six for one in fp32) and
 // what a wavefront alone on its SIMD waits per chunk, or the whole layer's on 1024 SIMDs where that is longer; the meeting of the
 // sums.  On 72 random layers (maps 4 to 56, batch 1-64) its choice takes 3 % longer than the best of the variants on average, 17 % at
@@ -616,7 +625,7 @@ int launch_conv_dense(const cprune_conv_desc& d, const void* x, const void* w, c
       a.w_bytes = (unsigned)((size_t)d.c_out * d.c_in * 9 * es);
       a.y_bytes = (unsigned)((size_t)d.n * d.c_out * d.h * d.w * es);
       a.w_raw = nullptr; a.w_raw_bytes = 0;
-      a.nchunk = (d.c_in + 31) / 32; a.act = d.act; a.pool = 0;
+      a.nchunk = (d.c_in + 31) / 32; a.act = d.act; a.pool = 0; a.m_major = 0;
       a.magic_m = magic_for((unsigned)a.tiles_m); a.magic_x = magic_for((unsigned)a.tiles_x); a.magic_y = magic_for((unsigned)a.tiles_y);
       const dim3 grid((unsigned)((a.strips + tv.wn - 1) / tv.wn * a.tiles_m));
       const int rc = d.dtype == CPRUNE_F32 ? launch_conv_rows_nchw_f32(tv.patch_id, grid, s, a) :
@@ -648,8 +657,10 @@ int launch_conv_dense(const cprune_conv_desc& d, const void* x, const void* w, c
       a.w2_raw_bytes = (unsigned)((size_t)q.c_out * lay.cp_in * es);
       a.y2_bytes = (unsigned)((size_t)d.n * q.cp_out * a.H * a.W * es);
     }
-    a.magic_m = magic_for((unsigned)a.tiles_m); a.magic_x = magic_for((unsigned)a.tiles_x); a.magic_y = magic_for((unsigned)a.tiles_y);
-    const dim3 grid((unsigned)((a.strips + tv.wn - 1) / tv.wn * a.tiles_m));
+    const int groups_s = (a.strips + tv.wn - 1) / tv.wn;
+    a.m_major = rows_m_major(a, groups_s, lay.pair != nullptr) ? groups_s : 0;
+    a.magic_m = magic_for((unsigned)(a.m_major ? a.m_major : a.tiles_m)); a.magic_x = magic_for((unsigned)a.tiles_x); a.magic_y = magic_for((unsigned)a.tiles_y);
+    const dim3 grid((unsigned)(groups_s * a.tiles_m));
     int rc;
     if (tv.stride == 2)
       rc = d.dtype == CPRUNE_F32 ? launch_conv_rows_s2_f32(tv.patch_id, grid, s, a) :

@@ -38,7 +38,8 @@ struct RowsArgs {
   int strips;                      // of the whole batch
   int lane_shift;                  // lanes per image: 1 << lane_shift
   int step;                        // columns from strip to strip: 16, or 14 (12 with a pool) where strips overlap (fp32), 15 at stride 2
-  unsigned magic_m, magic_x, magic_y;
+  int m_major;                     // 0: filter tiles run fastest; otherwise slowest, and the work-groups of one filter tile
+  unsigned magic_m, magic_x, magic_y;   // (magic_m: of m_major where that is set)
   unsigned x_bytes, w_bytes, y_bytes;
   int nchunk;                      // chunks of 32 channels
   int act, pool;
@@ -74,8 +75,9 @@ __device__ __forceinline__ RowsAt rows_at(const RowsArgs& a) {
     const int q = G >> 3, rem = G & 7;
     tile = xcd * q + (xcd < rem ? xcd : rem) + local;
   }
-  const int group = (int)fast_div((unsigned)tile, a.magic_m);      // of NS strips
-  p.tile_m = tile - group * a.tiles_m;
+  const int major = (int)fast_div((unsigned)tile, a.magic_m), minor = tile - major * (a.m_major ? a.m_major : a.tiles_m);
+  const int group = a.m_major ? minor : major;                     // of NS strips
+  p.tile_m = a.m_major ? major : minor;
   p.o0 = p.tile_m * (MB * 16);
   const int strip = group * NS + p.sub;
   const int q_x = (int)fast_div((unsigned)strip, a.magic_x);
