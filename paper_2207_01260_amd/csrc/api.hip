@@ -719,14 +719,24 @@ static int net_run_stem2(cprune_net* net, int i, int n, const void* x, void* dst
   return launch_conv_stem2(d2, layer_layout(L), x, F.d.c_in, F.w_stem, F.b, F.d.c_out, F.d.act, L.w, L.b, dst, s);
 }
 
-// Strips of a map in the inverted-residual kernel.
-static void mbrow_tiles(const NetLayer& D, int mb, int low, MbArgs* a) {
+// Whether the strips of depthwise layer D and the 1x1 layer P multiply on three bf16 parts, in every form.
+static bool block_parts(int dtype, const NetLayer& D, const NetLayer& P) {
+  int mb = 0, xh = 0;
+  return dtype == CPRUNE_F32 && mbrow_form(dtype, P.d.c_out, 0, &mb, &xh) && mbrow_parts(D.d.k, mb);
+}
+
+// Rows of a strip.
+static int block_rows(int dtype, const NetLayer& D, const NetLayer& P, int mb, int xh, int low) {
+  return block_parts(dtype, D, P) ? mbrow3_strip_rows(D.d.stride, mb, xh, low) : mbrow_rows(D.d.k, D.d.stride, mb, low);
+}
+
+// Strips of r rows of a map in the inverted-residual kernel.
+static void mbrow_tiles(const NetLayer& D, int r, MbArgs* a) {
   const int hl = mbrow_halo_left(D.d.k, D.d.stride), hr = mbrow_halo_right(D.d.k, D.d.stride), step = 16 - hl - hr;
   // two images side by side where an image with the columns its windows reach past the right edge fits eight lanes
   const int last = D.d.stride == 1 ? D.w_in + hr : D.w_out + 1;
   a->ipt = last <= 8 ? 2 : 1;
   a->tiles_x = a->ipt == 2 || D.w_out <= 16 ? 1 : (D.w_out - hl - hr + step - 1) / step;
-  const int r = mbrow_rows(D.d.k, D.d.stride, mb, low);
   a->tiles_y = (D.h_out + r - 1) / r;
 }
 
@@ -745,6 +755,9 @@ static bool mbrow_form_of(const cprune_net& net, const NetLayer& P, const NetLay
   if (E && E->nchw_in) return mbrow_image_form(net.dtype, P.d.c_out, mb, xh);
   return mbrow_form(net.dtype, P.d.c_out, E ? E->cp_in : 0, mb, xh);
 }
+
+// Three parts: rounds of the expansion's reduction in three parts (four window rows a round on the image)
+static int expand_rounds(const NetLayer& E, int xh) { return E.nchw_in ? 3 : (xh + 1) / 2; }
 
 static int net_run_mbrow(cprune_net* net, int i, int n, const void* x, void* dst, hipStream_t s) {
   const NetLayer& P = net->layers[i];
@@ -765,14 +778,16 @@ static int net_run_mbrow(cprune_net* net, int i, int n, const void* x, void* dst
   a.Cpi = image ? E->d.c_in : E ? E->cp_in : 0; a.Ce = D.d.c_out; a.Cpe = D.cp_in; a.O = P.d.c_out; a.Cop = P.cp_out;
   a.act_e = E ? E->d.act : CPRUNE_ACT_NONE; a.act_dw = D.d.act; a.act_out = P.d.act;
   const int low = E ? P.block_low : P.dw_tile != kTallStrips;
-  mbrow_tiles(D, mb, low, &a);
+  mbrow_tiles(D, block_rows(net->dtype, D, P, mb, xh, low), &a);
   a.magic_x = strip_magic(a.tiles_x); a.magic_y = strip_magic(a.tiles_y);
   a.x_bytes = (unsigned)((size_t)n * (image ? (size_t)a.Hi * a.Wi : (size_t)a.H * a.W) * (E ? a.Cpi : a.Cpe) * es);
-  a.we_bytes = E ? (unsigned)expand_packed_bytes(a.Ce, xh, net->dtype) : 0u;
-  a.wp_bytes = (unsigned)rows_packed_bytes(a.O, a.Cpe, net->dtype);
+  const bool parts = block_parts(net->dtype, D, P);
+  a.nchunk = (int)((a.Cpe * es + 63) / 64);
+  a.we_raw = E ? E->w : nullptr; a.wp_raw = P.w;
+  a.we_bytes = !E ? 0u : (unsigned)(parts ? parts_packed_bytes(a.Ce, expand_rounds(*E, xh), mbrow3_twice(D.d.stride, xh, image)) : expand_packed_bytes(a.Ce, xh, net->dtype));
+  a.wp_bytes = (unsigned)(parts ? parts_packed_bytes(a.O, a.nchunk, false) : rows_packed_bytes(a.O, a.Cpe, net->dtype));
   a.wdw_bytes = (unsigned)((size_t)D.d.k * D.d.k * a.Cpe * es);
   a.y_bytes = (unsigned)((size_t)n * a.Ho * a.Wo * a.Cop * es);
-  a.nchunk = (int)((a.Cpe * es + 63) / 64);
   a.slots = 0;
   const int tiles_m = (a.O + mb * 16 - 1) / (mb * 16);
   const dim3 grid((unsigned)((n + a.ipt - 1) / a.ipt * a.tiles_y * a.tiles_x), (unsigned)tiles_m);
@@ -878,13 +893,16 @@ static bool block_joins(const cprune_net& net, int i, int* mb, int* xh) {
          E.cp_out == round_up_vec(ed.c_out, net.dtype) && mbrow_form(net.dtype, P.d.c_out, E.cp_in, mb, xh);
 }
 
-static int pack_expansion(cprune_net* net, NetLayer& E, int xh, hipStream_t s) {
+static int pack_expansion(cprune_net* net, NetLayer& E, const NetLayer& D, const NetLayer& P, int xh, hipStream_t s) {
   if (E.w_expand) return CPRUNE_OK;
   void* copy = nullptr;
-  CPRUNE_HIP_TRY(hipMalloc(&copy, expand_packed_bytes(E.d.c_out, xh, net->dtype)));
+  const int terms = E.nchw_in ? E.d.c_in * 9 : E.cp_in;
+  const bool parts = block_parts(net->dtype, D, P), twice = mbrow3_twice(D.d.stride, xh, E.nchw_in);
+  CPRUNE_HIP_TRY(hipMalloc(&copy, parts ? parts_packed_bytes(E.d.c_out, expand_rounds(E, xh), twice) + 16 : expand_packed_bytes(E.d.c_out, xh, net->dtype)));
   net->allocs.push_back(copy);
   E.w_expand = copy;
-  return launch_pack_expand(E.w, E.d.c_out, E.nchw_in ? E.d.c_in * 9 : E.cp_in, xh, net->dtype, copy, s);
+  if (parts) return launch_pack_parts(E.w, E.d.c_out, terms, expand_rounds(E, xh), twice, E.nchw_in, copy, s);
+  return launch_pack_expand(E.w, E.d.c_out, terms, xh, net->dtype, copy, s);
 }
 
 // The variant a layer of a handle for larger batches runs at n images, where none was timed for that shape.  Without a timed
@@ -1037,9 +1055,9 @@ static int time_mbrow(cprune_net* net, const int* layers, int n_layers, bool str
   };
   mbrow_form_of(*net, P, P.fuse_block >= 0 ? &net->layers[P.fuse_block] : nullptr, &mb, &xh);
   for (int l = 0; l < 2 && strips; ++l) {
-    if (l && mbrow_rows(D.d.k, D.d.stride, mb, 0) == mbrow_rows(D.d.k, D.d.stride, mb, 1)) break;
+    if (l && block_rows(net->dtype, D, P, mb, xh, 0) == block_rows(net->dtype, D, P, mb, xh, 1)) break;
     MbArgs a;
-    mbrow_tiles(D, mb, l, &a);
+    mbrow_tiles(D, block_rows(net->dtype, D, P, mb, xh, l), &a);
     a.nchunk = (int)((D.cp_in * dtype_size(net->dtype) + 63) / 64);
     const int k0 = mbrow_auto_ks(a, net->max_batch, (P.d.c_out + mb * 16 - 1) / (mb * 16), 1);
     for (int k = k0; k <= 8 && k <= 2 * k0; k *= 2) {
@@ -1547,8 +1565,14 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     if (P.cp_out != round_up_vec(pd.c_out, dtype) || P.nchw_in || P.map2x2 || P.fused_pool) continue;
     D.dw_reader = reader;
     P.dw_tile = dw_tile_untimed(P, D, max_batch, dtype);
-    P.w_proj = P.w_rows;
-    if (!P.w_proj) {
+    if (block_parts(dtype, D, P)) {
+      const int rounds = (P.cp_in + 15) / 16;
+      rc = dev_alloc(parts_packed_bytes(pd.c_out, rounds, false) + 16, &P.w_proj);
+      if (rc == CPRUNE_OK) rc = launch_pack_parts(P.w, pd.c_out, P.cp_in, rounds, false, false, P.w_proj, s);
+      if (rc != CPRUNE_OK) break;
+    } else if (P.w_rows) {
+      P.w_proj = P.w_rows;
+    } else {
       rc = dev_alloc(rows_packed_bytes(pd.c_out, P.cp_in, dtype), &P.w_proj);
       if (rc == CPRUNE_OK) rc = launch_repack_rows(P.w, pd.c_out, P.cp_in, dtype, P.w_proj, s);
       if (rc != CPRUNE_OK) break;
@@ -1560,7 +1584,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     const bool on_request = block && !E.nchw_in && block_on_request(*net, E, D, P);
     block = block && (on_request || tune);       // (the first layer in the expansion's place: only where timed as faster)
     if (block) {
-      rc = pack_expansion(net, E, xh, s);
+      rc = pack_expansion(net, E, D, P, xh, s);
       if (rc != CPRUNE_OK) break;
       if (on_request) D.block_expand = dd.input;
     }
@@ -1848,7 +1872,7 @@ extern "C" int cprune_net_block_form(cprune_net* net, int layer, int form, int t
   CPRUNE_HIP_TRY(hipDeviceSynchronize());
   drop_graphs(net);
   if (form == 2 && !joined) {
-    const int rc = pack_expansion(net, E, xh, nullptr);
+    const int rc = pack_expansion(net, E, D, P, xh, nullptr);
     if (rc != CPRUNE_OK) return rc;
     CPRUNE_HIP_TRY(hipDeviceSynchronize());
   }

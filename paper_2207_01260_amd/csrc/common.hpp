@@ -176,12 +176,13 @@ struct MbArgs {
   unsigned magic_x, magic_y;   // strip_magic of tiles_x and tiles_y
   unsigned x_bytes, we_bytes, wp_bytes, wdw_bytes, y_bytes;
   int nchunk;           // 64-byte chunks of expanded channels
+  const void *we_raw, *wp_raw;   // fp32: the weights as they are, [ce][terms] and [o][cpe]
   int slots;            // wavefronts whose sums fit the exchange area (set by the launcher)
 };
 
 // Output rows a wavefront owns (k in {3, 5}, stride in {1, 2}, mb filter blocks): about as many as its registers hold beside the
 // window's weights, multiples or halves of 7 where possible (the maps of the evaluated networks are 7 x 2^n); low = 1: about
-// half as many, for maps whose tall strips leave units idle.  Some forms hold more than fit and spill: 14 of the 82 fp32 forms, 21 of the
+// half as many, for maps whose tall strips leave units idle.  Some forms hold more than fit and spill: 19 of the 31 fp32 forms (5x5), 21 of the
 // 75 bf16 and 8 of the 75 fp16 ones, by 1 to 94 registers, most where the window is 5x5 (its widened weights are 100
 // registers) or a tall strip has 48 filters and more.  Timing chooses among tall and low all the same.
 constexpr int mbrow_rows(int k, int s, int mb, int low) {
@@ -189,6 +190,15 @@ constexpr int mbrow_rows(int k, int s, int mb, int low) {
   if (s == 1) return mb <= 2 ? (low ? 2 : 4) : 2;
   if (k == 3) return mb <= 4 ? (low ? 2 : 4) : 2;
   return mb <= 4 ? 2 : 1;
+}
+// Whether fp32 strips multiply on three bf16 parts (mbrow3_kernel.hpp).  5x5 windows not (their 100 registers of weights leave too few: 24 -> 60 ->
+// 40 at 56x56 stride 2, batch 48, 34.2 us on the fp32 instruction, 41.8 on parts, 80 -> 300 -> 80 at 14x14 46 / 118), nor tiles of 128
+// filters (96 -> 280 -> 160 at 14x14 stride 2, depthwise and projection, 22.4 / 26.5).
+constexpr bool mbrow_parts(int k, int mb) { return k == 3 && mb <= 6; }
+// Likewise there: eight registers of weights a filter block and not four, so that tall strips of 64 filters do not fit (5 of the 36 forms spill).
+constexpr int mbrow3_strip_rows(int s, int mb, int xh, int low) {
+  if (s == 1) return mb <= 2 ? (low ? 4 : 7) : mb == 4 ? (low && xh > 4 ? 2 : 4) : mb == 6 && !xh ? 3 : 2;
+  return mb <= 2 ? (low ? 2 : 4) : 2;
 }
 // elements from row to row of the staged image: 33 columns and what turns the rows' banks
 constexpr int mbrow_image_pitch(int es) { return es == 4 ? 35 : 38; }
@@ -204,11 +214,19 @@ bool mbrow_image_form(int dt, int c_out, int* mb, int* xh);
 // grid = (strips, filter tiles), ks in {1, 2, 4, 8} wavefronts that share a strip.
 // CPRUNE_ERR_UNSUPPORTED for other combinations.
 int launch_mbrow_f32(int k, int stride, int mb, int xh, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a);
+int launch_mbrow3_f32(int stride, int mb, int xh, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a);
 int launch_mbrow_f16(int k, int stride, int mb, int xh, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a);
 int launch_mbrow_bf16(int k, int stride, int mb, int xh, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a);
 // expansion weights [ce][cp] -> the operand order of that kernel, [block of 16 channels][xh 32-byte units], zero padded
 size_t expand_packed_bytes(int ce, int xh, int dt);
 int launch_pack_expand(const void* w, int ce, int cp, int xh, int dt, void* y, hipStream_t s);
+// fp32 weights [rows][terms] -> three bf16 parts in the operand order of mbrow3_kernel, [tile of 16 rows][round of 16 terms][operand], zero
+// padded to `rounds`; image: terms (channel, window row, window column) in rounds of four window rows of four columns.  Behind them a
+// word that is not zero if a weight is 2^60 or more.
+// The expansion's operands for xh 32-byte units of input are three a round, with each part twice where a round's weights are used for few.
+constexpr bool mbrow3_twice(int stride, int xh, bool image) { return stride == 1 && xh <= 4 && !image; }
+size_t parts_packed_bytes(int rows, int rounds, bool twice);
+int launch_pack_parts(const void* w, int rows, int terms, int rounds, bool twice, bool image, void* y, hipStream_t s);
 
 // The depthwise 5x5 layer and the 1x1 convolution behind it through local memory, an 8 x 8 block of output pixels per work-group.
 struct DwProjArgs {

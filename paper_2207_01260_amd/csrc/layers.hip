@@ -502,6 +502,37 @@ __global__ __launch_bounds__(256) void pack_expand_kernel(const T* __restrict__ 
   y[i] = (ch < ce && k < cp) ? w[(long)ch * cp + k] : (T)0.0f;
 }
 
+// fp32 weights [rows][terms] -> the operands of mbrow3_kernel: [tile of 16 rows][round of 16 terms][operand][lane = quad * 16 + row], of four
+// terms (wh, wl), (wm, wh) or, twice, (wh, wl), (wm, wm), (wh, wh).  image: a round is four window rows (channel, row) of four
+// columns, the last of them zero.
+__global__ __launch_bounds__(256) void pack_parts_kernel(const float* __restrict__ w, uint4* __restrict__ y, int total, int rows, int terms,
+                                                         int rounds, int twice, int image) {
+  const int i = blockIdx.x * 256 + threadIdx.x;          // one lane of one round
+  if (i >= total) return;
+  const int lane = i & 63, unit = i >> 6, rnd = unit % rounds, row = unit / rounds * 16 + (lane & 15);
+  float v[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int p = rnd * 4 + (lane >> 4), k = image ? p * 3 + q : p * 4 + q;
+    v[q] = row < rows && k < terms && !(image && q == 3) ? w[(long)row * terms + k] : 0.0f;
+  }
+  uint32_t h[2], m[2], l[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) split3(__float_as_uint(v[2 * q]), __float_as_uint(v[2 * q + 1]), h[q], m[q], l[q]);
+  uint4* const dst = y + (size_t)unit * (twice ? 192 : 128) + lane;
+  dst[0] = make_uint4(h[0], h[1], l[0], l[1]);
+  dst[64] = twice ? make_uint4(m[0], m[1], m[0], m[1]) : make_uint4(m[0], m[1], h[0], h[1]);
+  if (twice) dst[128] = make_uint4(h[0], h[1], h[0], h[1]);
+}
+
+// Whether a weight is 2^60 or more, or not finite (one work-group).
+__global__ __launch_bounds__(256) void parts_limit_kernel(const float* __restrict__ w, long n, unsigned* __restrict__ flag) {
+  unsigned top = 0;
+  for (long i = threadIdx.x; i < n; i += 256) top = max(top, __float_as_uint(w[i]) & 0x7fffffffu);
+  const int any = __syncthreads_or(top >= (127u + 60u) << 23);
+  if (threadIdx.x == 0) *flag = any ? 1u : 0u;
+}
+
 // Weights -> the operand order of the split kernel: [filter tile of 16][round][part][lane = quarter * 16 + filter]
 // [8 channels].  A round holds four (tap, 8-channel group) units, one per quarter.
 template <typename T>
@@ -877,6 +908,19 @@ int launch_pack_expand(const void* w, int ce, int cp, int xh, int dt, void* y, h
   const long total = (long)(expand_packed_bytes(ce, xh, dt) / dtype_size(dt));
   CPRUNE_BY_DTYPE(dt, hipLaunchKernelGGL(pack_expand_kernel<T>, blocks_for(total), dim3(256), 0, s, (const T*)w, (T*)y,
                                          total, ce, cp, xh));
+  CPRUNE_LAUNCH_CHECK();
+  return CPRUNE_OK;
+}
+
+size_t parts_packed_bytes(int rows, int rounds, bool twice) { return (size_t)((rows + 15) / 16) * rounds * (twice ? 3072 : 2048); }
+
+int launch_pack_parts(const void* w, int rows, int terms, int rounds, bool twice, bool image, void* y, hipStream_t s) {
+  const int total = (rows + 15) / 16 * rounds * 64;
+  hipLaunchKernelGGL(pack_parts_kernel, blocks_for(total), dim3(256), 0, s, (const float*)w, (uint4*)y, total, rows, terms, rounds, twice ? 1 : 0,
+                     image ? 1 : 0);
+  CPRUNE_LAUNCH_CHECK();
+  hipLaunchKernelGGL(parts_limit_kernel, dim3(1), dim3(256), 0, s, (const float*)w, (long)rows * terms,
+                     (unsigned*)((unsigned char*)y + parts_packed_bytes(rows, rounds, twice)));
   CPRUNE_LAUNCH_CHECK();
   return CPRUNE_OK;
 }

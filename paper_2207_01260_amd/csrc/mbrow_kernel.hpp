@@ -22,15 +22,11 @@
 //
 // Values handed from step to step are rounded to the activation type, as the separate layers store them.
 //
+// fp32 with 3x3 windows and up to 96 filters runs mbrow3_kernel.hpp instead, the same strips on three bf16 parts.
+//
 // Measured (expansion + depthwise + projection, us): the layers apart or with the depthwise layer fused through LDS, the
-// faster of both / this kernel.  MobileNetV2 fp32 at batch 64: 16 -> 50 -> 24, 112x112 stride 2: 110 / 42; 24 -> 65 -> 24 at 56x56:
-// 70 / 33; 24 -> 86 -> 32, 56x56 stride 2: 56 / 24; 32 -> 92 -> 32 at 28x28: 30 / 18; 64 -> 330 -> 64 at 14x14: 38 / 26.  MnasNet bf16 at
-// batch 16: 16 -> 38 -> 24, 112x112: 20 / 11; 24 -> 58 -> 24 at 56x56: 15 / 9.  Without an expansion: 32 -> 16 at 112x112, fp32 b64
-// 52 / 42; with the first layer in front of it (image 3 -> 32 -> 16) 88 / 62, bf16 b16 20.3 / 16.6 (the windows' gather from LDS).  In fp32 the
-// matrix cores bound it most: over whole launches of MobileNetV2's blocks they are busy 29-58 % of the cycles in which their units have
-// work, the vector ALU 18-37 % (image form 37 and 60), and wavefronts wait to issue for 34-60 % of their cycles and for memory 15-39;
-// in the chunk loop 24 -> 65 -> 24 takes 4.9 us per chunk for 2048 strips, 3.0 us of it MFMA issue; launch, staging and stores are 9
-// of its 33 us.
+// faster of both / this kernel.  MnasNet bf16 at batch 16: 16 -> 38 -> 24, 112x112: 20 / 11; 24 -> 58 -> 24 at 56x56: 15 / 9; image 3 -> 32 -> 16
+// 20.3 / 16.6 (the windows' gather from LDS).  In fp32 the matrix instruction bounds it, which takes turns with the vector ALU (mbrow3_kernel.hpp).
 #pragma once
 #include <atomic>
 #include "conv_nhwc_kernel.hpp"
@@ -47,12 +43,159 @@ __device__ __forceinline__ float row_shift(float v) {
   }
 }
 
+// Where a wavefront works.
+struct MbAt {
+  int lane, r, g4, wave, ks;       // wavefront of the strip's ks
+  int o0;                          // first filter of the projection tile
+  int tx, ty, n0, img;             // strip, its first image, the lane's image
+  int j0, lr, cj, iy0;             // first output column of the strip, the lane's place in its image's columns, its output column; input row 0
+  bool two, lane_out;              // two images side by side; the lane's column is one that this strip stores
+};
+
+template <int K, int S, int MB, int R>
+__device__ __forceinline__ MbAt mbrow_at(const MbArgs& a) {
+  constexpr int HL = mbrow_halo_left(K, S), HR = mbrow_halo_right(K, S);
+  MbAt p;
+  p.lane = threadIdx.x & 63;
+  p.ks = (int)blockDim.x >> 6;
+  p.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  p.r = p.lane & 15; p.g4 = p.lane >> 4;
+  int tile;
+  {
+    const int G = gridDim.x;
+    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+    const int q = G >> 3, rem = G & 7;
+    tile = xcd * q + (xcd < rem ? xcd : rem) + local;
+  }
+  p.o0 = blockIdx.y * (MB * 16);
+  const StripAt strip = strip_at(tile, a.tiles_x, a.tiles_y, a.magic_x, a.magic_y);
+  p.tx = strip.tx; p.ty = strip.ty;
+  p.two = a.ipt == 2;
+  p.n0 = p.two ? 2 * strip.group : strip.group;
+  p.j0 = p.tx * (16 - HL - HR);
+  p.lr = p.two ? (p.r & 7) : p.r;
+  p.img = p.two ? p.n0 + (p.r >> 3) : p.n0;
+  p.cj = p.j0 + p.lr;
+  p.iy0 = p.ty * R * S - K / 2;
+  p.lane_out = (p.img < a.N) & (p.cj < a.Wo) & ((p.tx == 0) | (p.lr >= HL)) & ((p.tx == a.tiles_x - 1) | (p.lr < 16 - HR));
+  return p;
+}
+
+// Shortcut (all loads before the first store), activation, store of four filters of one pixel; where several wavefronts share the
+// strip, behind the sum of theirs.
+template <typename T, int R, int MB>
+__device__ __forceinline__ void mbrow_finish(const MbArgs& a, const MbAt& at, unsigned char* lds, float4_t (&acc)[R][MB]) {
+  constexpr int ES = (int)sizeof(T);
+  const int lane = at.lane, ks = at.ks, wave = at.wave, g4 = at.g4;
+  const __amdgpu_buffer_rsrc_t rr = make_rsrc(a.res, a.res ? a.y_bytes : 0u);
+  const float lo_o = a.act_out == CPRUNE_ACT_NONE ? -__builtin_inff() : 0.0f;
+  const float hi_o = a.act_out == CPRUNE_ACT_RELU6 ? 6.0f : __builtin_inff();
+  auto out_at = [&](int y, int m) -> unsigned {
+    const int oy = at.ty * R + y, o = at.o0 + m * 16 + 4 * g4;
+    return at.lane_out & (oy < a.Ho) & (o < a.Cop) ? (unsigned)(((at.img * a.Ho + oy) * a.Wo + at.cj) * a.Cop + o) * ES : kOutOfRange;
+  };
+  auto load_res = [&](unsigned off) -> float4_t {
+    if constexpr (ES == 4) {
+      const uint4 q = load_b128(rr, off, 0);
+      return __builtin_bit_cast(float4_t, q);
+    } else {
+      return widen4<T>(load_b64(rr, off, 0));
+    }
+  };
+  auto store = [&](unsigned off, float4_t v) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = __builtin_amdgcn_fmed3f(v[q], lo_o, hi_o);
+    if (off == kOutOfRange) return;
+    if constexpr (ES == 4) *(float4_t*)((char*)a.y + off) = v;
+    else *(uint2*)((char*)a.y + off) = narrow4<T>(v);
+  };
+  if (ks == 1) {
+    constexpr int GROUP = MB > 4 ? 2 : 16 / MB;       // rows whose shortcuts are in flight together
+#pragma unroll
+    for (int y0 = 0; y0 < R; y0 += GROUP) {
+      if (a.res) {
+        float4_t res[GROUP][MB];
+#pragma unroll
+        for (int y = 0; y < GROUP; ++y)
+#pragma unroll
+          for (int m = 0; m < MB; ++m)
+            if (y0 + y < R) res[y][m] = load_res(out_at(y0 + y, m));
+#pragma unroll
+        for (int y = 0; y < GROUP; ++y)
+#pragma unroll
+          for (int m = 0; m < MB; ++m)
+            if (y0 + y < R) acc[y0 + y][m] += res[y][m];
+      }
+#pragma unroll
+      for (int y = 0; y < GROUP; ++y)
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+          if (y0 + y < R) store(out_at(y0 + y, m), acc[y0 + y][m]);
+    }
+    return;
+  }
+
+  // the sums of the wavefronts meet in LDS: the upper half hands over to the lower one until a.slots of them are left,
+  // whose sums are then added in order, the (row, filter block) units shared by all wavefronts
+  constexpr int SLOT = R * MB * 64;
+  float4_t* const xch = (float4_t*)lds;
+  int nw = ks;
+  while (nw > a.slots) {
+    const int hw = nw >> 1;
+    __syncthreads();
+    if (wave >= hw && wave < nw) {
+      float4_t* const dst = xch + (wave - hw) * SLOT + lane;
+#pragma unroll
+      for (int y = 0; y < R; ++y)
+#pragma unroll
+        for (int m = 0; m < MB; ++m) dst[(y * MB + m) * 64] = acc[y][m];
+    }
+    __syncthreads();
+    if (wave < hw) {
+      const float4_t* const src = xch + wave * SLOT + lane;
+#pragma unroll
+      for (int y = 0; y < R; ++y)
+#pragma unroll
+        for (int m = 0; m < MB; ++m) acc[y][m] += src[(y * MB + m) * 64];
+    }
+    nw = hw;
+  }
+  __syncthreads();
+  if (wave < nw) {
+    float4_t* const dst = xch + wave * SLOT + lane;
+#pragma unroll
+    for (int y = 0; y < R; ++y)
+#pragma unroll
+      for (int m = 0; m < MB; ++m) dst[(y * MB + m) * 64] = acc[y][m];
+  }
+  __syncthreads();
+  constexpr int UNITS = R * MB;
+  for (int q0 = wave; q0 < UNITS; q0 += 4 * ks) {
+    float4_t res[4];
+    unsigned off[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int q = q0 + j * ks;
+      off[j] = q < UNITS ? out_at(q / MB, q % MB) : kOutOfRange;
+      if (a.res) res[j] = load_res(off[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int q = q0 + j * ks;
+      if (q >= UNITS) break;
+      float4_t s = xch[q * 64 + lane];
+      for (int w = 1; w < nw; ++w) s += xch[w * SLOT + q * 64 + lane];
+      if (a.res) s += res[j];
+      store(off[j], s);
+    }
+  }
+}
+
 template <typename T, int K, int S, int MB, int XH, int R, bool IMG>
 __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   constexpr int ES = (int)sizeof(T);
   constexpr int EPI = 16 / ES;
   constexpr int PAD = K / 2;
-  constexpr int HL = mbrow_halo_left(K, S), HR = mbrow_halo_right(K, S);
   constexpr int ROWS = (R - 1) * S + K;        // input rows of a strip
   constexpr int CW = 16 * S;                   // input columns of a strip
   constexpr int NH = ES == 4 ? 1 : 2;          // blocks of 16 channels in a chunk
@@ -64,30 +207,10 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   constexpr bool AHEAD = !(EXP && K == 5 && ES == 2);   // window weights asked for one block ahead (there they do not fit)
 
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const int t = threadIdx.x;
-  const int lane = t & 63;
-  const int ks = (int)blockDim.x >> 6;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int r = lane & 15, g4 = lane >> 4;
-
-  int tile;
-  {
-    const int G = gridDim.x;
-    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-    const int q = G >> 3, rem = G & 7;
-    tile = xcd * q + (xcd < rem ? xcd : rem) + local;
-  }
-  const int o0 = blockIdx.y * (MB * 16);
-  const StripAt strip = strip_at(tile, a.tiles_x, a.tiles_y, a.magic_x, a.magic_y);
-  const int tx = strip.tx, ty = strip.ty, grp = strip.group;
-  const bool two = a.ipt == 2;
-  const int n0 = two ? 2 * grp : grp;
-  const int j0 = tx * (16 - HL - HR);
-  const int lr = two ? (r & 7) : r;
-  const int img = two ? n0 + (r >> 3) : n0;
-  const int cj = j0 + lr;                      // the lane's output column
-  const int iy0 = ty * R * S - PAD;
-  const bool lane_out = (img < a.N) & (cj < a.Wo) & ((tx == 0) | (lr >= HL)) & ((tx == a.tiles_x - 1) | (lr < 16 - HR));
+  const MbAt at = mbrow_at<K, S, MB, R>(a);
+  const int t = threadIdx.x, lane = at.lane, ks = at.ks, wave = at.wave, r = at.r, g4 = at.g4, o0 = at.o0;
+  const bool two = at.two;
+  const int n0 = at.n0, j0 = at.j0, img = at.img, cj = at.cj, iy0 = at.iy0;
 
   const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, a.x_bytes);
   const __amdgpu_buffer_rsrc_t er = make_rsrc(a.we, a.we_bytes);
@@ -381,109 +504,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
     if constexpr (NH == 2) half(std::integral_constant<int, 1>{});
   }
 
-  // shortcut (all loads before the first store), activation, store of four filters of one pixel
-  const __amdgpu_buffer_rsrc_t rr = make_rsrc(a.res, a.res ? a.y_bytes : 0u);
-  const float lo_o = a.act_out == CPRUNE_ACT_NONE ? -__builtin_inff() : 0.0f;
-  const float hi_o = a.act_out == CPRUNE_ACT_RELU6 ? 6.0f : __builtin_inff();
-  auto out_at = [&](int y, int m) -> unsigned {
-    const int oy = ty * R + y, o = o0 + m * 16 + 4 * g4;
-    return lane_out & (oy < a.Ho) & (o < a.Cop) ? (unsigned)(((img * a.Ho + oy) * a.Wo + cj) * a.Cop + o) * ES : kOutOfRange;
-  };
-  auto load_res = [&](unsigned off) -> float4_t {
-    if constexpr (ES == 4) {
-      const uint4 q = load_b128(rr, off, 0);
-      return __builtin_bit_cast(float4_t, q);
-    } else {
-      return widen4<T>(load_b64(rr, off, 0));
-    }
-  };
-  auto store = [&](unsigned off, float4_t v) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = __builtin_amdgcn_fmed3f(v[q], lo_o, hi_o);
-    if (off == kOutOfRange) return;
-    if constexpr (ES == 4) *(float4_t*)((char*)a.y + off) = v;
-    else *(uint2*)((char*)a.y + off) = narrow4<T>(v);
-  };
-  if (ks == 1) {
-    constexpr int GROUP = MB > 4 ? 2 : 16 / MB;       // rows whose shortcuts are in flight together
-#pragma unroll
-    for (int y0 = 0; y0 < R; y0 += GROUP) {
-      if (a.res) {
-        float4_t res[GROUP][MB];
-#pragma unroll
-        for (int y = 0; y < GROUP; ++y)
-#pragma unroll
-          for (int m = 0; m < MB; ++m)
-            if (y0 + y < R) res[y][m] = load_res(out_at(y0 + y, m));
-#pragma unroll
-        for (int y = 0; y < GROUP; ++y)
-#pragma unroll
-          for (int m = 0; m < MB; ++m)
-            if (y0 + y < R) acc[y0 + y][m] += res[y][m];
-      }
-#pragma unroll
-      for (int y = 0; y < GROUP; ++y)
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-          if (y0 + y < R) store(out_at(y0 + y, m), acc[y0 + y][m]);
-    }
-    return;
-  }
-
-  // the sums of the wavefronts meet in LDS: the upper half hands over to the lower one until a.slots of them are left,
-  // whose sums are then added in order, the (row, filter block) units shared by all wavefronts
-  constexpr int SLOT = R * MB * 64;
-  float4_t* const xch = (float4_t*)lds;
-  int nw = ks;
-  while (nw > a.slots) {
-    const int hw = nw >> 1;
-    __syncthreads();
-    if (wave >= hw && wave < nw) {
-      float4_t* const dst = xch + (wave - hw) * SLOT + lane;
-#pragma unroll
-      for (int y = 0; y < R; ++y)
-#pragma unroll
-        for (int m = 0; m < MB; ++m) dst[(y * MB + m) * 64] = acc[y][m];
-    }
-    __syncthreads();
-    if (wave < hw) {
-      const float4_t* const src = xch + wave * SLOT + lane;
-#pragma unroll
-      for (int y = 0; y < R; ++y)
-#pragma unroll
-        for (int m = 0; m < MB; ++m) acc[y][m] += src[(y * MB + m) * 64];
-    }
-    nw = hw;
-  }
-  __syncthreads();
-  if (wave < nw) {
-    float4_t* const dst = xch + wave * SLOT + lane;
-#pragma unroll
-    for (int y = 0; y < R; ++y)
-#pragma unroll
-      for (int m = 0; m < MB; ++m) dst[(y * MB + m) * 64] = acc[y][m];
-  }
-  __syncthreads();
-  constexpr int UNITS = R * MB;
-  for (int q0 = wave; q0 < UNITS; q0 += 4 * ks) {
-    float4_t res[4];
-    unsigned off[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int q = q0 + j * ks;
-      off[j] = q < UNITS ? out_at(q / MB, q % MB) : kOutOfRange;
-      if (a.res) res[j] = load_res(off[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int q = q0 + j * ks;
-      if (q >= UNITS) break;
-      float4_t s = xch[q * 64 + lane];
-      for (int w = 1; w < nw; ++w) s += xch[w * SLOT + q * 64 + lane];
-      if (a.res) s += res[j];
-      store(off[j], s);
-    }
-  }
+  mbrow_finish<T, R, MB>(a, at, lds, acc);
 }
 
 // LDS of a work-group: the strip's input, later the sums of `slots` wavefronts
@@ -520,6 +541,10 @@ template <typename T, int K, int S>
 inline int launch_mbrow_ks(int mb, int xh, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a) {
 #define CPRUNE_MBROW(MB_, XH_) \
   if (mb == MB_ && xh == XH_) return launch_mbrow_one<T, K, S, MB_, XH_>(low, grid, ks, s, a);
+  if constexpr (sizeof(T) == 4 && K == 3) {      // (up to 96 filters: mbrow3_kernel.hpp)
+    CPRUNE_MBROW(8, 0) CPRUNE_MBROW(8, 12)
+    return CPRUNE_ERR_UNSUPPORTED;
+  } else {
   CPRUNE_MBROW(1, 0) CPRUNE_MBROW(2, 0) CPRUNE_MBROW(4, 0) CPRUNE_MBROW(6, 0) CPRUNE_MBROW(8, 0)
   if constexpr (sizeof(T) == 4) {
     CPRUNE_MBROW(2, 2) CPRUNE_MBROW(2, 3) CPRUNE_MBROW(2, 4)
@@ -528,8 +553,9 @@ inline int launch_mbrow_ks(int mb, int xh, int low, dim3 grid, int ks, hipStream
     CPRUNE_MBROW(2, 2) CPRUNE_MBROW(2, 4) CPRUNE_MBROW(4, 2) CPRUNE_MBROW(4, 4) CPRUNE_MBROW(6, 4)
     CPRUNE_MBROW(6, 6) CPRUNE_MBROW(8, 10)
   }
-#undef CPRUNE_MBROW
   return CPRUNE_ERR_UNSUPPORTED;
+  }
+#undef CPRUNE_MBROW
 }
 
 // The image form: 27 terms in one 32-byte unit per 8 (16) numbers.
@@ -543,7 +569,9 @@ inline int launch_mbrow_image(int mb, int low, dim3 grid, int ks, hipStream_t s,
 
 template <typename T>
 inline int launch_mbrow(int k, int stride, int mb, int xh, int low, dim3 grid, int ks, hipStream_t s, const MbArgs& a) {
-  if (a.Hi > 0) return k == 3 && stride == 1 ? launch_mbrow_image<T>(mb, low, grid, ks, s, a) : CPRUNE_ERR_UNSUPPORTED;
+  if constexpr (sizeof(T) == 2) {      // (fp32: mbrow3_kernel.hpp)
+    if (a.Hi > 0) return k == 3 && stride == 1 ? launch_mbrow_image<T>(mb, low, grid, ks, s, a) : CPRUNE_ERR_UNSUPPORTED;
+  }
   if (k == 3 && stride == 1) return launch_mbrow_ks<T, 3, 1>(mb, xh, low, grid, ks, s, a);
   if (k == 3 && stride == 2) return launch_mbrow_ks<T, 3, 2>(mb, xh, low, grid, ks, s, a);
   if (k == 5 && stride == 1) return launch_mbrow_ks<T, 5, 1>(mb, xh, low, grid, ks, s, a);
