@@ -99,7 +99,9 @@ def lib():
                      "cprune_fc_workspace_bytes", "cprune_probe_scratch_bytes", "cprune_probe_l2_bytes"):
             getattr(L, name).restype = C.c_size_t
         L.cprune_clear_tile_cache.restype = None
-        # (the call that is made most often: with its types known, addresses are passed as plain integers)
+        # (the calls that are made most often: with their types known, addresses are passed as plain integers)
+        L.cprune_cached_tile.argtypes = [C.POINTER(ConvDesc), C.POINTER(C.c_int), C.POINTER(C.c_int)]
+        L.cprune_conv_workspace_bytes.argtypes = [C.POINTER(ConvDesc), C.c_int]
         L.cprune_conv2d_bn_relu.argtypes = [C.POINTER(ConvDesc)] + [C.c_void_p] * 5 + [C.c_int, C.c_void_p, C.c_size_t, C.c_void_p]
         _lib = L
     return _lib
@@ -125,13 +127,21 @@ def _addr(t: Optional[torch.Tensor]):
     return t.data_ptr()
 
 
+def _raw_stream(stream=None) -> int:
+    """The caller's stream, or the current device's current one (torch.cuda.current_stream().cuda_stream without the object: 0.3 us, not 3)."""
+    return stream.cuda_stream if stream is not None else torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    return C.c_void_p(_raw_stream(stream))
 
 
 def _ws(nbytes: int, device) -> Optional[torch.Tensor]:
-    return torch.empty(max(int(nbytes), 16) if nbytes else 0, dtype=torch.uint8, device=device)
+    return torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=device) if nbytes else None
+
+
+def _size(ws: Optional[torch.Tensor]) -> int:
+    return ws.numel() if ws is not None else 0
 
 
 # ---- ranking / gather ------------------------------------------------------
@@ -149,7 +159,7 @@ def cprune_rank_filters(w: torch.Tensor, keep: int, want_scores=True, want_order
     ws = _ws(nws, dev)
     st = lib().cprune_rank_filters(_ptr(w), C.c_int(c_out), C.c_int(cpg), C.c_int(kh), C.c_int(kw),
                                    C.c_int(keep), _ptr(scores), _ptr(order), _ptr(kept), _ptr(ws),
-                                   C.c_size_t(ws.numel()), _stream(stream))
+                                   C.c_size_t(_size(ws)), _stream(stream))
     _check(st, "cprune_rank_filters")
     return scores, order, kept
 
@@ -262,7 +272,7 @@ def cprune_rank_filter_group(ws_list, keep: int, want_scores=True, want_order=Tr
     kept = torch.empty(max(keep, 1), dtype=torch.int32, device=dev)
     ws = _ws(lib().cprune_rank_filters_workspace_bytes(C.c_int(c_out)), dev)
     st = lib().cprune_rank_filter_group(ptrs, lens, C.c_int(n), C.c_int(c_out), C.c_int(keep), _ptr(scores),
-                                        _ptr(order), _ptr(kept), _ptr(ws), C.c_size_t(ws.numel()),
+                                        _ptr(order), _ptr(kept), _ptr(ws), C.c_size_t(_size(ws)),
                                         _stream(stream))
     _check(st, "cprune_rank_filter_group")
     return scores, order, kept
@@ -341,21 +351,23 @@ def cprune_conv_workspace_bytes(d: ConvDesc, variant: int = -1) -> int:
 def cprune_conv2d_bn_relu(d: ConvDesc, x, w, bias=None, residual=None, tile_variant: int = -1,
                           ws: Optional[torch.Tensor] = None, y: Optional[torch.Tensor] = None,
                           stream=None) -> torch.Tensor:
-    L = lib()
+    # (what the caller's thread does per call is the time of a small layer: 64 -> 45 at 32x32, one image, 11.7 us before, the kernel 6.5)
+    L = _lib or lib()
     if y is None:
         y = x.new_empty(out_shape(d), dtype=TORCH_DTYPE[d.dtype])
+        y_addr = y.data_ptr()
+    else:
+        y_addr = _addr(y)
     if ws is None:
         # the scratch of the variant the call will run, not the most any variant could ask for (128 -> 83 at 56x56, batch 8:
         # 0.7 MB and 264 MB, and looking through all variants is 4 us of the call); most variants need none
-        ref = C.byref(d)
         if tile_variant == -1 and d.groups == 1:
             v = C.c_int()
-            if L.cprune_cached_tile(ref, C.byref(v), None) == OK:
+            if L.cprune_cached_tile(d, v, None) == OK:
                 tile_variant = v.value
-        ws = _ws(L.cprune_conv_workspace_bytes(ref, C.c_int(tile_variant)), x.device)
-    st = L.cprune_conv2d_bn_relu(d, _addr(x), _addr(w), _addr(bias), _addr(residual), _addr(y), tile_variant, _addr(ws),
-                                 ws.numel(),
-                                 (stream if stream is not None else torch.cuda.current_stream()).cuda_stream)
+        ws = _ws(L.cprune_conv_workspace_bytes(d, tile_variant), x.device)
+    st = L.cprune_conv2d_bn_relu(d, _addr(x), _addr(w), _addr(bias), _addr(residual), y_addr, tile_variant, _addr(ws),
+                                 _size(ws), _raw_stream(stream))
     _check(st, "cprune_conv2d_bn_relu")
     return y
 
@@ -369,7 +381,7 @@ def cprune_select_tile(d: ConvDesc, x, w, bias=None, residual=None, warmup: int 
     all_ms = (C.c_float * nv)()
     v, best = C.c_int(-1), C.c_float(0)
     st = lib().cprune_select_tile(C.byref(d), _ptr(x), _ptr(w), _ptr(bias), _ptr(residual), _ptr(y),
-                                  _ptr(ws), C.c_size_t(ws.numel()), C.c_int(warmup), C.c_int(iters),
+                                  _ptr(ws), C.c_size_t(_size(ws)), C.c_int(warmup), C.c_int(iters),
                                   C.byref(v), C.byref(best), all_ms, _stream(stream))
     _check(st, "cprune_select_tile")
     return v.value, best.value, list(all_ms)
@@ -416,7 +428,7 @@ def cprune_fc(x, w, bias=None, act=ACT_NONE, stream=None):
     ws = _ws(lib().cprune_fc_workspace_bytes(C.c_int(n), C.c_int(f), C.c_int(c_out), C.c_int(dt)),
              x.device)
     st = lib().cprune_fc(_ptr(x), _ptr(w), _ptr(bias), C.c_int(n), C.c_int(f), C.c_int(c_out),
-                         C.c_int(act), C.c_int(dt), _ptr(y), _ptr(ws), C.c_size_t(ws.numel()),
+                         C.c_int(act), C.c_int(dt), _ptr(y), _ptr(ws), C.c_size_t(_size(ws)),
                          _stream(stream))
     _check(st, "cprune_fc")
     return y
@@ -534,7 +546,7 @@ def cprune_probe_mfma(dtype: int = F32, stream=None) -> float:
     """TFLOP/s of back-to-back MFMA instructions of `dtype` on register operands."""
     ws = _ws(lib().cprune_probe_scratch_bytes(), "cuda")
     out = C.c_float(0.0)
-    st = lib().cprune_probe_mfma(C.c_int(dtype), _ptr(ws), C.c_size_t(ws.numel()), C.byref(out),
+    st = lib().cprune_probe_mfma(C.c_int(dtype), _ptr(ws), C.c_size_t(_size(ws)), C.byref(out),
                                  _stream(stream))
     _check(st, "cprune_probe_mfma")
     return float(out.value)
