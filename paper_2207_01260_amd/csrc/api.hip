@@ -453,6 +453,7 @@ struct NetLayer {
   int dw_ks = 0;              // ... and how many wavefronts share a strip there (1, 2, 4, 8; 0: not timed), or a pixel block (4, 8)
   int dw_tile = kLowStrips;   // ... and what a work-group owns (DwTile)
   bool fused_away = false;    // depthwise conv that runs inside its consumer's kernel (no launch, no activation)
+  float* w_dw32 = nullptr;    // ... 16-bit data, 3x3: its weights as fp32, for the strip kernel
   int dw_reader = -1;         // depthwise conv that may run inside the 1x1 conv dw_reader's kernel
   int fuse_block = -1;        // 1x1 conv with fuse_dw set: index of the 1x1 expansion in front of that depthwise
                               // layer when the whole block (expansion, depthwise, this projection) is one kernel
@@ -771,7 +772,7 @@ static int net_run_mbrow(cprune_net* net, int i, int n, const void* x, void* dst
   a.x = image ? x : net->layers[E ? E->d.input : D.d.input].act;
   a.Hi = image ? E->h_in : 0; a.Wi = image ? E->w_in : 0;
   a.we = E ? E->w_expand : nullptr; a.be = E ? E->b : nullptr;
-  a.wdw = D.w; a.bdw = D.b; a.wp = P.w_proj; a.bp = P.b;
+  a.wdw = D.w_dw32 ? D.w_dw32 : D.w; a.bdw = D.b; a.wp = P.w_proj; a.bp = P.b;
   a.res = P.d.residual >= 0 ? net->layers[P.d.residual].act : nullptr;
   a.y = dst;
   a.N = n; a.H = D.h_in; a.W = D.w_in; a.Ho = D.h_out; a.Wo = D.w_out;
@@ -786,7 +787,7 @@ static int net_run_mbrow(cprune_net* net, int i, int n, const void* x, void* dst
   a.we_raw = E ? E->w : nullptr; a.wp_raw = P.w;
   a.we_bytes = !E ? 0u : (unsigned)(parts ? parts_packed_bytes(a.Ce, expand_rounds(*E, xh), mbrow3_twice(D.d.stride, xh, image)) : expand_packed_bytes(a.Ce, xh, net->dtype));
   a.wp_bytes = (unsigned)(parts ? parts_packed_bytes(a.O, a.nchunk, false) : rows_packed_bytes(a.O, a.Cpe, net->dtype));
-  a.wdw_bytes = (unsigned)((size_t)D.d.k * D.d.k * a.Cpe * es);
+  a.wdw_bytes = (unsigned)((size_t)D.d.k * D.d.k * a.Cpe * (D.w_dw32 ? 4 : es));
   a.y_bytes = (unsigned)((size_t)n * a.Ho * a.Wo * a.Cop * es);
   a.slots = 0;
   const int tiles_m = (a.O + mb * 16 - 1) / (mb * 16);
@@ -1565,6 +1566,14 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     if (P.cp_out != round_up_vec(pd.c_out, dtype) || P.nchw_in || P.map2x2 || P.fused_pool) continue;
     D.dw_reader = reader;
     P.dw_tile = dw_tile_untimed(P, D, max_batch, dtype);
+    if (dtype != CPRUNE_F32 && dd.k == 3) {
+      const long count = (long)9 * D.cp_in;
+      void* copy = nullptr;
+      rc = dev_alloc((size_t)count * 4, &copy);
+      D.w_dw32 = (float*)copy;
+      if (rc == CPRUNE_OK) rc = launch_widen(D.w, count, dtype, D.w_dw32, s);
+      if (rc != CPRUNE_OK) break;
+    }
     if (block_parts(dtype, D, P)) {
       const int rounds = (P.cp_in + 15) / 16;
       rc = dev_alloc(parts_packed_bytes(pd.c_out, rounds, false) + 16, &P.w_proj);

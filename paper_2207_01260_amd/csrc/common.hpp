@@ -162,7 +162,7 @@ struct MbArgs {
   const void* x;        // xh > 0: [n][h][w][cpi] block input; xh = 0: [n][h][w][cpe] expanded activations
   const void* we;       // expansion weights from launch_pack_expand, or null
   const float* be;      // [ce] or null
-  const void* wdw;      // [k][k][cpe] depthwise weights (folded)
+  const void* wdw;      // [k][k][cpe] depthwise weights (folded); 3x3: as fp32 in every type
   const float* bdw;     // [ce] or null
   const void* wp;       // [o][cpe] projection weights from launch_repack_rows
   const float* bp;      // [o] or null
@@ -220,6 +220,8 @@ int launch_mbrow_bf16(int k, int stride, int mb, int xh, int low, dim3 grid, int
 // expansion weights [ce][cp] -> the operand order of that kernel, [block of 16 channels][xh 32-byte units], zero padded
 size_t expand_packed_bytes(int ce, int xh, int dt);
 int launch_pack_expand(const void* w, int ce, int cp, int xh, int dt, void* y, hipStream_t s);
+// numbers of a 16-bit type as fp32
+int launch_widen(const void* x, long count, int dt, float* y, hipStream_t s);
 // fp32 weights [rows][terms] -> three bf16 parts in the operand order of mbrow3_kernel, [tile of 16 rows][round of 16 terms][operand], zero
 // padded to `rounds`; image: terms (channel, window row, window column) in rounds of four window rows of four columns.  Behind them a
 // word that is not zero if a weight is 2^60 or more.

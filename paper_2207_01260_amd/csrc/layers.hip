@@ -525,6 +525,12 @@ __global__ __launch_bounds__(256) void pack_parts_kernel(const float* __restrict
   if (twice) dst[128] = make_uint4(h[0], h[1], h[0], h[1]);
 }
 
+template <typename T>
+__global__ __launch_bounds__(256) void widen_kernel(const T* __restrict__ x, float* __restrict__ y, long count) {
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i < count) y[i] = (float)x[i];
+}
+
 // Whether a weight is 2^60 or more, or not finite (one work-group).
 __global__ __launch_bounds__(256) void parts_limit_kernel(const float* __restrict__ w, long n, unsigned* __restrict__ flag) {
   unsigned top = 0;
@@ -908,6 +914,12 @@ int launch_pack_expand(const void* w, int ce, int cp, int xh, int dt, void* y, h
   const long total = (long)(expand_packed_bytes(ce, xh, dt) / dtype_size(dt));
   CPRUNE_BY_DTYPE(dt, hipLaunchKernelGGL(pack_expand_kernel<T>, blocks_for(total), dim3(256), 0, s, (const T*)w, (T*)y,
                                          total, ce, cp, xh));
+  CPRUNE_LAUNCH_CHECK();
+  return CPRUNE_OK;
+}
+
+int launch_widen(const void* x, long count, int dt, float* y, hipStream_t s) {
+  CPRUNE_BY_DTYPE(dt, hipLaunchKernelGGL(widen_kernel<T>, blocks_for(count), dim3(256), 0, s, (const T*)x, y, count));
   CPRUNE_LAUNCH_CHECK();
   return CPRUNE_OK;
 }

@@ -25,8 +25,9 @@
 // fp32 with 3x3 windows and up to 96 filters runs mbrow3_kernel.hpp instead, the same strips on three bf16 parts.
 //
 // Measured (expansion + depthwise + projection, us): the layers apart or with the depthwise layer fused through LDS, the
-// faster of both / this kernel.  MnasNet bf16 at batch 16: 16 -> 38 -> 24, 112x112: 20 / 11; 24 -> 58 -> 24 at 56x56: 15 / 9; image 3 -> 32 -> 16
-// 20.3 / 16.6 (the windows' gather from LDS).  In fp32 the matrix instruction bounds it, which takes turns with the vector ALU (mbrow3_kernel.hpp).
+// faster of both / this kernel.  MnasNet bf16 at batch 16: 16 -> 38 -> 24, 112x112: 20 / 10; 24 -> 58 -> 24 at 56x56: 15 / 8.3; image 3 -> 32 -> 16
+// 20.3 / 16 (the windows' gather from LDS).  Window weights as fp32 and operands a row ahead, 3x3, before / with: 24 -> 58 -> 24 8.9 / 8.3, 32 -> 92 -> 32 at
+// 28x28 batch 64 11.0 / 10.1, 64 -> 330 -> 64 at 14x14 13.1 / 12.5; with 5x5 windows they spill (40 -> 88 -> 40 at 28x28 12.5 / 13.3).  In fp32 the matrix instruction bounds it, which takes turns with the vector ALU (mbrow3_kernel.hpp).
 #pragma once
 #include <atomic>
 #include "conv_nhwc_kernel.hpp"
@@ -204,7 +205,11 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   constexpr int XR = XH / 2;                   // whole 64-byte rounds of the expansion's reduction
   constexpr bool EXP = XH > 0;
   constexpr int IROWS = 2 * ROWS + 1, IPITCH = mbrow_image_pitch(ES);   // IMG: rows and row pitch of the staged image
+
   constexpr bool AHEAD = !(EXP && K == 5 && ES == 2);   // window weights asked for one block ahead (there they do not fit)
+  // 3x3 windows in 16-bit data: their weights come as fp32 (widened here they were a tenth of the vector operations and, until then, 18
+  // registers more), and the expansion's operands are read from LDS a row ahead; 5x5 windows have no room for either
+  constexpr bool W32 = ES == 4 || K == 3, READ_AHEAD = EXP && K == 3;
 
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const MbAt at = mbrow_at<K, S, MB, R>(a);
@@ -273,7 +278,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   unsigned w_off[K];
 #pragma unroll
   for (int v = 0; v < K; ++v)
-    w_off[v] = (unsigned)(cj * S + v - PAD) < (unsigned)a.W ? (unsigned)(g4 * 4 * NH * ES) : kOutOfRange;
+    w_off[v] = (unsigned)(cj * S + v - PAD) < (unsigned)a.W ? (unsigned)(g4 * 4 * NH * (W32 ? 4 : ES)) : kOutOfRange;
   // XH = 0: byte offset of the lane's pixel(s) in row 0 of the strip
   int x_base[S];
   if constexpr (!EXP) {
@@ -335,7 +340,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   };
   // Weights of one block of 16 channels (chunk c, block h), carried in registers: those of the next block are asked for as
   // soon as the last row has used the present ones.
-  typedef typename std::conditional<ES == 4, uint4, uint2>::type Quad;     // four channels
+  typedef typename std::conditional<W32, uint4, uint2>::type Quad;     // four channels
   Quad wq[K][K];
   uint4 ae[EXP ? XR : 1], ap[MB];
   uint2 ae_last;
@@ -345,8 +350,8 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
     const unsigned inval = (unsigned)(first_channel(c, h) >= a.Cpe) << 31;
 #pragma unroll
     for (int v = 0; v < K; ++v) {
-      const unsigned soff = (unsigned)(((u * K + v) * a.Cpe + c * 16 * NH + h * 4) * ES);
-      if constexpr (ES == 4) wq[u][v] = load_b128(dr, w_off[v] | inval, soff);
+      const unsigned soff = (unsigned)(((u * K + v) * a.Cpe + c * 16 * NH + h * 4) * (W32 ? 4 : ES));
+      if constexpr (W32) wq[u][v] = load_b128(dr, w_off[v] | inval, soff);
       else wq[u][v] = load_b64(dr, w_off[v] | inval, soff);
     }
   };
@@ -374,6 +379,17 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   }
   load_project(wave);
   if constexpr (EXP) __syncthreads();
+  uint4 xb[S][READ_AHEAD ? XR : 1];            // operands of the row that is expanded next
+  auto operands = [&](int i) {
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int j = 0; j < XR; ++j) {
+        if constexpr (IMG) xb[s][j] = window(i, j);
+        else xb[s][j] = *(const uint4*)&xl[(i * CW + s) * XP + j * 64];
+      }
+  };
+  if constexpr (READ_AHEAD) operands(0);
 
   for (int c = wave; c < a.nchunk; c += ks) {
     uint2 bq[ES == 4 ? 1 : R];                 // 16-bit data: finished rows of the chunk's first half
@@ -389,7 +405,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
       for (int u = 0; u < K; ++u)
 #pragma unroll
         for (int v = 0; v < K; ++v) {
-          if constexpr (ES == 4) wd[u][v] = __builtin_bit_cast(float4_t, wq[u][v]);
+          if constexpr (W32) wd[u][v] = __builtin_bit_cast(float4_t, wq[u][v]);
           else wd[u][v] = widen4<T>(wq[u][v]);
         }
       float4_t dacc[R];
@@ -412,7 +428,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
 #pragma unroll
             for (int j = 0; j < XR; ++j) {
               uint4 b;
-              if constexpr (IMG) b = window(i, j);
+              if constexpr (READ_AHEAD) b = xb[s][j];
               else b = *(const uint4*)&xl[(i * CW + s) * XP + j * 64];
               float4_t d[1][1] = {{ev}};
               const uint4 aa[1] = {ae[j]}, bb[1] = {b};
@@ -429,6 +445,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
             if constexpr (ES == 2) ev = widen4<T>(narrow4<T>(ev));
             en[s] = ev;
           }
+          if constexpr (READ_AHEAD) operands(i + 1 < ROWS ? i + 1 : 0);
         } else if (i < ROWS) {
 #pragma unroll
           for (int s = 0; s < S; ++s) {
