@@ -647,66 +647,43 @@ static int net_run_stem(cprune_net* net, int i, int n, const void* x, void* dst,
   return CPRUNE_OK;
 }
 
-// The fp32 7x7 / stride 2 first-layer kernel.  A work-group walks over a band of rows and repeats the row above it for the pool;
-// the bands are those for which the rounds of 1024 work-groups that fit the chip (four of two wavefronts per unit) take the fewest steps,
-// a work-group's start and its repeated row counted as one step and a fifth.  64 filters at 224x224 (us), as many bands as fit one
-// round / this rule: batch 32 60 / 60, 33 76 / 69; one image 9.0 / 8.6.
-static int net_run_stem7_f32(const NetLayer& L, int pool, int n, StemArgs a, hipStream_t s) {
+// The 7x7 / stride 2 first-layer kernel on the caller's NCHW input, with or without the max-pool behind it.  A work-group walks over a band
+// of rows and repeats the row above it for the pool; the bands are those for which the rounds of work-groups that fit the chip (two wavefronts each;
+// two, in 16-bit data four, on a SIMD) take the fewest steps, a work-group's start and its repeated row counted as one step and a fifth.  64 filters at
+// 224x224 in fp32 (us), as many bands as fit one round / this rule: batch 32 60 / 60, 33 76 / 69; one image 9.0 / 8.6.
+static int net_run_stem7(cprune_net* net, int i, int n, const void* x, void* dst, hipStream_t s) {
+  const NetLayer& L = net->layers[i];
+  const bool f32 = net->dtype == CPRUNE_F32;
+  const int pool = L.stem7 >= 2 ? L.stem7 - 1 : 0;
+  const size_t es = dtype_size(net->dtype);
+  StemArgs a;
+  a.x = x; a.w = L.w_stem7; a.bias = L.b; a.y = dst;
+  a.N = n; a.C = L.d.c_in; a.H = L.h_in; a.W = L.w_in; a.Ho = L.h_out; a.Wo = L.w_out;
+  a.O = L.d.c_out; a.Cop = L.cp_out; a.pad = L.d.pad; a.act = L.d.act;
+  if (pool) {
+    const NetLayer& P = net->layers[L.pool3];
+    a.y = P.act; a.Hp = P.h_out; a.Wp = P.w_out; a.Cop = P.cp_out;
+    if (pool == 2) a.y_map = dst;
+  }
   const int mb = a.O <= 32 ? 1 : 2;
   a.tiles_m = (a.O + 32 * mb - 1) / (32 * mb);
   a.tiles_x = pool ? (a.Wp + 6) / 7 : (a.Wo + 15) / 16;
-  const long strips = (long)n * a.tiles_x * a.tiles_m, steps = pool ? a.Hp : (a.Ho + 1) / 2;
+  const long strips = (long)n * a.tiles_x * a.tiles_m, steps = pool ? a.Hp : (a.Ho + 1) / 2, resident = f32 ? 1024 : mb == 1 ? 2560 : 2048;
   double best = 0.0;
   for (long bands = 1; bands <= steps; ++bands) {
     const long band = (steps + bands - 1) / bands;
-    const double cost = ((strips * bands + 1023) / 1024) * (band + 1.2);
+    const double cost = ((strips * bands + resident - 1) / resident) * (band + 1.2);
     if (bands == 1 || cost < best) { best = cost; a.band = (int)band; }
   }
   a.tiles_y = (int)((steps + a.band - 1) / a.band);
   a.magic_x = strip_magic(a.tiles_x); a.magic_y = strip_magic(a.tiles_y);
   a.w_raw = L.w;
-  a.x_bytes = (unsigned)((size_t)n * a.C * a.H * a.W * 4);
-  a.w_bytes = (unsigned)stem7_packed_bytes(a.O);
-  a.w_raw_bytes = (unsigned)((size_t)a.O * a.C * 49 * 4);
-  const int rc = launch_conv_stem7_f32(mb, pool, dim3((unsigned)((long)n * a.tiles_y * a.tiles_x), (unsigned)a.tiles_m), s, a);
-  if (rc != CPRUNE_OK) return rc;
-  CPRUNE_LAUNCH_CHECK();
-  return CPRUNE_OK;
-}
-
-// The 7x7 / stride 2 first-layer kernel on the caller's NCHW input, with or without the max-pool behind it.
-static int net_run_stem7(cprune_net* net, int i, int n, const void* x, void* dst, hipStream_t s) {
-  const NetLayer& L = net->layers[i];
-  const bool pool = L.stem7 >= 2;
-  StemArgs a;
-  a.x = x; a.w = L.w_stem7; a.bias = L.b; a.y = dst;
-  a.N = n; a.C = L.d.c_in; a.H = L.h_in; a.W = L.w_in; a.Ho = L.h_out; a.Wo = L.w_out;
-  a.O = L.d.c_out; a.Cop = L.cp_out; a.pad = L.d.pad; a.act = L.d.act;
-  const int mb = L.d.c_out <= 32 ? 2 : 4;
-  a.tiles_m = (a.O + mb * 16 - 1) / (mb * 16);
-  if (pool) {
-    const NetLayer& P = net->layers[L.pool3];
-    a.y = P.act; a.Hp = P.h_out; a.Wp = P.w_out; a.Cop = P.cp_out;
-    a.tiles_y = (a.Hp + 6) / 7; a.tiles_x = (a.Wp + 6) / 7;
-    if (L.stem7 == 3) a.y_map = dst;
-    if (net->dtype == CPRUNE_F32) return net_run_stem7_f32(L, L.stem7 - 1, n, a, s);
-  } else {
-    if (net->dtype == CPRUNE_F32) return net_run_stem7_f32(L, 0, n, a, s);
-    a.tiles_y = (a.Ho + 15) / 16; a.tiles_x = (a.Wo + 15) / 16;
-  }
-  a.vec_out = (a.Cop % 4) == 0 ? 1 : 0;
-  a.magic_x = strip_magic(a.tiles_x); a.magic_y = strip_magic(a.tiles_y);
-  const long ptiles = (long)n * a.tiles_y * a.tiles_x;
-  // as many workers as stay resident: weight tile + patch (+ the conv block the pool reads)
-  const long lds = (long)mb * 16 * (kStem7K * 2 + 16) + 37L * 320 + (pool ? 256L * (mb * 32 + 16) : 16L);
-  long per_cu = (160 * 1024) / lds;
-  per_cu = per_cu > 8 ? 8 : (per_cu < 1 ? 1 : per_cu);
-  const long workers = ptiles < 256 * per_cu ? ptiles : 256 * per_cu;
-  dim3 grid((unsigned)workers, (unsigned)a.tiles_m);
-  int rc;
-  if (net->dtype == CPRUNE_F16) rc = launch_conv_stem7_f16(mb, pool ? 1 : 0, grid, s, a);
-  else if (net->dtype == CPRUNE_BF16) rc = launch_conv_stem7_bf16(mb, pool ? 1 : 0, grid, s, a);
-  else rc = CPRUNE_ERR_UNSUPPORTED;
+  a.x_bytes = (unsigned)((size_t)n * a.C * a.H * a.W * es);
+  a.w_bytes = (unsigned)stem7_packed_bytes(a.O, net->dtype);
+  a.w_raw_bytes = (unsigned)((size_t)a.O * a.C * 49 * es);
+  const dim3 grid((unsigned)((long)n * a.tiles_y * a.tiles_x), (unsigned)a.tiles_m);
+  const int rc = f32 ? launch_conv_stem7_f32(mb, pool, grid, s, a) :
+                 net->dtype == CPRUNE_F16 ? launch_conv_stem7_f16(mb, pool, grid, s, a) : launch_conv_stem7_bf16(mb, pool, grid, s, a);
   if (rc != CPRUNE_OK) return rc;
   CPRUNE_LAUNCH_CHECK();
   return CPRUNE_OK;
@@ -1475,17 +1452,9 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
     NetLayer& L = net->layers[i];
     const cprune_layer_desc& d = L.d;
     if (!stem7_layer(L)) continue;
-    if (dtype == CPRUNE_F32) {
-      rc = dev_alloc(stem7_packed_bytes(d.c_out), &L.w_stem7);
-      if (rc == CPRUNE_OK) rc = launch_pack_stem7(L.w, d.c_out, d.c_in, L.w_stem7, s);
-      if (rc != CPRUNE_OK) break;
-    } else {
-      const int mb = d.c_out <= 32 ? 2 : 4;
-      const int rows = (d.c_out + mb * 16 - 1) / (mb * 16) * (mb * 16);
-      rc = dev_alloc((size_t)rows * kStem7K * es, &L.w_stem7);
-      if (rc == CPRUNE_OK) rc = launch_repack_stem7(L.w, d.c_out, d.c_in, rows, dtype, L.w_stem7, s);
-      if (rc != CPRUNE_OK) break;
-    }
+    rc = dev_alloc(stem7_packed_bytes(d.c_out, dtype), &L.w_stem7);
+    if (rc == CPRUNE_OK) rc = launch_pack_stem7(L.w, d.c_out, d.c_in, dtype, L.w_stem7, s);
+    if (rc != CPRUNE_OK) break;
     int reader = -1, readers = 0;
     for (int j = 0; j < n_layers; ++j) {
       if (net->layers[j].d.input == i) { reader = j; ++readers; }

@@ -274,10 +274,10 @@ struct StemArgs {
   unsigned magic_x, magic_y;   // strip_magic of tiles_x, tiles_y
   int vec_out;
   int Hp = 0, Wp = 0;   // 7x7 / stride 2 kernels with the 3x3 / stride 2 / pad 1 max-pool inside: the pooled map; y is
-                        // then [n][hp][wp][cop] and tiles_y, tiles_x count 7 x 7 blocks of it (fp32: bands of rows x 7 columns)
+                        // then [n][hp][wp][cop] and tiles_y, tiles_x count bands of its rows x 7 columns
   void* y_map = nullptr;   // fp32 7x7 / stride 2 kernel with the pool inside: the conv map as well (pool = 2)
-  int band = 0;         // fp32 7x7 / stride 2 kernel: pairs of conv rows a work-group walks over
-  const void* w_raw = nullptr;          // ... the weights as they are, [o][c][7][7]
+  int band = 0;         // 7x7 / stride 2 kernels: pairs of conv rows a work-group walks over
+  const void* w_raw = nullptr;          // ... fp32: the weights as they are, [o][c][7][7]
   unsigned x_bytes = 0, w_bytes = 0, w_raw_bytes = 0;
 };
 // (k, stride) in {(3, 1), (3, 2), (7, 2)}, mb in {2, 4} (16-filter blocks per tile); grid.x = workers
@@ -288,20 +288,15 @@ int launch_repack_stem(const void* w, int o, int ktot, int rows, int kp, int dt,
 int launch_conv_stem_f32(int k, int stride, int mb, dim3 grid, hipStream_t s, const StemArgs& a);
 int launch_conv_stem_f16(int k, int stride, int mb, dim3 grid, hipStream_t s, const StemArgs& a);
 int launch_conv_stem_bf16(int k, int stride, int mb, dim3 grid, hipStream_t s, const StemArgs& a);
-// 16-bit 7x7 / stride 2 / pad 3 first layer with the reduction ordered (window row, 8 window columns, 4 channels):
-// weights [rows][224] from launch_repack_stem7 (k = u * 32 + (v + 1) * 4 + c; zero for column slot 0, channel
-// slot 3, channels beyond c and rows beyond o).  mb in {2, 4}; pool = 1 runs the 3x3 / stride 2 / pad 1 max-pool
-// too (StemArgs::Hp, Wp); grid.x = workers sharing the (image, block) list, grid.y = filter tiles.
-constexpr int kStem7K = 224;
-int launch_repack_stem7(const void* w, int o, int c, int rows, int dt, void* y, hipStream_t s);
+// 7x7 / stride 2 / pad 3 first layer, fp32 on three bf16 parts: reduction ordered (channel, window row, 8 columns: zero, then the window's),
+// weights [16-filter block][6 rounds][part][lane][16 bytes] from launch_pack_stem7.  mb in {1, 2} blocks per wavefront, two wavefronts per
+// work-group; grid.x = (image, band of rows, strip), grid.y = tiles of 32 mb filters; pool = 1 runs the 3x3 / stride 2 / pad 1 max-pool too
+// (StemArgs::Hp, Wp), 2 (fp32) stores the conv map as well.
+constexpr int kStem7Rounds = 6;
+inline size_t stem7_packed_bytes(int o, int dt) { return (size_t)((o + 15) / 16) * kStem7Rounds * (dt == CPRUNE_F32 ? 3 : 1) * 1024; }
+int launch_pack_stem7(const void* w, int o, int c, int dt, void* y, hipStream_t s);
 int launch_conv_stem7_f16(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a);
 int launch_conv_stem7_bf16(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a);
-// The same layer in fp32 on three bf16 parts, reduction ordered (channel, window row, 8 columns: zero, then the window's), weights
-// [16-filter block][6 rounds][3 parts][lane][16 bytes] from launch_pack_stem7.  mb in {1, 2} blocks per wavefront, two wavefronts per
-// work-group; grid.x = (image, band of rows, strip), grid.y = tiles of 32 mb filters.
-constexpr int kStem7SplitRounds = 6;
-inline size_t stem7_packed_bytes(int o) { return (size_t)((o + 15) / 16) * kStem7SplitRounds * 3 * 1024; }
-int launch_pack_stem7(const void* w, int o, int c, void* y, hipStream_t s);
 int launch_conv_stem7_f32(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a);
 
 }  // namespace cprune

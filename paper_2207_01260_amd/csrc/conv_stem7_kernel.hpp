@@ -1,250 +1,204 @@
-// First layer of an ImageNet-style network in 16-bit data: 7 x 7 / stride 2 / pad 3 convolution of an
-// NCHW image with at most 3 channels, channels-last output, optionally with the 3 x 3 / stride 2 / pad 1
-// max-pool that follows it in the same kernel.
+// First layer of an ImageNet-style network in 16-bit data: 7 x 7 / stride 2 / pad 3 convolution of an NCHW image with at most 3
+// channels, channels-last output, optionally with the 3 x 3 / stride 2 / pad 1 max-pool behind it in the same kernel.
 //
-// The general first-layer kernel builds a lane's B operand element by element from a planar patch (one
-// 2-byte LDS read per k).  Here the patch is staged pixel-major, four channels per pixel (the fourth is
-// zero), and the reduction is ordered (window row, window column, channel) with the window row padded to 8
-// columns: one MFMA round of k = 32 is then one window row, and a lane's 16-byte quad of it is two
-// neighbouring pixels of the patch, 16-byte aligned because the output column stride is 2 pixels.  One LDS
-// read per operand and round; 7 rounds; 147 of the 224 multiplied terms are real (the rest meet zero
-// weights), which costs nothing noticeable at this data type.  A third of the LDS instructions of the general
-// kernel; by itself that only draws level with it, because in 16-bit data this layer's time is the vector work
-// around the MFMAs (bias, activation, conversion, addresses) and waiting.  What pays is the pool:
+// The strips of conv_stem7_split_kernel.hpp on numbers as they are: the image in planes [channel][16 rows as a ring][columns], a reduction of
+// (channel, window row) units of 8 columns (147 of 192 terms real), weights in registers for good, two conv rows and one barrier a
+// step, the next four image rows on their way meanwhile, rows pooled across lanes and steps in registers before they are rounded (the
+// maximum of rounded numbers is the rounded maximum).
 //
-// A work-group owns a 16 x 16 block of conv outputs and MT = 16 * MB filters, keeps its weight tile in
-// LDS and walks over several blocks (the next block's patch travels to registers meanwhile).  With the
-// pool fused the block sits at conv offset (2 * py0 - 1, 2 * px0 - 1) and yields the 7 x 7 pooled
-// outputs whose windows lie inside it (rows and columns 0..14; the sixteenth is computed and not used):
-// activated conv outputs go to LDS in the activation type, as the separate layer would store them, and
-// the pooled maxima are written with 16-byte stores.  The conv map, the largest tensor of such a network,
-// never reaches memory, and the pool's launch goes away.
+// The kernel it replaced gave a work-group a 16 x 16 block of conv outputs, four channels a pixel (224 terms), and handed the block to the
+// pool through LDS.  What bounds this one: the vector work around the MFMAs (per row and filter block 4 sums' bias, clamp and maxima).
+// Measured with the pool, 16 x 16 blocks / this kernel (us): 64 filters at 224x224, batch 32 29.6 / 23.6, 8 10.0 / 9.7, 3 8.0 / 6.6, 1 7.9 / 4.5; 64 at
+// 64x64, batch 16 7.9 / 4.9; 96 at 160x160, batch 8 14.2 / 9.4; 10 at 96x96, batch 33 7.0 / 6.3.  17 to 32 filters, 16 for each wavefront, leave the rows'
+// addresses and reads to half the products: 24 at 301x301, batch 5 8.6 / 8.8, 32 at 224x224, batch 8 6.9 / 7.9 (two strips side by side with
+// all filters in each wavefront: 9.8).
 #pragma once
-#include "conv_patch_kernel.hpp"
+#include "conv_split_kernel.hpp"
 #include "strip_index.hpp"
 
 namespace cprune {
 
+// POOL 0: the layer alone; 1: with the pool
 template <typename T, int MB, int POOL>
-__global__ __launch_bounds__(256) void conv_stem7_kernel(StemArgs a) {
+__global__ __launch_bounds__(128, MB == 1 ? 5 : 4) void conv_stem7_kernel(StemArgs a) {
   static_assert(sizeof(T) == 2, "16-bit data");
-  constexpr int NT = 256;
-  constexpr int K = 7;
-  constexpr int TH = 16, NB = 4;              // wave w owns conv rows 4w .. 4w + 3 of the block, 16 columns each
-  constexpr int MT = MB * 16;
-  constexpr int PH = (TH - 1) * 2 + K;        // 37 patch rows
-  constexpr int PWC = 40;                     // patch columns (38 used), 4 channels x 2 bytes each
-  constexpr int PROW = PWC * 8;               // bytes per patch row
-  constexpr int KP = K * 32;                  // k per filter: 7 window rows x (8 columns x 4 channels)
-  constexpr int AROW = KP * 2 + 16;           // bytes per weight row
-  constexpr int CROW = MT * 2 + 16;           // bytes per pixel of the conv block kept for the pool
-  constexpr int NL = (PH * (PWC / 2) + NT - 1) / NT;   // pixel pairs of the patch per thread
-
-  __shared__ __attribute__((aligned(16))) unsigned char sA[MT * AROW];
-  __shared__ __attribute__((aligned(16))) unsigned char sP[PH * PROW];
-  __shared__ __attribute__((aligned(16))) unsigned char sC[POOL ? 256 * CROW : 16];
+  constexpr int NT = 128, NR = kStem7Rounds;
+  constexpr int STEP = POOL ? 14 : 16;          // conv columns, or image column pairs, from strip to strip
+  constexpr int PAIRS = 19;                     // column pairs a strip needs: 2 * 15 + 8 columns
+  constexpr int PITCH = 21;                     // dwords (column pairs) per staged row
+  constexpr int FIRST = POOL ? 11 : 9;          // image rows under the first step
+  __shared__ uint32_t sP[3 * 16 * PITCH];
 
   const int t = threadIdx.x;
   const int lane = t & 63;
-  const int wave = t >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r = lane & 15, g4 = lane >> 4;
 
-  int worker;
+  int tile;
   {
     const int G = gridDim.x;
     const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
     const int q = G >> 3, rem = G & 7;
-    worker = xcd * q + (xcd < rem ? xcd : rem) + local;
+    tile = xcd * q + (xcd < rem ? xcd : rem) + local;
   }
-  const int o0 = blockIdx.y * MT;
-  const unsigned short* __restrict__ xg = (const unsigned short*)a.x;
+  const StripAt strip = strip_at(tile, a.tiles_x, a.tiles_y, a.magic_x, a.magic_y);
+  const int n = strip.group, tx = strip.tx, ty = strip.ty;
+  const int o0 = ((int)blockIdx.y * 2 + wave) * (MB * 16);
+  const int p_end = POOL ? a.Hp : (a.Ho + 1) >> 1;            // steps of the whole map
+  const int p0 = ty * a.band, p1 = min(p0 + a.band, p_end);
+  const int cx = STEP * tx - (POOL ? 1 : 0) + r;        // the lane's conv column
+  const int ix0 = 2 * (cx - r) - 4;                           // image column of staged column 0
 
-  // ---- once per worker: the weight tile (16-byte copies of packed rows) ----
+  const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, a.x_bytes);
+  const __amdgpu_buffer_rsrc_t wr = make_rsrc(a.w, a.w_bytes);
+
+  // ---- staging: item = (row, channel, column pair); row iy lives in ring row (iy + 8) & 15 ----
+  struct Item { int off, lds, row; bool c0, c1; };            // byte offset in image row 0; dword of ring row 0
+  auto item = [&](int idx, int rows) CPRUNE_INLINE -> Item {
+    const int rc = idx / PAIRS, pair = idx - rc * PAIRS;
+    const int row = rc / 3, c = rc - row * 3;
+    const int ix = ix0 + 2 * pair;
+    const bool in = row < rows && c < a.C;
+    return Item{((n * a.C + c) * a.H * a.W + ix) * 2, c * (16 * PITCH) + pair, row < rows ? row : -1,
+                in && (unsigned)ix < (unsigned)a.W, in && (unsigned)(ix + 1) < (unsigned)a.W};
+  };
+  auto load_item = [&](const Item& it, int iy, uint32_t (&v)[2]) CPRUNE_INLINE {
+    const bool in = (unsigned)iy < (unsigned)a.H;
+    const unsigned off = (unsigned)(it.off + iy * a.W * 2);
+    v[0] = Elem<T>::load(xr, in & it.c0 ? off : kOutOfRange, 0);
+    v[1] = Elem<T>::load(xr, in & it.c1 ? off + 2u : kOutOfRange, 0);
+  };
+  auto store_item = [&](const Item& it, int iy, const uint32_t (&v)[2]) CPRUNE_INLINE {
+    if (it.row < 0) return;
+    sP[it.lds + ((iy + 8) & 15) * PITCH] = v[0] | v[1] << 16;
+  };
+
+  // ---- the first rows, then the weights, on their way together ----
+  const int iy_first = 4 * p0 + 6 - FIRST;
   {
-    constexpr int QROW = KP * 2 / 16;
-    const uint4* __restrict__ wq = (const uint4*)a.w + (size_t)o0 * QROW;
-    for (int idx = t; idx < MT * QROW; idx += NT) {
-      const int m = idx / QROW, q = idx - m * QROW;
-      *(uint4*)&sA[m * AROW + q * 16] = wq[idx];
+    constexpr int U = (FIRST * 3 * PAIRS + NT - 1) / NT;
+    Item it[U];
+    uint32_t v[U][2];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      it[j] = item(t + NT * j, FIRST);
+      load_item(it[j], iy_first + it[j].row, v[j]);
     }
+#pragma unroll
+    for (int j = 0; j < U; ++j) store_item(it[j], iy_first + it[j].row, v[j]);
   }
-  float4_t bias4[MB];
+  uint4 wt[MB][NR];
 #pragma unroll
-  for (int i = 0; i < MB; ++i) bias4[i] = load_bias4(a.bias, a.O, o0 + i * 16 + 4 * g4);
-
-  int b_frag[NB];
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
-  for (int j = 0; j < NB; ++j) b_frag[j] = (2 * (4 * wave + j)) * PROW + 16 * (r + g4);
-  const int a_frag = r * AROW + g4 * 16;
-  int mb_count = (a.O - o0 + 15) / 16;
-  mb_count = mb_count > MB ? MB : mb_count;
-
-  // block -> (image, conv origin of the 16 x 16 block)
-  auto origin = [&](int tile, int& n, int& cy0, int& cx0) {
-    const StripAt at = strip_at(tile, a.tiles_x, a.tiles_y, a.magic_x, a.magic_y);
-    n = at.group;
-    cy0 = POOL ? 14 * at.ty - 1 : 16 * at.ty;
-    cx0 = POOL ? 14 * at.tx - 1 : 16 * at.tx;
-  };
-
-  // the patch of the next block travels to registers while this one is multiplied: per thread NL pairs of
-  // neighbouring pixels (an even input column and the next), one 32-bit word per channel
-  uint32_t pre[NL][3];
-  const bool w_even = (a.W & 1) == 0;
-  auto load_patch = [&](int tile) {
-    int n, cy0, cx0;
-    origin(tile, n, cy0, cx0);
-    const int iy0 = 2 * cy0 - 3, ix0 = 2 * cx0 - 4;   // ix0 is even: a pair never straddles the image edge when W is even
+    for (int j = 0; j < NR; ++j)
+      wt[i][j] = load_b128(wr, o0 + i * 16 < a.O ? (unsigned)(((o0 >> 4) + i) * NR + j) * 1024u + (unsigned)lane * 16u : kOutOfRange, 0);
+  float4_t bias[MB];
 #pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      const int idx = t + NT * j;
-      const int pr = idx / (PWC / 2), pp = idx - pr * (PWC / 2);
-      const int iy = iy0 + pr, ix = ix0 + 2 * pp;
-      const bool row_ok = pr < PH && (unsigned)iy < (unsigned)a.H;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        uint32_t v = 0;
-        if (row_ok && c < a.C) {
-          const size_t base = ((size_t)(n * a.C + c) * a.H + iy) * a.W;
-          if (w_even) {
-            if ((unsigned)ix < (unsigned)a.W) v = *(const uint32_t*)(xg + base + ix);
-          } else {
-            if ((unsigned)ix < (unsigned)a.W) v = xg[base + ix];
-            if ((unsigned)(ix + 1) < (unsigned)a.W) v |= (uint32_t)xg[base + ix + 1] << 16;
-          }
-        }
-        pre[j][c] = v;
-      }
-    }
-  };
-  auto store_patch = [&]() {
-#pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      const int idx = t + NT * j;
-      if (idx >= PH * (PWC / 2)) continue;
-      uint4 q;   // pixel 0: (c0, c1, c2, 0), pixel 1 the same
-      q.x = (pre[j][0] & 0xffffu) | (pre[j][1] << 16);
-      q.y = pre[j][2] & 0xffffu;
-      q.z = (pre[j][0] >> 16) | (pre[j][1] & 0xffff0000u);
-      q.w = pre[j][2] >> 16;
-      *(uint4*)&sP[idx * 16] = q;   // (pr * (PWC / 2) + pp) * 16 = pr * PROW + pp * 16
-    }
-  };
+  for (int i = 0; i < MB; ++i) bias[i] = load_bias4(a.bias, a.O, o0 + i * 16 + 4 * g4);
 
-  ConvArgs e;
-  e.bias = a.bias; e.res = nullptr; e.y = a.y; e.O = a.O; e.Cop = a.Cop; e.act = a.act; e.vec_out = a.vec_out; e.pool4 = 0;
+  constexpr int U = (4 * 3 * PAIRS + NT - 1) / NT;            // items of a later step
+  Item it[U];
+#pragma unroll
+  for (int j = 0; j < U; ++j) it[j] = item(t + NT * j, 4);
 
-  // Order inside a block: multiply; barrier; the NEXT block's patch goes from registers to LDS; this block's
-  // stores; barrier; the loads of the block after next (so the wait for a patch never has stores issued just
-  // before it in front of it: loads and stores share one in-order counter).
-  const int ptiles = a.N * a.tiles_y * a.tiles_x;
-  if (worker < ptiles) {
-    load_patch(worker);
-    store_patch();
-    __syncthreads();
-    if (worker + (int)gridDim.x < ptiles) load_patch(worker + gridDim.x);
+  // the lane's unit of each round: window row, dword of its channel's plane
+  int unit_row[NR], unit_lds[NR];
+#pragma unroll
+  for (int j = 0; j < NR; ++j) {
+    const int q = min(4 * j + g4, 20), c = q / 7;             // (units past the last meet zero weights)
+    unit_row[j] = q - c * 7;
+    unit_lds[j] = c * (16 * PITCH) + r;
   }
-  for (int tile = worker; tile < ptiles; tile += gridDim.x) {
-    int n, cy0, cx0;
-    origin(tile, n, cy0, cx0);
-    const bool more = tile + (int)gridDim.x < ptiles;
 
-    // ---- multiply: one round per window row ----
-    float4_t accs[1][MB][NB];
+  // conv row cy: sums of the lane's pixel
+  auto multiply = [&](int cy, float4_t (&out)[MB]) CPRUNE_INLINE {
+#pragma unroll
+    for (int i = 0; i < MB; ++i) out[i] = bias[i];
+    uint4 x[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) __builtin_memcpy(&x[j], sP + unit_lds[j] + ((2 * cy + 5 + unit_row[j]) & 15) * PITCH, 16);    // (2 cy - 3 + row) + 8
+#pragma unroll
+    for (int j = 0; j < NR; ++j)
+#pragma unroll
+      for (int i = 0; i < MB; ++i) out[i] = mfma_split<T>(wt[i][j], x[j], out[i]);
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) accs[0][i][j] = (float4_t){0.f, 0.f, 0.f, 0.f};
-    auto main_loop = [&](auto mbc_tag) {
-      constexpr int MBC = decltype(mbc_tag)::value;
-      uint4 af[2][MB], bf[2][NB];
-      auto fetch = [&](int ky, uint4 (&fa)[MB], uint4 (&fb)[NB]) {
+      for (int q = 0; q < 4; ++q) out[i][q] = apply_act(out[i][q], a.act);
+  };
+  // the largest of three neighbouring columns, in the lane of the first (an activated value is never NaN)
+  const bool col_ok = (unsigned)cx < (unsigned)a.Wo;
+  auto across = [&](float4_t (&v)[MB]) CPRUNE_INLINE {
 #pragma unroll
-        for (int j = 0; j < NB; ++j) fb[j] = *(const uint4*)&sP[b_frag[j] + ky * PROW];
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int i = 0; i < MBC; ++i) fa[i] = *(const uint4*)&sA[a_frag + i * 16 * AROW + ky * 64];
-      };
-      fetch(0, af[0], bf[0]);
-#pragma unroll
-      for (int ky = 0; ky < K; ++ky) {
-        if (ky + 1 < K) fetch(ky + 1, af[(ky + 1) & 1], bf[(ky + 1) & 1]);
-        mma_round<T, MBC, NB, MB, 1>(af[ky & 1], bf[ky & 1], accs, ky);
+      for (int q = 0; q < 4; ++q) {
+        const float c0 = col_ok ? v[i][q] : -__builtin_inff();
+        auto next = [&](auto d) CPRUNE_INLINE {
+          return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, c0), 0x100 + decltype(d)::value, 0xf, 0xf, true));
+        };
+        v[i][q] = fmaxf(fmaxf(c0, next(std::integral_constant<int, 1>{})), next(std::integral_constant<int, 2>{}));
       }
-    };
-    switch (mb_count) {
-      case 1: main_loop(std::integral_constant<int, 1>{}); break;
-      case 2: if constexpr (MB >= 2) main_loop(std::integral_constant<int, 2>{}); break;
-      case 3: if constexpr (MB >= 3) main_loop(std::integral_constant<int, 3>{}); break;
-      case 4: if constexpr (MB >= 4) main_loop(std::integral_constant<int, 4>{}); break;
-      default: break;
+  };
+  auto store = [&](void* map, int y, int x, int w, int h, bool lane_ok, const float4_t (&v)[MB]) CPRUNE_INLINE {
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      const int o = o0 + i * 16 + 4 * g4;
+      if (lane_ok & (x < w) & (o < a.Cop)) *(uint2*)((T*)map + ((size_t)(n * h + y) * w + x) * a.Cop + o) = narrow4<T>(v[i]);
     }
+  };
 
-    if constexpr (POOL) {
-      // activated conv outputs in the activation type, pixel-major
+  __syncthreads();
+  float4_t carry[MB];
 #pragma unroll
-      for (int j = 0; j < NB; ++j)
+  for (int i = 0; i < MB; ++i) carry[i] = (float4_t){-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
+  if (POOL && p0 > 0 && o0 < a.O) {
+    multiply(2 * p0 - 1, carry);
+  }
+  for (int p = p0; p < p1; ++p) {
+    const bool more = p + 1 < p1;
+    uint32_t v[U][2];
+    if (more) {
 #pragma unroll
-        for (int i = 0; i < MB; ++i) {
-          T h[4];
-#pragma unroll
-          for (int c = 0; c < 4; ++c) h[c] = Elem<T>::from_f32(apply_act(accs[0][i][j][c] + bias4[i][c], a.act));
-          *(uint2*)&sC[((4 * wave + j) * 16 + r) * CROW + (i * 16 + 4 * g4) * 2] = *(const uint2*)h;
-        }
+      for (int j = 0; j < U; ++j) load_item(it[j], 4 * p + 6 + it[j].row, v[j]);
     }
-    __syncthreads();          // everyone is done reading the patch (and the conv block is complete)
-    if (more) store_patch();
-
-    if constexpr (!POOL) {
+    if (o0 < a.O) {
+      float4_t top[MB], s[MB];                   // the first row of the step, and the largest of the window's; the second row
+      multiply(2 * p, top);
+      const bool second = 2 * p + 1 < a.Ho;
+      if (second) multiply(2 * p + 1, s);
+      if constexpr (POOL != 0) {
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const int oy = cy0 + 4 * wave + j, ox = cx0 + r;
-        if (oy >= a.Ho || ox >= a.Wo) continue;
-        const int p = (n * a.Ho + oy) * a.Wo + ox;
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int i = 0; i < MB; ++i) nhwc_store4<T>(e, accs[0][i][j], p, o0 + i * 16 + 4 * g4, bias4[i]);
-      }
-    } else {
-      // the 3 x 3 / stride 2 maxima of the conv block
-      constexpr int QN = MT / 8;                  // 16-byte channel groups per pixel
-      const int py0 = (cy0 + 1) >> 1, px0 = (cx0 + 1) >> 1;
-      for (int idx = t; idx < 49 * QN; idx += NT) {
-        const int q = idx % QN, pp = idx / QN;
-        const int pyl = pp / 7, pxl = pp - pyl * 7;
-        const int py = py0 + pyl, px = px0 + pxl;
-        if (py >= a.Hp || px >= a.Wp || o0 + q * 8 >= a.Cop) continue;
-        float m[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) m[c] = -INFINITY;
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy)
-#pragma unroll
-          for (int dx = 0; dx < 3; ++dx) {
-            const int cyl = 2 * pyl + dy, cxl = 2 * pxl + dx;
-            if ((unsigned)(cy0 + cyl) >= (unsigned)a.Ho || (unsigned)(cx0 + cxl) >= (unsigned)a.Wo) continue;
-            const uint4 v = *(const uint4*)&sC[(cyl * 16 + cxl) * CROW + q * 16];
-            const T* hv = (const T*)&v;
-#pragma unroll
-            for (int c = 0; c < 8; ++c) m[c] = fmaxf(m[c], Elem<T>::to_f32(hv[c]));
+          for (int q = 0; q < 4; ++q) {
+            top[i][q] = fmaxf(carry[i][q], second ? fmaxf(top[i][q], s[i][q]) : top[i][q]);
+            carry[i][q] = s[i][q];
           }
-        T h[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) h[c] = Elem<T>::from_f32(m[c]);
-        *(uint4*)((T*)a.y + ((size_t)(n * a.Hp + py) * a.Wp + px) * a.Cop + o0 + q * 8) = *(const uint4*)h;
+        across(top);
+        store(a.y, p, 7 * tx + (r >> 1), a.Wp, a.Hp, ((r & 1) == 0) & (r < 14), top);
+      } else {
+        store(a.y, 2 * p, cx, a.Wo, a.Ho, true, top);
+        if (second) store(a.y, 2 * p + 1, cx, a.Wo, a.Ho, true, s);
       }
     }
-    __syncthreads();          // the next patch is in place; the conv block may be overwritten
-    if (tile + 2 * (int)gridDim.x < ptiles) load_patch(tile + 2 * gridDim.x);
+    if (more) {
+#pragma unroll
+      for (int j = 0; j < U; ++j) store_item(it[j], 4 * p + 6 + it[j].row, v[j]);
+    }
+    __syncthreads();
   }
 }
 
 template <typename T>
 inline int launch_stem7(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a) {
-#define CPRUNE_STEM7(MB_, POOL_)                                                                   \
-  if (mb == MB_ && pool == POOL_) {                                                                \
-    hipLaunchKernelGGL((conv_stem7_kernel<T, MB_, POOL_>), grid, dim3(256), 0, s, a);              \
-    return CPRUNE_OK;                                                                              \
+#define CPRUNE_STEM7(MB_, POOL_)                                                                        \
+  if (mb == MB_ && pool == POOL_) {                                                                     \
+    hipLaunchKernelGGL((conv_stem7_kernel<T, MB_, POOL_>), grid, dim3(128), 0, s, a);                   \
+    return CPRUNE_OK;                                                                                   \
   }
-  CPRUNE_STEM7(2, 0) CPRUNE_STEM7(2, 1) CPRUNE_STEM7(4, 0) CPRUNE_STEM7(4, 1)
+  CPRUNE_STEM7(1, 0) CPRUNE_STEM7(1, 1) CPRUNE_STEM7(2, 0) CPRUNE_STEM7(2, 1)
 #undef CPRUNE_STEM7
   return CPRUNE_ERR_UNSUPPORTED;
 }

@@ -32,7 +32,7 @@ namespace cprune {
 // POOL 0: the layer alone; 1: with the pool; 2: with the pool, and the conv map written as well
 template <int MB, int POOL>
 __global__ __launch_bounds__(128, 2) void conv_stem7_split_kernel(StemArgs a) {
-  constexpr int NT = 128, NR = kStem7SplitRounds;
+  constexpr int NT = 128, NR = kStem7Rounds;
   constexpr int PAIRS = 19;                     // column pairs a strip needs: 2 * 15 + 8 columns
   constexpr int PITCH = 21;                     // dwords (column pairs) per staged row
   constexpr int PLANE = 3 * 16 * PITCH;         // dwords per part

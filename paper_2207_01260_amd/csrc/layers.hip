@@ -614,39 +614,31 @@ __global__ __launch_bounds__(256) void repack_stem_kernel(const T* __restrict__ 
   y[i] = v;
 }
 
-// OIHW 7x7 weights -> [rows][224]: k = u * 32 + (v + 1) * 4 + c (window row, window column shifted by one slot,
-// channel), zero elsewhere
-template <typename T>
-__global__ __launch_bounds__(256) void repack_stem7_kernel(const T* __restrict__ w, T* __restrict__ y, long total,
-                                                           int o_count, int c_count) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const int k = (int)(i % kStem7K);
-  const long o = i / kStem7K;
-  const int u = k >> 5, slot = (k >> 2) & 7, c = k & 3;
-  T v = (T)0.0f;
-  if (o < o_count && c < c_count && slot >= 1) v = w[((o * c_count + c) * 7 + u) * 7 + (slot - 1)];
-  y[i] = v;
-}
-
-// OIHW 7x7 fp32 weights -> [16-filter block][round][part][lane = quarter * 16 + filter][8 columns]: unit 4 * round + quarter =
+// OIHW 7x7 weights -> [16-filter block][round][part (fp32: of three)][lane = quarter * 16 + filter][8 columns]: unit 4 * round + quarter =
 // (channel, window row), its columns a zero and the window row's seven
-__global__ __launch_bounds__(256) void pack_stem7_kernel(const float* __restrict__ w, uint4* __restrict__ y, int total, int o_count,
-                                                         int c_count) {
+template <typename T>
+__global__ __launch_bounds__(256) void pack_stem7_kernel(const T* __restrict__ w, uint4* __restrict__ y, int total, int o_count, int c_count) {
   const int i = blockIdx.x * 256 + threadIdx.x;      // one lane of one round of one block
   if (i >= total) return;
-  const int lane = i & 63, round = (i >> 6) % kStem7SplitRounds, block = (i >> 6) / kStem7SplitRounds;
+  const int lane = i & 63, round = (i >> 6) % kStem7Rounds, block = (i >> 6) / kStem7Rounds;
   const int o = block * 16 + (lane & 15), q = 4 * round + (lane >> 4), c = q / 7, u = q - c * 7;
   const bool row = o < o_count && c < c_count;
-  const float* const src = w + (row ? ((o * c_count + c) * 7 + u) * 7 : 0);
-  uint32_t v[8], part[3][4];
-  v[0] = 0;
+  const T* const src = w + (row ? ((o * c_count + c) * 7 + u) * 7 : 0);
+  T v[8];
+  v[0] = (T)0.0f;
 #pragma unroll
-  for (int e = 0; e < 7; ++e) v[e + 1] = row ? __float_as_uint(src[e]) : 0u;
+  for (int e = 0; e < 7; ++e) v[e + 1] = row ? src[e] : (T)0.0f;
+  if constexpr (sizeof(T) == 2) {
+    uint4 all;
+    __builtin_memcpy(&all, v, 16);
+    y[(size_t)(i >> 6) * 64 + lane] = all;
+  } else {
+    uint32_t part[3][4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) split3(v[2 * e], v[2 * e + 1], part[0][e], part[1][e], part[2][e]);
+    for (int e = 0; e < 4; ++e) split3(__float_as_uint(v[2 * e]), __float_as_uint(v[2 * e + 1]), part[0][e], part[1][e], part[2][e]);
 #pragma unroll
-  for (int p = 0; p < 3; ++p) y[((size_t)(i >> 6) * 3 + p) * 64 + lane] = make_uint4(part[p][0], part[p][1], part[p][2], part[p][3]);
+    for (int p = 0; p < 3; ++p) y[((size_t)(i >> 6) * 3 + p) * 64 + lane] = make_uint4(part[p][0], part[p][1], part[p][2], part[p][3]);
+  }
 }
 
 inline dim3 blocks_for(long total) { return dim3((unsigned)((total + 255) / 256)); }
@@ -964,17 +956,9 @@ int launch_repack_stem(const void* w, int o, int ktot, int rows, int kp, int dt,
   return CPRUNE_OK;
 }
 
-int launch_repack_stem7(const void* w, int o, int c, int rows, int dt, void* y, hipStream_t s) {
-  const long total = (long)rows * kStem7K;
-  CPRUNE_BY_DTYPE(dt, hipLaunchKernelGGL(repack_stem7_kernel<T>, blocks_for(total), dim3(256), 0, s, (const T*)w, (T*)y,
-                                         total, o, c));
-  CPRUNE_LAUNCH_CHECK();
-  return CPRUNE_OK;
-}
-
-int launch_pack_stem7(const void* w, int o, int c, void* y, hipStream_t s) {
-  const int total = (o + 15) / 16 * kStem7SplitRounds * 64;
-  hipLaunchKernelGGL(pack_stem7_kernel, blocks_for(total), dim3(256), 0, s, (const float*)w, (uint4*)y, total, o, c);
+int launch_pack_stem7(const void* w, int o, int c, int dt, void* y, hipStream_t s) {
+  const int total = (o + 15) / 16 * kStem7Rounds * 64;
+  CPRUNE_BY_DTYPE(dt, hipLaunchKernelGGL(pack_stem7_kernel<T>, blocks_for(total), dim3(256), 0, s, (const T*)w, (uint4*)y, total, o, c));
   CPRUNE_LAUNCH_CHECK();
   return CPRUNE_OK;
 }
