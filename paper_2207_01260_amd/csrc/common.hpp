@@ -61,7 +61,9 @@ struct TileVariant {
   // channels at 56x56, batch 8, fp32, 128 / 112 / 96 filters on 8 rows 39.4 / 37.7 / 36.6 us, 8 rows shared by two 41.5 / 40.7 / 31.5, 4 rows
   // 43.9 / 42.7 / 33.7; bf16 on 4 rows 21.5 / 21.1 / 16.9.  At stride 2 fp32, batch 32, 4 rows, 128 / 112 / 96 / 80 / 64 filters 80 / 76 / 58 / 59 / 40,
   // batch 8, 2 rows shared by two 28.1 / 27.6 / 21.9 / 21.6 / 15.5; in the boundary's layout, batch 8, 4 rows 56 / 50 / 40 / 40 / 28.
-  int step_m() const { return rows && mb == 1 ? 32 : tile_m(); }
+  // Strips of seven rows come out even at 128 filters there (two wavefronts to each SIMD), and a single block shows: 128 / 112 / 96 / 64 filters
+  // 36.2 / 33.2 / 32.6 / 21.0, shared by two 38.1 / 35.4 / 28.2 / 20.5: a box of one.
+  int step_m() const { return rows && mb == 1 && th != 7 ? 32 : tile_m(); }
   int tile_p() const { return wn * nb * 16; }
 };
 int num_variants();

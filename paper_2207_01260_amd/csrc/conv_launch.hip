@@ -241,11 +241,13 @@ constexpr int kFirstRows = kFirstSplit + kNumSplit;
 constexpr int kFirstPw3 = kFirstRows + kNumRows;
 constexpr int kFirstRowsS2 = kFirstPw3 + kNumPw3;
 constexpr int kFirstRowsNchw = kFirstRowsS2 + kNumRowsS2;
-int num_variants() { return kFirstRowsNchw + kNumRowsNchw; }
+constexpr int kFirstRows7 = kFirstRowsNchw + kNumRowsNchw;
+constexpr int kNumVariants = kFirstRows7 + kNumRows7;
+int num_variants() { return kNumVariants; }
 
 namespace {
 struct VariantTable {
-  TileVariant table[kFirstRowsNchw + kNumRowsNchw];
+  TileVariant table[kNumVariants];
   VariantTable() {
 #define CPRUNE_PATCH_ROW(ID, MB_, TH_, TW_, NI_, KQ_, KS_)                                 \
     {                                                                         \
@@ -335,6 +337,14 @@ struct VariantTable {
     }
     CPRUNE_ROWS_NCHW_LIST(CPRUNE_ROWS_NCHW_ROW)
 #undef CPRUNE_ROWS_NCHW_ROW
+#define CPRUNE_ROWS7_ROW(ID, MB_, R_, KS_)                                                 \
+    {                                                                                      \
+      TileVariant& kv = table[kFirstRows7 + ID];                                           \
+      kv.wm = 1; kv.wn = KS_ >= 4 ? 1 : 4 / KS_; kv.mb = MB_; kv.nb = R_; kv.kq = 1; kv.sched = -1; kv.rows = 1; \
+      kv.th = R_; kv.tw = 16; kv.patch_id = kNumRows + ID; kv.ks = KS_;                    \
+    }
+    CPRUNE_ROWS7_LIST(CPRUNE_ROWS7_ROW)
+#undef CPRUNE_ROWS7_ROW
     for (int t = 0; t < kNumTiles; ++t)
       for (int s = 0; s < kNumScheds; ++s) {
         table[t * kNumScheds + s] = kTiles[t];
@@ -502,7 +512,7 @@ bool variant_supports(const cprune_conv_desc& d, int v, const ConvLayout& lay) {
     }
     if (!(lay.nhwc && (d.dtype == CPRUNE_F32 ? lay.w_rows3 && tv.mb == 1 && (tv.stride == 1 || tv.th <= 4) : lay.w_wave != nullptr) && d.kh == 3 && d.kw == 3 &&
           d.stride == tv.stride && d.pad == 1)) return false;
-    if (lay.pool == 2 || (lay.pool && (((d.h | d.w) & 1) || tv.stride != 1))) return false;
+    if (lay.pool == 2 || (lay.pool && (((d.h | d.w) & 1) || tv.stride != 1 || (tv.th & 1)))) return false;
     if (lay.cp_out & 3) return false;      // four filters per store: not a dense map of logits
     const RowsArgs p = rows_tiles(d, tv, lay);
     const long waves = (long)p.strips * p.tiles_m;

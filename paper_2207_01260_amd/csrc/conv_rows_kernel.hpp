@@ -163,11 +163,11 @@ __device__ __forceinline__ void rows_finish(const RowsArgs& a, const RowsAt& p, 
       }
 #pragma unroll
       for (int y = 0; y < R; y += 2) {
-        if (a.pool) {
-          store(at(y, m), window(clamp4(acc[y][m] + bias), clamp4(acc[y + 1][m] + bias)));
+        if (R % 2 == 0 && a.pool) {
+          store(at(y, m), window(clamp4(acc[y][m] + bias), clamp4(acc[y + (R % 2 == 0)][m] + bias)));
         } else {
 #pragma unroll
-          for (int z = y; z < y + 2; ++z) {
+          for (int z = y; z < y + 2 && z < R; ++z) {
             float4_t v = acc[z][m] + bias;
             if (a.res) v += widen(res[z]);
             store(at(z, m), clamp4(v));
@@ -201,34 +201,35 @@ __device__ __forceinline__ void rows_finish(const RowsArgs& a, const RowsAt& p, 
       for (int q = 0; q < R * MB; ++q) mine[p.slice * SLOT + q * 64] = acc[q / MB][q % MB];
     }
     __syncthreads();
-    for (int q = p.slice; q < R / 2 * MB; q += KS) {
+    for (int q = p.slice; q < (R + 1) / 2 * MB; q += KS) {
       const int y = 2 * (q / MB), m = q % MB;
       const float4_t bias = load_bias4(a.bias, a.O, p.o0 + m * 16 + 4 * p.g4);
       Quad res[2];
-      if (a.res) { res[0] = load_res(at(y, m)); res[1] = load_res(at(y + 1, m)); }
+      const bool two = R % 2 == 0 || y + 1 < R;
+      if (a.res) { res[0] = load_res(at(y, m)); if (two) res[1] = load_res(at(y + 1, m)); }
       float4_t s[2];
 #pragma unroll
       for (int z = 0; z < 2; ++z) {
-        const float4_t* const src = mine + ((y + z) * MB + m) * 64;
+        const float4_t* const src = mine + ((y + (two ? z : 0)) * MB + m) * 64;
         s[z] = src[0];
 #pragma unroll
         for (int w = 1; w < SLOTS; ++w) s[z] += src[w * SLOT];
         s[z] += bias;
-        if (a.res) s[z] += widen(res[z]);
+        if (a.res) s[z] += widen(res[two ? z : 0]);
         s[z] = clamp4(s[z]);
       }
-      if (a.pool) store(at(y, m), window(s[0], s[1]));
-      else { store(at(y, m), s[0]); store(at(y + 1, m), s[1]); }
+      if (R % 2 == 0 && a.pool) store(at(y, m), window(s[0], s[1]));
+      else { store(at(y, m), s[0]); if (two) store(at(y + 1, m), s[1]); }
     }
   }
 }
 
 template <typename T, int MB, int R, int KS, int EDGE>
 __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_rows_kernel(RowsArgs a) {
-  static_assert(sizeof(T) == 2 && R % 2 == 0, "16-bit data, pairs of rows");
+  static_assert(sizeof(T) == 2, "16-bit data");
   constexpr bool HALO = EDGE == kEdgeLoad;
   constexpr int ROWS = R + 2;
-  constexpr int PF = R == 8 ? 5 : MB <= 2 ? 6 : 3;   // rows asked for ahead
+  constexpr int PF = R == 8 ? 5 : R == 7 || MB > 2 ? 3 : 6;   // rows asked for ahead
   static_assert(ROWS % PF == 0, "ring of rows");
   const RowsAt at = rows_at<MB, KS>(a);
   const int lane = at.lane, r = at.r, g4 = at.g4, slice = at.slice, tile_m = at.tile_m, o0 = at.o0, lr = at.lr, img = at.img, cx = at.cx;
@@ -337,8 +338,7 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_rows_kernel(RowsA
 // batch 32): matrix pipes busy 46-61 %, vector ALU 40-50 %, wavefronts waiting for memory 17-23 % and to issue 27-44 %.
 template <int R, int KS, bool IMAGES>
 __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_split_rows_kernel(RowsArgs a) {
-  static_assert(R % 2 == 0, "pairs of rows");
-  constexpr int ROWS = R + 2, PF = 2;
+  constexpr int ROWS = R + 2, PF = R == 7 ? 3 : 2;
   static_assert(ROWS % PF == 0, "ring of rows");
   const RowsAt at = rows_at<1, KS>(a);
   const int lane = at.lane, r = at.r, g4 = at.g4, slice = at.slice, o0 = at.o0, lr = at.lr, img = at.img, cx = at.cx;
@@ -392,7 +392,7 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_split_rows_kernel
     return s;
   };
 
-  // Row i + 1 is cut while row i is multiplied; its place in the ring of raw rows then takes row i + 3.  (What the loop
+  // Row i + 1 is cut while row i is multiplied; its place in the ring of raw rows then takes row i + 1 + PF.  (What the loop
   // finds in flight is asked for here in the order of its last steps, so that the waits at its head count the same loads.)
   load_row(slice, 0, 0);
   __builtin_amdgcn_sched_barrier(0);
@@ -402,8 +402,9 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_split_rows_kernel
   __builtin_amdgcn_sched_barrier(0);
   load_taps(slice, 1);
   __builtin_amdgcn_sched_barrier(0);
+  if constexpr (PF == 3) load_row(slice, 2, 2);
   Cut x = cut(pre[0]);
-  load_row(slice, 2, 0);
+  load_row(slice, PF, 0);
   __builtin_amdgcn_sched_barrier(0);
   load_taps(slice, 2);
   __builtin_amdgcn_sched_barrier(0);
@@ -452,8 +453,8 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_split_rows_kernel
       }
       x = nx;
       __builtin_amdgcn_sched_barrier(0);
-      if (i + 3 < ROWS) load_row(c, i + 3, slot);
-      else load_row(c + KS, i + 3 - ROWS, slot);
+      if (i + 1 + PF < ROWS) load_row(c, i + 1 + PF, slot);
+      else load_row(c + KS, i + 1 + PF - ROWS, slot);
       if (i >= R - 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < 3; ++u)
@@ -516,6 +517,16 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_split_rows_kernel
 
 constexpr int kNumRows = 16;
 
+// Strips of seven rows (no fused pool): the maps of ImageNet networks are 7 x 2^n high.  Eight rows compute an eighth too much on 7 and 14, and
+// on 56 x 56 at batch 32 leave 2.6 wavefronts to a SIMD where seven give exactly three of an eighth less.  The ring of nine input rows is three
+// deep.  Eight rows -> seven, us, the best of each at batch 32: fp32 64->40 at 56x56 31.7 -> 29.5, 85->128 at 28x28 30.4 -> 28.2, 173->256 at
+// 14x14 29.2 -> 26.7, 512->411 at 7x7 34.0 -> 32.8; bf16 14.4 -> 12.9, 11.9 -> 9.8, 9.1 -> 8.4, 10.5 -> 9.6.  They lose on powers of two (fp32
+// 209->197 at 8x8, batch 64: 20.0 -> over 23.8; 56->55 at 16x16 9.4 -> 12.0), so both stay and a handle times both; without timing the choice
+// is among the sixteen above, as before.
+#define CPRUNE_ROWS7_LIST(X) X(0, 1, 7, 1) X(1, 1, 7, 2) X(2, 1, 7, 4) X(3, 2, 7, 1) X(4, 2, 7, 2) X(5, 2, 7, 4)
+
+constexpr int kNumRows7 = 6;
+
 inline RowsEdge rows_edge(const RowsArgs& a) {
   return a.lane_shift < 4 ? kEdgeImage : a.tiles_x > 1 && a.step == 16 ? kEdgeLoad : kEdgeZero;
 }
@@ -531,7 +542,9 @@ inline int launch_rows(int id, dim3 grid, hipStream_t s, const RowsArgs& a) {
     else hipLaunchKernelGGL((conv_rows_kernel<T, MB_, R_, KS_, kEdgeZero>), grid, block, 0, s, a);                   \
     break;                                                                                                           \
   }
-  switch (id) { CPRUNE_ROWS_LIST(CPRUNE_ROWS_CASE) default: return CPRUNE_ERR_UNSUPPORTED; }
+  switch (id) { CPRUNE_ROWS_LIST(CPRUNE_ROWS_CASE) default: break; }
+  if (id < kNumRows) return CPRUNE_OK;
+  switch (id - kNumRows) { CPRUNE_ROWS7_LIST(CPRUNE_ROWS_CASE) default: return CPRUNE_ERR_UNSUPPORTED; }
 #undef CPRUNE_ROWS_CASE
   return CPRUNE_OK;
 }
@@ -548,7 +561,10 @@ inline int launch_rows3(int id, dim3 grid, hipStream_t s, const RowsArgs& a) {
       return CPRUNE_OK;                                                                                              \
     }                                                                                                                \
     break;
-  switch (id) { CPRUNE_ROWS_LIST(CPRUNE_ROWS_CASE) default: break; }
+  if (id < kNumRows)
+    switch (id) { CPRUNE_ROWS_LIST(CPRUNE_ROWS_CASE) default: break; }
+  else
+    switch (id - kNumRows) { CPRUNE_ROWS7_LIST(CPRUNE_ROWS_CASE) default: break; }
 #undef CPRUNE_ROWS_CASE
   return CPRUNE_ERR_UNSUPPORTED;
 }
