@@ -205,7 +205,10 @@ typedef struct {
  * cprune_conv2d_bn_relu, where each call packs the weights into the caller's scratch, in fp32 and 16-bit
  * data, and in fp32 handles, which keep packed copies for the layers that run it.  The fp32 row-strip
  * kernels, the 1x1 kernel and the kernel of a 7x7 / stride 2 first layer (cprune_net_first_layer_form) multiply fp32 data in the
- * same way, within the same limits, in a handle from packed copies of their own.
+ * same way, within the same limits, in a handle from packed copies of their own; so do inverted-residual blocks in one kernel with 3x3
+ * windows and at most 96 filters (cprune_net_block_form), which take the fp32 instruction also where a block's own weights or an input
+ * could lift the last bits of numbers below 2^-110 into results of 2^-50 and more, and for projections of fewer than 16 terms without
+ * an expansion in front.
  * sched -2: likewise channels-last only, for layers whose reduction is one contiguous run
  * per pixel (1x1 stride 1, fully connected): 16 filters x tile_p pixels per work-group, the
  * wavefronts of the group splitting the reduction; chosen when pixels are few.

@@ -871,6 +871,17 @@ static bool block_joins(const cprune_net& net, int i, int* mb, int* xh) {
          E.cp_out == round_up_vec(ed.c_out, net.dtype) && mbrow_form(net.dtype, P.d.c_out, E.cp_in, mb, xh);
 }
 
+// Behind packed weights of three parts: the limit of the block's strips (with the expansion E, or none).
+static int pack_parts_limit(const NetLayer* E, const NetLayer& D, const NetLayer& P, void* copy, size_t bytes, hipStream_t s) {
+  PartsLimits p;
+  p.we = E ? (const float*)E->w : nullptr; p.wd = (const float*)D.w; p.wp = (const float*)P.w;
+  p.be = E ? E->b : nullptr; p.bd = D.b;
+  p.ce = D.d.c_out; p.terms = !E ? 0 : E->nchw_in ? E->d.c_in * 9 : E->cp_in; p.cpe = P.cp_in; p.o = P.d.c_out;
+  p.act_e = E ? E->d.act : CPRUNE_ACT_NONE; p.act_d = D.d.act;
+  p.limit = (unsigned*)((unsigned char*)copy + bytes);
+  return launch_parts_limit(p, s);
+}
+
 static int pack_expansion(cprune_net* net, NetLayer& E, const NetLayer& D, const NetLayer& P, int xh, hipStream_t s) {
   if (E.w_expand) return CPRUNE_OK;
   void* copy = nullptr;
@@ -879,7 +890,10 @@ static int pack_expansion(cprune_net* net, NetLayer& E, const NetLayer& D, const
   CPRUNE_HIP_TRY(hipMalloc(&copy, parts ? parts_packed_bytes(E.d.c_out, expand_rounds(E, xh), twice) + 16 : expand_packed_bytes(E.d.c_out, xh, net->dtype)));
   net->allocs.push_back(copy);
   E.w_expand = copy;
-  if (parts) return launch_pack_parts(E.w, E.d.c_out, terms, expand_rounds(E, xh), twice, E.nchw_in, copy, s);
+  if (parts) {
+    const int rc = launch_pack_parts(E.w, E.d.c_out, terms, expand_rounds(E, xh), twice, E.nchw_in, copy, s);
+    return rc == CPRUNE_OK ? pack_parts_limit(&E, D, P, copy, parts_packed_bytes(E.d.c_out, expand_rounds(E, xh), twice), s) : rc;
+  }
   return launch_pack_expand(E.w, E.d.c_out, terms, xh, net->dtype, copy, s);
 }
 
@@ -1547,6 +1561,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
       const int rounds = (P.cp_in + 15) / 16;
       rc = dev_alloc(parts_packed_bytes(pd.c_out, rounds, false) + 16, &P.w_proj);
       if (rc == CPRUNE_OK) rc = launch_pack_parts(P.w, pd.c_out, P.cp_in, rounds, false, false, P.w_proj, s);
+      if (rc == CPRUNE_OK) rc = pack_parts_limit(nullptr, D, P, P.w_proj, parts_packed_bytes(pd.c_out, rounds, false), s);
       if (rc != CPRUNE_OK) break;
     } else if (P.w_rows) {
       P.w_proj = P.w_rows;

@@ -225,12 +225,21 @@ int launch_pack_expand(const void* w, int ce, int cp, int xh, int dt, void* y, h
 // numbers of a 16-bit type as fp32
 int launch_widen(const void* x, long count, int dt, float* y, hipStream_t s);
 // fp32 weights [rows][terms] -> three bf16 parts in the operand order of mbrow3_kernel, [tile of 16 rows][round of 16 terms][operand], zero
-// padded to `rounds`; image: terms (channel, window row, window column) in rounds of four window rows of four columns.  Behind them a
-// word that is not zero if a weight is 2^60 or more.
+// padded to `rounds`; image: terms (channel, window row, window column) in rounds of four window rows of four columns.  Behind them
+// the word of launch_parts_limit.
 // The expansion's operands for xh 32-byte units of input are three a round, with each part twice where a round's weights are used for few.
 constexpr bool mbrow3_twice(int stride, int xh, bool image) { return stride == 1 && xh <= 4 && !image; }
 size_t parts_packed_bytes(int rows, int rounds, bool twice);
 int launch_pack_parts(const void* w, int rows, int terms, int rounds, bool twice, bool image, void* y, hipStream_t s);
+// The numbers from which on a strip of that kernel runs on the fp32 instruction, written to *limit: with an expansion the upper half of
+// the smallest such input, without one the bits of the smallest such depthwise result.
+struct PartsLimits {
+  const float *we, *wd, *wp;       // [ce][terms] or null, [9][cpe], [o][cpe]
+  const float *be, *bd;            // [ce] or null
+  int ce, terms, cpe, o, act_e, act_d;
+  unsigned* limit;
+};
+int launch_parts_limit(const PartsLimits& p, hipStream_t s);
 
 // The depthwise 5x5 layer and the 1x1 convolution behind it through local memory, an 8 x 8 block of output pixels per work-group.
 struct DwProjArgs {

@@ -4,6 +4,7 @@
 // these are plain coalesced kernels: consecutive lanes take consecutive output
 // columns of one (image, channel) plane.
 #include "conv_split_kernel.hpp"
+#include "parts_limit.hpp"
 
 namespace cprune {
 namespace {
@@ -531,12 +532,40 @@ __global__ __launch_bounds__(256) void widen_kernel(const T* __restrict__ x, flo
   if (i < count) y[i] = (float)x[i];
 }
 
-// Whether a weight is 2^60 or more, or not finite (one work-group).
-__global__ __launch_bounds__(256) void parts_limit_kernel(const float* __restrict__ w, long n, unsigned* __restrict__ flag) {
-  unsigned top = 0;
-  for (long i = threadIdx.x; i < n; i += 256) top = max(top, __float_as_uint(w[i]) & 0x7fffffffu);
-  const int any = __syncthreads_or(top >= (127u + 60u) << 23);
-  if (threadIdx.x == 0) *flag = any ? 1u : 0u;
+// What the strips of mbrow3_kernel may meet before they have to run on the fp32 instruction, from a block's weights (one work-group; the
+// bounds are derived at PartsLimits).
+__global__ __launch_bounds__(256) void parts_limit_kernel(PartsLimits p) {
+  __shared__ unsigned s_top[4][5], s_small[4][2];
+  // largest magnitude as bits (infinities and NaN above all numbers); whether there is one below 2^-110 that is not zero
+  unsigned top[5] = {0, 0, 0, 0, 0}, small[2] = {0, 0};
+  auto scan = [&](const float* w, long n, unsigned& most, unsigned* low) {
+    for (long i = threadIdx.x; w && i < n; i += 256) {
+      const unsigned mag = __float_as_uint(w[i]) & 0x7fffffffu;
+      most = max(most, mag);
+      if (low) *low |= mag - 1 < ((127u - 110u) << 23) - 1 ? 1u : 0u;
+    }
+  };
+  scan(p.we, (long)p.ce * p.terms, top[0], &small[0]);
+  scan(p.wd, (long)9 * p.cpe, top[1], nullptr);
+  scan(p.wp, (long)p.o * p.cpe, top[2], &small[1]);
+  scan(p.be, p.ce, top[3], nullptr);
+  scan(p.bd, p.ce, top[4], nullptr);
+  for (int step = 32; step; step >>= 1) {
+    for (unsigned& v : top) v = max(v, (unsigned)__shfl_xor((int)v, step));
+    for (unsigned& v : small) v |= (unsigned)__shfl_xor((int)v, step);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    for (int i = 0; i < 5; ++i) s_top[threadIdx.x >> 6][i] = top[i];
+    for (int i = 0; i < 2; ++i) s_small[threadIdx.x >> 6][i] = small[i];
+  }
+  __syncthreads();
+  if (threadIdx.x) return;
+  for (int w = 1; w < 4; ++w) {
+    for (int i = 0; i < 5; ++i) top[i] = max(top[i], s_top[w][i]);
+    for (int i = 0; i < 2; ++i) small[i] |= s_small[w][i];
+  }
+  *p.limit = parts_limit(p, __uint_as_float(top[0]), __uint_as_float(top[1]), __uint_as_float(top[2]), __uint_as_float(top[3]),
+                         __uint_as_float(top[4]), small[0], small[1]);
 }
 
 // Weights -> the operand order of the split kernel: [filter tile of 16][round][part][lane = quarter * 16 + filter]
@@ -923,8 +952,11 @@ int launch_pack_parts(const void* w, int rows, int terms, int rounds, bool twice
   hipLaunchKernelGGL(pack_parts_kernel, blocks_for(total), dim3(256), 0, s, (const float*)w, (uint4*)y, total, rows, terms, rounds, twice ? 1 : 0,
                      image ? 1 : 0);
   CPRUNE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(parts_limit_kernel, dim3(1), dim3(256), 0, s, (const float*)w, (long)rows * terms,
-                     (unsigned*)((unsigned char*)y + parts_packed_bytes(rows, rounds, twice)));
+  return CPRUNE_OK;
+}
+
+int launch_parts_limit(const PartsLimits& p, hipStream_t s) {
+  hipLaunchKernelGGL(parts_limit_kernel, dim3(1), dim3(256), 0, s, p);
   CPRUNE_LAUNCH_CHECK();
   return CPRUNE_OK;
 }

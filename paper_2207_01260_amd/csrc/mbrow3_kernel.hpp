@@ -20,17 +20,18 @@
 // 24 at 112x112 stride 2 42.5 / 39.5; 24 -> 65 -> 24 at 56x56 34.6 / 34; image -> 32 -> 16 64 / 58; MobileNetV2 542 -> 494.  Error against 64 bits: 24 -> 65 -> 24 1.5e-7 /
 // 1.1e-7, 64 -> 330 -> 64 2.7e-7 / 1.7e-7.  Left to the compiler's order of the row's operations the same kernel gained nothing (24 -> 65 -> 24 38.6).
 //
-// Numbers three parts do not hold.  An input or expansion weight of 2^60 and more (infinities and NaN among them) sends the strip's
-// wavefronts through mbrow3_slow, the same steps on the fp32 instruction; so does a sum that is not finite at the end, or not
-// zero and below 2^-50.  (Below 2^60 nothing in between can overflow where the fp32 instruction's sums do not, and a large depthwise result shows in
-// the projection's sums.)
+// Numbers three parts do not hold send the strip's wavefronts through mbrow3_slow, the same steps on the fp32 instruction: where an input, or
+// without an expansion a depthwise result, is from the limit up that launch_parts_limit puts behind the packed weights (infinities and
+// NaN always are, whatever the block's weights), and where a sum at the end is not finite, or not zero and below 2^-50.  Within the limit
+// what numbers below 2^-110 lose stays below the last place of every sum from 2^-50 up (parts_limit.hpp); numbers below 2^-133, all denormal,
+// count as zero, and a sum that comes out as zero is not made again.  Projections of fewer than 16 terms without an expansion always go that way:
+// the instruction rounds those less than what parts leave out (3 -> 4 -> 24: 6.5e-8 / 7.3e-8); expansions of few terms are no worse on
+// parts (3 -> 40 -> 24 8.7e-8 / 7.4e-8, 1 -> 40 -> 24 9.0e-8 / 7.5e-8, whole blocks against 64 bits).
 #pragma once
 #include "conv_split_kernel.hpp"
 #include "mbrow_kernel.hpp"
 
 namespace cprune {
-
-constexpr unsigned kPartsLimit = 0x5d80u;      // 2^60 as bf16
 
 typedef unsigned long long ulong2_t __attribute__((ext_vector_type(2)));
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
@@ -201,6 +202,7 @@ __global__ __launch_bounds__(512, 2) void mbrow3_kernel(MbArgs a) {
   const __amdgpu_buffer_rsrc_t dr = make_rsrc(a.wdw, a.wdw_bytes);
 
   unsigned odd = 0;                            // numbers that three parts do not hold: bit 0, or 1 for the second of two images
+  const unsigned limit = EXP ? *(const unsigned*)((const unsigned char*)a.we + a.we_bytes) : *(const unsigned*)((const unsigned char*)a.wp + a.wp_bytes);
   if constexpr (EXP) {
     const int nthr = ks * 64;
     unsigned seen = 0, seen2 = 0;
@@ -281,7 +283,7 @@ __global__ __launch_bounds__(512, 2) void mbrow3_kernel(MbArgs a) {
           }
       }
     }
-    auto beyond = [](unsigned v) -> bool { return ((v & 0xffffu) >= kPartsLimit) | ((v >> 16) >= kPartsLimit); };
+    auto beyond = [&](unsigned v) -> bool { return ((v & 0xffffu) >= limit) | ((v >> 16) >= limit); };
     odd = (__any(beyond(seen)) ? 1u : 0u) | (__any(beyond(seen2)) ? 2u : 0u);
     if (lane == 0) *(unsigned*)(lds + FLAGS + wave * 4) = odd;
   }
@@ -396,14 +398,15 @@ __global__ __launch_bounds__(512, 2) void mbrow3_kernel(MbArgs a) {
   constexpr int SX = EXP ? S * XR : 1, RING = SX <= 4 ? SX : SX % 4 ? 3 : 4;
   static_assert(SX % RING == 0, "whole turns a row");
   PartsB<TE> xb[RING];
+  uint32_t top_d = 0;                          // XH = 0: the largest depthwise result (of negative ones any counts as larger)
   load_expand(wave);
   bd = load_bias4(a.bdw, a.Ce, wave * 16 + g4 * 4);
 #pragma unroll
   for (int u = 0; u < K; ++u) load_taps(wave, u);
   load_project(wave);
   if constexpr (EXP) {
-    odd = *(const unsigned*)((const unsigned char*)a.we + a.we_bytes) ? 3u : 0u;       // (an expansion weight, by launch_pack_parts)
     __syncthreads();
+    odd = 0;
     for (int w = 0; w < ks; ++w) odd |= *(const unsigned*)(lds + FLAGS + w * 4);
     odd = __builtin_amdgcn_readfirstlane(odd);
 #pragma unroll
@@ -459,8 +462,10 @@ __global__ __launch_bounds__(512, 2) void mbrow3_kernel(MbArgs a) {
           } else if constexpr (completes) {
             constexpr int p = n - 4 * K;
             uint32_t h, m, l;
-            split3(__float_as_uint(__builtin_amdgcn_fmed3f(dacc[y_done][2 * p], lo_d, hi_d)),
-                   __float_as_uint(__builtin_amdgcn_fmed3f(dacc[y_done][2 * p + 1], lo_d, hi_d)), h, m, l);
+            const uint32_t d0 = __float_as_uint(__builtin_amdgcn_fmed3f(dacc[y_done][2 * p], lo_d, hi_d));
+            const uint32_t d1 = __float_as_uint(__builtin_amdgcn_fmed3f(dacc[y_done][2 * p + 1], lo_d, hi_d));
+            split3(d0, d1, h, m, l);
+            if constexpr (!EXP) top_d = max(max(top_d, d0), d1);
             if constexpr (p == 0) { nf.lh.x = l; nf.lh.z = h; nf.m.x = m; }
             else { nf.lh.y = l; nf.lh.w = h; nf.m.y = m; }
           }
@@ -534,7 +539,7 @@ __global__ __launch_bounds__(512, 2) void mbrow3_kernel(MbArgs a) {
         top = max(top, mag);
         low = min(low, mag - 1);      // (zero goes to the other end)
       }
-  const bool bad = top >= kInf || low < kSmall - 1, second = two && r >= 8;
+  const bool bad = top >= kInf || low < kSmall - 1 || (!EXP && top_d >= limit), second = two && r >= 8;
   odd |= (__any(bad && !second) ? 1u : 0u) | (__any(bad && second) ? 2u : 0u);
   if (odd) mbrow3_slow<S, MB, R, EXP, IMG>(a, at, odd >> (second ? 1 : 0) & 1u, acc);
 
