@@ -145,7 +145,15 @@ __global__ __launch_bounds__(128, MB == 1 ? 5 : 4) void conv_stem7_kernel(StemAr
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       const int o = o0 + i * 16 + 4 * g4;
-      if (lane_ok & (x < w) & (o < a.Cop)) *(uint2*)((T*)map + ((size_t)(n * h + y) * w + x) * a.Cop + o) = narrow4<T>(v[i]);
+      if (!(lane_ok & (x < w) & (o < a.Cop))) continue;
+      T* const dst = (T*)map + ((size_t)(n * h + y) * w + x) * a.Cop + o;
+      if (POOL == 0 && (a.Cop & 3)) {            // a dense last layer: no room behind its filters, no 8-byte alignment
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (o + q < a.Cop) dst[q] = Elem<T>::from_f32(v[i][q]);
+      } else {
+        *(uint2*)dst = narrow4<T>(v[i]);
+      }
     }
   };
 
