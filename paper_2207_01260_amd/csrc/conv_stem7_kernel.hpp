@@ -106,10 +106,13 @@ __global__ __launch_bounds__(128, MB == 1 ? 5 : 4) void conv_stem7_kernel(StemAr
   int unit_row[NR], unit_lds[NR];
 #pragma unroll
   for (int j = 0; j < NR; ++j) {
-    const int q = min(4 * j + g4, 20), c = q / 7;             // (units past the last meet zero weights)
+    const int q = min(4 * j + g4, 20), c = q / 7;
     unit_row[j] = q - c * 7;
     unit_lds[j] = c * (16 * PITCH) + r;
   }
+  // Units past the last, of the last round, are zeros: behind their zero weights a finite number would do, an infinity not.  (As a row of zeros
+  // in LDS they cost 2-3 % of a 3.6 us launch, as these selects 1.)
+  const bool real = 4 * (NR - 1) + g4 <= 20;
 
   // conv row cy: sums of the lane's pixel
   auto multiply = [&](int cy, float4_t (&out)[MB]) CPRUNE_INLINE {
@@ -118,6 +121,8 @@ __global__ __launch_bounds__(128, MB == 1 ? 5 : 4) void conv_stem7_kernel(StemAr
     uint4 x[NR];
 #pragma unroll
     for (int j = 0; j < NR; ++j) __builtin_memcpy(&x[j], sP + unit_lds[j] + ((2 * cy + 5 + unit_row[j]) & 15) * PITCH, 16);    // (2 cy - 3 + row) + 8
+    uint4& q = x[NR - 1];
+    q.x = real ? q.x : 0u; q.y = real ? q.y : 0u; q.z = real ? q.z : 0u; q.w = real ? q.w : 0u;
 #pragma unroll
     for (int j = 0; j < NR; ++j)
 #pragma unroll
