@@ -477,6 +477,7 @@ struct NetLayer {
   void* w_split = nullptr;    // fp32 dense layer: weights once more, cut and packed for the split kernel
   void* w_rows3 = nullptr;    // fp32 3x3 / pad 1 layer, or 1x1 layer of any type: likewise, for the row-strip (the 1x1) kernel
   bool stem = false;          // nchw_in layer that runs the first-layer kernel (whole reduction in LDS)
+  void* w_stem7b = nullptr;   // ... 16-bit data, up to 48 filters or a dense last map: packed for its kernel in 16 x 16 blocks
   void* w_stem7 = nullptr;    // 7x7 / stride 2 / pad 3 first layer: weights packed for the kernel made for it
   int stem7 = 0;              // 1: that kernel runs the layer; 2: and the 3x3 / stride 2 max-pool pool3 with it; 3 (fp32): the same,
                               // and the conv map is stored too
@@ -598,8 +599,10 @@ static void drop_copies(cprune_net* net, NetLayer& L, int v) {
 }
 
 // The opening of the ImageNet networks, which has kernels of its own.
-static bool stem7_layer(const NetLayer& L) {
-  return L.nchw_in && L.d.c_in <= 3 && L.d.k == 7 && L.d.stride == 2 && L.d.pad == 3 && L.d.residual < 0;
+// (fp32: not as a last layer whose map lies dense in the caller's buffer, which its kernel stores four filters at a time)
+static bool stem7_layer(const NetLayer& L, int dtype) {
+  return L.nchw_in && L.d.c_in <= 3 && L.d.k == 7 && L.d.stride == 2 && L.d.pad == 3 && L.d.residual < 0 &&
+         !(dtype == CPRUNE_F32 && (L.cp_out & 3));
 }
 
 constexpr size_t kMaxGraphs = 8;
@@ -647,6 +650,49 @@ static int net_run_stem(cprune_net* net, int i, int n, const void* x, void* dst,
   return CPRUNE_OK;
 }
 
+constexpr int kStem7BlockFilters = 48;
+static int stem7_block_tile(int c_out) { return c_out <= 32 ? 32 : 64; }
+
+// Whether the 16-bit 7x7 / stride 2 first layer runs in 16 x 16 blocks of conv outputs rather than in strips.  Blocks take rounds of the work-groups that
+// fit the chip (three per CU, two above 32 filters), whatever a round holds; strips take what their steps take.  Both times (us) as fitted to 20
+// sizes each from 64x64 to 448x448, batch 2 to 256, in bf16; choosing so is at most 6 % over the better one there (16 filters without the pool, 24 and 32 images, where blocks would be the better), in most 0.  Blocks / strips, with the
+// pool, 32 filters at 224x224: batch 3 5.8 / 5.6, 4 5.8 / 6.1, 8 6.9 / 8.1, 12 8.0 / 10.0, 16 13.1 / 11.9, 24 13.2 / 15.9, 64 34.7 / 31.0; 16 filters, batch 8 6.5 /
+// 6.6, 12 7.4 / 7.9, 16 11.6 / 9.4; 48, batch 8 9.6 / 10.0, 12 15.8 / 12.6; without it, 16 filters, batch 12 6.1 / 7.4, 32 12.4 / 13.1; 32, batch 12 8.1 / 9.3,
+// 32 19.6 / 17.3; 48, batch 8 8.6 / 9.3, 12 13.9 / 12.0.  64 filters, batch 8: 10.3 / 10.3 with the pool, 11.3 / 10.6 without.
+static bool stem7_blocks(const StemArgs& a, bool pool) {
+  if (a.Cop & 3) return true;                  // a last layer's dense map: strips store four filters at a time
+  if (a.O > kStem7BlockFilters) return false;
+  struct Times { double one, more, first, round, strips, step; };      // one group per CU, each further one; several rounds; strips: fixed, per 1000 steps
+  constexpr double kNever = 1e9;
+  static const Times times[2][3] = {
+    {{4.92, 0.5, 0.0, kNever, 3.21, 0.95}, {5.85, 0.95, 0.0, kNever, 3.05, 1.32}, {7.1, 1.3, 0.0, kNever, 3.5, 1.75}},
+    {{5.5, 0.9, 2.63, 4.42, 4.0, 0.69}, {5.75, 1.05, 2.07, 5.32, 4.12, 1.04}, {7.6, 1.9, 0.0, kNever, 4.9, 1.42}}};
+  const Times& t = times[pool][(a.O - 1) / 16];
+  const long h = pool ? a.Hp : a.Ho, w = pool ? a.Wp : a.Wo, side = pool ? 7 : 16;
+  const long blocks = a.N * ((h + side - 1) / side) * ((w + side - 1) / side), steps = a.N * ((w + side - 1) / side) * (pool ? h : (h + 1) / 2);
+  const long resident = 256 * (a.O <= 32 ? 3 : 2);
+  const double in_blocks = blocks <= resident ? t.one + t.more * ((blocks + 255) / 256 - 1) : t.first + t.round * ((blocks + resident - 1) / resident);
+  return in_blocks < t.strips + t.step * 1e-3 * steps;
+}
+
+static int net_run_stem7_blocks(const NetLayer& L, int dtype, int pool, StemArgs a, hipStream_t s) {
+  const int tile = stem7_block_tile(a.O), side = pool ? 7 : 16;
+  a.w = L.w_stem7b;
+  a.tiles_m = (a.O + tile - 1) / tile;
+  a.tiles_y = ((pool ? a.Hp : a.Ho) + side - 1) / side;
+  a.tiles_x = ((pool ? a.Wp : a.Wo) + side - 1) / side;
+  a.vec_out = (a.Cop % 4) == 0 ? 1 : 0;
+  a.magic_x = strip_magic(a.tiles_x); a.magic_y = strip_magic(a.tiles_y);
+  const long blocks = (long)a.N * a.tiles_y * a.tiles_x;
+  // as many workers as stay resident: weight tile + patch (+ the conv block the pool reads)
+  const long lds = tile * (kStem7K * 2L + 16) + 37L * 320 + (pool ? 256L * (tile * 2 + 16) : 16L), resident = 256 * (160 * 1024 / lds);
+  const dim3 grid((unsigned)(blocks < resident ? blocks : resident), (unsigned)a.tiles_m);
+  const int rc = dtype == CPRUNE_F16 ? launch_conv_stem7_block_f16(tile / 16, pool, grid, s, a) : launch_conv_stem7_block_bf16(tile / 16, pool, grid, s, a);
+  if (rc != CPRUNE_OK) return rc;
+  CPRUNE_LAUNCH_CHECK();
+  return CPRUNE_OK;
+}
+
 // The 7x7 / stride 2 first-layer kernel on the caller's NCHW input, with or without the max-pool behind it.  A work-group walks over a band
 // of rows and repeats the row above it for the pool; the bands are those for which the rounds of work-groups that fit the chip (two wavefronts each;
 // two, in 16-bit data four, on a SIMD) take the fewest steps, a work-group's start and its repeated row counted as one step and a fifth.  64 filters at
@@ -665,6 +711,7 @@ static int net_run_stem7(cprune_net* net, int i, int n, const void* x, void* dst
     a.y = P.act; a.Hp = P.h_out; a.Wp = P.w_out; a.Cop = P.cp_out;
     if (pool == 2) a.y_map = dst;
   }
+  if (!f32 && stem7_blocks(a, pool)) return net_run_stem7_blocks(L, net->dtype, pool, a, s);
   const int mb = a.O <= 32 ? 1 : 2;
   a.tiles_m = (a.O + 32 * mb - 1) / (32 * mb);
   a.tiles_x = pool ? (a.Wp + 6) / 7 : (a.Wo + 15) / 16;
@@ -1441,7 +1488,7 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
       if (rc != CPRUNE_OK) break;
     }
     bool use = true;
-    if (tune && !(dtype == CPRUNE_F32 && stem7_layer(L))) {
+    if (tune && !(dtype == CPRUNE_F32 && stem7_layer(L, dtype))) {
       float ms[2] = {0.f, 0.f};
       for (int form = 0; form < 2 && rc == CPRUNE_OK; ++form) {   // 0: general kernel, 1: first-layer kernel
         L.stem = form == 1;
@@ -1465,9 +1512,14 @@ extern "C" int cprune_net_create(const cprune_layer_desc* layers, int n_layers, 
   for (int i = 0; i < n_layers && rc == CPRUNE_OK; ++i) {
     NetLayer& L = net->layers[i];
     const cprune_layer_desc& d = L.d;
-    if (!stem7_layer(L)) continue;
+    if (!stem7_layer(L, dtype)) continue;
     rc = dev_alloc(stem7_packed_bytes(d.c_out, dtype), &L.w_stem7);
     if (rc == CPRUNE_OK) rc = launch_pack_stem7(L.w, d.c_out, d.c_in, dtype, L.w_stem7, s);
+    if (rc == CPRUNE_OK && dtype != CPRUNE_F32 && (d.c_out <= kStem7BlockFilters || (L.cp_out & 3))) {
+      const int rows = (d.c_out + stem7_block_tile(d.c_out) - 1) / stem7_block_tile(d.c_out) * stem7_block_tile(d.c_out);
+      rc = dev_alloc((size_t)rows * kStem7K * es, &L.w_stem7b);
+      if (rc == CPRUNE_OK) rc = launch_repack_stem7(L.w, d.c_out, d.c_in, rows, dtype, L.w_stem7b, s);
+    }
     if (rc != CPRUNE_OK) break;
     int reader = -1, readers = 0;
     for (int j = 0; j < n_layers; ++j) {

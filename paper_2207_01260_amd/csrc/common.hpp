@@ -309,5 +309,13 @@ int launch_pack_stem7(const void* w, int o, int c, int dt, void* y, hipStream_t 
 int launch_conv_stem7_f16(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a);
 int launch_conv_stem7_bf16(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a);
 int launch_conv_stem7_f32(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a);
+// The same layer in 16-bit data, 16 x 16 conv outputs a work-group, reduction ordered (window row, 8 window columns, 4 channels):
+// weights [rows][224] from launch_repack_stem7 (k = u * 32 + (v + 1) * 4 + c; zero for column slot 0, channel slot 3, channels beyond c and
+// rows beyond o).  mb in {2, 4}; pool = 1 runs the max-pool too; tiles_y, tiles_x count blocks of the map, or 7 x 7 blocks of the pooled one;
+// grid.x = workers sharing the (image, block) list, grid.y = filter tiles.
+constexpr int kStem7K = 224;
+int launch_repack_stem7(const void* w, int o, int c, int rows, int dt, void* y, hipStream_t s);
+int launch_conv_stem7_block_f16(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a);
+int launch_conv_stem7_block_bf16(int mb, int pool, dim3 grid, hipStream_t s, const StemArgs& a);
 
 }  // namespace cprune

@@ -6,12 +6,13 @@
 // step, the next four image rows on their way meanwhile, rows pooled across lanes and steps in registers before they are rounded (the
 // maximum of rounded numbers is the rounded maximum).
 //
-// The kernel it replaced gave a work-group a 16 x 16 block of conv outputs, four channels a pixel (224 terms), and handed the block to the
-// pool through LDS.  What bounds this one: the vector work around the MFMAs (per row and filter block 4 sums' bias, clamp and maxima).
-// Measured with the pool, 16 x 16 blocks / this kernel (us): 64 filters at 224x224, batch 32 29.6 / 23.6, 8 10.0 / 9.7, 3 8.0 / 6.6, 1 7.9 / 4.5; 64 at
-// 64x64, batch 16 7.9 / 4.9; 96 at 160x160, batch 8 14.2 / 9.4; 10 at 96x96, batch 33 7.0 / 6.3.  17 to 32 filters, 16 for each wavefront, leave the rows'
-// addresses and reads to half the products: 24 at 301x301, batch 5 8.6 / 8.8, 32 at 224x224, batch 8 6.9 / 7.9 (two strips side by side with
-// all filters in each wavefront: 9.8).
+// What bounds it: the vector work around the MFMAs (per row and filter block 4 sums' bias, clamp and maxima).
+// Measured with the pool, 16 x 16 blocks of outputs (conv_stem7_block_kernel.hpp) / this kernel (us): 64 filters at 224x224, batch 32 30.4 / 24.9, 8 10.3 /
+// 10.3, 1 7.9 / 4.5; 64 at 64x64, batch 16 7.9 / 4.8; 10 at 96x96, batch 33 7.1 / 6.5.  Few filters leave the rows' addresses and reads to few
+// products, 17 to 32 of them 16 to a wavefront: 32 at 224x224, batch 8 6.9 / 8.1, batch 12 8.0 / 10.0 (two strips side by side with all
+// filters in each wavefront at batch 8: 9.8; one wavefront a work-group with all of them 9.0).  There the blocks run (stem7_blocks in api.hip).
+//
+// The output's pixels hold a multiple of four filters (Cop).
 #pragma once
 #include "conv_split_kernel.hpp"
 #include "strip_index.hpp"
@@ -150,15 +151,7 @@ __global__ __launch_bounds__(128, MB == 1 ? 5 : 4) void conv_stem7_kernel(StemAr
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       const int o = o0 + i * 16 + 4 * g4;
-      if (!(lane_ok & (x < w) & (o < a.Cop))) continue;
-      T* const dst = (T*)map + ((size_t)(n * h + y) * w + x) * a.Cop + o;
-      if (POOL == 0 && (a.Cop & 3)) {            // a dense last layer: no room behind its filters, no 8-byte alignment
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (o + q < a.Cop) dst[q] = Elem<T>::from_f32(v[i][q]);
-      } else {
-        *(uint2*)dst = narrow4<T>(v[i]);
-      }
+      if (lane_ok & (x < w) & (o < a.Cop)) *(uint2*)((T*)map + ((size_t)(n * h + y) * w + x) * a.Cop + o) = narrow4<T>(v[i]);
     }
   };
 

@@ -211,15 +211,7 @@ __global__ __launch_bounds__(128, 2) void conv_stem7_split_kernel(StemArgs a) {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       const int o = o0 + i * 16 + 4 * g4;
-      if (!(lane_ok & (x < w) & (o < a.Cop))) continue;
-      float* const dst = (float*)map + ((size_t)(n * h + y) * w + x) * a.Cop + o;
-      if (POOL == 0 && (a.Cop & 3)) {            // a dense last layer: no room behind its filters, no 16-byte alignment
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (o + q < a.Cop) dst[q] = v[i][q];
-      } else {
-        *(float4_t*)dst = v[i];
-      }
+      if (lane_ok & (x < w) & (o < a.Cop)) *(float4_t*)((float*)map + ((size_t)(n * h + y) * w + x) * a.Cop + o) = v[i];
     }
   };
 
