@@ -208,8 +208,9 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
 
   constexpr bool AHEAD = !(EXP && K == 5 && ES == 2);   // window weights asked for one block ahead (there they do not fit)
   // 3x3 windows in 16-bit data: their weights come as fp32 (widened here they were a tenth of the vector operations and, until then, 18
-  // registers more), and the expansion's operands are read from LDS a row ahead; 5x5 windows have no room for either
-  constexpr bool W32 = ES == 4 || K == 3, READ_AHEAD = EXP && K == 3;
+  // registers more), and the expansion's operands are read from LDS a row ahead; 5x5 windows have no room for either.  fp32 (128 filters, 96
+  // channels in) has room for the latter in low strips at stride 1: without / with, 56x56, batch 8, low 66.5 / 65.0 us, tall 86.0 / 87.8, stride 2 36.6 / 38.0
+  constexpr bool W32 = ES == 4 || K == 3, READ_AHEAD = EXP && K == 3 && (ES == 2 || (S == 1 && R == 2));
 
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const MbAt at = mbrow_at<K, S, MB, R>(a);
