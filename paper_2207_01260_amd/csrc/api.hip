@@ -798,7 +798,7 @@ static int net_run_mbrow(cprune_net* net, int i, int n, const void* x, void* dst
   a.x = image ? x : net->layers[E ? E->d.input : D.d.input].act;
   a.Hi = image ? E->h_in : 0; a.Wi = image ? E->w_in : 0;
   a.we = E ? E->w_expand : nullptr; a.be = E ? E->b : nullptr;
-  a.wdw = D.w_dw32 ? D.w_dw32 : D.w; a.bdw = D.b; a.wp = P.w_proj; a.bp = P.b;
+  a.wdw = D.w; a.wdw32 = D.w_dw32; a.bdw = D.b; a.wp = P.w_proj; a.bp = P.b;
   a.res = P.d.residual >= 0 ? net->layers[P.d.residual].act : nullptr;
   a.y = dst;
   a.N = n; a.H = D.h_in; a.W = D.w_in; a.Ho = D.h_out; a.Wo = D.w_out;
@@ -813,7 +813,7 @@ static int net_run_mbrow(cprune_net* net, int i, int n, const void* x, void* dst
   a.we_raw = E ? E->w : nullptr; a.wp_raw = P.w;
   a.we_bytes = !E ? 0u : (unsigned)(parts ? parts_packed_bytes(a.Ce, expand_rounds(*E, xh), mbrow3_twice(D.d.stride, xh, image)) : expand_packed_bytes(a.Ce, xh, net->dtype));
   a.wp_bytes = (unsigned)(parts ? parts_packed_bytes(a.O, a.nchunk, false) : rows_packed_bytes(a.O, a.Cpe, net->dtype));
-  a.wdw_bytes = (unsigned)((size_t)D.d.k * D.d.k * a.Cpe * (D.w_dw32 ? 4 : es));
+  a.wdw_bytes = (unsigned)((size_t)D.d.k * D.d.k * a.Cpe * es);
   a.y_bytes = (unsigned)((size_t)n * a.Ho * a.Wo * a.Cop * es);
   a.slots = 0;
   const int tiles_m = (a.O + mb * 16 - 1) / (mb * 16);

@@ -164,7 +164,8 @@ struct MbArgs {
   const void* x;        // xh > 0: [n][h][w][cpi] block input; xh = 0: [n][h][w][cpe] expanded activations
   const void* we;       // expansion weights from launch_pack_expand, or null
   const float* be;      // [ce] or null
-  const void* wdw;      // [k][k][cpe] depthwise weights (folded); 3x3: as fp32 in every type
+  const void* wdw;      // [k][k][cpe] depthwise weights (folded)
+  const float* wdw32;   // 16-bit data, 3x3: the same as fp32, for the forms that read them so
   const float* bdw;     // [ce] or null
   const void* wp;       // [o][cpe] projection weights from launch_repack_rows
   const float* bp;      // [o] or null

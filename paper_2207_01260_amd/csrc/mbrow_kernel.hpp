@@ -26,8 +26,9 @@
 //
 // Measured (expansion + depthwise + projection, us): the layers apart or with the depthwise layer fused through LDS, the
 // faster of both / this kernel.  MnasNet bf16 at batch 16: 16 -> 38 -> 24, 112x112: 20 / 10; 24 -> 58 -> 24 at 56x56: 15 / 8.3; image 3 -> 32 -> 16
-// 20.3 / 16 (the windows' gather from LDS).  Window weights as fp32 and operands a row ahead, 3x3, before / with: 24 -> 58 -> 24 8.9 / 8.3, 32 -> 92 -> 32 at
-// 28x28 batch 64 11.0 / 10.1, 64 -> 330 -> 64 at 14x14 13.1 / 12.5; with 5x5 windows they spill (40 -> 88 -> 40 at 28x28 12.5 / 13.3).  In fp32 the matrix instruction bounds it, which takes turns with the vector ALU (mbrow3_kernel.hpp).
+// 20.3 / 16 (the windows' gather from LDS).  Without window weights as fp32 and operands
+// a row ahead / with them (mbrow_wide, mbrow_read_ahead): 32 -> 92 -> 32 at 28x28 batch 64 11.0 / 10.1, 64 -> 330 -> 64 at 14x14 13.1 / 12.5.
+//  In fp32 the matrix instruction bounds it, which takes turns with the vector ALU (mbrow3_kernel.hpp).
 #pragma once
 #include <atomic>
 #include "conv_nhwc_kernel.hpp"
@@ -192,6 +193,31 @@ __device__ __forceinline__ void mbrow_finish(const MbArgs& a, const MbAt& at, un
   }
 }
 
+// What a strip with a 3x3 window has registers for beside its sums, 4 R MB of them.  Wide (16-bit data): the window's weights come as fp32 (widened
+// where they are used they are a tenth of the vector operations; waiting for that they are 18 registers fewer); without an expansion the input
+// rows of a chunk lie in registers too.  Reading ahead: the expansion's operands of a row are read from LDS while the row before it
+// is multiplied, 4 a round.  Neither / ahead / wide / both, us, expanded to 86-400 channels, 56x56, batch 8: bf16 24 -> 32 9.7 / 9.4 / 9.3 / 9.2, stride 2 8.7 / 8.3 /
+// 8.6 / 8.1, 64 -> 96 low 18.7 / 17.9 / 17.7 / 16.8; 64 -> 64 tall 16.0 / 17.6 / 16.1 / 16.7; 160 -> 128 tall 37.7 / 43 / 41 / 48, stride 2 17.5 / 18.5 / 17.9 / 19.7; fp16
+// 64 -> 64 tall 14.5 / 14.2 / 16.4 / 16.9, 96 -> 96 tall 31 / 33 / 40 / 40, low 24.0 / 22.9 / 23.2 / 24.2.  Depthwise and projection alone, narrow / wide: bf16 64 filters
+// tall 9.3 / 11.1, low 8.0 / 7.8, stride 2 tall 7.1 / 7.8, 128 9.8 / 9.5; fp16 64 tall 9.1 / 12.0, low 7.9 / 7.9, stride 2 tall 7.7 / 11.0, 128 stride 2 6.4 / 7.7.  fp32
+// 96 -> 128 (of 128 filters only), not ahead / ahead: low 66.5 / 65.0, tall 86 / 88, stride 2 36.6 / 38.0.  5x5 windows have no room for either (40 -> 88 -> 40 at 28x28 12.5 / 13.3
+// with both).
+template <typename T>
+constexpr bool mbrow_wide(int k, int s, int mb, int xh, int r) {
+  if (sizeof(T) != 2 || k != 3) return false;
+  const int sums = 4 * r * mb, rows = (r - 1) * s + k;
+  if (std::is_same<T, __bf16>::value) return xh ? mb < 8 : sums + 4 * rows * s <= 120;
+  return xh && mb <= 4 && sums <= 64;          // (fp16 forms spill where those of bf16 do not)
+}
+template <typename T>
+constexpr bool mbrow_read_ahead(int k, int s, int mb, int xh, int r) {
+  if (k != 3 || xh == 0) return false;
+  const bool low = 4 * r * mb <= 72;
+  if (sizeof(T) == 4) return low && s == 1;
+  if (std::is_same<T, __bf16>::value) return (xh <= 2 || low) && !(mb == 8 && s == 2);
+  return mb <= 4 || low;
+}
+
 template <typename T, int K, int S, int MB, int XH, int R, bool IMG>
 __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   constexpr int ES = (int)sizeof(T);
@@ -207,10 +233,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   constexpr int IROWS = 2 * ROWS + 1, IPITCH = mbrow_image_pitch(ES);   // IMG: rows and row pitch of the staged image
 
   constexpr bool AHEAD = !(EXP && K == 5 && ES == 2);   // window weights asked for one block ahead (there they do not fit)
-  // 3x3 windows in 16-bit data: their weights come as fp32 (widened here they were a tenth of the vector operations and, until then, 18
-  // registers more), and the expansion's operands are read from LDS a row ahead; 5x5 windows have no room for either.  fp32 (128 filters, 96
-  // channels in) has room for the latter in low strips at stride 1: without / with, 56x56, batch 8, low 66.5 / 65.0 us, tall 86.0 / 87.8, stride 2 36.6 / 38.0
-  constexpr bool W32 = ES == 4 || K == 3, READ_AHEAD = EXP && K == 3 && (ES == 2 || (S == 1 && R == 2));
+  constexpr bool W32 = ES == 4 || mbrow_wide<T>(K, S, MB, XH, R), READ_AHEAD = mbrow_read_ahead<T>(K, S, MB, XH, R);
 
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const MbAt at = mbrow_at<K, S, MB, R>(a);
@@ -221,7 +244,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, a.x_bytes);
   const __amdgpu_buffer_rsrc_t er = make_rsrc(a.we, a.we_bytes);
   const __amdgpu_buffer_rsrc_t pr = make_rsrc(a.wp, a.wp_bytes);
-  const __amdgpu_buffer_rsrc_t dr = make_rsrc(a.wdw, a.wdw_bytes);
+  const __amdgpu_buffer_rsrc_t dr = W32 && ES == 2 ? make_rsrc(a.wdw32, 2 * a.wdw_bytes) : make_rsrc(a.wdw, a.wdw_bytes);
 
   if constexpr (EXP) {
     // the strip's block input: zeros outside the image and past the last channel

@@ -61,3 +61,14 @@ def test_fp32_strips_of_128_filters(spills):
     forms = {f: n for f, n in spills.items() if f[0] == "f" and f[1] == 3}
     assert len(forms) == 6
     assert all(n <= 4 for n in forms.values()), forms
+
+
+@pytest.mark.parametrize("dtype,most_forms,most", [("DF16b", 8, 60), ("DF16_", 6, 30)])
+def test_strips_of_16_bit_data(spills, dtype, most_forms, most):
+    """3x3 windows: their weights are held as fp32, and operands read a row ahead, by the forms that have the registers."""
+    forms = {f: n for f, n in spills.items() if f[0] == dtype and f[1] == 3}
+    assert len(forms) == 43
+    spilled = {f: n for f, n in forms.items() if n}
+    assert len(spilled) <= most_forms and max(spilled.values()) <= most, spilled
+    # two sums' blocks and fewer, and the lower of the heights: nothing
+    assert not any(f[3] <= 2 for f in spilled), spilled
