@@ -236,10 +236,36 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   constexpr bool W32 = ES == 4 || mbrow_wide<T>(K, S, MB, XH, R), READ_AHEAD = mbrow_read_ahead<T>(K, S, MB, XH, R);
 
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const MbAt at = mbrow_at<K, S, MB, R>(a);
-  const int t = threadIdx.x, lane = at.lane, ks = at.ks, wave = at.wave, r = at.r, g4 = at.g4, o0 = at.o0;
-  const bool two = at.two;
-  const int n0 = at.n0, j0 = at.j0, img = at.img, cj = at.cj, iy0 = at.iy0;
+  constexpr int HL = mbrow_halo_left(K, S), HR = mbrow_halo_right(K, S);
+  // (mbrow_at's lines: through its result 5x5 forms spilled up to twice as much, bf16 24 -> 64 at 28x28, batch 32 15.5 / 16.5 us, and all were 2 % slower)
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  const int ks = (int)blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int r = lane & 15, g4 = lane >> 4;
+
+  int tile;
+  {
+    const int G = gridDim.x;
+    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+    const int q = G >> 3, rem = G & 7;
+    tile = xcd * q + (xcd < rem ? xcd : rem) + local;
+  }
+  const int o0 = blockIdx.y * (MB * 16);
+  const StripAt strip = strip_at(tile, a.tiles_x, a.tiles_y, a.magic_x, a.magic_y);
+  const int tx = strip.tx, ty = strip.ty, grp = strip.group;
+  const bool two = a.ipt == 2;
+  const int n0 = two ? 2 * grp : grp;
+  const int j0 = tx * (16 - HL - HR);
+  const int lr = two ? (r & 7) : r;
+  const int img = two ? n0 + (r >> 3) : n0;
+  const int cj = j0 + lr;                      // the lane's output column
+  const int iy0 = ty * R * S - PAD;
+  const bool lane_out = (img < a.N) & (cj < a.Wo) & ((tx == 0) | (lr >= HL)) & ((tx == a.tiles_x - 1) | (lr < 16 - HR));
+  MbAt at;                                     // for mbrow_finish
+  at.lane = lane; at.r = r; at.g4 = g4; at.wave = wave; at.ks = ks; at.o0 = o0;
+  at.tx = tx; at.ty = ty; at.n0 = n0; at.img = img; at.j0 = j0; at.lr = lr; at.cj = cj; at.iy0 = iy0;
+  at.two = two; at.lane_out = lane_out;
 
   const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, a.x_bytes);
   const __amdgpu_buffer_rsrc_t er = make_rsrc(a.we, a.we_bytes);

@@ -72,3 +72,9 @@ def test_strips_of_16_bit_data(spills, dtype, most_forms, most):
     assert len(spilled) <= most_forms and max(spilled.values()) <= most, spilled
     # two sums' blocks and fewer, and the lower of the heights: nothing
     assert not any(f[3] <= 2 for f in spilled), spilled
+
+
+@pytest.mark.parametrize("form,most", [(("DF16b", 5, 1, 4, 2, 2), 8), (("DF16b", 5, 1, 4, 4, 2), 14), (("DF16_", 5, 1, 6, 6, 2), 8)])
+def test_5x5_strips(spills, form, most):
+    """Forms that spilled up to twice as much with the strip's place handed over in a struct."""
+    assert spills[form] <= most
