@@ -202,20 +202,24 @@ __device__ __forceinline__ void mbrow_finish(const MbArgs& a, const MbAt& at, un
 // tall 9.3 / 11.1, low 8.0 / 7.8, stride 2 tall 7.1 / 7.8, 128 9.8 / 9.5; fp16 64 tall 9.1 / 12.0, low 7.9 / 7.9, stride 2 tall 7.7 / 11.0, 128 stride 2 6.4 / 7.7.  fp32
 // 96 -> 128 (of 128 filters only), not ahead / ahead: low 66.5 / 65.0, tall 86 / 88, stride 2 36.6 / 38.0.  5x5 windows have no room for either (40 -> 88 -> 40 at 28x28 12.5 / 13.3
 // with both).
+// At 112x112, batch 64, the chip full, a third wavefront on a SIMD counts: fp16 64 -> 32 stride 2 tall 70 neither / 81 ahead / 85 wide, 24 -> 32 low 33 / 32 / 32, both 34,
+// 64 -> 64 low 81 / 90 / 94; the image form with 16 filters at 224x224, batch 64, fp16 tall 45.5 / 45.1 / 52.3 / 52.2, low 57.6 / 57.8 / 57.0 / 57.3, bf16 tall 53.7 / 53.2 /
+// 52.5 / 52.4, low 59.7 / 59.5 / 57.6 / 57.1.
 template <typename T>
-constexpr bool mbrow_wide(int k, int s, int mb, int xh, int r) {
+constexpr bool mbrow_wide(int k, int s, int mb, int xh, int r, bool image) {
   if (sizeof(T) != 2 || k != 3) return false;
   const int sums = 4 * r * mb, rows = (r - 1) * s + k;
   if (std::is_same<T, __bf16>::value) return xh ? mb < 8 : sums + 4 * rows * s <= 120;
-  return xh && mb <= 4 && sums <= 64;          // (fp16 forms spill where those of bf16 do not)
+  if (image) return (mb == 1) == (r <= 4);               // (the others have three wavefronts without, two with)
+  return xh && s == 1 && mb <= 4 && sums <= 64;          // (fp16 forms spill where those of bf16 do not)
 }
 template <typename T>
-constexpr bool mbrow_read_ahead(int k, int s, int mb, int xh, int r) {
+constexpr bool mbrow_read_ahead(int k, int s, int mb, int xh, int r, bool image) {
   if (k != 3 || xh == 0) return false;
   const bool low = 4 * r * mb <= 72;
   if (sizeof(T) == 4) return low && s == 1;
   if (std::is_same<T, __bf16>::value) return (xh <= 2 || low) && !(mb == 8 && s == 2);
-  return mb <= 4 || low;
+  return (mb <= 4 || low) && !image && !(s == 2 && xh == 4 && r * mb == 8);      // (those two: 165 registers without, 170 with)
 }
 
 template <typename T, int K, int S, int MB, int XH, int R, bool IMG>
@@ -233,7 +237,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
   constexpr int IROWS = 2 * ROWS + 1, IPITCH = mbrow_image_pitch(ES);   // IMG: rows and row pitch of the staged image
 
   constexpr bool AHEAD = !(EXP && K == 5 && ES == 2);   // window weights asked for one block ahead (there they do not fit)
-  constexpr bool W32 = ES == 4 || mbrow_wide<T>(K, S, MB, XH, R), READ_AHEAD = mbrow_read_ahead<T>(K, S, MB, XH, R);
+  constexpr bool W32 = ES == 4 || mbrow_wide<T>(K, S, MB, XH, R, IMG), READ_AHEAD = mbrow_read_ahead<T>(K, S, MB, XH, R, IMG);
 
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   constexpr int HL = mbrow_halo_left(K, S), HR = mbrow_halo_right(K, S);
@@ -479,6 +483,7 @@ __global__ __launch_bounds__(512, 2) void mbrow_kernel(MbArgs a) {
             for (int j = 0; j < XR; ++j) {
               uint4 b;
               if constexpr (READ_AHEAD) b = xb[s][j];
+              else if constexpr (IMG) b = window(i, j);
               else b = *(const uint4*)&xl[(i * CW + s) * XP + j * 64];
               float4_t d[1][1] = {{ev}};
               const uint4 aa[1] = {ae[j]}, bb[1] = {b};
