@@ -37,14 +37,15 @@ PEAK_GBS = 8000.0
 def kernel_peak(kernel: str, dtype: int) -> float:
     """Dense MFMA TFLOP/s a kernel (cprune_tile_variant_name) can reach: the kernels on three bf16 parts run an fp32
     product as six bf16 ones."""
-    parts = kernel.startswith(("conv_split", "conv_pw3", "conv_rows_s2", "conv_rows_nchw", "conv_stem7_split"))
+    parts = kernel.startswith(("conv_split", "conv_pw3", "conv_rows_s2", "conv_rows_nchw", "conv_stem7_split", "mbrow3"))
     return PEAK_TFLOPS[B.BF16] / 6 if dtype == B.F32 and parts else PEAK_TFLOPS[dtype]
 
 
-def layer_kernels(net, handle, dtype, first_layer_form=None):
+def layer_kernels(net, handle, dtype, first_layer_form=None, kept_counts=None):
     """The kernel every layer of a handle runs in, as far as its peak depends on it: the variant's; for a 1x1 layer in a 3x3
-    layer's launch that layer's; for a 7x7 / stride 2 first layer of a fp32 handle the one made for it.  "" for other layers
-    without a variant of their own (on the fp32 instruction in fp32)."""
+    layer's launch that layer's; for a 7x7 / stride 2 first layer of a fp32 handle the one made for it; for the 1x1 (or first) layers around
+    a fused 3x3 depthwise layer in fp32 the block's strips on three parts, up to 96 filters and not for fewer than 16 terms alone.  "" for
+    other layers without a variant of their own (on the fp32 instruction in fp32).  kept_counts: of pruned layers."""
     n = len(net.layers)
     variants = [handle.layer_variant(i) for i in range(n)]
     names = [B.cprune_tile_variant_name(v, True, dtype) if v >= 0 else "" for v in variants]
@@ -55,6 +56,19 @@ def layer_kernels(net, handle, dtype, first_layer_form=None):
         if (dtype == B.F32 and first_layer_form != 0 and variants[i] < 0 and L.kind == "conv" and L.groups == 1 and L.input < 0
                 and L.c_in <= 3 and (L.k, L.stride, L.pad) == (7, 2, 3) and L.residual is None):
             names[i] = "conv_stem7_split_kernel"
+    channels = [s[1] for s in synth.shapes(net, kept_counts)]
+    for i, L in enumerate(net.layers):
+        d = L.input
+        if dtype != B.F32 or L.kind != "conv" or L.groups != 1 or d is None or d < 0:
+            continue
+        D = net.layers[d]
+        if D.kind != "conv" or D.groups == 1 or D.k != 3 or not handle.layer_fused(d) or channels[i] > 96:
+            continue
+        block = D.input >= 0 and handle.layer_fused(D.input)
+        if block:
+            names[D.input] = "mbrow3_kernel"
+        if block or channels[d] >= 16:
+            names[i] = "mbrow3_kernel"
     return names
 
 
@@ -112,7 +126,7 @@ def net_report(name, net, cid, batch, dtype, steps, ceilings=None, variants=None
     ms_cold = time_forward_cold(handle, x, min(steps, 20)) if batch == 1 else None
     lt = handle.layer_times(x, iters=10)
     shp = synth.shapes(net, kept_counts)
-    kernels = layer_kernels(net, handle, dtype, first_layer_form)
+    kernels = layer_kernels(net, handle, dtype, first_layer_form, kept_counts)
     es = 4 if dtype == B.F32 else 2
     groups = {}
     for i, (L, t) in enumerate(zip(net.layers, lt)):
