@@ -1,5 +1,6 @@
 """The 16-bit 7x7 / stride 2 first layer of up to 48 filters on both sides of its rule (strips, or 16 x 16 blocks where those fill the chip evenly):
-one, two and three work-groups of blocks per CU and the next round, one to three channels, ragged maps, with and without the pool."""
+one, two and three work-groups of blocks per CU and the next round; strips that walk over bands of several steps, their ring of image rows coming
+round, which do not divide the map; one to three channels, ragged maps, with and without the pool."""
 import pytest
 import torch
 
@@ -12,9 +13,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype,tol", [(B.F16, 2.0 ** -10), (B.BF16, 2.0 ** -7)])        # one rounding of each result, and its fp32 sum's
 @pytest.mark.parametrize("c_in,c_out,h,w,batch", [
     (3, 8, 224, 224, 2), (3, 16, 224, 224, 12), (3, 16, 224, 224, 16),          # strips / blocks, three per CU / strips
-    (2, 17, 61, 45, 50), (1, 32, 98, 130, 23), (3, 24, 224, 224, 24),           # blocks: one, two per CU, two rounds
-    (3, 33, 98, 130, 23), (3, 48, 224, 224, 8), (1, 48, 224, 223, 12),
+    (2, 17, 224, 221, 4), (1, 32, 98, 130, 23), (3, 24, 224, 224, 24),          # blocks: one, two per CU, two rounds (strips without the pool)
+    (3, 33, 98, 130, 23), (3, 48, 224, 224, 8), (1, 48, 224, 223, 12),          # strips / blocks without the pool, blocks, strips
     (3, 49, 98, 130, 23),                                                       # strips only
+    (3, 24, 41, 29, 700), (1, 40, 61, 29, 300), (1, 10, 85, 31, 500), (3, 33, 75, 61, 260), (2, 64, 43, 40, 400),     # bands of 4 to 11 steps
 ])
 def test_strips_and_blocks(dtype, tol, c_in, c_out, h, w, batch):
     gen = torch.Generator().manual_seed(c_out + batch)
