@@ -349,7 +349,7 @@ int cprune_net_layer_variant(const cprune_net* net, int layer, int* variant_out)
 int cprune_net_fuse_first_layers(cprune_net* net, int enable);
 /* How a 7x7 / stride 2 / pad 3 first layer on the image (at most 3 channels) runs: the
  * opening of the ImageNet networks of Section 4.1 (ResNet-18, Table 1).  form 0: the general kernels;
- * 1: the kernel made for this layer (16-bit handles only); 2: that kernel with the 3x3 / stride 2 / pad 1 max-pool
+ * 1: the kernels made for this layer (16-bit handles only; two, by size); 2: those with the 3x3 / stride 2 / pad 1 max-pool
  * behind the layer inside it (the conv map is then never stored: cprune_net_copy_activation of the conv
  * layer returns CPRUNE_ERR_UNSUPPORTED, the pool layer's activation is the pooled map as always; form 0 brings it back).
  * A 16-bit handle: cprune_net_create(tune = 1) times the forms and keeps the fastest, tune = 0 takes the highest available.

@@ -185,8 +185,8 @@ struct MbArgs {
 
 // Output rows a wavefront owns (k in {3, 5}, stride in {1, 2}, mb filter blocks): about as many as its registers hold beside the
 // window's weights, multiples or halves of 7 where possible (the maps of the evaluated networks are 7 x 2^n); low = 1: about
-// half as many, for maps whose tall strips leave units idle.  Some forms hold more than fit and spill: 19 of the 31 fp32 forms (5x5), 21 of the
-// 75 bf16 and 8 of the 75 fp16 ones, by 1 to 94 registers, most where the window is 5x5 (its widened weights are 100
+// half as many, for maps whose tall strips leave units idle.  Some forms hold more than fit and spill: 7 of the 37 fp32 forms (all 5x5), 22 of the
+// 75 bf16 and 9 of the 75 fp16 ones, by 1 to 84 registers, most where the window is 5x5 (its widened weights are 100
 // registers) or a tall strip has 48 filters and more.  Timing chooses among tall and low all the same.
 constexpr int mbrow_rows(int k, int s, int mb, int low) {
   if (s == 1 && k == 3) return mb <= 4 ? (low ? 4 : 7) : mb == 6 ? (low ? 3 : 5) : (low ? 2 : 3);
@@ -198,7 +198,7 @@ constexpr int mbrow_rows(int k, int s, int mb, int low) {
 // 40 at 56x56 stride 2, batch 48, 34.2 us on the fp32 instruction, 41.8 on parts, 80 -> 300 -> 80 at 14x14 46 / 118), nor tiles of 128
 // filters (96 -> 280 -> 160 at 14x14 stride 2, depthwise and projection, 22.4 / 26.5).
 constexpr bool mbrow_parts(int k, int mb) { return k == 3 && mb <= 6; }
-// Likewise there: eight registers of weights a filter block and not four, so that tall strips of 64 filters do not fit (5 of the 36 forms spill).
+// Likewise there: eight registers of weights a filter block and not four, so that tall strips of 64 filters do not fit (5 of the 37 forms spill).
 constexpr int mbrow3_strip_rows(int s, int mb, int xh, int low) {
   if (s == 1) return mb <= 2 ? (low ? 4 : 7) : mb == 4 ? (low && xh > 4 ? 2 : 4) : mb == 6 && !xh ? 3 : 2;
   return mb <= 2 ? (low ? 2 : 4) : 2;

@@ -7,7 +7,7 @@
 // staged, into planes [part][channel][16 rows as a ring][columns], and the reduction is a list of (channel, window row)
 // units of 8 columns, the first of them a column left of the window that meets a zero weight.  A lane's operand of a unit
 // is then 16 consecutive bytes of a plane; 21 units make 6 rounds of 32 terms, 147 of 192 real.  (Four-channel pixels,
-// as the 16-bit kernel has them, take 7.)
+// as conv_stem7_block_kernel.hpp has them, take 7.)
 //   weights   a wavefront holds those of its MB 16-filter blocks in registers for good: 6 rounds x 3 parts, 144 registers at
 //             two blocks.  The two wavefronts of a work-group take the two halves of a filter tile on the same pixels.
 //   pixels    a work-group walks down a strip of 16 conv columns, two conv rows a step; four new image rows a step are
