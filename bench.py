@@ -34,22 +34,22 @@ if ROOT not in sys.path:
 # to the kernel sources they were measured on: TRAFFIC_SOURCE_HASH is kernel_source_hash() of that tree,
 # and any change to a file under csrc/ since then reports null instead of a stale figure (as does a
 # selection that runs a kernel on a layer it was not profiled on).
-TRAFFIC_SOURCE_HASH = "a51cab823751d270"
+TRAFFIC_SOURCE_HASH = "7dee747020209fd7"
 TRAFFIC = {
-    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3351368,
-    ("conv_split_rows_kernel<4, 1>", 64, "conv3"): 11213257,
-    ("conv_split_rows_kernel<8, 1>", 64, "conv3"): 14311407,
-    ("conv_split_rows_kernel<8, 4>", 64, "conv4"): 19437732,
-    ("conv_split_rows_kernel<4, 2>", 64, "conv5"): 6012307,
-    ("conv_split_rows_kernel<4, 4>", 64, "conv6"): 15570208,
-    ("conv_split_rows_kernel<8, 4>", 64, "conv6"): 15678650,
-    ("conv_split_rows_kernel<4, 4>", 64, "conv7"): 18452216,
-    ("conv_split_rows_kernel<4, 2>", 64, "conv8"): 27363604,
-    ("conv_split_rows_kernel<4, 8>", 64, "conv9"): 35619892,
-    ("conv_split_rows_kernel<4, 4>", 64, "conv10"): 33343775,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7679426,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392445,
-    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537599,
+    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3351056,
+    ("conv_split_rows_kernel<4, 1>", 64, "conv3"): 11202844,
+    ("conv_split_rows_kernel<8, 1>", 64, "conv3"): 14324460,
+    ("conv_split_rows_kernel<8, 4>", 64, "conv4"): 19442400,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv5"): 6006996,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv6"): 15570679,
+    ("conv_split_rows_kernel<8, 4>", 64, "conv6"): 15675001,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv7"): 18452176,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv8"): 11152661,
+    ("conv_split_rows_kernel<4, 8>", 64, "conv9"): 17360851,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv10"): 13543956,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7678833,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392166,
+    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537262,
 }
 
 

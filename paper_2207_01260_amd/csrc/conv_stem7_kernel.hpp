@@ -6,7 +6,8 @@
 // step, the next four image rows on their way meanwhile, rows pooled across lanes and steps in registers before they are rounded (the
 // maximum of rounded numbers is the rounded maximum).
 //
-// What bounds it: the vector work around the MFMAs (per row and filter block 4 sums' bias, clamp and maxima).
+// What bounds it: the vector work around the MFMAs (per row and filter block 4 sums' bias, clamp and maxima): with the pool, 64
+// filters at 224x224, batch 32, the vector ALU is busy 72 % of the cycles in which a unit has work, the matrix pipes 24.
 // Measured with the pool, 16 x 16 blocks of outputs (conv_stem7_block_kernel.hpp) / this kernel (us): 64 filters at 224x224, batch 32 30.4 / 24.9, 8 10.3 /
 // 10.3, 1 7.9 / 4.5; 64 at 64x64, batch 16 7.9 / 4.8; 10 at 96x96, batch 33 7.1 / 6.5.  Few filters leave the rows' addresses and reads to few
 // products, 17 to 32 of them 16 to a wavefront: 32 at 224x224, batch 8 6.9 / 8.1, batch 12 8.0 / 10.0 (two strips side by side with all
