@@ -29,7 +29,7 @@ if ROOT not in sys.path:
 
 # Bytes between L2 and fabric per launch (FETCH_SIZE + WRITE_SIZE, each scaled by what the counter
 # reads for a copy kernel of known size), by (kernel instantiation, batch, layer), for the default
-# workload: from the rocprofv3 counter runs summarised in profiles/vgg16_b64_f32_hbm_traffic.md (two
+# workload: from the rocprofv3 counter runs summarised in profiles/vgg16_b64_f32_hbm_traffic.md (three
 # pinned selections, because the timed selection flips between near-equal variants).  The figures belong
 # to the kernel sources they were measured on: TRAFFIC_SOURCE_HASH is kernel_source_hash() of that tree,
 # and any change to a file under csrc/ since then reports null instead of a stale figure (as does a
@@ -39,16 +39,23 @@ TRAFFIC = {
     ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3351056,
     ("conv_split_rows_kernel<4, 1>", 64, "conv3"): 11202844,
     ("conv_split_rows_kernel<8, 1>", 64, "conv3"): 14324460,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv4"): 12005256,
     ("conv_split_rows_kernel<8, 4>", 64, "conv4"): 19442400,
     ("conv_split_rows_kernel<4, 2>", 64, "conv5"): 6006996,
-    ("conv_split_rows_kernel<4, 4>", 64, "conv6"): 15570679,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv6"): 15570309,
     ("conv_split_rows_kernel<8, 4>", 64, "conv6"): 15675001,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv7"): 18441838,
     ("conv_split_rows_kernel<4, 4>", 64, "conv7"): 18452176,
     ("conv_split_rows_kernel<4, 2>", 64, "conv8"): 11152661,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv9"): 17353110,
     ("conv_split_rows_kernel<4, 8>", 64, "conv9"): 17360851,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv10"): 13556191,
     ("conv_split_rows_kernel<4, 4>", 64, "conv10"): 13543956,
     ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7678833,
+    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv11"): 7403146,
     ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392166,
+    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv12"): 6411595,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv13"): 7767844,
     ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537262,
 }
 
