@@ -34,29 +34,29 @@ if ROOT not in sys.path:
 # to the kernel sources they were measured on: TRAFFIC_SOURCE_HASH is kernel_source_hash() of that tree,
 # and any change to a file under csrc/ since then reports null instead of a stale figure (as does a
 # selection that runs a kernel on a layer it was not profiled on).
-TRAFFIC_SOURCE_HASH = "7dee747020209fd7"
+TRAFFIC_SOURCE_HASH = "23089d51be4c9abf"
 TRAFFIC = {
-    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3351056,
-    ("conv_split_rows_kernel<4, 1>", 64, "conv3"): 11202844,
-    ("conv_split_rows_kernel<8, 1>", 64, "conv3"): 14324460,
-    ("conv_split_rows_kernel<4, 2>", 64, "conv4"): 12005256,
-    ("conv_split_rows_kernel<8, 4>", 64, "conv4"): 19442400,
-    ("conv_split_rows_kernel<4, 2>", 64, "conv5"): 6006996,
-    ("conv_split_rows_kernel<4, 4>", 64, "conv6"): 15570309,
-    ("conv_split_rows_kernel<8, 4>", 64, "conv6"): 15675001,
-    ("conv_split_rows_kernel<4, 2>", 64, "conv7"): 18441838,
-    ("conv_split_rows_kernel<4, 4>", 64, "conv7"): 18452176,
-    ("conv_split_rows_kernel<4, 2>", 64, "conv8"): 11152661,
-    ("conv_split_rows_kernel<4, 4>", 64, "conv9"): 17353110,
-    ("conv_split_rows_kernel<4, 8>", 64, "conv9"): 17360851,
-    ("conv_split_rows_kernel<4, 2>", 64, "conv10"): 13556191,
-    ("conv_split_rows_kernel<4, 4>", 64, "conv10"): 13543956,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7678833,
-    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv11"): 7403146,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392166,
-    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv12"): 6411595,
-    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv13"): 7767844,
-    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537262,
+    ("conv_stem2_kernel<float, 2>", 64, "conv2"): 3351054,
+    ("conv_split_rows_kernel<4, 1>", 64, "conv3"): 11202840,
+    ("conv_split_rows_kernel<8, 1>", 64, "conv3"): 14323946,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv4"): 12005277,
+    ("conv_split_rows_kernel<8, 4>", 64, "conv4"): 19442354,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv5"): 6006992,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv6"): 15570693,
+    ("conv_split_rows_kernel<8, 4>", 64, "conv6"): 15674988,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv7"): 18441872,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv7"): 18451999,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv8"): 11152651,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv9"): 17353141,
+    ("conv_split_rows_kernel<4, 8>", 64, "conv9"): 17360835,
+    ("conv_split_rows_kernel<4, 2>", 64, "conv10"): 13556217,
+    ("conv_split_rows_kernel<4, 4>", 64, "conv10"): 13543944,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv11"): 7678826,
+    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv11"): 7402904,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv12"): 6392160,
+    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv12"): 6411606,
+    ("conv_ksplit_kernel<float, 1, 4>", 64, "conv13"): 7767859,
+    ("conv_ksplit_kernel<float, 2, 4>", 64, "conv13"): 7537255,
 }
 
 

@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256) void conv_stem7_block_kernel(StemArgs a) {
   // the patch of the next block travels to registers while this one is multiplied: per thread NL pairs of
   // neighbouring pixels (an even input column and the next), one 32-bit word per channel
   uint32_t pre[NL][3];
-  const bool w_even = (a.W & 1) == 0;
+  const bool w_even = ((a.W | (int)((size_t)xg >> 1)) & 1) == 0;      // (and the image begins at a word)
   auto load_patch = [&](int tile) {
     int n, cy0, cx0;
     origin(tile, n, cy0, cx0);

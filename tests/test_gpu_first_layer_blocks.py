@@ -44,3 +44,22 @@ def test_strips_and_blocks(dtype, tol, c_in, c_out, h, w, batch):
             got = handle.activation(i, batch, want.shape[1:]).float().cpu()
             assert ((got - want).abs() <= tol * want.abs() + 1e-5).all(), (i, float((got - want).abs().max()))
     handle.close()
+
+
+@pytest.mark.parametrize("c_out,batch", [(24, 8), (40, 8), (24, 1)])      # blocks, blocks, strips
+def test_an_input_off_a_word(c_out, batch):
+    """An image that begins at an odd element of its storage gives the same bits."""
+    gen = torch.Generator().manual_seed(9)
+    net = synth.NetSpec("odd7", 3, 224, 224)
+    a = net.add(synth.Layer("conv", -1, 3, c_out, k=7, stride=2, pad=3, act=synth.ACT_RELU, name="a"))
+    p = net.add(synth.Layer("maxpool", a, c_out, c_out, k=3, stride=2, pad=1, name="p"))
+    net.add(synth.Layer("conv", p, c_out, 8, k=1, act=synth.ACT_NONE, name="b"))
+    mk = lambda *s: {"w": (torch.randn(*s, generator=gen) * 0.1).bfloat16().cuda(), "b": torch.zeros(s[0], device="cuda")}
+    handle = pipeline.build_net(net, [mk(c_out, 3, 7, 7), {}, mk(8, c_out, 1, 1)], batch, B.BF16, tune=False)
+    x = torch.randn(batch, 3, 224, 224, generator=gen).bfloat16().cuda()
+    room = torch.empty(x.numel() + 1, dtype=torch.bfloat16, device="cuda")
+    off = room[1:].view(x.shape)
+    off.copy_(x)
+    assert off.data_ptr() % 4 == 2
+    assert torch.equal(handle.forward(off), handle.forward(x))
+    handle.close()
